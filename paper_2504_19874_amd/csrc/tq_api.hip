@@ -6,6 +6,7 @@
 #include <mutex>
 
 #include "tq_attend.h"
+#include "tq_h2.h"
 #include "tq_score_i8.h"
 
 using namespace tq;
@@ -28,7 +29,7 @@ int device_cu_count() {
 
 namespace {
 
-constexpr int64_t kChunkRows = 65536;  // rows per pass when a residual workspace is needed
+constexpr int64_t kChunkRows = 65536;  // rows per pass of the quantiser at most (with a sketch the workspace holds half as many)
 // Row strides of vectors (x, q) and of dequantised output: the kernels address a tile's rows with 32-bit byte
 // offsets from a 64-bit tile base (up to 256 rows of ld * 4 bytes)
 constexpr int64_t kMaxRowStride = int64_t(1) << 22;
@@ -121,6 +122,80 @@ struct Workspace {
   }
 };
 
+// params.images at every d other than 128: [Pi][S Pi^T] as two fp16 pieces (4 d^2 bytes each), then the inverse scales of
+// the two, each followed by a word that tq_build_images uses
+const char* h2_images(const tq_params* p) { return p->d != 128 ? static_cast<const char*>(p->images) : nullptr; }
+float* h2_image_scale(const void* images, int d, int which) {
+  return reinterpret_cast<float*>(const_cast<char*>(static_cast<const char*>(images)) + 2 * h2_image_bytes(d, d)) + 2 * which;
+}
+// without them: the images a call makes for itself in the workspace
+size_t h2_own_images_bytes(int d, bool prod) { return kH2ImageHeader + (prod ? 2 : 1) * h2_image_bytes(d, d); }
+
+// The quantiser on the fp16 matrix cores: passes of as many vectors as the workspace holds the pieces of.  False when it
+// holds too few (nothing has been launched then).
+bool quantize_h2(const tq_params* p, const void* x, bool bf16, int64_t n, int64_t ldx, uint32_t* idx, uint32_t* qjl, float* gamma,
+                 float* norm, bool prod, hipStream_t stream, tq_status* st) {
+  const int d = p->d;
+  Workspace ws{static_cast<char*>(p->workspace), p->workspace_bytes, 0};
+  const char* pi_img = h2_images(p);
+  const bool build = pi_img == nullptr || !aligned16(pi_img);
+  const char* s_img = pi_img + h2_image_bytes(d, d);
+  float* w_inv = h2_image_scale(pi_img, d, 0);
+  if (build) {  // the same bits as tq_build_images makes
+    char* const own = static_cast<char*>(ws.take(h2_own_images_bytes(d, prod)));
+    if (own == nullptr) return false;
+    w_inv = reinterpret_cast<float*>(own);
+    pi_img = own + kH2ImageHeader;
+    s_img = pi_img + h2_image_bytes(d, d);
+  }
+  // per vector: pieces, two factors; with a sketch the residual's pieces and the partial sums of its norm
+  const size_t x_bytes = (size_t)d * (bf16 ? 2 : 4);
+  const size_t per_row = x_bytes + 8 + (prod ? (size_t)d * 4 + (size_t)((d + 63) / 64) * 4 : 0);
+  const size_t room = ws.size > ws.used + 2048 ? ws.size - ws.used - 2048 : 0;  // alignment of the five arrays
+  int64_t chunk = (int64_t)(room / per_row);
+  if (chunk > kChunkRows) chunk = kChunkRows;
+  if (chunk < n) {
+    chunk = h2_full_rows(d, chunk);
+    if (chunk < 256) return false;
+  } else {
+    chunk = n;
+  }
+  void* const xp = ws.take((size_t)chunk * x_bytes);
+  float* const fac = static_cast<float*>(ws.take((size_t)chunk * 4));
+  float* const esc = static_cast<float*>(ws.take((size_t)chunk * 4));
+  void* const ep = prod ? ws.take((size_t)chunk * d * 4) : nullptr;
+  float* const part = prod ? static_cast<float*>(ws.take((size_t)chunk * ((d + 63) / 64) * 4)) : nullptr;
+  if (xp == nullptr || fac == nullptr || esc == nullptr || (prod && (ep == nullptr || part == nullptr))) return false;
+
+  *st = TQ_ERR_HIP;
+  if (build) {
+    if (launch_h2_image(p->Pi, d, d, d, const_cast<char*>(pi_img), w_inv, stream) != hipSuccess) return true;
+    if (prod && launch_h2_image(p->SPiT, d, d, d, const_cast<char*>(s_img), w_inv + 2, stream) != hipSuccess) return true;
+  }
+  const size_t esz = bf16 ? 2 : 4;
+  const int words_per_row = (d / 32) * p->bits_mse;
+  const Codebook cb = make_codebook(p);
+  const bool cut = !prod || two_piece_x_serves_prod(d, p->bits_mse);
+  for (int64_t r0 = 0; r0 < n; r0 += chunk) {
+    const int64_t rows = n - r0 < chunk ? n - r0 : chunk;
+    if (launch_h2_split(static_cast<const char*>(x) + (size_t)r0 * ldx * esz, bf16, cut, ldx, rows, d, norm != nullptr, w_inv, xp,
+                        norm ? norm + r0 : nullptr, fac, esc, stream) != hipSuccess)
+      return true;
+    H2Quant a;
+    std::memset(&a, 0, sizeof(a));
+    a.W = pi_img; a.w_inv = w_inv; a.X = xp; a.npx = bf16 ? 1 : 2; a.d = d; a.n = rows;
+    a.fac = fac; a.esc = esc; a.words = idx ? idx + r0 * words_per_row : nullptr; a.E = ep; a.part = part;
+    if (launch_h2_quant(p->bits_mse, a, cb, stream) != hipSuccess) return true;
+    if (prod) {
+      a.W = s_img; a.X = ep; a.npx = 2; a.E = nullptr;
+      a.words = qjl + r0 * (d / 32); a.part_tiles = h2_part_tiles(d, rows); a.gamma = gamma + r0;
+      if (launch_h2_sign(a, stream) != hipSuccess) return true;
+    }
+  }
+  *st = TQ_OK;
+  return true;
+}
+
 tq_status quantize_common(const tq_params* p, const void* x, int32_t dtype, int64_t n, int64_t ldx,
                           uint32_t* idx, uint32_t* qjl, float* gamma, float* norm, bool prod,
                           hipStream_t stream, int64_t out_first = 0, int64_t out_step = 1, bool scattered = false) {
@@ -192,20 +267,18 @@ tq_status quantize_common(const tq_params* p, const void* x, int32_t dtype, int6
   a.cb = make_codebook(p);
   const bool pieces = !fp32_mfma_only(p);
   a.pieces = pieces && !(prod && dtype == TQ_F32 && !two_piece_x_serves_prod(d, p->bits_mse));
-  // (d = 128 arrives here with bf16 rows that are only 8-byte aligned; params.images then holds the images of the
-  // d = 128 kernels, which are not this kernel's)
-  const char* const gemm_images = d != 128 ? static_cast<const char*>(p->images) : nullptr;
-  a.W1_image = a.pieces ? gemm_images : nullptr;
+  const bool h2_serves = pieces && h2_codebook_serves(p->bits_mse, a.cb) && (!prod || aligned16(p->SPiT));
   const NKind nk = dtype == TQ_F32 ? N_F32 : N_BF16;
 
   if (!prod) {
     // a handful of long vectors: a matrix-vector product per vector instead of the tiled contraction's serial k-loop,
     // when the workspace holds the rotated vectors
-    if (rows_route_serves(n, d, 1) && !fp32_mfma_only(p)) {
+    if (rows_route_serves(n, d, 1, 54) && !fp32_mfma_only(p)) {
       Workspace ws{static_cast<char*>(p->workspace), p->workspace_bytes, 0};
       if (float* const yw = static_cast<float*>(ws.take((size_t)n * d * sizeof(float))); yw != nullptr)
         return from_hip(launch_quant_rows(p->bits_mse, dtype == TQ_BF16, x, ldx, n, d, p->Pi, make_codebook(p), yw, idx, norm, stream));
     }
+    if (h2_serves && quantize_h2(p, x, dtype == TQ_BF16, n, ldx, idx, nullptr, nullptr, norm, false, stream, &st)) return st;
     a.X = x;
     a.n = n;
     a.rownorm_out = norm;
@@ -214,7 +287,7 @@ tq_status quantize_common(const tq_params* p, const void* x, int32_t dtype, int6
   }
 
   // a handful of long vectors: the matrix-vector route (see above), the sketch included
-  if (rows_route_serves(n, d, 2) && !fp32_mfma_only(p)) {
+  if (rows_route_serves(n, d, 2, 90) && !fp32_mfma_only(p)) {
     Workspace ws2{static_cast<char*>(p->workspace), p->workspace_bytes, 0};
     float* const yw = static_cast<float*>(ws2.take((size_t)n * d * sizeof(float)));
     float* const ew = static_cast<float*>(ws2.take((size_t)n * d * sizeof(float)));
@@ -222,6 +295,8 @@ tq_status quantize_common(const tq_params* p, const void* x, int32_t dtype, int6
       return from_hip(launch_quant_rows(p->bits_mse, dtype == TQ_BF16, x, ldx, n, d, p->Pi, make_codebook(p), yw, idx, norm, stream,
                                         p->SPiT, ew, qjl, gamma));
   }
+
+  if (h2_serves && quantize_h2(p, x, dtype == TQ_BF16, n, ldx, idx, qjl, gamma, norm, true, stream, &st)) return st;
 
   // prod: pass 1 writes idx and the rotated-basis residual e = y - c[idx];
   // pass 2 streams e (its row norms are gamma) against S Pi^T and packs signs.
@@ -260,7 +335,6 @@ tq_status quantize_common(const tq_params* p, const void* x, int32_t dtype, int6
     a2.rownorm_out = gamma + r0;
     a2.words_out = qjl + r0 * (d / 32);
     a2.pieces = pieces;  // the residual's own two pieces leave out 2^-17 of the residual: relative to gamma as it must be
-    a2.W1_image = pieces && gemm_images != nullptr ? gemm_images + gemm_image_bytes(d, d, 3) : nullptr;
     e = launch_gemm(N_F32, E_SIGN, 0, a2, 1, stream);
     if (e != hipSuccess) return TQ_ERR_HIP;
   }
@@ -285,7 +359,7 @@ const char* tq_status_string(tq_status s) {
 size_t tq_images_bytes(int32_t d) {
   if (d == 128) return quant128_bf3_image_bytes() + dequant128_bf3_image_bytes();
   if (d <= 0 || d % 32 != 0 || d > 16384) return 0;
-  return gemm_image_bytes(d, d, 3) + gemm_image_bytes(d, d, 2);  // Pi in three pieces, S Pi^T in two
+  return (size_t)d * d * 10;  // Pi and S Pi^T as two fp16 pieces each, and their scales
 }
 
 tq_status tq_build_images(const tq_params* p, void* images, void* stream) {
@@ -297,9 +371,10 @@ tq_status tq_build_images(const tq_params* p, void* images, void* stream) {
     if ((p->S == nullptr) != (p->SPiT == nullptr)) return TQ_ERR_INVALID_ARG;
     if (!aligned16(images) || !aligned16(p->Pi) || (p->SPiT != nullptr && !aligned16(p->SPiT))) return TQ_ERR_UNSUPPORTED;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    if (launch_gemm_image(p->Pi, p->d, p->d, p->d, 3, images, s) != hipSuccess) return TQ_ERR_HIP;
+    const int d = p->d;
+    if (launch_h2_image(p->Pi, d, d, d, images, h2_image_scale(images, d, 0), s) != hipSuccess) return TQ_ERR_HIP;
     if (p->SPiT != nullptr &&
-        launch_gemm_image(p->SPiT, p->d, p->d, p->d, 2, static_cast<char*>(images) + gemm_image_bytes(p->d, p->d, 3), s) != hipSuccess)
+        launch_h2_image(p->SPiT, d, d, d, static_cast<char*>(images) + h2_image_bytes(d, d), h2_image_scale(images, d, 1), s) != hipSuccess)
       return TQ_ERR_HIP;
     return TQ_OK;
   }
@@ -346,8 +421,10 @@ tq_status tq_derive_params(int32_t d, const float* Pi, const float* S, float* Pi
 size_t tq_workspace_bytes(const tq_params* p, int64_t n, int64_t nq, int32_t topk) {
   if (p == nullptr || p->d <= 0 || n < 0 || nq < 0) return 0;
   const size_t d = (size_t)p->d;
-  const size_t rows = (size_t)(n < kChunkRows ? n : kChunkRows);
-  size_t bytes = round_up(rows * d * sizeof(float), 256);          // residual of quantize_prod
+  const size_t rows = (size_t)(n < kChunkRows / 2 ? n : kChunkRows / 2);
+  // the quantiser's pieces of the vectors and of the residual, two factors and the partial residual norms per vector
+  size_t bytes = round_up(rows * (2 * d * sizeof(float) + 8 + (d + 63) / 64 * 4), 256) + 4096;
+  if (n > 0 && p->images == nullptr) bytes += round_up(h2_own_images_bytes(p->d, p->S != nullptr), 256);
   // a handful of long vectors: their rotated coordinates beside the residual (the matrix-vector route)
   bytes += round_up((size_t)(n < kRowsQuantMax ? n : kRowsQuantMax) * d * sizeof(float), 256);
   bytes += 2 * round_up((size_t)nq * d * sizeof(float), 256);      // rotated / sketched queries

@@ -30,7 +30,8 @@ __device__ __forceinline__ uint32_t shift_in(uint32_t nib, uint64_t mask) {
 // XOR of the compare masks at positions k = 2^p - 1 (mod 2^p); a 4-bit nibble of a plane is
 // built by shift-and-add-carry, most significant element first.  Returns the lane's share of
 // the squared residual norm; word[p] is the finished plane word (both half-waves merged).
-template <int B>
+// RES = false: the indices only; acc keeps the rotated coordinates.
+template <int B, bool RES = true>
 __device__ __forceinline__ float quantise_tile(floatx16& acc, const float inv, const Codebook& cb, const int h,
                                                uint32_t (&word)[4]) {
   float g2 = 0.f;
@@ -52,16 +53,18 @@ __device__ __forceinline__ float quantise_tile(floatx16& acc, const float inv, c
         // merged by the compiler into ONE indexed load from the table's memory, a round trip per coordinate
         const float tj = cb.t[j], cj = cb.c[j + 1];
         const bool ge = y >= tj;
-        yt = ge ? cj : yt;
+        if (RES) yt = ge ? cj : yt;
         const uint64_t gem = __builtin_amdgcn_ballot_w64(ge);
 #pragma unroll
         for (int pl = 0; pl < B; ++pl)
           if ((j & ((1 << pl) - 1)) == (1 << pl) - 1) bit[pl] ^= gem;
       }
-      float e = y - yt;
-      asm volatile("" : "+v"(e));  // keep the residual here: sunk later it would need the masks again
-      g2 = fmaf(e, e, g2);
-      acc[4 * k + r] = e;
+      if constexpr (RES) {
+        float e = y - yt;
+        asm volatile("" : "+v"(e));  // keep the residual here: sunk later it would need the masks again
+        g2 = fmaf(e, e, g2);
+        acc[4 * k + r] = e;
+      }
 #pragma unroll
       for (int pl = 0; pl < B; ++pl) nib[k][pl] = shift_in(nib[k][pl], bit[pl]);
     }
@@ -80,11 +83,11 @@ __device__ __forceinline__ float quantise_tile(floatx16& acc, const float inv, c
 // complement and the top plane is the sign compare.  "On a boundary, the upper cell" means |y| >= T for y >= 0 but
 // |y| > T for y < 0: negative coordinates are compared one ulp smaller (a subtract-with-borrow whose borrow is the
 // sign mask).  An empty table (B = 0) is the generic case.
-template <int B>
+template <int B, bool RES = true>
 __device__ __forceinline__ float quantise_tile_sym(floatx16& acc, const float inv, const Codebook& cb, const int h,
                                                    uint32_t (&word)[4]) {
   if constexpr (B == 0) {
-    return quantise_tile<0>(acc, inv, cb, h, word);
+    return quantise_tile<0, RES>(acc, inv, cb, h, word);
   } else {
     constexpr int H = 1 << (B - 1);
     float g2 = 0.f;
@@ -112,18 +115,20 @@ __device__ __forceinline__ float quantise_tile_sym(floatx16& acc, const float in
         for (int j = 0; j < H - 1; ++j) {
           const float tj = cb.t[H + j], cj = cb.c[H + j + 1];  // read before the select, see quantise_tile
           const bool ge = ayf >= tj;
-          ym = ge ? cj : ym;
+          if (RES) ym = ge ? cj : ym;
           const uint64_t gem = __builtin_amdgcn_ballot_w64(ge);
 #pragma unroll
           for (int pl = 0; pl < B - 1; ++pl)
             if ((j & ((1 << pl) - 1)) == (1 << pl) - 1) mbit[pl] ^= gem;
         }
         // the centroid takes the sign of y
-        const float yt = __uint_as_float((__float_as_uint(ym) & 0x7fffffffu) | (__float_as_uint(y) & 0x80000000u));
-        float e = y - yt;
-        asm volatile("" : "+v"(e));
-        g2 = fmaf(e, e, g2);
-        acc[4 * k + r] = e;
+        if constexpr (RES) {
+          const float yt = __uint_as_float((__float_as_uint(ym) & 0x7fffffffu) | (__float_as_uint(y) & 0x80000000u));
+          float e = y - yt;
+          asm volatile("" : "+v"(e));
+          g2 = fmaf(e, e, g2);
+          acc[4 * k + r] = e;
+        }
 #pragma unroll
         for (int pl = 0; pl < B - 1; ++pl) nib[k][pl] = shift_in(nib[k][pl], mbit[pl] ^ ~pos);
         nib[k][B - 1] = shift_in(nib[k][B - 1], pos);
@@ -141,11 +146,11 @@ __device__ __forceinline__ float quantise_tile_sym(floatx16& acc, const float in
 // The cheaper of the two for a symmetric table: from 3 bits on the decision on |y| wins (C3 shape, 3 bits: 150 us
 // against 167); at 1 and 2 bits its longer dependent chain per coordinate costs more than the two instructions it
 // saves (2 bits: 140 us against 130).
-template <int B>
+template <int B, bool RES = true>
 __device__ __forceinline__ float quantise_tile_best(floatx16& acc, const float inv, const Codebook& cb, const int h,
                                                     uint32_t (&word)[4]) {
-  if constexpr (B >= 3) return quantise_tile_sym<B>(acc, inv, cb, h, word);
-  else return quantise_tile<B>(acc, inv, cb, h, word);
+  if constexpr (B >= 3) return quantise_tile_sym<B, RES>(acc, inv, cb, h, word);
+  else return quantise_tile<B, RES>(acc, inv, cb, h, word);
 }
 
 // c[i] == -c[K-1-i] and t[j] == -t[K-2-j] for a table of K = 2^bits entries (the middle boundary is then 0)
