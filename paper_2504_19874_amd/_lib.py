@@ -69,6 +69,21 @@ SIGNATURES = {
 }
 
 _lib = None
+_call = None
+
+
+def call():
+    """The compiled per-call half of the binding (csrc/tq_python.cpp)."""
+    global _call
+    if _call is None:
+        load()
+        try:
+            from . import _tqcall
+        except ImportError as e:
+            raise RuntimeError("_tqcall.so is missing or does not load: build it with "
+                               "`python -m paper_2504_19874_amd.build`") from e
+        _call = _tqcall
+    return _call
 
 
 def load():

@@ -3,7 +3,9 @@
 Argument marshalling only: every function takes torch tensors that already
 live on the GPU (plus numpy arrays for the host-side codebook), passes their
 addresses and the current HIP stream to the library, and raises on a non-zero
-status.  No arithmetic of the method happens here.
+status.  No arithmetic of the method happens here.  The calls of a program's
+loop first go to their compiled form (csrc/tq_python.cpp), which takes plain
+arguments only; what follows it here is the checked path for everything else.
 """
 from __future__ import annotations
 
@@ -205,6 +207,9 @@ def _dtype_of(x: torch.Tensor) -> int:
 
 
 def tq_quantize_mse(p: Params, x: torch.Tensor, idx: torch.Tensor, norm: torch.Tensor | None):
+    st = _lib.call().quantize_mse(p.c, x, idx, norm)
+    if st is not None:
+        return _check(st, "tq_quantize_mse")
     n = x.shape[0]
     _check_codes(p, n, idx, None, None, norm)
     _check(_lib.load().tq_quantize_mse(C.byref(p.c), _ptr_rows(x), _dtype_of(x), n, x.stride(0) if n else p.d,
@@ -213,6 +218,9 @@ def tq_quantize_mse(p: Params, x: torch.Tensor, idx: torch.Tensor, norm: torch.T
 
 def tq_quantize_prod(p: Params, x: torch.Tensor, idx: torch.Tensor, qjl: torch.Tensor,
                      gamma: torch.Tensor, norm: torch.Tensor | None):
+    st = _lib.call().quantize_prod(p.c, x, idx, qjl, gamma, norm)
+    if st is not None:
+        return _check(st, "tq_quantize_prod")
     n = x.shape[0]
     _check_codes(p, n, idx, qjl, gamma, norm)
     _check(_lib.load().tq_quantize_prod(C.byref(p.c), _ptr_rows(x), _dtype_of(x), n, x.stride(0) if n else p.d,
@@ -221,6 +229,9 @@ def tq_quantize_prod(p: Params, x: torch.Tensor, idx: torch.Tensor, qjl: torch.T
 
 
 def tq_dequantize(p: Params, idx, qjl, gamma, norm, x_out: torch.Tensor):
+    st = _lib.call().dequantize(p.c, idx, qjl, gamma, norm, x_out)
+    if st is not None:
+        return _check(st, "tq_dequantize")
     n = x_out.shape[0]
     _check_codes(p, n, idx, qjl, gamma, norm)
     _need(x_out, torch.float32, 0, "x_out")
@@ -245,6 +256,9 @@ def _check_score_args(p, q, n_groups, q_per_group, idx, qjl, gamma, norm, n_per_
 def tq_score(p: Params, q: torch.Tensor, n_groups: int, q_per_group: int, idx, qjl, gamma, norm,
              n_per_group: int, scores: torch.Tensor | None, topk: int = 0,
              topk_idx: torch.Tensor | None = None, topk_val: torch.Tensor | None = None):
+    st = _lib.call().score(p.c, q, n_groups, q_per_group, idx, qjl, gamma, norm, n_per_group, scores, topk, topk_idx, topk_val)
+    if st is not None:
+        return _check(st, "tq_score")
     lds = scores.stride(0) if scores is not None and scores.shape[0] else n_per_group
     _check_score_args(p, q, n_groups, q_per_group, idx, qjl, gamma, norm, n_per_group, scores, topk, topk_idx, topk_val)
     _check(_lib.load().tq_score(C.byref(p.c), _ptr_rows(q), q.stride(0) if q.shape[0] else p.d, n_groups,
@@ -276,6 +290,9 @@ def tq_attend_workspace_bytes(pk: Params, pv: Params, n_groups: int, q_per_group
 
 def tq_append(p: Params, x: torch.Tensor, idx, qjl, gamma, norm, first_row: int, row_step: int):
     """Quantise the rows of x into code rows first_row + i * row_step of a cache (qjl None: the MSE quantiser)."""
+    st = _lib.call().append(p.c, x, idx, qjl, gamma, norm, first_row, row_step)
+    if st is not None:
+        return _check(st, "tq_append")
     n = x.shape[0]
     if n:
         _check_codes(p, first_row + (n - 1) * row_step + 1, idx, qjl, gamma, norm)
@@ -288,6 +305,9 @@ def tq_attend(pk: Params, pv: Params, q: torch.Tensor, n_groups: int, q_per_grou
     """k_codes, v_codes: (idx, qjl, gamma, norm) tensors, None where the quantiser has no such output.
     group_stride: token slots per group when the cache holds more than n_per_group (tq_attend_cache).
     Sizes pk's workspace for the call when it is too small."""
+    st = _lib.call().attend(pk.c, pv.c, q, n_groups, q_per_group, k_codes, v_codes, n_per_group, scale, out, group_stride)
+    if st is not None:
+        return _check(st, "tq_attend" if group_stride is None else "tq_attend_cache")
     need = tq_attend_workspace_bytes(pk, pv, n_groups, q_per_group, n_per_group)
     if pk.workspace is None or pk.workspace.numel() < need:
         pk.workspace = torch.empty(need, dtype=torch.uint8, device=pk.device)

@@ -10,11 +10,13 @@ from __future__ import annotations
 import os
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libturboquant.so")
+CALL_LIB = os.path.join(HERE, "_tqcall.so")  # the per-call half of the Python binding
 PROBE_LIB = os.path.join(HERE, "libtqprobe.so")  # measurement aid of bench_kernels, not part of the library
 OBJ = os.path.join(HERE, "_build")
 
@@ -35,14 +37,29 @@ def _compile(src: str) -> str:
     return obj
 
 
+def _compile_call_lib() -> None:
+    """A CPython extension (C API, torch's headers for the tensor objects); finds libturboquant.so beside itself."""
+    import torch
+    t = os.path.dirname(torch.__file__)
+    cmd = ["g++", "-O2", "-fPIC", "-std=c++17", "-shared", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+           *[f"-I{d}" for d in (os.path.join(t, "include"), os.path.join(t, "include", "torch", "csrc", "api", "include"),
+                                "/opt/rocm/include", sysconfig.get_paths()["include"])],
+           os.path.join(CSRC, "tq_python.cpp"), "-o", CALL_LIB, LIB, f"-L{os.path.join(t, 'lib')}",
+           "-ltorch_python", "-ltorch_cpu", "-lc10_hip", "-lc10", "-Wl,-rpath,$ORIGIN"]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError(f"{' '.join(cmd)}\n{r.stdout}\n{r.stderr}")
+
+
 def build_library(verbose: bool = True) -> str:
     os.makedirs(OBJ, exist_ok=True)
     with ThreadPoolExecutor(max_workers=min(8, len(SOURCES))) as pool:
         objs = list(pool.map(_compile, SOURCES))
-    cmd = ["hipcc", "-shared", "-fPIC", "--offload-arch=gfx950", "-o", LIB, *objs]
+    cmd = ["hipcc", "-shared", "-fPIC", "--offload-arch=gfx950", "-Wl,-soname,libturboquant.so", "-o", LIB, *objs]
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError(f"{' '.join(cmd)}\n{r.stdout}\n{r.stderr}")
+    _compile_call_lib()
     cmd = ["hipcc", *HIP_FLAGS, "-shared", os.path.join(CSRC, "probe_intake.hip"), "-o", PROBE_LIB]
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
