@@ -19,7 +19,11 @@
 // coordinate 32 t + 8 k + 4 h + r of vector lane % 32.
 #include "tq_d128_tile.h"
 
+#include <type_traits>
+
 namespace tq {
+
+typedef float floatx4 __attribute__((ext_vector_type(4)));
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
@@ -264,12 +268,210 @@ __global__ __launch_bounds__(512) void quant128_small_kernel(const QuantSmallArg
   }
 }
 
+// Blocks of 16 vectors, for batches that give a compute unit at most about one of them.  What such a call waits for is
+// one workgroup's chain, so the chain is cut: a wavefront owns 16 coordinates of all 16 vectors over the whole contraction
+// index (32 v_mfma_f32_16x16x4_f32, a quarter of the matrix time of the kernel above per contraction), holds every
+// vector's norm itself, decides its own four coordinates per lane and stores its halves of the plane words, so that the
+// only workgroup barrier of Alg. 2 is the one the residual crosses (two more for two instances, whose norms come from
+// the rotated coordinates).  Eight bf16 vectors: 2 + 1 bits 8.8 us in the kernel above, 6.5 here; 2 bits without a sketch
+// 5.0 and 3.8.  Most of what is left is the launch and one compute unit fetching 64 or 128 KB of matrices.
+// Operands: row / column = lane % 16, contraction index 32 (lane / 16) + step on both sides; accumulator register r is
+// coordinate 16 wave + 4 (lane / 16) + r of vector lane % 16.
+template <int BITS, bool PROD, bool BF16IN, bool MIXED>
+__global__ __launch_bounds__(512) void quant128_few_kernel(const QuantSmallArgs a) {
+  __shared__ __attribute__((aligned(16))) float e_s[PROD ? 16 * E_LD : 4];  // residual [vector][coordinate]
+  __shared__ float ss_s[MIXED ? 8 : 1][16];                                // squared norms of the rotated coordinates by wavefront
+  __shared__ float g2_s[8][16];                                            // squared residual norms by wavefront
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int col = lane & 15, kq = lane >> 4;
+  const int mt = wave >> 1;  // coordinate group of 32; this wavefront has its half wave & 1
+  const int gs = MIXED ? a.gs_hi : 0;
+  const bool hi = MIXED && mt < gs;  // uniform
+  const int wpr = MIXED ? gs * (BITS + 1) + (4 - gs) * BITS : 4 * BITS;
+  const int woff = MIXED ? (mt < gs ? mt * (BITS + 1) : gs * (BITS + 1) + (mt - gs) * BITS) : mt * BITS;
+  const int64_t i = (int64_t)blockIdx.x * 16 + col;
+  const bool valid = i < a.n;
+  const int64_t oi = a.out_first + i * a.out_step;  // code row
+
+  f32x4 pa[8], sa[8];
+  {
+    const float* prow = a.Pi + (16 * wave + col) * 128 + 32 * kq;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) pa[j] = *reinterpret_cast<const f32x4*>(prow + 4 * j);
+  }
+  float xb[32];
+  {
+    constexpr int RAW = BF16IN ? 4 : 8;  // 16-byte loads per lane for its quarter row
+    u32x4 raw[RAW];
+    const char* src = reinterpret_cast<const char*>(a.X) + ((valid ? i : a.n - 1) * a.ldx + 32 * kq) * (BF16IN ? 2 : 4);
+#pragma unroll
+    for (int v = 0; v < RAW; ++v) raw[v] = *reinterpret_cast<const u32x4*>(src + 16 * v);
+    if (PROD) {
+      const float* srow = a.SPiT + (16 * wave + col) * 128 + 32 * kq;
+#pragma unroll
+      for (int j = 0; j < 8; ++j) sa[j] = *reinterpret_cast<const f32x4*>(srow + 4 * j);
+    }
+#pragma unroll
+    for (int v = 0; v < RAW; ++v)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        if (BF16IN) {
+          xb[8 * v + 2 * e] = __uint_as_float(raw[v][e] << 16);
+          xb[8 * v + 2 * e + 1] = __uint_as_float(raw[v][e] & 0xffff0000u);
+        } else {
+          xb[(4 * v + e) & 31] = __uint_as_float(raw[v][e]);
+        }
+      }
+  }
+  // sum over the four lanes that share a vector
+  auto over_vector = [](float v) {
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return add_across_halves(__uint_as_float(r[0]) + __uint_as_float(r[1]));
+  };
+  auto merge16 = [](uint32_t w) {
+    const auto r = __builtin_amdgcn_permlane16_swap(w, w, false, false);
+    return or_across_halves(r[0] | r[1]);
+  };
+
+  float nu = 1.f, nu_other = 1.f, inv = 1.f;
+  if (!MIXED && a.normalise) {
+    float s0 = 0.f, s1 = 0.f;
+#pragma unroll
+    for (int k = 0; k < 32; k += 2) {
+      s0 = fmaf(xb[k], xb[k], s0);
+      s1 = fmaf(xb[k + 1], xb[k + 1], s1);
+    }
+    nu = sqrtf(over_vector(s0 + s1));
+    inv = nu > 0.f ? 1.f / nu : 0.f;
+  }
+  // two accumulators, so that consecutive matrix instructions do not wait for each other
+  floatx4 y0 = {0.f, 0.f, 0.f, 0.f}, y1 = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int j = 0; j < 8; ++j) {
+    y0 = __builtin_amdgcn_mfma_f32_16x16x4f32(pa[j].x, xb[4 * j + 0], y0, 0, 0, 0);
+    y1 = __builtin_amdgcn_mfma_f32_16x16x4f32(pa[j].y, xb[4 * j + 1], y1, 0, 0, 0);
+    y0 = __builtin_amdgcn_mfma_f32_16x16x4f32(pa[j].z, xb[4 * j + 2], y0, 0, 0, 0);
+    y1 = __builtin_amdgcn_mfma_f32_16x16x4f32(pa[j].w, xb[4 * j + 3], y1, 0, 0, 0);
+  }
+  y0 += y1;
+  if (MIXED) {
+    const float ss = over_vector(fmaf(y0[0], y0[0], y0[1] * y0[1]) + fmaf(y0[2], y0[2], y0[3] * y0[3]));
+    if (kq == 0) ss_s[wave][col] = ss;
+    __syncthreads();
+    float s_hi = 0.f, s_lo = 0.f;
+#pragma unroll
+    for (int w = 0; w < 8; ++w) {
+      const float v = ss_s[MIXED ? w : 0][col];
+      s_hi += (w >> 1) < gs ? v : 0.f;
+      s_lo += (w >> 1) < gs ? 0.f : v;
+    }
+    nu = sqrtf(hi ? s_hi : s_lo);
+    nu_other = sqrtf(hi ? s_lo : s_hi);
+    inv = nu > 0.f ? 1.f / nu : 0.f;
+  }
+
+  // the decision of Alg. 1 on four coordinates: bucket = number of boundaries not above y
+  constexpr int NPL = BITS + (MIXED && BITS < 4 ? 1 : 0);
+  uint32_t half[NPL > 0 ? NPL : 1];
+  float e[4], g2 = 0.f;
+  auto decide = [&](auto bits_c, const Codebook& cb) {
+    constexpr int B = decltype(bits_c)::value;
+    uint32_t lv[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const float y = y0[r] * inv;
+      float yt = cb.c[0];
+      lv[r] = 0u;
+#pragma unroll
+      for (int j = 0; j < (1 << B) - 1; ++j) {
+        const float tj = cb.t[j], cj = cb.c[j + 1];  // read before the select, see quantise_tile
+        const bool ge = y >= tj;
+        yt = ge ? cj : yt;
+        lv[r] += ge ? 1u : 0u;
+      }
+      e[r] = y - yt;
+      g2 = fmaf(e[r], e[r], g2);
+    }
+#pragma unroll
+    for (int pl = 0; pl < NPL; ++pl) {
+      uint32_t nib = 0u;
+      if (pl < B)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) nib |= ((lv[r] >> pl) & 1u) << r;
+      half[pl] = merge16(nib << (4 * kq));
+    }
+  };
+  if (hi) decide(std::integral_constant<int, NPL>{}, a.cb_hi);
+  else decide(std::integral_constant<int, BITS>{}, a.cb);
+  if (valid) {
+    // lanes of quarter kq store plane kq: 16 bits each
+    if (NPL > 0) {
+      uint32_t w = half[0];
+#pragma unroll
+      for (int pl = 1; pl < NPL; ++pl) w = kq == pl ? half[pl] : w;
+      if (kq < BITS + (hi ? 1 : 0)) reinterpret_cast<uint16_t*>(a.idx + oi * wpr + woff + kq)[wave & 1] = (uint16_t)w;
+    }
+    if (wave == 0 && kq == 0 && a.norm != nullptr) {
+      if (MIXED) {
+        a.norm[2 * oi] = nu;  // wavefront 0 always belongs to instance hi
+        a.norm[2 * oi + 1] = nu_other;
+      } else {
+        a.norm[oi] = nu;
+      }
+    }
+  }
+  if (!PROD) return;
+
+  g2 = over_vector(g2);
+  if (kq == 0) g2_s[wave][col] = g2;
+  *reinterpret_cast<f32x4*>(&e_s[col * E_LD + 16 * wave + 4 * kq]) = f32x4{e[0], e[1], e[2], e[3]};
+  __syncthreads();
+  floatx4 u0 = {0.f, 0.f, 0.f, 0.f}, u1 = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int j = 0; j < 8; ++j) {
+    const f32x4 ev = *reinterpret_cast<const f32x4*>(&e_s[col * E_LD + 32 * kq + 4 * j]);
+    u0 = __builtin_amdgcn_mfma_f32_16x16x4f32(sa[j].x, ev.x, u0, 0, 0, 0);
+    u1 = __builtin_amdgcn_mfma_f32_16x16x4f32(sa[j].y, ev.y, u1, 0, 0, 0);
+    u0 = __builtin_amdgcn_mfma_f32_16x16x4f32(sa[j].z, ev.z, u0, 0, 0, 0);
+    u1 = __builtin_amdgcn_mfma_f32_16x16x4f32(sa[j].w, ev.w, u1, 0, 0, 0);
+  }
+  u0 += u1;
+  uint32_t nib = 0u;
+#pragma unroll
+  for (int r = 0; r < 4; ++r) nib |= (u0[r] >= 0.f ? 1u : 0u) << r;
+  const uint32_t z = merge16(nib << (4 * kq));
+  if (valid && kq == 0) {
+    reinterpret_cast<uint16_t*>(a.qjl + oi * 4 + mt)[wave & 1] = (uint16_t)z;
+    if (wave == 0) {
+      float g[2] = {0.f, 0.f};  // instance lo (or the only one), instance hi
+#pragma unroll
+      for (int w = 0; w < 8; ++w) g[MIXED && (w >> 1) < gs ? 1 : 0] += g2_s[w][col];
+      if (MIXED) {
+        a.gamma[2 * oi] = sqrtf(g[1]);
+        a.gamma[2 * oi + 1] = sqrtf(g[0]);
+      } else {
+        a.gamma[oi] = sqrtf(g[0]);
+      }
+    }
+  }
+}
+
 // a workgroup takes one block up to this many workgroups; beyond that it loops over blocks,
 // keeping its parameter slices in registers
 constexpr int kSmallGrid = 1024;
+// up to here blocks of 16: one per compute unit.  Where a unit gets two of them the blocks of 32 win (4936 vectors in two
+// instances: 12.0 us against 11.0).
+constexpr int64_t kFewRows = 4096;
 
 template <int BITS, bool PROD, bool MIXED>
 static hipError_t launch_in(const QuantSmallArgs& a, bool bf16, hipStream_t s) {
+  if (a.n <= kFewRows) {
+    const dim3 few((unsigned)((a.n + 15) / 16));
+    if (bf16) hipLaunchKernelGGL((quant128_few_kernel<BITS, PROD, true, MIXED>), few, dim3(512), 0, s, a);
+    else hipLaunchKernelGGL((quant128_few_kernel<BITS, PROD, false, MIXED>), few, dim3(512), 0, s, a);
+    return hipGetLastError();
+  }
   const int64_t blocks = (a.n + 31) / 32;
   const dim3 grid((unsigned)(blocks < kSmallGrid ? blocks : kSmallGrid));
   if (bf16)
