@@ -813,19 +813,23 @@ tq_status tq_score_static(const tq_params* p, const float* q, int64_t ldq, int32
 namespace {
 struct AttendPlan {
   bool fast;  // the d = 128 kernel on the integer matrix cores takes the value codes
-  int nchunks;
+  int nchunks, max_chunks, tiles;
   int64_t ld_scores;
   size_t scores_bytes, part_bytes, score_ws_bytes;
 };
-AttendPlan attend_plan(const tq_params* pk, const tq_params* pv, bool v_prod, int64_t nq, int64_t n_per_group) {
+AttendPlan attend_plan(const tq_params* pk, const tq_params* pv, bool v_prod, int n_groups, int q_per_group, int64_t n_per_group) {
   AttendPlan pl;
+  const int64_t nq = (int64_t)n_groups * q_per_group;
   const Codebook v_hi = make_codebook_hi(pv);
   pl.fast = pv->centroids != nullptr && (pv->d_hi == 0 || pv->centroids_hi != nullptr) &&
             attend128_applicable(pv->d, v_prod, make_codebook(pv), pv->d_hi != 0 ? &v_hi : nullptr);
-  pl.nchunks = pl.fast ? attend128_chunks(n_per_group) : attend_simple_chunks(n_per_group);
+  pl.tiles = attend128_tiles(n_per_group, n_groups, q_per_group);
+  pl.nchunks = pl.fast ? attend128_chunks(n_per_group, pl.tiles) : attend_simple_chunks(n_per_group);
+  // what is reported covers every shorter cache too, whose chunks may be more
+  pl.max_chunks = pl.fast ? attend128_max_chunks(n_per_group, n_groups, q_per_group) : pl.nchunks;
   pl.ld_scores = (n_per_group + 3) / 4 * 4;
   pl.scores_bytes = round_up((size_t)nq * pl.ld_scores * sizeof(float), 256);
-  pl.part_bytes = round_up((size_t)nq * pl.nchunks * attend_part_stride(pv->d) * sizeof(float), 256);
+  pl.part_bytes = round_up((size_t)nq * pl.max_chunks * attend_part_stride(pv->d) * sizeof(float), 256);
   pl.score_ws_bytes = tq_workspace_bytes(pk, 0, nq, 0);
   return pl;
 }
@@ -838,8 +842,8 @@ size_t tq_attend_workspace_bytes(const tq_params* pk, const tq_params* pv, int32
   if (pk == nullptr || pv == nullptr || pk->d <= 0 || pv->d <= 0 || n_groups < 0 || q_per_group < 0 || n_per_group < 0)
     return 0;
   // whichever kind of value code the call then brings
-  const AttendPlan pl = attend_plan(pk, pv, true, (int64_t)n_groups * q_per_group, n_per_group);
-  const AttendPlan pm = attend_plan(pk, pv, false, (int64_t)n_groups * q_per_group, n_per_group);
+  const AttendPlan pl = attend_plan(pk, pv, true, n_groups, q_per_group, n_per_group);
+  const AttendPlan pm = attend_plan(pk, pv, false, n_groups, q_per_group, n_per_group);
   return pl.scores_bytes + (pl.part_bytes > pm.part_bytes ? pl.part_bytes : pm.part_bytes) + pl.score_ws_bytes + 512;
 }
 
@@ -871,20 +875,20 @@ tq_status tq_attend_cache(const tq_params* pk, const tq_params* pv, const float*
     return TQ_ERR_UNSUPPORTED;
   hipStream_t s = static_cast<hipStream_t>(stream);
 
-  const AttendPlan pl = attend_plan(pk, pv, v_prod, nq, n_per_group);
+  const AttendPlan pl = attend_plan(pk, pv, v_prod, n_groups, q_per_group, n_per_group);
   // value codes of two instances: the d = 128 kernel or nothing
   if (pv->d_hi != 0 && !pl.fast) return TQ_ERR_UNSUPPORTED;
   if (pl.nchunks > 4096) return TQ_ERR_UNSUPPORTED;  // the joining kernel keeps one factor per chunk in LDS
   Workspace ws{static_cast<char*>(pk->workspace), pk->workspace_bytes, 0};
   float* scores = static_cast<float*>(ws.take(pl.scores_bytes));
-  float* part = static_cast<float*>(ws.take(pl.part_bytes));
+  float* part = static_cast<float*>(ws.take((size_t)nq * pl.nchunks * attend_part_stride(pv->d) * sizeof(float)));
   char* rest = static_cast<char*>(ws.take(pl.score_ws_bytes));
   if (scores == nullptr || part == nullptr || rest == nullptr) return TQ_ERR_WORKSPACE;
   if (n_per_group > 0) {
     AttendArgs a;
     a.scores = scores; a.lds = pl.ld_scores;
     a.idx = v_idx; a.qjl = v_qjl; a.gamma = v_gamma; a.norm = v_norm;
-    a.part = part; a.nchunks = pl.nchunks; a.n = n_per_group; a.group_stride = group_stride; a.d = pv->d; a.q_per_group = q_per_group;
+    a.part = part; a.nchunks = pl.nchunks; a.tiles = pl.tiles; a.n = n_per_group; a.group_stride = group_stride; a.d = pv->d; a.q_per_group = q_per_group;
     a.scale = scale; a.cb = make_codebook(pv); a.gs_hi = pv->d_hi / 32; a.cb_hi = make_codebook_hi(pv);
     // keys the single-kernel d = 128 scoring path takes are scored inside the read-out kernel
     const bool k_prod = k_qjl != nullptr;

@@ -6,7 +6,18 @@
 
 namespace tq {
 
-int attend128_chunks(int64_t n) { return (int)((n + AT_CHUNK - 1) / AT_CHUNK); }
+namespace {
+int64_t long_limit(int n_groups, int q_per_group) {  // keys per group up to which short chunks are taken
+  const int64_t others = (int64_t)n_groups * ((q_per_group + 3) / 4);
+  return others > 0 ? device_cu_count() / 2 / others * (128 * AT_TILES) : 0;
+}
+}  // namespace
+int attend128_tiles(int64_t n, int n_groups, int q_per_group) { return n <= long_limit(n_groups, q_per_group) ? AT_TILES_SHORT : AT_TILES; }
+int attend128_max_chunks(int64_t n, int n_groups, int q_per_group) {
+  const int64_t lim = long_limit(n_groups, q_per_group);
+  const int a = attend128_chunks(n < lim ? n : lim, AT_TILES_SHORT), b = attend128_chunks(n, AT_TILES);
+  return a > b ? a : b;
+}
 
 // value codes the kernel covers: d = 128, tables symmetric about zero; codes of Alg. 1 with 1..4 index bits,
 // codes of Alg. 2 with 0..2, or two instances of Alg. 1 (cb_hi != NULL) with 1 + 2 or 2 + 3

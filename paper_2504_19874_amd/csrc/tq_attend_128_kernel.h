@@ -18,9 +18,9 @@
 // expand 16 bits (16 keys of one coordinate) to 16 bytes through a 256-entry table, as the scoring
 // kernels do.
 //
-// Workgroup of 8 wavefronts = 2048 keys of one group, 4 queries; a wavefront owns 256 consecutive
-// keys and takes 128 per pass.  Per pass and wavefront: 2 k-blocks of 64 keys x 8 coordinate
-// blocks x terms MFMAs.
+// Workgroup of 8 wavefronts = 128 TILES keys of one group, 4 queries; a wavefront owns 16 TILES consecutive
+// keys (256, or 64 where 2048 keys per workgroup would leave compute units without one: attend128_tiles) and takes
+// 128 (64) per pass.  Per pass and wavefront: 2 (1) k-blocks of 64 keys x 8 coordinate blocks x terms MFMAs.
 //
 // FUSED: the logits come from the d = 128 scoring kernel run in place (tq_score_i8_128_body.h: the
 // lane of (query, key) keeps its score in a register), so neither a score nor a dequantised
@@ -34,23 +34,22 @@
 
 namespace tq {
 
-constexpr int AT_WAVE_KEYS = 256;                    // keys a wavefront owns
-constexpr int AT_PASS_KEYS = 128;                    // ... and handles per pass
-constexpr int AT_PASSES = AT_WAVE_KEYS / AT_PASS_KEYS;
-constexpr int AT_CHUNK = 8 * AT_WAVE_KEYS;
-constexpr int AT_WD_BYTES = 8 * 4 * 4 * AT_PASS_KEYS;  // weight digits [wave][query][digit][key]
-constexpr int AT_XCH_BYTES = 8 * 8 * 64 * 4;            // per plane: [wave][block of 16 keys][64 words]
+__host__ __device__ constexpr int at_pass_keys(int tiles) { return tiles >= 8 ? 128 : 64; }    // keys a wavefront handles per pass
+__host__ __device__ constexpr int at_wd_bytes(int tiles) { return 8 * 4 * 4 * at_pass_keys(tiles); }        // weight digits [wave][query][digit][key]
+__host__ __device__ constexpr int at_xch_bytes(int tiles) { return 8 * (at_pass_keys(tiles) / 16) * 64 * 4; }  // per plane: [wave][block of 16 keys][64 words]
+constexpr int AT_FSUM_BYTES = 8 * 4 * 128 * 4;  // [wave][query][coordinate], over the exchange area in the end
 constexpr int AT_RED_FLOATS = 3 * 8 * 4;  // [maxima | norm maxima | sums][wave][4]
 
 // dynamic LDS: digits, exchange area (or, before them in time, what the scoring body needs), then the
 // reduction scratch, which is written while other wavefronts may still be scoring
 // (two: a second set of weight digits and one more plane: the signs of Alg. 2, or the top plane of instance hi)
-__host__ __device__ constexpr int attend128_work_bytes(int kb, int vb, bool two, bool fused) {
-  const int own = (two ? 2 : 1) * AT_WD_BYTES + (vb + (two ? 1 : 0)) * AT_XCH_BYTES;
+__host__ __device__ constexpr int attend128_work_bytes(int kb, int vb, bool two, bool fused, int tiles) {
+  const int xch = (vb + (two ? 1 : 0)) * at_xch_bytes(tiles);
+  const int own = (two ? 2 : 1) * at_wd_bytes(tiles) + (xch > AT_FSUM_BYTES ? xch : AT_FSUM_BYTES);
   return fused && score128_lds(kb) > own ? score128_lds(kb) : own;
 }
-__host__ __device__ constexpr int attend128_lds(int kb, int vb, bool two, bool fused) {
-  return attend128_work_bytes(kb, vb, two, fused) + AT_RED_FLOATS * 4;
+__host__ __device__ constexpr int attend128_lds(int kb, int vb, bool two, bool fused, int tiles) {
+  return attend128_work_bytes(kb, vb, two, fused, tiles) + AT_RED_FLOATS * 4;
 }
 
 struct AttendCoefs {
@@ -93,7 +92,7 @@ __device__ __forceinline__ void transpose16x32(uint32_t (&x)[16]) {
 // VKIND, the kind of value code: 0 = Alg. 1; 1 = Alg. 2 (one more plane: the signs, with weights ... * gamma);
 // 2 = two instances of Alg. 1 over a split of the coordinates (Sec. 4.3): groups g < a.gs_hi have VB + 1 index
 // planes, the table cfh and the weights exp(.) * nu_hi, the others VB planes, cf and exp(.) * nu_lo.
-template <int KB, bool KPROD, int VB, int VKIND, bool FUSED>
+template <int KB, bool KPROD, int VB, int VKIND, bool FUSED, int TILES>
 __global__ __launch_bounds__(512) void attend128_kernel(const ScoreI8Args ka, const AttendArgs a, const AttendCoefs cf,
                                                         const AttendCoefs cfh) {
   constexpr bool VPROD = VKIND == 1, VSPLIT = VKIND == 2, TWO = VKIND != 0;  // TWO: a second set of weights
@@ -101,31 +100,36 @@ __global__ __launch_bounds__(512) void attend128_kernel(const ScoreI8Args ka, co
   extern __shared__ __attribute__((aligned(16))) unsigned char dyn_s[];
   constexpr int NPL = VB + (TWO ? 1 : 0);  // bit planes of a value code: index planes, then the signs of Alg. 2 / the top plane of instance hi
   constexpr int NVB = VB > 0 ? VB : 1;
-  constexpr int ROUNDS = (NPL + 1) / 2;       // planes a transposing lane takes: ph, ph + 2
+  constexpr int WAVE_KEYS = 16 * TILES, PASS_KEYS = at_pass_keys(TILES), PASSES = WAVE_KEYS / PASS_KEYS;
+  constexpr int PT = PASS_KEYS / 16, KK = PASS_KEYS / 64;  // tiles (= blocks of 16 keys), k-blocks of 64 keys per pass
+  constexpr int WD_BYTES = at_wd_bytes(TILES), XCH_WORDS = at_xch_bytes(TILES) / 4;
+  constexpr int NPH = 16 / PT;                     // planes the wavefront transposes at a time
+  constexpr int ROUNDS = (NPL + NPH - 1) / NPH;    // planes a transposing lane takes: ph, ph + NPH, ...
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int col = lane & 15;  // key within a tile; B column (coordinate within a block of 16); A row (query, digit)
   const int kc = lane >> 4;   // query of this lane's logits and sums; k-chunk (16 keys of a k-block)
   const int chunk = blockIdx.x, group = blockIdx.y, q0 = blockIdx.z * 4;
-  constexpr int WD_ALL = (TWO ? 2 : 1) * AT_WD_BYTES;
-  unsigned char* const wd = dyn_s + wave * (4 * 4 * AT_PASS_KEYS);  // digits of exp(.) nu; + AT_WD_BYTES: of exp(.) nu gamma
-  uint32_t* const xch = reinterpret_cast<uint32_t*>(dyn_s + WD_ALL) + wave * (8 * 64);  // + plane * 8 * 8 * 64
+  constexpr int WD_ALL = (TWO ? 2 : 1) * WD_BYTES;
+  static_assert(!VPROD || WD_ALL >= AT_FSUM_BYTES, "the sums of the sign term lie over the digits");
+  unsigned char* const wd = dyn_s + wave * (4 * 4 * PASS_KEYS);  // digits of exp(.) nu; + WD_BYTES: of exp(.) nu gamma
+  uint32_t* const xch = reinterpret_cast<uint32_t*>(dyn_s + WD_ALL) + wave * (PT * 64);  // + plane * XCH_WORDS
   float* const fsum_s = reinterpret_cast<float*>(dyn_s + WD_ALL);  // [8][4][128], over the exchange area
   float* const fsumz_s = reinterpret_cast<float*>(dyn_s);          // the same for the sign sums, over the digits
-  float* const red_s = reinterpret_cast<float*>(dyn_s + attend128_work_bytes(KB, VB, TWO, FUSED));  // [3][8][4]
+  float* const red_s = reinterpret_cast<float*>(dyn_s + attend128_work_bytes(KB, VB, TWO, FUSED, TILES));  // [3][8][4]
 
   const int64_t gbase = (int64_t)group * a.group_stride;
-  const int64_t wave_key0 = ((int64_t)chunk * 8 + wave) * AT_WAVE_KEYS;
-  // transposing role: block kb of 16 keys, coordinate group tg, planes ph and ph + 2
-  const int kb = lane & 7, tg = (lane >> 3) & 3, ph = lane >> 5;
+  const int64_t wave_key0 = ((int64_t)chunk * 8 + wave) * WAVE_KEYS;
+  // transposing role: block kb of 16 keys, coordinate group tg, planes ph, ph + NPH, ...
+  const int kb = lane & (PT - 1), tg = (lane / PT) & 3, ph = lane / (4 * PT);
 
   uint32_t vw[ROUNDS][16];
   auto load_codes = [&](int ps) {
-    const int64_t k0 = wave_key0 + ps * AT_PASS_KEYS + 16 * kb;
+    const int64_t k0 = wave_key0 + ps * PASS_KEYS + 16 * kb;
 #pragma unroll
     for (int r = 0; r < ROUNDS; ++r) {
-      const int plane = ph + 2 * r;
+      const int plane = ph + NPH * r;
       // an odd number of planes: the last round has work for half the lanes only
 #pragma unroll
       for (int i = 0; i < 16; ++i) {
@@ -142,11 +146,12 @@ __global__ __launch_bounds__(512) void attend128_kernel(const ScoreI8Args ka, co
     }
   };
 
-  // value norms: lane L holds those of keys L, L + 64, L + 128, L + 192 of the wavefront
+  // value norms: lane L holds those of keys L, L + 64, ... of the wavefront
   // (and nu gamma, the factor of the sign term of Alg. 2)
-  float nuv[4], ngv[4];
+  constexpr int NE = WAVE_KEYS / 64;
+  float nuv[NE], ngv[NE];
 #pragma unroll
-  for (int e = 0; e < 4; ++e) {
+  for (int e = 0; e < NE; ++e) {
     const int64_t key = wave_key0 + 64 * e + lane;
     if (VSPLIT) {  // (nu_hi, nu_lo) per token
       nuv[e] = key < a.n ? a.norm[2 * (gbase + key) + 1] : 0.f;
@@ -160,20 +165,20 @@ __global__ __launch_bounds__(512) void attend128_kernel(const ScoreI8Args ka, co
   constexpr bool EARLY = !FUSED || KB + (KPROD ? 1 : 0) <= 4;
   if (EARLY) load_codes(0);
 
-  // ---- logits: lane (kc, col) holds those of (query q0 + kc, key wave_key0 + 16 t + col), t < 16 ----
+  // ---- logits: lane (kc, col) holds those of (query q0 + kc, key wave_key0 + 16 t + col), t < TILES ----
   // (kept in units of log 2, so that the weights are one v_exp_f32 each)
-  float lg[16];
+  float lg[TILES];
   const float scale2 = a.scale * 1.44269504088896341f;
 #pragma unroll
-  for (int t = 0; t < 16; ++t) lg[t] = -INFINITY;
+  for (int t = 0; t < TILES; ++t) lg[t] = -INFINITY;
   if (FUSED) {
     auto sink = [&](int t, float score, bool key_live) { lg[t] = key_live ? scale2 * score : -INFINITY; };
-    score128_body<KB, KPROD, TILES_128, SCORE128_ROUND_TILES, SCORE128_ROUNDS_AHEAD>(ka, dyn_s, sink);
+    score128_body<KB, KPROD, TILES, SCORE128_ROUND_TILES, SCORE128_ROUNDS_AHEAD>(ka, dyn_s, sink);
   } else {
     const int64_t qrow = (int64_t)group * a.q_per_group + (q0 + kc < a.q_per_group ? q0 + kc : q0);
     const float* srow = a.scores + qrow * a.lds + wave_key0 + col;
 #pragma unroll
-    for (int t = 0; t < 16; ++t)
+    for (int t = 0; t < TILES; ++t)
       if (wave_key0 + 16 * t + col < a.n) lg[t] = scale2 * srow[16 * t];
   }
   {
@@ -190,13 +195,19 @@ __global__ __launch_bounds__(512) void attend128_kernel(const ScoreI8Args ka, co
   {
     float v = lg[0];
 #pragma unroll
-    for (int t = 1; t < 16; ++t) v = fmaxf(v, lg[t]);
+    for (int t = 1; t < TILES; ++t) v = fmaxf(v, lg[t]);
     v = row_max(v);
     if (col == 0) red_s[wave * 4 + kc] = v;
-    const float nm = wave_max(fmaxf(fmaxf(nuv[0], nuv[1]), fmaxf(nuv[2], nuv[3])));
+    float nv = nuv[0], gv = ngv[0];
+#pragma unroll
+    for (int e = 1; e < NE; ++e) {
+      nv = fmaxf(nv, nuv[e]);
+      gv = fmaxf(gv, ngv[e]);
+    }
+    const float nm = wave_max(nv);
     if (lane == 1) red_s[32 + wave * 4] = nm;
     if (TWO) {
-      const float gm = wave_max(fmaxf(fmaxf(ngv[0], ngv[1]), fmaxf(ngv[2], ngv[3])));
+      const float gm = wave_max(gv);
       if (lane == 2) red_s[32 + wave * 4 + 1] = gm;
     }
   }
@@ -235,56 +246,56 @@ __global__ __launch_bounds__(512) void attend128_kernel(const ScoreI8Args ka, co
   const v4i ones = v4i{0x01010101, 0x01010101, 0x01010101, 0x01010101};
 
 #pragma unroll
-  for (int ps = 0; ps < AT_PASSES; ++ps) {
+  for (int ps = 0; ps < PASSES; ++ps) {
     // weights of this lane's (query, key) pairs -> four base-128 digits
 #pragma unroll
-    for (int tt = 0; tt < 8; ++tt) {
-      const int t = 8 * ps + tt;
+    for (int tt = 0; tt < PT; ++tt) {
+      const int t = PT * ps + tt;
       const float nu = __int_as_float(__builtin_amdgcn_ds_bpermute(4 * (16 * (t & 3) + col), __float_as_int(nuv[t >> 2])));
       const float p = __builtin_amdgcn_exp2f(lg[t] - m);  // 0 for keys past the end (logit -inf)
       lsum += p;
       // the weight is not negative: plain base-128 digits 0..127 fit the signed bytes of the operand
       const uint32_t Q = (uint32_t)__float2int_rn(p * nu * wscale);
-      unsigned char* o = wd + (kc * 4) * AT_PASS_KEYS + 16 * tt + col;
+      unsigned char* o = wd + (kc * 4) * PASS_KEYS + 16 * tt + col;
       o[0] = (unsigned char)(Q & 127u);
-      o[AT_PASS_KEYS] = (unsigned char)((Q >> 7) & 127u);
-      o[2 * AT_PASS_KEYS] = (unsigned char)((Q >> 14) & 127u);
-      o[3 * AT_PASS_KEYS] = (unsigned char)(Q >> 21);
+      o[PASS_KEYS] = (unsigned char)((Q >> 7) & 127u);
+      o[2 * PASS_KEYS] = (unsigned char)((Q >> 14) & 127u);
+      o[3 * PASS_KEYS] = (unsigned char)(Q >> 21);
       if (TWO) {
         const float ng = __int_as_float(__builtin_amdgcn_ds_bpermute(4 * (16 * (t & 3) + col), __float_as_int(ngv[t >> 2])));
         const uint32_t Z = (uint32_t)__float2int_rn(p * ng * zscale);
-        o[AT_WD_BYTES] = (unsigned char)(Z & 127u);
-        o[AT_WD_BYTES + AT_PASS_KEYS] = (unsigned char)((Z >> 7) & 127u);
-        o[AT_WD_BYTES + 2 * AT_PASS_KEYS] = (unsigned char)((Z >> 14) & 127u);
-        o[AT_WD_BYTES + 3 * AT_PASS_KEYS] = (unsigned char)(Z >> 21);
+        o[WD_BYTES] = (unsigned char)(Z & 127u);
+        o[WD_BYTES + PASS_KEYS] = (unsigned char)((Z >> 7) & 127u);
+        o[WD_BYTES + 2 * PASS_KEYS] = (unsigned char)((Z >> 14) & 127u);
+        o[WD_BYTES + 3 * PASS_KEYS] = (unsigned char)(Z >> 21);
       }
     }
     // value code words: 16 keys x 32 coordinates -> 32 coordinates x 16 keys
 #pragma unroll
     for (int r = 0; r < ROUNDS; ++r) {
-      const int plane = ph + 2 * r;
+      const int plane = ph + NPH * r;
       transpose16x32(vw[r]);
       if (plane < NPL) {
         // word c: low half = coordinate 32 tg + c, high half = coordinate 32 tg + 16 + c.  Odd key blocks swap
         // the halves of a row of 32 words, which keeps the reads below free of bank conflicts.
-        uint4* dst = reinterpret_cast<uint4*>(xch + plane * (8 * 8 * 64) + kb * 64 + ((tg ^ (kb & 1)) * 16));
+        uint4* dst = reinterpret_cast<uint4*>(xch + plane * XCH_WORDS + kb * 64 + ((tg ^ (kb & 1)) * 16));
 #pragma unroll
         for (int c = 0; c < 4; ++c) dst[c] = make_uint4(vw[r][4 * c], vw[r][4 * c + 1], vw[r][4 * c + 2], vw[r][4 * c + 3]);
       }
     }
-    if (ps + 1 < AT_PASSES) load_codes(ps + 1);
+    if (ps + 1 < PASSES) load_codes(ps + 1);
     __syncthreads();
 
-    v4i aop[2], zop[2];
+    v4i aop[KK], zop[KK];
 #pragma unroll
-    for (int kk = 0; kk < 2; ++kk) {
-      aop[kk] = *reinterpret_cast<const v4i*>(wd + col * AT_PASS_KEYS + kk * 64 + kc * 16);
-      if (TWO) zop[kk] = *reinterpret_cast<const v4i*>(wd + AT_WD_BYTES + col * AT_PASS_KEYS + kk * 64 + kc * 16);
+    for (int kk = 0; kk < KK; ++kk) {
+      aop[kk] = *reinterpret_cast<const v4i*>(wd + col * PASS_KEYS + kk * 64 + kc * 16);
+      if (TWO) zop[kk] = *reinterpret_cast<const v4i*>(wd + WD_BYTES + col * PASS_KEYS + kk * 64 + kc * 16);
     }
     {
       v4i tot = v4i{0, 0, 0, 0}, ztot = v4i{0, 0, 0, 0};
 #pragma unroll
-      for (int kk = 0; kk < 2; ++kk) {
+      for (int kk = 0; kk < KK; ++kk) {
         tot = __builtin_amdgcn_mfma_i32_16x16x64_i8(aop[kk], ones, tot, 0, 0, 0);
         if (TWO) ztot = __builtin_amdgcn_mfma_i32_16x16x64_i8(zop[kk], ones, ztot, 0, 0, 0);
       }
@@ -294,32 +305,34 @@ __global__ __launch_bounds__(512) void attend128_kernel(const ScoreI8Args ka, co
 #pragma unroll
     for (int g = 0; g < 4; ++g) {
       constexpr int NPW = VSPLIT ? VB + 1 : NVB;  // index planes read (instance lo: the top one is all zero)
-      uint32_t pw[2][NPW], pz[2] = {0u, 0u};
+      uint32_t pw[KK][NPW], pz[KK];
 #pragma unroll
-      for (int kk = 0; kk < 2; ++kk) {
+      for (int kk = 0; kk < KK; ++kk) {
+        pz[kk] = 0u;
 #pragma unroll
         for (int pl = 0; pl < (VSPLIT ? VB + 1 : VB); ++pl)
-          pw[kk][pl] = xch[pl * (8 * 8 * 64) + (4 * kk + kc) * 64 + ((g ^ (kc & 1)) * 16) + col];
-        if (VPROD) pz[kk] = xch[VB * (8 * 8 * 64) + (4 * kk + kc) * 64 + ((g ^ (kc & 1)) * 16) + col];
+          pw[kk][pl] = xch[pl * XCH_WORDS + (4 * kk + kc) * 64 + ((g ^ (kc & 1)) * 16) + col];
+        if (VPROD) pz[kk] = xch[VB * XCH_WORDS + (4 * kk + kc) * 64 + ((g ^ (kc & 1)) * 16) + col];
       }
       // masked sums of one coordinate group: plane subsets of odd size, weights and table of the group's instance
-      auto terms = [&](auto planes_c, const v4i (&wop)[2], const AttendCoefs& tab) {
+      auto terms = [&](auto planes_c, const v4i (&wop)[KK], const AttendCoefs& tab) {
         constexpr int NP = decltype(planes_c)::value;
 #pragma unroll
         for (int mset = 1; mset < (1 << NP); ++mset) {
           if (!i8_term(mset)) continue;
-          uint32_t mk[2] = {0u, 0u};
+          uint32_t mk[KK];
 #pragma unroll
-          for (int pl = 0; pl < NP; ++pl)
-            if (mset & (1 << pl)) {
-              mk[0] ^= pw[0][pl];
-              mk[1] ^= pw[1][pl];
-            }
+          for (int kk = 0; kk < KK; ++kk) {
+            mk[kk] = 0u;
+#pragma unroll
+            for (int pl = 0; pl < NP; ++pl)
+              if (mset & (1 << pl)) mk[kk] ^= pw[kk][pl];
+          }
 #pragma unroll
           for (int h = 0; h < 2; ++h) {
             v4i acc = v4i{0, 0, 0, 0};
 #pragma unroll
-            for (int kk = 0; kk < 2; ++kk) acc = __builtin_amdgcn_mfma_i32_16x16x64_i8(wop[kk], expand16(mk[kk], h), acc, 0, 0, 0);
+            for (int kk = 0; kk < KK; ++kk) acc = __builtin_amdgcn_mfma_i32_16x16x64_i8(wop[kk], expand16(mk[kk], h), acc, 0, 0, 0);
             f[2 * g + h] = fmaf(tab.c[mset], digits_sum(acc), f[2 * g + h]);
           }
         }
@@ -331,7 +344,7 @@ __global__ __launch_bounds__(512) void attend128_kernel(const ScoreI8Args ka, co
         for (int h = 0; h < 2; ++h) {
           v4i acc = v4i{0, 0, 0, 0};
 #pragma unroll
-          for (int kk = 0; kk < 2; ++kk) acc = __builtin_amdgcn_mfma_i32_16x16x64_i8(zop[kk], expand16(pz[kk], h), acc, 0, 0, 0);
+          for (int kk = 0; kk < KK; ++kk) acc = __builtin_amdgcn_mfma_i32_16x16x64_i8(zop[kk], expand16(pz[kk], h), acc, 0, 0, 0);
           fz[2 * g + h] += digits_sum(acc);
         }
       }
@@ -377,16 +390,23 @@ __global__ __launch_bounds__(512) void attend128_kernel(const ScoreI8Args ka, co
   }
 }
 
+template <int KB, bool KPROD, int VB, int VKIND, bool FUSED, int TILES>
+hipError_t launch_attend128_tiles(const ScoreI8Args& ka, const AttendArgs& a, const AttendCoefs& cf, const AttendCoefs& cfh,
+                                int n_groups, hipStream_t s) {
+  constexpr int lds = attend128_lds(KB, VB, VKIND != 0, FUSED, TILES);
+  static_assert(I8_TABLE_BYTES + lds <= 160 * 1024, "LDS budget");
+  static LdsLimit lds_limit;  // per instantiation: the limit is raised once per device
+  if (const hipError_t e = raise_lds_limit(lds_limit, reinterpret_cast<const void*>(&attend128_kernel<KB, KPROD, VB, VKIND, FUSED, TILES>), lds); e != hipSuccess) return e;
+  const dim3 grid(a.nchunks, n_groups, (a.q_per_group + 3) / 4);
+  hipLaunchKernelGGL((attend128_kernel<KB, KPROD, VB, VKIND, FUSED, TILES>), grid, dim3(512), lds, s, ka, a, cf, cfh);
+  return hipGetLastError();
+}
+
 template <int KB, bool KPROD, int VB, int VKIND, bool FUSED>
 hipError_t launch_attend128_one(const ScoreI8Args& ka, const AttendArgs& a, const AttendCoefs& cf, const AttendCoefs& cfh,
                                 int n_groups, hipStream_t s) {
-  constexpr int lds = attend128_lds(KB, VB, VKIND != 0, FUSED);
-  static_assert(I8_TABLE_BYTES + lds <= 160 * 1024, "LDS budget");
-  static LdsLimit lds_limit;  // per instantiation: the limit is raised once per device
-  if (const hipError_t e = raise_lds_limit(lds_limit, reinterpret_cast<const void*>(&attend128_kernel<KB, KPROD, VB, VKIND, FUSED>), lds); e != hipSuccess) return e;
-  const dim3 grid(a.nchunks, n_groups, (a.q_per_group + 3) / 4);
-  hipLaunchKernelGGL((attend128_kernel<KB, KPROD, VB, VKIND, FUSED>), grid, dim3(512), lds, s, ka, a, cf, cfh);
-  return hipGetLastError();
+  return a.tiles == AT_TILES_SHORT ? launch_attend128_tiles<KB, KPROD, VB, VKIND, FUSED, AT_TILES_SHORT>(ka, a, cf, cfh, n_groups, s)
+                                   : launch_attend128_tiles<KB, KPROD, VB, VKIND, FUSED, AT_TILES>(ka, a, cf, cfh, n_groups, s);
 }
 
 // all key variants for one kind of value code; kb < 0: logits from a.scores
