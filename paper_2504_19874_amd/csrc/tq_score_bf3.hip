@@ -571,54 +571,6 @@ __global__ __launch_bounds__(512) void score_bf3_kernel(const Bf3Args a) {
   }
 }
 
-// One wavefront per query: the ranges * k (score, index) pairs of the row, k rounds of arg-best.
-__global__ __launch_bounds__(64) void topk_merge_kernel(const float* __restrict__ part_val, const int32_t* __restrict__ part_idx,
-                                                        const int cands, const int k, int32_t* __restrict__ out_idx,
-                                                        float* __restrict__ out_val) {
-  constexpr int PER = 64;  // pairs per lane: at most 4096 pairs per row (checked at launch)
-  const int lane = threadIdx.x;
-  const int64_t row = blockIdx.x;
-  const float NEG = -__builtin_inff();
-  float v[PER];
-  int id[PER];
-#pragma unroll
-  for (int e = 0; e < PER; ++e) {
-    const int c = e * 64 + lane;
-    v[e] = c < cands ? part_val[row * cands + c] : NEG;
-    id[e] = c < cands ? part_idx[row * cands + c] : 0x7fffffff;
-  }
-  for (int r = 0; r < k; ++r) {
-    float bv = NEG;
-    int bi = 0x7fffffff;
-#pragma unroll
-    for (int e = 0; e < PER; ++e)
-      if (e * 64 < cands && better(v[e], id[e], bv, bi)) {
-        bv = v[e];
-        bi = id[e];
-      }
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) {
-      const float ov = __shfl_xor(bv, off);
-      const int oi = __shfl_xor(bi, off);
-      if (better(ov, oi, bv, bi)) {
-        bv = ov;
-        bi = oi;
-      }
-    }
-    // the winner leaves the set (indices of real pairs are distinct)
-#pragma unroll
-    for (int e = 0; e < PER; ++e)
-      if (id[e] == bi && bi != 0x7fffffff) {
-        v[e] = NEG;
-        id[e] = 0x7fffffff;
-      }
-    if (lane == 0) {
-      out_idx[row * k + r] = bi == 0x7fffffff ? -1 : bi;
-      if (out_val != nullptr) out_val[row * k + r] = bv;
-    }
-  }
-}
-
 // Ranges of code tiles per query block for the fused top-k: about one workgroup per compute unit in all
 // (the kernel's LDS admits one), every range at least one tile; from 8 ranges on the count is kept a multiple
 // of 8 so that every XCD can take whole ranges (xcd_split = ranges per XCD, 0: no such split).
@@ -693,14 +645,6 @@ int score_bf3_topk_ranges(int bits, bool prod, int64_t n, int n_groups, int q_pe
   if (nqb > 0x7fffffff / 256) return 0;
   int xs;
   return plan_ranges((n + tn - 1) / tn, (int)nqb, &xs);
-}
-
-hipError_t launch_topk_merge(const float* part_val, const int32_t* part_idx, int64_t rows, int ranges, int k,
-                             int32_t* out_idx, float* out_val, hipStream_t s) {
-  if (rows == 0) return hipSuccess;
-  if (ranges < 1 || k < 1 || k > 64 || (int64_t)ranges * k > 4096 || rows > 0x7fffffff) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(topk_merge_kernel, dim3((unsigned)rows), dim3(64), 0, s, part_val, part_idx, ranges * k, k, out_idx, out_val);
-  return hipGetLastError();
 }
 
 hipError_t launch_score_bf3(int bits, bool prod, const float* qr, const float* qs, int q_per_group, int d,

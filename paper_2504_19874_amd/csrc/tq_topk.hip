@@ -1,157 +1,189 @@
-// Per-query top-k over a row of scores (the "return top-10" step of the ANN
-// configurations).  One workgroup per row: every thread keeps its own sorted
-// list of the k best (value, index) it has seen while striding over the row,
-// then the 256 lists are merged by k rounds of a workgroup-wide arg-max.
-// Order: larger score first; equal scores by lower index.
-// A few long rows (one query against a million codes) would leave the chip to
-// a few workgroups: such rows are cut into chunks, one workgroup per (row,
-// chunk) writes the chunk's k best pairs, and launch_topk_merge joins them.
+// Per-query top-k over a row of scores (the "return top-10" step of the nearest-neighbour configurations).
+// Order: larger score first, equal scores by lower index; a NaN is never taken.
+//
+// A workgroup walks its part of a row in segments of 8192 scores, 32 per thread in registers, and keeps the k best pairs so
+// far in LDS.  The first segment has no bar yet: the k-th largest of the 256 threads' own maxima is one (k threads hold a
+// score that high), found by ranking the maxima against each other, and only scores that reach it, little more than k, are
+// looked at again.  In later segments a score has to beat the k-th best pair, which a handful do.  The ones that pass are
+// appended to a list and ranked against it.  A few long rows (one query against a million codes) are cut into chunks, one
+// workgroup each, whose lists topk_merge_kernel joins in the same way.
+// (Before: a sorted list per thread, k rounds of arg-max to join them.  4 rows of 10^6 scores, k = 10: 35 + 30 us for the
+// chunks and the merge, 11.5 + 7.5 here; 16 rows, k = 64: 1.2 ms in all, 70 us here.)
 #include "tq_internal.h"
 
 namespace tq {
+namespace {
+
+constexpr int SEG = 8192;              // scores per segment
+constexpr int PER = SEG / 256;         // per thread
+constexpr int LIST = SEG + 64;         // all of a segment may pass (equal scores), and the k best before it
 
 __device__ __forceinline__ bool better(float va, int ia, float vb, int ib) {
   return va > vb || (va == vb && ia < ib);
 }
 
-template <int KMAX>
-__global__ __launch_bounds__(256) void topk_kernel(const float* __restrict__ scores, const int64_t n_row,
-                                                   const int64_t ld, const int k, const int vec4,
-                                                   int32_t* __restrict__ out_idx,
-                                                   float* __restrict__ out_val, const int64_t chunk_len) {
-  extern __shared__ unsigned char smem_raw[];
-  float* cand_v = reinterpret_cast<float*>(smem_raw);            // [256 * k]
-  int* cand_i = reinterpret_cast<int*>(cand_v + 256 * k);        // [256 * k]
-  __shared__ float red_v[4];
-  __shared__ int red_i[4];
-  __shared__ int red_slot[4];
+// order-preserving map to the unsigned integers
+__device__ __forceinline__ uint32_t ordered(float f) {
+  const uint32_t b = __float_as_uint(f);
+  return b & 0x80000000u ? ~b : b | 0x80000000u;
+}
 
+struct TopkLds {
+  float v[LIST];
+  int i[LIST];
+  float best_v[64];
+  int best_i[64];
+  uint32_t mx[256];
+  uint32_t bar;
+  int count;
+};
+
+// v[e]: this thread's scores of one segment, NaN where there is none; pair(e) fetches score and index of the e-th again (a
+// handful are asked for, and a register array cannot be indexed).  kept: pairs in best so far (uniform).  Afterwards best
+// holds the k best of all segments up to this one, and the number of them is returned.
+// (Straight code for 32 elements would be 12 KB of instructions that a 10 us kernel has to fetch first: it is kept short.)
+template <int N, class Pair>
+__device__ int take_segment(TopkLds& s, const float (&v)[N], Pair pair, int k, int kept, int tid) {
+  float bar;
+  if (kept < k) {
+    float mx = -__builtin_inff();
+#pragma unroll
+    for (int e = 0; e < N; ++e) mx = fmaxf(mx, v[e]);  // ignores NaN
+    const uint32_t key = ordered(mx);
+    s.mx[tid] = key;
+    if (tid == 0) s.bar = 0xffffffffu;
+    __syncthreads();
+    int above = 0;
+    const uint4* m4 = reinterpret_cast<const uint4*>(s.mx);
+#pragma unroll 8
+    for (int t = 0; t < 64; ++t) {
+      const uint4 o = m4[t];
+      above += (o.x > key ? 1 : 0) + (o.y > key ? 1 : 0) + (o.z > key ? 1 : 0) + (o.w > key ? 1 : 0);
+    }
+    if (above < k) atomicMin(&s.bar, key);  // the smallest of the k largest
+    __syncthreads();
+    const uint32_t b = s.bar;
+    bar = __uint_as_float(b & 0x80000000u ? b & 0x7fffffffu : ~b);
+  } else {
+    bar = s.best_v[k - 1];
+  }
+  if (tid < kept) {
+    s.v[tid] = s.best_v[tid];
+    s.i[tid] = s.best_i[tid];
+  }
+  if (tid == 0) s.count = kept;
+  __syncthreads();
+  // (an equal score of a later segment has a later index and does not beat a kept one, but it may be ranked all the same)
+  uint32_t pass = 0u;
+#pragma unroll
+  for (int e = N - 1; e >= 0; --e) pass = pass + pass + (v[e] >= bar ? 1u : 0u);
+  while (pass != 0u) {
+    const int e = __builtin_ctz(pass);
+    pass &= pass - 1u;
+    const int pos = atomicAdd(&s.count, 1);
+    pair(e, s.v[pos], s.i[pos]);
+  }
+  __syncthreads();
+  const int n = s.count;
+  if (n == kept) return kept;  // uniform; nothing passed
+  for (int c = tid; c < n; c += 256) {
+    const float cv = s.v[c];
+    const int ci = s.i[c];
+    int rank = 0;
+#pragma unroll 4
+    for (int o = 0; o < n; ++o) rank += better(s.v[o], s.i[o], cv, ci) ? 1 : 0;
+    if (rank < k) {
+      s.best_v[rank] = cv;
+      s.best_i[rank] = ci;
+    }
+  }
+  __syncthreads();
+  return n < k ? n : k;
+}
+
+__device__ __forceinline__ void write_best(const TopkLds& s, int kept, int k, int none, int32_t* out_idx, float* out_val, int tid) {
+  if (tid < k) {
+    out_idx[tid] = tid < kept ? s.best_i[tid] : none;
+    if (out_val != nullptr) out_val[tid] = tid < kept ? s.best_v[tid] : -__builtin_inff();
+  }
+}
+
+// chunk_len > 0: workgroup (row, chunk) takes columns [c0, c0 + chunk_len) of the row (chunk_len is a multiple of
+// 4, so a chunk is as aligned as the row) and writes k (value, index) pairs, -inf / INT_MAX where it has fewer
+__global__ __launch_bounds__(256) void topk_kernel(const float* __restrict__ scores, const int64_t n_row, const int64_t ld, const int k,
+                                                   const int vec4, int32_t* __restrict__ out_idx, float* __restrict__ out_val,
+                                                   const int64_t chunk_len) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
+  TopkLds& s = *reinterpret_cast<TopkLds*>(smem_raw);
   const int tid = threadIdx.x;
-  // chunk_len > 0: workgroup (row, chunk) takes columns [c0, c0 + chunk_len) of the row (chunk_len is a multiple of
-  // 4, so a chunk is as aligned as the row) and writes k (value, index) pairs, -inf / INT_MAX where it has fewer
   const int64_t c0 = chunk_len > 0 ? (int64_t)blockIdx.y * chunk_len : 0;
   const int64_t n = chunk_len > 0 ? (n_row - c0 < chunk_len ? n_row - c0 : chunk_len) : n_row;
   const float* row = scores + (int64_t)blockIdx.x * ld + c0;
   const int64_t out_row = chunk_len > 0 ? (int64_t)blockIdx.x * gridDim.y + blockIdx.y : blockIdx.x;
-  const float NEG = -__builtin_inff();
-
-  float bv[KMAX];
-  int bi[KMAX];
-#pragma unroll
-  for (int j = 0; j < KMAX; ++j) {
-    bv[j] = NEG;
-    bi[j] = 0x7fffffff;
-  }
-  // position k-1 of a thread's list is its current worst kept entry: almost every element is
-  // rejected by one compare against it
-  float worst_v = NEG;
-  int worst_i = 0x7fffffff;
-  auto consider = [&](float v, int id) {
-    if (better(v, id, worst_v, worst_i)) {
-      // insert by a single pass of compare-exchange from the top
-#pragma unroll
-      for (int j = 0; j < KMAX; ++j) {
-        if (j < k && better(v, id, bv[j], bi[j])) {
-          const float tv = bv[j];
-          const int ti = bi[j];
-          bv[j] = v;
-          bi[j] = id;
-          v = tv;
-          id = ti;
-        }
-        if (j == k - 1) {
-          worst_v = bv[j];
-          worst_i = bi[j];
-        }
-      }
-    }
-  };
-  if (vec4) {
-    // 16-byte loads, four of them in flight per thread before any compare
+  const float NONE = __builtin_nanf("");
+  float v[PER];
+  // element e of a thread: column 4 (tid + 256 (e / 4)) + e % 4 of the segment
+  int kept = 0;
+  for (int64_t seg = 0; seg < n; seg += SEG) {
     typedef float f32x4 __attribute__((ext_vector_type(4)));
-    const f32x4* row4 = reinterpret_cast<const f32x4*>(row);
-    const int64_t n4 = n >> 2;
-    constexpr int U = 4;
-    for (int64_t i0 = tid; i0 < n4; i0 += 256 * U) {
-      f32x4 v[U];
+    if (vec4 && seg + SEG <= n) {  // uniform: all loads in flight together
 #pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const int64_t i = i0 + 256 * u;
-        v[u] = i < n4 ? __builtin_nontemporal_load(row4 + i) : f32x4{NEG, NEG, NEG, NEG};
+      for (int u = 0; u < PER / 4; ++u) {
+        const f32x4 w = *reinterpret_cast<const f32x4*>(row + seg + 4 * (tid + 256 * u));
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[4 * u + e] = w[e];
       }
+    } else {
+      const int left = (int)(n - seg < SEG ? n - seg : SEG);
+      const float* const src = row + seg;
 #pragma unroll
-      for (int u = 0; u < U; ++u) {
-        if (i0 + 256 * u >= n4) break;  // padding of the last round: no element, no index
-        const int id = (int)(c0 + ((i0 + 256 * u) << 2));
-        consider(v[u].x, id);
-        consider(v[u].y, id + 1);
-        consider(v[u].z, id + 2);
-        consider(v[u].w, id + 3);
+      for (int e = 0; e < PER; ++e) {
+        const int c = 4 * (tid + 256 * (e >> 2)) + (e & 3);
+        const float w = src[c < left ? c : left - 1];
+        v[e] = c < left ? w : NONE;
       }
     }
-    for (int64_t i = (n4 << 2) + tid; i < n; i += 256) consider(row[i], (int)(c0 + i));
-  } else {
-    for (int64_t i = tid; i < n; i += 256) consider(row[i], (int)(c0 + i));
+    kept = take_segment(s, v, [&](int e, float& pv, int& pi) {
+      const int64_t c = seg + 4 * (tid + 256 * (e >> 2)) + (e & 3);
+      pv = row[c];
+      pi = (int)(c0 + c);
+    }, k, kept, tid);
   }
-#pragma unroll
-  for (int j = 0; j < KMAX; ++j)
-    if (j < k) {
-      cand_v[tid * k + j] = bv[j];
-      cand_i[tid * k + j] = bi[j];
-    }
-  __syncthreads();
-
-  // k rounds: each thread's list is sorted, so its best remaining entry is at
-  // its own cursor; the workgroup picks the best of the 256 cursors.
-  int cursor = 0;
-  for (int r = 0; r < k; ++r) {
-    float v = (cursor < k) ? cand_v[tid * k + cursor] : NEG;
-    int id = (cursor < k) ? cand_i[tid * k + cursor] : 0x7fffffff;
-    int who = tid;
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) {
-      const float ov = __shfl_xor(v, off);
-      const int oi = __shfl_xor(id, off);
-      const int ow = __shfl_xor(who, off);
-      if (better(ov, oi, v, id)) {
-        v = ov;
-        id = oi;
-        who = ow;
-      }
-    }
-    if ((tid & 63) == 0) {
-      red_v[tid >> 6] = v;
-      red_i[tid >> 6] = id;
-      red_slot[tid >> 6] = who;
-    }
-    __syncthreads();
-    float fv = red_v[0];
-    int fi = red_i[0], fw = red_slot[0];
-#pragma unroll
-    for (int w = 1; w < 4; ++w)
-      if (better(red_v[w], red_i[w], fv, fi)) {
-        fv = red_v[w];
-        fi = red_i[w];
-        fw = red_slot[w];
-      }
-    if (tid == fw) ++cursor;
-    if (tid == 0) {
-      out_idx[out_row * k + r] = (fi == 0x7fffffff && chunk_len == 0) ? -1 : fi;
-      if (out_val != nullptr) out_val[out_row * k + r] = fv;
-    }
-    __syncthreads();
-  }
+  write_best(s, kept, k, chunk_len > 0 ? 0x7fffffff : -1, out_idx + out_row * k, out_val != nullptr ? out_val + out_row * k : nullptr, tid);
 }
 
+// One workgroup per row: the k best of its cands <= 4096 (score, index) pairs (index INT_MAX: no pair).
+__global__ __launch_bounds__(256) void topk_merge_kernel(const float* __restrict__ part_val, const int32_t* __restrict__ part_idx,
+                                                         const int cands, const int k, int32_t* __restrict__ out_idx,
+                                                         float* __restrict__ out_val) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
+  TopkLds& s = *reinterpret_cast<TopkLds*>(smem_raw);
+  const int tid = threadIdx.x;
+  const int64_t row = blockIdx.x;
+  constexpr int N = 16;
+  float v[N];
+#pragma unroll
+  for (int e = 0; e < N; ++e) {
+    const int c = e * 256 + tid, cc = c < cands ? c : cands - 1;
+    const float w = part_val[row * cands + cc];
+    v[e] = c < cands && part_idx[row * cands + cc] != 0x7fffffff ? w : __builtin_nanf("");
+  }
+  const int kept = take_segment(s, v, [&](int e, float& pv, int& pi) {
+    pv = part_val[row * cands + e * 256 + tid];
+    pi = part_idx[row * cands + e * 256 + tid];
+  }, k, 0, tid);
+  write_best(s, kept, k, -1, out_idx + row * k, out_val != nullptr ? out_val + row * k : nullptr, tid);
+}
+
+}  // namespace
+
 // Chunks per row when a call's rows are too few to fill the chip: 0 (one workgroup per row) unless the rows are
-// few and long; then chunks of at least 8192 scores, about four workgroups per compute unit in all, and no more
-// pairs per row than the joining kernel takes (4096).  (Short chunks are the cheaper ones: while a thread has seen
-// fewer than some hundred scores nearly every score enters some lane's list, so a wavefront pays the insertion
-// for every element; one row of 10^6 scores: 35 us in 122 chunks, 103 us in 30.)
+// few and long; then chunks of at least a segment, about four workgroups per compute unit in all, and no more
+// pairs per row than the joining kernel takes (4096).
 int topk_chunks(int64_t rows, int64_t n, int k) {
   if (k < 1 || rows < 1 || rows > 128 || n < 65536) return 0;
   int64_t c = (4 * (int64_t)device_cu_count() + rows - 1) / rows;
-  if (c > n / 8192) c = n / 8192;
+  if (c > n / SEG) c = n / SEG;
   if (c > 4096 / k) c = 4096 / k;
   if (c > 65535) c = 65535;
   return c >= 2 ? (int)c : 0;
@@ -165,7 +197,6 @@ hipError_t launch_topk(const float* scores, int64_t rows, int64_t n, int64_t ld,
   if (rows == 0 || k == 0) return hipSuccess;
   if (k < 1 || k > 64 || rows > 0x7fffffff || n > 0x7fffffff) return hipErrorInvalidValue;
   if (chunks > 0 && (part_val == nullptr || part_idx == nullptr || chunks > 65535)) return hipErrorInvalidValue;
-  const size_t smem = (size_t)256 * k * 8;
   const int vec4 = (ld % 4 == 0) && ((reinterpret_cast<uintptr_t>(scores) & 15u) == 0);
   const int64_t chunk_len = chunks > 0 ? ((n + chunks - 1) / chunks + 3) / 4 * 4 : 0;
   const dim3 grid((unsigned)rows, chunks > 0 ? (unsigned)chunks : 1u);
@@ -173,15 +204,19 @@ hipError_t launch_topk(const float* scores, int64_t rows, int64_t n, int64_t ld,
     out_idx = part_idx;
     out_val = part_val;
   }
-  if (k <= 16)
-    hipLaunchKernelGGL((topk_kernel<16>), grid, dim3(256), smem, stream, scores, n, ld, k, vec4, out_idx, out_val, chunk_len);
-  else {
-    // more than 64 KB of dynamic LDS has to be allowed explicitly
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&topk_kernel<64>),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((topk_kernel<64>), grid, dim3(256), smem, stream, scores, n, ld, k, vec4, out_idx, out_val, chunk_len);
-  }
+  static LdsLimit lds_limit;
+  if (const hipError_t e = raise_lds_limit(lds_limit, reinterpret_cast<const void*>(&topk_kernel), (int)sizeof(TopkLds)); e != hipSuccess) return e;
+  hipLaunchKernelGGL(topk_kernel, grid, dim3(256), sizeof(TopkLds), stream, scores, n, ld, k, vec4, out_idx, out_val, chunk_len);
+  return hipGetLastError();
+}
+
+hipError_t launch_topk_merge(const float* part_val, const int32_t* part_idx, int64_t rows, int ranges, int k,
+                             int32_t* out_idx, float* out_val, hipStream_t s) {
+  if (rows == 0) return hipSuccess;
+  if (ranges < 1 || k < 1 || k > 64 || (int64_t)ranges * k > 4096 || rows > 0x7fffffff) return hipErrorInvalidValue;
+  static LdsLimit lds_limit;
+  if (const hipError_t e = raise_lds_limit(lds_limit, reinterpret_cast<const void*>(&topk_merge_kernel), (int)sizeof(TopkLds)); e != hipSuccess) return e;
+  hipLaunchKernelGGL(topk_merge_kernel, dim3((unsigned)rows), dim3(256), sizeof(TopkLds), s, part_val, part_idx, ranges * k, k, out_idx, out_val);
   return hipGetLastError();
 }
 
