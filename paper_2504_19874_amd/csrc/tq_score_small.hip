@@ -16,6 +16,8 @@
 // lane the values of its query (lane%4) for four consecutive coordinates.
 #include "tq_internal.h"
 
+#include <type_traits>
+
 namespace tq {
 
 typedef float floatx4 __attribute__((ext_vector_type(4)));
@@ -61,46 +63,93 @@ __global__ __launch_bounds__(256) void matvec_small_kernel(const int d, const in
   (blockIdx.z == 0 ? out0 : out1)[(int64_t)(q0 + r) * d + j] = (a0 + a1) + (a2 + a3);
 }
 
-// The same product for long vectors: one wavefront per output row j, its lanes striding over the row with
-// 16-byte loads (a wavefront's load is 1 KB of one row; a thread per row, as above, touches 64 rows per load and
-// walks each of them alone: 43 us at d = 1536, 110 us for two matrices at d = 3072).  Four rows per workgroup, the
-// block of 4 queries in LDS; blockIdx.x: rows, .y: query block, .z: matrix.
+// Long vectors: a wavefront takes R rows of the matrix at a time, 16 bytes per lane and load, against Q vectors that the
+// workgroup has staged in LDS.  Bound by the matrix coming from memory; R = 4 shares the staging and the LDS reads over four
+// rows where that still gives the chip enough workgroups.  (Four vectors, two matrices of 3072 x 3072, 75 MB: 57 us with
+// one row per wavefront and the vectors staged a float at a time, 18.5 here; one vector, 1536 x 1536: 7.2 us -> 2.2 - 3.2.)
+template <int Q, int R>
 __global__ __launch_bounds__(256) void matvec_rows_kernel(const int d, const int nq, const float* __restrict__ W0,
                                                           const float* __restrict__ W1, const float* __restrict__ x,
                                                           const int64_t ldx, float* __restrict__ out0,
-                                                          float* __restrict__ out1, const int x_bf16) {
-  extern __shared__ __attribute__((aligned(16))) float xs[];  // [MV_Q][d]
+                                                          float* __restrict__ out1, const int64_t ldo, const int x_bf16) {
+  extern __shared__ __attribute__((aligned(16))) float xs[];  // [Q][d]
   const int tid = threadIdx.x, lane = tid & 63;
-  const int q0 = blockIdx.y * MV_Q;
-  for (int e = tid; e < MV_Q * d; e += 256) {
-    const int r = e / d, k = e - r * d;
-    float v = 0.f;
-    if (q0 + r < nq)
-      v = x_bf16 ? __uint_as_float((uint32_t)reinterpret_cast<const uint16_t*>(x)[(int64_t)(q0 + r) * ldx + k] << 16)
-                 : x[(int64_t)(q0 + r) * ldx + k];
-    xs[e] = v;
-  }
-  __syncthreads();
-  const int j = blockIdx.x * 4 + (tid >> 6);
-  if (j >= d) return;  // the whole wavefront
-  const float4* w4 = reinterpret_cast<const float4*>((blockIdx.z == 0 ? W0 : W1) + (int64_t)j * d);
-  float acc[MV_Q] = {0.f, 0.f, 0.f, 0.f};
-  for (int k4 = lane; k4 < d / 4; k4 += 64) {
-    const float4 w = w4[k4];
+  const int q0 = blockIdx.y * Q;
 #pragma unroll
-    for (int r = 0; r < MV_Q; ++r) {
+  for (int r = 0; r < Q; ++r) {
+    const int64_t row = q0 + r < nq ? q0 + r : nq - 1;  // past the end: the last one again, not stored
+    if (x_bf16) {
+      const uint2* src = reinterpret_cast<const uint2*>(reinterpret_cast<const uint16_t*>(x) + row * ldx);
+      for (int k4 = tid; k4 < d / 4; k4 += 256) {
+        const uint2 w = src[k4];
+        reinterpret_cast<float4*>(xs + r * d)[k4] = make_float4(__uint_as_float(w.x << 16), __uint_as_float(w.x & 0xffff0000u),
+                                                                __uint_as_float(w.y << 16), __uint_as_float(w.y & 0xffff0000u));
+      }
+    } else {
+      const float4* src = reinterpret_cast<const float4*>(x + row * ldx);
+#pragma unroll 4
+      for (int k4 = tid; k4 < d / 4; k4 += 256) reinterpret_cast<float4*>(xs + r * d)[k4] = src[k4];
+    }
+  }
+  const int j0 = (blockIdx.x * 4 + (tid >> 6)) * R;
+  const bool live = j0 < d;  // d is a multiple of 4 R: whole wavefronts
+  const float4* w4 = reinterpret_cast<const float4*>((blockIdx.z == 0 ? W0 : W1) + (int64_t)(live ? j0 : 0) * d);
+  float acc[R][Q];
+#pragma unroll
+  for (int i = 0; i < R; ++i)
+#pragma unroll
+    for (int r = 0; r < Q; ++r) acc[i][r] = 0.f;
+  __syncthreads();
+#pragma unroll 2
+  for (int k4 = lane; k4 < d / 4; k4 += 64) {
+    float4 w[R];
+#pragma unroll
+    for (int i = 0; i < R; ++i) w[i] = w4[i * (d / 4) + k4];
+#pragma unroll
+    for (int r = 0; r < Q; ++r) {
       const float4 v = reinterpret_cast<const float4*>(xs + r * d)[k4];
-      acc[r] = fmaf(w.x, v.x, fmaf(w.y, v.y, fmaf(w.z, v.z, fmaf(w.w, v.w, acc[r]))));
+#pragma unroll
+      for (int i = 0; i < R; ++i) acc[i][r] = fmaf(w[i].x, v.x, fmaf(w[i].y, v.y, fmaf(w[i].z, v.z, fmaf(w[i].w, v.w, acc[i][r]))));
     }
   }
 #pragma unroll
   for (int off = 32; off >= 1; off >>= 1)
 #pragma unroll
-    for (int r = 0; r < MV_Q; ++r) acc[r] += __shfl_xor(acc[r], off);
-  if (lane < MV_Q && q0 + lane < nq) {
-    const float v = lane == 0 ? acc[0] : lane == 1 ? acc[1] : lane == 2 ? acc[2] : acc[3];
-    (blockIdx.z == 0 ? out0 : out1)[(int64_t)(q0 + lane) * d + j] = v;
+    for (int i = 0; i < R; ++i)
+#pragma unroll
+      for (int r = 0; r < Q; ++r) acc[i][r] += __shfl_xor(acc[i][r], off);
+  if (!live) return;
+  float* const out = blockIdx.z == 0 ? out0 : out1;
+#pragma unroll
+  for (int i = 0; i < R; ++i)
+#pragma unroll
+    for (int r = 0; r < Q; ++r)
+      if (lane == i * Q + r && q0 + r < nq) out[(q0 + r) * ldo + j0 + i] = acc[i][r];
+}
+
+hipError_t launch_matvec_rows(int d, int64_t n, const float* W0, const float* W1, const float* x, int64_t ldx, float* out0,
+                              float* out1, int64_t ldo, bool bf16, hipStream_t s) {
+  if (n == 0) return hipSuccess;
+  if (d % 32 != 0 || ldx % 4 != 0 || (size_t)MV_Q * d * sizeof(float) > 65536) return hipErrorInvalidValue;
+  constexpr int64_t most = (int64_t)65535 * MV_Q;  // blocks of vectors are a grid dimension
+  for (; n > most; n -= most) {
+    if (const hipError_t e = launch_matvec_rows(d, most, W0, W1, x, ldx, out0, out1, ldo, bf16, s); e != hipSuccess) return e;
+    x = bf16 ? reinterpret_cast<const float*>(reinterpret_cast<const uint16_t*>(x) + most * ldx) : x + most * ldx;
+    out0 += most * ldo;
+    out1 = out1 != nullptr ? out1 + most * ldo : nullptr;
   }
+  const int nq = (int)n;
+  const int mats = W1 != nullptr ? 2 : 1;
+  auto go = [&](auto q_c, auto r_c) {
+    constexpr int Q = decltype(q_c)::value, R = decltype(r_c)::value;
+    hipLaunchKernelGGL((matvec_rows_kernel<Q, R>), dim3((d + 4 * R - 1) / (4 * R), (nq + Q - 1) / Q, mats), dim3(256),
+                       (size_t)Q * d * sizeof(float), s, d, nq, W0, W1, x, ldx, out0, out1, ldo, bf16 ? 1 : 0);
+    return hipGetLastError();
+  };
+  using std::integral_constant;
+  const bool many = (int64_t)(d / 16) * ((nq + 3) / 4) * mats >= device_cu_count();
+  if (nq == 1) return many ? go(integral_constant<int, 1>{}, integral_constant<int, 4>{}) : go(integral_constant<int, 1>{}, integral_constant<int, 1>{});
+  return many ? go(integral_constant<int, MV_Q>{}, integral_constant<int, 4>{}) : go(integral_constant<int, MV_Q>{}, integral_constant<int, 1>{});
 }
 
 // Alg. 1 for a handful of long vectors (adding to an index one vector at a time): y = Pi x by the row-per-wavefront
@@ -175,10 +224,8 @@ hipError_t launch_quant_rows(int bits, bool bf16, const void* x, int64_t ldx, in
                              const float* SPiT, float* ew, uint32_t* qjl, float* gamma) {
   if (n == 0) return hipSuccess;
   if (n > 65535 * MV_Q || d % 32 != 0 || (size_t)MV_Q * d * sizeof(float) > 65536) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(matvec_rows_kernel, dim3((d + 3) / 4, (unsigned)((n + MV_Q - 1) / MV_Q), 1), dim3(256),
-                     (size_t)MV_Q * d * sizeof(float), stream, d, (int)n, Pi, nullptr, static_cast<const float*>(x), ldx, yw,
-                     nullptr, bf16 ? 1 : 0);
-  if (const hipError_t e = hipGetLastError(); e != hipSuccess) return e;
+  if (const hipError_t e = launch_matvec_rows(d, n, Pi, nullptr, static_cast<const float*>(x), ldx, yw, nullptr, d, bf16, stream); e != hipSuccess)
+    return e;
   const dim3 grid((unsigned)n);
   const int xb = bf16 ? 1 : 0;
   switch (bits) {
@@ -191,9 +238,7 @@ hipError_t launch_quant_rows(int bits, bool bf16, const void* x, int64_t ldx, in
   }
   if (const hipError_t e = hipGetLastError(); e != hipSuccess || ew == nullptr) return e;
   // Alg. 2: u = (S Pi^T) e, again one wavefront per matrix row (into the buffer the rotation has left), signs packed
-  hipLaunchKernelGGL(matvec_rows_kernel, dim3((d + 3) / 4, (unsigned)((n + MV_Q - 1) / MV_Q), 1), dim3(256),
-                     (size_t)MV_Q * d * sizeof(float), stream, d, (int)n, SPiT, nullptr, ew, (int64_t)d, yw, nullptr, 0);
-  if (const hipError_t e = hipGetLastError(); e != hipSuccess) return e;
+  if (const hipError_t e = launch_matvec_rows(d, n, SPiT, nullptr, ew, (int64_t)d, yw, nullptr, d, false, stream); e != hipSuccess) return e;
   return launch_stage_sign_pack(d, yw, n, qjl, stream);
 }
 
@@ -301,9 +346,7 @@ hipError_t launch_matvec_small(int d, int nq, const float* W0, const float* W1, 
   if (nq == 0) return hipSuccess;
   if (d % 4 != 0 || (size_t)MV_Q * d * sizeof(float) > 65536) return hipErrorInvalidValue;
   if (d >= 512) {
-    hipLaunchKernelGGL(matvec_rows_kernel, dim3((d + 3) / 4, (nq + MV_Q - 1) / MV_Q, W1 != nullptr ? 2 : 1), dim3(256),
-                       (size_t)MV_Q * d * sizeof(float), stream, d, nq, W0, W1, x, ldx, out0, out1, 0);
-    return hipGetLastError();
+    return launch_matvec_rows(d, nq, W0, W1, x, ldx, out0, out1, d, false, stream);
   }
   hipLaunchKernelGGL(matvec_small_kernel, dim3((d + 63) / 64, (nq + MV_Q - 1) / MV_Q, W1 != nullptr ? 2 : 1),
                      dim3(256), (size_t)MV_Q * d * sizeof(float), stream, d, nq, W0, W1, x, ldx, out0, out1);
