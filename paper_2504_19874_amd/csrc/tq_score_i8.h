@@ -1,6 +1,6 @@
-// Shared by the two few-query scoring kernels on the integer matrix cores
-// (tq_score_i8.hip: any d that is a multiple of 128 up to 4096, queries prepared by a
-// kernel of their own, 512 coordinates per launch; tq_score_i8_128.hip: d = 128 with everything in one kernel).
+// Shared by the few-query scoring kernels on the integer matrix cores (tq_score_stream.hip: any d that is a multiple of
+// 128 up to 4096, queries prepared by kernels of their own in tq_score_i8.hip; tq_score_i8_128.hip: d = 128 with
+// everything in one kernel; tq_score_i8_split.hip: d = 128 split into two instances).
 #pragma once
 #include "tq_internal.h"
 
@@ -11,7 +11,7 @@ typedef int v4i __attribute__((ext_vector_type(4)));
 // coordinate block of (k-step s, k-chunk kq): 16 coordinates starting here
 __host__ __device__ constexpr int i8_coord0(int s, int kq) { return 32 * (kq + 4 * (s >> 1)) + 16 * (s & 1); }
 
-// Image of one query's A operand, written by prep_i8_kernel: for matrix m (0: Pi q, 1: S q),
+// Image of one query's A operand for split codes, written by prep_i8_kernel: for matrix m (0: Pi q, 1: S q),
 // k-step s, digit row dg, k-chunk kq the 16 bytes of coordinates i8_coord0(s, kq) .. + 15.
 //   bytes:   img[((q * 2 + m) * ks + s) * 16 + dg * 4 + kq]      (16-byte units)
 //   scalars: scal[(q * 2 + m) * 4 + {0: 1/scale, 1: sum of the rounded coordinates, 2 and 3: the same sum over
@@ -36,24 +36,19 @@ struct ScoreI8Args {
   int q_per_group;
   float kappa;
   float coef[16];  // coef[0]: factor of sum_j qr_j; coef[S]: factor of M_S (odd |S| only)
-  // tq_score_i8.hip only: one launch covers k-steps [k0, k0 + ks_slice) of the d / 64; a launch with `accumulate`
-  // adds its masked sums to the scores an earlier launch left (the terms that do not depend on the code are
-  // added by the launch without it)
-  int k0;
-  int ks_slice;
-  int accumulate;
 };
 
-constexpr int I8_MAX_KS = 8;     // k-steps of one launch: 512 coordinates (the A operands of a launch sit in registers)
-constexpr int I8_MAX_D = 4096;   // longer vectors take several launches, each adding its 512 coordinates
+constexpr int I8_MAX_D = 4096;
 // the terms the kernel evaluates: plane subsets of odd size (symmetric codebook)
 __host__ __device__ constexpr bool i8_term(int m) { return __builtin_popcount((unsigned)m) & 1; }
-// tiles of 16 keys per wavefront: as many as the register file holds code words for
-__host__ __device__ constexpr int i8_tiles(int bits, int ksm) { return (bits >= 4 ? 16 : 32) / ksm; }
 constexpr int I8_COPIES = 32;
 constexpr int I8_TABLE_BYTES = 256 * I8_COPIES * 8;
 
 
+// the codes against digit images that are ready (tq_score_stream.hip)
+hipError_t launch_score_stream(int bits, bool prod, const uint4* img, const float* scal, const uint32_t* idx, const uint32_t* qjl,
+                               const float* gamma, const float* norm, float* scores, int64_t lds, int64_t n, int d, int n_groups,
+                               int q_per_group, float kappa, const float* coef, hipStream_t stream);
 hipError_t launch_score_i8_128(int bits, bool prod, const ScoreI8Args& a, int n_groups, hipStream_t stream);
 bool score128_args(int bits, bool prod, const float* PiT, const float* ST, const float* q, int64_t ldq,
                    const uint32_t* idx, const uint32_t* qjl, const float* gamma, const float* norm, int64_t n,
