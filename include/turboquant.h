@@ -224,6 +224,7 @@ typedef struct tq_params {
  * the speed; meant for measurements against the fp32 peak and for callers who
  * want the plain fp32 evaluation. */
 #define TQ_FLAG_FP32_MFMA 1u
+#define TQ_FLAG_DEQUANT_IMAGES 2u  /* params.images: see tq_build_dequant_images */
 
 /*
  * Fill the derived matrices from Pi and S on the device: PiT = Pi^T,
@@ -249,6 +250,15 @@ tq_status tq_derive_params(int32_t d, const float* Pi, const float* S, float* Pi
  * matrices), TQ_ERR_UNSUPPORTED (misaligned), TQ_ERR_HIP. */
 size_t tq_images_bytes(int32_t d);
 tq_status tq_build_images(const tq_params* p, void* images, void* stream);
+
+/* The same for tq_dequantize at d other than 128 (0 bytes, nothing done, at d = 128): Pi^T and S^T as the tiles its
+ * workgroups stage, read from p->Pi and p->S.  They lie behind the images above: `images` is a buffer of
+ * tq_images_bytes(d) + tq_dequant_images_bytes(d) bytes, and TQ_FLAG_DEQUANT_IMAGES in params.flags says that
+ * params.images is such a buffer with both parts filled.  Without the flag tq_dequantize makes these tiles in the
+ * workspace in every call, where it has room (8 d^2 + 256 bytes), or takes kernels that do without, the same up to
+ * rounding. */
+size_t tq_dequant_images_bytes(int32_t d);
+tq_status tq_build_dequant_images(const tq_params* p, void* images, void* stream);
 
 /* Device scratch large enough for any call with up to n vectors (per call),
  * nq queries and this topk under these params: an upper bound that counts a

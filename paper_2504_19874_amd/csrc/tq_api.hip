@@ -6,6 +6,7 @@
 #include <mutex>
 
 #include "tq_attend.h"
+#include "tq_code_gemm.h"
 #include "tq_h2.h"
 #include "tq_score_i8.h"
 
@@ -123,10 +124,14 @@ struct Workspace {
 };
 
 // params.images at every d other than 128: [Pi][S Pi^T] as two fp16 pieces (4 d^2 bytes each), then the inverse scales of
-// the two, each followed by a word that tq_build_images uses
+// the two, each followed by a word that tq_build_images uses; with TQ_FLAG_DEQUANT_IMAGES behind those (tq_images_bytes)
+// [Pi^T][S^T] in the order in which codes are decoded and the scales of these
 const char* h2_images(const tq_params* p) { return p->d != 128 ? static_cast<const char*>(p->images) : nullptr; }
+const char* h2_image(const void* images, int d, int which) {
+  return static_cast<const char*>(images) + (which >= 2 ? tq_images_bytes(d) : 0) + (which & 1) * h2_image_bytes(d, d);
+}
 float* h2_image_scale(const void* images, int d, int which) {
-  return reinterpret_cast<float*>(const_cast<char*>(static_cast<const char*>(images)) + 2 * h2_image_bytes(d, d)) + 2 * which;
+  return reinterpret_cast<float*>(const_cast<char*>(h2_image(images, d, which & 2)) + 2 * h2_image_bytes(d, d)) + 2 * (which & 1);
 }
 // without them: the images a call makes for itself in the workspace
 size_t h2_own_images_bytes(int d, bool prod) { return kH2ImageHeader + (prod ? 2 : 1) * h2_image_bytes(d, d); }
@@ -139,8 +144,8 @@ bool quantize_h2(const tq_params* p, const void* x, bool bf16, int64_t n, int64_
   Workspace ws{static_cast<char*>(p->workspace), p->workspace_bytes, 0};
   const char* pi_img = h2_images(p);
   const bool build = pi_img == nullptr || !aligned16(pi_img);
-  const char* s_img = pi_img + h2_image_bytes(d, d);
-  float* w_inv = h2_image_scale(pi_img, d, 0);
+  const char* s_img = h2_image(pi_img, d, 1);
+  float* w_inv = h2_image_scale(pi_img, d, 0);  // of the second image two floats on
   if (build) {  // the same bits as tq_build_images makes
     char* const own = static_cast<char*>(ws.take(h2_own_images_bytes(d, prod)));
     if (own == nullptr) return false;
@@ -373,8 +378,7 @@ tq_status tq_build_images(const tq_params* p, void* images, void* stream) {
     hipStream_t s = static_cast<hipStream_t>(stream);
     const int d = p->d;
     if (launch_h2_image(p->Pi, d, d, d, images, h2_image_scale(images, d, 0), s) != hipSuccess) return TQ_ERR_HIP;
-    if (p->SPiT != nullptr &&
-        launch_h2_image(p->SPiT, d, d, d, static_cast<char*>(images) + h2_image_bytes(d, d), h2_image_scale(images, d, 1), s) != hipSuccess)
+    if (p->SPiT != nullptr && launch_h2_image(p->SPiT, d, d, d, const_cast<char*>(h2_image(images, d, 1)), h2_image_scale(images, d, 1), s) != hipSuccess)
       return TQ_ERR_HIP;
     return TQ_OK;
   }
@@ -385,6 +389,24 @@ tq_status tq_build_images(const tq_params* p, void* images, void* stream) {
   hipStream_t s = static_cast<hipStream_t>(stream);
   if (launch_quant128_bf3_image(p->Pi, p->SPiT, images, s) != hipSuccess) return TQ_ERR_HIP;
   if (launch_dequant128_bf3_image(p->PiT, p->ST, static_cast<char*>(images) + quant128_bf3_image_bytes(), s) != hipSuccess)
+    return TQ_ERR_HIP;
+  return TQ_OK;
+}
+
+size_t tq_dequant_images_bytes(int32_t d) {
+  if (d == 128 || d <= 0 || d % 32 != 0 || d > 16384) return 0;
+  return 2 * h2_image_bytes(d, d) + 256;
+}
+
+tq_status tq_build_dequant_images(const tq_params* p, void* images, void* stream) {
+  if (p == nullptr || p->d <= 0) return TQ_ERR_INVALID_ARG;
+  if (tq_dequant_images_bytes(p->d) == 0) return TQ_OK;
+  if (images == nullptr || p->Pi == nullptr) return TQ_ERR_INVALID_ARG;
+  if (!aligned16(images)) return TQ_ERR_UNSUPPORTED;
+  const hipStream_t s = static_cast<hipStream_t>(stream);
+  const int d = p->d;
+  if (launch_code_image(p->Pi, d, const_cast<char*>(h2_image(images, d, 2)), h2_image_scale(images, d, 2), s) != hipSuccess ||
+      (p->S != nullptr && launch_code_image(p->S, d, const_cast<char*>(h2_image(images, d, 3)), h2_image_scale(images, d, 3), s) != hipSuccess))
     return TQ_ERR_HIP;
   return TQ_OK;
 }
@@ -497,6 +519,29 @@ tq_status tq_dequantize(const tq_params* p, const uint32_t* idx, const uint32_t*
   if (p->d < 4096 && !fp32_mfma_only(p) && rows_route_serves(prod ? 2 * n : n, p->d, prod ? 2 : 1, 300))
     return from_hip(launch_dequant_rows(p->bits_mse, prod, p->d, n, idx, qjl, gamma, norm, p->PiT, p->ST, make_codebook(p),
                                         kappa_of(p->d), x_out, ldo, static_cast<hipStream_t>(stream)));
+  // many codes: fp16 pieces of Pi^T and S^T, from the images or made here where the workspace holds them
+  if (!fp32_mfma_only(p) && code_gemm_serves(p->bits_mse, make_codebook(p)) && (p->bits_mse > 0 || prod) && p->Pi != nullptr && (!prod || p->S != nullptr)) {
+    const hipStream_t s = static_cast<hipStream_t>(stream);
+    const int d = p->d;
+    const char *pit = nullptr, *sit = nullptr;
+    float *pit_inv = nullptr, *sit_inv = nullptr;
+    if (const char* const img = h2_images(p); img != nullptr && aligned16(img) && (p->flags & TQ_FLAG_DEQUANT_IMAGES) != 0) {
+      pit = h2_image(img, d, 2), sit = h2_image(img, d, 3);
+      pit_inv = h2_image_scale(img, d, 2), sit_inv = h2_image_scale(img, d, 3);
+    } else {
+      Workspace ws{static_cast<char*>(p->workspace), p->workspace_bytes, 0};
+      if (char* const own = static_cast<char*>(ws.take(h2_own_images_bytes(d, prod))); own != nullptr) {
+        pit = own + kH2ImageHeader, sit = h2_image(pit, d, 1);
+        pit_inv = reinterpret_cast<float*>(own), sit_inv = pit_inv + 2;
+        if (launch_code_image(p->Pi, d, const_cast<char*>(pit), pit_inv, s) != hipSuccess ||
+            (prod && launch_code_image(p->S, d, const_cast<char*>(sit), sit_inv, s) != hipSuccess))
+          return TQ_ERR_HIP;
+      }
+    }
+    if (pit != nullptr)
+      return from_hip(launch_code_dequant(p->bits_mse, prod, pit, pit_inv, sit, sit_inv, d, idx, qjl, gamma, norm, n, x_out, ldo,
+                                          kappa_of(d), make_codebook(p), s));
+  }
   // x~_i[k] = <e_k, DeQuant(code i)>: the scoring contraction with the rows of Pi^T (and S^T) as the queries,
   // stored one row per code; on the bf16 matrix cores where that kernel takes the codes
   if (!fp32_mfma_only(p) && score_bf3_applicable(p->bits_mse, prod, p->d, n, 1, p->d, make_codebook(p)))

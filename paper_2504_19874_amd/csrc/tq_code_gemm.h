@@ -1,0 +1,32 @@
+// Dense contractions of packed codes against the rows of a fixed operand on the fp16 matrix cores (tq_code_gemm.hip):
+// dequantisation (rows of Pi^T and S^T) and the first pass of a nearest-neighbour search (rotated queries).
+#pragma once
+#include "tq_h2.h"
+
+namespace tq {
+
+// Order of the 32 coordinates of a word group along the contraction: four bytes' worth of bits at the same bit position are
+// decoded together, so position 4 k + e (k = 0..7) is coordinate k + {0, 16, 8, 24}[e].
+__host__ __device__ constexpr int code_position(int coord) {
+  const int b = coord >> 3;
+  return 4 * (coord & 7) + (b == 0 ? 0 : b == 2 ? 1 : b == 1 ? 2 : 3);
+}
+
+// A centroid table symmetric about zero as fp16 pieces by bytes: byte m of hh / hl is the high / low byte of the leading
+// piece of the m-th magnitude, lh / ll those of the second piece
+struct CodeTable {
+  uint32_t hh[2], hl[2], lh[2], ll[2];
+  float inv;  // 1 / scale of the pieces; 1 bit: the centroid itself, the operand being +-1
+};
+bool code_gemm_serves(int bits, const Codebook& cb);  // symmetric tables of up to 4 bits
+CodeTable make_code_table(int bits, const Codebook& cb);
+
+// Image of a d x d matrix's transpose in the order above: rows of two fp16 pieces, h2_image_bytes(d, d) bytes
+hipError_t launch_code_image(const float* W, int d, void* image, float* w_inv, hipStream_t s);
+
+// x~_i = nu_i (Pi^T c[idx_i] + kappa gamma_i S^T z_i) for n codes, out rows ldo floats apart (ldo and d multiples of 4)
+hipError_t launch_code_dequant(int bits, bool prod, const void* pit_image, const float* pit_inv, const void* st_image, const float* st_inv,
+                               int d, const uint32_t* idx, const uint32_t* qjl, const float* gamma, const float* norm, int64_t n,
+                               float* out, int64_t ldo, float kappa, const Codebook& cb, hipStream_t s);
+
+}  // namespace tq

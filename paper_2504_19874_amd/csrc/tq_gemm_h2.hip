@@ -526,11 +526,16 @@ bool h2_codebook_serves(int bits, const Codebook& cb) { return bits < 3 || codeb
 
 size_t h2_image_bytes(int M, int d) { return (size_t)M * d * 4; }
 
+hipError_t launch_h2_max(const float* W, int64_t ldw, int M, int d, uint32_t* max_bits, hipStream_t s) {
+  hipLaunchKernelGGL(h2_zero_kernel, dim3(1), dim3(1), 0, s, max_bits);
+  hipLaunchKernelGGL(h2_max_kernel, dim3(256), dim3(256), 0, s, W, ldw, M, d, max_bits);
+  return hipGetLastError();
+}
+
 hipError_t launch_h2_image(const float* W, int64_t ldw, int M, int d, void* image, float* w_inv, hipStream_t s) {
   if (M <= 0 || d <= 0 || d % 32 != 0 || ldw % 4 != 0) return hipErrorInvalidValue;
   uint32_t* const max_bits = reinterpret_cast<uint32_t*>(w_inv) + 1;
-  hipLaunchKernelGGL(h2_zero_kernel, dim3(1), dim3(1), 0, s, max_bits);
-  hipLaunchKernelGGL(h2_max_kernel, dim3(256), dim3(256), 0, s, W, ldw, M, d, max_bits);
+  if (const hipError_t e = launch_h2_max(W, ldw, M, d, max_bits, s); e != hipSuccess) return e;
   const int64_t threads = (int64_t)M * d / 8;
   hipLaunchKernelGGL(h2_image_kernel, dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, s, W, ldw, M, d, max_bits, w_inv,
                      static_cast<unsigned char*>(image));
