@@ -90,21 +90,21 @@ __device__ __forceinline__ void load_plane_words(const uint32_t* p, uint32_t (&w
   if constexpr (BITS == 4) { const v4 v = *reinterpret_cast<const v4*>(p); w[0] = v[0]; w[1] = v[1]; w[2] = v[2]; w[3] = v[3]; }
 }
 
-template <int BITS, bool PROD, int TW, int WM, int WN>
+template <int BITS, bool PROD, int TW, int WM, int WN, int NBUF>
 struct CodeCfg {
   static constexpr int UW = WM;  // so that every thread decodes half a group of one code per step
   static constexpr int THREADS = 64 * WM * WN, TM = WM * TW * 32, TN = WN * UW * 32;
   static constexpr int NPA = 2, NPB = BITS >= 2 ? 2 : 1;
   static constexpr int A_BYTES = TM * 64 * NPA, B_BYTES = TN * 64 * NPB;
-  static constexpr int NS = 2;
+  static constexpr int NS = NBUF;
   static constexpr int LDS = NS * (A_BYTES + B_BYTES) + 2 * TN * 4;
   static constexpr int AL = A_BYTES / 1024 / (WM * WN);  // direct loads per wavefront and step
   static_assert(THREADS == 2 * TN && AL * WM * WN * 1024 == A_BYTES, "roles");
 };
 
-template <int BITS, bool PROD, int TW, int WM, int WN>
+template <int BITS, bool PROD, int TW, int WM, int WN, int NBUF>
 __global__ __launch_bounds__(64 * WM * WN, 2) void code_gemm_kernel(const CodeGemmArgs a) {
-  using C = CodeCfg<BITS, PROD, TW, WM, WN>;
+  using C = CodeCfg<BITS, PROD, TW, WM, WN, NBUF>;
   constexpr int UW = C::UW, TM = C::TM, TN = C::TN, NPA = C::NPA, NPB = C::NPB, NS = C::NS, AL = C::AL;
   constexpr bool HAVE_P = BITS > 0, HAVE_S = PROD;
   constexpr int NW = BITS > 0 ? BITS : 1;
@@ -275,29 +275,33 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void code_gemm_kernel(const CodeGe
     h2_wait_barrier<(NS - 2) * (AL + 1) + 1>();
   };
   // (two loops: with the segments' products in two arms of one loop the accumulators are copied between them)
-  using std::integral_constant;
+  auto round = [&](auto in_s) {  // one step in each buffer
+    step(std::integral_constant<int, 0>{}, in_s);
+    step(std::integral_constant<int, 1>{}, in_s);
+    if constexpr (NS == 4) {
+      step(std::integral_constant<int, 2>{}, in_s);
+      step(std::integral_constant<int, 3>{}, in_s);
+    }
+  };
   int left = HAVE_P ? G : 0;
   if constexpr (HAVE_S) {
     int st = 0;
-    for (; st + 2 <= n_s; st += 2) {
-      step(integral_constant<int, 0>{}, std::true_type{});
-      step(integral_constant<int, 1>{}, std::true_type{});
-    }
-    if (st < n_s) step(integral_constant<int, 0>{}, std::true_type{});
+    for (; st + NS <= n_s; st += NS) round(std::true_type{});
+    if constexpr (NS == 2)  // with four buffers the number of groups is a multiple of four
+      if (st < n_s) step(std::integral_constant<int, 0>{}, std::true_type{});
     if constexpr (HAVE_P) {
       scale();
-      if (st < n_s) {
-        step(integral_constant<int, 1>{}, std::false_type{});
-        --left;
-      }
+      if constexpr (NS == 2)
+        if (st < n_s) {
+          step(std::integral_constant<int, 1>{}, std::false_type{});
+          --left;
+        }
     }
   }
   if constexpr (HAVE_P) {
-    for (; left >= 2; left -= 2) {
-      step(integral_constant<int, 0>{}, std::false_type{});
-      step(integral_constant<int, 1>{}, std::false_type{});
-    }
-    if (left > 0) step(integral_constant<int, 0>{}, std::false_type{});
+    for (; left >= NS; left -= NS) round(std::false_type{});
+    if constexpr (NS == 2)
+      if (left > 0) step(std::integral_constant<int, 0>{}, std::false_type{});
   }
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // nothing of this workgroup's is under way to LDS when it ends
 
@@ -319,28 +323,35 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void code_gemm_kernel(const CodeGe
     }
 }
 
-template <int BITS, bool PROD, int TW, int WM, int WN>
+template <int BITS, bool PROD, int TW, int WM, int WN, int NBUF>
 hipError_t launch_tile(CodeGemmArgs a, hipStream_t s) {
-  using C = CodeCfg<BITS, PROD, TW, WM, WN>;
+  using C = CodeCfg<BITS, PROD, TW, WM, WN, NBUF>;
   a.tiles_m = (a.M + C::TM - 1) / C::TM;
   const int64_t tiles_n = (a.n + C::TN - 1) / C::TN;
   if (tiles_n * a.tiles_m > (int64_t)1 << 30) return hipErrorInvalidValue;
   a.tiles_n = (int)tiles_n;
   a.per_xcd = (a.tiles_m * a.tiles_n + XCDS - 1) / XCDS;
   static LdsLimit lds_limit;  // per instantiation: the limit is raised once per device
-  if (const hipError_t e = raise_lds_limit(lds_limit, reinterpret_cast<const void*>(&code_gemm_kernel<BITS, PROD, TW, WM, WN>), C::LDS);
+  if (const hipError_t e = raise_lds_limit(lds_limit, reinterpret_cast<const void*>(&code_gemm_kernel<BITS, PROD, TW, WM, WN, NBUF>), C::LDS);
       e != hipSuccess)
     return e;
-  hipLaunchKernelGGL((code_gemm_kernel<BITS, PROD, TW, WM, WN>), dim3(a.per_xcd * XCDS), dim3(C::THREADS), C::LDS, s, a);
+  hipLaunchKernelGGL((code_gemm_kernel<BITS, PROD, TW, WM, WN, NBUF>), dim3(a.per_xcd * XCDS), dim3(C::THREADS), C::LDS, s, a);
   return hipGetLastError();
 }
 
+// The large tile while it gives most compute units one (its reads per product are half those of the next); below that
+// smaller ones, whose steps are shorter than a load's latency: four buffers then, where d is a multiple of 128.  Matrices
+// of up to 64 rows have a tile of their own.
 template <int BITS, bool PROD>
 hipError_t launch_dequant(const CodeGemmArgs& a, hipStream_t s) {
-  // the large tile while it gives most compute units one (its reads per product are half those of the small one)
-  const int64_t large = (int64_t)((a.M + 255) / 256) * ((a.n + 255) / 256);
-  if (large * 4 >= (int64_t)device_cu_count() * 3 || (a.M <= 256 && a.M > 128 && large * 2 >= device_cu_count())) return launch_tile<BITS, PROD, 2, 4, 2>(a, s);
-  return launch_tile<BITS, PROD, 2, 2, 2>(a, s);
+  const int64_t cus = device_cu_count();
+  auto count = [&](int tm, int tn) { return (int64_t)((a.M + tm - 1) / tm) * ((a.n + tn - 1) / tn); };
+  const bool four = a.d % 128 == 0;
+  if (a.M <= 64) return launch_tile<BITS, PROD, 1, 2, 4, 2>(a, s);
+  const bool wide = (a.M + 255) / 256 * 256 * 5 < (a.M + 127) / 128 * 128 * 6;  // little more padding than the next tile
+  if (wide && count(256, 256) * 4 >= cus * 3) return launch_tile<BITS, PROD, 2, 4, 2, 2>(a, s);
+  if (count(128, 128) * 2 >= cus || !four) return four ? launch_tile<BITS, PROD, 2, 2, 2, 4>(a, s) : launch_tile<BITS, PROD, 2, 2, 2, 2>(a, s);
+  return launch_tile<BITS, PROD, 1, 2, 1, 4>(a, s);
 }
 
 // ---- images ----------------------------------------------------------------------------------------------
