@@ -9,7 +9,8 @@
 // for 10^6 vectors).
 //
 // Tile.  256 rows of the matrix x 256 vectors per workgroup of eight wavefronts (2 x 4 tiles of 32 x 32 each: twelve
-// 16-byte LDS reads feed 24 matrix instructions), k in steps of 32 through two buffers of 64 KB.  The fragments of the
+// 16-byte LDS reads feed 24 matrix instructions), k in steps of 32 through two buffers of 64 KB (smaller tiles, whose steps are
+// shorter than a load's latency: four).  The fragments of the
 // next 16 k are read while the present ones are multiplied; the one barrier of a step sits between its two halves, so
 // that a step's first fragments are in registers before the step begins.  The vector is on the lane axis of the result: a lane holds 16
 // coordinates of one vector per tile and the decision is lane-local.
@@ -191,6 +192,7 @@ struct H2Args {
   const unsigned char* X;
   const float* fac;
   const float* esc;
+  float* out;
   uint32_t* words;
   unsigned char* E;
   float* part;
@@ -199,9 +201,9 @@ struct H2Args {
   int d, part_tiles, tiles_m, tiles_n, per_xcd;
 };
 
-// EK 0: indices, 1: indices and residual, 2: signs.  A wavefront owns TW x UW tiles of 32 x 32, the workgroup WM x WN
+// EK 0: indices, 1: indices and residual, 2: signs, 3: the products themselves, out[vector][row].  A wavefront owns TW x UW tiles of 32 x 32, the workgroup WM x WN
 // wavefronts.
-template <int EK, int BITS, int NPX, int TW, int UW, int WM, int WN>
+template <int EK, int BITS, int NPX, int TW, int UW, int WM, int WN, int NBUF>
 __global__ __launch_bounds__(WM* WN * 64, 2) void h2_kernel(const H2Args a, const Codebook cb) {
   constexpr int NW = WM * WN;
   constexpr int TM = WM * TW * 32, TN = WN * UW * 32;
@@ -247,7 +249,7 @@ __global__ __launch_bounds__(WM* WN * 64, 2) void h2_kernel(const H2Args a, cons
   int requested = 0;
   auto dma_one = [&](int buf, int j) {
     if (j < AL) h2_dma(gA, va[j < AL ? j : 0], lds0 + buf * A_BYTES + (wave * AL + j) * 1024);
-    else h2_dma(gB, vb[j < AL ? 0 : j - AL], lds0 + 2 * A_BYTES + buf * B_BYTES + (wave * BL + j - AL) * 1024);
+    else h2_dma(gB, vb[j < AL ? 0 : j - AL], lds0 + NBUF * A_BYTES + buf * B_BYTES + (wave * BL + j - AL) * 1024);
   };
   auto dma_next = [&] {  // the last k-step is requested again and again rather than branching around the loads
     const bool more = ++requested < n_kt;
@@ -267,7 +269,7 @@ __global__ __launch_bounds__(WM* WN * 64, 2) void h2_kernel(const H2Args a, cons
 #pragma unroll
     for (int p = 0; p < 2; ++p) pa[p][s] = lds + h2_place<2>(wm * TW * 32 + l32, p * 4 + s * 2 + h);
 #pragma unroll
-    for (int p = 0; p < NPX; ++p) pb[p][s] = lds + 2 * A_BYTES + h2_place<NPX>(wn * UW * 32 + l32, p * 4 + s * 2 + h);
+    for (int p = 0; p < NPX; ++p) pb[p][s] = lds + NBUF * A_BYTES + h2_place<NPX>(wn * UW * 32 + l32, p * 4 + s * 2 + h);
   }
   struct Frag {
     f16x8 a[TW][2], b[UW][NPX];
@@ -304,9 +306,9 @@ __global__ __launch_bounds__(WM* WN * 64, 2) void h2_kernel(const H2Args a, cons
     }
   };
 
-  dma(0);
-  dma(1);
-  h2_wait_barrier<AL + BL>();
+#pragma unroll
+  for (int i = 0; i < NBUF; ++i) dma(i);
+  h2_wait_barrier<(NBUF - 1) * (AL + BL)>();
   Frag f0, f1;
   read(f0, 0, 0);
   // Every step is the same straight-line code (branches around the loads would make the compiler wait for more than it
@@ -321,10 +323,10 @@ __global__ __launch_bounds__(WM* WN * 64, 2) void h2_kernel(const H2Args a, cons
       __builtin_amdgcn_sched_barrier(0);
     });
     __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0), so that the compiler knows the fragments have arrived
-    h2_wait_barrier<0>();                // everyone has read this step; the next one has arrived
+    h2_wait_barrier<(NBUF - 2) * (AL + BL)>();  // everyone has read this step; the next one has arrived
     multiply(f1, [&](int i) {
 #pragma unroll
-      for (int r = from(i); r < from(i + 1); ++r) read_one(f0, buf ^ 1, 0, r);
+      for (int r = from(i); r < from(i + 1); ++r) read_one(f0, (buf + 1) % NBUF, 0, r);
 #pragma unroll
       for (int r = i * (AL + BL) / NM; r < (i + 1) * (AL + BL) / NM; ++r) dma_one(buf, r);
       __builtin_amdgcn_sched_barrier(0);
@@ -332,15 +334,23 @@ __global__ __launch_bounds__(WM* WN * 64, 2) void h2_kernel(const H2Args a, cons
     dma_next();
   };
   int kt = 0;
-  for (; kt + 2 <= n_kt; kt += 2) {
+  for (; kt + NBUF <= n_kt; kt += NBUF) {
     step(std::integral_constant<int, 0>{});
     step(std::integral_constant<int, 1>{});
+    if constexpr (NBUF == 4) {
+      step(std::integral_constant<int, 2>{});
+      step(std::integral_constant<int, 3>{});
+    }
   }
   if (kt < n_kt) step(std::integral_constant<int, 0>{});
+  if constexpr (NBUF == 4) {
+    if (kt + 1 < n_kt) step(std::integral_constant<int, 1>{});
+    if (kt + 2 < n_kt) step(std::integral_constant<int, 2>{});
+  }
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // nothing of this workgroup's is under way to LDS when it ends
 
   // ------------------------------- epilogue -------------------------------
-  constexpr int PL = EK == 2 ? 1 : BITS;
+  constexpr int PL = EK == 2 ? 1 : EK == 3 ? 0 : BITS;
   const int words_per_row = n_kt * PL;
 #pragma unroll
   for (int u = 0; u < UW; ++u) {
@@ -350,6 +360,18 @@ __global__ __launch_bounds__(WM* WN * 64, 2) void h2_kernel(const H2Args a, cons
     const int64_t ic = valid ? i : n0;
     float scale = 1.f, es = 1.f, g2 = 0.f;
     if (EK != 2) scale = a.fac[ic];
+    if constexpr (EK == 3) {
+#pragma unroll
+      for (int t = 0; t < TW; ++t) {
+        const int mb = m0 + (wm * TW + t) * 32;
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+          if (valid && mb < a.d)
+            *reinterpret_cast<float4*>(a.out + i * a.d + mb + 8 * k + 4 * h) =
+                make_float4(acc[t][u][4 * k] * scale, acc[t][u][4 * k + 1] * scale, acc[t][u][4 * k + 2] * scale, acc[t][u][4 * k + 3] * scale);
+      }
+      continue;
+    }
     if (EK == 1) es = a.esc[ic];
     uint32_t w[TW][4];
 #pragma unroll
@@ -447,10 +469,10 @@ Tile pick_tile(int d, int64_t n) {
   return T64;
 }
 
-template <int EK, int BITS, int NPX, int TW, int UW, int WM, int WN>
+template <int EK, int BITS, int NPX, int TW, int UW, int WM, int WN, int NBUF>
 hipError_t launch_tile(H2Args a, const Codebook& cb, hipStream_t s) {
   constexpr int TM = WM * TW * 32, TN = WN * UW * 32;
-  constexpr int lds_bytes = 2 * (TM * 128 + TN * NPX * 64);
+  constexpr int lds_bytes = NBUF * (TM * 128 + TN * NPX * 64);
   a.tiles_m = (a.d + TM - 1) / TM;
   const int64_t tiles_n = (a.n + TN - 1) / TN;
   if (tiles_n * a.tiles_m > (int64_t)1 << 30) return hipErrorInvalidValue;
@@ -458,21 +480,21 @@ hipError_t launch_tile(H2Args a, const Codebook& cb, hipStream_t s) {
   const int total = a.tiles_m * a.tiles_n;
   a.per_xcd = (total + XCDS - 1) / XCDS;
   static LdsLimit lds_limit;  // per instantiation: the limit is raised once per device
-  if (const hipError_t e = raise_lds_limit(lds_limit, reinterpret_cast<const void*>(&h2_kernel<EK, BITS, NPX, TW, UW, WM, WN>), lds_bytes);
+  if (const hipError_t e = raise_lds_limit(lds_limit, reinterpret_cast<const void*>(&h2_kernel<EK, BITS, NPX, TW, UW, WM, WN, NBUF>), lds_bytes);
       e != hipSuccess)
     return e;
-  hipLaunchKernelGGL((h2_kernel<EK, BITS, NPX, TW, UW, WM, WN>), dim3(a.per_xcd * XCDS), dim3(WM * WN * 64), lds_bytes, s, a, cb);
+  hipLaunchKernelGGL((h2_kernel<EK, BITS, NPX, TW, UW, WM, WN, NBUF>), dim3(a.per_xcd * XCDS), dim3(WM * WN * 64), lds_bytes, s, a, cb);
   return hipGetLastError();
 }
 
 template <int EK, int BITS, int NPX>
 hipError_t launch_any(const H2Args& a, const Codebook& cb, hipStream_t s) {
   switch (pick_tile(a.d, a.n)) {
-    case T256: return launch_tile<EK, BITS, NPX, 2, 4, 4, 2>(a, cb, s);
+    case T256: return launch_tile<EK, BITS, NPX, 2, 4, 4, 2, 2>(a, cb, s);
     case T128:  // indices only: eight wavefronts of 64 x 32 hide the decisions better than four of 64 x 64 (5 - 15 %)
-      if constexpr (EK == 0) return launch_tile<EK, BITS, NPX, 2, 1, 2, 4>(a, cb, s);
-      else return launch_tile<EK, BITS, NPX, 2, 2, 2, 2>(a, cb, s);
-    default: return launch_tile<EK, BITS, NPX, 1, 1, 2, 2>(a, cb, s);
+      if constexpr (EK == 0) return launch_tile<EK, BITS, NPX, 2, 1, 2, 4, 4>(a, cb, s);
+      else return launch_tile<EK, BITS, NPX, 2, 2, 2, 2, 4>(a, cb, s);
+    default: return launch_tile<EK, BITS, NPX, 1, 1, 2, 2, 4>(a, cb, s);
   }
 }
 
@@ -494,7 +516,7 @@ H2Args args_of(const H2Quant& q) {
   H2Args a;
   a.W = static_cast<const unsigned char*>(q.W);
   a.X = static_cast<const unsigned char*>(q.X);
-  a.fac = q.fac; a.esc = q.esc; a.words = q.words;
+  a.fac = q.fac; a.esc = q.esc; a.out = q.out; a.words = q.words;
   a.E = static_cast<unsigned char*>(q.E);
   a.part = q.part; a.gamma = q.gamma; a.n = q.n; a.d = q.d; a.part_tiles = q.part_tiles;
   a.tiles_m = a.tiles_n = a.per_xcd = 0;
@@ -565,6 +587,11 @@ hipError_t launch_h2_quant(int bits, const H2Quant& q, const Codebook& cb, hipSt
   const H2Args a = args_of(q);
   if (q.E != nullptr) return q.npx == 1 ? launch_bits<1, 1>(bits, a, cb, s) : launch_bits<1, 2>(bits, a, cb, s);
   return q.npx == 1 ? launch_bits<0, 1>(bits, a, cb, s) : launch_bits<0, 2>(bits, a, cb, s);
+}
+
+hipError_t launch_h2_store(const H2Quant& q, hipStream_t s) {
+  const Codebook none = {};
+  return launch_any<3, 0, 2>(args_of(q), none, s);
 }
 
 hipError_t launch_h2_sign(const H2Quant& q, hipStream_t s) {

@@ -83,6 +83,7 @@ struct H2Quant {
   int64_t n;
   const float* fac;      // [n] accumulator -> rotated coordinate of the (unit-normalised) vector
   const float* esc;      // [n] power of two for the residual's pieces
+  float* out;            // launch_h2_store: the products, [n][d]
   uint32_t* words;       // packed indices or signs
   void* E;               // residual pieces out (two), nullable
   float* part;           // [ceil(d / tile)][n] partial squared residual norms: out with E, in for the sketch
@@ -102,5 +103,6 @@ int h2_part_tiles(int d, int64_t n);                         // rows of H2Quant:
 int64_t h2_full_rows(int d, int64_t rows);                   // the largest useful pass over at most `rows` vectors
 hipError_t launch_h2_quant(int bits, const H2Quant& a, const Codebook& cb, hipStream_t s);
 hipError_t launch_h2_sign(const H2Quant& a, hipStream_t s);
+hipError_t launch_h2_store(const H2Quant& a, hipStream_t s);  // out = W X^T as it is
 
 }  // namespace tq
