@@ -9,6 +9,7 @@
 #include "tq_code_gemm.h"
 #include "tq_h2.h"
 #include "tq_score_i8.h"
+#include "tq_search.h"
 
 using namespace tq;
 
@@ -457,6 +458,9 @@ size_t tq_workspace_bytes(const tq_params* p, int64_t n, int64_t nq, int32_t top
   if (topk > 0) bytes += round_up((size_t)nq * (size_t)(n + 3) * sizeof(float), 256);  // scores when not returned
   // partial top-k lists of a few long rows: at most 4096 (score, index) pairs for each of at most 128 rows
   if (topk > 0) bytes += 2 * round_up((size_t)(nq < 128 ? nq : 128) * 4096 * sizeof(float), 256);
+  // candidates of a search by many queries, and their rotation
+  if (topk > 0 && nq > 0 && n > 0) bytes += search_workspace_bytes(p->d, n, nq, topk) + 256;
+  bytes += round_up((size_t)nq * d * 4, 256) + 2 * round_up((size_t)nq * 4, 256) + 256;
   return bytes + 256;
 }
 
@@ -574,6 +578,26 @@ tq_status tq_dequantize(const tq_params* p, const uint32_t* idx, const uint32_t*
 
 namespace {
 
+constexpr int64_t kMatvecQueries = 64;  // up to here queries are rotated by matrix-vector products
+
+// Pi q and S q = (S Pi^T) Pi q of many queries by the fp16 pieces of the images
+size_t rotate_workspace_bytes(int d, int64_t nq) { return round_up((size_t)nq * d * 4, 256) + 2 * round_up((size_t)nq * 4, 256); }
+bool rotate_h2(const tq_params* p, const float* q, int64_t ldq, int64_t nq, float* qr, float* qs, void* scratch, hipStream_t s) {
+  const int d = p->d;
+  const char* const img = h2_images(p);
+  char* const base = static_cast<char*>(scratch);
+  float* const fac = reinterpret_cast<float*>(base + round_up((size_t)nq * d * 4, 256));
+  for (int m = 0; m < (qs != nullptr ? 2 : 1); ++m) {
+    const float* const w_inv = h2_image_scale(img, d, m);
+    if (launch_h2_split(m == 0 ? q : qr, false, false, m == 0 ? ldq : d, nq, d, false, w_inv, base, nullptr, fac, nullptr, s) != hipSuccess) return false;
+    H2Quant a;
+    std::memset(&a, 0, sizeof(a));
+    a.W = h2_image(img, d, m); a.w_inv = w_inv; a.X = base; a.npx = 2; a.d = d; a.n = nq; a.fac = fac; a.out = m == 0 ? qr : qs;
+    if (launch_h2_store(a, s) != hipSuccess) return false;
+  }
+  return true;
+}
+
 // How one tq_score call is carried out and what scratch memory it takes.  tq_score follows it and
 // tq_score_workspace_bytes reports it, so the two cannot drift apart.
 struct ScorePlan {
@@ -586,7 +610,10 @@ struct ScorePlan {
   int topk_chunks;      // > 0: top-k over a score matrix of few long rows, this many chunks (partial lists) per row
   size_t part_bytes;    // one array [nq][ranges or topk_chunks][topk] (values; indices take the same again)
   bool prod;
-  size_t total() const {
+  size_t search_bytes;  // top-k of many queries by candidates (tq_search.hip); without room for it every score is looked at
+  size_t rotate_bytes;  // many queries rotated on the fp16 matrix cores; without room for it on the fp32 ones
+  size_t total() const { return needed() + round_up(search_bytes, 256) + round_up(rotate_bytes, 256); }
+  size_t needed() const {
     const size_t a = 256;
     size_t t = round_up(img_bytes, a) + (q_bytes ? round_up(q_bytes, a) * (prod ? 2 : 1) : 0) + round_up(scores_bytes, a) +
                2 * round_up(part_bytes, a);
@@ -606,6 +633,11 @@ ScorePlan plan_score(const tq_params* p, bool prod, int n_groups, int q_per_grou
     pl.topk_chunks = topk_chunks(nq, n_per_group, topk);
     if (pl.topk_chunks > 0) pl.part_bytes = (size_t)nq * pl.topk_chunks * topk * sizeof(float);
   }
+  const int64_t nq = (int64_t)n_groups * q_per_group;
+  if (pl.route == ScorePlan::R_BF3 && topk > 0 && !scores_given && n_groups == 1 &&
+      search_applicable(p->bits_mse, prod, p->d, n_per_group, q_per_group, topk, make_codebook(p)))
+    pl.search_bytes = search_workspace_bytes(p->d, n_per_group, nq, topk);
+  if (pl.q_bytes > 0 && nq > kMatvecQueries && h2_images(p) != nullptr && !fp32_mfma_only(p)) pl.rotate_bytes = rotate_workspace_bytes(p->d, nq);
   return pl;
 }
 
@@ -723,7 +755,10 @@ tq_status score_impl(const tq_params* p, Workspace ws, const float* q, int64_t l
       return TQ_ERR_HIP;
   } else {
     // queries into the rotated basis and the sketch basis: Pi q and S q
-    if (nq <= 64 && d <= 4096) {
+    void* const rot = pl.rotate_bytes > 0 && aligned16(h2_images(p)) ? ws.take(pl.rotate_bytes) : nullptr;
+    if (rot != nullptr && ldq % 4 == 0) {
+      if (!rotate_h2(p, q, ldq, nq, qr, qs, rot, s)) return TQ_ERR_HIP;
+    } else if (nq <= kMatvecQueries && d <= 4096) {
       if (launch_matvec_small(d, (int)nq, p->Pi, prod ? p->S : nullptr, q, ldq, qr, qs, s) != hipSuccess)
         return TQ_ERR_HIP;
     } else {
@@ -752,14 +787,24 @@ tq_status score_impl(const tq_params* p, Workspace ws, const float* q, int64_t l
                              d, n_groups, q_per_group, kappa_of(d), make_codebook(p), s) != hipSuccess)
         return TQ_ERR_HIP;
     } else if (pl.route == ScorePlan::R_BF3) {
+      // top-k alone: candidates from one piece of every factor, scored again; what follows then only serves the queries
+      // whose candidates were too many
+      const int32_t* flags = nullptr;
+      if (void* const space = pl.search_bytes > 0 ? ws.take(pl.search_bytes) : nullptr; space != nullptr) {
+        SearchArgs sa;
+        sa.bits = p->bits_mse; sa.prod = prod; sa.nq = (int)nq; sa.d = d; sa.topk = topk; sa.qr = qr; sa.qs = qs; sa.idx = idx; sa.qjl = qjl;
+        sa.gamma = gamma; sa.norm = norm; sa.n = n_per_group; sa.kappa = kappa_of(d); sa.topk_idx = topk_idx; sa.topk_val = topk_val;
+        if (launch_search(sa, make_codebook(p), space, &flags, s) != hipSuccess) return TQ_ERR_HIP;
+      }
       // many queries per code: dense contraction on the bf16 matrix cores, every fp32 factor as two bf16 pieces;
       // with top-k wanted the kernel keeps the k best pairs of every query itself and a small kernel joins them
       if (launch_score_bf3(p->bits_mse, prod, qr, qs, q_per_group, d, idx, qjl, gamma, norm, n_per_group, n_groups, scores,
                            ld_scores, false, kappa_of(d), make_codebook(p), s, pl.ranges > 0 ? topk : 0, part_val,
-                           part_idx) != hipSuccess)
+                           part_idx, flags) != hipSuccess)
         return TQ_ERR_HIP;
       if (pl.ranges > 0)
-        return from_hip(launch_topk_merge(part_val, part_idx, nq, pl.ranges, topk, topk_idx, topk_val, s));
+        return from_hip(launch_topk_merge(part_val, part_idx, nq, pl.ranges, topk, topk_idx, topk_val, s, flags));
+      if (flags != nullptr) return from_hip(launch_topk(scores, nq, n_per_group, ld_scores, topk, topk_idx, topk_val, s, 0, nullptr, nullptr, flags));
     } else if (n_per_group > 0) {
       GemmArgs a;
       std::memset(&a, 0, sizeof(a));
@@ -827,15 +872,28 @@ tq_status tq_score(const tq_params* p, const float* q, int64_t ldq, int32_t n_gr
                     idx, qjl, gamma, norm, n_per_group, scores, lds, topk, topk_idx, topk_val, stream);
 }
 
-size_t tq_score_workspace_bytes(const tq_params* p, int32_t n_groups, int32_t q_per_group, int64_t n_per_group,
-                                int32_t prod, int32_t scores_given, int32_t topk) {
+}  // extern "C"
+
+namespace {
+// most: with everything a call makes use of; otherwise what it cannot do without
+size_t score_workspace(const tq_params* p, int32_t n_groups, int32_t q_per_group, int64_t n_per_group, int32_t prod, int32_t scores_given,
+                       int32_t topk, bool most) {
   if (p == nullptr || p->d <= 0 || p->bits_mse < 0 || p->bits_mse > 4 || n_groups < 0 || q_per_group < 0 || n_per_group < 0 ||
       topk < 0 || topk > 64 || p->centroids == nullptr || (p->bits_mse > 0 && p->bounds == nullptr))
     return 0;
   // codes that are not 16-byte aligned can take a route with the smaller need; report the larger
-  const size_t a = plan_score(p, prod != 0, n_groups, q_per_group, n_per_group, scores_given != 0, topk, true).total();
-  const size_t b = plan_score(p, prod != 0, n_groups, q_per_group, n_per_group, scores_given != 0, topk, false).total();
+  const ScorePlan x = plan_score(p, prod != 0, n_groups, q_per_group, n_per_group, scores_given != 0, topk, true);
+  const ScorePlan y = plan_score(p, prod != 0, n_groups, q_per_group, n_per_group, scores_given != 0, topk, false);
+  const size_t a = most ? x.total() : x.needed(), b = most ? y.total() : y.needed();
   return a > b ? a : b;
+}
+}  // namespace
+
+extern "C" {
+
+size_t tq_score_workspace_bytes(const tq_params* p, int32_t n_groups, int32_t q_per_group, int64_t n_per_group,
+                                int32_t prod, int32_t scores_given, int32_t topk) {
+  return score_workspace(p, n_groups, q_per_group, n_per_group, prod, scores_given, topk, true);
 }
 
 size_t tq_score_static_scratch_bytes(void) { return kStaticScratchBytes; }
@@ -846,7 +904,7 @@ tq_status tq_score_static(const tq_params* p, const float* q, int64_t ldq, int32
                           int32_t* topk_idx, float* topk_val, void* stream) {
   if (p == nullptr || n_groups < 0 || q_per_group < 0 || n_per_group < 0) return TQ_ERR_INVALID_ARG;
   // the whole need of the call must fit the static array
-  const size_t need = tq_score_workspace_bytes(p, n_groups, q_per_group, n_per_group, qjl != nullptr, scores != nullptr, topk);
+  const size_t need = score_workspace(p, n_groups, q_per_group, n_per_group, qjl != nullptr, scores != nullptr, topk, false);
   if (need == 0) return TQ_ERR_INVALID_ARG;
   if (need > kStaticScratchBytes) return TQ_ERR_WORKSPACE;
   void* base = nullptr;

@@ -20,6 +20,7 @@ struct CodeTable {
 };
 bool code_gemm_serves(int bits, const Codebook& cb);  // symmetric tables of up to 4 bits
 CodeTable make_code_table(int bits, const Codebook& cb);
+float code_table_error(int bits, const Codebook& cb);  // largest relative error of a leading piece (2 bits or more)
 
 // Image of a d x d matrix's transpose in the order above: rows of two fp16 pieces, h2_image_bytes(d, d) bytes
 hipError_t launch_code_image(const float* W, int d, void* image, float* w_inv, hipStream_t s);
@@ -28,5 +29,26 @@ hipError_t launch_code_image(const float* W, int d, void* image, float* w_inv, h
 hipError_t launch_code_dequant(int bits, bool prod, const void* pit_image, const float* pit_inv, const void* st_image, const float* st_inv,
                                int d, const uint32_t* idx, const uint32_t* qjl, const float* gamma, const float* norm, int64_t n,
                                float* out, int64_t ldo, float kappa, const Codebook& cb, hipStream_t s);
+
+// The first pass of a search: scores of all codes from ONE piece of every factor, each within
+//     eps = nu (e1 + kappa gamma e2)
+// of the exact one.  sample != NULL: score - eps of codes 0, code_step, 2 code_step, ... (n of them) to sample[query][ld_sample].
+// Otherwise every (score + eps, code) with score + eps >= bar[query] is appended to the query's list; count may pass cap.
+struct CodeSearch {
+  const void* r_pieces;  // [nq][d] fp16, the contraction's order (code_position): Pi q scaled
+  const void* s_pieces;  // S q scaled
+  int nq;
+  const float *inv, *e1, *e2, *bar;
+  int bar_step;          // floats between the bars of consecutive queries
+  float s_rel;           // scale of r_pieces over that of s_pieces (the same for all queries)
+  float* sample;
+  int64_t ld_sample;
+  float* list_u;
+  int32_t* list_i;
+  int32_t* count;
+  int cap;
+};
+hipError_t launch_code_search(int bits, bool prod, const CodeSearch& q, int d, const uint32_t* idx, const uint32_t* qjl, const float* gamma,
+                              const float* norm, int64_t n, int64_t code_step, float kappa, const Codebook& cb, hipStream_t s);
 
 }  // namespace tq

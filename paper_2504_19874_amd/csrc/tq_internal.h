@@ -169,14 +169,16 @@ bool score_bf3_applicable(int bits, bool prod, int d, int64_t n, int n_groups, i
 hipError_t launch_score_bf3(int bits, bool prod, const float* qr, const float* qs, int q_per_group, int d,
                             const uint32_t* idx, const uint32_t* qjl, const float* gamma, const float* norm, int64_t n,
                             int n_groups, float* out, int64_t ldo, bool transposed, float kappa, const Codebook& cb,
-                            hipStream_t s, int topk = 0, float* part_val = nullptr, int32_t* part_idx = nullptr);
+                            hipStream_t s, int topk = 0, float* part_val = nullptr, int32_t* part_idx = nullptr,
+                            const int32_t* flags = nullptr);
+// flags (these three): a device word per query, only queries with a non-zero one are worked on (blocks of them here).
 // transposed: out[code][query] (queries = rows of Pi^T: dequantisation).  topk in 1..16 (not transposed): the
 // kernel also keeps the topk best (score, index) pairs of every query per range of code tiles and writes them
 // to part_val / part_idx [n_groups * q_per_group][ranges][topk], ranges = score_bf3_topk_ranges(...); out may
 // then be NULL.  launch_topk_merge joins the ranges (descending, equal scores by lower index, -1 past n).
 int score_bf3_topk_ranges(int bits, bool prod, int64_t n, int n_groups, int q_per_group, int topk);
 hipError_t launch_topk_merge(const float* part_val, const int32_t* part_idx, int64_t rows, int ranges, int k,
-                             int32_t* out_idx, float* out_val, hipStream_t s);
+                             int32_t* out_idx, float* out_val, hipStream_t s, const int32_t* flags = nullptr);
 
 // codec stages
 hipError_t launch_stage_pack(const Codebook& cb, int d, const float* y, int64_t n, uint32_t* idx,
@@ -195,6 +197,6 @@ hipError_t launch_transpose(int d, const float* in, float* out, hipStream_t stre
 int topk_chunks(int64_t rows, int64_t n, int k);
 hipError_t launch_topk(const float* scores, int64_t rows, int64_t n, int64_t ld, int k,
                        int32_t* out_idx, float* out_val, hipStream_t stream, int chunks = 0, float* part_val = nullptr,
-                       int32_t* part_idx = nullptr);
+                       int32_t* part_idx = nullptr, const int32_t* flags = nullptr);
 
 }  // namespace tq

@@ -90,6 +90,7 @@ struct Bf3Args {
   int qblocks;       // query blocks per group
   int tiles_n;       // code tiles per group
   int xcd_split;     // fused top-k: ranges per XCD (0: no split by XCD); plain kernel: 1 = query block fastest
+  const int32_t* flags;  // nullable: query blocks without a flagged query are skipped
   float* part_val;   // [groups * M][ranges][topk]
   int32_t* part_idx;
 };
@@ -160,6 +161,11 @@ __global__ __launch_bounds__(512) void score_bf3_kernel(const Bf3Args a) {
       tile_begin = blockIdx.x;
     }
     tile_end = tile_begin + 1;
+  }
+  if (a.flags != nullptr) {
+    int any = 0;
+    for (int m = m0 + tid; m < m0 + TM && m < a.M; m += 512) any |= a.flags[(int64_t)group * a.M + m];
+    if (__syncthreads_or(any) == 0) return;
   }
   // fused top-k state, behind the staging buffers and the piece table
   // [TM][RS] (score bits, index): slots [0, k) sorted, best first; slots [k, RS) appended since the last ranking
@@ -650,11 +656,11 @@ int score_bf3_topk_ranges(int bits, bool prod, int64_t n, int n_groups, int q_pe
 hipError_t launch_score_bf3(int bits, bool prod, const float* qr, const float* qs, int q_per_group, int d,
                             const uint32_t* idx, const uint32_t* qjl, const float* gamma, const float* norm, int64_t n,
                             int n_groups, float* out, int64_t ldo, bool transposed, float kappa, const Codebook& cb,
-                            hipStream_t s, int topk, float* part_val, int32_t* part_idx) {
+                            hipStream_t s, int topk, float* part_val, int32_t* part_idx, const int32_t* flags) {
   Bf3Args a;
   std::memset(&a, 0, sizeof(a));
   if (topk > 0 && (transposed || topk > KL || part_val == nullptr || part_idx == nullptr)) return hipErrorInvalidValue;
-  a.topk = topk; a.part_val = part_val; a.part_idx = part_idx;
+  a.flags = flags; a.topk = topk; a.part_val = part_val; a.part_idx = part_idx;
   a.transposed = transposed ? 1 : 0;
   a.qr = qr; a.qs = qs; a.M = q_per_group; a.d = d; a.idx = idx; a.qjl = qjl; a.gamma = gamma; a.norm = norm;
   a.n = n; a.out = out; a.ldo = ldo; a.kappa = kappa; a.cb = cb;

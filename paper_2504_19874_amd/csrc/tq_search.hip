@@ -1,0 +1,391 @@
+// Nearest-neighbour search by many queries: the k best codes of each, without a score matrix and at a third of the matrix
+// work of evaluating every score to full precision.
+//
+// 1. prepare     every query's rotated coordinates as ONE fp16 piece, and a bound of what that leaves out: with the codes'
+//                centroids as one piece too, a score is off by at most eps = nu (e1 + kappa gamma e2),
+//                  e1 = (|q - q^| + r |q^|) sqrt(d) max |c|,   e2 = (|s - s^| + a |s|) sqrt(d)
+//                (Cauchy-Schwarz; r: largest relative error of a centroid's piece, plus a for the fp32 sums).
+// 2. sample      score - eps of some thousand codes, evenly spaced; the k-th best of a query is a bar that its k-th best
+//                code reaches for certain (topk_kernel).
+// 3. find        every score once with one matrix instruction per product instead of three; the codes whose
+//                score + eps reaches the bar go to the query's list (expected: a thousand).
+// 4. select      the k-th best of score - eps over the list is a better bar, which little more than k candidates pass;
+//                those are scored with the pieces, products and order of tq_score_bf3.hip (the same bits), and ranked.
+// A list that overflows (thousands of equal scores) flags its query: the caller runs the kernels that look at everything,
+// which skip blocks of queries without a flag.
+//
+// 1000 queries, 10^6 codes, k = 10, d = 1536, 4 bits: SEARCH_A; FIND_A for the find kernel.
+#include <cmath>
+
+#include "tq_bf3.h"
+#include "tq_code_gemm.h"
+#include "tq_search.h"
+#include "tq_select.h"
+
+namespace tq {
+namespace {
+
+constexpr int CAP = 4096;  // candidates per query
+
+struct SearchFactors {
+  float c_rel;    // largest relative error of a centroid's leading piece
+  float c_norm;   // sqrt(d) max |c|
+  float acc_rel;  // fp32 sums of d products
+  float sqrt_d;
+  float s_rel;    // scale of the rotated queries' pieces over that of the sketched ones
+};
+
+// grid nq, 256 threads
+__global__ __launch_bounds__(256) void search_prepare_kernel(const int d, const float* __restrict__ qr, const float* __restrict__ qs,
+                                                             const SearchFactors f, uint32_t* __restrict__ r_pieces,
+                                                             uint32_t* __restrict__ s_pieces, float* __restrict__ inv, float* __restrict__ e1,
+                                                             float* __restrict__ e2, int32_t* __restrict__ count, int32_t* __restrict__ flags) {
+  __shared__ float red[4][4];
+  __shared__ float red_mx[4];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int64_t q = blockIdx.x;
+  const float* const r = qr != nullptr ? qr + q * d : nullptr;
+  const float* const z = qs != nullptr ? qs + q * d : nullptr;
+  const float s_fac = 1.f / f.s_rel;
+  float mx = 0.f;
+  for (int k = tid; k < d; k += 256) {
+    if (r != nullptr) mx = fmaxf(mx, fabsf(r[k]));
+    if (z != nullptr) mx = fmaxf(mx, fabsf(z[k]) * s_fac);
+  }
+#pragma unroll
+  for (int off = 32; off >= 1; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off));
+  if (lane == 0) red_mx[tid >> 6] = mx;
+  __syncthreads();
+  mx = fmaxf(fmaxf(red_mx[0], red_mx[1]), fmaxf(red_mx[2], red_mx[3]));
+  float s, si;
+  h2_scale(__float_as_uint(mx), s, si);
+  float sum[4] = {0.f, 0.f, 0.f, 0.f};  // |q|^2, |q - q^|^2 of the two
+  for (int u = tid; u < d / 4; u += 256) {
+    const int g = u >> 3, k = u & 7;
+    auto pieces = [&](const float* v, float scale, float back, float& n2, float& d2) {
+      const float w[4] = {v[32 * g + k], v[32 * g + k + 16], v[32 * g + k + 8], v[32 * g + k + 24]};
+      uint32_t o[2];
+#pragma unroll
+      for (int e = 0; e < 2; ++e) {
+        const f16x2 p = {(_Float16)(w[2 * e] * scale), (_Float16)(w[2 * e + 1] * scale)};
+        const float a = w[2 * e] - (float)p[0] * back, b = w[2 * e + 1] - (float)p[1] * back;
+        n2 = fmaf(w[2 * e], w[2 * e], fmaf(w[2 * e + 1], w[2 * e + 1], n2));
+        d2 = fmaf(a, a, fmaf(b, b, d2));
+        o[e] = h2_bits(p);
+      }
+      return make_uint2(o[0], o[1]);
+    };
+    if (r != nullptr) *reinterpret_cast<uint2*>(r_pieces + (q * d) / 2 + g * 16 + k * 2) = pieces(r, s, si, sum[0], sum[1]);
+    if (z != nullptr) *reinterpret_cast<uint2*>(s_pieces + (q * d) / 2 + g * 16 + k * 2) = pieces(z, s * s_fac, si * f.s_rel, sum[2], sum[3]);
+  }
+#pragma unroll
+  for (int off = 32; off >= 1; off >>= 1)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) sum[i] += __shfl_xor(sum[i], off);
+  if (lane == 0)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) red[tid >> 6][i] = sum[i];
+  __syncthreads();
+  if (tid == 0) {
+    float t[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) t[i] = sqrtf((red[0][i] + red[1][i]) + (red[2][i] + red[3][i])) * 1.001f;
+    inv[q] = si;
+    e1[q] = 1.01f * (t[1] + (f.c_rel + f.acc_rel) * (t[0] + t[1])) * f.c_norm;
+    e2[q] = 1.01f * (t[3] + f.acc_rel * t[2]) * f.sqrt_d;
+    count[q] = 0;
+    flags[q] = 0;
+  }
+}
+
+struct SelectArgs {
+  const float *qr, *qs, *e1, *e2;
+  int d, topk;
+  const uint32_t *idx, *qjl;
+  const float *gamma, *norm;
+  float kappa;
+  const float* list_u;
+  const int32_t *list_i, *count;
+  int32_t* flags;
+  int32_t* out_idx;
+  float* out_val;
+  Codebook cb;
+};
+
+template <int BITS, bool PROD>
+__global__ __launch_bounds__(256) void search_select_kernel(const SelectArgs a) {
+  constexpr int SEGS = (BITS > 0 ? 1 : 0) + (PROD ? 1 : 0);
+  constexpr int NB = BITS > 0 ? BITS : 1;
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  int* const cand = reinterpret_cast<int*>(smem);                                // [CAP] codes that are scored again
+  float* const score = reinterpret_cast<float*>(cand + CAP);                     // [CAP]
+  unsigned short* const qp = reinterpret_cast<unsigned short*>(score + CAP);     // [segment][2 pieces][d]
+  __shared__ __attribute__((aligned(16))) uint32_t keys[256];
+  __shared__ uint32_t bar_s;
+  __shared__ int n_s;
+  __shared__ uint2 table_s[16];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int64_t q = blockIdx.x;
+  const int d = a.d, k = a.topk;
+  const int total = a.count[q];
+  if (total > CAP) {
+    if (tid == 0) a.flags[q] = 1;
+    return;
+  }
+  if (tid < 16) {
+    uint32_t p1, p2, p3;
+    split3(a.cb.c[tid], p1, p2, p3);
+    table_s[tid] = make_uint2(p1 | (p2 << 16), p3);
+  }
+  if (tid == 0) n_s = 0;
+  // the query's pieces, as the scoring kernel stages them
+  for (int e = tid; e < d / 4; e += 256) {
+    int seg = 0;
+#pragma unroll
+    for (int m = 0; m < 2; ++m) {
+      if (m == 0 ? BITS == 0 : !PROD) continue;
+      const f32x4 v = *reinterpret_cast<const f32x4*>((m == 0 ? a.qr : a.qs) + q * d + 4 * e);
+      uint32_t lo[3], hi[3];
+      split3_pair(f32x2{v[0], v[1]}, lo[0], lo[1], lo[2]);
+      split3_pair(f32x2{v[2], v[3]}, hi[0], hi[1], hi[2]);
+#pragma unroll
+      for (int pc = 0; pc < 2; ++pc) *reinterpret_cast<uint2*>(qp + (seg * 2 + pc) * d + 4 * e) = make_uint2(lo[pc], hi[pc]);
+      ++seg;
+    }
+  }
+  // candidates: score + eps from the list, eps again from the code's scalars
+  constexpr int N = CAP / 256;
+  const float e1 = a.e1[q], e2 = a.e2[q];
+  float mx = -__builtin_inff();
+  float top[N];
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    top[i] = __builtin_nanf("");
+    if (i * 256 < total) {  // uniform
+      const int c = i * 256 + tid;
+      if (c < total) {
+        const int64_t row = a.list_i[q * CAP + c];
+        const float nu = a.norm != nullptr ? a.norm[row] : 1.f;
+        float eps = nu * e1;
+        if (PROD) eps = fmaf(nu * (a.kappa * a.gamma[row]), e2, eps);
+        top[i] = a.list_u[q * CAP + c];
+        mx = fmaxf(mx, fmaf(-2.f, eps, top[i]));
+      }
+    }
+  }
+  const float bar = kth_of_maxima(mx, k, keys, &bar_s, tid);
+  uint32_t pass = 0u;
+#pragma unroll
+  for (int i = N - 1; i >= 0; --i) pass = pass + pass + (top[i] >= bar ? 1u : 0u);
+  while (pass != 0u) {
+    const int i = __builtin_ctz(pass);
+    pass &= pass - 1u;
+    cand[atomicAdd(&n_s, 1)] = a.list_i[q * CAP + i * 256 + tid];
+  }
+  __syncthreads();
+  const int n = n_s;
+
+  // scores as tq_score_bf3.hip makes them: 32 candidates of a wavefront are the columns, every row is the query
+  const int gw = d >> 5, h = lane >> 5;
+  for (int b = wave; b * 32 < n; b += 4) {
+    const int s = b * 32 + (lane & 31);
+    const int64_t row = cand[s < n ? s : n - 1];
+    const uint32_t* const wi = a.idx + row * ((int64_t)gw * BITS);
+    const uint32_t* const wz = PROD ? a.qjl + row * gw : nullptr;
+    floatx16 acc1, acc2;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc1[r] = acc2[r] = 0.f;
+    uint32_t w[NB], z = 0u, wn[NB], zn = 0u;
+    auto load = [&](int g) {
+      const int gg = g < gw ? g : gw - 1;
+#pragma unroll
+      for (int pl = 0; pl < BITS; ++pl) wn[pl] = wi[gg * BITS + pl];
+      if (PROD) zn = wz[gg];
+    };
+    auto signs = [&](uint32_t bits) -> bf16x8 {
+      uint32_t v[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[e] = 0xBF80BF80u ^ (((bits >> (2 * e)) & 1u) << 15) ^ (((bits >> (2 * e + 1)) & 1u) << 31);
+      const u32x4 o = u32x4{v[0], v[1], v[2], v[3]};
+      return *reinterpret_cast<const bf16x8*>(&o);
+    };
+    load(0);
+    for (int g = 0; g < gw; ++g) {
+#pragma unroll
+      for (int pl = 0; pl < BITS; ++pl) w[pl] = wn[pl];
+      z = zn;
+      load(g + 1);
+#pragma unroll
+      for (int half = 0; half < 2; ++half) {
+        const int off = 16 * half + 8 * h, at = 32 * g + off;
+        auto piece = [&](int seg, int pc) { return *reinterpret_cast<const bf16x8*>(qp + (seg * 2 + pc) * d + at); };
+        if (BITS == 1) {
+          const bf16x8 f = signs(w[0] >> off);
+          acc1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(piece(0, 1), f, acc1, 0, 0, 0);
+          acc1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(piece(0, 0), f, acc1, 0, 0, 0);
+        } else if (BITS > 1) {
+          uint32_t lv[2];
+#pragma unroll
+          for (int e = 0; e < 2; ++e) {
+            lv[e] = 0u;
+#pragma unroll
+            for (int pl = 0; pl < BITS; ++pl) lv[e] |= ((((w[pl] >> (off + 4 * e)) & 0xFu) * 0x00204081u) & 0x01010101u) << pl;
+          }
+          u32x4 v1, v2;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const uint2 lo = table_s[(lv[e >> 1] >> (16 * (e & 1))) & 0xFFu], hi = table_s[(lv[e >> 1] >> (16 * (e & 1) + 8)) & 0xFFu];
+            v1[e] = __builtin_amdgcn_perm(hi.x, lo.x, 0x05040100u);
+            v2[e] = __builtin_amdgcn_perm(hi.x, lo.x, 0x07060302u);
+          }
+          const bf16x8 f1 = *reinterpret_cast<const bf16x8*>(&v1), f2 = *reinterpret_cast<const bf16x8*>(&v2);
+          const bf16x8 a1 = piece(0, 0);
+          acc1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(piece(0, 1), f1, acc1, 0, 0, 0);
+          acc1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a1, f2, acc1, 0, 0, 0);
+          acc1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a1, f1, acc1, 0, 0, 0);
+        }
+        if (PROD) {
+          const bf16x8 f = signs(z >> off);
+          acc2 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(piece(SEGS - 1, 1), f, acc2, 0, 0, 0);
+          acc2 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(piece(SEGS - 1, 0), f, acc2, 0, 0, 0);
+        }
+      }
+    }
+    const float c1 = BITS == 1 ? a.cb.c[1] : 1.f;
+    const float nu = a.norm != nullptr ? a.norm[row] : 1.f;
+    const float kg = PROD ? a.kappa * a.gamma[row] : 0.f;
+    if (h == 0 && s < n) score[s] = nu * fmaf(kg, PROD ? acc2[0] : 0.f, c1 * acc1[0]);
+  }
+  __syncthreads();
+  for (int c = tid; c < n; c += 256) {
+    const float cv = score[c];
+    const int ci = cand[c];
+    int rank = cv == cv ? 0 : k;  // a NaN is not returned
+#pragma unroll 4
+    for (int o = 0; o < n; ++o) rank += better(score[o], cand[o], cv, ci) ? 1 : 0;
+    if (rank < k) {
+      a.out_idx[q * k + rank] = ci;
+      if (a.out_val != nullptr) a.out_val[q * k + rank] = cv;
+    }
+  }
+  // fewer candidates than wanted: the rest of the list says so (NaN scores leave gaps only behind real ones)
+  if (n < k) {
+    int real = 0;
+    for (int o = 0; o < n; ++o) real += score[o] == score[o] ? 1 : 0;
+    if (tid >= real && tid < k) {
+      a.out_idx[q * k + tid] = -1;
+      if (a.out_val != nullptr) a.out_val[q * k + tid] = -__builtin_inff();
+    }
+  }
+}
+
+size_t align256(size_t v) { return (v + 255) / 256 * 256; }
+
+// codes of the sample: with m times as many codes in all, about k m of them reach the k-th best of the sample.  The lists
+// are sized for four times the thousand that this aims at (the number is a sum of k exponentials: for k >= 8 more than four
+// times its mean does not happen; below, the sample is that for k = 8).
+int64_t sample_codes(int64_t n, int topk) {
+  const int64_t k = topk < 8 ? 8 : topk;
+  int64_t m = n * k / (CAP / 4);
+  if (m < 4096) m = 4096;
+  return m < n ? m : n;
+}
+
+struct SearchSpace {
+  size_t r, s, sample, list_u, list_i, top_v, top_i, inv, e1, e2, count, flags, total;
+  SearchSpace(int d, int64_t n, int64_t nq, int topk) {
+    size_t at = 0;
+    auto take = [&](size_t bytes) {
+      const size_t o = at;
+      at += align256(bytes);
+      return o;
+    };
+    r = take((size_t)nq * d * 2);
+    s = take((size_t)nq * d * 2);
+    sample = take((size_t)nq * ((sample_codes(n, topk) + 3) / 4 * 4) * 4);
+    list_u = take((size_t)nq * CAP * 4);
+    list_i = take((size_t)nq * CAP * 4);
+    top_v = take((size_t)nq * topk * 4);
+    top_i = take((size_t)nq * topk * 4);
+    inv = take((size_t)nq * 4);
+    e1 = take((size_t)nq * 4);
+    e2 = take((size_t)nq * 4);
+    count = take((size_t)nq * 4);
+    flags = take((size_t)nq * 4);
+    total = at;
+  }
+};
+
+template <int BITS, bool PROD>
+hipError_t launch_select(const SelectArgs& a, int nq, hipStream_t s) {
+  const int lds = CAP * 8 + ((BITS > 0 ? 1 : 0) + (PROD ? 1 : 0)) * 2 * a.d * 2;
+  static LdsLimit lds_limit;  // per instantiation: the limit is raised once per device
+  if (const hipError_t e = raise_lds_limit(lds_limit, reinterpret_cast<const void*>(&search_select_kernel<BITS, PROD>), 80 * 1024); e != hipSuccess)
+    return e;
+  hipLaunchKernelGGL((search_select_kernel<BITS, PROD>), dim3((unsigned)nq), dim3(256), lds, s, a);
+  return hipGetLastError();
+}
+
+}  // namespace
+
+bool search_applicable(int bits, bool prod, int d, int64_t n, int nq, int topk, const Codebook& cb) {
+  return topk >= 1 && topk <= 64 && nq > 0 && n >= 8192 && n <= 0x7fffffff && d % 32 == 0 && d <= 4096 && (bits > 0 || prod) && code_gemm_serves(bits, cb);
+}
+
+size_t search_workspace_bytes(int d, int64_t n, int64_t nq, int topk) { return SearchSpace(d, n, nq, topk).total; }
+
+hipError_t launch_search(const SearchArgs& a, const Codebook& cb, void* workspace, const int32_t** flags, hipStream_t s) {
+  const SearchSpace sp(a.d, a.n, a.nq, a.topk);
+  char* const base = static_cast<char*>(workspace);
+  auto at = [&](size_t o) { return static_cast<void*>(base + o); };
+  *flags = static_cast<const int32_t*>(at(sp.flags));
+  const float sqrt_d = std::sqrt((float)a.d);
+  SearchFactors f;
+  f.c_rel = f.c_norm = 0.f;
+  for (int i = 0; i < (1 << a.bits); ++i) {
+    const float c = std::fabs(cb.c[i]);
+    f.c_norm = std::fmax(f.c_norm, c * sqrt_d);
+  }
+  if (a.bits > 1) f.c_rel = code_table_error(a.bits, cb);
+  f.acc_rel = (float)a.d * 1.5e-8f;
+  f.sqrt_d = sqrt_d;
+  f.s_rel = std::exp2(std::round(std::log2(sqrt_d)));
+  hipLaunchKernelGGL(search_prepare_kernel, dim3((unsigned)a.nq), dim3(256), 0, s, a.d, a.bits > 0 ? a.qr : nullptr, a.prod ? a.qs : nullptr, f,
+                     static_cast<uint32_t*>(at(sp.r)), static_cast<uint32_t*>(at(sp.s)), static_cast<float*>(at(sp.inv)),
+                     static_cast<float*>(at(sp.e1)), static_cast<float*>(at(sp.e2)), static_cast<int32_t*>(at(sp.count)),
+                     static_cast<int32_t*>(at(sp.flags)));
+  if (const hipError_t e = hipGetLastError(); e != hipSuccess) return e;
+
+  const int64_t m = sample_codes(a.n, a.topk), ld = (m + 3) / 4 * 4;
+  CodeSearch c;
+  c.r_pieces = at(sp.r); c.s_pieces = at(sp.s); c.nq = a.nq;
+  c.inv = static_cast<const float*>(at(sp.inv)); c.e1 = static_cast<const float*>(at(sp.e1)); c.e2 = static_cast<const float*>(at(sp.e2));
+  c.bar = static_cast<const float*>(at(sp.top_v)) + a.topk - 1; c.bar_step = a.topk; c.s_rel = f.s_rel;
+  c.sample = static_cast<float*>(at(sp.sample)); c.ld_sample = ld;
+  c.list_u = nullptr; c.list_i = static_cast<int32_t*>(at(sp.list_i)); c.count = static_cast<int32_t*>(at(sp.count)); c.cap = CAP;
+  if (const hipError_t e = launch_code_search(a.bits, a.prod, c, a.d, a.idx, a.qjl, a.gamma, a.norm, m, a.n / m, a.kappa, cb, s); e != hipSuccess) return e;
+  if (const hipError_t e = launch_topk(c.sample, a.nq, m, ld, a.topk, static_cast<int32_t*>(at(sp.top_i)), static_cast<float*>(at(sp.top_v)), s);
+      e != hipSuccess)
+    return e;
+  c.list_u = static_cast<float*>(at(sp.list_u));
+  if (const hipError_t e = launch_code_search(a.bits, a.prod, c, a.d, a.idx, a.qjl, a.gamma, a.norm, a.n, 1, a.kappa, cb, s); e != hipSuccess) return e;
+
+  SelectArgs g;
+  g.qr = a.qr; g.qs = a.qs; g.e1 = c.e1; g.e2 = c.e2; g.d = a.d; g.topk = a.topk; g.idx = a.idx; g.qjl = a.qjl; g.gamma = a.gamma; g.norm = a.norm;
+  g.kappa = a.kappa; g.list_u = c.list_u; g.list_i = c.list_i; g.count = c.count; g.flags = static_cast<int32_t*>(at(sp.flags));
+  g.out_idx = a.topk_idx; g.out_val = a.topk_val; g.cb = cb;
+  switch (a.bits * 2 + (a.prod ? 1 : 0)) {
+    case 1: return launch_select<0, true>(g, a.nq, s);
+    case 2: return launch_select<1, false>(g, a.nq, s);
+    case 3: return launch_select<1, true>(g, a.nq, s);
+    case 4: return launch_select<2, false>(g, a.nq, s);
+    case 5: return launch_select<2, true>(g, a.nq, s);
+    case 6: return launch_select<3, false>(g, a.nq, s);
+    case 7: return launch_select<3, true>(g, a.nq, s);
+    case 8: return launch_select<4, false>(g, a.nq, s);
+    case 9: return launch_select<4, true>(g, a.nq, s);
+    default: return hipErrorInvalidValue;
+  }
+}
+
+}  // namespace tq

@@ -9,7 +9,7 @@
 // workgroup each, whose lists topk_merge_kernel joins in the same way.
 // (Before: a sorted list per thread, k rounds of arg-max to join them.  4 rows of 10^6 scores, k = 10: 35 + 30 us for the
 // chunks and the merge, 11.5 + 7.5 here; 16 rows, k = 64: 1.2 ms in all, 70 us here.)
-#include "tq_internal.h"
+#include "tq_select.h"
 
 namespace tq {
 namespace {
@@ -17,16 +17,6 @@ namespace {
 constexpr int SEG = 8192;              // scores per segment
 constexpr int PER = SEG / 256;         // per thread
 constexpr int LIST = SEG + 64;         // all of a segment may pass (equal scores), and the k best before it
-
-__device__ __forceinline__ bool better(float va, int ia, float vb, int ib) {
-  return va > vb || (va == vb && ia < ib);
-}
-
-// order-preserving map to the unsigned integers
-__device__ __forceinline__ uint32_t ordered(float f) {
-  const uint32_t b = __float_as_uint(f);
-  return b & 0x80000000u ? ~b : b | 0x80000000u;
-}
 
 struct TopkLds {
   float v[LIST];
@@ -49,21 +39,7 @@ __device__ int take_segment(TopkLds& s, const float (&v)[N], Pair pair, int k, i
     float mx = -__builtin_inff();
 #pragma unroll
     for (int e = 0; e < N; ++e) mx = fmaxf(mx, v[e]);  // ignores NaN
-    const uint32_t key = ordered(mx);
-    s.mx[tid] = key;
-    if (tid == 0) s.bar = 0xffffffffu;
-    __syncthreads();
-    int above = 0;
-    const uint4* m4 = reinterpret_cast<const uint4*>(s.mx);
-#pragma unroll 8
-    for (int t = 0; t < 64; ++t) {
-      const uint4 o = m4[t];
-      above += (o.x > key ? 1 : 0) + (o.y > key ? 1 : 0) + (o.z > key ? 1 : 0) + (o.w > key ? 1 : 0);
-    }
-    if (above < k) atomicMin(&s.bar, key);  // the smallest of the k largest
-    __syncthreads();
-    const uint32_t b = s.bar;
-    bar = __uint_as_float(b & 0x80000000u ? b & 0x7fffffffu : ~b);
+    bar = kth_of_maxima(mx, k, s.mx, &s.bar, tid);
   } else {
     bar = s.best_v[k - 1];
   }
@@ -112,7 +88,8 @@ __device__ __forceinline__ void write_best(const TopkLds& s, int kept, int k, in
 // 4, so a chunk is as aligned as the row) and writes k (value, index) pairs, -inf / INT_MAX where it has fewer
 __global__ __launch_bounds__(256) void topk_kernel(const float* __restrict__ scores, const int64_t n_row, const int64_t ld, const int k,
                                                    const int vec4, int32_t* __restrict__ out_idx, float* __restrict__ out_val,
-                                                   const int64_t chunk_len) {
+                                                   const int64_t chunk_len, const int32_t* __restrict__ flags) {
+  if (flags != nullptr && flags[blockIdx.x] == 0) return;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
   TopkLds& s = *reinterpret_cast<TopkLds*>(smem_raw);
   const int tid = threadIdx.x;
@@ -155,7 +132,8 @@ __global__ __launch_bounds__(256) void topk_kernel(const float* __restrict__ sco
 // One workgroup per row: the k best of its cands <= 4096 (score, index) pairs (index INT_MAX: no pair).
 __global__ __launch_bounds__(256) void topk_merge_kernel(const float* __restrict__ part_val, const int32_t* __restrict__ part_idx,
                                                          const int cands, const int k, int32_t* __restrict__ out_idx,
-                                                         float* __restrict__ out_val) {
+                                                         float* __restrict__ out_val, const int32_t* __restrict__ flags) {
+  if (flags != nullptr && flags[blockIdx.x] == 0) return;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
   TopkLds& s = *reinterpret_cast<TopkLds*>(smem_raw);
   const int tid = threadIdx.x;
@@ -193,7 +171,7 @@ int topk_chunks(int64_t rows, int64_t n, int k) {
 // chunk to part_idx / part_val [rows][chunks][k], to be joined by launch_topk_merge.
 hipError_t launch_topk(const float* scores, int64_t rows, int64_t n, int64_t ld, int k,
                        int32_t* out_idx, float* out_val, hipStream_t stream, int chunks, float* part_val,
-                       int32_t* part_idx) {
+                       int32_t* part_idx, const int32_t* flags) {
   if (rows == 0 || k == 0) return hipSuccess;
   if (k < 1 || k > 64 || rows > 0x7fffffff || n > 0x7fffffff) return hipErrorInvalidValue;
   if (chunks > 0 && (part_val == nullptr || part_idx == nullptr || chunks > 65535)) return hipErrorInvalidValue;
@@ -206,17 +184,17 @@ hipError_t launch_topk(const float* scores, int64_t rows, int64_t n, int64_t ld,
   }
   static LdsLimit lds_limit;
   if (const hipError_t e = raise_lds_limit(lds_limit, reinterpret_cast<const void*>(&topk_kernel), (int)sizeof(TopkLds)); e != hipSuccess) return e;
-  hipLaunchKernelGGL(topk_kernel, grid, dim3(256), sizeof(TopkLds), stream, scores, n, ld, k, vec4, out_idx, out_val, chunk_len);
+  hipLaunchKernelGGL(topk_kernel, grid, dim3(256), sizeof(TopkLds), stream, scores, n, ld, k, vec4, out_idx, out_val, chunk_len, flags);
   return hipGetLastError();
 }
 
 hipError_t launch_topk_merge(const float* part_val, const int32_t* part_idx, int64_t rows, int ranges, int k,
-                             int32_t* out_idx, float* out_val, hipStream_t s) {
+                             int32_t* out_idx, float* out_val, hipStream_t s, const int32_t* flags) {
   if (rows == 0) return hipSuccess;
   if (ranges < 1 || k < 1 || k > 64 || (int64_t)ranges * k > 4096 || rows > 0x7fffffff) return hipErrorInvalidValue;
   static LdsLimit lds_limit;
   if (const hipError_t e = raise_lds_limit(lds_limit, reinterpret_cast<const void*>(&topk_merge_kernel), (int)sizeof(TopkLds)); e != hipSuccess) return e;
-  hipLaunchKernelGGL(topk_merge_kernel, dim3((unsigned)rows), dim3(256), sizeof(TopkLds), s, part_val, part_idx, ranges * k, k, out_idx, out_val);
+  hipLaunchKernelGGL(topk_merge_kernel, dim3((unsigned)rows), dim3(256), sizeof(TopkLds), s, part_val, part_idx, ranges * k, k, out_idx, out_val, flags);
   return hipGetLastError();
 }
 
