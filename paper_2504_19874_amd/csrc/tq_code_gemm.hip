@@ -15,7 +15,7 @@
 #include <cmath>
 #include <cstring>
 
-#include "tq_code_gemm.h"
+#include "tq_code_decode.h"
 #include "tq_d128_tile.h"
 
 #include <type_traits>
@@ -40,99 +40,31 @@ struct CodeGemmArgs {
   CodeTable tab;
   float* out;
   int64_t ldo;
-  // search (M queries): inverse scale and error bound factors of each, lists of candidates
-  const float* q_inv;
-  const float* e1;
-  const float* e2;
-  const float* bar;
-  int bar_step;
-  float* list_u;
-  int32_t* list_i;
-  int32_t* count;
-  int cap;
-  int64_t code_step;  // sample pass: code i is row i * code_step
-  float s_rel;        // sketch segment: scale of the queries' first image over that of their second
   int tiles_m, tiles_n, per_xcd;
 };
 
-enum CodeMode {
-  M_DEQUANT,  // two pieces on both sides, out[code][row]
-  M_SAMPLE,   // one piece on both sides, out[row][code] = score - its error bound
-  M_FIND      // ... scores that may reach the query's bar, appended to its list
-};
-
-// 16 of a group's 32 values (bit positions 4 half .. 4 half + 3 of the four bytes), as they lie along the contraction
-template <int BITS, int NP>
-__device__ __forceinline__ void decode16(const uint32_t* w, int half, const CodeTable& tab, uint32_t (&out)[NP][8]) {
-  const int sh = 4 * half;
-  if constexpr (BITS == 1) {
-    const uint32_t n = ~w[0] >> sh;  // bit set: negative
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      out[0][2 * k] = ((n << (15 - k)) & 0x80008000u) | 0x3C003C00u;
-      out[0][2 * k + 1] = ((n << (7 - k)) & 0x80008000u) | 0x3C003C00u;
-    }
-  } else {
-    // magnitude bits: the low planes, complemented where the top plane says negative
-    uint32_t u[BITS > 1 ? BITS - 1 : 1];
-#pragma unroll
-    for (int p = 0; p < BITS - 1; ++p) u[p] = ~(w[p] ^ w[BITS - 1]) >> sh;
-    const uint32_t n = ~w[BITS - 1] >> sh;
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      uint32_t sel = 0u;
-#pragma unroll
-      for (int p = 0; p < BITS - 1; ++p) sel |= (k >= p ? u[p] >> (k - p) : u[p] << (p - k)) & (0x01010101u << p);
-      const uint32_t neg = (n << (7 - k)) & 0x80808080u;
-#pragma unroll
-      for (int pc = 0; pc < NP; ++pc) {
-        const uint32_t* th = pc == 0 ? tab.hh : tab.lh;
-        const uint32_t* tl = pc == 0 ? tab.hl : tab.ll;
-        const uint32_t hi = (BITS == 4 ? __builtin_amdgcn_perm(th[1], th[0], sel) : __builtin_amdgcn_perm(th[0], th[0], sel)) ^ neg;
-        const uint32_t lo = BITS == 4 ? __builtin_amdgcn_perm(tl[1], tl[0], sel) : __builtin_amdgcn_perm(tl[0], tl[0], sel);
-        out[pc][2 * k] = __builtin_amdgcn_perm(hi, lo, 0x06020400u);
-        out[pc][2 * k + 1] = __builtin_amdgcn_perm(hi, lo, 0x07030501u);
-      }
-    }
-  }
-}
-
-template <int BITS>
-__device__ __forceinline__ void load_plane_words(const uint32_t* p, uint32_t (&w)[BITS]) {
-  typedef uint32_t v2 __attribute__((ext_vector_type(2), aligned(4)));
-  typedef uint32_t v3 __attribute__((ext_vector_type(3), aligned(4)));
-  typedef uint32_t v4 __attribute__((ext_vector_type(4), aligned(4)));
-  if constexpr (BITS == 1) w[0] = *p;
-  if constexpr (BITS == 2) { const v2 v = *reinterpret_cast<const v2*>(p); w[0] = v[0]; w[1] = v[1]; }
-  if constexpr (BITS == 3) { const v3 v = *reinterpret_cast<const v3*>(p); w[0] = v[0]; w[1] = v[1]; w[2] = v[2]; }
-  if constexpr (BITS == 4) { const v4 v = *reinterpret_cast<const v4*>(p); w[0] = v[0]; w[1] = v[1]; w[2] = v[2]; w[3] = v[3]; }
-}
-
-template <int MODE, int BITS, bool PROD, int TW, int WM, int WN, int NBUF>
+template <int BITS, bool PROD, int TW, int WM, int WN, int NBUF>
 struct CodeCfg {
   static constexpr int UW = WM;  // so that every thread decodes half a group of one code per step
   static constexpr int THREADS = 64 * WM * WN, TM = WM * TW * 32, TN = WN * UW * 32;
-  static constexpr int NPA = MODE == M_DEQUANT ? 2 : 1, NPB = MODE == M_DEQUANT && BITS >= 2 ? 2 : 1;
+  static constexpr int NPA = 2, NPB = BITS >= 2 ? 2 : 1;
   static constexpr int A_BYTES = TM * 64 * NPA, B_BYTES = TN * 64 * NPB;
   static constexpr int NS = NBUF;
-  static constexpr int LDS = NS * (A_BYTES + B_BYTES) + 4 * TN * 4 + (MODE == M_DEQUANT ? 0 : 4 * TM * 4);
+  static constexpr int LDS = NS * (A_BYTES + B_BYTES) + 2 * TN * 4;
   static constexpr int LOADERS = A_BYTES / 1024 < WM * WN ? A_BYTES / 1024 : WM * WN;  // wavefronts that load the fixed operand
   static constexpr int AL = A_BYTES / 1024 / LOADERS;                                  // their direct loads per step
   static_assert(THREADS == 2 * TN && AL * LOADERS * 1024 == A_BYTES, "roles");
 };
 
-template <int MODE, int BITS, bool PROD, int TW, int WM, int WN, int NBUF>
+template <int BITS, bool PROD, int TW, int WM, int WN, int NBUF>
 __global__ __launch_bounds__(64 * WM * WN, 2) void code_gemm_kernel(const CodeGemmArgs a) {
-  using C = CodeCfg<MODE, BITS, PROD, TW, WM, WN, NBUF>;
+  using C = CodeCfg<BITS, PROD, TW, WM, WN, NBUF>;
   constexpr int UW = C::UW, TM = C::TM, TN = C::TN, NPA = C::NPA, NPB = C::NPB, NS = C::NS, AL = C::AL;
   constexpr bool HAVE_P = BITS > 0, HAVE_S = PROD;
   constexpr int NW = BITS > 0 ? BITS : 1;
   extern __shared__ __attribute__((aligned(1024))) unsigned char lds[];
   float* const first_s = reinterpret_cast<float*>(lds + NS * (C::A_BYTES + C::B_BYTES));  // [TN] factor of the sketch sums
   float* const last_s = first_s + TN;                                                     // [TN] factor of everything
-  float* const nu_s = last_s + TN;   // search: [TN] norm, norm kappa gamma
-  float* const nk_s = nu_s + TN;
-  float* const qi_s = nk_s + TN;     // search: [TM] inverse scale, error factors, bar
 
   const int total = a.tiles_m * a.tiles_n;
   const int logical = (int)(blockIdx.x % XCDS) * a.per_xcd + (int)(blockIdx.x / XCDS);
@@ -178,7 +110,7 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void code_gemm_kernel(const CodeGe
 
   // ---- codes -----------------------------------------------------------------------------------------
   const int code = tid % TN, half = __builtin_amdgcn_readfirstlane(tid / TN);
-  const int64_t row = (n0 + min(code, rows_n - 1)) * (MODE == M_SAMPLE ? a.code_step : 1);  // codes past the end: the last one again, not stored
+  const int64_t row = n0 + min(code, rows_n - 1);  // codes past the end: the last one again, not stored
   const uint32_t* const widx = HAVE_P ? a.idx + row * G * BITS : nullptr;
   const uint32_t* const wz = HAVE_S ? a.qjl + row * G : nullptr;
   uint32_t words[NS][NW];
@@ -245,8 +177,7 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void code_gemm_kernel(const CodeGe
         for (int t = 0; t < TW; ++t)
 #pragma unroll
           for (int u = 0; u < UW; ++u)
-            acc[t][u] = MODE == M_DEQUANT ? __builtin_amdgcn_mfma_f32_32x32x16_f16(fb[u][q], fa[t][p], acc[t][u], 0, 0, 0)
-                                          : __builtin_amdgcn_mfma_f32_32x32x16_f16(fa[t][p], fb[u][q], acc[t][u], 0, 0, 0);
+            acc[t][u] = __builtin_amdgcn_mfma_f32_32x32x16_f16(fb[u][q], fa[t][p], acc[t][u], 0, 0, 0);
       };
       if (NPA == 2) read_a(NPA - 1);
       read_b(0);
@@ -264,42 +195,19 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void code_gemm_kernel(const CodeGe
 #pragma unroll
   for (int i = 0; i + 1 < NS; ++i) dma(i);
   {
-    const float pi = HAVE_P ? (MODE == M_DEQUANT ? a.wp_inv[0] : 1.f) * a.tab.inv : 1.f;
-    const float si = HAVE_S ? (MODE == M_DEQUANT ? a.ws_inv[0] : a.s_rel) : 1.f;
+    const float pi = HAVE_P ? a.wp_inv[0] * a.tab.inv : 1.f;
+    const float si = HAVE_S ? a.ws_inv[0] : 1.f;
     for (int c = tid; c < TN; c += C::THREADS) {
-      const int64_t r = (n0 + min(c, rows_n - 1)) * (MODE == M_SAMPLE ? a.code_step : 1);
+      const int64_t r = n0 + min(c, rows_n - 1);
       const float nu = a.norm != nullptr ? a.norm[r] : 1.f;
       const float kg = HAVE_S ? a.kappa * a.gamma[r] : 0.f;
       first_s[c] = HAVE_P ? kg * si / pi : 1.f;
       last_s[c] = HAVE_P ? nu * pi : nu * (kg * si);
-      if (MODE != M_DEQUANT) {
-        nu_s[c] = c < rows_n ? nu : __builtin_nanf("");  // a code past the end compares false
-        nk_s[c] = nu * kg;
-      }
     }
-    if (MODE != M_DEQUANT)
-      for (int m = tid; m < TM; m += C::THREADS) {
-        const int q = m0 + min(m, rows_m - 1);
-        qi_s[m] = a.q_inv[q];
-        qi_s[TM + m] = a.e1[q];
-        qi_s[2 * TM + m] = a.e2[q];
-        if (MODE == M_FIND) qi_s[3 * TM + m] = m < rows_m ? a.bar[(int64_t)q * a.bar_step] : __builtin_inff();
-      }
   }
   decode_step(0, words[0], std::bool_constant<HAVE_S>{});
   h2_wait_barrier<0>();
   auto scale = [&] {  // the sketch sums in units of the centroid segment
-    if constexpr (MODE != M_DEQUANT) {
-#pragma unroll
-      for (int u = 0; u < UW; ++u) {
-        const float f = first_s[wn * UW * 32 + u * 32 + l32];
-#pragma unroll
-        for (int t = 0; t < TW; ++t)
-#pragma unroll
-          for (int r = 0; r < 16; ++r) acc[t][u][r] *= f;
-      }
-      return;
-    }
 #pragma unroll
     for (int u = 0; u < UW; ++u)
 #pragma unroll
@@ -353,50 +261,6 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void code_gemm_kernel(const CodeGe
   }
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // nothing of this workgroup's is under way to LDS when it ends
 
-  if constexpr (MODE != M_DEQUANT) {
-    // a lane has 16 queries of one code per tile
-#pragma unroll
-    for (int u = 0; u < UW; ++u) {
-      const int c = wn * UW * 32 + u * 32 + l32;
-      const float last = last_s[c], nu = nu_s[c], nk = nk_s[c];
-#pragma unroll
-      for (int t = 0; t < TW; ++t)
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-          const int m = (wm * TW + t) * 32 + 8 * k + 4 * h;
-          __builtin_amdgcn_sched_barrier(0);  // one quad's factors at a time (registers)
-          const float4 qi = *reinterpret_cast<const float4*>(qi_s + m), e1 = *reinterpret_cast<const float4*>(qi_s + TM + m);
-          const float4 e2 = HAVE_S ? *reinterpret_cast<const float4*>(qi_s + 2 * TM + m) : e1;
-          const float qe[4] = {qi.x, qi.y, qi.z, qi.w}, e1e[4] = {e1.x, e1.y, e1.z, e1.w}, e2e[4] = {e2.x, e2.y, e2.z, e2.w};
-          float bar[4] = {0.f, 0.f, 0.f, 0.f};
-          if (MODE == M_FIND) {
-            const float4 b = *reinterpret_cast<const float4*>(qi_s + 3 * TM + m);
-            bar[0] = b.x, bar[1] = b.y, bar[2] = b.z, bar[3] = b.w;
-          }
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            float eps = nu * e1e[e];
-            if (HAVE_S) eps = fmaf(nk, e2e[e], eps);
-            const float v = acc[t][u][4 * k + e] * last;
-            if constexpr (MODE == M_SAMPLE) {
-              if (c < rows_n && m + e < rows_m) a.out[(int64_t)(m0 + m + e) * a.ldo + n0 + c] = fmaf(v, qe[e], -eps);
-            } else {
-              const float top = fmaf(v, qe[e], eps);
-              if (top >= bar[e]) {
-                const int q = m0 + m + e;
-                const int pos = atomicAdd(a.count + q, 1);
-                if (pos < a.cap) {
-                  a.list_u[(int64_t)q * a.cap + pos] = top;
-                  a.list_i[(int64_t)q * a.cap + pos] = (int)(n0 + c);
-                }
-              }
-            }
-          }
-        }
-    }
-    return;
-  }
-
   // ---- x~ = nu acc: a lane has 16 codes of one coordinate, a half-wave stores 128 bytes of a row ----------
 #pragma unroll
   for (int u = 0; u < UW; ++u)
@@ -415,19 +279,19 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void code_gemm_kernel(const CodeGe
     }
 }
 
-template <int MODE, int BITS, bool PROD, int TW, int WM, int WN, int NBUF>
+template <int BITS, bool PROD, int TW, int WM, int WN, int NBUF>
 hipError_t launch_tile(CodeGemmArgs a, hipStream_t s) {
-  using C = CodeCfg<MODE, BITS, PROD, TW, WM, WN, NBUF>;
+  using C = CodeCfg<BITS, PROD, TW, WM, WN, NBUF>;
   a.tiles_m = (a.M + C::TM - 1) / C::TM;
   const int64_t tiles_n = (a.n + C::TN - 1) / C::TN;
   if (tiles_n * a.tiles_m > (int64_t)1 << 30) return hipErrorInvalidValue;
   a.tiles_n = (int)tiles_n;
   a.per_xcd = (a.tiles_m * a.tiles_n + XCDS - 1) / XCDS;
   static LdsLimit lds_limit;  // per instantiation: the limit is raised once per device
-  if (const hipError_t e = raise_lds_limit(lds_limit, reinterpret_cast<const void*>(&code_gemm_kernel<MODE, BITS, PROD, TW, WM, WN, NBUF>), C::LDS);
+  if (const hipError_t e = raise_lds_limit(lds_limit, reinterpret_cast<const void*>(&code_gemm_kernel<BITS, PROD, TW, WM, WN, NBUF>), C::LDS);
       e != hipSuccess)
     return e;
-  hipLaunchKernelGGL((code_gemm_kernel<MODE, BITS, PROD, TW, WM, WN, NBUF>), dim3(a.per_xcd * XCDS), dim3(C::THREADS), C::LDS, s, a);
+  hipLaunchKernelGGL((code_gemm_kernel<BITS, PROD, TW, WM, WN, NBUF>), dim3(a.per_xcd * XCDS), dim3(C::THREADS), C::LDS, s, a);
   return hipGetLastError();
 }
 
@@ -439,27 +303,11 @@ hipError_t launch_dequant(const CodeGemmArgs& a, hipStream_t s) {
   const int64_t cus = device_cu_count();
   auto count = [&](int tm, int tn) { return (int64_t)((a.M + tm - 1) / tm) * ((a.n + tn - 1) / tn); };
   const bool four = a.d % 128 == 0;
-  if (a.M <= 64) return launch_tile<M_DEQUANT, BITS, PROD, 1, 2, 4, 2>(a, s);
+  if (a.M <= 64) return launch_tile<BITS, PROD, 1, 2, 4, 2>(a, s);
   const bool wide = (a.M + 255) / 256 * 256 * 5 < (a.M + 127) / 128 * 128 * 6;  // little more padding than the next tile
-  if (wide && count(256, 256) * 4 >= cus * 3) return launch_tile<M_DEQUANT, BITS, PROD, 2, 4, 2, 2>(a, s);
-  if (count(128, 128) * 2 >= cus || !four) return four ? launch_tile<M_DEQUANT, BITS, PROD, 2, 2, 2, 4>(a, s) : launch_tile<M_DEQUANT, BITS, PROD, 2, 2, 2, 2>(a, s);
-  return launch_tile<M_DEQUANT, BITS, PROD, 1, 2, 1, 4>(a, s);
-}
-
-// Search: the query tile that holds the queries, 256 codes; four buffers (with one piece a step is a third of the dequantiser's)
-template <int MODE, int BITS, bool PROD, int NBUF>
-hipError_t launch_search_tile(const CodeGemmArgs& a, hipStream_t s) {
-  if (a.M > 128) return launch_tile<MODE, BITS, PROD, 2, 4, 2, NBUF>(a, s);
-  if (a.M > 64) return launch_tile<MODE, BITS, PROD, 2, 2, 4, NBUF>(a, s);
-  if (a.M > 32) return launch_tile<MODE, BITS, PROD, 1, 2, 4, NBUF>(a, s);
-  return launch_tile<MODE, BITS, PROD, 1, 1, 8, NBUF>(a, s);
-}
-
-template <int BITS, bool PROD>
-hipError_t launch_search(const CodeGemmArgs& a, hipStream_t s) {
-  if (a.list_u == nullptr)
-    return a.d % 128 == 0 ? launch_search_tile<M_SAMPLE, BITS, PROD, 4>(a, s) : launch_search_tile<M_SAMPLE, BITS, PROD, 2>(a, s);
-  return a.d % 128 == 0 ? launch_search_tile<M_FIND, BITS, PROD, 4>(a, s) : launch_search_tile<M_FIND, BITS, PROD, 2>(a, s);
+  if (wide && count(256, 256) * 4 >= cus * 3) return launch_tile<BITS, PROD, 2, 4, 2, 2>(a, s);
+  if (count(128, 128) * 2 >= cus || !four) return four ? launch_tile<BITS, PROD, 2, 2, 2, 4>(a, s) : launch_tile<BITS, PROD, 2, 2, 2, 2>(a, s);
+  return launch_tile<BITS, PROD, 1, 2, 1, 4>(a, s);
 }
 
 // ---- images ----------------------------------------------------------------------------------------------
@@ -547,32 +395,7 @@ hipError_t launch_code_dequant(int bits, bool prod, const void* pit_image, const
   a.WP = static_cast<const unsigned char*>(pit_image); a.WS = static_cast<const unsigned char*>(st_image);
   a.wp_inv = pit_inv; a.ws_inv = st_inv; a.M = d; a.d = d; a.idx = idx; a.qjl = qjl; a.gamma = gamma; a.norm = norm; a.n = n;
   a.kappa = kappa; a.tab = make_code_table(bits, cb); a.out = out; a.ldo = ldo;
-#define TQ_CODE_BITS(F)                       \
-  switch (bits * 2 + (prod ? 1 : 0)) {        \
-    case 1: return F<0, true>(a, s);          \
-    case 2: return F<1, false>(a, s);         \
-    case 3: return F<1, true>(a, s);          \
-    case 4: return F<2, false>(a, s);         \
-    case 5: return F<2, true>(a, s);          \
-    case 6: return F<3, false>(a, s);         \
-    case 7: return F<3, true>(a, s);          \
-    case 8: return F<4, false>(a, s);         \
-    case 9: return F<4, true>(a, s);          \
-    default: return hipErrorInvalidValue;     \
-  }
   TQ_CODE_BITS(launch_dequant)
-}
-
-hipError_t launch_code_search(int bits, bool prod, const CodeSearch& q, int d, const uint32_t* idx, const uint32_t* qjl, const float* gamma,
-                              const float* norm, int64_t n, int64_t code_step, float kappa, const Codebook& cb, hipStream_t s) {
-  CodeGemmArgs a;
-  std::memset(&a, 0, sizeof(a));
-  a.WP = static_cast<const unsigned char*>(q.r_pieces); a.WS = static_cast<const unsigned char*>(q.s_pieces);
-  a.M = q.nq; a.d = d; a.idx = idx; a.qjl = qjl; a.gamma = gamma; a.norm = norm; a.n = n; a.kappa = kappa; a.tab = make_code_table(bits, cb);
-  a.q_inv = q.inv; a.e1 = q.e1; a.e2 = q.e2; a.bar = q.bar; a.bar_step = q.bar_step; a.out = q.sample; a.ldo = q.ld_sample; a.code_step = code_step;
-  a.list_u = q.list_u; a.list_i = q.list_i; a.count = q.count; a.cap = q.cap; a.s_rel = q.s_rel;
-  TQ_CODE_BITS(launch_search)
-#undef TQ_CODE_BITS
 }
 
 }  // namespace tq

@@ -329,7 +329,7 @@ hipError_t launch_select(const SelectArgs& a, int nq, hipStream_t s) {
 }  // namespace
 
 bool search_applicable(int bits, bool prod, int d, int64_t n, int nq, int topk, const Codebook& cb) {
-  return topk >= 1 && topk <= 64 && nq > 0 && n >= 8192 && n <= 0x7fffffff && d % 32 == 0 && d <= 4096 && (bits > 0 || prod) && code_gemm_serves(bits, cb);
+  return topk >= 1 && topk <= 64 && nq > 0 && n >= 8192 && n <= 0x7fffffff && d % 128 == 0 && d <= 4096 && (bits > 0 || prod) && code_gemm_serves(bits, cb);
 }
 
 size_t search_workspace_bytes(int d, int64_t n, int64_t nq, int topk) { return SearchSpace(d, n, nq, topk).total; }
