@@ -10,10 +10,12 @@
 // kappa gamma E2) / A, two or three instructions per score and no multiplication of the score itself; what passes is
 // evaluated and tested again before it goes to the query's list.  That is a round trip to a counter in memory, with dozens
 // per tile more than a short tile itself takes: they are gathered in LDS, the counters are asked for all of them at once at
-// the end of the next tile, and the pairs stored at the end of the one after that (d = 128: LIST_NOTE).
+// the end of the next tile, and the pairs stored at the end of the one after that (d = 128, 10^6 codes, 1000
+// queries: 605 us, was 1037 with a trip each).
 //
 // Bound by the matrix cores and, at 3 and 4 bits, by the decoding's vector instructions (10^6 codes, 1000 queries: d = 1536, 4 bits
-// GEMM_A; d = 3072, 1 + 1 bits GEMM_B; d = 128, 4 bits GEMM_C).
+// 3.2 ms, 0.95 PFLOP/s; d = 3072, 1 + 1 bits 10.6 ms, 1.16; d = 128, 4 bits 0.48 ms, 0.53).  With the loading and the decoding
+// given to four wavefronts each it was no faster at d = 3072 and slower elsewhere (registers).
 #include <cstring>
 
 #include "tq_code_decode.h"
@@ -460,7 +462,8 @@ hipError_t launch_tile(SearchGemmArgs a, int per_cu, hipStream_t s) {
 template <bool FIND, int BITS, bool PROD>
 hipError_t launch_fits(const SearchGemmArgs& a, hipStream_t s) {
   const int64_t cus = device_cu_count(), cols = (a.n + 255) / 256;
-  auto fills = [&](int tm) { return (a.M + tm - 1) / tm * cols * 4 >= cus * 3; };
+  // (half of them: a tile of half the queries decodes every code twice as often)
+  auto fills = [&](int tm) { return (a.M + tm - 1) / tm * cols * 2 >= cus; };
   if (a.M > 128 && fills(256)) return launch_tile<FIND, BITS, PROD, 2, 4, 2>(a, 1, s);
   if (a.M > 64 && fills(128)) return launch_tile<FIND, BITS, PROD, 2, 2, 4>(a, 1, s);
   if (a.M > 32 && fills(64)) return launch_tile<FIND, BITS, PROD, 1, 2, 4>(a, 1, s);
