@@ -1,0 +1,119 @@
+"""Sizes at which the kernels chosen by size change over: edges of tiles and blocks, remainders, the smallest and the
+largest of each kernel's range.  The comparisons are those of the tests that are called."""
+import numpy as np
+import pytest
+import torch
+
+import workloads as W
+from tests import test_gpu_attend as A
+from tests import test_gpu_parity as T
+from tests import test_gpu_split as S
+
+pytestmark = pytest.mark.gpu
+
+tq = pytest.importorskip("paper_2504_19874_amd")
+
+
+@pytest.mark.parametrize("bits,n,kind", [(2, 1, "bf16"), (3, 15, "f32"), (0, 16, "unit"), (4, 17, "bf16unit"), (1, 4095, "f32"),
+                                         (2, 4096, "bf16"), (3, 4097, "f32")])
+def test_small_batches_at_128(bits, n, kind):
+    """Blocks of 16 vectors up to 4096 vectors."""
+    T.test_quantize_prod(128, bits, n, kind)
+    if bits:
+        T.test_quantize_mse(128, bits, n, kind)
+
+
+@pytest.mark.parametrize("d_hi,bits_lo,prod,n,bf16", [(32, 1, True, 1, True), (64, 2, False, 17, False), (96, 0, True, 4096, True),
+                                                      (32, 3, False, 4097, True)])
+def test_small_split_batches(d_hi, bits_lo, prod, n, bf16):
+    S.test_quantize_split(d_hi, bits_lo, prod, n, bf16)
+
+
+@pytest.mark.parametrize("vb,vprod,groups,qpg,npg", [(2, False, 1, 4, 511), (4, False, 2, 1, 512), (1, True, 1, 5, 513), (3, False, 1, 16, 1),
+                                                     (2, False, 128, 1, 2048), (2, False, 128, 1, 2049)])
+def test_attend_chunks(vb, vprod, groups, qpg, npg):
+    """Workgroups of 512 keys while those of 2048 would leave half of the chip idle; the last two lie on either side."""
+    A.run_attend(128, 2, True, vb, vprod, groups, qpg, npg, True)
+
+
+@pytest.mark.parametrize("d_hi,vbits_lo,npg", [(64, 2, 512), (96, 1, 513)])
+def test_attend_chunks_of_split_values(d_hi, vbits_lo, npg):
+    S.test_attend_with_values_in_two_instances(d_hi, vbits_lo, 0, 2, 4, npg)
+
+
+@pytest.mark.parametrize("d,bits,prod,groups,qpg,npg,topk", [
+    (256, 4, True, 1, 1, 1, 1), (384, 1, False, 2, 2, 255, 0), (640, 2, True, 1, 3, 257, 3), (896, 4, False, 1, 4, 1025, 0),
+    (3072, 1, True, 1, 5, 513, 10), (1536, 3, True, 3, 7, 63, 0), (4096, 0, True, 1, 8, 130, 2), (512, 2, True, 1, 2, 20000, 5),
+])
+def test_few_queries_at_multiples_of_128(d, bits, prod, groups, qpg, npg, topk):
+    T.test_score_and_topk(d, bits, prod, groups, qpg, npg, topk)
+
+
+@pytest.mark.parametrize("npg,topk", [(8191, 64), (8192, 1), (8193, 16), (16385, 33), (65, 64)])
+def test_topk_segments(npg, topk):
+    """Segments of a row, with equal scores on both sides of their edges and scores that are not numbers."""
+    p = T.setup(128, 2, False)[0]
+    c = T._random_codes(p, 128, 2, False, npg, npg)
+    c["norm"][npg // 2:npg // 2 + 40] = 90.0
+    c["idx"][npg // 2:npg // 2 + 40] = c["idx"][0]
+    c["norm"][max(0, npg - 3):] = 90.0
+    T._topk_both_ways(p, T.dev(W.gaussian_queries(3, 128, 5, unit=False)), 1, 3, c, npg, topk)
+    c["norm"][5] = float("nan")
+    ti = torch.zeros((3, topk), dtype=torch.int32, device=T.DEV)
+    tq.tq_score(p, T.dev(W.gaussian_queries(3, 128, 5, unit=False)), 1, 3, c["idx"], None, None, c["norm"], npg, None, topk, ti, None)
+    assert bool((ti >= -1).all()) and bool((ti < npg).all())
+
+
+@pytest.mark.parametrize("d,bits,n,prod", [
+    (32, 2, 1, True), (64, 3, 257, True), (64, 1, 256, False), (96, 4, 63, True), (160, 0, 129, True), (384, 2, 3001, False),
+    (512, 3, 700, True), (640, 1, 65, False), (1024, 4, 255, True), (768, 2, 6000, True), (1536, 1, 9000, False), (544, 3, 4097, True),
+])
+def test_dequantiser_tiles(d, bits, n, prod):
+    """Every tile and depth of buffers; with the matrices' images, and with images built for the call in the workspace."""
+    T.test_dequantize(d, bits, n, prod, True)
+    p = T.setup(d, bits, prod)[0]
+    keep = (p.workspace, p.c.workspace, p.c.workspace_bytes)
+    try:
+        p.drop_images().reserve(n)
+        T.test_dequantize(d, bits, n, prod, False)
+        p.workspace, p.c.workspace, p.c.workspace_bytes = None, 0, 0
+        T.test_dequantize(d, bits, n, prod, False)
+    finally:
+        p.workspace, p.c.workspace, p.c.workspace_bytes = keep
+        p.build_images()
+
+
+@pytest.mark.parametrize("d,bits,n,kind", [(512, 2, 65, "f32"), (512, 1, 16384, "bf16"), (256, 3, 16385, "f32"), (768, 4, 129, "unit"),
+                                           (1024, 0, 1025, "bf16"), (640, 2, 2600, "f32"), (3072, 1, 66, "f32")])
+def test_quantiser_tiles(d, bits, n, kind):
+    """The small tiles' four buffers, and either side of the line between the two contractions."""
+    T.test_quantize_prod(d, bits, n, kind)
+    if bits:
+        T.test_quantize_mse(d, bits, n, kind)
+
+
+@pytest.mark.parametrize("d,bits,prod,nq,n,topk", [
+    (128, 4, False, 17, 8191, 10), (128, 4, False, 17, 8192, 10), (128, 3, True, 33, 8193, 1), (256, 2, False, 65, 20000, 16),
+    (384, 0, True, 129, 9001, 5), (512, 1, True, 257, 30001, 64), (640, 3, False, 130, 40000, 64), (1536, 4, False, 64, 12000, 2),
+    (4096, 1, True, 20, 8200, 3),
+])
+def test_search_by_candidates(d, bits, prod, nq, n, topk):
+    """Top-k alone, by candidates and their exact scores: the same indices and bits as from the score matrix."""
+    p = T.setup(d, bits, prod)[0]
+    c = T._random_codes(p, d, bits, prod, n, d + n)
+    T._topk_both_ways(p, T.dev(W.gaussian_queries(nq, d, 3, unit=False)), 1, nq, c, n, topk)
+
+
+@pytest.mark.parametrize("d,bits,prod", [(128, 2, True), (256, 3, False)])
+def test_search_by_candidates_with_too_many_of_them(d, bits, prod):
+    """Equal scores fill every query's list; rising ones defeat a bar from a sample; vectors of length zero tie at zero."""
+    nq, n, topk = 40, 30000, 10
+    p = T.setup(d, bits, prod)[0]
+    q = T.dev(W.gaussian_queries(nq, d, 9, unit=False))
+    c = T._random_codes(p, d, bits, prod, n, 4)
+    for name in ("idx", "qjl", "gamma"):
+        if c[name] is not None:
+            c[name] = c[name][:1].repeat(n, *[1] * (c[name].dim() - 1)).contiguous()
+    for norm in (np.ones(n), np.linspace(1.0, 2.0, n), np.where(np.arange(n) % 3 == 0, 1.0, 0.0)):
+        c["norm"] = T.dev(norm.astype(np.float32))
+        T._topk_both_ways(p, q, 1, nq, c, n, topk)
