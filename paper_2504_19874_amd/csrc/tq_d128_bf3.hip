@@ -10,9 +10,12 @@
 //     of its vector's row and a half-wave stores one whole row per instruction.
 // Pieces: a centroid and an entry of Pi^T are taken as their two leading bf16 pieces and the three products
 // of combined weight >= 2^-9 are summed (what is left out is 2^-17.8 of a term in the root mean square, 2^-15 at
-// worst: about 5e-6 of a coordinate's typical size, against the 1e-4 the output has to meet).  The sign part is folded into the same
-// accumulator: its operand is +-(kappa gamma_i), the two leading pieces of kappa gamma_i with the sign bit of
-// z_ij, against two pieces of S^T, again three products.  A 1-bit table is +-c_1: the pieces of c_1 with a sign.
+// worst: about 5e-6 of a coordinate's typical size, against the 1e-4 the output has to meet).  A sign is one exact
+// piece: the sign part comes first, two products, and its sums are multiplied by their vector's kappa gamma before the
+// centroid part goes into the same accumulators.  A 1-bit table is +-c_1, so that part is a sign part as well and c_1 joins
+// the factors.  The kernel runs at the rate the matrix cores sustain (leaving out the LDS reads changes nothing): what
+// counts is the number of products (131072 vectors: 2 + 1 bits 25.6 -> 23.2 us, 1 + 1 bits 27.8 -> 20.3, where kappa gamma and
+// c_1 were two pieces each of the operand; below that the stores of 67 MB bound it, 4 bits without sketch 17.0 us).
 // Workgroup = 8 wavefronts, two per SIMD; a wavefront takes 32 vectors per block, workgroups stride over the
 // blocks of 256 vectors.  (Four wavefronts of 64 vectors halve the LDS reads per MFMA but leave every SIMD idle
 // while its one wavefront pushes out the block's stores: 13-20 % slower.)
@@ -85,11 +88,10 @@ __global__ __launch_bounds__(256) void dq128_image_kernel(const float* PiT, cons
 template <int BITS, bool PROD, bool MIXED, int VT>
 __global__ __launch_bounds__(512 / VT) void dequant128_bf3_kernel(const Dq128Args a) {
   constexpr int NT = 512 / VT;  // threads
-  constexpr bool TABLE = BITS >= 2 || MIXED;  // centroid pieces looked up in LDS (1 bit: the pieces of c_1 with a sign)
+  constexpr bool TABLE = BITS >= 2 || MIXED;  // centroid pieces looked up in LDS (1 bit: signs)
   constexpr int NB = (BITS > 0 ? BITS : 1) + (MIXED ? 1 : 0);  // plane words per coordinate group, at most
   constexpr int MATS = (BITS > 0 || MIXED ? 1 : 0) + (PROD ? 1 : 0);
   constexpr bool PI = BITS > 0 || MIXED;  // there is a centroid part
-  constexpr int READS = 4 * 2 * MATS;  // B operands per step: 4 tiles x 2 pieces x matrices
   extern __shared__ __attribute__((aligned(16))) unsigned short lds_s[];  // [matrix][piece][k][128], then the table
   uint32_t* const table_s = reinterpret_cast<uint32_t*>(lds_s + MATS * 2 * MAT_ELEMS);
   const int tid = threadIdx.x;
@@ -125,13 +127,6 @@ __global__ __launch_bounds__(512 / VT) void dequant128_bf3_kernel(const Dq128Arg
   __syncthreads();
 
   const int vi = lane & 31, jg = lane >> 5;  // A: vector within the tile, which 8 of the 16 values of j
-  uint32_t c1p[2] = {0u, 0u};  // 1 bit: the two pieces of c_1, each twice in a word
-  if (BITS == 1) {
-    uint32_t p1, p2, p3;
-    split3(a.cb.c[1], p1, p2, p3);
-    c1p[0] = p1 * 0x00010001u;
-    c1p[1] = p2 * 0x00010001u;
-  }
   const int64_t blocks = (a.n + 255) / 256;
   const int gs = MIXED ? a.gs_hi : 0;
   // MIXED: which of this lane's four output columns belong to instance hi.  The matrices are block diagonal up to a
@@ -187,10 +182,10 @@ __global__ __launch_bounds__(512 / VT) void dequant128_bf3_kernel(const Dq128Arg
     }
   };
 
-  // B operand r of a step: tile r % 4 (columns k = 4 l + tile), then piece 1 before piece 0 of Pi^T, then of S^T
-  auto b_piece = [&](int s, int r) {
-    const int ct = r & 3, q = r >> 2;  // q: (matrix, piece) in the order (0, 1), (0, 0), (1, 1), (1, 0)
-    const int m = q >> 1, pc = 1 - (q & 1);
+  // B operand i: of S^T first, then of Pi^T; of a matrix: step (i / 8) % 8, piece 1 before piece 0, tile i % 4 (columns
+  // k = 4 l + tile)
+  auto b_piece = [&](int i) {
+    const int m = i / 64 == MATS - 1 ? 0 : 1, s = (i >> 3) & 7, pc = 1 - ((i >> 2) & 1), ct = i & 3;
     return *reinterpret_cast<const bf16x8*>(lds_s + (m * 2 + pc) * MAT_ELEMS + lds_at(4 * vi + ct, 16 * s + 8 * jg));
   };
 
@@ -217,20 +212,13 @@ __global__ __launch_bounds__(512 / VT) void dequant128_bf3_kernel(const Dq128Arg
       for (int ct = 0; ct < 4; ++ct)
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc[mt][ct][r] = 0.f;
-    uint32_t kgp[VT][2], kghp[VT][2];  // the two pieces of kappa gamma of this lane's vectors, each twice in a word
-#pragma unroll
-    for (int mt = 0; mt < VT; ++mt) {
-      uint32_t p1, p2, p3;
-      split3(kg[mt], p1, p2, p3);
-      kgp[mt][0] = p1 * 0x00010001u;
-      kgp[mt][1] = p2 * 0x00010001u;
-      split3(kgh[mt], p1, p2, p3);
-      kghp[mt][0] = p1 * 0x00010001u;
-      kghp[mt][1] = p2 * 0x00010001u;
-    }
     bf16x8 ring[RING];
 #pragma unroll
-    for (int r = 0; r < RING; ++r) ring[r] = b_piece(0, r);
+    for (int r = 0; r < RING; ++r) ring[r] = b_piece(r);
+    auto refill = [&](int i) {  // after the last use of operand i
+      if (i + RING < 64 * MATS) ring[i % RING] = b_piece(i + RING);
+      __builtin_amdgcn_sched_barrier(0);
+    };
     // table entries of the coordinates of one step, looked up one step ahead: they travel during the MFMAs
     uint32_t te[VT][8];
     auto look_up = [&](int s) {
@@ -248,25 +236,58 @@ __global__ __launch_bounds__(512 / VT) void dequant128_bf3_kernel(const Dq128Arg
         for (int u = 0; u < 8; ++u) te[mt][u] = tab[(lv[u >> 2] >> (8 * (u & 3))) & 0xFFu];
       }
     };
-    if (TABLE) look_up(0);
+    // ---- sums of the matrix whose operands begin at i0 with the signs of word group g (bit 1 = +1) ---------
+    auto sign_sums = [&](int i0, auto word) __attribute__((always_inline)) {
 #pragma unroll
-    for (int s = 0; s < 8; ++s) {
-      const int g = s >> 1, off = (s & 1) * 16 + 8 * jg;  // word of the code, first bit
-      // ---- A operands: this lane's 8 coordinates of two vectors decoded into pieces ----------------------
-      bf16x8 ca[VT][2], za[VT][2];
+      for (int s = 0; s < 8; ++s) {
+        bf16x8 za[VT];
 #pragma unroll
-      for (int mt = 0; mt < VT; ++mt) {
-        if (BITS == 1 && !MIXED) {
-          u32x4 v1, v2;
+        for (int mt = 0; mt < VT; ++mt) {
+          const uint32_t bits = ~word(mt, s >> 1) >> (8 * jg);
+          u32x4 v;
 #pragma unroll
-          for (int e = 0; e < 4; ++e) {  // bit 1 = +c_1: the sign bit is set where the code bit is 0
-            const uint32_t sg = ((((w[mt][g][0] >> (off + 2 * e)) & 1u) << 15) | (((w[mt][g][0] >> (off + 2 * e + 1)) & 1u) << 31)) ^ 0x80008000u;
-            v1[e] = c1p[0] ^ sg;
-            v2[e] = c1p[1] ^ sg;
+          for (int e = 0; e < 4; ++e) {
+            const int b = (s & 1) * 16 + 2 * e;  // the bits of this word's two coordinates
+            v[e] = 0x3F803F80u | ((b < 15 ? bits << (15 - b) : bits >> (b - 15)) & 0x8000u) | ((bits << (30 - b)) & 0x80000000u);
           }
-          ca[mt][0] = *reinterpret_cast<const bf16x8*>(&v1);
-          ca[mt][1] = *reinterpret_cast<const bf16x8*>(&v2);
-        } else if (TABLE) {
+          za[mt] = *reinterpret_cast<const bf16x8*>(&v);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int r = 0; r < 8; ++r) {
+#pragma unroll
+          for (int mt = 0; mt < VT; ++mt)
+            acc[mt][r & 3] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(za[mt], ring[(i0 + 8 * s + r) % RING], acc[mt][r & 3], 0, 0, 0);
+          refill(i0 + 8 * s + r);
+        }
+      }
+    };
+    // factor f of the vector that row r of the accumulators belongs to: it sits in the lane with that number
+    auto of_row = [&](int r, float f) {
+      return __int_as_float(__builtin_amdgcn_ds_bpermute(4 * (8 * (r >> 2) + (r & 3) + 4 * (lane >> 5)), __float_as_int(f)));
+    };
+    constexpr bool UNIT = BITS == 1 && !MIXED;  // the centroid part as signs, c_1 among the factors
+    if (PROD) {
+      sign_sums(0, [&](int mt, int g) { return z[mt][g]; });
+      if (PI) {  // in the units of the centroid part
+#pragma unroll
+        for (int mt = 0; mt < VT; ++mt)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) {
+            const float f = of_row(r, UNIT ? kg[mt] / a.cb.c[1] : kg[mt]), fh = MIXED ? of_row(r, kgh[mt]) : 0.f;
+#pragma unroll
+            for (int ct = 0; ct < 4; ++ct) acc[mt][ct][r] *= MIXED && ((hi_cols >> ct) & 1u) ? fh : f;
+          }
+      }
+    }
+    if (UNIT) sign_sums(PROD ? 64 : 0, [&](int mt, int g) { return w[mt][g][0]; });
+    if (TABLE) {
+      look_up(0);
+#pragma unroll
+      for (int s = 0; s < 8; ++s) {
+        bf16x8 ca[VT][2];  // this lane's 8 coordinates decoded into pieces
+#pragma unroll
+        for (int mt = 0; mt < VT; ++mt) {
           u32x4 v1, v2;
 #pragma unroll
           for (int u = 0; u < 4; ++u) {
@@ -276,41 +297,19 @@ __global__ __launch_bounds__(512 / VT) void dequant128_bf3_kernel(const Dq128Arg
           ca[mt][0] = *reinterpret_cast<const bf16x8*>(&v1);
           ca[mt][1] = *reinterpret_cast<const bf16x8*>(&v2);
         }
-        if (PROD) {
-          u32x4 v1, v2;
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {  // bit 1 = +1
-            const uint32_t sg = ((((z[mt][g] >> (off + 2 * e)) & 1u) << 15) | (((z[mt][g] >> (off + 2 * e + 1)) & 1u) << 31)) ^ 0x80008000u;
-            v1[e] = (MIXED && g < gs ? kghp[mt][0] : kgp[mt][0]) ^ sg;
-            v2[e] = (MIXED && g < gs ? kghp[mt][1] : kgp[mt][1]) ^ sg;
-          }
-          za[mt][0] = *reinterpret_cast<const bf16x8*>(&v1);
-          za[mt][1] = *reinterpret_cast<const bf16x8*>(&v2);
-        }
-      }
-      __builtin_amdgcn_sched_barrier(0);
-      if (TABLE && s + 1 < 8) look_up(s + 1);
-      __builtin_amdgcn_sched_barrier(0);
-      // ---- B operands through the ring, MFMAs ----------------------------------------------------------
-#pragma unroll
-      for (int r = 0; r < READS; ++r) {
-        const int ct = r & 3, q = r >> 2;
-        const bool sign_part = !PI || q >= 2;  // which matrix this operand belongs to
-        const int pc = 1 - (q & 1);
-        const bf16x8 b = ring[(s * READS + r) % RING];
-        // piece pc of the matrix meets the pieces a of the decoded operand with a + pc <= 1; the two MFMAs on
-        // one accumulator are kept apart by the other vector tile's
-        if (pc == 0) {
-#pragma unroll
-          for (int mt = 0; mt < VT; ++mt)
-            acc[mt][ct] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(sign_part ? za[mt][1] : ca[mt][1], b, acc[mt][ct], 0, 0, 0);
-        }
-#pragma unroll
-        for (int mt = 0; mt < VT; ++mt)
-          acc[mt][ct] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(sign_part ? za[mt][0] : ca[mt][0], b, acc[mt][ct], 0, 0, 0);
-        const int nxt = s * READS + r + RING;  // the read that takes this slot
-        if (nxt < 8 * READS) ring[nxt % RING] = b_piece(nxt / READS, nxt % READS);
         __builtin_amdgcn_sched_barrier(0);
+        if (s + 1 < 8) look_up(s + 1);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int r = 0; r < 8; ++r) {  // piece p of the matrix meets the pieces q of the centroids with p + q <= 1
+          const int i = (PROD ? 64 : 0) + 8 * s + r;
+#pragma unroll
+          for (int q = r < 4 ? 0 : 1; q >= 0; --q)
+#pragma unroll
+            for (int mt = 0; mt < VT; ++mt)
+              acc[mt][r & 3] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ca[mt][q], ring[i % RING], acc[mt][r & 3], 0, 0, 0);
+          refill(i);
+        }
       }
     }
     // ---- epilogue: D[vector][k]; the factors of a row's vector sit in the lane with that number --------
@@ -329,9 +328,8 @@ __global__ __launch_bounds__(512 / VT) void dequant128_bf3_kernel(const Dq128Arg
       float rnu[16], rnuh[MIXED ? 16 : 1];
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
-        rnu[r] = __int_as_float(__builtin_amdgcn_ds_bpermute(4 * (8 * (r >> 2) + (r & 3) + 4 * (lane >> 5)), __float_as_int(nu[mt])));
-        if (MIXED)
-          rnuh[r] = __int_as_float(__builtin_amdgcn_ds_bpermute(4 * (8 * (r >> 2) + (r & 3) + 4 * (lane >> 5)), __float_as_int(nuh[mt])));
+        rnu[r] = of_row(r, !PI ? nu[mt] * kg[mt] : UNIT ? nu[mt] * a.cb.c[1] : nu[mt]);
+        if (MIXED) rnuh[r] = of_row(r, nuh[mt]);
       }
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
@@ -366,12 +364,12 @@ hipError_t launch_one(const Dq128Args& a, hipStream_t s) {
 
 }  // namespace
 
-// d = 128; a 1-bit table of one instance must be +-c; rows of the output 16-byte aligned
+// d = 128; a 1-bit table of one instance must be +-c, c > 0; rows of the output 16-byte aligned
 bool dequant128_bf3_applicable(int bits, bool prod, const Codebook& cb, const float* out, int64_t ldo) {
   if (bits < 0 || bits > 4 || (bits == 0 && !prod)) return false;
   if ((reinterpret_cast<uintptr_t>(out) & 15u) != 0 || ldo % 4 != 0) return false;
   if (ldo < 128 || ldo > (1 << 22)) return false;  // 64 rows of a wavefront are addressed with 32-bit byte offsets
-  return bits != 1 || cb.c[0] == -cb.c[1];
+  return bits != 1 || (cb.c[0] == -cb.c[1] && cb.c[1] > 1e-30f && cb.c[1] < 1e30f);  // (a factor is divided by c_1)
 }
 
 // gs_hi > 0: two instances (cb_hi with bits + 1 bits and kappa_hi for the first gs_hi coordinate groups; norm and
