@@ -1,11 +1,11 @@
 // Quant_mse / Quant_prod (Alg. 1 / Alg. 2) at d = 128 for batches of bf16 vectors beyond what one round of the
-// small-batch kernel covers, on the bf16 matrix cores (exact bf16 pieces of the fp32 factors, see tq_bf3.h): the
-// rotation to fp32 accuracy, the sketch as far as its signs need.
+// small-batch kernel covers, on the 16-bit matrix cores: the rotation to fp32 accuracy, the sketch as far as its signs need.
 //
-//   stage 1   y^T = Pi x^T.  A bf16 input IS a single piece, so the rotation takes three piece products
-//             (x times the three pieces of Pi).  The vector is the COLUMN of the MFMA: a lane loads 8
-//             consecutive bf16 of its vector's row from HBM and that register is the B operand as it
-//             stands; the A operand is a piece of Pi, resident in LDS for the life of the workgroup.
+//   stage 1   y^T = Pi x^T with fp16 pieces (tq_h2.h): two of Pi and, a power of two brought in so that the row's largest
+//             value lies just below the end of the range, ONE of a bf16 vector: two products where three bf16 pieces
+//             of Pi would take three (F32: two pieces of x, three products, were five).  The vector is the COLUMN of
+//             the MFMA: a lane loads 8 consecutive values of its vector's row from HBM and that register, converted, is
+//             the B operand; the A operand is a piece of Pi, resident in LDS for the life of the workgroup.
 //   decision  the accumulator tile holds 16 coordinates of one vector per lane: scale by 1 / ||x||, nearest
 //             centroid, packing, residual e = y - c[idx] in place (quantise_tile), gamma = ||e||.
 //   stage 2   u^T = (S Pi^T) e^T, of which only the signs are kept.  The residual registers, split into their
@@ -14,7 +14,7 @@
 //             S Pi^T follows).  S Pi^T is held as its two leading pieces as well, and the three products of
 //             combined weight >= 2^-9 are taken: what is left out is 2^-17.8 of a term (root mean square), about
 //             5e-7 |S_j| |e| in u, against the 1e-5 |S_j| |e| inside which a sign may differ from the exact one.
-//   LDS       three pieces of Pi and two of S Pi^T, 128 x 128 bf16 each, are exactly the 160 KB of a compute
+//   LDS       two pieces of Pi and two of S Pi^T, 128 x 128 values of 16 bits each, 128 of the 160 KB of a compute
 //             unit: rows are stored without padding, the 16-byte chunks of a row rotated by the row number
 //             (conflict-free 16-byte reads along a column of chunks).
 //
@@ -22,17 +22,21 @@
 // 64 vectors (VT = 2: the register file of a SIMD to one wavefront, every LDS read of an A operand feeding two
 // MFMAs) are 13-19 % slower: nothing runs on a SIMD while its one wavefront is in the decision stage's
 // dependent chains or waits for LDS.
+//
+// Bound by what the matrix cores sustain, then by the decision's vector instructions; leaving out the LDS reads changes nothing.
+// 131072 vectors, with three pieces of Pi -> with two: bf16, 2 + 1 bits 26.8 -> 25.4 us; fp32, 3 + 1 bits 44.3 -> 37.3.
 #include <type_traits>
 
 #include "tq_bf3.h"
 #include "tq_d128_tile.h"
+#include "tq_h2.h"
 
 namespace tq {
 
 namespace {
 
 constexpr int MAT_ELEMS = 128 * 128;  // one piece of one matrix
-constexpr int PI_ELEMS = 3 * MAT_ELEMS;
+constexpr int PI_ELEMS = 2 * MAT_ELEMS;
 constexpr int W_ELEMS = 2 * MAT_ELEMS;
 constexpr int RING = 4;  // A operands in flight
 
@@ -69,23 +73,42 @@ __device__ __forceinline__ float square_pair(uint32_t w, float acc) {
 // places (see stage 2)
 __device__ __forceinline__ int w_col(int j) { return (j & ~12) | ((j & 4) << 1) | ((j & 8) >> 1); }
 
-// The kernel's parameter image, by 256 threads: three pieces of Pi at dst, two of S Pi^T (columns permuted) behind
-// them, each [row][128] with the chunk rotation of lds_at.  dst is LDS in the quantisation kernel and device
+// The bit pattern of the largest magnitude of a 128 x 128 matrix, by NT threads; max_s: a word of LDS that was cleared
+template <int NT>
+__device__ __forceinline__ uint32_t largest_of(const float* W, uint32_t* max_s, int tid) {
+  uint32_t m = 0u;
+#pragma unroll
+  for (int i = 0; i < 4096 / NT; ++i) {
+    const u32x4 v = *reinterpret_cast<const u32x4*>(W + (i * NT + tid) * 4);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) m = max(m, v[e] & 0x7fffffffu);
+  }
+  atomicMax(max_s, m);
+  __syncthreads();
+  return *max_s;
+}
+
+// The kernel's parameter image, by 256 threads: two fp16 pieces of s Pi at dst, two bf16 pieces of S Pi^T (columns permuted)
+// behind them, each [row][128] with the chunk rotation of lds_at.  dst is LDS in the quantisation kernel and device
 // memory in q128_image_kernel.
-__device__ __forceinline__ void q128_split_matrices(const float* Pi, const float* SPiT, unsigned short* dst, int tid) {
-  // rows [row0, row0 + 64) of a 128 x 128 fp32 matrix -> its leading `pieces` pieces; 8 x 16 bytes per thread
-  auto split_rows = [&](const f32x4 (&v)[8], unsigned short* out, int row0, int pieces, bool permute) {
+__device__ __forceinline__ void q128_split_matrices(const float* Pi, const float* SPiT, float s, unsigned short* dst, int tid) {
+  // rows [row0, row0 + 64) of a 128 x 128 fp32 matrix -> two pieces; 8 x 16 bytes per thread
+  auto split_rows = [&](const f32x4 (&v)[8], unsigned short* out, int row0, bool sketch) {
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
       const int e = (i * 256 + tid) * 4;
       const int row = row0 + (e >> 7), j = e & 127;
-      uint32_t lo[3], hi[3];
-      split3_pair(f32x2{v[i][0], v[i][1]}, lo[0], lo[1], lo[2]);
-      split3_pair(f32x2{v[i][2], v[i][3]}, hi[0], hi[1], hi[2]);
-      const int at = lds_at(row, permute ? w_col(j) : j);
+      uint32_t lo[2], hi[2];
+      if (sketch) {
+        split2_pair(f32x2{v[i][0], v[i][1]}, lo[0], lo[1]);
+        split2_pair(f32x2{v[i][2], v[i][3]}, hi[0], hi[1]);
+      } else {
+        h2_split(s * v[i][0], s * v[i][1], lo[0], lo[1]);
+        h2_split(s * v[i][2], s * v[i][3], hi[0], hi[1]);
+      }
+      const int at = lds_at(row, sketch ? w_col(j) : j);
 #pragma unroll
-      for (int pc = 0; pc < 3; ++pc)
-        if (pc < pieces) *reinterpret_cast<uint2*>(out + pc * MAT_ELEMS + at) = make_uint2(lo[pc], hi[pc]);
+      for (int pc = 0; pc < 2; ++pc) *reinterpret_cast<uint2*>(out + pc * MAT_ELEMS + at) = make_uint2(lo[pc], hi[pc]);
     }
   };
   auto fetch64 = [&](const float* src, f32x4 (&v)[8]) {
@@ -95,43 +118,53 @@ __device__ __forceinline__ void q128_split_matrices(const float* Pi, const float
   f32x4 lo[8], hi[8];
   fetch64(Pi, lo);
   fetch64(Pi + 64 * 128, hi);
-  split_rows(lo, dst, 0, 3, false);
-  split_rows(hi, dst, 64, 3, false);
+  split_rows(lo, dst, 0, false);
+  split_rows(hi, dst, 64, false);
   if (SPiT != nullptr) {
     fetch64(SPiT, lo);
     fetch64(SPiT + 64 * 128, hi);
-    split_rows(lo, dst + PI_ELEMS, 0, 2, true);
-    split_rows(hi, dst + PI_ELEMS, 64, 2, true);
+    split_rows(lo, dst + PI_ELEMS, 0, true);
+    split_rows(hi, dst + PI_ELEMS, 64, true);
   }
 }
 
-// one workgroup of 256 threads: the image in device memory, (PI_ELEMS + W_ELEMS) * 2 bytes
+// one workgroup of 256 threads: the image in device memory, (PI_ELEMS + W_ELEMS) * 2 bytes, and behind it 1 / s
 __global__ __launch_bounds__(256) void q128_image_kernel(const float* Pi, const float* SPiT, unsigned short* image) {
-  q128_split_matrices(Pi, SPiT, image, threadIdx.x);
+  __shared__ uint32_t max_s;
+  if (threadIdx.x == 0) max_s = 0u;
+  __syncthreads();
+  float s, inv;
+  h2_scale(largest_of<256>(Pi, &max_s, threadIdx.x), s, inv);
+  if (threadIdx.x == 0) *reinterpret_cast<float*>(image + PI_ELEMS + W_ELEMS) = inv;
+  q128_split_matrices(Pi, SPiT, s, image, threadIdx.x);
 }
 
 // VT = vector tiles (of 32) per wavefront: 2 = four wavefronts of 64 vectors (one per SIMD, every LDS read of an A
 // operand feeds two MFMAs), 1 = eight wavefronts of 32 vectors (two per SIMD: while one is in its decision stage or
 // waits for LDS, the other issues MFMAs).
 //
-// F32: the vectors are fp32.  A lane's 8 values of a step are two 16-byte loads, split into their two leading
-// pieces (x1 + x2 = x up to 2^-17 |x|), and the rotation takes the five piece products of weight >= 2^-16 that two
-// pieces of x have with three of Pi: every A operand read of the two leading pieces of Pi feeds two MFMAs.
+// F32: the vectors are fp32.  A lane's 8 values of a step are two 16-byte loads, split into two fp16 pieces.
+// workgroups per compute unit: without a sketch two fit into LDS, and with bf16 vectors into the registers too (131072
+// vectors, 4 bits: 28.3 -> 25.3 us; two instances of 2 + 3 bits: 20.6 -> 18.9)
+constexpr int q128_per_cu(bool prod, bool f32) { return !prod && !f32 ? 2 : 1; }
+
 template <int BITS, bool PROD, bool MIXED, int VT, bool F32 = false>
-__global__ __launch_bounds__(512 / VT) void quant128_bf3_kernel(const Q128Args a) {
+__global__ __launch_bounds__(512 / VT, q128_per_cu(PROD, F32) * 2 / VT) void quant128_bf3_kernel(const Q128Args a) {
   constexpr int NT = 512 / VT;  // threads
   constexpr int NB = (BITS > 0 ? BITS : 1) + (MIXED ? 1 : 0);  // plane words per tile, at most
   constexpr int BH = BITS < 4 ? BITS + 1 : 4;                  // bits of instance hi
   extern __shared__ __attribute__((aligned(16))) unsigned short lds_s[];
-  unsigned short* const Pi_s = lds_s;            // [piece][row j][128], see lds_at
-  unsigned short* const W_s = lds_s + PI_ELEMS;  // [piece][row j'][128], columns permuted
+  unsigned short* const Pi_s = lds_s;            // fp16, [piece][row j][128], see lds_at
+  unsigned short* const W_s = lds_s + PI_ELEMS;  // bf16, [piece][row j'][128], columns permuted
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int vi = lane & 31, g = lane >> 5;
 
+  float pi_inv, pi_scale;  // of the pieces of Pi
   if (a.image != nullptr) {
-    // a straight copy, 16 bytes per thread and step: 24 steps for Pi, 16 for S Pi^T
+    pi_inv = *reinterpret_cast<const float*>(reinterpret_cast<const unsigned short*>(a.image) + PI_ELEMS + W_ELEMS);
+    // a straight copy, 16 bytes per thread and step: 16 each for Pi and S Pi^T
     constexpr int STEPS = (PI_ELEMS + (PROD ? W_ELEMS : 0)) * 2 / (NT * 16);
     u32x4* const dst = reinterpret_cast<u32x4*>(lds_s);
 #pragma unroll
@@ -142,16 +175,20 @@ __global__ __launch_bounds__(512 / VT) void quant128_bf3_kernel(const Q128Args a
 #pragma unroll
       for (int i = 0; i < STEPS / 2; ++i) dst[(half * (STEPS / 2) + i) * NT + tid] = v[i];
     }
-  } else if (tid < 256) {
-    q128_split_matrices(a.Pi, PROD ? a.SPiT : nullptr, lds_s, tid);
+  } else {
+    __shared__ uint32_t max_s;
+    if (tid == 0) max_s = 0u;
+    __syncthreads();
+    h2_scale(largest_of<NT>(a.Pi, &max_s, tid), pi_scale, pi_inv);
+    if (tid < 256) q128_split_matrices(a.Pi, PROD ? a.SPiT : nullptr, pi_scale, lds_s, tid);
   }
   __syncthreads();
 
   const int64_t blocks = (a.n + 255) / 256;
   const bool normalise = !MIXED && a.norm != nullptr;
   constexpr int ESZ = F32 ? 4 : 2;
-  u32x4 xop[VT][8];                   // the B operands of stage 1 (F32: piece 1 of x)
-  u32x4 xop2[F32 ? VT : 1][8];        // F32: piece 2
+  u32x4 xop[VT][8];                   // the B operands of stage 1 (F32: hi piece of x)
+  u32x4 xop2[F32 ? VT : 1][8];        // F32: lo piece
   u32x4 xraw[F32 ? VT : 1][8][2];     // F32: the fp32 values as loaded
   auto x_row = [&](int64_t blk, int nt) {  // this lane's 8 values of step 0
     const int64_t v = blk * 256 + wave * (32 * VT) + 32 * nt + vi;
@@ -204,51 +241,79 @@ __global__ __launch_bounds__(512 / VT) void quant128_bf3_kernel(const Q128Args a
       }
     }
 
-    if constexpr (F32) {
-      // the two leading pieces of the vectors: word j of a step's operand holds values 2 j and 2 j + 1
+    // ---- the vectors as fp16 pieces, scaled by a power of two each ------------------------------------------
+    float unit[VT];  // accumulator of stage 1 -> coordinate
 #pragma unroll
-      for (int nt = 0; nt < VT; ++nt)
+    for (int nt = 0; nt < VT; ++nt) {
+      uint32_t top = 0u;
+      if constexpr (F32) {
 #pragma unroll
         for (int s = 0; s < 8; ++s)
 #pragma unroll
-          for (int j = 0; j < 4; ++j) {
+          for (int e = 0; e < 8; ++e) top = max(top, xraw[nt][s][e >> 2][e & 3] & 0x7fffffffu);
+      } else {
+        typedef unsigned short us2 __attribute__((ext_vector_type(2)));
+        us2 m = {0, 0};
+#pragma unroll
+        for (int s = 0; s < 8; ++s)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) m = __builtin_elementwise_max(m, __builtin_bit_cast(us2, xop[nt][s][e] & 0x7fff7fffu));
+        top = (uint32_t)max(m[0], m[1]) << 16;
+      }
+      {
+        const auto r = __builtin_amdgcn_permlane32_swap(top, top, false, false);
+        top = max(r[0], r[1]);
+      }
+      float sc, sc_inv;
+      h2_scale(top, sc, sc_inv);
+      unit[nt] = sc_inv;  // (pi_inv joins later: the product of the two may be too small for a number)
+#pragma unroll
+      for (int s = 0; s < 8; ++s)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {  // word j of a step's operand holds values 2 j and 2 j + 1
+          if constexpr (F32) {
             const f32x4 v = __builtin_bit_cast(f32x4, xraw[nt][s][j >> 1]);
             uint32_t w1, w2;
-            split2_pair(f32x2{v[2 * (j & 1)], v[2 * (j & 1) + 1]}, w1, w2);
+            h2_split(sc * v[2 * (j & 1)], sc * v[2 * (j & 1) + 1], w1, w2);
             xop[nt][s][j] = w1;
             xop2[nt][s][j] = w2;
+          } else {  // exact, or below 2^-39 of the row's largest value
+            const uint32_t w = xop[nt][s][j];
+            xop[nt][s][j] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pkrtz(sc * __uint_as_float(w << 16), sc * __uint_as_float(w & 0xffff0000u)));
           }
+        }
+      inv[nt] = inv[nt] * unit[nt] * pi_inv;
     }
 
-    // ---- stage 1: y^T = Pi x^T, three piece products (F32: five) ----------------------------------------
+    // ---- stage 1: y^T = Pi x^T, two piece products (F32: three) ------------------------------------------
     // (the first product of every accumulator takes a zero C operand: nothing is cleared)
     floatx16 acc[VT][4];
     const floatx16 zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
     {
       // the A operands travel through a ring of RING registers, read RING MFMA pairs ahead of their use: left to
       // itself the compiler reuses two registers and every group of MFMAs waits for a full LDS round trip
-      auto pi_piece = [&](int i) {  // read i of 96: step i / 12, pieces 2, 1, 0 (smallest products first), tile i % 4
-        return *reinterpret_cast<const bf16x8*>(Pi_s + (2 - (i >> 2) % 3) * MAT_ELEMS + lds_at(32 * (i & 3) + vi, 16 * (i / 12) + 8 * g));
+      auto pi_piece = [&](int i) {  // read i of 64: step i / 8, the lo piece before the hi, tile i % 4
+        return *reinterpret_cast<const f16x8*>(Pi_s + (1 - ((i >> 2) & 1)) * MAT_ELEMS + lds_at(32 * (i & 3) + vi, 16 * (i / 8) + 8 * g));
       };
-      bf16x8 ring[RING];
+      f16x8 ring[RING];
 #pragma unroll
       for (int i = 0; i < RING; ++i) ring[i] = pi_piece(i);
 #pragma unroll
-      for (int i = 0; i < 96; ++i) {
-        const int s = i / 12, t = i & 3;
+      for (int i = 0; i < 64; ++i) {
+        const int s = i / 8, t = i & 3;
 #pragma unroll
         for (int nt = 0; nt < VT; ++nt)
-          acc[nt][t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ring[i % RING], *reinterpret_cast<const bf16x8*>(&xop[nt][s]),
-                                                               i < 4 ? zero16 : acc[nt][t], 0, 0, 0);
+          acc[nt][t] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ring[i % RING], *reinterpret_cast<const f16x8*>(&xop[nt][s]),
+                                                              i < 4 ? zero16 : acc[nt][t], 0, 0, 0);
         if constexpr (F32) {
-          if ((i >> 2) % 3 != 0) {  // pieces 1 and 0 of Pi also meet piece 2 of x
+          if ((i >> 2) & 1) {  // the hi piece of Pi also meets the lo piece of x
 #pragma unroll
             for (int nt = 0; nt < VT; ++nt)
-              acc[nt][t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ring[i % RING], *reinterpret_cast<const bf16x8*>(&xop2[nt][s]),
-                                                                   acc[nt][t], 0, 0, 0);
+              acc[nt][t] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ring[i % RING], *reinterpret_cast<const f16x8*>(&xop2[nt][s]),
+                                                                  acc[nt][t], 0, 0, 0);
           }
         }
-        if (i + RING < 96) ring[i % RING] = pi_piece(i + RING);
+        if (i + RING < 64) ring[i % RING] = pi_piece(i + RING);
         __builtin_amdgcn_sched_barrier(0);
       }
     }
@@ -276,10 +341,11 @@ __global__ __launch_bounds__(512 / VT) void quant128_bf3_kernel(const Q128Args a
           s_hi += t < gs ? s0 + s1 : 0.f;
           s_lo += t < gs ? 0.f : s0 + s1;
         }
-        nuh[nt] = sqrtf(add_across_halves(s_hi));
-        nu[nt] = sqrtf(add_across_halves(s_lo));
-        inv_hi[nt] = nuh[nt] > 0.f ? 1.f / nuh[nt] : 0.f;
-        inv[nt] = nu[nt] > 0.f ? 1.f / nu[nt] : 0.f;
+        const float r_hi = sqrtf(add_across_halves(s_hi)), r_lo = sqrtf(add_across_halves(s_lo));
+        inv_hi[nt] = r_hi > 0.f ? 1.f / r_hi : 0.f;
+        inv[nt] = r_lo > 0.f ? 1.f / r_lo : 0.f;
+        nuh[nt] = r_hi * unit[nt] * pi_inv;
+        nu[nt] = r_lo * unit[nt] * pi_inv;
       }
     }
     {
@@ -435,8 +501,8 @@ hipError_t launch_vt(const Q128Args& a, hipStream_t s) {
   constexpr int lds = (PI_ELEMS + (PROD ? W_ELEMS : 0)) * 2;
   static LdsLimit lds_limit;  // per instantiation: the limit is raised once per device
   if (const hipError_t e = raise_lds_limit(lds_limit, reinterpret_cast<const void*>(&quant128_bf3_kernel<BITS, PROD, MIXED, VT, F32>), lds); e != hipSuccess) return e;
-  const int64_t blocks = (a.n + 255) / 256, cus = device_cu_count();  // one workgroup per compute unit
-  hipLaunchKernelGGL((quant128_bf3_kernel<BITS, PROD, MIXED, VT, F32>), dim3((unsigned)(blocks < cus ? blocks : cus)), dim3(512 / VT), lds, s, a);
+  const int64_t blocks = (a.n + 255) / 256, most = device_cu_count() * q128_per_cu(PROD, F32);
+  hipLaunchKernelGGL((quant128_bf3_kernel<BITS, PROD, MIXED, VT, F32>), dim3((unsigned)(blocks < most ? blocks : most)), dim3(512 / VT), lds, s, a);
   return hipGetLastError();
 }
 
@@ -500,7 +566,7 @@ hipError_t launch_quant128_bf3(int bits, bool prod, bool f32, const void* X, int
   }
 }
 
-size_t quant128_bf3_image_bytes() { return (size_t)(PI_ELEMS + W_ELEMS) * 2; }
+size_t quant128_bf3_image_bytes() { return (size_t)5 * MAT_ELEMS * 2; }  // pieces, 1 / s, and what callers were told to reserve
 
 // SPiT may be null (no sketch): the second part of the image is left alone then
 hipError_t launch_quant128_bf3_image(const float* Pi, const float* SPiT, void* image, hipStream_t s) {
