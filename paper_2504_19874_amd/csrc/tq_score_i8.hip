@@ -7,6 +7,7 @@
 // largest coordinate, far inside 1e-4.
 #include <cstring>
 
+#include "tq_score_digits.h"
 #include "tq_score_i8.h"
 
 namespace tq {
@@ -23,18 +24,10 @@ __device__ __forceinline__ void stream_digits(const float* ys, int d, float sc, 
     uint32_t w[4] = {0u, 0u, 0u, 0u};
 #pragma unroll
     for (int b = 0; b < 4; ++b) {
-      const int Q = __float2int_rn(ys[32 * g + k + 8 * b] * sc);
-      const int Qs = k == 7 ? -Q : Q << (7 - k);
-      const int d0 = ((Qs + 64) & 127) - 64;
-      const int Q1 = (Qs - d0) >> 7;
-      const int d1 = ((Q1 + 64) & 127) - 64;
-      const int Q2 = (Q1 - d1) >> 7;
-      const int d2 = ((Q2 + 64) & 127) - 64;
-      const int d3 = (Q2 - d2) >> 7;
-      w[0] |= ((uint32_t)d0 & 0xFFu) << (8 * b);
-      w[1] |= ((uint32_t)d1 & 0xFFu) << (8 * b);
-      w[2] |= ((uint32_t)d2 & 0xFFu) << (8 * b);
-      w[3] |= ((uint32_t)d3 & 0xFFu) << (8 * b);
+      int dig[4];
+      stream_digits_of(__float2int_rn(ys[32 * g + k + 8 * b] * sc), k, dig);
+#pragma unroll
+      for (int dg = 0; dg < 4; ++dg) w[dg] |= ((uint32_t)dig[dg] & 0xFFu) << (8 * b);
     }
 #pragma unroll
     for (int dg = 0; dg < 4; ++dg) img[((g * 4 + dg) * 2 + (k >> 2)) * 4 + (k & 3)] = w[dg];

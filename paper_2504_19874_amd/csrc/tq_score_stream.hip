@@ -21,6 +21,7 @@
 // different times.)
 #include <cstring>
 
+#include "tq_score_digits.h"
 #include "tq_score_i8.h"
 
 namespace tq {
@@ -142,9 +143,7 @@ __global__ __launch_bounds__(512, 2) void score_stream_kernel(const StreamArgs a
     for (int i = 0; i < 4; ++i) b[i] = (int)(w & (0x01010101u << (4 * s + i)));
     return b;
   };
-  auto digits_sum = [&](const v4i& c) -> float {  // (D0 + 2^7 D1 + 2^14 D2 + 2^21 D3) / 128, D0 a multiple of 128
-    return (float)((((c[3] << 7) + c[2]) << 7) + c[1] + (c[0] >> 7));
-  };
+  auto digits_sum = [&](const v4i& c) -> float { return stream_digits_sum(c[0], c[1], c[2], c[3]); };
   v4i acc[T][NT][QB];
   auto clear = [&] {
 #pragma unroll
