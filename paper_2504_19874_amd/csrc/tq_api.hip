@@ -181,10 +181,9 @@ bool quantize_h2(const tq_params* p, const void* x, bool bf16, int64_t n, int64_
   const size_t esz = bf16 ? 2 : 4;
   const int words_per_row = (d / 32) * p->bits_mse;
   const Codebook cb = make_codebook(p);
-  const bool cut = !prod || two_piece_x_serves_prod(d, p->bits_mse);
   for (int64_t r0 = 0; r0 < n; r0 += chunk) {
     const int64_t rows = n - r0 < chunk ? n - r0 : chunk;
-    if (launch_h2_split(static_cast<const char*>(x) + (size_t)r0 * ldx * esz, bf16, cut, ldx, rows, d, norm != nullptr, w_inv, xp,
+    if (launch_h2_split(static_cast<const char*>(x) + (size_t)r0 * ldx * esz, bf16, ldx, rows, d, norm != nullptr, w_inv, xp,
                         norm ? norm + r0 : nullptr, fac, esc, stream) != hipSuccess)
       return true;
     H2Quant a;
@@ -589,7 +588,7 @@ bool rotate_h2(const tq_params* p, const float* q, int64_t ldq, int64_t nq, floa
   float* const fac = reinterpret_cast<float*>(base + round_up((size_t)nq * d * 4, 256));
   for (int m = 0; m < (qs != nullptr ? 2 : 1); ++m) {
     const float* const w_inv = h2_image_scale(img, d, m);
-    if (launch_h2_split(m == 0 ? q : qr, false, false, m == 0 ? ldq : d, nq, d, false, w_inv, base, nullptr, fac, nullptr, s) != hipSuccess) return false;
+    if (launch_h2_split(m == 0 ? q : qr, false, m == 0 ? ldq : d, nq, d, false, w_inv, base, nullptr, fac, nullptr, s) != hipSuccess) return false;
     H2Quant a;
     std::memset(&a, 0, sizeof(a));
     a.W = h2_image(img, d, m); a.w_inv = w_inv; a.X = base; a.npx = 2; a.d = d; a.n = nq; a.fac = fac; a.out = m == 0 ? qr : qs;

@@ -94,10 +94,8 @@ bool h2_codebook_serves(int bits, const Codebook& cb);
 size_t h2_image_bytes(int M, int d);                         // pieces only
 hipError_t launch_h2_image(const float* W, int64_t ldw, int M, int d, void* image, float* w_inv, hipStream_t s);
 hipError_t launch_h2_max(const float* W, int64_t ldw, int M, int d, uint32_t* max_bits, hipStream_t s);  // bits of the largest magnitude
-// rows of x as pieces, their norms and factors; w_inv: of the matrix they will meet.  cut: an fp32 value is first rounded
-// to its two leading bf16 pieces, the reading of fp32 vectors that the other quantisation kernels have (a decision within
-// 2^-18.6 |x| / sqrt(d) of a cell boundary then does not depend on the batch size); the pieces here hold that exactly.
-hipError_t launch_h2_split(const void* x, bool bf16, bool cut, int64_t ldx, int64_t n, int d, bool normalise, const float* w_inv, void* pieces,
+// rows of x as pieces, their norms and factors; w_inv: of the matrix they will meet
+hipError_t launch_h2_split(const void* x, bool bf16, int64_t ldx, int64_t n, int d, bool normalise, const float* w_inv, void* pieces,
                            float* norm, float* fac, float* esc, hipStream_t s);
 int h2_part_tiles(int d, int64_t n);                         // rows of H2Quant::part
 int64_t h2_full_rows(int d, int64_t rows);                   // the largest useful pass over at most `rows` vectors

@@ -1,0 +1,44 @@
+"""How much of an fp32 vector the quantisers read: with Pi = I and no normalisation the rotated coordinates are the
+vector itself, and coordinates a little beside the cell boundaries show the bits that an operand form leaves out."""
+import numpy as np
+import pytest
+import torch
+
+from tests import test_gpu_parity as T
+from oracle import turboquant_oracle as o
+
+pytestmark = pytest.mark.gpu
+
+tq = pytest.importorskip("paper_2504_19874_amd")
+
+
+def check_decisions(d, bits, prod, n, beside):
+    """beside(t): fp32 values next to the boundaries t, whose cells the quantiser has to tell apart."""
+    c, t, _ = tq.tq_build_codebook(d, bits)
+    eye = torch.eye(d)
+    p = tq.Params(d, bits, eye, eye if prod else None, c, t).reserve(n)
+    rng = np.random.default_rng(d + n)
+    x = beside(t[rng.integers(0, t.size, size=(n, d))], rng)
+    assert x.dtype == np.float32
+    idx = torch.zeros((n, p.idx_words), dtype=torch.int32, device=T.DEV)
+    if prod:
+        qjl = torch.zeros((n, p.qjl_words), dtype=torch.int32, device=T.DEV)
+        gamma = torch.zeros(n, device=T.DEV)
+        tq.tq_quantize_prod(p, T.dev(x), idx, qjl, gamma, None)
+    else:
+        tq.tq_quantize_mse(p, T.dev(x), idx, None)
+    got = o.unpack_planes(T.words(idx), bits, d)
+    want = np.searchsorted(t, x, side="right")  # on a boundary: the upper cell
+    assert np.array_equal(got, want), f"{(got != want).sum()} of {got.size} decisions"
+
+
+def two_pieces(t, rng):
+    """2^-20 beside a boundary: what two fp16 pieces of the vector (22 bits) keep."""
+    e = np.float32(2.0**-20) * rng.choice(np.float32([-1, 1]), size=t.shape)
+    return np.where(t == 0, e, t * (1 + e)).astype(np.float32)
+
+
+@pytest.mark.parametrize("d,bits,prod,n", [(512, 4, False, 100), (768, 4, False, 5000), (1024, 3, False, 300), (1536, 4, False, 70),
+                                           (160, 3, True, 700), (1024, 3, True, 130), (3072, 4, False, 66)])
+def test_two_pieces_of_fp32_vectors(d, bits, prod, n):
+    check_decisions(d, bits, prod, n, two_pieces)
