@@ -36,11 +36,14 @@ constexpr int64_t kChunkRows = 65536;  // rows per pass of the quantiser at most
 // offsets from a 64-bit tile base (up to 256 rows of ld * 4 bytes)
 constexpr int64_t kMaxRowStride = int64_t(1) << 22;
 constexpr int64_t kRowsQuantMax = 64;  // at most this many long vectors take the matrix-vector route of the quantiser
-// That route reads every matrix once per block of four vectors, the tiled contraction once per 128: it wins while
-// blocks x d^2 x matrices stays below about 4e7 elements (measured: d = 1536, Alg. 1: 14 / 18 / 52 us for 1 / 8 / 64
-// vectors against 78; d = 3072, Alg. 2: 47 / 112 us for 1 / 8 against 223, but 722 us for 64).
-// (The dequantiser's route reads both matrices in one kernel and has no second stage: d = 1536, Alg. 1: 10 / 12 / 50
-// us for 1 / 8 / 64 vectors against 108; d = 3072, Alg. 2: 17 us for one against 153; its bound is twice as wide.)
+// That route reads every matrix once per block of four vectors, plain fp32 multiply-adds; the fp16 contraction once per
+// tile, and holds 22 bits of a factor.  The line between them, blocks x d^2 x matrices, lies at 4e7 elements: up to there
+// fp32 vectors keep all their bits (mean error of a rotated coordinate 0.8 - 1.2e-7 sigma, 2.2 - 4.2e-7 on the contraction)
+// at no more than a few us.  Measured, this route / the contraction in us:
+//   Alg. 1  d = 1024: 64 vectors 15.1 / 12.4; 1536: 8 vectors 13.3, 32 16.5 / 14.5, 64 22.3 / 15.4; 3072: 4 24.1, 8 27.7 / 22.3,
+//           16 29.6 / 22.4; 4096: 1 31.4 / 29.0, 8 35.6 / 29.6
+//   Alg. 2  d = 1024: 64 27.8 / 23.3; 1536: 32 29.2 / 29.7; 3072: 4 35.8, 8 43.8 / 40.6; 4096: 1 45.7 / 50.0, 4 52.9 / 51.4
+// (The dequantiser's route reads both matrices in one kernel and has no second stage; its bound is twice as wide.)
 bool rows_route_serves(int64_t n, int d, int matrices, int64_t limit = 150) {
   return n <= kRowsQuantMax && d >= 512 && d <= 4096 && ((n + 3) / 4) * (int64_t)d * d * matrices <= limit * 512 * 512;
 }
@@ -281,7 +284,7 @@ tq_status quantize_common(const tq_params* p, const void* x, int32_t dtype, int6
   if (!prod) {
     // a handful of long vectors: a matrix-vector product per vector instead of the tiled contraction's serial k-loop,
     // when the workspace holds the rotated vectors
-    if (rows_route_serves(n, d, 1, 54) && !fp32_mfma_only(p)) {
+    if (rows_route_serves(n, d, 1) && !fp32_mfma_only(p)) {
       Workspace ws{static_cast<char*>(p->workspace), p->workspace_bytes, 0};
       if (float* const yw = static_cast<float*>(ws.take((size_t)n * d * sizeof(float))); yw != nullptr)
         return from_hip(launch_quant_rows(p->bits_mse, dtype == TQ_BF16, x, ldx, n, d, p->Pi, make_codebook(p), yw, idx, norm, stream));
@@ -295,7 +298,7 @@ tq_status quantize_common(const tq_params* p, const void* x, int32_t dtype, int6
   }
 
   // a handful of long vectors: the matrix-vector route (see above), the sketch included
-  if (rows_route_serves(n, d, 2, 90) && !fp32_mfma_only(p)) {
+  if (rows_route_serves(n, d, 2) && !fp32_mfma_only(p)) {
     Workspace ws2{static_cast<char*>(p->workspace), p->workspace_bytes, 0};
     float* const yw = static_cast<float*>(ws2.take((size_t)n * d * sizeof(float)));
     float* const ew = static_cast<float*>(ws2.take((size_t)n * d * sizeof(float)));

@@ -42,3 +42,15 @@ def two_pieces(t, rng):
                                            (160, 3, True, 700), (1024, 3, True, 130), (3072, 4, False, 66)])
 def test_two_pieces_of_fp32_vectors(d, bits, prod, n):
     check_decisions(d, bits, prod, n, two_pieces)
+
+
+def all_bits(t, rng):
+    """The boundary itself and the fp32 value below it: 24 bits."""
+    return np.where(rng.random(t.shape) < 0.5, t, np.nextafter(t, np.float32(-1))).astype(np.float32)
+
+
+@pytest.mark.parametrize("d,bits,prod,n", [(512, 4, False, 64), (1024, 4, False, 64), (1536, 4, False, 61), (3072, 3, False, 16), (4096, 4, False, 1),
+                                           (4096, 3, False, 8), (1024, 3, True, 64), (1536, 4, True, 32), (3072, 4, True, 8), (4096, 3, True, 4)])
+def test_few_long_vectors_in_fp32(d, bits, prod, n):
+    """Up to 64 vectors of 512 coordinates and more, while their blocks of four times d^2 stay within the limit: plain fp32."""
+    check_decisions(d, bits, prod, n, all_bits)
