@@ -278,7 +278,7 @@ tq_status quantize_common(const tq_params* p, const void* x, int32_t dtype, int6
   // below d = 512 a large batch is bound by the passes over memory that the fp16 contraction adds (pieces of the vectors and of
   // the residual), and the contraction that splits its vectors on the fly is the faster one (2 + 1 bits, 60000 / 8000 vectors: d = 256
   // 87 against 147 us / 30 against 24; d = 384 169 against 197 / 40 against 32; d = 512 284 against 223)
-  const bool h2_serves = pieces && (d >= 512 || n <= 16384) && h2_codebook_serves(p->bits_mse, a.cb) && (!prod || aligned16(p->SPiT));
+  const bool h2_serves = a.pieces && (d >= 512 || n <= 16384) && h2_codebook_serves(p->bits_mse, a.cb) && (!prod || aligned16(p->SPiT));
   const NKind nk = dtype == TQ_F32 ? N_F32 : N_BF16;
 
   if (!prod) {

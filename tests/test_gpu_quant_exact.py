@@ -54,3 +54,9 @@ def all_bits(t, rng):
 def test_few_long_vectors_in_fp32(d, bits, prod, n):
     """Up to 64 vectors of 512 coordinates and more, while their blocks of four times d^2 stay within the limit: plain fp32."""
     check_decisions(d, bits, prod, n, all_bits)
+
+
+@pytest.mark.parametrize("d,bits,n", [(32, 2, 100), (64, 3, 1000), (96, 3, 65), (384, 4, 3000), (416, 4, 129), (64, 3, 16384)])
+def test_small_residuals_in_fp32(d, bits, n):
+    """Alg. 2 of fp32 vectors whose residual is small: the rotation stays on the fp32 instructions whatever the batch size."""
+    check_decisions(d, bits, True, n, all_bits)
