@@ -252,11 +252,12 @@ size_t tq_images_bytes(int32_t d);
 tq_status tq_build_images(const tq_params* p, void* images, void* stream);
 
 /* The same for tq_dequantize at d other than 128 (0 bytes, nothing done, at d = 128): Pi^T and S^T as the tiles its
- * workgroups stage, read from p->Pi and p->S.  They lie behind the images above: `images` is a buffer of
+ * workgroups stage, and S for the sketch of many queries in tq_score, read from p->Pi and p->S.  They lie behind the
+ * images above: `images` is a buffer of
  * tq_images_bytes(d) + tq_dequant_images_bytes(d) bytes, and TQ_FLAG_DEQUANT_IMAGES in params.flags says that
  * params.images is such a buffer with both parts filled.  Without the flag tq_dequantize makes these tiles in the
  * workspace in every call, where it has room (8 d^2 + 256 bytes), or takes kernels that do without, the same up to
- * rounding. */
+ * rounding; tq_score likewise for more than 64 queries (tq_score_workspace_bytes counts the room). */
 size_t tq_dequant_images_bytes(int32_t d);
 tq_status tq_build_dequant_images(const tq_params* p, void* images, void* stream);
 

@@ -128,17 +128,42 @@ struct Workspace {
 };
 
 // params.images at every d other than 128: [Pi][S Pi^T] as two fp16 pieces (4 d^2 bytes each), then the inverse scales of
-// the two, each followed by a word that tq_build_images uses; with TQ_FLAG_DEQUANT_IMAGES behind those (tq_images_bytes)
-// [Pi^T][S^T] in the order in which codes are decoded and the scales of these
-const char* h2_images(const tq_params* p) { return p->d != 128 ? static_cast<const char*>(p->images) : nullptr; }
+// the two, each followed by a word that tq_build_images uses.  With TQ_FLAG_DEQUANT_IMAGES behind those (tq_images_bytes)
+// [Pi^T][S^T] in the order in which codes are decoded, [S] as it is, and the scales of these.
+enum H2Image { IMG_PI = 0, IMG_SPIT = 1, IMG_CODE_PI = 2, IMG_CODE_S = 3, IMG_S = 4 };
+const char* h2_images(const tq_params* p) { return p->d != 128 && aligned16(p->images) ? static_cast<const char*>(p->images) : nullptr; }
+const char* h2_dequant_images(const tq_params* p) { return (p->flags & TQ_FLAG_DEQUANT_IMAGES) != 0 ? h2_images(p) : nullptr; }
 const char* h2_image(const void* images, int d, int which) {
-  return static_cast<const char*>(images) + (which >= 2 ? tq_images_bytes(d) : 0) + (which & 1) * h2_image_bytes(d, d);
+  return static_cast<const char*>(images) + (which >= 2 ? tq_images_bytes(d) : 0) + (which >= 2 ? which - 2 : which) * h2_image_bytes(d, d);
 }
 float* h2_image_scale(const void* images, int d, int which) {
-  return reinterpret_cast<float*>(const_cast<char*>(h2_image(images, d, which & 2)) + 2 * h2_image_bytes(d, d)) + 2 * (which & 1);
+  const char* const at = which >= 2 ? h2_image(images, d, 5) + 8 * (which - 2) : h2_image(images, d, 0) + 2 * h2_image_bytes(d, d) + 8 * which;
+  return reinterpret_cast<float*>(const_cast<char*>(at));
 }
 // without them: the images a call makes for itself in the workspace
 size_t h2_own_images_bytes(int d, bool prod) { return kH2ImageHeader + (prod ? 2 : 1) * h2_image_bytes(d, d); }
+
+constexpr int64_t kMatvecQueries = 64;  // up to here queries are rotated by matrix-vector products
+
+// Pi q and S q of many queries on the fp16 matrix cores, from the images of Pi and S or from ones made here.  (The error of
+// a rotated coordinate is 0.62 of the fp32 instructions' at every d from 256 to 4096, 4.4e-7 against 7.0e-7 of its size at
+// d = 1536; 1000 queries take 29 us against 111 there, 63 against 217 at d = 3072; an image made here 20 and 40.)
+struct RotateSpace {
+  size_t pieces, fac, image[2], total;  // offsets; image: 0 where params.images holds it (then no room is taken)
+  RotateSpace(const tq_params* p, int64_t nq, bool prod) {
+    const size_t d = (size_t)p->d;
+    fac = round_up((size_t)nq * d * 4, 256);
+    total = fac + round_up((size_t)nq * 4, 256);
+    pieces = 0;  // first
+    image[0] = image[1] = 0;
+    const bool own[2] = {h2_images(p) == nullptr, prod && h2_dequant_images(p) == nullptr};
+    for (int m = 0; m < 2; ++m)
+      if (own[m]) {
+        image[m] = total + kH2ImageHeader;
+        total += kH2ImageHeader + round_up(h2_image_bytes(p->d, p->d), 256);
+      }
+  }
+};
 
 // The quantiser on the fp16 matrix cores: passes of as many vectors as the workspace holds the pieces of.  False when it
 // holds too few (nothing has been launched then).
@@ -147,10 +172,13 @@ bool quantize_h2(const tq_params* p, const void* x, bool bf16, int64_t n, int64_
   const int d = p->d;
   Workspace ws{static_cast<char*>(p->workspace), p->workspace_bytes, 0};
   const char* pi_img = h2_images(p);
-  const bool build = pi_img == nullptr || !aligned16(pi_img);
-  const char* s_img = h2_image(pi_img, d, 1);
-  float* w_inv = h2_image_scale(pi_img, d, 0);  // of the second image two floats on
-  if (build) {  // the same bits as tq_build_images makes
+  const bool build = pi_img == nullptr;
+  const char* s_img;
+  float* w_inv;  // of the second image two floats on
+  if (!build) {
+    s_img = h2_image(pi_img, d, IMG_SPIT);
+    w_inv = h2_image_scale(pi_img, d, IMG_PI);
+  } else {  // the same bits as tq_build_images makes
     char* const own = static_cast<char*>(ws.take(h2_own_images_bytes(d, prod)));
     if (own == nullptr) return false;
     w_inv = reinterpret_cast<float*>(own);
@@ -383,8 +411,9 @@ tq_status tq_build_images(const tq_params* p, void* images, void* stream) {
     if (!aligned16(images) || !aligned16(p->Pi) || (p->SPiT != nullptr && !aligned16(p->SPiT))) return TQ_ERR_UNSUPPORTED;
     hipStream_t s = static_cast<hipStream_t>(stream);
     const int d = p->d;
-    if (launch_h2_image(p->Pi, d, d, d, images, h2_image_scale(images, d, 0), s) != hipSuccess) return TQ_ERR_HIP;
-    if (p->SPiT != nullptr && launch_h2_image(p->SPiT, d, d, d, const_cast<char*>(h2_image(images, d, 1)), h2_image_scale(images, d, 1), s) != hipSuccess)
+    if (launch_h2_image(p->Pi, d, d, d, images, h2_image_scale(images, d, IMG_PI), s) != hipSuccess) return TQ_ERR_HIP;
+    if (p->SPiT != nullptr &&
+        launch_h2_image(p->SPiT, d, d, d, const_cast<char*>(h2_image(images, d, IMG_SPIT)), h2_image_scale(images, d, IMG_SPIT), s) != hipSuccess)
       return TQ_ERR_HIP;
     return TQ_OK;
   }
@@ -401,7 +430,7 @@ tq_status tq_build_images(const tq_params* p, void* images, void* stream) {
 
 size_t tq_dequant_images_bytes(int32_t d) {
   if (d == 128 || d <= 0 || d % 32 != 0 || d > 16384) return 0;
-  return 2 * h2_image_bytes(d, d) + 256;
+  return 3 * h2_image_bytes(d, d) + 256;
 }
 
 tq_status tq_build_dequant_images(const tq_params* p, void* images, void* stream) {
@@ -411,8 +440,12 @@ tq_status tq_build_dequant_images(const tq_params* p, void* images, void* stream
   if (!aligned16(images)) return TQ_ERR_UNSUPPORTED;
   const hipStream_t s = static_cast<hipStream_t>(stream);
   const int d = p->d;
-  if (launch_code_image(p->Pi, d, const_cast<char*>(h2_image(images, d, 2)), h2_image_scale(images, d, 2), s) != hipSuccess ||
-      (p->S != nullptr && launch_code_image(p->S, d, const_cast<char*>(h2_image(images, d, 3)), h2_image_scale(images, d, 3), s) != hipSuccess))
+  auto image = [&](int which) { return const_cast<char*>(h2_image(images, d, which)); };
+  if (launch_code_image(p->Pi, d, image(IMG_CODE_PI), h2_image_scale(images, d, IMG_CODE_PI), s) != hipSuccess ||
+      (p->S != nullptr && launch_code_image(p->S, d, image(IMG_CODE_S), h2_image_scale(images, d, IMG_CODE_S), s) != hipSuccess))
+    return TQ_ERR_HIP;
+  // (an S that is not 16-byte aligned is refused wherever the last one is used)
+  if (p->S != nullptr && aligned16(p->S) && launch_h2_image(p->S, d, d, d, image(IMG_S), h2_image_scale(images, d, IMG_S), s) != hipSuccess)
     return TQ_ERR_HIP;
   return TQ_OK;
 }
@@ -462,7 +495,7 @@ size_t tq_workspace_bytes(const tq_params* p, int64_t n, int64_t nq, int32_t top
   if (topk > 0) bytes += 2 * round_up((size_t)(nq < 128 ? nq : 128) * 4096 * sizeof(float), 256);
   // candidates of a search by many queries, and their rotation
   if (topk > 0 && nq > 0 && n > 0) bytes += search_workspace_bytes(p->d, n, nq, topk) + 256;
-  bytes += round_up((size_t)nq * d * 4, 256) + 2 * round_up((size_t)nq * 4, 256) + 256;
+  if (nq > kMatvecQueries && p->d != 128) bytes += RotateSpace(p, nq, p->S != nullptr).total + 256;
   return bytes + 256;
 }
 
@@ -534,9 +567,9 @@ tq_status tq_dequantize(const tq_params* p, const uint32_t* idx, const uint32_t*
     const int d = p->d;
     const char *pit = nullptr, *sit = nullptr;
     float *pit_inv = nullptr, *sit_inv = nullptr;
-    if (const char* const img = h2_images(p); img != nullptr && aligned16(img) && (p->flags & TQ_FLAG_DEQUANT_IMAGES) != 0) {
-      pit = h2_image(img, d, 2), sit = h2_image(img, d, 3);
-      pit_inv = h2_image_scale(img, d, 2), sit_inv = h2_image_scale(img, d, 3);
+    if (const char* const img = h2_dequant_images(p); img != nullptr) {
+      pit = h2_image(img, d, IMG_CODE_PI), sit = h2_image(img, d, IMG_CODE_S);
+      pit_inv = h2_image_scale(img, d, IMG_CODE_PI), sit_inv = h2_image_scale(img, d, IMG_CODE_S);
     } else {
       Workspace ws{static_cast<char*>(p->workspace), p->workspace_bytes, 0};
       if (char* const own = static_cast<char*>(ws.take(h2_own_images_bytes(d, prod))); own != nullptr) {
@@ -580,21 +613,26 @@ tq_status tq_dequantize(const tq_params* p, const uint32_t* idx, const uint32_t*
 
 namespace {
 
-constexpr int64_t kMatvecQueries = 64;  // up to here queries are rotated by matrix-vector products
-
-// Pi q and S q = (S Pi^T) Pi q of many queries by the fp16 pieces of the images
-size_t rotate_workspace_bytes(int d, int64_t nq) { return round_up((size_t)nq * d * 4, 256) + 2 * round_up((size_t)nq * 4, 256); }
 bool rotate_h2(const tq_params* p, const float* q, int64_t ldq, int64_t nq, float* qr, float* qs, void* scratch, hipStream_t s) {
   const int d = p->d;
-  const char* const img = h2_images(p);
+  const RotateSpace sp(p, nq, qs != nullptr);
   char* const base = static_cast<char*>(scratch);
-  float* const fac = reinterpret_cast<float*>(base + round_up((size_t)nq * d * 4, 256));
+  float* const fac = reinterpret_cast<float*>(base + sp.fac);
   for (int m = 0; m < (qs != nullptr ? 2 : 1); ++m) {
-    const float* const w_inv = h2_image_scale(img, d, m);
-    if (launch_h2_split(m == 0 ? q : qr, false, m == 0 ? ldq : d, nq, d, false, w_inv, base, nullptr, fac, nullptr, s) != hipSuccess) return false;
+    const char* image;
+    float* w_inv;
+    if (sp.image[m] == 0) {
+      image = h2_image(h2_images(p), d, m == 0 ? IMG_PI : IMG_S);
+      w_inv = h2_image_scale(h2_images(p), d, m == 0 ? IMG_PI : IMG_S);
+    } else {
+      image = base + sp.image[m];
+      w_inv = reinterpret_cast<float*>(base + sp.image[m] - kH2ImageHeader);
+      if (launch_h2_image(m == 0 ? p->Pi : p->S, d, d, d, base + sp.image[m], w_inv, s) != hipSuccess) return false;
+    }
+    if (launch_h2_split(q, false, ldq, nq, d, false, w_inv, base + sp.pieces, nullptr, fac, nullptr, s) != hipSuccess) return false;
     H2Quant a;
     std::memset(&a, 0, sizeof(a));
-    a.W = h2_image(img, d, m); a.w_inv = w_inv; a.X = base; a.npx = 2; a.d = d; a.n = nq; a.fac = fac; a.out = m == 0 ? qr : qs;
+    a.W = image; a.w_inv = w_inv; a.X = base + sp.pieces; a.npx = 2; a.d = d; a.n = nq; a.fac = fac; a.out = m == 0 ? qr : qs;
     if (launch_h2_store(a, s) != hipSuccess) return false;
   }
   return true;
@@ -639,7 +677,7 @@ ScorePlan plan_score(const tq_params* p, bool prod, int n_groups, int q_per_grou
   if (pl.route == ScorePlan::R_BF3 && topk > 0 && !scores_given && n_groups == 1 &&
       search_applicable(p->bits_mse, prod, p->d, n_per_group, q_per_group, topk, make_codebook(p)))
     pl.search_bytes = search_workspace_bytes(p->d, n_per_group, nq, topk);
-  if (pl.q_bytes > 0 && nq > kMatvecQueries && h2_images(p) != nullptr && !fp32_mfma_only(p)) pl.rotate_bytes = rotate_workspace_bytes(p->d, nq);
+  if (pl.q_bytes > 0 && nq > kMatvecQueries && p->d != 128 && !fp32_mfma_only(p)) pl.rotate_bytes = RotateSpace(p, nq, prod).total;
   return pl;
 }
 
@@ -757,8 +795,8 @@ tq_status score_impl(const tq_params* p, Workspace ws, const float* q, int64_t l
       return TQ_ERR_HIP;
   } else {
     // queries into the rotated basis and the sketch basis: Pi q and S q
-    void* const rot = pl.rotate_bytes > 0 && aligned16(h2_images(p)) ? ws.take(pl.rotate_bytes) : nullptr;
-    if (rot != nullptr && ldq % 4 == 0) {
+    void* const rot = pl.rotate_bytes > 0 ? ws.take(pl.rotate_bytes) : nullptr;
+    if (rot != nullptr) {
       if (!rotate_h2(p, q, ldq, nq, qr, qs, rot, s)) return TQ_ERR_HIP;
     } else if (nq <= kMatvecQueries && d <= 4096) {
       if (launch_matvec_small(d, (int)nq, p->Pi, prod ? p->S : nullptr, q, ldq, qr, qs, s) != hipSuccess)
