@@ -5,7 +5,8 @@
 // far in LDS.  The first segment has no bar yet: the k-th largest of the 256 threads' own maxima is one (k threads hold a
 // score that high), found by ranking the maxima against each other, and only scores that reach it, little more than k, are
 // looked at again.  In later segments a score has to beat the k-th best pair, which a handful do.  The ones that pass are
-// appended to a list and ranked against it.  A few long rows (one query against a million codes) are cut into chunks, one
+// appended to a list and ranked against it.  Where they are many (equal scores, a row that rises), the k-th best of the
+// threads' best PAIRS is the bar instead: pairs are never equal, so at most k threads have any that reach it.  A few long rows (one query against a million codes) are cut into chunks, one
 // workgroup each, whose lists topk_merge_kernel joins in the same way.
 // (Before: a sorted list per thread, k rounds of arg-max to join them.  4 rows of 10^6 scores, k = 10: 35 + 30 us for the
 // chunks and the merge, 11.5 + 7.5 here; 16 rows, k = 64: 1.2 ms in all, 70 us here.)
@@ -16,7 +17,10 @@ namespace {
 
 constexpr int SEG = 8192;              // scores per segment
 constexpr int PER = SEG / 256;         // per thread
-constexpr int LIST = SEG + 64;         // all of a segment may pass (equal scores), and the k best before it
+constexpr int LIST = 64 + 64 * PER;    // the k best so far, and all that k threads hold
+// more than this many are not ranked against each other as they are (two rows of 50001 equal scores, whole segments ranked:
+// 144 ms; 54 us as it is, 39 for scores that differ, 163 for rising ones)
+constexpr int MANY = 512;
 
 struct TopkLds {
   float v[LIST];
@@ -26,7 +30,14 @@ struct TopkLds {
   uint32_t mx[256];
   uint32_t bar;
   int count;
+  unsigned long long pair_bar;
+  unsigned long long pairs[256];
 };
+
+// pairs in the order of better() as unsigned integers; 0 is below every one of them
+__device__ __forceinline__ unsigned long long pair_key(float v, int i) {
+  return (unsigned long long)ordered(v + 0.f) << 32 | (uint32_t)~i;  // + 0: a negative zero is equal to a positive one
+}
 
 // v[e]: this thread's scores of one segment, NaN where there is none; pair(e) fetches score and index of the e-th again (a
 // handful are asked for, and a register array cannot be indexed).  kept: pairs in best so far (uniform).  Afterwards best
@@ -41,7 +52,8 @@ __device__ int take_segment(TopkLds& s, const float (&v)[N], Pair pair, int k, i
     for (int e = 0; e < N; ++e) mx = fmaxf(mx, v[e]);  // ignores NaN
     bar = kth_of_maxima(mx, k, s.mx, &s.bar, tid);
   } else {
-    bar = s.best_v[k - 1];
+    // the next larger value: an equal score of a later segment has a later index and does not beat a kept one
+    bar = from_ordered(ordered(s.best_v[k - 1] + 0.f) + 1u);  // + 0: see pair_key
   }
   if (tid < kept) {
     s.v[tid] = s.best_v[tid];
@@ -49,18 +61,49 @@ __device__ int take_segment(TopkLds& s, const float (&v)[N], Pair pair, int k, i
   }
   if (tid == 0) s.count = kept;
   __syncthreads();
-  // (an equal score of a later segment has a later index and does not beat a kept one, but it may be ranked all the same)
   uint32_t pass = 0u;
 #pragma unroll
   for (int e = N - 1; e >= 0; --e) pass = pass + pass + (v[e] >= bar ? 1u : 0u);
-  while (pass != 0u) {
-    const int e = __builtin_ctz(pass);
-    pass &= pass - 1u;
-    const int pos = atomicAdd(&s.count, 1);
-    pair(e, s.v[pos], s.i[pos]);
+  if (pass != 0u) {
+    int pos = atomicAdd(&s.count, __builtin_popcount(pass));
+    for (uint32_t left = pass; left != 0u; left &= left - 1u, ++pos)
+      if (pos < LIST) pair(__builtin_ctz(left), s.v[pos], s.i[pos]);
   }
   __syncthreads();
-  const int n = s.count;
+  int n = s.count;
+  if (n > MANY) {  // uniform
+    unsigned long long key = 0;
+    for (uint32_t left = pass; left != 0u; left &= left - 1u) {
+      float pv;
+      int pi;
+      pair(__builtin_ctz(left), pv, pi);
+      const unsigned long long o = pair_key(pv, pi);
+      key = o > key ? o : key;
+    }
+    s.pairs[tid] = key;
+    if (tid == 0) s.pair_bar = ~0ull;
+    __syncthreads();  // everyone has read the count, too
+    int above = 0;
+#pragma unroll 4
+    for (int t = 0; t < 256; ++t) above += s.pairs[t] > key ? 1 : 0;
+    if (above < k) atomicMin(&s.pair_bar, key);
+    if (tid == 0) s.count = kept;
+    __syncthreads();
+    const unsigned long long pair_bar = s.pair_bar;
+    if (key >= pair_bar)
+      for (uint32_t left = pass; left != 0u; left &= left - 1u) {
+        float pv;
+        int pi;
+        pair(__builtin_ctz(left), pv, pi);
+        if (pair_key(pv, pi) >= pair_bar) {
+          const int pos = atomicAdd(&s.count, 1);  // below LIST: at most k threads come here with any
+          s.v[pos] = pv;
+          s.i[pos] = pi;
+        }
+      }
+    __syncthreads();
+    n = s.count;
+  }
   if (n == kept) return kept;  // uniform; nothing passed
   for (int c = tid; c < n; c += 256) {
     const float cv = s.v[c];

@@ -1,0 +1,76 @@
+"""Top-k over rows in which many scores pass for candidates: equal ones, rising ones, infinities and zeros of both signs."""
+import numpy as np
+import pytest
+import torch
+
+import workloads as W
+from tests import test_gpu_parity as T
+
+pytestmark = pytest.mark.gpu
+
+tq = pytest.importorskip("paper_2504_19874_amd")
+
+
+def rows(kind, n):
+    """Factors of one code's score, so that they are the scores up to rounding and a common sign."""
+    i = np.arange(n)
+    rng = np.random.default_rng(n)
+    return {"drawn": rng.uniform(1, 2, n), "rising": 1.0 + i / n, "falling": 2.0 - i / n, "equal": np.ones(n),
+            "ties at the end": np.where(rng.random(n) < 20 / n, 2.0, 0.0), "zeros": np.where(i % 2 == 0, -0.0, 0.0),
+            "steps": 1.0 + i // 1000, "period": 1.0 + (i % 1024 < 40) * i, "infinite": np.where(i % 3 == 0, np.inf, 1.0),
+            }[kind].astype(np.float32)
+
+
+def call(p, q, c, n, topk):
+    scores = torch.zeros((2, n), device=T.DEV)
+    top = torch.zeros((2, topk), dtype=torch.int32, device=T.DEV), torch.zeros((2, topk), device=T.DEV)
+    p.reserve_score(1, 2, n, False, True, topk)
+    run = lambda: tq.tq_score(p, q, 1, 2, c["idx"], None, None, c["norm"], n, scores, topk, *top)  # noqa: E731
+    run()
+    return scores, top, run
+
+
+def case(kind, n):
+    p = T.setup(128, 2, False)[0]
+    c = T._random_codes(p, 128, 2, False, 1, 3)
+    c["idx"] = c["idx"].repeat(n, 1).contiguous()
+    c["norm"] = T.dev(rows(kind, n))
+    return p, c
+
+
+@pytest.mark.parametrize("topk", [1, 10, 64])
+@pytest.mark.parametrize("n", [8192, 50001, 300000])  # one segment, a workgroup's several, chunks and their joining
+@pytest.mark.parametrize("kind", ["rising", "falling", "equal", "ties at the end", "zeros", "steps", "period", "infinite"])
+def test_many_candidates(kind, n, topk):
+    p, c = case(kind, n)
+    q = W.gaussian_queries(1, 128, 5, unit=False)
+    scores, (ti, tv), _ = call(p, T.dev(np.concatenate([q, -q])), c, n, topk)
+    s = scores.cpu().numpy()
+    for r in range(2):
+        want = np.argsort(-s[r], kind="stable")[:topk]  # equal scores by lower index
+        assert np.array_equal(ti[r].cpu().numpy(), want)
+        assert np.array_equal(tv[r].cpu().numpy(), s[r][want])
+
+
+@pytest.mark.parametrize("kind", ["rising", "equal", "ties at the end", "steps"])
+def test_their_cost_is_bounded(kind):
+    """50001 scores per row in one workgroup: within ten times a row of drawn scores (the quadratic ranking of whole segments
+    that this guards against takes thousands of times as long)."""
+    def us(kind):
+        p, c = case(kind, 50001)
+        q = W.gaussian_queries(1, 128, 5, unit=False)
+        _, _, run = call(p, T.dev(np.concatenate([q, -q])), c, 50001, 10)
+        e = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+        torch.cuda.synchronize()
+        best = float("inf")
+        for _ in range(5):
+            e[0].record()
+            run()
+            e[1].record()
+            torch.cuda.synchronize()
+            best = min(best, e[0].elapsed_time(e[1]) * 1e3)
+        return best
+
+    many, drawn = us(kind), us("drawn")
+    print(f"{kind}: {many:.0f} us, drawn {drawn:.0f} us")
+    assert many <= 10 * drawn + 20
