@@ -149,11 +149,13 @@ constexpr int64_t kMatvecQueries = 64;  // up to here queries are rotated by mat
 // a rotated coordinate is 0.62 of the fp32 instructions' at every d from 256 to 4096, 4.4e-7 against 7.0e-7 of its size at
 // d = 1536; 1000 queries take 29 us against 111 there, 63 against 217 at d = 3072; an image made here 20 and 40.)
 struct RotateSpace {
+  int64_t rows;                         // queries per pass
   size_t pieces, fac, image[2], total;  // offsets; image: 0 where params.images holds it (then no room is taken)
   RotateSpace(const tq_params* p, int64_t nq, bool prod) {
     const size_t d = (size_t)p->d;
-    fac = round_up((size_t)nq * d * 4, 256);
-    total = fac + round_up((size_t)nq * 4, 256);
+    rows = nq < 16384 ? nq : 16384;
+    fac = round_up((size_t)rows * d * 4, 256);
+    total = fac + round_up((size_t)rows * 4, 256);
     pieces = 0;  // first
     image[0] = image[1] = 0;
     const bool own[2] = {h2_images(p) == nullptr, prod && h2_dequant_images(p) == nullptr};
@@ -629,11 +631,14 @@ bool rotate_h2(const tq_params* p, const float* q, int64_t ldq, int64_t nq, floa
       w_inv = reinterpret_cast<float*>(base + sp.image[m] - kH2ImageHeader);
       if (launch_h2_image(m == 0 ? p->Pi : p->S, d, d, d, base + sp.image[m], w_inv, s) != hipSuccess) return false;
     }
-    if (launch_h2_split(q, false, ldq, nq, d, false, w_inv, base + sp.pieces, nullptr, fac, nullptr, s) != hipSuccess) return false;
-    H2Quant a;
-    std::memset(&a, 0, sizeof(a));
-    a.W = image; a.w_inv = w_inv; a.X = base + sp.pieces; a.npx = 2; a.d = d; a.n = nq; a.fac = fac; a.out = m == 0 ? qr : qs;
-    if (launch_h2_store(a, s) != hipSuccess) return false;
+    for (int64_t r0 = 0; r0 < nq; r0 += sp.rows) {
+      const int64_t rows = nq - r0 < sp.rows ? nq - r0 : sp.rows;
+      if (launch_h2_split(q + r0 * ldq, false, ldq, rows, d, false, w_inv, base + sp.pieces, nullptr, fac, nullptr, s) != hipSuccess) return false;
+      H2Quant a;
+      std::memset(&a, 0, sizeof(a));
+      a.W = image; a.w_inv = w_inv; a.X = base + sp.pieces; a.npx = 2; a.d = d; a.n = rows; a.fac = fac; a.out = (m == 0 ? qr : qs) + r0 * d;
+      if (launch_h2_store(a, s) != hipSuccess) return false;
+    }
   }
   return true;
 }

@@ -17,6 +17,7 @@
 // 1000 queries, 10^6 codes, k = 10, d = 1536, 4 bits: 3.5 ms, 9.9 with every score from the exact kernel; 3.2 of it are
 // the find kernel's.  500 queries, 30000 codes, k = 64, d = 512: 156 us (284 with 4096 codes in the sample: the gathering
 // overflowed).
+#include <algorithm>
 #include <cmath>
 
 #include "tq_bf3.h"
@@ -296,7 +297,7 @@ int64_t sample_codes(int64_t n, int topk) {
 }
 
 struct SearchSpace {
-  size_t r, s, sample, list_u, list_i, top_v, top_i, inv, e1, e2, count, flags, total;
+  size_t r, s, sample, list_u, list_i, top_v, top_i, inv, e1, e2, count, total;
   SearchSpace(int d, int64_t n, int64_t nq, int topk) {
     size_t at = 0;
     auto take = [&](size_t bytes) {
@@ -315,10 +316,19 @@ struct SearchSpace {
     e1 = take((size_t)nq * 4);
     e2 = take((size_t)nq * 4);
     count = take((size_t)nq * 4);
-    flags = take((size_t)nq * 4);
     total = at;
   }
 };
+
+// Queries per block: their lists (78 KB a query at k = 10 and 10^6 codes, of which 40 the sample's scores) stay below
+// 512 MB, 1000 queries at k = 64 and 10^6 codes among it; at least 64, and blocks of about the same size.
+int64_t block_queries(int d, int64_t n, int64_t nq, int topk) {
+  const int64_t one = (int64_t)SearchSpace(d, n, 64, topk).total / 64 + 1;
+  const int64_t most = std::max<int64_t>(64, (int64_t(512) << 20) / one / 128 * 128);
+  if (nq <= most) return nq;
+  const int64_t blocks = (nq + most - 1) / most;
+  return std::min(most, ((nq + blocks - 1) / blocks + 127) / 128 * 128);
+}
 
 template <int BITS, bool PROD>
 hipError_t launch_select(const SelectArgs& a, int nq, hipStream_t s) {
@@ -330,19 +340,9 @@ hipError_t launch_select(const SelectArgs& a, int nq, hipStream_t s) {
   return hipGetLastError();
 }
 
-}  // namespace
-
-bool search_applicable(int bits, bool prod, int d, int64_t n, int nq, int topk, const Codebook& cb) {
-  return topk >= 1 && topk <= 64 && nq > 0 && n >= 8192 && n <= 0x7fffffff && d % 128 == 0 && d <= 4096 && (bits > 0 || prod) && code_gemm_serves(bits, cb);
-}
-
-size_t search_workspace_bytes(int d, int64_t n, int64_t nq, int topk) { return SearchSpace(d, n, nq, topk).total; }
-
-hipError_t launch_search(const SearchArgs& a, const Codebook& cb, void* workspace, const int32_t** flags, hipStream_t s) {
+hipError_t launch_block(const SearchArgs& a, const Codebook& cb, char* base, int32_t* flags, hipStream_t s) {
   const SearchSpace sp(a.d, a.n, a.nq, a.topk);
-  char* const base = static_cast<char*>(workspace);
   auto at = [&](size_t o) { return static_cast<void*>(base + o); };
-  *flags = static_cast<const int32_t*>(at(sp.flags));
   const float sqrt_d = std::sqrt((float)a.d);
   SearchFactors f;
   f.c_rel = f.c_norm = 0.f;
@@ -357,7 +357,7 @@ hipError_t launch_search(const SearchArgs& a, const Codebook& cb, void* workspac
   hipLaunchKernelGGL(search_prepare_kernel, dim3((unsigned)a.nq), dim3(256), 0, s, a.d, a.bits > 0 ? a.qr : nullptr, a.prod ? a.qs : nullptr, f,
                      static_cast<uint32_t*>(at(sp.r)), static_cast<uint32_t*>(at(sp.s)), static_cast<float*>(at(sp.inv)),
                      static_cast<float*>(at(sp.e1)), static_cast<float*>(at(sp.e2)), static_cast<int32_t*>(at(sp.count)),
-                     static_cast<int32_t*>(at(sp.flags)));
+                     flags);
   if (const hipError_t e = hipGetLastError(); e != hipSuccess) return e;
 
   const int64_t m = sample_codes(a.n, a.topk), ld = (m + 3) / 4 * 4;
@@ -376,7 +376,7 @@ hipError_t launch_search(const SearchArgs& a, const Codebook& cb, void* workspac
 
   SelectArgs g;
   g.qr = a.qr; g.qs = a.qs; g.e1 = c.e1; g.e2 = c.e2; g.d = a.d; g.topk = a.topk; g.idx = a.idx; g.qjl = a.qjl; g.gamma = a.gamma; g.norm = a.norm;
-  g.kappa = a.kappa; g.list_u = c.list_u; g.list_i = c.list_i; g.count = c.count; g.flags = static_cast<int32_t*>(at(sp.flags));
+  g.kappa = a.kappa; g.list_u = c.list_u; g.list_i = c.list_i; g.count = c.count; g.flags = flags;
   g.out_idx = a.topk_idx; g.out_val = a.topk_val; g.cb = cb;
   switch (a.bits * 2 + (a.prod ? 1 : 0)) {
     case 1: return launch_select<0, true>(g, a.nq, s);
@@ -390,6 +390,33 @@ hipError_t launch_search(const SearchArgs& a, const Codebook& cb, void* workspac
     case 9: return launch_select<4, true>(g, a.nq, s);
     default: return hipErrorInvalidValue;
   }
+}
+
+}  // namespace
+
+bool search_applicable(int bits, bool prod, int d, int64_t n, int nq, int topk, const Codebook& cb) {
+  return topk >= 1 && topk <= 64 && nq > 0 && n >= 8192 && n <= 0x7fffffff && d % 128 == 0 && d <= 4096 && (bits > 0 || prod) && code_gemm_serves(bits, cb);
+}
+
+size_t search_workspace_bytes(int d, int64_t n, int64_t nq, int topk) {
+  return align256((size_t)nq * 4) + SearchSpace(d, n, block_queries(d, n, nq, topk), topk).total;
+}
+
+hipError_t launch_search(const SearchArgs& a, const Codebook& cb, void* workspace, const int32_t** flags, hipStream_t s) {
+  int32_t* const all_flags = static_cast<int32_t*>(workspace);  // [nq], then the space of a block
+  *flags = all_flags;
+  const int64_t block = block_queries(a.d, a.n, a.nq, a.topk);
+  for (int64_t q0 = 0; q0 < a.nq; q0 += block) {
+    SearchArgs b = a;
+    b.nq = (int)std::min(block, a.nq - q0);
+    if (a.qr != nullptr) b.qr += q0 * a.d;
+    if (a.qs != nullptr) b.qs += q0 * a.d;
+    b.topk_idx += q0 * a.topk;
+    if (a.topk_val != nullptr) b.topk_val += q0 * a.topk;
+    if (const hipError_t e = launch_block(b, cb, static_cast<char*>(workspace) + align256((size_t)a.nq * 4), all_flags + q0, s); e != hipSuccess)
+      return e;
+  }
+  return hipSuccess;
 }
 
 }  // namespace tq
