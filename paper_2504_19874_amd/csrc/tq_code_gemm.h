@@ -31,7 +31,7 @@ hipError_t launch_code_dequant(int bits, bool prod, const void* pit_image, const
                                float* out, int64_t ldo, float kappa, const Codebook& cb, hipStream_t s);
 
 // The first pass of a search: scores of all codes from ONE piece of every factor, each within
-//     eps = nu (e1 + kappa gamma e2)
+//     eps = |nu| (e1 + kappa |gamma| e2)
 // of the exact one.  sample != NULL: score - eps of codes 0, code_step, 2 code_step, ... (n of them) to sample[query][ld_sample].
 // Otherwise every (score + eps, code) with score + eps >= bar[query] is appended to the query's list; count may pass cap.
 struct CodeSearch {

@@ -2,7 +2,7 @@
 // work of evaluating every score to full precision.
 //
 // 1. prepare     every query's rotated coordinates as ONE fp16 piece, and a bound of what that leaves out: with the codes'
-//                centroids as one piece too, a score is off by at most eps = nu (e1 + kappa gamma e2),
+//                centroids as one piece too, a score is off by at most eps = |nu| (e1 + kappa |gamma| e2),
 //                  e1 = (|q - q^| + r |q^|) sqrt(d) max |c|,   e2 = (|s - s^| + a |s|) sqrt(d)
 //                (Cauchy-Schwarz; r: largest relative error of a centroid's piece, plus a for the fp32 sums).
 // 2. sample      score - eps of some thousand codes, evenly spaced; the k-th best of a query is a bar that its k-th best
@@ -169,8 +169,8 @@ __global__ __launch_bounds__(256) void search_select_kernel(const SelectArgs a) 
       if (c < total) {
         const int64_t row = a.list_i[q * CAP + c];
         const float nu = a.norm != nullptr ? a.norm[row] : 1.f;
-        float eps = nu * e1;
-        if (PROD) eps = fmaf(nu * (a.kappa * a.gamma[row]), e2, eps);
+        float eps = fabsf(nu) * e1;
+        if (PROD) eps = fmaf(fabsf(nu * (a.kappa * a.gamma[row])), e2, eps);
         top[i] = a.list_u[q * CAP + c];
         mx = fmaxf(mx, fmaf(-2.f, eps, top[i]));
       }

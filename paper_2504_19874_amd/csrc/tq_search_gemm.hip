@@ -6,8 +6,8 @@
 // its steps and its comparisons and no round trip to memory (128 coordinates are only four steps).  Within a step the
 // fragments of the next 16 k are read, and the codes of the next step decoded, between the matrix instructions, in pinned order.
 //
-// A score is compared as it lies in the accumulator: nu (acc A + E1 + kappa gamma E2) >= bar is acc >= (bar / nu - E1 -
-// kappa gamma E2) / A, two or three instructions per score and no multiplication of the score itself; what passes is
+// A score is compared as it lies in the accumulator: nu (acc A + E1 + kappa |gamma| E2) >= bar is acc >= (bar / nu - E1 -
+// kappa |gamma| E2) / A for nu > 0 (the others pass to the second test), two or three instructions per score and no multiplication of the score itself; what passes is
 // evaluated and tested again before it goes to the query's list.  That is a round trip to a counter in memory, with dozens
 // per tile more than a short tile itself takes: they are gathered in LDS, the counters are asked for all of them at once at
 // the end of the next tile, and the pairs stored at the end of the one after that (d = 128, 10^6 codes, 1000
@@ -368,7 +368,7 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void search_gemm_kernel(const Sear
       kg[u] = HAVE_S ? cs[3 * TN + c0 + 32 * u] : 0.f;
       const float per = nu * fac;
       inv[u] = per > 0.f ? 1.f / per : __builtin_nanf("");
-      rest[u] = HAVE_P ? 1.f : 1.f / fac;
+      rest[u] = HAVE_P ? 1.f : 1.f / fabsf(fac);
     }
 #pragma unroll
     for (int t = 0; t < TW; ++t)
@@ -383,8 +383,8 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void search_gemm_kernel(const Sear
         auto exact = [&](int u, int e, float sign) {  // score + sign * its error bound
           const float* const q = query_s + m + e;
           const float nu = cs[2 * TN + c0 + 32 * u], fac = cs[TN + c0 + 32 * u];
-          float eps = nu * q[4 * TM];
-          if (HAVE_S) eps = fmaf(nu * kg[u], q[5 * TM], eps);
+          float eps = fabsf(nu) * q[4 * TM];
+          if (HAVE_S) eps = fmaf(fabsf(nu * kg[u]), q[5 * TM], eps);
           return fmaf(acc[t][u][4 * k + e] * (nu * fac), q[3 * TM], sign * eps);
         };
         if constexpr (!FIND) {
@@ -404,7 +404,7 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void search_gemm_kernel(const Sear
             uint64_t maybe[4];
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-              float bound = HAVE_S ? fmaf(d2[e], kg[u], d1[e]) : d1[e];
+              float bound = HAVE_S ? fmaf(d2[e], fabsf(kg[u]), d1[e]) : d1[e];
               if (!HAVE_P) bound *= rest[u];
               maybe[e] = __builtin_amdgcn_ballot_w64(!(acc[t][u][4 * k + e] < fmaf(b[e], inv[u], -bound)));
             }

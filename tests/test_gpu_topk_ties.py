@@ -74,3 +74,16 @@ def test_their_cost_is_bounded(kind):
     many, drawn = us(kind), us("drawn")
     print(f"{kind}: {many:.0f} us, drawn {drawn:.0f} us")
     assert many <= 10 * drawn + 20
+
+
+@pytest.mark.parametrize("d,bits,prod", [(128, 2, True), (256, 3, False), (384, 0, True), (512, 1, True)])
+def test_search_with_scalars_of_both_signs(d, bits, prod):
+    """Norms and residual norms are lengths, but nothing refuses others: the bounds of a search by candidates hold for them."""
+    n, nq, rng = 20000, 40, np.random.default_rng(d)
+    p = T.setup(d, bits, prod)[0]
+    q = T.dev(W.gaussian_queries(nq, d, 9, unit=False))
+    c = T._random_codes(p, d, bits, prod, n, 4)
+    for name in ("norm", "gamma"):
+        if c[name] is not None:
+            c[name] = c[name] * T.dev(rng.choice(np.float32([-1, 1]), size=n))
+    T._topk_both_ways(p, q, 1, nq, c, n, 10)
