@@ -460,14 +460,12 @@ __global__ __launch_bounds__(512) void quant128_few_kernel(const QuantSmallArgs 
 // a workgroup takes one block up to this many workgroups; beyond that it loops over blocks,
 // keeping its parameter slices in registers
 constexpr int kSmallGrid = 1024;
-// up to here blocks of 16: one per compute unit.  Where a unit gets two of them the blocks of 32 win (4936 vectors in two
-// instances: 12.0 us against 11.0).
-constexpr int64_t kFewRows = 4096;
-
 template <int BITS, bool PROD, bool MIXED>
 static hipError_t launch_in(const QuantSmallArgs& a, bool bf16, hipStream_t s) {
-  if (a.n <= kFewRows) {
-    const dim3 few((unsigned)((a.n + 15) / 16));
+  // blocks of 16 while every one has a compute unit to itself; where a unit gets two of them the blocks of 32 win (256 units,
+  // 4936 vectors in two instances: 12.0 us against 11.0)
+  if (const int64_t few_blocks = (a.n + 15) / 16; few_blocks <= device_cu_count()) {
+    const dim3 few((unsigned)few_blocks);
     if (bf16) hipLaunchKernelGGL((quant128_few_kernel<BITS, PROD, true, MIXED>), few, dim3(512), 0, s, a);
     else hipLaunchKernelGGL((quant128_few_kernel<BITS, PROD, false, MIXED>), few, dim3(512), 0, s, a);
     return hipGetLastError();
