@@ -13,8 +13,8 @@ whole step.  `rooflines` prices every call of the step against the roofline
 that bounds it, from its ALGORITHMIC flops or bytes and its HIP-event time on
 the launch stream inside the timed region; `roofline` is the entry of the call
 that takes the largest share of the step.  A contraction that the library
-feeds to the bf16 matrix cores as pieces of its fp32 factors is priced
-against the bf16 peak on its algorithmic flops (`frac`); the share of the
+feeds to the 16-bit matrix cores as pieces of its fp32 factors is priced
+against their peak on its algorithmic flops (`frac`); the share of the
 peak that the executed piece products reach (`executed_frac`) and the
 fp32-equivalent rate are given beside it, and `fp32_mfma_reference` times the
 same calls with TQ_FLAG_FP32_MFMA (every contraction on fp32 MFMA).
@@ -97,49 +97,74 @@ def make_calls(tq, cfg, p, b):
     return [("quantize", quantize), ("dequantize", dequantize), ("score", score)]
 
 
+def few_queries(cfg):
+    """tq_score runs on the int8 matrix cores: masked sums of the query's digits (one instance, symmetric codebook)."""
+    if cfg.d % 128:
+        return False
+    if cfg.d <= 512:
+        return cfg.q_per_group <= 32 or (cfg.q_per_group <= 64 and cfg.n <= 16384)
+    return cfg.nq <= 64 and cfg.d <= 4096 and cfg.q_per_group <= (32 if cfg.d <= 1024 else 16)
+
+
+def routing(cfg, call: str):
+    """How the library carries out the fp32 contractions of `call` on the 16-bit matrix cores: (products per fp32 product of
+    the rotation or centroid part, the same of the sketch or sign part, in words), or None where the call runs on the fp32
+    or the int8 matrix cores.  Mirrors the library's choice for one instance and the workspace that it asks for."""
+    n, prod, bits = cfg.n * cfg.n_groups, cfg.kind == "prod", cfg.bits_mse
+    bf16 = cfg.in_dtype == "bf16"
+    # Alg. 2 of fp32 vectors whose residual is small keeps the rotation on the fp32 instructions
+    small_residual = prod and not bf16 and (1.0, 0.60, 0.342, 0.183, 0.097)[bits] * cfg.d ** 0.5 < 2.0
+    if call == "quantize":
+        if small_residual or (cfg.d == 128 and n <= 8192):
+            return None
+        if cfg.d == 128:
+            return 2 if bf16 else 3, 3, (f"fp16 MFMA, {'a bf16 vector as one exact piece' if bf16 else 'two pieces of x'} against two "
+                                         "of Pi (rotation); bf16 MFMA, two pieces of the residual against two of S Pi^T (signs only)")
+        if cfg.d >= 512 or n <= 16384:
+            if n <= 64 and cfg.d >= 512 and (n + 3) // 4 * cfg.d ** 2 * (2 if prod else 1) <= 150 * 512 ** 2:
+                return None
+            return 2 if bf16 else 3, 3, (f"fp16 MFMA, {'a bf16 vector as one exact piece' if bf16 else 'two pieces of x'} against two "
+                                         "of Pi (rotation), two of the residual against two of S Pi^T (signs only)")
+        return 3 if bf16 else 5, 3, (f"bf16 MFMA, {'one exact piece' if bf16 else 'the two leading pieces'} of x against three of Pi "
+                                     "(rotation), two of the residual against two of S Pi^T (signs only)")
+    if call == "dequantize":
+        if cfg.d == 128 and n <= 8192:
+            return None
+        kind = "bf16" if cfg.d == 128 else "fp16"
+        return 2 if bits == 1 else 3, 2, f"{kind} MFMA, two pieces of a centroid (a sign is one) against two of Pi^T and S^T"
+    if few_queries(cfg) or (cfg.q_per_group <= 32 and cfg.d % 128 == 0 and cfg.d <= 1024):
+        return None
+    if cfg.topk and cfg.n_groups == 1 and cfg.n >= 8192 and cfg.d % 128 == 0 and cfg.d <= 4096:
+        return 1, 1, ("fp16 MFMA, one piece of every factor finds the candidates; these are scored again from two bf16 pieces of "
+                      "every factor")
+    return 2 if bits == 1 else 3, 2, "bf16 MFMA, two pieces of a query coordinate against two of a centroid (a sign is one)"
+
+
 def piece_products(cfg, call: str):
-    """bf16 piece products the library executes per fp32 contraction of `call`, or 0 when the call runs on the
-    fp32 matrix cores.  Mirrors the library's routing (d = 128, one instance): large bf16 batches are quantised
-    with x as one piece against three pieces of Pi, and the residual's two pieces against two of S Pi^T (three
-    products each); DeQuant takes three products for the centroid part and three for the sign part."""
-    n, prod = cfg.n * cfg.n_groups, cfg.kind == "prod"
-    if cfg.d != 128:
-        # the generic kernel: rotation with three pieces of Pi against the two leading pieces of an fp32 vector
-        # (five products; three against the single piece of a bf16 vector), the sketch with two of each (three)
-        if call == "quantize":
-            rot = 3.0 if cfg.in_dtype == "bf16" else 5.0
-            return (rot + 3.0) / 2 if prod else rot
-        if call == "dequantize" or cfg.q_per_group > 32 or cfg.d > 512:
-            # the many-query scoring kernel (also DeQuant, with the rows of Pi^T as queries): two pieces of a query
-            # coordinate against two of a centroid (three products; two for a 1-bit table) or against a sign (two)
-            cen = 0 if cfg.bits_mse == 0 else 2 if cfg.bits_mse == 1 else 3
-            return (cen + (2 if prod else 0)) / ((1 if cfg.bits_mse else 0) + (1 if prod else 0))
+    """Piece products that the matrix cores execute per fp32 product of `call`, over both of its parts; 0 where it does not
+    run on pieces."""
+    r = routing(cfg, call)
+    if r is None:
         return 0.0
-    if getattr(cfg, "d_hi", 0):
-        return 0.0
-    if call == "quantize" and cfg.in_dtype == "bf16" and n > 8192:
-        return 3.0
-    if call == "dequantize" and n > 8192:
-        return 3.0  # two pieces of each factor, three products, for the centroid part and for the sign part alike
-    return 0.0
+    parts = ([r[0]] if cfg.bits_mse else []) + ([r[1]] if cfg.kind == "prod" else [])
+    if call == "quantize" and not cfg.bits_mse:
+        parts = [r[0], r[1]]  # the rotation is there without index bits too
+    return sum(parts) / len(parts)
 
 
 def arithmetic(cfg):
     """What each call of this workload multiplies in (every result meets the fp32 tolerances of the parity tests)."""
-    if cfg.d == 128:
-        q = ("bf16 MFMA on exact pieces: bf16 input x three pieces of Pi (rotation), two pieces of the residual x two "
-             "of S Pi^T (signs only); fp32 accumulation and bucket decision") if piece_products(cfg, "quantize") else \
-            "fp32 MFMA (rotation and sketch), fp32 bucket decision"
-        dq = "bf16 MFMA on two-piece splits of the fp32 factors (error < 3e-5 of a coordinate), fp32 accumulation" \
-            if piece_products(cfg, "dequantize") else "fp32 MFMA"
-    else:
-        q = ("bf16 MFMA on pieces: three (exact) pieces of Pi x the two leading pieces of x (rotation, y to 8e-6 |x|; a bf16 "
-             "x is one exact piece), two x two for the sketch (signs only); fp32 accumulation and bucket decision")
-        dq = "bf16 MFMA on two-piece splits of the fp32 factors (the scoring kernel with the rows of Pi^T as queries), fp32 accumulation"
-    few = cfg.q_per_group <= 32 and cfg.d <= 512
-    sc = "int8 MFMA on exact base-128 digits of 2^-19-scaled rotated queries, fp32 combination" if few else \
-        "bf16 MFMA on two-piece splits of the rotated queries and centroids (scores within 3e-6 |q| norm), fp32 accumulation"
-    return {"quantize": q, "dequantize": dq, "score": sc}
+    out = {}
+    for call in ("quantize", "dequantize", "score"):
+        r = routing(cfg, call)
+        if r is not None:
+            out[call] = r[2] + "; fp32 accumulation"
+        elif call == "score" and few_queries(cfg):
+            unit = 19 if cfg.d == 128 else 20
+            out[call] = f"int8 MFMA on exact base-128 digits of rotated queries in 2^-{unit} fixed point, fp32 combination"
+        else:
+            out[call] = "fp32"
+    return out
 
 
 def algorithmic_work(cfg, call: str):
@@ -232,7 +257,7 @@ def call_roofline(cfg, name: str, ms: float):
     else:
         r = {"bound": "mfma", "achieved": flops / sec / 1e12, "peak": peak_tf, "unit": "TFLOP/s",
              "frac": flops / sec / 1e12 / peak_tf,
-             "dtype": "bf16 pieces of fp32 factors, fp32 accumulate" if pieces else "f32"}
+             "dtype": "16-bit pieces of fp32 factors, fp32 accumulate" if pieces else "f32"}
         if pieces:
             r["piece_products_per_fp32_product"] = pieces
             r["executed_frac"] = flops * pieces / sec / 1e12 / PEAK_BF16_MFMA_TFLOPS
@@ -249,9 +274,10 @@ def path_dtype(cfg):
     for name in ("quantize", "dequantize", "score"):
         pc = piece_products(cfg, name)
         if pc:
-            parts.append(f"{name}: bf16 pieces of fp32 factors ({pc:g} products per fp32 product), f32 accumulate")
-        elif name == "score" and cfg.q_per_group <= 32 and cfg.d <= 512:
-            parts.append("score: i8 digits of a 2^-19 fixed-point query, i32 accumulate")
+            kinds = " and ".join(k for k in ("fp16", "bf16") if k + " MFMA" in routing(cfg, name)[2])
+            parts.append(f"{name}: {kinds} pieces of fp32 factors ({pc:g} products per fp32 product), f32 accumulate")
+        elif name == "score" and few_queries(cfg):
+            parts.append("score: i8 digits of a fixed-point query, i32 accumulate")
         else:
             parts.append(f"{name}: f32")
     return "; ".join(parts)
