@@ -59,9 +59,15 @@ def test_topk_segments(npg, topk):
     c["norm"][max(0, npg - 3):] = 90.0
     T._topk_both_ways(p, T.dev(W.gaussian_queries(3, 128, 5, unit=False)), 1, 3, c, npg, topk)
     c["norm"][5] = float("nan")
+    q = T.dev(W.gaussian_queries(3, 128, 5, unit=False))
+    scores = torch.zeros((3, npg), device=T.DEV)
+    tq.tq_score(p, q, 1, 3, c["idx"], None, None, c["norm"], npg, scores)
     ti = torch.zeros((3, topk), dtype=torch.int32, device=T.DEV)
-    tq.tq_score(p, T.dev(W.gaussian_queries(3, 128, 5, unit=False)), 1, 3, c["idx"], None, None, c["norm"], npg, None, topk, ti, None)
-    assert bool((ti >= -1).all()) and bool((ti < npg).all())
+    tq.tq_score(p, q, 1, 3, c["idx"], None, None, c["norm"], npg, None, topk, ti, None)
+    s = scores.cpu().numpy()
+    assert np.isnan(s[:, 5]).all() and np.isnan(s).sum() == 3
+    s[:, 5] = -np.inf  # never taken: every row has topk others
+    assert np.array_equal(ti.cpu().numpy(), np.argsort(-s, axis=1, kind="stable")[:, :topk])
 
 
 @pytest.mark.parametrize("d,bits,n,prod", [
