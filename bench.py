@@ -183,7 +183,7 @@ def algorithmic_work(cfg, call: str):
 
 
 def measured_traffic(workload: str, kernel: str):
-    """HBM bytes per launch of the dominant call, from the rocprofv3 --pmc FETCH_SIZE and
+    """HBM bytes of one call, over all of its kernels, from the rocprofv3 --pmc FETCH_SIZE and
     WRITE_SIZE runs recorded under profiles/ (scaled there by a plain copy of known size);
     None when no measurement has been recorded for this workload and call."""
     path = os.path.join(ROOT, "profiles", "traffic.json")

@@ -2,7 +2,7 @@
 
     python -m paper_2504_19874_amd.profile_summary stats  <dir with *_kernel_stats.csv>
     python -m paper_2504_19874_amd.profile_summary traffic <FETCH_SIZE dir> <WRITE_SIZE dir> \
-           --workload C2 [--json profiles/traffic.json]
+           --workload C2 --calls 12 [--json profiles/traffic.json]
 
     python -m paper_2504_19874_amd.profile_summary counters <dir of a --pmc run>
 
@@ -19,8 +19,9 @@ all SIMDs; SQ_ACTIVE_INST_VALU counts units of 4 cycles).  `traffic` reads the t
 --pmc runs (FETCH_SIZE in one, WRITE_SIZE in the other; both made with
 bench.py --calibration-copy so that a plain 256 MiB device copy is in the same
 trace), derives the scale factor of each counter from that copy, prints the
-per-kernel table and, with --json, records bytes per launch for the library's
-entry points in the file bench.py reads for `roofline.traffic`.
+per-kernel table and, with --json, records the bytes of one call of the library's
+entry points, over all kernels that a call launches, in the file bench.py reads
+for `roofline.traffic`.
 """
 from __future__ import annotations
 
@@ -34,8 +35,12 @@ import os
 import sys
 
 COPY_KIB = 256 * 1024  # what bench.py --calibration-copy reads and writes
-# kernel name prefix -> entry point whose dominant kernel it is
-ENTRY_OF = (("tq::quant128_kernel", "tq_quantize_prod"), ("tq::(anonymous namespace)::quant128_bf3_kernel", "tq_quantize_prod"), ("tq::dequant128_kernel", "tq_dequantize"),
+# kernel name prefix -> entry point that launches it ("quantize": of either quantiser)
+ANON = "tq::(anonymous namespace)::"
+ENTRY_OF = ((ANON + "h2_kernel<0", "tq_quantize_mse"), (ANON + "h2_kernel<1", "tq_quantize_prod"), (ANON + "h2_kernel<2", "tq_quantize_prod"),
+            (ANON + "h2_kernel<3", "tq_score"), (ANON + "split_rows_kernel", "quantize"), (ANON + "code_gemm_kernel", "tq_dequantize"),
+            (ANON + "search_", "tq_score"), (ANON + "topk_", "tq_score"), (ANON + "score_stream_kernel", "tq_score"),
+            ("tq::quant128_kernel", "tq_quantize_prod"), ("tq::(anonymous namespace)::quant128_bf3_kernel", "tq_quantize_prod"), ("tq::dequant128_kernel", "tq_dequantize"),
             ("tq::(anonymous namespace)::dequant128_bf3_kernel", "tq_dequantize"),
             ("tq::(anonymous namespace)::score_bf3_kernel", "tq_score"),
             ("tq::score_i8_128_kernel", "tq_score"), ("tq::score_i8_kernel", "tq_score"),
@@ -95,7 +100,7 @@ def per_kernel(dirname, counter):
     return acc
 
 
-def traffic(fetch_dir, write_dir, workload, json_path):
+def traffic(fetch_dir, write_dir, workload, json_path, calls):
     fetch, write = per_kernel(fetch_dir, "FETCH_SIZE"), per_kernel(write_dir, "WRITE_SIZE")
     # the calibration copy is the launch of a copy kernel that wrote 256 MiB (WRITE_SIZE counts every byte
     # written, which the copy itself shows); other copies in the trace (inputs being laid out) have other sizes.
@@ -116,7 +121,7 @@ def traffic(fetch_dir, write_dir, workload, json_path):
           f"WRITE_SIZE {w_copy:.1f} KiB -> scale {w_scale:.4f}\n")
     print("| call | kernel | launches | FETCH_SIZE KiB | WRITE_SIZE KiB | HBM bytes (scaled) |")
     print("|---|---|---|---|---|---|")
-    table = {}
+    table, of_call = {}, collections.defaultdict(lambda: {"kernels": [], "traffic_bytes": 0.0})
     for k in sorted(fetch):
         if not k.startswith("void tq::") and not k.startswith("tq::"):
             continue
@@ -125,10 +130,17 @@ def traffic(fetch_dir, write_dir, workload, json_path):
         f, w = sum(fetch[k]) / len(fetch[k]), sum(write[k]) / len(write[k])
         total = (f * f_scale + w * w_scale) * 1024
         print(f"| {entry} | `{short(k, 70)}` | {len(fetch[k])} | {f:.1f} | {w:.1f} | {total / 1e6:.2f} MB |")
-        if entry and len(fetch[k]) > 2:
-            table[entry] = {"kernel": re.match(r"(.*?kernel(?:<[^>]*>)?)", name).group(1) if "kernel" in name else name.split("(")[0], "fetch_kib_raw": round(f, 1), "write_kib_raw": round(w, 1),
-                            "fetch_scale": round(f_scale, 4), "write_scale": round(w_scale, 4),
-                            "traffic_bytes": int(total), "launches_averaged": len(fetch[k])}
+        if entry and len(fetch[k]) >= max(calls, 1):
+            of_call[entry]["kernels"].append(re.match(r"(.*?kernel(?:<[^>]*>)?)", name).group(1) if "kernel" in name else name.split("(")[0])
+            of_call[entry]["traffic_bytes"] += total * len(fetch[k]) / max(calls, 1)
+    shared = of_call.pop("quantize", None)
+    for entry, t in of_call.items():
+        if shared and entry.startswith("tq_quantize"):
+            t["kernels"] += shared["kernels"]
+            t["traffic_bytes"] += shared["traffic_bytes"]
+        table[entry] = {"kernels": t["kernels"], "fetch_scale": round(f_scale, 4), "write_scale": round(w_scale, 4),
+                        "traffic_bytes": int(t["traffic_bytes"]), "calls": calls}
+    print("\nper call: " + ", ".join(f"{e} {t['traffic_bytes'] / 1e6:.1f} MB" for e, t in sorted(table.items())))
     if json_path:
         try:
             with open(json_path) as fh:
@@ -152,6 +164,7 @@ def main():
     t.add_argument("fetch_dir")
     t.add_argument("write_dir")
     t.add_argument("--workload", required=True)
+    t.add_argument("--calls", type=int, required=True, help="passes of the step in the trace, warm-up included")
     t.add_argument("--json", default="")
     args = ap.parse_args()
     if args.cmd == "stats":
@@ -159,7 +172,7 @@ def main():
     elif args.cmd == "counters":
         counters(args.dir)
     else:
-        traffic(args.fetch_dir, args.write_dir, args.workload, args.json)
+        traffic(args.fetch_dir, args.write_dir, args.workload, args.json, args.calls)
 
 
 if __name__ == "__main__":
