@@ -351,11 +351,12 @@ hipError_t launch_block(const SearchArgs& a, const Codebook& cb, char* base, int
     f.c_norm = std::fmax(f.c_norm, c * sqrt_d);
   }
   if (a.bits > 1) f.c_rel = code_table_error(a.bits, cb);
-  // A matrix instruction adds its 16 products and the accumulator with an error of at most 6 2^-24 of the sum of their
-  // magnitudes (the largest seen over drawn operands of one size and of widely different ones; 2 2^-24 where the accumulator
-  // is the largest).  The chains are d / 16 instructions here and 3 d / 16 in the exact kernel, whose two bf16 pieces of
-  // a factor leave out 2^-17 of it and their smallest product 2^-18; the score's own three roundings are far below.
-  f.acc_rel = (float)a.d * (4.f / 16.f * 6.f * 0x1p-24f) + 0x1p-15f;
+  // A matrix instruction adds its 16 products to the accumulator with an error of at most 2^-24 (2.02 |accumulator| + 8 sum of
+  // |products|), measured with operands of one size, of widely different ones and with a few large ones (2.01 and 7.2 were the
+  // largest; a chain of them makes 2.02 2^-24 per instruction of all magnitudes together, and the second term once).  The
+  // chains are d / 16 instructions here and 3 d / 16 in the exact kernel, whose two bf16 pieces of a factor leave out 2^-17
+  // of it and their smallest product 2^-16; the score's own three roundings are far below.
+  f.acc_rel = ((float)a.d * (4.f / 16.f * 2.04f) + 16.f) * 0x1p-24f + 0x1p-15f;
   f.sqrt_d = sqrt_d;
   f.s_rel = std::exp2(std::round(std::log2(sqrt_d)));
   hipLaunchKernelGGL(search_prepare_kernel, dim3((unsigned)a.nq), dim3(256), 0, s, a.d, a.bits > 0 ? a.qr : nullptr, a.prod ? a.qs : nullptr, f,
