@@ -37,9 +37,9 @@ constexpr int64_t kChunkRows = 65536;  // rows per pass of the quantiser at most
 constexpr int64_t kMaxRowStride = int64_t(1) << 22;
 constexpr int64_t kRowsQuantMax = 64;  // at most this many long vectors take the matrix-vector route of the quantiser
 // That route reads every matrix once per block of four vectors, plain fp32 multiply-adds; the fp16 contraction once per
-// tile, and holds 22 bits of a factor.  The line between them, blocks x d^2 x matrices, lies at 4e7 elements: up to there
-// fp32 vectors keep all their bits (mean error of a rotated coordinate 0.8 - 1.2e-7 sigma, 2.2 - 4.2e-7 on the contraction)
-// at no more than a few us.  Measured, this route / the contraction in us:
+// tile, and reads 17 bits of an fp32 vector.  The line between them, blocks x d^2 x matrices, lies at 4e7 elements: up to
+// there vectors keep all their bits (mean error of a rotated coordinate 0.8 - 1.2e-7 sigma; 2.0e-6 on the contraction, 2.4e-7
+// for bf16 vectors) at no more than a few us.  Measured, this route / the contraction in us:
 //   Alg. 1  d = 1024: 64 vectors 15.1 / 12.4; 1536: 8 vectors 13.3, 32 16.5 / 14.5, 64 22.3 / 15.4; 3072: 4 24.1, 8 27.7 / 22.3,
 //           16 29.6 / 22.4; 4096: 1 31.4 / 29.0, 8 35.6 / 29.6
 //   Alg. 2  d = 1024: 64 27.8 / 23.3; 1536: 32 29.2 / 29.7; 3072: 4 35.8, 8 43.8 / 40.6; 4096: 1 45.7 / 50.0, 4 52.9 / 51.4
@@ -216,7 +216,7 @@ bool quantize_h2(const tq_params* p, const void* x, bool bf16, int64_t n, int64_
   const Codebook cb = make_codebook(p);
   for (int64_t r0 = 0; r0 < n; r0 += chunk) {
     const int64_t rows = n - r0 < chunk ? n - r0 : chunk;
-    if (launch_h2_split(static_cast<const char*>(x) + (size_t)r0 * ldx * esz, bf16, ldx, rows, d, norm != nullptr, w_inv, xp,
+    if (launch_h2_split(static_cast<const char*>(x) + (size_t)r0 * ldx * esz, bf16, true, ldx, rows, d, norm != nullptr, w_inv, xp,
                         norm ? norm + r0 : nullptr, fac, esc, stream) != hipSuccess)
       return true;
     H2Quant a;
@@ -633,7 +633,7 @@ bool rotate_h2(const tq_params* p, const float* q, int64_t ldq, int64_t nq, floa
     }
     for (int64_t r0 = 0; r0 < nq; r0 += sp.rows) {
       const int64_t rows = nq - r0 < sp.rows ? nq - r0 : sp.rows;
-      if (launch_h2_split(q + r0 * ldq, false, ldq, rows, d, false, w_inv, base + sp.pieces, nullptr, fac, nullptr, s) != hipSuccess) return false;
+      if (launch_h2_split(q + r0 * ldq, false, false, ldq, rows, d, false, w_inv, base + sp.pieces, nullptr, fac, nullptr, s) != hipSuccess) return false;
       H2Quant a;
       std::memset(&a, 0, sizeof(a));
       a.W = image; a.w_inv = w_inv; a.X = base + sp.pieces; a.npx = 2; a.d = d; a.n = rows; a.fac = fac; a.out = (m == 0 ? qr : qs) + r0 * d;

@@ -27,7 +27,7 @@ constexpr int XCDS = 8;
 
 // d fp32 / bf16 values per row -> pieces.  L lanes per row (a power of two up to 64), U chunks of eight values per lane
 // held in registers; rows longer than 64 * 8 * U values are read twice instead (U = 0).
-template <bool BF16, int U>
+template <bool BF16, bool CUT, int U>
 __global__ __launch_bounds__(256) void split_rows_kernel(const void* x, int64_t ldx, int64_t n, int d, int lanes_log2, int normalise,
                                                          const float* w_inv, unsigned char* pieces, float* norm, float* fac, float* esc) {
   const int L = 1 << lanes_log2;
@@ -52,6 +52,11 @@ __global__ __launch_bounds__(256) void split_rows_kernel(const void* x, int64_t 
       const float4 a = *reinterpret_cast<const float4*>(xf + c * 8), b = *reinterpret_cast<const float4*>(xf + c * 8 + 4);
       o[0] = a.x; o[1] = a.y; o[2] = a.z; o[3] = a.w; o[4] = b.x; o[5] = b.y; o[6] = b.z; o[7] = b.w;
     }
+  };
+  // CUT: the value's two leading bf16 pieces, 17 significant bits (see launch_h2_split)
+  auto cut = [](float f) {
+    const float f1 = __uint_as_float(bf16_bits(f) << 16);
+    return f1 + __uint_as_float(bf16_bits(f - f1) << 16);
   };
   float ss = 0.f;
   uint32_t mx = 0;
@@ -106,7 +111,10 @@ __global__ __launch_bounds__(256) void split_rows_kernel(const void* x, int64_t 
   auto store = [&](int c, const float (&o)[8]) {
     uint32_t hi[4], lo[4];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) h2_split(o[2 * i] * s, o[2 * i + 1] * s, hi[i], lo[i]);
+    for (int i = 0; i < 4; ++i) {
+      const float f0 = CUT ? cut(o[2 * i]) : o[2 * i], f1 = CUT ? cut(o[2 * i + 1]) : o[2 * i + 1];
+      h2_split(f0 * s, f1 * s, hi[i], lo[i]);
+    }
     unsigned char* const q = dst + (c >> 2) * (64 * NP) + (c & 3) * 16;
     *reinterpret_cast<uint4*>(q) = make_uint4(hi[0], hi[1], hi[2], hi[3]);
     if (!BF16) *reinterpret_cast<uint4*>(q + 64) = make_uint4(lo[0], lo[1], lo[2], lo[3]);
@@ -515,7 +523,7 @@ H2Args args_of(const H2Quant& q) {
   return a;
 }
 
-template <bool BF16>
+template <bool BF16, bool CUT>
 hipError_t launch_split(const void* x, int64_t ldx, int64_t n, int d, bool normalise, const float* w_inv, void* pieces, float* norm,
                         float* fac, float* esc, hipStream_t s) {
   int lg = 2;  // d >= 32: at least four chunks of eight
@@ -524,7 +532,7 @@ hipError_t launch_split(const void* x, int64_t ldx, int64_t n, int d, bool norma
   const dim3 grid((unsigned)((n + rows - 1) / rows));
   const int u = (d / 8 + (1 << lg) - 1) >> lg;
   unsigned char* const pc = static_cast<unsigned char*>(pieces);
-#define TQ_SPLIT(U) hipLaunchKernelGGL((split_rows_kernel<BF16, U>), grid, dim3(256), 0, s, x, ldx, n, d, lg, normalise ? 1 : 0, w_inv, pc, norm, fac, esc)
+#define TQ_SPLIT(U) hipLaunchKernelGGL((split_rows_kernel<BF16, CUT, U>), grid, dim3(256), 0, s, x, ldx, n, d, lg, normalise ? 1 : 0, w_inv, pc, norm, fac, esc)
   if (u <= 1) TQ_SPLIT(1);
   else if (u <= 2) TQ_SPLIT(2);
   else if (u <= 3) TQ_SPLIT(3);
@@ -556,10 +564,11 @@ hipError_t launch_h2_image(const float* W, int64_t ldw, int M, int d, void* imag
   return hipGetLastError();
 }
 
-hipError_t launch_h2_split(const void* x, bool bf16, int64_t ldx, int64_t n, int d, bool normalise, const float* w_inv, void* pieces,
+hipError_t launch_h2_split(const void* x, bool bf16, bool cut, int64_t ldx, int64_t n, int d, bool normalise, const float* w_inv, void* pieces,
                            float* norm, float* fac, float* esc, hipStream_t s) {
-  return bf16 ? launch_split<true>(x, ldx, n, d, normalise, w_inv, pieces, norm, fac, esc, s)
-              : launch_split<false>(x, ldx, n, d, normalise, w_inv, pieces, norm, fac, esc, s);
+  if (bf16) return launch_split<true, false>(x, ldx, n, d, normalise, w_inv, pieces, norm, fac, esc, s);
+  return cut ? launch_split<false, true>(x, ldx, n, d, normalise, w_inv, pieces, norm, fac, esc, s)
+             : launch_split<false, false>(x, ldx, n, d, normalise, w_inv, pieces, norm, fac, esc, s);
 }
 
 int h2_part_tiles(int d, int64_t n) {

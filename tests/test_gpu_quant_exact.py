@@ -32,18 +32,6 @@ def check_decisions(d, bits, prod, n, beside):
     assert np.array_equal(got, want), f"{(got != want).sum()} of {got.size} decisions"
 
 
-def two_pieces(t, rng):
-    """2^-20 beside a boundary: what two fp16 pieces of the vector (22 bits) keep."""
-    e = np.float32(2.0**-20) * rng.choice(np.float32([-1, 1]), size=t.shape)
-    return np.where(t == 0, e, t * (1 + e)).astype(np.float32)
-
-
-@pytest.mark.parametrize("d,bits,prod,n", [(512, 4, False, 100), (768, 4, False, 5000), (1024, 3, False, 300), (1536, 4, False, 70),
-                                           (160, 3, True, 700), (1024, 3, True, 130), (3072, 4, False, 66)])
-def test_two_pieces_of_fp32_vectors(d, bits, prod, n):
-    check_decisions(d, bits, prod, n, two_pieces)
-
-
 def all_bits(t, rng):
     """The boundary itself and the fp32 value below it: 24 bits."""
     return np.where(rng.random(t.shape) < 0.5, t, np.nextafter(t, np.float32(-1))).astype(np.float32)
