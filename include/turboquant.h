@@ -51,38 +51,57 @@
  *
  * Arithmetic.  Every contraction has fp32 operands and an fp32 (or int32)
  * accumulator; the bucket decision is an fp32 comparison.  Where it is faster
- * the fp32 factors are fed to the bf16 or int8 matrix cores as exact pieces
- * (bf16 pieces of 8 significant bits each, or base-128 digits of a fixed-point
- * value with 2^-19 relative spacing):
- *   quantise, bf16 batches above 8192 vectors at d = 128 and every d other
- *     than 128: the rotation from three pieces of Pi and the two leading
- *     pieces of an fp32 x (a bf16 x is one exact piece); what is dropped of x is
- *     below 2^-17 |x_k| per element, so a rotated coordinate moves by at most
- *     2^-17 |Pi_j| |x| = 7.6e-6 of the unit norm and the rotated vector by that in
- *     L2 norm: an index can differ from the fp32 evaluation only inside the
- *     1e-5 band around a cell boundary that every path is allowed.  The sketch,
- *     of which only signs are kept, from two pieces of the residual and two of
- *     S Pi^T (a sign can differ from the exact one only where
- *     |<S_j, r>| < 1e-6 |S_j| |r|).  tq_quantize_prod of fp32 vectors keeps the
- *     rotation on the fp32 instructions where the residual is so small that the
- *     part of x left out would show in gamma (4-bit MSE stage up to d = 416,
- *     3 bits up to d = 96, 2 bits at d = 32);
- *     Up to 64 vectors at d >= 512 with params.workspace large enough for
- *     their rotated coordinates (tq_workspace_bytes counts them) are rotated by
- *     plain fp32 multiply-adds, one matrix-vector product per vector, and so
- *     are a handful of long vectors in tq_dequantize;
- *   dequantise, large batches: two pieces of each factor (error
- *     below 4e-5 of a coordinate's typical size), at every d;
- *   scoring: two bf16 pieces of each factor (many queries; scores within
- *     3e-6 |q| norm of the exact ones) or int8 digits (few queries: up to 32
- *     per group at d <= 1024, up to 16 per group at d <= 4096 (64 in all
- *     beyond d = 512),
- *     d a multiple of 128, codebook symmetric about zero).
- * At d = 128, fp32 inputs and smaller batches run on the fp32 matrix
- * instructions.  All paths meet the same tolerances (indices equal to an fp32
- * evaluation except within 1e-5 of a cell boundary; values and scores within
- * 1e-4 relative).  With TQ_FLAG_FP32_MFMA in params.flags every contraction of
- * tq_quantize_*, tq_dequantize and many-query tq_score stays on the fp32 matrix
+ * the fp32 factors are fed to the 16-bit or int8 matrix cores as pieces: bf16
+ * pieces of 8 significant bits each, two fp16 pieces under a power-of-two scale
+ * (22 bits: what is left out is below 2^-22 of the value, 2^-24.5 in the root
+ * mean square, or below 2^-39 of the row's largest value), or base-128 digits
+ * of a fixed-point value with 2^-19 (d = 128) or 2^-20 relative spacing:
+ *   quantise, rotation, more than 8192 vectors at d = 128: two fp16 pieces of Pi
+ *     and of an fp32 x (a bf16 x is one exact piece).
+ *   quantise, rotation, every d other than 128: two fp16 pieces of Pi where
+ *     d >= 512 or n <= 16384 and params.workspace holds the pieces of the vectors
+ *     (tq_workspace_bytes counts them; codebooks of 3 and 4 bits have to be symmetric
+ *     about zero), three bf16 pieces (all 24 bits) elsewhere;
+ *     a bf16 x is one exact piece, of an fp32 x the two leading bf16 pieces are
+ *     taken in both: what is dropped of x is below 2^-17 |x_k| per element, so a
+ *     rotated coordinate moves by at most 2^-17 |Pi_j| |x| = 7.6e-6 of the unit
+ *     norm and the rotated vector by that in L2 norm: an index can differ from
+ *     the fp32 evaluation only inside the 1e-5 band around a cell boundary that
+ *     every path is allowed.
+ *     Measured against 64-bit arithmetic, two fp16 pieces of Pi decide as well as
+ *     three of bf16 (the sums' own rounding is larger): of 4.3e9 coordinates at
+ *     d = 128, 4 bits, bf16 vectors, 1186 on the other side of a boundary against
+ *     1125 for keys with outlier channels, 1195 against 1222 for normal vectors.
+ *   quantise, sketch, of which only signs are kept: two pieces of the residual and
+ *     two of S Pi^T (a sign can differ from the exact one only where
+ *     |<S_j, r>| < 1e-6 |S_j| |r|).
+ *   tq_quantize_prod of fp32 vectors keeps the rotation on the fp32 instructions,
+ *     whatever the batch size, where the residual is so small that the part of x
+ *     left out would show in gamma (4-bit MSE stage up to d = 416, 3 bits up to
+ *     d = 96, 2 bits at d = 32).
+ *   Up to 64 vectors at d >= 512, while ceil(n / 4) d^2 (twice that with a sketch)
+ *     is at most 150 x 512^2 and params.workspace holds their rotated coordinates,
+ *     are rotated by plain fp32 multiply-adds, one matrix-vector product per
+ *     vector, and so are a handful of long vectors in tq_dequantize;
+ *   dequantise, more than 8192 vectors at d = 128 and every other d: two pieces of
+ *     a centroid and of an entry of Pi^T or S^T, a sign as one exact piece (error
+ *     below 4e-5 of a coordinate's typical size);
+ *   scoring, Pi q and S q: plain fp32 for up to 64 queries in all; more of them at d
+ *     other than 128 from two fp16 pieces of the query and of Pi and S each, where the
+ *     workspace has the room that tq_score_workspace_bytes counts (0.62 of the
+ *     fp32 instructions' error), on the fp32 instructions elsewhere;
+ *   scoring, many queries: two bf16 pieces of each factor (scores within
+ *     3e-6 |q| norm of the exact ones); with top-k alone one fp16 piece finds
+ *     what can be among the k best within a derived bound, and these are scored
+ *     the same way, to the same bits;
+ *   scoring, few queries: int8 digits (up to 32 per group at d <= 1024, up to 16
+ *     per group at d <= 4096 (64 in all beyond d = 512), d a multiple of 128,
+ *     codebook symmetric about zero).
+ * Smaller batches at d = 128 run on the fp32 matrix instructions.  All paths meet
+ * the same tolerances (indices equal to an fp32 evaluation except within 1e-5 of a
+ * cell boundary; values and scores within 1e-4 relative).  With TQ_FLAG_FP32_MFMA
+ * in params.flags every contraction of tq_quantize_*, tq_dequantize and
+ * many-query tq_score stays on the fp32 matrix
  * instructions.
  */
 #ifndef TURBOQUANT_H
@@ -219,7 +238,7 @@ typedef struct tq_params {
 
 /* Keep every contraction of tq_quantize_*, tq_dequantize and many-query
  * tq_score on the fp32 matrix instructions (v_mfma_f32_32x32x2_f32) instead
- * of feeding them to the bf16 matrix cores as pieces (see "Arithmetic" at the
+ * of feeding them to the 16-bit matrix cores as pieces (see "Arithmetic" at the
  * head of this file).  Same results within the stated tolerances, about half
  * the speed; meant for measurements against the fp32 peak and for callers who
  * want the plain fp32 evaluation. */
@@ -236,26 +255,29 @@ typedef struct tq_params {
 tq_status tq_derive_params(int32_t d, const float* Pi, const float* S, float* PiT, float* ST,
                            float* SPiT, void* stream);
 
-/* Optional, once per parameter set: the matrices already split into the bf16 pieces the quantisation and
+/* Optional, once per parameter set: the matrices already split into the pieces the quantisation and
  * dequantisation kernels multiply (see "Arithmetic" above), in the kernels' own order, so that no launch splits them
  * again (Alg. 1 / Alg. 2 fix the matrices "at setup"; this is that setup carried one step further).  d = 128: Pi,
  * S Pi^T, Pi^T and S^T as the large-batch kernels keep them in on-chip memory (their prologue becomes a copy);
- * every other d: Pi and S Pi^T as the tiles the quantiser's workgroups stage (10 d^2 bytes).
+ * every other d: Pi and S Pi^T as rows of two fp16 pieces (10 d^2 bytes), which tq_quantize_* and the rotation of many
+ * queries multiply.  At those d the quantisers use them only together with a params.workspace that holds the pieces of
+ * at least 256 vectors, or of all of them (tq_workspace_bytes(p, n, 0, 0) is enough; a smaller one means fewer vectors
+ * per pass); without it, and for more than 16384 vectors below d = 512, the launch splits the matrices itself.
  * tq_images_bytes: size of the buffer for dimension d (0: none is taken at this d, tq_build_images then does
  * nothing).  tq_build_images reads p->Pi and, when p->S is set, p->SPiT (at d = 128 also p->PiT and p->ST), device
  * memory as tq_derive_params left it, and writes `images` (device, 16-byte aligned, owned by the caller) on
- * `stream`; the caller then stores the pointer in params.images.  A null params.images is always valid and gives
- * identical results.  The image must be rebuilt whenever one of the matrices changes: the kernels that take it do
- * not look at the fp32 matrices again.  Errors: TQ_ERR_INVALID_ARG (null pointers, S given without its derived
- * matrices), TQ_ERR_UNSUPPORTED (misaligned), TQ_ERR_HIP. */
+ * `stream`; the caller then stores the pointer in params.images.  A null params.images is always valid: with a workspace
+ * of the size that tq_workspace_bytes / tq_score_workspace_bytes report then, the call makes the pieces there and gives
+ * identical results, with less other kernels serve, the same up to rounding.  The image must be rebuilt whenever one of
+ * the matrices changes: the kernels that take it do not look at the fp32 matrices again.  Errors: TQ_ERR_INVALID_ARG
+ * (null pointers, S given without its derived matrices), TQ_ERR_UNSUPPORTED (misaligned), TQ_ERR_HIP. */
 size_t tq_images_bytes(int32_t d);
 tq_status tq_build_images(const tq_params* p, void* images, void* stream);
 
 /* The same for tq_dequantize at d other than 128 (0 bytes, nothing done, at d = 128): Pi^T and S^T as the tiles its
  * workgroups stage, and S for the sketch of many queries in tq_score, read from p->Pi and p->S.  They lie behind the
- * images above: `images` is a buffer of
- * tq_images_bytes(d) + tq_dequant_images_bytes(d) bytes, and TQ_FLAG_DEQUANT_IMAGES in params.flags says that
- * params.images is such a buffer with both parts filled.  Without the flag tq_dequantize makes these tiles in the
+ * images above: `images` is a buffer of tq_images_bytes(d) + tq_dequant_images_bytes(d) bytes, and
+ * TQ_FLAG_DEQUANT_IMAGES in params.flags says that params.images is such a buffer with both parts filled.  Without the flag tq_dequantize makes these tiles in the
  * workspace in every call, where it has room (8 d^2 + 256 bytes), or takes kernels that do without, the same up to
  * rounding; tq_score likewise for more than 64 queries (tq_score_workspace_bytes counts the room). */
 size_t tq_dequant_images_bytes(int32_t d);
@@ -315,12 +337,14 @@ tq_status tq_dequantize(const tq_params* p, const uint32_t* idx, const uint32_t*
  *            out [n_groups*q_per_group][topk]; topk_val nullable.  Where
  *            topk > n_per_group the surplus entries are index -1, value -inf.
  *            NaN scores are never returned.
- * Workspace (tq_score_workspace_bytes gives the exact need of a call): the
+ * Workspace (tq_score_workspace_bytes gives what a call makes use of): the
  * rotated queries or their int8 digit images, and for top-k without a score
- * buffer either nothing more than topk candidates per query and per range of
- * codes (many queries per code, topk <= 16: the selection runs inside the
- * scoring kernel and no score matrix exists anywhere) or a score matrix
- * [nq][n_per_group] (other cases).
+ * buffer either topk candidates per query and per range of codes (many queries
+ * per code, topk <= 16: the selection runs inside the scoring kernel and no
+ * score matrix exists anywhere) or a score matrix [nq][n_per_group] (other
+ * cases); and, which a call does without where there is no room for it, the
+ * pieces of 16384 queries for their rotation and, many queries in one group,
+ * the candidate lists of as many queries as fit 512 MB.
  * n_groups <= 65535 and q_per_group <= 262140, else TQ_ERR_UNSUPPORTED.
  */
 size_t tq_score_workspace_bytes(const tq_params* p, int32_t n_groups, int32_t q_per_group,
