@@ -5,8 +5,8 @@
 // the contraction then moves both operands into LDS by direct loads and its k-loop holds nothing but LDS reads and
 // matrix instructions.  Splitting inside the contraction instead costs about 25 vector instructions per k-step and
 // thread for every one of the d / 256 row tiles that meet the same vectors, and vector instructions do not overlap with
-// matrix instructions on this chip; the extra pass costs 8 d bytes of traffic per vector once (d = 1536: 2.6 of 14 ms
-// for 10^6 vectors).
+// matrix instructions on this chip; the extra pass costs 8 d bytes of traffic per vector once (d = 1536: 1.9 of 13.1
+// ms for 10^6 vectors).
 //
 // Tile.  256 rows of the matrix x 256 vectors per workgroup of eight wavefronts (2 x 4 tiles of 32 x 32 each: twelve
 // 16-byte LDS reads feed 24 matrix instructions), k in steps of 32 through two buffers of 64 KB (smaller tiles, whose steps are

@@ -24,7 +24,11 @@
 // dependent chains or waits for LDS.
 //
 // Bound by what the matrix cores sustain, then by the decision's vector instructions; leaving out the LDS reads changes nothing.
-// 131072 vectors, with three pieces of Pi -> with two: bf16, 2 + 1 bits 26.8 -> 25.4 us; fp32, 3 + 1 bits 44.3 -> 37.3.
+// 131072 vectors, with three pieces of Pi -> with two: bf16, 2 + 1 bits 25.5 -> 23.8 us; fp32, 3 + 1 bits 44.3 -> 37.3.
+// Against 64-bit arithmetic the 22 bits of Pi cost nothing, the sums' own rounding is larger and there are fewer of them: of
+// 4.3e9 decisions (4 bits, bf16) 1186 on the other side of a boundary against 1125 for keys with outlier channels, 1195
+// against 1222 for normal vectors; gamma at 3 + 1 bits off by 1.01e-7 against 1.07e-7 in the root mean square.  An fp32
+// vector gains 17 -> 22 bits: 1785 -> 105 of 2.7e8, gamma 1.24e-6 -> 1.1e-7.
 #include <type_traits>
 
 #include "tq_bf3.h"

@@ -15,7 +15,7 @@
 // a wavefront takes T tiles of 16 keys and walks their rows, 64 W (BITS or 1) contiguous bytes of a key per step, the words of the next
 // step on their way while those of this one are expanded.  Every operand read from LDS serves T tiles.
 // (Before: 512 coordinates per launch, each launch adding to the scores of the one before.  10^6 codes, 4 queries,
-// kernel time: d = 3072, 1 + 1 bits 500 us -> 181; d = 1536, 4 bits 255 -> 187, where the expansion, 8 ANDs and
+// kernel time: d = 3072, 1 + 1 bits 500 us -> 182; d = 1536, 4 bits 255 -> 200, where the expansion, 8 ANDs and
 // 8 matrix instructions per 4 coordinates of a lane, is what is left.  Cutting the rows over the wavefronts of a workgroup instead, digits in
 // registers and the parts added through LDS, gave 190 - 202 us for the first: every line of the codes then meets several wavefronts at
 // different times.)
