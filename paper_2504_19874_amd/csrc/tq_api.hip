@@ -37,12 +37,11 @@ constexpr int64_t kChunkRows = 65536;  // rows per pass of the quantiser at most
 constexpr int64_t kMaxRowStride = int64_t(1) << 22;
 constexpr int64_t kRowsQuantMax = 64;  // at most this many long vectors take the matrix-vector route of the quantiser
 // That route reads every matrix once per block of four vectors, plain fp32 multiply-adds; the fp16 contraction once per
-// tile, and reads 17 bits of an fp32 vector.  The line between them, blocks x d^2 x matrices, lies at 4e7 elements: up to
-// there vectors keep all their bits (mean error of a rotated coordinate 0.8 - 1.2e-7 sigma; 2.0e-6 on the contraction, 2.4e-7
-// for bf16 vectors) at no more than a few us.  Measured, this route / the contraction in us:
-//   Alg. 1  d = 1024: 64 vectors 15.1 / 12.4; 1536: 8 vectors 13.3, 32 16.5 / 14.5, 64 22.3 / 15.4; 3072: 4 24.1, 8 27.7 / 22.3,
-//           16 29.6 / 22.4; 4096: 1 31.4 / 29.0, 8 35.6 / 29.6
-//   Alg. 2  d = 1024: 64 27.8 / 23.3; 1536: 32 29.2 / 29.7; 3072: 4 35.8, 8 43.8 / 40.6; 4096: 1 45.7 / 50.0, 4 52.9 / 51.4
+// tile, and reads 17 bits of an fp32 vector.  The line between them, blocks x d^2 x matrices, lies at 4e7 elements, about where
+// the two take the same time: up to there vectors keep all their bits (mean error of a rotated coordinate 0.8 - 1.2e-7 sigma;
+// 2.0e-6 on the contraction, 2.4e-7 for bf16 vectors).  Measured, this route, and the contraction at the next larger size, in us:
+//   Alg. 1  d = 1024: 64 vectors 9.5, 65 12.0; 1536: 32 9.7, 64 15.7, 65 14.9; 3072: 8 13.9, 16 16.7, 24 22.7; 4096: 8 23.4, 12 29.5
+//   Alg. 2  d = 1024: 64 18.6, 65 21.7; 1536: 32 19.8, 48 29.6; 3072: 8 28.6, 12 43.5; 4096: 4 44.5, 8 54.4
 // (The dequantiser's route reads both matrices in one kernel and has no second stage; its bound is twice as wide.)
 bool rows_route_serves(int64_t n, int d, int matrices, int64_t limit = 150) {
   return n <= kRowsQuantMax && d >= 512 && d <= 4096 && ((n + 3) / 4) * (int64_t)d * d * matrices <= limit * 512 * 512;
@@ -312,13 +311,9 @@ tq_status quantize_common(const tq_params* p, const void* x, int32_t dtype, int6
   const NKind nk = dtype == TQ_F32 ? N_F32 : N_BF16;
 
   if (!prod) {
-    // a handful of long vectors: a matrix-vector product per vector instead of the tiled contraction's serial k-loop,
-    // when the workspace holds the rotated vectors
-    if (rows_route_serves(n, d, 1) && !fp32_mfma_only(p)) {
-      Workspace ws{static_cast<char*>(p->workspace), p->workspace_bytes, 0};
-      if (float* const yw = static_cast<float*>(ws.take((size_t)n * d * sizeof(float))); yw != nullptr)
-        return from_hip(launch_quant_rows(p->bits_mse, dtype == TQ_BF16, x, ldx, n, d, p->Pi, make_codebook(p), yw, idx, norm, stream));
-    }
+    // a handful of long vectors: a matrix-vector product per vector instead of the tiled contraction's serial k-loop
+    if (rows_route_serves(n, d, 1) && !fp32_mfma_only(p))
+      return from_hip(launch_quant_rows(p->bits_mse, dtype == TQ_BF16, x, ldx, n, d, p->Pi, make_codebook(p), idx, norm, stream));
     if (h2_serves && quantize_h2(p, x, dtype == TQ_BF16, n, ldx, idx, nullptr, nullptr, norm, false, stream, &st)) return st;
     a.X = x;
     a.n = n;
@@ -327,13 +322,11 @@ tq_status quantize_common(const tq_params* p, const void* x, int32_t dtype, int6
     return from_hip(launch_gemm(nk, E_QUANT, p->bits_mse, a, 1, stream));
   }
 
-  // a handful of long vectors: the matrix-vector route (see above), the sketch included
+  // a handful of long vectors: the matrix-vector route (see above), the sketch included, when the workspace holds the residual
   if (rows_route_serves(n, d, 2) && !fp32_mfma_only(p)) {
     Workspace ws2{static_cast<char*>(p->workspace), p->workspace_bytes, 0};
-    float* const yw = static_cast<float*>(ws2.take((size_t)n * d * sizeof(float)));
-    float* const ew = static_cast<float*>(ws2.take((size_t)n * d * sizeof(float)));
-    if (yw != nullptr && ew != nullptr)
-      return from_hip(launch_quant_rows(p->bits_mse, dtype == TQ_BF16, x, ldx, n, d, p->Pi, make_codebook(p), yw, idx, norm, stream,
+    if (float* const ew = static_cast<float*>(ws2.take((size_t)n * d * sizeof(float))); ew != nullptr)
+      return from_hip(launch_quant_rows(p->bits_mse, dtype == TQ_BF16, x, ldx, n, d, p->Pi, make_codebook(p), idx, norm, stream,
                                         p->SPiT, ew, qjl, gamma));
   }
 

@@ -126,12 +126,11 @@ hipError_t launch_dequant128_bf3(int bits, bool prod, const uint32_t* idx, const
                                  const void* image, hipStream_t s);
 
 // few queries per code (tq_score_small.hip)
-// Quant_mse / Quant_prod for a handful of long vectors: y = Pi x by a matrix-vector kernel into yw [n][d], then norm,
-// decision and packing per vector (tq_score_small.hip); with ew != NULL also the residual e = y - c[idx] into ew
-// [n][d], gamma = |e|, u = (S Pi^T) e by the same matrix-vector kernel and its signs into qjl.  d a multiple of 32 up
-// to 4096.
+// Quant_mse / Quant_prod for a handful of long vectors (tq_quant_rows.hip): matrix-vector products that decide and pack what they
+// have multiplied; with ew != NULL also the residual e = y - c[idx] into ew [n][d], then gamma = |e| and the signs of
+// (S Pi^T) e into qjl.  d a multiple of 32 up to 4096.
 hipError_t launch_quant_rows(int bits, bool bf16, const void* x, int64_t ldx, int64_t n, int d, const float* Pi,
-                             const Codebook& cb, float* yw, uint32_t* idx, float* norm, hipStream_t stream,
+                             const Codebook& cb, uint32_t* idx, float* norm, hipStream_t stream,
                              const float* SPiT = nullptr, float* ew = nullptr, uint32_t* qjl = nullptr, float* gamma = nullptr);
 // DeQuant for a handful of long vectors by matrix-vector products (tq_score_small.hip); d a multiple of 32 up to 4096
 hipError_t launch_dequant_rows(int bits, bool prod, int d, int64_t n, const uint32_t* idx, const uint32_t* qjl,

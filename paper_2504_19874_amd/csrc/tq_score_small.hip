@@ -152,96 +152,6 @@ hipError_t launch_matvec_rows(int d, int64_t n, const float* W0, const float* W1
   return many ? go(integral_constant<int, MV_Q>{}, integral_constant<int, 4>{}) : go(integral_constant<int, MV_Q>{}, integral_constant<int, 1>{});
 }
 
-// Alg. 1 for a handful of long vectors (adding to an index one vector at a time): y = Pi x by the row-per-wavefront
-// kernel above, then one workgroup per vector takes the norm of x, scales, decides and packs.  (The tiled contraction
-// walks d / 32 k-steps in series whatever the batch: 78 us for one vector at d = 1536.)  Rotating first and dividing
-// by the norm afterwards differs from the other kernels' order by rounding only.
-// ew != NULL (Alg. 2): the residual in the rotated basis, e = y - c[idx], goes to ew [n][d] and its norm to gamma.
-template <int BITS>
-__global__ __launch_bounds__(256) void quant_rows_finish_kernel(const int d, const void* __restrict__ x, const int64_t ldx,
-                                                                const int x_bf16, const float* __restrict__ yw,
-                                                                const Codebook cb, uint32_t* __restrict__ idx,
-                                                                float* __restrict__ norm, float* __restrict__ ew,
-                                                                float* __restrict__ gamma) {
-  __shared__ float red_s[4];
-  __shared__ float red_e[4];
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int64_t row = blockIdx.x;
-  float inv = 1.f;
-  if (norm != nullptr) {
-    float ss = 0.f;
-    for (int k = tid; k < d; k += 256) {
-      const float v = x_bf16 ? __uint_as_float((uint32_t)reinterpret_cast<const uint16_t*>(x)[row * ldx + k] << 16)
-                             : reinterpret_cast<const float*>(x)[row * ldx + k];
-      ss = fmaf(v, v, ss);
-    }
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) ss += __shfl_xor(ss, off);
-    if (lane == 0) red_s[tid >> 6] = ss;
-    __syncthreads();
-    const float nu = sqrtf((red_s[0] + red_s[1]) + (red_s[2] + red_s[3]));
-    inv = nu > 0.f ? 1.f / nu : 0.f;  // a zero row stays zero
-    if (tid == 0) norm[row] = nu;
-  }
-  if (BITS == 0 && ew == nullptr) return;
-  const int groups = d >> 5;
-  float ee = 0.f;
-  for (int j0 = 0; j0 < d; j0 += 256) {  // uniform trip count; a wavefront covers 64 consecutive coordinates
-    const int j = j0 + tid;
-    int code = 0;
-    if (j < d) {
-      const float y = yw[row * d + j] * inv;
-#pragma unroll
-      for (int t = 0; t < (1 << BITS) - 1; ++t) code += (y >= cb.t[t]) ? 1 : 0;  // on a boundary: the upper cell
-      if (ew != nullptr) {
-        float c = cb.c[0];
-#pragma unroll
-        for (int t = 1; t < (1 << BITS); ++t) c = code == t ? cb.c[t] : c;
-        const float e = y - c;
-        ew[row * d + j] = e;
-        ee = fmaf(e, e, ee);
-      }
-    }
-    const int g = (j0 + (tid & ~63)) >> 5;  // first of the wavefront's two groups of 32
-#pragma unroll
-    for (int pl = 0; pl < BITS; ++pl) {
-      const unsigned long long m = __ballot((code >> pl) & 1);
-      if (lane == 0 && g < groups) idx[row * (int64_t)(groups * BITS) + g * BITS + pl] = (uint32_t)m;
-      if (lane == 32 && g + 1 < groups) idx[row * (int64_t)(groups * BITS) + (g + 1) * BITS + pl] = (uint32_t)(m >> 32);
-    }
-  }
-  if (ew != nullptr) {
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) ee += __shfl_xor(ee, off);
-    if (lane == 0) red_e[tid >> 6] = ee;
-    __syncthreads();
-    if (tid == 0) gamma[row] = sqrtf((red_e[0] + red_e[1]) + (red_e[2] + red_e[3]));
-  }
-}
-
-hipError_t launch_quant_rows(int bits, bool bf16, const void* x, int64_t ldx, int64_t n, int d, const float* Pi,
-                             const Codebook& cb, float* yw, uint32_t* idx, float* norm, hipStream_t stream,
-                             const float* SPiT, float* ew, uint32_t* qjl, float* gamma) {
-  if (n == 0) return hipSuccess;
-  if (n > 65535 * MV_Q || d % 32 != 0 || (size_t)MV_Q * d * sizeof(float) > 65536) return hipErrorInvalidValue;
-  if (const hipError_t e = launch_matvec_rows(d, n, Pi, nullptr, static_cast<const float*>(x), ldx, yw, nullptr, d, bf16, stream); e != hipSuccess)
-    return e;
-  const dim3 grid((unsigned)n);
-  const int xb = bf16 ? 1 : 0;
-  switch (bits) {
-    case 0: hipLaunchKernelGGL(quant_rows_finish_kernel<0>, grid, dim3(256), 0, stream, d, x, ldx, xb, yw, cb, idx, norm, ew, gamma); break;
-    case 1: hipLaunchKernelGGL(quant_rows_finish_kernel<1>, grid, dim3(256), 0, stream, d, x, ldx, xb, yw, cb, idx, norm, ew, gamma); break;
-    case 2: hipLaunchKernelGGL(quant_rows_finish_kernel<2>, grid, dim3(256), 0, stream, d, x, ldx, xb, yw, cb, idx, norm, ew, gamma); break;
-    case 3: hipLaunchKernelGGL(quant_rows_finish_kernel<3>, grid, dim3(256), 0, stream, d, x, ldx, xb, yw, cb, idx, norm, ew, gamma); break;
-    case 4: hipLaunchKernelGGL(quant_rows_finish_kernel<4>, grid, dim3(256), 0, stream, d, x, ldx, xb, yw, cb, idx, norm, ew, gamma); break;
-    default: return hipErrorInvalidValue;
-  }
-  if (const hipError_t e = hipGetLastError(); e != hipSuccess || ew == nullptr) return e;
-  // Alg. 2: u = (S Pi^T) e, again one wavefront per matrix row (into the buffer the rotation has left), signs packed
-  if (const hipError_t e = launch_matvec_rows(d, n, SPiT, nullptr, ew, (int64_t)d, yw, nullptr, d, false, stream); e != hipSuccess) return e;
-  return launch_stage_sign_pack(d, yw, n, qjl, stream);
-}
-
 // DeQuant of Alg. 1 / Alg. 2 for a handful of long vectors: x~[k] = nu (sum_j Pi^T[k][j] c[idx_j] + kappa gamma
 // sum_j S^T[k][j] z_j), one wavefront per output coordinate k (a row of Pi^T and of S^T, 1 KB per load), the decoded
 // codes of Q vectors in LDS (4 for Alg. 1; 2 for Alg. 2, whose sign vector sits beside them).

@@ -23,6 +23,14 @@ def test_small_batches_at_128(bits, n, kind):
         T.test_quantize_mse(128, bits, n, kind)
 
 
+@pytest.mark.parametrize("d,bits,n,kind", [(512, 2, 1, "bf16"), (544, 3, 1, "f32"), (4096, 1, 1, "bf16unit"), (1568, 4, 2, "bf16"),
+                                          (1024, 1, 13, "f32"), (544, 2, 64, "bf16")])
+def test_long_vectors_decided_where_they_are_multiplied(d, bits, n, kind):
+    """One vector, four at a time with 8 and with 16 rows per workgroup; row lengths that are no multiple of 256."""
+    T.test_quantize_a_handful_of_long_vectors(d, bits, n, kind)
+    T.test_quantize_prod_of_a_handful_of_long_vectors(d, bits, n, kind)
+
+
 @pytest.mark.parametrize("d_hi,bits_lo,prod,n,bf16", [(32, 1, True, 1, True), (64, 2, False, 17, False), (96, 0, True, 4096, True),
                                                       (32, 3, False, 4097, True)])
 def test_small_split_batches(d_hi, bits_lo, prod, n, bf16):
