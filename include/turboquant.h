@@ -80,9 +80,9 @@
  *     left out would show in gamma (4-bit MSE stage up to d = 416, 3 bits up to
  *     d = 96, 2 bits at d = 32).
  *   Up to 64 vectors at d >= 512, while ceil(n / 4) d^2 (twice that with a sketch)
- *     is at most 150 x 512^2 and params.workspace holds their rotated coordinates,
- *     are rotated by plain fp32 multiply-adds, one matrix-vector product per
- *     vector, and so are a handful of long vectors in tq_dequantize;
+ *     is at most 150 x 512^2 (and, with a sketch, params.workspace holds their
+ *     residuals) are rotated by plain fp32 multiply-adds, one matrix-vector
+ *     product per vector, and so are a handful of long vectors in tq_dequantize;
  *   dequantise, more than 8192 vectors at d = 128 and every other d: two pieces of
  *     a centroid and of an entry of Pi^T or S^T, a sign as one exact piece (error
  *     below 4e-5 of a coordinate's typical size);
@@ -97,7 +97,8 @@
  *   scoring, few queries: int8 digits (up to 32 per group at d <= 1024, up to 16
  *     per group at d <= 4096 (64 in all beyond d = 512), d a multiple of 128,
  *     codebook symmetric about zero).
- * Smaller batches at d = 128 run on the fp32 matrix instructions.  All paths meet
+ * Smaller batches of fp32 vectors, and of codes, at d = 128 run on the fp32 matrix
+ * instructions.  All paths meet
  * the same tolerances (indices equal to an fp32 evaluation except within 1e-5 of a
  * cell boundary; values and scores within 1e-4 relative).  With TQ_FLAG_FP32_MFMA
  * in params.flags every contraction of tq_quantize_*, tq_dequantize and
@@ -258,7 +259,7 @@ tq_status tq_derive_params(int32_t d, const float* Pi, const float* S, float* Pi
 /* Optional, once per parameter set: the matrices already split into the pieces the quantisation and
  * dequantisation kernels multiply (see "Arithmetic" above), in the kernels' own order, so that no launch splits them
  * again (Alg. 1 / Alg. 2 fix the matrices "at setup"; this is that setup carried one step further).  d = 128: Pi,
- * S Pi^T, Pi^T and S^T as the large-batch kernels keep them in on-chip memory (their prologue becomes a copy);
+ * S Pi^T, Pi^T and S^T as the kernels keep them on chip (their prologue becomes a copy);
  * every other d: Pi and S Pi^T as rows of two fp16 pieces (10 d^2 bytes), which tq_quantize_* and the rotation of many
  * queries multiply.  At those d the quantisers use them only together with a params.workspace that holds the pieces of
  * at least 256 vectors, or of all of them (tq_workspace_bytes(p, n, 0, 0) is enough; a smaller one means fewer vectors

@@ -257,16 +257,27 @@ tq_status quantize_common(const tq_params* p, const void* x, int32_t dtype, int6
     // rows scattered into a larger store (tq_append): the short-chain d = 128 kernel only
     if (d != 128 || n > kSmallQuantRows || !aligned16(x) || (ldx * esz) % 16 != 0) return TQ_ERR_UNSUPPORTED;
     if (p->d_hi != 0 && norm == nullptr) return TQ_ERR_INVALID_ARG;
+    if (dtype == TQ_BF16 && !fp32_mfma_only(p))
+      return from_hip(launch_quant128_few(p->bits_mse, prod, x, ldx, n, p->Pi, prod ? p->SPiT : nullptr, idx, qjl, gamma, norm, make_codebook(p),
+                                          p->d_hi / 32, make_codebook_hi(p), quant_image(p), stream, out_first, out_step));
     return from_hip(launch_quant128_small(p->bits_mse, prod, dtype == TQ_BF16, x, ldx, n, p->Pi,
                                           prod ? p->SPiT : nullptr, idx, qjl, gamma, norm, make_codebook(p),
                                           p->d_hi / 32, p->d_hi != 0 ? make_codebook_hi(p) : make_codebook(p), stream,
                                           out_first, out_step));
   }
 
+  // head dimension 128, a small batch of bf16 vectors
+  auto few128 = [&] {
+    return from_hip(launch_quant128_few(p->bits_mse, prod, x, ldx, n, p->Pi, prod ? p->SPiT : nullptr, idx, qjl, gamma, norm, make_codebook(p),
+                                        p->d_hi / 32, make_codebook_hi(p), quant_image(p), stream));
+  };
+  const bool few128_serves = d == 128 && dtype == TQ_BF16 && n <= kFewQuantRows && !fp32_mfma_only(p) && aligned16(x) && ldx % 8 == 0;
+
   if (p->d_hi != 0) {
     // two instances: the d = 128 kernels; both norms are always stored
     if (norm == nullptr) return TQ_ERR_INVALID_ARG;
     if (!aligned16(x) || (ldx * esz) % 16 != 0) return TQ_ERR_UNSUPPORTED;
+    if (few128_serves) return few128();
     const Codebook cb_hi = make_codebook_hi(p);
     if (dtype == TQ_BF16 && n >= kBf3QuantRows && !fp32_mfma_only(p) && (!prod || aligned16(qjl)) &&
         quant128_bf3_applicable(p->bits_mse, prod, false, x, ldx, make_codebook(p), &cb_hi))
@@ -277,7 +288,9 @@ tq_status quantize_common(const tq_params* p, const void* x, int32_t dtype, int6
                                     p->d_hi / 32, make_codebook_hi(p), stream));
   }
 
-  // head dimension 128, a large batch of bf16 or fp32 vectors: the contractions on the bf16 matrix cores
+  if (few128_serves) return few128();
+
+  // head dimension 128, a large batch of bf16 or fp32 vectors: the contractions on the 16-bit matrix cores
   if (d == 128 && n >= kBf3QuantRows && !fp32_mfma_only(p) && !(prod && dtype == TQ_F32 && !two_piece_x_serves_prod(d, p->bits_mse)) &&
       quant128_bf3_applicable(p->bits_mse, prod, dtype == TQ_F32, x, ldx, make_codebook(p), nullptr) &&
       (p->bits_mse == 0 || aligned16(idx)) && (!prod || aligned16(qjl)))

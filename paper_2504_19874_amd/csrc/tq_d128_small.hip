@@ -1,6 +1,6 @@
-// Quantisation at d = 128 for a small number of vectors: the tokens a decoding
-// step appends to a key cache (Sec. 4.3), or any batch too small to fill the
-// chip with the streaming kernel of tq_d128.hip.
+// Quantisation at d = 128 on the fp32 matrix instructions for a number of vectors too small to fill the
+// chip with the streaming kernel of tq_d128.hip: fp32 vectors, and any with TQ_FLAG_FP32_MFMA (bf16 ones otherwise go to
+// tq_q128_few.hip).
 //
 // There, one wavefront carries a block of 32 vectors through both contractions
 // (512 MFMAs in a row, 14 us) behind a 128 KB parameter load into LDS: fine when

@@ -109,11 +109,18 @@ hipError_t launch_dequant128(int bits, bool prod, const uint32_t* idx, const uin
 
 // d = 128, large batches, bf16 matrix cores at fp32 accuracy (tq_d128_bf3.hip)
 bool dequant128_bf3_applicable(int bits, bool prod, const Codebook& cb, const float* out, int64_t ldo);
-constexpr int64_t kBf3QuantRows = 8193;   // from here on the kernel on 16-bit pieces wins (17 us flat up to 65536 rows against 20 / 29 / 37)
+constexpr int64_t kBf3QuantRows = 8193;   // fp32 vectors: from here on the kernel on 16-bit pieces wins (17 us flat up to 65536 rows against 20 / 29 / 37)
 bool quant128_bf3_applicable(int bits, bool prod, bool f32, const void* X, int64_t ldx, const Codebook& cb, const Codebook* cb_hi);
 hipError_t launch_quant128_bf3(int bits, bool prod, bool f32, const void* X, int64_t ldx, int64_t n, const float* Pi,
                                const float* SPiT, uint32_t* idx, uint32_t* qjl, float* gamma, float* norm,
                                const Codebook& cb, int gs_hi, const Codebook& cb_hi, const void* image, hipStream_t s);
+// d = 128, few bf16 vectors, 16-bit matrix cores (tq_q128_few.hip); image: that of launch_quant128_bf3_image or null.
+// Up to here it is faster than the kernel above whatever the bits (2 + 1 bits, 24576 / 32768 vectors: 10.5 / 12.8 us against 11.6 /
+// 11.7; 4 bits 9.7 / 12.0 against 14.2 / 14.2)
+constexpr int64_t kFewQuantRows = 24576;
+hipError_t launch_quant128_few(int bits, bool prod, const void* X, int64_t ldx, int64_t n, const float* Pi, const float* SPiT, uint32_t* idx,
+                               uint32_t* qjl, float* gamma, float* norm, const Codebook& cb, int gs_hi, const Codebook& cb_hi,
+                               const void* image, hipStream_t s, int64_t out_first = 0, int64_t out_step = 1);
 // the matrices of those two kernels as they sit in LDS, made once (tq_build_images); null pointers above mean
 // "split the fp32 matrices in the kernel's prologue"
 size_t quant128_bf3_image_bytes();

@@ -8,12 +8,12 @@
 //             the B operand; the A operand is a piece of Pi, resident in LDS for the life of the workgroup.
 //   decision  the accumulator tile holds 16 coordinates of one vector per lane: scale by 1 / ||x||, nearest
 //             centroid, packing, residual e = y - c[idx] in place (quantise_tile), gamma = ||e||.
-//   stage 2   u^T = (S Pi^T) e^T, of which only the signs are kept.  The residual registers, split into their
-//             two leading pieces, are directly the B operand (the order in which they enumerate the
+//   stage 2   u^T = (S Pi^T) e^T, of which only the signs are kept.  The residual registers, split into two fp16
+//             pieces (the decision works on 64 y against 64 times the tables, exactly the same comparisons, so that
+//             64 e comes out of it in the middle of the type's range), are directly the B operand (the order in which they enumerate the
 //             contraction index is a fixed permutation inside every run of 16, which the LDS image of
-//             S Pi^T follows).  S Pi^T is held as its two leading pieces as well, and the three products of
-//             combined weight >= 2^-9 are taken: what is left out is 2^-17.8 of a term (root mean square), about
-//             5e-7 |S_j| |e| in u, against the 1e-5 |S_j| |e| inside which a sign may differ from the exact one.
+//             S Pi^T follows).  S Pi^T is two fp16 pieces as well, and three products are taken: what is left out
+//             is below the fp32 sums' own rounding, where two bf16 pieces each left out 5e-7 |S_j| |e| in u.
 //   LDS       two pieces of Pi and two of S Pi^T, 128 x 128 values of 16 bits each, 128 of the 160 KB of a compute
 //             unit: rows are stored without padding, the 16-byte chunks of a row rotated by the row number
 //             (conflict-free 16-byte reads along a column of chunks).
@@ -29,23 +29,19 @@
 // 4.3e9 decisions (4 bits, bf16) 1186 on the other side of a boundary against 1125 for keys with outlier channels, 1195
 // against 1222 for normal vectors; gamma at 3 + 1 bits off by 1.01e-7 against 1.07e-7 in the root mean square.  An fp32
 // vector gains 17 -> 22 bits: 1785 -> 105 of 2.7e8, gamma 1.24e-6 -> 1.1e-7.
+// Signs on the other side of zero: 1.23 of 10^6 with bf16 pieces in the sketch, 0.10 with fp16 ones (fp32 instructions 0.13), same time.
 #include <type_traits>
 
 #include "tq_bf3.h"
 #include "tq_d128_tile.h"
 #include "tq_h2.h"
+#include "tq_q128.h"
 
 namespace tq {
 
 namespace {
 
-constexpr int MAT_ELEMS = 128 * 128;  // one piece of one matrix
-constexpr int PI_ELEMS = 2 * MAT_ELEMS;
-constexpr int W_ELEMS = 2 * MAT_ELEMS;
 constexpr int RING = 4;  // A operands in flight
-
-// element offset of column col (a multiple of 4) of row `row` inside a piece: chunk (col / 8) xor (row % 16)
-__device__ __forceinline__ int lds_at(int row, int col) { return row * 128 + ((((col >> 3) ^ row) & 15) << 3) + (col & 7); }
 
 struct Q128Args {
   const void* X;  // bf16, or fp32 in the F32 instantiations
@@ -66,51 +62,30 @@ struct Q128Args {
   Codebook cb_hi;
 };
 
-// sum of the squares of two bf16 values added to acc: one two-element dot product with fp32 accumulation
-typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
-__device__ __forceinline__ float square_pair(uint32_t w, float acc) {
-  const bf16x2_t v = __builtin_bit_cast(bf16x2_t, w);
-  return __builtin_amdgcn_fdot2_f32_bf16(v, v, acc, false);
-}
-
-// position of column j inside its run of 16 in the image of S Pi^T: the two middle groups of four change
-// places (see stage 2)
-__device__ __forceinline__ int w_col(int j) { return (j & ~12) | ((j & 4) << 1) | ((j & 8) >> 1); }
-
-// The bit pattern of the largest magnitude of a 128 x 128 matrix, by NT threads; max_s: a word of LDS that was cleared
-template <int NT>
-__device__ __forceinline__ uint32_t largest_of(const float* W, uint32_t* max_s, int tid) {
-  uint32_t m = 0u;
-#pragma unroll
-  for (int i = 0; i < 4096 / NT; ++i) {
-    const u32x4 v = *reinterpret_cast<const u32x4*>(W + (i * NT + tid) * 4);
-#pragma unroll
-    for (int e = 0; e < 4; ++e) m = max(m, v[e] & 0x7fffffffu);
-  }
-  atomicMax(max_s, m);
-  __syncthreads();
-  return *max_s;
-}
-
-// The kernel's parameter image, by 256 threads: two fp16 pieces of s Pi at dst, two bf16 pieces of S Pi^T (columns permuted)
-// behind them, each [row][128] with the chunk rotation of lds_at.  dst is LDS in the quantisation kernel and device
-// memory in q128_image_kernel.
+// The kernel's parameter image, by 256 threads: two fp16 pieces of s Pi at dst, two of S Pi^T (every row under a power of two
+// of its own, which its signs do not see; columns permuted) behind them, each [row][128] with the chunk rotation of q128_at.
+// dst is LDS in the quantisation kernel and device memory in q128_image_kernel.
 __device__ __forceinline__ void q128_split_matrices(const float* Pi, const float* SPiT, float s, unsigned short* dst, int tid) {
-  // rows [row0, row0 + 64) of a 128 x 128 fp32 matrix -> two pieces; 8 x 16 bytes per thread
+  // rows [row0, row0 + 64) of a 128 x 128 fp32 matrix -> two pieces; 8 x 16 bytes per thread, a row to 32 lanes
   auto split_rows = [&](const f32x4 (&v)[8], unsigned short* out, int row0, bool sketch) {
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
       const int e = (i * 256 + tid) * 4;
       const int row = row0 + (e >> 7), j = e & 127;
-      uint32_t lo[2], hi[2];
+      float sc = s;
       if (sketch) {
-        split2_pair(f32x2{v[i][0], v[i][1]}, lo[0], lo[1]);
-        split2_pair(f32x2{v[i][2], v[i][3]}, hi[0], hi[1]);
-      } else {
-        h2_split(s * v[i][0], s * v[i][1], lo[0], lo[1]);
-        h2_split(s * v[i][2], s * v[i][3], hi[0], hi[1]);
+        uint32_t m = 0u;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) m = max(m, __float_as_uint(v[i][k]) & 0x7fffffffu);
+#pragma unroll
+        for (int k = 1; k < 32; k <<= 1) m = max(m, (uint32_t)__shfl_xor((int)m, k));
+        float inv;
+        h2_scale(m, sc, inv);
       }
-      const int at = lds_at(row, sketch ? w_col(j) : j);
+      uint32_t lo[2], hi[2];
+      h2_split(sc * v[i][0], sc * v[i][1], lo[0], lo[1]);
+      h2_split(sc * v[i][2], sc * v[i][3], hi[0], hi[1]);
+      const int at = q128_at(row, sketch ? q128_w_col(j) : j);
 #pragma unroll
       for (int pc = 0; pc < 2; ++pc) *reinterpret_cast<uint2*>(out + pc * MAT_ELEMS + at) = make_uint2(lo[pc], hi[pc]);
     }
@@ -158,8 +133,8 @@ __global__ __launch_bounds__(512 / VT, q128_per_cu(PROD, F32) * 2 / VT) void qua
   constexpr int NB = (BITS > 0 ? BITS : 1) + (MIXED ? 1 : 0);  // plane words per tile, at most
   constexpr int BH = BITS < 4 ? BITS + 1 : 4;                  // bits of instance hi
   extern __shared__ __attribute__((aligned(16))) unsigned short lds_s[];
-  unsigned short* const Pi_s = lds_s;            // fp16, [piece][row j][128], see lds_at
-  unsigned short* const W_s = lds_s + PI_ELEMS;  // bf16, [piece][row j'][128], columns permuted
+  unsigned short* const Pi_s = lds_s;            // fp16, [piece][row j][128], see q128_at
+  unsigned short* const W_s = lds_s + PI_ELEMS;  // fp16, [piece][row j'][128], columns permuted
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -286,7 +261,7 @@ __global__ __launch_bounds__(512 / VT, q128_per_cu(PROD, F32) * 2 / VT) void qua
             xop[nt][s][j] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pkrtz(sc * __uint_as_float(w << 16), sc * __uint_as_float(w & 0xffff0000u)));
           }
         }
-      inv[nt] = inv[nt] * unit[nt] * pi_inv;
+      inv[nt] = inv[nt] * unit[nt] * (pi_inv * Q128_RES);
     }
 
     // ---- stage 1: y^T = Pi x^T, two piece products (F32: three) ------------------------------------------
@@ -297,7 +272,7 @@ __global__ __launch_bounds__(512 / VT, q128_per_cu(PROD, F32) * 2 / VT) void qua
       // the A operands travel through a ring of RING registers, read RING MFMA pairs ahead of their use: left to
       // itself the compiler reuses two registers and every group of MFMAs waits for a full LDS round trip
       auto pi_piece = [&](int i) {  // read i of 64: step i / 8, the lo piece before the hi, tile i % 4
-        return *reinterpret_cast<const f16x8*>(Pi_s + (1 - ((i >> 2) & 1)) * MAT_ELEMS + lds_at(32 * (i & 3) + vi, 16 * (i / 8) + 8 * g));
+        return *reinterpret_cast<const f16x8*>(Pi_s + (1 - ((i >> 2) & 1)) * MAT_ELEMS + q128_at(32 * (i & 3) + vi, 16 * (i / 8) + 8 * g));
       };
       f16x8 ring[RING];
 #pragma unroll
@@ -346,8 +321,8 @@ __global__ __launch_bounds__(512 / VT, q128_per_cu(PROD, F32) * 2 / VT) void qua
           s_lo += t < gs ? 0.f : s0 + s1;
         }
         const float r_hi = sqrtf(add_across_halves(s_hi)), r_lo = sqrtf(add_across_halves(s_lo));
-        inv_hi[nt] = r_hi > 0.f ? 1.f / r_hi : 0.f;
-        inv[nt] = r_lo > 0.f ? 1.f / r_lo : 0.f;
+        inv_hi[nt] = r_hi > 0.f ? Q128_RES / r_hi : 0.f;
+        inv[nt] = r_lo > 0.f ? Q128_RES / r_lo : 0.f;
         nuh[nt] = r_hi * unit[nt] * pi_inv;
         nu[nt] = r_lo * unit[nt] * pi_inv;
       }
@@ -371,7 +346,7 @@ __global__ __launch_bounds__(512 / VT, q128_per_cu(PROD, F32) * 2 / VT) void qua
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
               uint32_t w1, w2;
-              split2_pair(f32x2{acc[nt][t][8 * p + 2 * e], acc[nt][t][8 * p + 2 * e + 1]}, w1, w2);
+              h2_split(acc[nt][t][8 * p + 2 * e], acc[nt][t][8 * p + 2 * e + 1], w1, w2);
               rp[0][nt][2 * t + p][e] = w1;
               rp[1][nt][2 * t + p][e] = w2;
             }
@@ -441,10 +416,10 @@ __global__ __launch_bounds__(512 / VT, q128_per_cu(PROD, F32) * 2 / VT) void qua
         floatx16 u[VT][2];
         {
           auto w_piece = [&](int i) {  // read i of 32: step i / 4, pieces 1, 0, tile i % 2
-            return *reinterpret_cast<const bf16x8*>(W_s + (1 - ((i >> 1) & 1)) * MAT_ELEMS +
-                                                    lds_at(64 * pass + 32 * (i & 1) + vi, 16 * (i >> 2) + 8 * g));
+            return *reinterpret_cast<const f16x8*>(W_s + (1 - ((i >> 1) & 1)) * MAT_ELEMS +
+                                                    q128_at(64 * pass + 32 * (i & 1) + vi, 16 * (i >> 2) + 8 * g));
           };
-          bf16x8 ring[RING];
+          f16x8 ring[RING];
 #pragma unroll
           for (int i = 0; i < RING; ++i) ring[i] = w_piece(i);
 #pragma unroll
@@ -454,8 +429,8 @@ __global__ __launch_bounds__(512 / VT, q128_per_cu(PROD, F32) * 2 / VT) void qua
             for (int pb = 1 - pa; pb >= 0; --pb)
 #pragma unroll
               for (int nt = 0; nt < VT; ++nt)
-                u[nt][mt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ring[i % RING], *reinterpret_cast<const bf16x8*>(&rp[pb][nt][s]),
-                                                                    i < 2 ? zero16 : u[nt][mt], 0, 0, 0);
+                u[nt][mt] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ring[i % RING], *reinterpret_cast<const f16x8*>(&rp[pb][nt][s]),
+                                                                   i < 2 ? zero16 : u[nt][mt], 0, 0, 0);
             if (i + RING < 32) ring[i % RING] = w_piece(i + RING);
             // the next block's vectors: all sixteen loads during the first pass
             if (pass == 0 && (i & 1) && (VT == 2 || !(i & 2)))
@@ -491,9 +466,9 @@ __global__ __launch_bounds__(512 / VT, q128_per_cu(PROD, F32) * 2 / VT) void qua
         *reinterpret_cast<u32x4*>(a.qjl + v_mine * 4) =
             g ? u32x4{sw[HI][0], sw[HI][1], sw[HI][2], sw[HI][3]} : u32x4{sw[0][0], sw[0][1], sw[0][2], sw[0][3]};
         if (MIXED) {
-          *reinterpret_cast<float2*>(a.gamma + 2 * v_mine) = make_float2(sqrtf(g ? g2h[HI] : g2h[0]), sqrtf(g ? g2[HI] : g2[0]));
+          *reinterpret_cast<float2*>(a.gamma + 2 * v_mine) = make_float2(sqrtf(g ? g2h[HI] : g2h[0]) * (1.f / Q128_RES), sqrtf(g ? g2[HI] : g2[0]) * (1.f / Q128_RES));
         } else {
-          a.gamma[v_mine] = sqrtf(g ? g2[HI] : g2[0]);
+          a.gamma[v_mine] = sqrtf(g ? g2[HI] : g2[0]) * (1.f / Q128_RES);
         }
       }
     }
@@ -542,7 +517,7 @@ hipError_t launch_quant128_bf3(int bits, bool prod, bool f32, const void* X, int
   Q128Args a;
   a.X = X; a.ldx = ldx; a.n = n; a.Pi = Pi; a.SPiT = SPiT; a.idx = idx; a.qjl = qjl;
   a.image = static_cast<const u32x4*>(image);
-  a.gamma = gamma; a.norm = norm; a.cb = cb; a.gs_hi = gs_hi; a.cb_hi = cb_hi;
+  a.gamma = gamma; a.norm = norm; a.cb = q128_scaled(cb); a.gs_hi = gs_hi; a.cb_hi = q128_scaled(cb_hi);
   if (gs_hi > 0) {
     switch (bits * 2 + (prod ? 1 : 0)) {
       case 0: return launch_one<0, false, true>(a, f32, s);

@@ -1,0 +1,61 @@
+"""bf16 vectors at d = 128 in batches too small for the kernel that keeps its matrices in LDS: blocks of 16 vectors, shared by
+up to eight workgroups while they leave compute units idle, two and more per workgroup at the other end."""
+import pytest
+import torch
+
+from tests import test_gpu_parity as T
+from tests import test_gpu_split as S
+
+pytestmark = pytest.mark.gpu
+
+tq = pytest.importorskip("paper_2504_19874_amd")
+
+
+@pytest.mark.parametrize("bits,n,kind", [(1, 1, "bf16unit"), (2, 512, "bf16"), (3, 513, "bf16"), (4, 1040, "bf16unit"), (0, 2065, "bf16"),
+                                         (2, 8193, "bf16unit"), (3, 24576, "bf16"), (1, 24577, "bf16")])
+def test_blocks_and_shares(bits, n, kind):
+    T.test_quantize_prod(128, bits, n, kind)
+    if bits:
+        T.test_quantize_mse(128, bits, n, kind)
+
+
+@pytest.mark.parametrize("d_hi,bits_lo,prod,n", [(64, 1, True, 513), (32, 3, True, 8209), (96, 0, False, 33), (96, 2, False, 24576)])
+def test_two_instances(d_hi, bits_lo, prod, n):
+    S.test_quantize_split(d_hi, bits_lo, prod, n, True)
+
+
+@pytest.mark.parametrize("bits,prod,n", [(2, True, 8), (4, False, 100), (3, True, 9000)])
+def test_without_images_and_scattered(bits, prod, n):
+    """The matrices split in the kernel, and rows written `step` apart: the same bits."""
+    p = T.setup(128, bits, prod)[0]
+    x = (torch.randn(n, 128, generator=torch.Generator().manual_seed(n)) * 3).to(torch.bfloat16).to(T.DEV)
+    x[n // 2] = 0  # a zero row stays zero
+    first, step = 5, 3
+
+    def run(scattered):
+        rows = first + step * n if scattered else n
+        c = [torch.full((rows, p.idx_words), 7, dtype=torch.int32, device=T.DEV), torch.full((rows, p.qjl_words), 7, dtype=torch.int32, device=T.DEV),
+             torch.full((rows,), 7.0, device=T.DEV), torch.full((rows,), 7.0, device=T.DEV)]
+        if not prod:
+            c[1] = c[2] = None
+        if scattered:
+            tq.tq_append(p, x, *c, first, step)
+            at = first + step * torch.arange(n, device=T.DEV)
+            others = torch.ones(rows, dtype=torch.bool, device=T.DEV)
+            others[at] = False
+            assert all(bool((v[others] == 7).all()) for v in c if v is not None)
+            return [v[at] for v in c if v is not None]
+        if prod:
+            tq.tq_quantize_prod(p, x, *c)
+        else:
+            tq.tq_quantize_mse(p, x, c[0], c[3])
+        return [v for v in c if v is not None]
+
+    want = run(False)
+    assert float(want[-1][n // 2]) == 0.0
+    assert all(torch.equal(a, b) for a, b in zip(want, run(True)))
+    try:
+        p.drop_images()
+        assert all(torch.equal(a, b) for a, b in zip(want, run(False)))
+    finally:
+        p.build_images()
