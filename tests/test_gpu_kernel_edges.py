@@ -131,3 +131,9 @@ def test_search_by_candidates_with_too_many_of_them(d, bits, prod):
     for norm in (np.ones(n), np.linspace(1.0, 2.0, n), np.where(np.arange(n) % 3 == 0, 1.0, 0.0)):
         c["norm"] = T.dev(norm.astype(np.float32))
         T._topk_both_ways(p, q, 1, nq, c, n, topk)
+
+
+@pytest.mark.parametrize("vprod,groups,qpg,npg", [(True, 2, 3, 1), (False, 64, 2, 30721), (True, 1, 1, 32768), (False, 1, 2, 131073)])
+def test_attend_joins_of_chunks(vprod, groups, qpg, npg):
+    """One chunk, more than sixteen, the 64 that a wavefront's lanes hold, and one more."""
+    A.run_attend(128, 2, True, 2, vprod, groups, qpg, npg, True)
