@@ -133,7 +133,7 @@ def test_search_by_candidates_with_too_many_of_them(d, bits, prod):
         T._topk_both_ways(p, q, 1, nq, c, n, topk)
 
 
-@pytest.mark.parametrize("vprod,groups,qpg,npg", [(True, 2, 3, 1), (False, 64, 2, 30721), (True, 1, 1, 32768), (False, 1, 2, 131073)])
+@pytest.mark.parametrize("vprod,groups,qpg,npg", [(True, 2, 3, 1), (False, 2, 2, 8193), (True, 1, 1, 32768), (False, 1, 2, 32769)])
 def test_attend_joins_of_chunks(vprod, groups, qpg, npg):
     """One chunk, more than sixteen, the 64 that a wavefront's lanes hold, and one more."""
     A.run_attend(128, 2, True, 2, vprod, groups, qpg, npg, True)
