@@ -7,7 +7,7 @@
 //     sum_i w_qi c[idx_ij] = coef[0] * sum_i w_qi + sum_S coef[S] * sum_i w_qi x_S(idx_ij):
 // sums of weights over the KEYS selected by a bit mask.  The sign term of Alg. 2 is one more
 // such sum, over the sign bits with the weights exp(logit - m) * nu_i * gamma_i (VPROD).  The weights w_qi = exp(logit - m) * nu_i
-// are scaled by a power of two to 26-bit integers and split into four base-128 digits (0..127);
+// are scaled by a power of two to 26-bit integers and split into four balanced base-256 digits;
 // one v_mfma_i32_16x16x64_i8 multiplies the 16 rows (4 queries x 4 digits) with 64 keys x 16
 // coordinates of 0/1 bytes.
 //
@@ -81,7 +81,12 @@ __device__ __forceinline__ void transpose16x32(uint32_t (&x)[16]) {
     x[k + J] = ((a >> J) & M) | (b & ~M);                        \
     x[k] = (a & ~(M << J)) | ((b << J) & (M << J));              \
   }
-  TQ_SWAP_STAGE(8, 0x00FF00FFu)
+#pragma unroll
+  for (int k = 0; k < 8; ++k) {  // whole bytes
+    const uint32_t a = x[k], b = x[k + 8];
+    x[k + 8] = __builtin_amdgcn_perm(b, a, 0x07030501u);
+    x[k] = __builtin_amdgcn_perm(b, a, 0x06020400u);
+  }
   TQ_SWAP_STAGE(4, 0x0F0F0F0Fu)
   TQ_SWAP_STAGE(2, 0x33333333u)
   TQ_SWAP_STAGE(1, 0x55555555u)
@@ -173,7 +178,7 @@ __global__ __launch_bounds__(512) void attend128_kernel(const ScoreI8Args ka, co
   for (int t = 0; t < TILES; ++t) lg[t] = -INFINITY;
   if (FUSED) {
     auto sink = [&](int t, float score, bool key_live) { lg[t] = key_live ? scale2 * score : -INFINITY; };
-    score128_body<KB, KPROD, TILES, SCORE128_ROUND_TILES, SCORE128_ROUNDS_AHEAD>(ka, dyn_s, sink);
+    score128_body<KB, KPROD, TILES>(ka, dyn_s, sink);
   } else {
     const int64_t qrow = (int64_t)group * a.q_per_group + (q0 + kc < a.q_per_group ? q0 + kc : q0);
     const float* srow = a.scores + qrow * a.lds + wave_key0 + col;
@@ -234,8 +239,17 @@ __global__ __launch_bounds__(512) void attend128_kernel(const ScoreI8Args ka, co
     const uint2 hi = *reinterpret_cast<const uint2*>(table + o1);
     return v4i{(int)lo.x, (int)lo.y, (int)hi.x, (int)hi.y};
   };
-  auto digits_sum = [&](const v4i& acc) -> float {  // D0 + 2^7 D1 + 2^14 D2 + 2^21 D3
-    return fmaf((float)acc[3], 2097152.f, (float)(acc[0] + acc[1] * 128 + acc[2] * 16384));
+  auto digits_sum = [&](const v4i& acc) -> float {  // D0 + 2^8 D1 + 2^16 D2 + 2^24 D3; |D0 .. D2| <= 2^14
+    return fmaf((float)acc[3], 16777216.f, (float)(acc[0] + (acc[1] << 8) + (acc[2] << 16)));
+  };
+  // A weight of at most 26 bits as four balanced base-256 digits (the first three of -128 .. 127, which is the integer's bytes
+  // after adding 128 to each and taking it off again), and of these, by a transposition among the four lanes of a quad, digit
+  // lane % 4 of the quad's four keys in one word: one store in place of a byte per digit, and a third of the instructions.
+  const uint32_t sel1 = lane & 1 ? 0x03070105u : 0x06020400u, sel2 = lane & 2 ? 0x03020706u : 0x05040100u;
+  auto four_digits = [&](uint32_t Q) -> uint32_t {
+    uint32_t w = (Q + 0x00808080u) ^ 0x00808080u;
+    w = __builtin_amdgcn_perm((uint32_t)dpp_move<0xB1>((int)w), w, sel1);
+    return __builtin_amdgcn_perm((uint32_t)dpp_move<0x4E>((int)w), w, sel2);
   };
 
   float f[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};  // coordinate 16 cb + col of query kc
@@ -247,27 +261,18 @@ __global__ __launch_bounds__(512) void attend128_kernel(const ScoreI8Args ka, co
 
 #pragma unroll
   for (int ps = 0; ps < PASSES; ++ps) {
-    // weights of this lane's (query, key) pairs -> four base-128 digits
+    // weights of this lane's (query, key) pairs -> four base-256 digits
 #pragma unroll
     for (int tt = 0; tt < PT; ++tt) {
       const int t = PT * ps + tt;
       const float nu = __int_as_float(__builtin_amdgcn_ds_bpermute(4 * (16 * (t & 3) + col), __float_as_int(nuv[t >> 2])));
       const float p = __builtin_amdgcn_exp2f(lg[t] - m);  // 0 for keys past the end (logit -inf)
       lsum += p;
-      // the weight is not negative: plain base-128 digits 0..127 fit the signed bytes of the operand
-      const uint32_t Q = (uint32_t)__float2int_rn(p * nu * wscale);
-      unsigned char* o = wd + (kc * 4) * PASS_KEYS + 16 * tt + col;
-      o[0] = (unsigned char)(Q & 127u);
-      o[PASS_KEYS] = (unsigned char)((Q >> 7) & 127u);
-      o[2 * PASS_KEYS] = (unsigned char)((Q >> 14) & 127u);
-      o[3 * PASS_KEYS] = (unsigned char)(Q >> 21);
+      uint32_t* const o = reinterpret_cast<uint32_t*>(wd + (kc * 4 + (col & 3)) * PASS_KEYS + 16 * tt + (col & 12));
+      *o = four_digits((uint32_t)__float2int_rn(p * nu * wscale));
       if (TWO) {
         const float ng = __int_as_float(__builtin_amdgcn_ds_bpermute(4 * (16 * (t & 3) + col), __float_as_int(ngv[t >> 2])));
-        const uint32_t Z = (uint32_t)__float2int_rn(p * ng * zscale);
-        o[WD_BYTES] = (unsigned char)(Z & 127u);
-        o[WD_BYTES + PASS_KEYS] = (unsigned char)((Z >> 7) & 127u);
-        o[WD_BYTES + 2 * PASS_KEYS] = (unsigned char)((Z >> 14) & 127u);
-        o[WD_BYTES + 3 * PASS_KEYS] = (unsigned char)(Z >> 21);
+        o[WD_BYTES / 4] = four_digits((uint32_t)__float2int_rn(p * ng * zscale));
       }
     }
     // value code words: 16 keys x 32 coordinates -> 32 coordinates x 16 keys

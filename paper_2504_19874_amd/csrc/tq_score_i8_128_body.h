@@ -18,11 +18,12 @@
 //     query coordinates through scalar registers; then digits into LDS).  That
 //     re-reads 128 KB of matrices per workgroup, which is cheaper than the
 //     launch-and-latency chain of a preparation kernel in front,
-//   * the mask operands need no lookup: a stored word ANDed with 0x01010101 << k is already four
-//     operand bytes (bit k + 8 b of the word in byte b, worth 2^k), and the query digits are
-//     written pre-scaled by 2^(7 - k) to match (I8Prep::digitise<true>), so a tile's operands cost
-//     eight ANDs per stored word where a table in LDS cost four 8-byte reads per word and bounded
-//     the tile phase (8 x 65536 keys, 4 queries each: 3.4 of 14.3 us).
+//   * the masked sums are taken on v_mfma_f32_16x16x128_f8f6f4, all 128 coordinates of a key at once: a stored word ANDed
+//     with 0x11111111 << v already is eight fp4 operands, and the query digits (balanced base 32, fp8) are written
+//     scaled to match (put_mask_digits): five instructions per stored word.  Digits and sums are integers below 2^24, so
+//     nothing is rounded.  As bytes for the integer instructions (eight per word, digits with 11 instructions to join where these
+//     take three) 8 x 65536 keys, 4 queries each, took 10.5 / 11.9 / 15.2 us at 1 + 1 / 2 + 1 / 3 + 1 bits and 16.6 at 4, now 9.6 / 11.2 / 13.7
+//     and 15.4, the same bits; an expansion table in LDS cost four 8-byte reads per word.
 //
 // Workgroup = 512 threads = 8 wavefronts; a wavefront owns 256 consecutive keys
 // = 16 tiles of 16, staged ROUND tiles at a time.  grid = (ceil(n / 2048),
@@ -34,6 +35,7 @@
 
 namespace tq {
 
+typedef int v8i __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
@@ -43,11 +45,8 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 // one in flight: 13.1; on another box 12.5 against rounds of 2 tiles with 2 / 3 / 4 / 6 in flight: 13.0 / 12.7 /
 // 12.9 / 13.7, and rounds of one tile with 5 / 8 in flight: 13.7 / 14.3).
 constexpr int SCORE128_ROUND_TILES = 4, SCORE128_ROUNDS_AHEAD = 2;
-constexpr int TILES_128 = 16;  // tiles per wavefront (the default; 8 or 4 where that would leave compute units idle)
-// tiles staged in LDS at a time
-__host__ __device__ constexpr int round_tiles(int bits) { return bits <= 3 ? 8 : 4; }
-// bytes of one wavefront's staging region: idx, qjl, gamma, norm of 16 * round_tiles rows
-__host__ __device__ constexpr int stage_bytes(int bits) { return 16 * round_tiles(bits) * (16 * bits + 16 + 4 + 4); }
+// bytes of one wavefront's staging region: idx, qjl, gamma, norm of a round's rows
+__host__ __device__ constexpr int stage_bytes(int bits) { return 16 * SCORE128_ROUND_TILES * (16 * bits + 16 + 4 + 4); }
 
 // staging regions, partial sums of the query preparation (8 KB), one 2 KB digit image per masked sum, scalars
 __host__ __device__ constexpr int score128_lds(int bits) { return 8 * stage_bytes(bits) + 2 * 2 * 4 * 128 * 4 + i8_terms(bits, true) * 2048 + 2 * 4 * 4 * 4; }
@@ -57,10 +56,9 @@ __host__ __device__ constexpr int score128_lds(int bits) { return 8 * stage_byte
 // (query q0 + lane / 16, key wave_key0 + 16 t + lane % 16), wave_key0 = (8 blockIdx.x + wave) * 16 TILES.
 // dyn_s: score128_lds(BITS) bytes, 8 staging regions, then the query preparation.  All of LDS may be reused after the workgroup's
 // next barrier.
-template <int BITS, bool PROD, int TILES = TILES_128, int RTP = 0, int INFLIGHT = 0, class Sink>
+template <int BITS, bool PROD, int TILES, class Sink>
 __device__ __forceinline__ void score128_body(const ScoreI8Args& a, unsigned char* dyn_s, Sink& sink) {
-  constexpr int RT0 = RTP > 0 ? RTP : round_tiles(BITS);
-  constexpr int RT = RT0 < TILES ? RT0 : TILES;
+  constexpr int RT = SCORE128_ROUND_TILES < TILES ? SCORE128_ROUND_TILES : TILES;
   constexpr int ROWS = 16 * RT;               // rows staged per round
   constexpr int ROUNDS = TILES / RT;
   constexpr int NM = (1 << BITS) - 1;
@@ -85,7 +83,7 @@ __device__ __forceinline__ void score128_body(const ScoreI8Args& a, unsigned cha
 
   unsigned char* const stage = dyn_s + wave * stage_bytes(BITS);
   float* const part_s = reinterpret_cast<float*>(dyn_s + 8 * stage_bytes(BITS));        // [2][2][4][128]
-  signed char* const dig_s = reinterpret_cast<signed char*>(part_s + 2 * 2 * 4 * 128);  // [term][4][4][128]
+  unsigned char* const dig_s = reinterpret_cast<unsigned char*>(part_s + 2 * 2 * 4 * 128);  // [term][4][4][128]
   float* const scal_s = reinterpret_cast<float*>(dig_s + i8_terms(BITS, true) * 2048);  // [2][4][4]
 
   // ---- 1. this thread's column of the transposed matrix: 64 values of k ---------------------
@@ -108,6 +106,8 @@ __device__ __forceinline__ void score128_body(const ScoreI8Args& a, unsigned cha
     const int p = i * 64 + lane;
     return count % 64 == 0 ? p : (p < count ? p : count - 1);
   };
+  // (codes without norms: something else with a word per row, so that the load needs no branch; chosen when it has arrived)
+  const float* const norms = a.norm != nullptr ? a.norm : PROD ? a.gamma : reinterpret_cast<const float*>(a.idx);
   auto issue_round = [&](int r) {
     const int64_t row0 = wrow0 + r * ROWS;
 #pragma unroll
@@ -127,12 +127,13 @@ __device__ __forceinline__ void score128_body(const ScoreI8Args& a, unsigned cha
       int64_t row = row0 + in_round(i, ROWS);
       if (!full) row = row < a.total_rows - 1 ? row : a.total_rows - 1;
       cg[r][i] = PROD ? a.gamma[row] : 0.f;
-      cn[r][i] = a.norm != nullptr ? a.norm[row] : 1.f;
+      cn[r][i] = norms[row];
     }
   };
-  constexpr int AHEAD = (INFLIGHT > 0 && INFLIGHT < ROUNDS) ? INFLIGHT : ROUNDS;  // rounds requested before the first is used
+  constexpr int AHEAD = SCORE128_ROUNDS_AHEAD < ROUNDS ? SCORE128_ROUNDS_AHEAD : ROUNDS;  // rounds requested before the first is used
 #pragma unroll
   for (int r = 0; r < AHEAD; ++r) issue_round(r);
+  __builtin_amdgcn_sched_barrier(0);  // all of these are asked for here (left to itself the compiler requests a matrix entry when it is due)
 
   // ---- 3. rotate / sketch this workgroup's four queries, 4. fixed point --------------------------
   prep.matvec(a, group, q0, part_s);
@@ -142,17 +143,15 @@ __device__ __forceinline__ void score128_body(const ScoreI8Args& a, unsigned cha
 
   // ---- 5. A operands: lane = row + 16 kq, row = 4 * query + digit; one image per masked sum --------
   const int a_query = col >> 2, a_digit = col & 3;
-  constexpr bool A_REGS = NTA <= 3;  // else read at every use (LDS has nothing else to do)
-  auto a_read = [&](int j, int s) -> v4i {
-    return *reinterpret_cast<const v4i*>(dig_s + ((j * 4 + a_query) * 4 + a_digit) * 128 + (s * 4 + kq) * 16);  // slot order of i8_shifted_slot
+  auto a_read = [&](int j) -> v8i {
+    const unsigned char* const row = dig_s + ((j * 4 + a_query) * 4 + a_digit) * 128 + 16 * kq;  // see mask_slot
+    const v4i lo = *reinterpret_cast<const v4i*>(row), hi = *reinterpret_cast<const v4i*>(row + 64);
+    return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
   };
-  v4i areg[A_REGS ? NTA : 1][2];
-  if (A_REGS) {
+  // (kept: read at every use they are 16 KB of LDS reads per tile at 4 bits, 22.9 us in place of 15.4)
+  v8i areg[NTA];
 #pragma unroll
-    for (int j = 0; j < NT; ++j)
-#pragma unroll
-      for (int s = 0; s < 2; ++s) areg[j][s] = a_read(j, s);
-  }
+  for (int j = 0; j < NT; ++j) areg[j] = a_read(j);
   float r_inv = 0.f, base_r = 0.f, s_inv = 0.f, s_sum = 0.f;
   if (BITS > 0) {
     r_inv = scal_s[(0 * 4 + kq) * 4];
@@ -163,19 +162,12 @@ __device__ __forceinline__ void score128_body(const ScoreI8Args& a, unsigned cha
     s_sum = scal_s[(1 * 4 + kq) * 4 + 1];
   }
 
-  // B operand of k-step s from the 32 stored bits w of this lane's k-chunk: dword i keeps bits
-  // 4 s + i + {0, 8, 16, 24} of w where they are, one AND each.  Byte b of it is bit
-  // k + 8 b (k = 4 s + i) times 2^k; the digits on the A side are those of the coordinate
-  // times 2^(7 - k) (negated for k = 7, where the byte reads as -128), so every product
-  // carries the same factor 128.
-  auto expand16 = [&](uint32_t w, int s) -> v4i {
-    v4i b;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) b[i] = (int)(w & (0x01010101u << (4 * s + i)));
-    return b;
+  // B operand from the 32 stored bits w of this lane's coordinate group
+  auto masks = [&](uint32_t w) -> v4i {
+    return v4i{(int)(w & 0x11111111u), (int)(w & 0x22222222u), (int)(w & 0x44444444u), (int)((w >> 3) & 0x11111111u)};
   };
-  auto digits_sum = [&](const v4i& acc) -> float {  // (D0 + 2^7 D1 + 2^14 D2 + 2^21 D3) / 128, D0 a multiple of 128
-    return (float)((((acc[3] << 7) + acc[2]) << 7) + acc[1] + (acc[0] >> 7));
+  auto digits_sum = [&](const f32x4& acc) -> float {  // D0 + 2^5 D1 + 2^10 D2 + 2^15 D3, the inner sums exact
+    return fmaf(fmaf(acc[3], 32.f, acc[2]), 1024.f, fmaf(acc[1], 32.f, acc[0]));
   };
 
   const float zs = 2.f * s_inv;
@@ -197,7 +189,7 @@ __device__ __forceinline__ void score128_body(const ScoreI8Args& a, unsigned cha
 #pragma unroll
     for (int i = 0; i < NR; ++i) {
       if (PROD) *reinterpret_cast<float*>(stage + GAM_OFF + in_round(i, ROWS) * 4) = cg[r][i];
-      *reinterpret_cast<float*>(stage + NRM_OFF + in_round(i, ROWS) * 4) = cn[r][i];
+      *reinterpret_cast<float*>(stage + NRM_OFF + in_round(i, ROWS) * 4) = a.norm != nullptr ? cn[r][i] : 1.f;
     }
   };
   auto fetch = [&](int t) {
@@ -209,7 +201,7 @@ __device__ __forceinline__ void score128_body(const ScoreI8Args& a, unsigned cha
     wkg[t & 3] = PROD ? *reinterpret_cast<const float*>(stage + GAM_OFF + lr * 4) : 0.f;
     wnu[t & 3] = *reinterpret_cast<const float*>(stage + NRM_OFF + lr * 4);
   };
-  auto lookups = [&](int t, int s, v4i (&b)[NTA]) {  // B operands of k-step s of tile t
+  auto operands = [&](int t, v4i (&b)[NTA]) {  // B operands of tile t
     int j = 0;
 #pragma unroll
     for (int m = 1; m <= NM; ++m) {
@@ -218,79 +210,74 @@ __device__ __forceinline__ void score128_body(const ScoreI8Args& a, unsigned cha
 #pragma unroll
       for (int pl = 0; pl < BITS; ++pl)
         if (m & (1 << pl)) x ^= wp[t & 3][pl];
-      b[j++] = expand16(x, s);
+      b[j++] = masks(x);
     }
-    if (PROD) b[j] = expand16(wz[t & 3], s);
+    if (PROD) b[j] = masks(wz[t & 3]);
   };
   // all masked sums of the rotated query go to accumulator 0, the sketch's to the last one
   constexpr int NACC = (BITS > 0 ? 1 : 0) + (PROD ? 1 : 0);
-  auto mfmas = [&](int s, const v4i (&b)[NTA], v4i (&c)[NACC]) {
+  auto mfmas = [&](const v4i (&b)[NTA], f32x4 (&c)[NACC]) {
 #pragma unroll
     for (int j = 0; j < NT; ++j) {
       const int to = (PROD && j == NT - 1) ? NACC - 1 : 0;
-      c[to] = __builtin_amdgcn_mfma_i32_16x16x64_i8(A_REGS ? areg[A_REGS ? j : 0][s] : a_read(j, s), b[j], c[to], 0, 0, 0);
+      const v8i bj = __builtin_shufflevector(b[j], b[j], 0, 1, 2, 3, -1, -1, -1, -1);  // fp4: four registers
+      c[to] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(areg[j], bj, c[to], 0, 4, 0, 127, 0, 127);
     }
   };
-  // with few masked sums per tile the operands of the next tile are looked up while this
+  // with few masked sums per tile the operands of the next tile are made while this
   // tile's MFMAs run; with many there are no registers for that
-  constexpr bool PIPE = NTA <= 3;
+  constexpr bool PIPE = NTA <= 5;
   auto run_tiles = [&](auto full_c) {
     constexpr bool FULL = decltype(full_c)::value;
-    v4i bop[PIPE ? 2 : 1][2][NTA];
-    v4i acc[2][NACC];
+    v4i bop[PIPE ? 2 : 1][NTA];
+    f32x4 acc[2][NACC];
     auto finish = [&](int t) {
-      const v4i(&c)[NACC] = acc[t & 1];
+      const f32x4(&c)[NACC] = acc[t & 1];
       float total = BITS > 0 ? fmaf(r_inv, digits_sum(c[0]), base_r) : 0.f;
       if (PROD) total = fmaf(a.kappa * wkg[t & 3], fmaf(zs, digits_sum(c[NACC - 1]), -s_sum), total);
       total *= wnu[t & 3];
+      // (formed here whatever the sink does with it: behind a branch of its own this compiler loses sight of the waits that the
+      // registers of the matrix instructions above need)
+      asm volatile("" : "+v"(total));
       sink(t, total, FULL || wave_key0 + t * 16 + col < a.n);
     };
     // everything needed before tile t's words can be fetched
     auto stage_for = [&](int t) {
       if (t % RT == 0) {
         put_round(t / RT);
+        __builtin_amdgcn_sched_barrier(0);
         if (t / RT + AHEAD < ROUNDS) issue_round(t / RT + AHEAD);
+        __builtin_amdgcn_sched_barrier(0);
       }
     };
     stage_for(0);
     fetch(0);
-    if (PIPE) {
-      lookups(0, 0, bop[0][0]);
-      lookups(0, 1, bop[0][1]);
-    }
+    if (PIPE) operands(0, bop[0]);
     stage_for(1);
     fetch(1);
-    // tiles that have at least one key (uniform over the wavefront)
-    const int live_tiles = FULL ? TILES : (int)((a.n - wave_key0 + 15) >> 4);
+    // (a wavefront with any keys at all works through all of its tiles: branches around them cost more than they
+    // save, and hide from this compiler which waits a matrix instruction's registers need)
 #pragma unroll
     for (int t = 0; t < TILES; ++t) {
-      if (FULL || t < live_tiles) {
-        if (t + 2 < TILES) {
-          stage_for(t + 2);
-          fetch(t + 2);
-        }
-#pragma unroll
-        for (int j = 0; j < NACC; ++j) acc[t & 1][j] = v4i{0, 0, 0, 0};
-        if (PIPE) {
-          if (t + 1 < TILES) {
-            lookups(t + 1, 0, bop[(t + 1) & 1][0]);
-            lookups(t + 1, 1, bop[(t + 1) & 1][1]);
-          }
-          mfmas(0, bop[t & 1][0], acc[t & 1]);
-          mfmas(1, bop[t & 1][1], acc[t & 1]);
-        } else {
-          lookups(t, 0, bop[0][0]);
-          lookups(t, 1, bop[0][1]);
-          mfmas(0, bop[0][0], acc[t & 1]);
-          mfmas(1, bop[0][1], acc[t & 1]);
-        }
+      if (t + 2 < TILES) {
+        stage_for(t + 2);
+        fetch(t + 2);
       }
-      if (t > 0 && (FULL || t - 1 < live_tiles)) finish(t - 1);
+#pragma unroll
+      for (int j = 0; j < NACC; ++j) acc[t & 1][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+      if (PIPE) {
+        if (t + 1 < TILES) operands(t + 1, bop[(t + 1) & 1]);
+        mfmas(bop[t & 1], acc[t & 1]);
+      } else {
+        operands(t, bop[0]);
+        mfmas(bop[0], acc[t & 1]);
+      }
+      if (t > 0) finish(t - 1);
     }
-    if (FULL || TILES - 1 < live_tiles) finish(TILES - 1);
+    finish(TILES - 1);
   };
   if (full) run_tiles(std::true_type{});
-  else run_tiles(std::false_type{});
+  else if (wave_key0 < a.n) run_tiles(std::false_type{});
 }
 
 }  // namespace tq

@@ -16,11 +16,13 @@
 
 namespace tq {
 
-// Slot of coordinate c (d = 128) among the 128 operand bytes of a digit row when the mask bytes are the stored
-// bits left in place: k-step s = bit 2 of c, k-chunk kq = c / 32, dword i = c % 4, byte b = (c / 8) % 4.
-__host__ __device__ constexpr int i8_shifted_slot(int c) {
-  return (((c >> 2) & 1) * 4 + (c >> 5)) * 16 + (c & 3) * 4 + ((c >> 3) & 3);
-}
+// Operands of v_mfma_f32_16x16x128_f8f6f4 for masked sums at d = 128.  The mask side is fp4: of the word of a coordinate group the
+// bits 4 i + {0, 1, 2} stay where they are and read as 0.5, 1 and 2, the bits 4 i + 3 are shifted down three places; dword v of a
+// lane's operand has the bits 4 i + v, i = 0..7 (element 8 v + i).  The query side is fp8: a digit of coordinate c times 2, 1, 1/2 or 2
+// by c % 4, so that every product is the digit itself.  A lane's 32 elements are k = 32 (lane / 16) + 0..31 of an fp4
+// operand, but 16 (lane / 16) + 0..15 and 64 more of an fp8 one (found with one-hot operands): mask_slot is the byte of
+// coordinate c in a digit row whose lanes read 16 bytes at 16 kq and 16 at 64 + 16 kq.
+__host__ __device__ constexpr int mask_slot(int c) { return (c & ~31) + 8 * (c & 3) + ((c >> 2) & 7); }
 
 constexpr int I8_PREP_BYTES = 2 * 2 * 4 * 128 * 4 + 2 * 4 * 4 * 128 + 2 * 4 * 4 * 4;  // partial sums, digits, scalars
 
@@ -85,10 +87,6 @@ struct I8Prep {
     for (int qi = 0; qi < 4; ++qi) part_s[((mat * 2 + kh) * 4 + qi) * 128 + j] = acc[qi];
   }
 
-  // SHIFTED: the digit image for operands whose mask bytes are the stored bits left in place (bit k of a byte
-  // reads as 2^k, as -128 for k = 7): coordinate c is written as Q 2^(7 - c % 8), negated where c % 8 = 7, in
-  // four digits, at slot i8_shifted_slot(c); the masked sum of the products is then 128 times that of Q.
-  template <bool SHIFTED = false>
   __device__ __forceinline__ static void digitise(const ScoreI8Args& a, int q0, int wave, int lane, int d_hi,
                                                   const float* part_s, signed char* dig_s, float* scal_s) {
     const int m = wave >> 2, qi = wave & 3;
@@ -111,20 +109,16 @@ struct I8Prep {
     const int tot_hi = wave_sum((lane < d_hi ? Q[0] : 0) + (lane + 64 < d_hi ? Q[1] : 0));
 #pragma unroll
     for (int u = 0; u < 2; ++u) {
-      // balanced base 128: D0, D1 in [-64, 63], D2 in [-64, 64] (SHIFTED: D2 as D1, |D3| <= 33)
-      const int c = lane + 64 * u, k = c & 7;
-      const int Qs = !SHIFTED ? Q[u] : k == 7 ? -Q[u] : Q[u] << (7 - k);
-      const int d0 = ((Qs + 64) & 127) - 64;
-      const int Q1 = (Qs - d0) >> 7;
+      // balanced base 128: D0, D1 in [-64, 63], D2 in [-64, 64]
+      const int c = lane + 64 * u;
+      const int d0 = ((Q[u] + 64) & 127) - 64;
+      const int Q1 = (Q[u] - d0) >> 7;
       const int d1 = ((Q1 + 64) & 127) - 64;
-      const int Q2 = (Q1 - d1) >> 7;
-      const int d2 = SHIFTED ? ((Q2 + 64) & 127) - 64 : Q2;
-      const int d3 = (Q2 - d2) >> 7;
-      signed char* o = dig_s + (m * 4 + qi) * 4 * 128 + (SHIFTED ? i8_shifted_slot(c) : c);
+      signed char* o = dig_s + (m * 4 + qi) * 4 * 128 + c;
       o[0] = (signed char)d0;
       o[128] = (signed char)d1;
-      o[256] = (signed char)d2;
-      o[384] = (signed char)d3;
+      o[256] = (signed char)((Q1 - d1) >> 7);
+      o[384] = 0;
     }
     if (lane == 0) {
       const float inv = ldexpf(1.f, e - 19);
@@ -136,22 +130,18 @@ struct I8Prep {
   }
 };
 
-// Four balanced base-128 digits of fixed-point value Q of coordinate c, in the shifted form (Q 2^(7 - c % 8), negated
-// where c % 8 = 7) at slot i8_shifted_slot(c) of image `term`, query qi: dig_s[term][qi][digit][slot].
-__device__ __forceinline__ void i8_put_shifted(signed char* dig_s, int term, int qi, int c, int Q) {
-  const int k = c & 7;
-  const int Qs = k == 7 ? -Q : Q << (7 - k);
-  const int d0 = ((Qs + 64) & 127) - 64;
-  const int Q1 = (Qs - d0) >> 7;
-  const int d1 = ((Q1 + 64) & 127) - 64;
-  const int Q2 = (Q1 - d1) >> 7;
-  const int d2 = ((Q2 + 64) & 127) - 64;
-  const int d3 = (Q2 - d2) >> 7;
-  signed char* o = dig_s + (term * 4 + qi) * 4 * 128 + i8_shifted_slot(c);
-  o[0] = (signed char)d0;
-  o[128] = (signed char)d1;
-  o[256] = (signed char)d2;
-  o[384] = (signed char)d3;
+// Four balanced base-32 digits of the integer Q, |Q| <= 2^19, of coordinate c in the form above:
+// dig_s[term][query][digit][slot] (integers up to 16 and their halves and doubles are exact in fp8, all steps here in fp32)
+__device__ __forceinline__ void put_mask_digits(unsigned char* dig_s, int term, int qi, int c, float Q) {
+  const float f = (c & 3) == 1 ? 1.f : (c & 3) == 2 ? 0.5f : 2.f;
+  const float q1 = rintf(Q * 0x1p-5f), q2 = rintf(q1 * 0x1p-5f), q3 = rintf(q2 * 0x1p-5f);
+  int w = __builtin_amdgcn_cvt_pk_fp8_f32(f * fmaf(-32.f, q1, Q), f * fmaf(-32.f, q2, q1), 0, false);
+  w = __builtin_amdgcn_cvt_pk_fp8_f32(f * fmaf(-32.f, q3, q2), f * q3, w, true);
+  unsigned char* o = dig_s + (term * 4 + qi) * 4 * 128 + mask_slot(c);
+  o[0] = (unsigned char)w;
+  o[128] = (unsigned char)(w >> 8);
+  o[256] = (unsigned char)(w >> 16);
+  o[384] = (unsigned char)(w >> 24);
 }
 
 __device__ __forceinline__ float wave_sum_f(float v) {
@@ -165,8 +155,7 @@ __device__ __forceinline__ float wave_sum_f(float v) {
 
 // Digit images for the d = 128 single-kernel path, one per masked sum, so that all the masked sums of the
 // rotated query share ONE accumulator: term t (the t-th plane subset of odd size, factor coef[m]) is the image of
-// Q = round(coef[m] y 2^s), s the power of two with max |coef| max |y| 2^s <= 2^19, in the shifted form of
-// I8Prep::digitise<true>; the sketch term (index 2^(BITS-1)) is that of S q as before.  Wavefront w takes
+// Q = round(coef[m] y 2^s), s the power of two with max |coef| max |y| 2^s <= 2^19; the sketch term (index 2^(BITS-1)) is that of S q as before.  Wavefront w takes
 // (matrix w / 4, query w % 4).
 //   dig_s[term][query][digit][slot]; scal_s[matrix][query][0: 2^-s, 1: matrix 0: coef[0] sum_j y_j, matrix 1:
 //   2^-s sum_j Q_j]
@@ -174,11 +163,12 @@ __host__ __device__ constexpr int i8_terms(int bits, bool prod) { return (bits >
 
 template <int BITS, bool PROD>
 __device__ __forceinline__ void i8_digitise_terms(const ScoreI8Args& a, int q0, int wave, int lane, const float* part_s,
-                                                  signed char* dig_s, float* scal_s) {
+                                                  unsigned char* dig_s, float* scal_s) {
   constexpr int NM = (1 << BITS) - 1;
   constexpr int NTM = BITS > 0 ? 1 << (BITS - 1) : 0;
-  const int m = wave >> 2, qi = wave & 3;
-  if (!(m == 0 ? BITS > 0 : PROD)) return;
+  // without a sketch both halves of the workgroup write images of the rotated query, every other one
+  const int m = PROD ? wave >> 2 : 0, qi = wave & 3, part = PROD ? 0 : wave >> 2;
+  if (!(m == 0 ? BITS > 0 : PROD) || (NTM == 1 && part != 0)) return;
   const bool live = q0 + qi < a.q_per_group;
   float y[2];
 #pragma unroll
@@ -186,7 +176,7 @@ __device__ __forceinline__ void i8_digitise_terms(const ScoreI8Args& a, int q0, 
     const int c = lane + 64 * u;
     y[u] = live ? part_s[((m * 2 + 0) * 4 + qi) * 128 + c] + part_s[((m * 2 + 1) * 4 + qi) * 128 + c] : 0.f;
   }
-  auto put = [&](int term, int u, int Q) { i8_put_shifted(dig_s, term, qi, lane + 64 * u, Q); };
+  auto put = [&](int term, int u, float Q) { put_mask_digits(dig_s, term, qi, lane + 64 * u, Q); };
   float cmax = 1.f;
   if (m == 0) {
     cmax = 0.f;
@@ -199,8 +189,8 @@ __device__ __forceinline__ void i8_digitise_terms(const ScoreI8Args& a, int q0, 
   if (mx > 0.f) (void)frexpf(mx, &e);  // mx = f * 2^e, f in [0.5, 1): |Q| <= 2^19
   const float sc = ldexpf(1.f, 19 - e), inv = ldexpf(1.f, e - 19);
   if (m == 1) {
-    const int Q0 = __float2int_rn(y[0] * sc), Q1 = __float2int_rn(y[1] * sc);
-    const int tot = wave_sum(Q0 + Q1);
+    const float Q0 = rintf(y[0] * sc), Q1 = rintf(y[1] * sc);
+    const int tot = wave_sum((int)Q0 + (int)Q1);
     put(NTM, 0, Q0);
     put(NTM, 1, Q1);
     if (lane == 0) {
@@ -212,12 +202,14 @@ __device__ __forceinline__ void i8_digitise_terms(const ScoreI8Args& a, int q0, 
 #pragma unroll
     for (int v = 1; v <= NM; ++v) {
       if (!i8_term(v)) continue;
-      put(term, 0, __float2int_rn(a.coef[v] * y[0] * sc));
-      put(term, 1, __float2int_rn(a.coef[v] * y[1] * sc));
+      if (PROD || NTM == 1 || (term & 1) == part) {  // uniform
+        put(term, 0, rintf(a.coef[v] * y[0] * sc));
+        put(term, 1, rintf(a.coef[v] * y[1] * sc));
+      }
       ++term;
     }
     const float ysum = wave_sum_f(y[0] + y[1]);
-    if (lane == 0) {
+    if (lane == 0 && part == 0) {
       scal_s[qi * 4 + 0] = inv;
       scal_s[qi * 4 + 1] = a.coef[0] * ysum;
     }

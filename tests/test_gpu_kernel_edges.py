@@ -137,3 +137,29 @@ def test_search_by_candidates_with_too_many_of_them(d, bits, prod):
 def test_attend_joins_of_chunks(vprod, groups, qpg, npg):
     """One chunk, more than sixteen, the 64 that a wavefront's lanes hold, and one more."""
     A.run_attend(128, 2, True, 2, vprod, groups, qpg, npg, True)
+
+
+@pytest.mark.parametrize("bits,prod,npg", [(0, True, 65), (1, False, 1), (2, True, 2049), (3, True, 511), (4, False, 20500), (4, True, 130)])
+def test_masked_sums_at_their_largest(bits, prod, npg):
+    """Queries whose rotated coordinates are one large value among zeros, all equal, and of every sign pattern mod 4 (the digit
+    scales go by coordinate mod 4); codes without norms."""
+    p, Pi, S, c32, _ = T.setup(128, bits, prod)
+    rng = np.random.default_rng(npg)
+    y = np.zeros((7, 128))
+    for k in range(4):
+        y[k, 5 + 31 * k] = (-1.0) ** k * 3.0
+    y[4] = 1.0
+    y[5] = np.where(np.arange(128) % 4 < 2, 1.0, -1.0)
+    y[6] = rng.standard_normal(128) * 10.0 ** rng.integers(-6, 7, 128)
+    q = (y @ Pi).astype(np.float32)  # Pi q = y
+    idx = rng.integers(0, 1 << bits, size=(npg, 128)).astype(np.int32)
+    z = rng.integers(0, 2, size=(npg, 128)).astype(bool)
+    gamma = rng.uniform(0.05, 0.6, size=npg).astype(np.float32)
+    ones = np.ones(npg, dtype=np.float32)
+    xt = T.o.dequant_prod(idx, z, gamma, Pi, S, c32, ones) if prod else T.o.dequant_mse(idx, Pi, c32, ones)
+    idx_w = T.dev(T.o.pack_planes(idx, bits).view(np.int32)) if bits else None
+    qjl_w = T.dev(T.o.pack_signs(z).view(np.int32)) if prod else None
+    scores = torch.zeros((7, npg), device=T.DEV)
+    p.reserve(npg, 7)
+    tq.tq_score(p, T.dev(q), 1, 7, idx_w, qjl_w, T.dev(gamma) if prod else None, None, npg, scores)
+    T.P.check_close(scores.cpu().numpy(), T.o.score(q, xt), np.linalg.norm(q.astype(np.float64), axis=1)[:, None] * ones[None, :], "score")
