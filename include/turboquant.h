@@ -86,6 +86,10 @@
  *   dequantise, more than 8192 vectors at d = 128 and every other d: two pieces of
  *     a centroid and of an entry of Pi^T or S^T, a sign as one exact piece (error
  *     below 4e-5 of a coordinate's typical size);
+ *   dequantise, d = 128, a table of up to two bits that is symmetric about zero, with the
+ *     images of tq_build_dequant_images or up to 24576 vectors: sums of signs times the 20 leading bits of an
+ *     entry (of its column's largest) above 8192 vectors, 25 bits up to them, where
+ *     the result is closer than that of the fp32 instructions;
  *   scoring, Pi q and S q: plain fp32 for up to 64 queries in all; more of them at d
  *     other than 128 from two fp16 pieces of the query and of Pi and S each, where the
  *     workspace has the room that tq_score_workspace_bytes counts (0.62 of the
@@ -275,11 +279,12 @@ tq_status tq_derive_params(int32_t d, const float* Pi, const float* S, float* Pi
 size_t tq_images_bytes(int32_t d);
 tq_status tq_build_images(const tq_params* p, void* images, void* stream);
 
-/* The same for tq_dequantize at d other than 128 (0 bytes, nothing done, at d = 128): Pi^T and S^T as the tiles its
- * workgroups stage, and S for the sketch of many queries in tq_score, read from p->Pi and p->S.  They lie behind the
+/* The same for tq_dequantize: Pi^T and S^T as the tiles its workgroups stage, and S for the sketch of many queries in
+ * tq_score; at d = 128 Pi^T and S^T as digits for tables that are sums of signs (up to two bits, symmetric about zero).
+ * Read from p->Pi and p->S.  They lie behind the
  * images above: `images` is a buffer of tq_images_bytes(d) + tq_dequant_images_bytes(d) bytes, and
  * TQ_FLAG_DEQUANT_IMAGES in params.flags says that params.images is such a buffer with both parts filled.  Without the flag tq_dequantize makes these tiles in the
- * workspace in every call, where it has room (8 d^2 + 256 bytes), or takes kernels that do without, the same up to
+ * workspace in every call, where it has room (8 d^2 + 256 bytes, less at d = 128), or takes kernels that do without (at d = 128 above 24576 vectors), the same up to
  * rounding; tq_score likewise for more than 64 queries (tq_score_workspace_bytes counts the room). */
 size_t tq_dequant_images_bytes(int32_t d);
 tq_status tq_build_dequant_images(const tq_params* p, void* images, void* stream);

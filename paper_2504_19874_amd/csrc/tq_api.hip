@@ -10,6 +10,7 @@
 #include "tq_h2.h"
 #include "tq_score_i8.h"
 #include "tq_search.h"
+#include "tq_sign.h"
 
 using namespace tq;
 
@@ -437,7 +438,8 @@ tq_status tq_build_images(const tq_params* p, void* images, void* stream) {
 }
 
 size_t tq_dequant_images_bytes(int32_t d) {
-  if (d == 128 || d <= 0 || d % 32 != 0 || d > 16384) return 0;
+  if (d <= 0 || d % 32 != 0 || d > 16384) return 0;
+  if (d == 128) return 2 * SIGN128_BYTES;
   return 3 * h2_image_bytes(d, d) + 256;
 }
 
@@ -448,6 +450,9 @@ tq_status tq_build_dequant_images(const tq_params* p, void* images, void* stream
   if (!aligned16(images)) return TQ_ERR_UNSUPPORTED;
   const hipStream_t s = static_cast<hipStream_t>(stream);
   const int d = p->d;
+  if (d == 128) {
+    return from_hip(launch_sign128_images(p->Pi, p->S, static_cast<char*>(images) + tq_images_bytes(d), s));
+  }
   auto image = [&](int which) { return const_cast<char*>(h2_image(images, d, which)); };
   if (launch_code_image(p->Pi, d, image(IMG_CODE_PI), h2_image_scale(images, d, IMG_CODE_PI), s) != hipSuccess ||
       (p->S != nullptr && launch_code_image(p->S, d, image(IMG_CODE_S), h2_image_scale(images, d, IMG_CODE_S), s) != hipSuccess))
@@ -552,6 +557,24 @@ tq_status tq_dequantize(const tq_params* p, const uint32_t* idx, const uint32_t*
     return from_hip(launch_dequant128(p->bits_mse, prod, idx, qjl, gamma, norm, p->Pi, p->S, x_out, ldo, n,
                                       kappa_of(p->d - p->d_hi), make_codebook(p), p->d_hi / 32,
                                       kappa_of(p->d_hi), make_codebook_hi(p), static_cast<hipStream_t>(stream)));
+  }
+  // d = 128, a table that is a sum of signs: digits of Pi^T and S^T from the images, or, for few codes, made here in the
+  // workspace.  That takes 3 us, more where they evict the matrices (us, 3 bits in all / 2 without a sketch, kernels below -> made here -> from
+  // images: 512 codes 9.2 / 6.8 -> 7.0 / 6.4 -> 3.3 / 3.3, 16384 11.1 / 7.7 -> 9.9 / 7.9 -> 5.9 / 4.1, 65536 14.1 / 11.1 -> 15.2 / 13.9 -> 11.3 / 9.0)
+  SignCoefs sc;
+  if (p->d == 128 && !fp32_mfma_only(p) && (p->bits_mse > 0 || prod) && sign_table(p->bits_mse, make_codebook(p), &sc)) {
+    const hipStream_t s = static_cast<hipStream_t>(stream);
+    const char* digits = p->images != nullptr && (p->flags & TQ_FLAG_DEQUANT_IMAGES) != 0
+                             ? static_cast<const char*>(p->images) + tq_images_bytes(128) : nullptr;
+    if (p->images == nullptr && n <= kSignOwnDigitRows && p->Pi != nullptr && (!prod || p->S != nullptr)) {
+      Workspace ws{static_cast<char*>(p->workspace), p->workspace_bytes, 0};
+      if (char* const own = static_cast<char*>(ws.take((prod ? 2 : 1) * SIGN128_BYTES)); own != nullptr) {
+        if (launch_sign128_images(p->Pi, prod ? p->S : nullptr, own, s) != hipSuccess) return TQ_ERR_HIP;
+        digits = own;
+      }
+    }
+    if (digits != nullptr)
+      return from_hip(launch_sign128_dequant(p->bits_mse, prod, idx, qjl, gamma, norm, digits, x_out, ldo, n, kappa_of(128), sc, s));
   }
   // large batches at d = 128: decoded codes straight into bf16 MFMA operands, pieces of Pi^T / S^T in LDS
   if (p->d == 128 && n > kBf3DequantRows && !fp32_mfma_only(p) && dequant128_bf3_applicable(p->bits_mse, prod, make_codebook(p), x_out, ldo))

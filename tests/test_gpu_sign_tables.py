@@ -1,0 +1,71 @@
+"""Dequantisation at d = 128 where the centroid table is a sum of signs (none, one bit, two symmetric bits): blocks of 32 codes, four or
+five digits of an entry, from the images or made in the workspace, and the tables that have to go elsewhere."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import turboquant_oracle as o
+from tests import test_gpu_parity as T
+
+pytestmark = pytest.mark.gpu
+
+tq = pytest.importorskip("paper_2504_19874_amd")
+
+D = 128
+
+
+def make(bits, prod, n):
+    p, Pi, S, c32, _ = T.setup(D, bits, prod)
+    rng = np.random.default_rng(100 * n + bits)
+    idx = rng.integers(0, 1 << bits, size=(n, D)).astype(np.int32)
+    z = rng.integers(0, 2, size=(n, D)).astype(bool)
+    gamma = rng.uniform(0.05, 0.6, size=n).astype(np.float32)
+    norm = np.exp(rng.normal(0, 1, size=n)).astype(np.float32)
+    codes = [T.dev(o.pack_planes(idx, bits).view(np.int32)) if bits else None, T.dev(o.pack_signs(z).view(np.int32)) if prod else None,
+             T.dev(gamma) if prod else None]
+    return p, codes, (idx, z, gamma, Pi, S, c32), norm
+
+
+def reference(parts, prod, norm):
+    idx, z, gamma, Pi, S, c = parts
+    return o.dequant_prod(idx, z, gamma, Pi, S, c, norm) if prod else o.dequant_mse(idx, Pi, c, norm)
+
+
+def close(got, want, norm, n):
+    # Five digits of an entry: the rounding of fp32 sums of 128 terms, below 128 2^-24 of a coordinate's typical size.  Four, above
+    # 8192 codes: an entry is off by at most half of its column's largest (0.4 here) / 17301504 * 32, uniformly: of 128 terms of
+    # typical size 1 / sqrt(128), 2.5e-6, and no more than 7 times that in a few million coordinates.  Two kinds of sign add.
+    scale = (np.ones(n) if norm is None else norm.astype(np.float64))[:, None] / np.sqrt(D)
+    assert np.abs((got.astype(np.float64) - want) / scale).max() < (8e-6 if n <= 8192 else 3.5e-5)
+
+
+@pytest.mark.parametrize("bits,prod,n", [(0, True, 1), (1, False, 31), (1, True, 33), (2, False, 64), (2, True, 511), (2, True, 2049),
+                                         (2, True, 8192), (1, True, 8193), (2, False, 16421), (0, True, 16385)])
+def test_blocks_and_images(bits, prod, n):
+    p, codes, parts, norm = make(bits, prod, n)
+    wide = torch.full((n + 1, 132), 7.0, device=T.DEV)  # rows of a larger matrix: what lies around them stays
+    tq.tq_dequantize(p, *codes, T.dev(norm), wide[:n, :D])
+    got = wide[:n, :D].clone()
+    assert bool((wide[:n, D:] == 7).all()) and bool((wide[n] == 7).all())
+    close(got.cpu().numpy(), reference(parts, prod, norm), norm, n)
+    out = torch.empty((n, D), device=T.DEV)
+    tq.tq_dequantize(p, *codes, None, out)
+    close(out.cpu().numpy(), reference(parts, prod, None), None, n)
+    try:
+        p.drop_images().reserve(n)  # the digits made in the call: the same bits
+        tq.tq_dequantize(p, *codes, T.dev(norm), out)
+        assert torch.equal(out, got)
+    finally:
+        p.build_images()
+
+
+@pytest.mark.parametrize("table", [(-0.09, -0.03, 0.04, 0.09), (-0.08, -0.08, 0.08, 0.08), (-0.1, 0.0, 0.0, 0.1), (0.0, 0.0, 0.0, 0.0)])
+@pytest.mark.parametrize("n", [100, 8200])
+def test_other_tables(table, n):
+    """Two bits that are not symmetric, or of one magnitude, or with zeros: whatever kernel takes them."""
+    p0, codes, parts, norm = make(2, False, n)
+    c = np.array(table, dtype=np.float32)
+    p = tq.Params(D, 2, p0.Pi, p0.S, c, (c[1:] + c[:-1]) / 2)
+    out = torch.empty((n, D), device=T.DEV)
+    tq.tq_dequantize(p, *codes, T.dev(norm), out)
+    T.P.check_close(out.cpu().numpy(), reference(parts[:5] + (c,), False, norm), norm.astype(np.float64)[:, None] / np.sqrt(D), "coordinate")
