@@ -98,7 +98,7 @@
  *     3e-6 |q| norm of the exact ones); with top-k alone one fp16 piece finds
  *     what can be among the k best within a derived bound, and these are scored
  *     the same way, to the same bits;
- *   scoring, few queries: int8 digits (up to 32 per group at d <= 1024, up to 16
+ *   scoring, few queries: fixed-point digits (up to 32 per group at d <= 1024, up to 16
  *     per group at d <= 4096 (64 in all beyond d = 512), d a multiple of 128,
  *     codebook symmetric about zero).
  * Smaller batches of fp32 vectors, and of codes, at d = 128 run on the fp32 matrix

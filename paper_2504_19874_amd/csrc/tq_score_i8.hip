@@ -1,9 +1,9 @@
-// Query preparation for the few-query scoring kernels on the integer matrix cores (tq_score_stream.hip and
+// Query preparation for the few-query scoring kernels on fixed-point digits (tq_score_stream.hip and, on the integer matrix cores,
 // tq_score_i8_split.hip: what they compute is told there): rotate / sketch a query, choose its fixed-point scale, write the
 // digit operands; and the Walsh coefficients of a centroid table.
 //
-// Fixed point: per query, Q_j = round(q_j * 2^e) with |Q_j| <= 2^20 (2^19 for split codes) in balanced base 128, digits in
-// [-64, 64] (valid signed bytes).  Integer arithmetic is exact; the only rounding is that of q, 2^-20 of the query's
+// Fixed point: per query, Q_j = round(q_j * 2^e) with |Q_j| <= 2^20 in base 49 (tq_score_digits.h), 2^19 for split codes in balanced
+// base 128, digits in [-64, 64] (valid signed bytes).  Integer arithmetic is exact; the only rounding is that of q, 2^-20 of the query's
 // largest coordinate, far inside 1e-4.
 #include <cstring>
 
@@ -15,22 +15,45 @@ namespace tq {
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 
-// The operand bytes of one rotated query ys [d] (LDS) for tq_score_stream.hip: per word group g and digit dg two 16-byte
-// operands, s = 0, 1, whose dword i holds the digits of coordinates 32 g + k + {0, 8, 16, 24}, k = 4 s + i, taken from
-// Q 2^(7 - k) (negated for k = 7).  img: [d / 32][digit][2] of this query and matrix.
-__device__ __forceinline__ void stream_digits(const float* ys, int d, float sc, uint32_t* img, int tid, int threads) {
-  for (int u = tid; u < d / 4; u += threads) {
-    const int g = u >> 3, k = u & 7;
+// The operand of one rotated query ys [d] (LDS) for tq_score_stream.hip: 32 words per word group g, digit dg of its coordinates as 32 values
+// of 6 bits, the first four words at 4 dg, the other two at 16 + 2 dg.  Value 8 v + i is coordinate 32 g + 4 i + v, negated for v = 3.  A mask
+// of bit b is 4 + 2 b, 2 + 2 b, 2 b or 1 - 2 b there (v = 0 .. 3); off_s[dg], zero before: what the parts without b come to.  A thread
+// for four coordinates, d / 4 <= blockDim.x.
+__device__ __forceinline__ void stream_digits(const float* ys, int d, float sc, uint32_t* img, int* off_s, int tid) {
+  int off[4] = {0, 0, 0, 0};
+  if (tid < d / 4) {  // eight threads of a group: four values = 24 bits of the 192 each
+    const int g = tid >> 3, v = (tid >> 1) & 3, half = tid & 1;
+    const int part = v == 0 ? 4 : v == 1 ? 2 : v == 2 ? 0 : 1;
     uint32_t w[4] = {0u, 0u, 0u, 0u};
 #pragma unroll
-    for (int b = 0; b < 4; ++b) {
+    for (int i = 0; i < 4; ++i) {
+      const int Q = __float2int_rn(ys[32 * g + 16 * half + 4 * i + v] * sc);
       int dig[4];
-      stream_digits_of(__float2int_rn(ys[32 * g + k + 8 * b] * sc), k, dig);
+      mask_digits_of(v == 3 ? -Q : Q, dig);
 #pragma unroll
-      for (int dg = 0; dg < 4; ++dg) w[dg] |= ((uint32_t)dig[dg] & 0xFFu) << (8 * b);
+      for (int dg = 0; dg < 4; ++dg) {
+        w[dg] |= mask_digit_code(dig[dg]) << (6 * i);
+        off[dg] += part * dig[dg];
+      }
     }
 #pragma unroll
-    for (int dg = 0; dg < 4; ++dg) img[((g * 4 + dg) * 2 + (k >> 2)) * 4 + (k & 3)] = w[dg];
+    for (int dg = 0; dg < 4; ++dg)
+#pragma unroll
+      for (int k = 0; k < 3; ++k) {
+        const int at = 6 * v + 3 * half + k;  // of the lane's 24 bytes
+        reinterpret_cast<uint8_t*>(img + g * 32 + (at < 16 ? dg * 4 : 16 + dg * 2 - 4))[at] = (uint8_t)(w[dg] >> (8 * k));
+      }
+  }
+  // two sums to a word: a wavefront's are at most 64 x 4 x 56 each
+  int o01 = off[0] + off[1] * 65536, o23 = off[2] + off[3] * 65536;
+#pragma unroll
+  for (int o = 32; o >= 1; o >>= 1) {
+    o01 += __shfl_xor(o01, o);
+    o23 += __shfl_xor(o23, o);
+  }
+  if ((tid & 63) < 4) {
+    const int both = (tid & 2) != 0 ? o23 : o01, low = (int)(int16_t)both;
+    atomicAdd(off_s + (tid & 3), (tid & 1) != 0 ? (both - low) >> 16 : low);
   }
 }
 
@@ -140,12 +163,14 @@ __global__ __launch_bounds__(512) void prep_i8_kernel(const int d_hi, const floa
 }
 
 // Digits for tq_score_stream.hip, in place: the d floats of rotated query q, matrix mat (written by a matrix-vector kernel)
-// become its d digit words.  grid (nq, matrices), 1024 threads: d <= 4096 values, four per thread.
+// become its digit words.  grid (nq, matrices), a thread for four of the d <= 4096 values.
 __global__ __launch_bounds__(1024) void digitise_i8_kernel(const int d, const int mat0, uint32_t* img, float* __restrict__ scal) {
   __shared__ float ys[4096];
   __shared__ float red_mx[16];
   __shared__ long long red_tot[16];
+  __shared__ int off_s[4];
   const int tid = threadIdx.x;
+  if (tid < 4) off_s[tid] = 0;
   const int64_t q = blockIdx.x;
   const int mat = mat0 + blockIdx.y;
   uint32_t* const own = img + (q * 2 + mat) * d;
@@ -160,23 +185,22 @@ __global__ __launch_bounds__(1024) void digitise_i8_kernel(const int d, const in
   if ((tid & 63) == 0) red_mx[tid >> 6] = mx;
   __syncthreads();
   mx = red_mx[0];
-#pragma unroll
-  for (int w = 1; w < 16; ++w) mx = fmaxf(mx, red_mx[w]);
+  for (int w = 1; w < (int)(blockDim.x >> 6); ++w) mx = fmaxf(mx, red_mx[w]);
   int e = 0;
   if (mx > 0.f) (void)frexpf(mx, &e);  // mx = f * 2^e, f in [0.5, 1)
   const float sc = ldexpf(1.f, 20 - e);
-  stream_digits(ys, d, sc, own, tid, 1024);  // everyone has read its floats
-  long long tot = 0;  // up to 4096 values of up to 2^20
+  stream_digits(ys, d, sc, own, off_s, tid);  // everyone has read its floats
+  int tot = 0;  // of a wavefront: 256 values of up to 2^20
 #pragma unroll
   for (int k = 0; k < 4; ++k) tot += __float2int_rn(v[k] * sc);
 #pragma unroll
   for (int off = 32; off >= 1; off >>= 1) tot += __shfl_xor(tot, off);
   if ((tid & 63) == 0) red_tot[tid >> 6] = tot;
   __syncthreads();
+  if (tid < 4) reinterpret_cast<float*>(own)[24 + tid] = (float)-off_s[tid];  // behind the first group's digits: where the sums start
   if (tid == 0) {
     long long t = 0;
-#pragma unroll
-    for (int w = 0; w < 16; ++w) t += red_tot[w];
+    for (int w = 0; w < (int)(blockDim.x >> 6); ++w) t += red_tot[w];
     const float inv = ldexpf(1.f, e - 20);
     scal[(q * 2 + mat) * 4 + 0] = inv;
     scal[(q * 2 + mat) * 4 + 1] = (float)t * inv;
@@ -287,7 +311,7 @@ hipError_t launch_score_i8(int bits, bool prod, const float* Pi, const float* S,
                              : launch_matvec_rows(d, nq, S, nullptr, q, ldq, y + d, nullptr, 2 * d, false, stream);
       e != hipSuccess)
     return e;
-  hipLaunchKernelGGL(digitise_i8_kernel, dim3((unsigned)nq, r && prod ? 2 : 1), dim3(1024), 0, stream, d, r ? 0 : 1, static_cast<uint32_t*>(workspace), scal);
+  hipLaunchKernelGGL(digitise_i8_kernel, dim3((unsigned)nq, r && prod ? 2 : 1), dim3((d / 4 + 63) / 64 * 64), 0, stream, d, r ? 0 : 1, static_cast<uint32_t*>(workspace), scal);
   if (const hipError_t e = hipGetLastError(); e != hipSuccess) return e;
   return launch_score_stream(bits, prod, img, scal, idx, qjl, gamma, norm, scores, lds, n, d, n_groups, q_per_group, kappa, a.coef, stream);
 }

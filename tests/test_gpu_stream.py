@@ -1,0 +1,48 @@
+"""Few queries against many long codes: steps of every width (whole lines, whole rows, what is left), wavefronts that gather the scores of
+several blocks, ragged ends, rows of scores that are not aligned.  The sums are exact, so a list gives the same bits in one call and in pieces;
+the pieces' kernel is checked against the oracle elsewhere and here on the first codes."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import turboquant_oracle as o
+from tests import test_gpu_parity as T
+
+pytestmark = pytest.mark.gpu
+
+tq = pytest.importorskip("paper_2504_19874_amd")
+
+
+@pytest.mark.parametrize("d,bits,prod,n,nq", [(2048, 0, True, 100037, 3), (1536, 1, True, 60037, 4), (1024, 1, True, 100037, 7), (768, 2, True, 60001, 4),
+                                              (1536, 1, False, 100001, 1), (3072, 1, True, 50003, 6), (256, 4, True, 300007, 8), (640, 3, False, 100037, 5)])
+def test_one_call_and_pieces(d, bits, prod, n, nq):
+    p, Pi, S, c32, _ = T.setup(d, bits, prod)
+    g = torch.Generator(device=T.DEV).manual_seed(d + n)
+
+    def words(k):
+        return torch.randint(-2**31, 2**31 - 1, (n, k), dtype=torch.int32, device=T.DEV, generator=g)
+
+    idx, qjl = words(p.idx_words) if bits else None, words(p.qjl_words) if prod else None
+    gamma = torch.rand(n, device=T.DEV, generator=g) if prod else None
+    norm = torch.rand(n, device=T.DEV, generator=g) + 0.5
+    q = torch.randn(nq, d, device=T.DEV, generator=g)
+    p.reserve(1, nq, 0)
+    wide = torch.full((nq, n + 5), 7.0, device=T.DEV)
+    tq.tq_score(p, q, 1, nq, idx, qjl, gamma, norm, n, wide[:, :n])
+    assert bool((wide[:, n:] == 7).all())
+    step = 20000
+    part = torch.empty((nq, step), device=T.DEV)
+    for a in range(0, n, step):
+        b = min(n, a + step)
+        cut = [None if t is None else t[a:b] for t in (idx, qjl, gamma, norm)]
+        tq.tq_score(p, q, 1, nq, *cut, b - a, part[:, :b - a])
+        assert torch.equal(part[:, :b - a], wide[:, a:b])
+    k = 64
+    planes = o.unpack_planes(idx[:k].cpu().numpy().view(np.uint32), bits, d) if bits else np.zeros((k, d), dtype=np.int32)
+    nrm = norm[:k].cpu().numpy()
+    if prod:
+        xt = o.dequant_prod(planes, o.unpack_signs(qjl[:k].cpu().numpy().view(np.uint32), d), gamma[:k].cpu().numpy(), Pi, S, c32, nrm)
+    else:
+        xt = o.dequant_mse(planes, Pi, c32, nrm)
+    qh = q.cpu().numpy()
+    T.P.check_close(wide[:, :k].cpu().numpy(), o.score(qh, xt), np.linalg.norm(qh.astype(np.float64), axis=1)[:, None] * nrm[None], "score")
