@@ -86,10 +86,11 @@
  *   dequantise, more than 8192 vectors at d = 128 and every other d: two pieces of
  *     a centroid and of an entry of Pi^T or S^T, a sign as one exact piece (error
  *     below 4e-5 of a coordinate's typical size);
- *   dequantise, d = 128, a table of up to two bits that is symmetric about zero, with the
- *     images of tq_build_dequant_images or up to 24576 vectors: sums of signs times the 20 leading bits of an
- *     entry (of its column's largest) above 8192 vectors, 25 bits up to them, where
- *     the result is closer than that of the fp32 instructions;
+ *   dequantise, a table of up to two bits that is symmetric about zero: sums of signs
+ *     times the 25 leading bits of an entry (of its column's largest), where the result is
+ *     closer than that of the fp32 instructions; at d = 128 (with the images of
+ *     tq_build_dequant_images or up to 24576 vectors) 20 bits above 8192 vectors; at d = 256,
+ *     384, 512, ... from 2^20 coordinates on for two bits without a sketch, always for the rest;
  *   scoring, Pi q and S q: plain fp32 for up to 64 queries in all; more of them at d
  *     other than 128 from two fp16 pieces of the query and of Pi and S each, where the
  *     workspace has the room that tq_score_workspace_bytes counts (0.62 of the
@@ -280,7 +281,8 @@ size_t tq_images_bytes(int32_t d);
 tq_status tq_build_images(const tq_params* p, void* images, void* stream);
 
 /* The same for tq_dequantize: Pi^T and S^T as the tiles its workgroups stage, and S for the sketch of many queries in
- * tq_score; at d = 128 Pi^T and S^T as digits for tables that are sums of signs (up to two bits, symmetric about zero).
+ * tq_score; at every d that is a multiple of 128 Pi^T and S^T as digits, too, for tables that are sums of signs (up to two
+ * bits, symmetric about zero).
  * Read from p->Pi and p->S.  They lie behind the
  * images above: `images` is a buffer of tq_images_bytes(d) + tq_dequant_images_bytes(d) bytes, and
  * TQ_FLAG_DEQUANT_IMAGES in params.flags says that params.images is such a buffer with both parts filled.  Without the flag tq_dequantize makes these tiles in the

@@ -140,6 +140,10 @@ float* h2_image_scale(const void* images, int d, int which) {
   const char* const at = which >= 2 ? h2_image(images, d, 5) + 8 * (which - 2) : h2_image(images, d, 0) + 2 * h2_image_bytes(d, d) + 8 * which;
   return reinterpret_cast<float*>(const_cast<char*>(at));
 }
+// behind those, where codes are decoded as signs (tq_sign_gemm.hip): the digits of Pi^T and of S^T
+char* sign_gemm_image(const void* images, int d, int which) {
+  return const_cast<char*>(h2_image(images, d, 5)) + 256 + which * sign_gemm_image_bytes(d);
+}
 // without them: the images a call makes for itself in the workspace
 size_t h2_own_images_bytes(int d, bool prod) { return kH2ImageHeader + (prod ? 2 : 1) * h2_image_bytes(d, d); }
 
@@ -440,7 +444,7 @@ tq_status tq_build_images(const tq_params* p, void* images, void* stream) {
 size_t tq_dequant_images_bytes(int32_t d) {
   if (d <= 0 || d % 32 != 0 || d > 16384) return 0;
   if (d == 128) return 2 * SIGN128_BYTES;
-  return 3 * h2_image_bytes(d, d) + 256;
+  return 3 * h2_image_bytes(d, d) + 256 + (sign_gemm_images(d) ? 2 * sign_gemm_image_bytes(d) : 0);
 }
 
 tq_status tq_build_dequant_images(const tq_params* p, void* images, void* stream) {
@@ -456,6 +460,9 @@ tq_status tq_build_dequant_images(const tq_params* p, void* images, void* stream
   auto image = [&](int which) { return const_cast<char*>(h2_image(images, d, which)); };
   if (launch_code_image(p->Pi, d, image(IMG_CODE_PI), h2_image_scale(images, d, IMG_CODE_PI), s) != hipSuccess ||
       (p->S != nullptr && launch_code_image(p->S, d, image(IMG_CODE_S), h2_image_scale(images, d, IMG_CODE_S), s) != hipSuccess))
+    return TQ_ERR_HIP;
+  if (sign_gemm_images(d) && (launch_sign_gemm_image(p->Pi, d, sign_gemm_image(images, d, 0), s) != hipSuccess ||
+                              (p->S != nullptr && launch_sign_gemm_image(p->S, d, sign_gemm_image(images, d, 1), s) != hipSuccess)))
     return TQ_ERR_HIP;
   // (an S that is not 16-byte aligned is refused wherever the last one is used)
   if (p->S != nullptr && aligned16(p->S) && launch_h2_image(p->S, d, d, d, image(IMG_S), h2_image_scale(images, d, IMG_S), s) != hipSuccess)
@@ -592,6 +599,26 @@ tq_status tq_dequantize(const tq_params* p, const uint32_t* idx, const uint32_t*
   if (p->d < 4096 && !fp32_mfma_only(p) && rows_route_serves(prod ? 2 * n : n, p->d, prod ? 2 : 1, 300))
     return from_hip(launch_dequant_rows(p->bits_mse, prod, p->d, n, idx, qjl, gamma, norm, p->PiT, p->ST, make_codebook(p),
                                         kappa_of(p->d), x_out, ldo, static_cast<hipStream_t>(stream)));
+  // many codes of a table that is a sum of signs: digits of Pi^T and S^T, from the images or made here where the workspace holds them
+  if (!fp32_mfma_only(p) && sign_gemm_serves(p->bits_mse, prod, p->d, n) && (p->bits_mse > 0 || prod) && p->Pi != nullptr &&
+      (!prod || p->S != nullptr) && sign_table(p->bits_mse, make_codebook(p), &sc)) {
+    const hipStream_t s = static_cast<hipStream_t>(stream);
+    const int d = p->d;
+    const char *pi = nullptr, *si = nullptr;
+    if (const char* const img = h2_dequant_images(p); img != nullptr) {
+      pi = sign_gemm_image(img, d, 0), si = sign_gemm_image(img, d, 1);
+    } else {
+      Workspace ws{static_cast<char*>(p->workspace), p->workspace_bytes, 0};
+      if (char* const own = static_cast<char*>(ws.take((prod ? 2 : 1) * sign_gemm_image_bytes(d))); own != nullptr) {
+        pi = own, si = own + sign_gemm_image_bytes(d);
+        if (launch_sign_gemm_image(p->Pi, d, own, s) != hipSuccess ||
+            (prod && launch_sign_gemm_image(p->S, d, own + sign_gemm_image_bytes(d), s) != hipSuccess))
+          return TQ_ERR_HIP;
+      }
+    }
+    if (pi != nullptr)
+      return from_hip(launch_sign_gemm(p->bits_mse, prod, pi, si, d, idx, qjl, gamma, norm, n, x_out, ldo, kappa_of(d), sc, s));
+  }
   // many codes: fp16 pieces of Pi^T and S^T, from the images or made here where the workspace holds them
   if (!fp32_mfma_only(p) && code_gemm_serves(p->bits_mse, make_codebook(p)) && (p->bits_mse > 0 || prod) && p->Pi != nullptr && (!prod || p->S != nullptr)) {
     const hipStream_t s = static_cast<hipStream_t>(stream);

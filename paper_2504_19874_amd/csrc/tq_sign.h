@@ -79,6 +79,15 @@ __device__ __forceinline__ floatx16 sign_mfma(const v8i_t& signs, const v8i_t& d
   else return __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(signs, digit, acc, 4, 2, 0, 127, 0, 150);
 }
 
+// d a multiple of 128 from 256 on: a tile's digits of one step in 8 KB, the units (powers of two here) behind those of step 0
+constexpr int SIGN_STEP_BYTES = 8192;
+__host__ __device__ constexpr size_t sign_gemm_image_bytes(int d) { return (size_t)(d / 64) * (d / 32) * SIGN_STEP_BYTES; }
+bool sign_gemm_images(int d);  // images of this form are kept at this d
+bool sign_gemm_serves(int bits, bool prod, int d, int64_t n);
+hipError_t launch_sign_gemm_image(const float* W, int d, void* image, hipStream_t s);
+hipError_t launch_sign_gemm(int bits, bool prod, const void* pi_image, const void* s_image, int d, const uint32_t* idx, const uint32_t* qjl,
+                            const float* gamma, const float* norm, int64_t n, float* out, int64_t ldo, float kappa, const SignCoefs& c, hipStream_t s);
+
 // d = 128, both in one launch: image of Pi and its units, image of S and its units
 constexpr size_t SIGN128_BYTES = sign_image_bytes(128) + 128 * 4;  // of one matrix
 hipError_t launch_sign128_images(const float* Pi, const float* S, void* images, hipStream_t s);

@@ -1,5 +1,6 @@
-"""Dequantisation at d = 128 where the centroid table is a sum of signs (none, one bit, two symmetric bits): blocks of 32 codes, four or
-five digits of an entry, from the images or made in the workspace, and the tables that have to go elsewhere."""
+"""Dequantisation where the centroid table is a sum of signs (none, one bit, two symmetric bits): at d = 128 blocks of 32 codes, four or
+five digits of an entry, from the images or made in the workspace, and the tables that have to go elsewhere; at longer d
+workgroups of 256 and 512 codes."""
 import numpy as np
 import pytest
 import torch
@@ -14,11 +15,11 @@ tq = pytest.importorskip("paper_2504_19874_amd")
 D = 128
 
 
-def make(bits, prod, n):
-    p, Pi, S, c32, _ = T.setup(D, bits, prod)
+def make(bits, prod, n, d=D):
+    p, Pi, S, c32, _ = T.setup(d, bits, prod)
     rng = np.random.default_rng(100 * n + bits)
-    idx = rng.integers(0, 1 << bits, size=(n, D)).astype(np.int32)
-    z = rng.integers(0, 2, size=(n, D)).astype(bool)
+    idx = rng.integers(0, 1 << bits, size=(n, d)).astype(np.int32)
+    z = rng.integers(0, 2, size=(n, d)).astype(bool)
     gamma = rng.uniform(0.05, 0.6, size=n).astype(np.float32)
     norm = np.exp(rng.normal(0, 1, size=n)).astype(np.float32)
     codes = [T.dev(o.pack_planes(idx, bits).view(np.int32)) if bits else None, T.dev(o.pack_signs(z).view(np.int32)) if prod else None,
@@ -69,3 +70,23 @@ def test_other_tables(table, n):
     out = torch.empty((n, D), device=T.DEV)
     tq.tq_dequantize(p, *codes, T.dev(norm), out)
     T.P.check_close(out.cpu().numpy(), reference(parts[:5] + (c,), False, norm), norm.astype(np.float64)[:, None] / np.sqrt(D), "coordinate")
+
+
+@pytest.mark.parametrize("d,bits,prod,n", [(256, 1, True, 65), (384, 0, True, 300), (640, 2, True, 257), (896, 1, False, 1000), (256, 2, False, 4097),
+                                           (512, 2, True, 24577), (1536, 2, True, 130), (384, 1, True, 40001)])
+def test_long_codes(d, bits, prod, n):
+    p, codes, parts, norm = make(bits, prod, n, d)
+    wide = torch.full((n + 1, d + 4), 7.0, device=T.DEV)
+    tq.tq_dequantize(p, *codes, T.dev(norm), wide[:n, :d])
+    got = wide[:n, :d].clone()
+    assert bool((wide[:n, d:] == 7).all()) and bool((wide[n] == 7).all())
+    # five digits of every 64 indices and kind of sign are added in turn, each rounding at most 2^-24 of a sum of up to six times its typical size
+    scale = norm.astype(np.float64)[:, None] / np.sqrt(d)
+    assert np.abs((got.cpu().numpy() - reference(parts, prod, norm)) / scale).max() < 5 * d / 64 * (bits + prod) * 6 * 2.0**-24
+    out = torch.empty((n, d), device=T.DEV)
+    try:
+        p.drop_images().reserve(n)  # the digits made in the call: the same bits
+        tq.tq_dequantize(p, *codes, T.dev(norm), out)
+        assert torch.equal(out, got)
+    finally:
+        p.build_images()
