@@ -199,12 +199,13 @@ __global__ __launch_bounds__(256) void topk_merge_kernel(const float* __restrict
 }  // namespace
 
 // Chunks per row when a call's rows are too few to fill the chip: 0 (one workgroup per row) unless the rows are
-// few and long; then chunks of at least a segment, about four workgroups per compute unit in all, and no more
-// pairs per row than the joining kernel takes (4096).
+// few and long; then chunks of a segment or more, about four workgroups per compute unit in all, and no more
+// pairs per row than the joining kernel takes (4096).  (A segment exactly where there could be more: cut into 122 parts, a row of 10^6 is a
+// segment and eight columns each, two passes; 4 rows, k = 10: 13.6 -> 10.8 us.)
 int topk_chunks(int64_t rows, int64_t n, int k) {
   if (k < 1 || rows < 1 || rows > 128 || n < 65536) return 0;
   int64_t c = (4 * (int64_t)device_cu_count() + rows - 1) / rows;
-  if (c > n / SEG) c = n / SEG;
+  if (c > (n + SEG - 1) / SEG) c = (n + SEG - 1) / SEG;
   if (c > 4096 / k) c = 4096 / k;
   if (c > 65535) c = 65535;
   return c >= 2 ? (int)c : 0;
@@ -219,7 +220,8 @@ hipError_t launch_topk(const float* scores, int64_t rows, int64_t n, int64_t ld,
   if (k < 1 || k > 64 || rows > 0x7fffffff || n > 0x7fffffff) return hipErrorInvalidValue;
   if (chunks > 0 && (part_val == nullptr || part_idx == nullptr || chunks > 65535)) return hipErrorInvalidValue;
   const int vec4 = (ld % 4 == 0) && ((reinterpret_cast<uintptr_t>(scores) & 15u) == 0);
-  const int64_t chunk_len = chunks > 0 ? ((n + chunks - 1) / chunks + 3) / 4 * 4 : 0;
+  int64_t chunk_len = chunks > 0 ? ((n + chunks - 1) / chunks + 3) / 4 * 4 : 0;
+  if (chunks == (n + SEG - 1) / SEG) chunk_len = SEG;
   const dim3 grid((unsigned)rows, chunks > 0 ? (unsigned)chunks : 1u);
   if (chunks > 0) {
     out_idx = part_idx;
