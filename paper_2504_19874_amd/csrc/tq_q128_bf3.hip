@@ -41,7 +41,6 @@ namespace tq {
 
 namespace {
 
-constexpr int RING = 4;  // A operands in flight
 
 struct Q128Args {
   const void* X;  // bf16, or fp32 in the F32 instantiations
@@ -61,6 +60,15 @@ struct Q128Args {
   int gs_hi;
   Codebook cb_hi;
 };
+
+// h2_split with the leading piece cut off, not rounded: a mask in place of a conversion back, which the vector units take
+// longer for (131072 vectors, bf16, 3 + 1 bits 28.0 -> 27.3 us; as v_fma_mix_f32 30.0).  The lo piece then has one bit less; the signs are the same.
+__device__ __forceinline__ void cut_split(float a, float b, uint32_t& hi, uint32_t& lo) {
+  typedef float f2 __attribute__((ext_vector_type(2)));
+  const float ha = __uint_as_float(__float_as_uint(a) & 0xffffe000u), hb = __uint_as_float(__float_as_uint(b) & 0xffffe000u);
+  hi = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pkrtz(ha, hb));
+  lo = h2_bits(__builtin_convertvector(f2{a - ha, b - hb}, f16x2));
+}
 
 // The kernel's parameter image, by 256 threads: two fp16 pieces of s Pi at dst, two of S Pi^T (every row under a power of two
 // of its own, which its signs do not see; columns permuted) behind them, each [row][128] with the chunk rotation of q128_at.
@@ -130,6 +138,8 @@ constexpr int q128_per_cu(bool prod, bool f32) { return !prod && !f32 ? 2 : 1; }
 template <int BITS, bool PROD, bool MIXED, int VT, bool F32 = false>
 __global__ __launch_bounds__(512 / VT, q128_per_cu(PROD, F32) * 2 / VT) void quant128_bf3_kernel(const Q128Args a) {
   constexpr int NT = 512 / VT;  // threads
+  // A operands in flight: six where the registers are there (131072 vectors, bf16, 2 + 1 bits 24.3 -> 23.8 us; fp32 30.9 -> 34.4)
+  constexpr int RING = PROD && !F32 ? 6 : 4;
   constexpr int NB = (BITS > 0 ? BITS : 1) + (MIXED ? 1 : 0);  // plane words per tile, at most
   constexpr int BH = BITS < 4 ? BITS + 1 : 4;                  // bits of instance hi
   extern __shared__ __attribute__((aligned(16))) unsigned short lds_s[];
@@ -346,7 +356,7 @@ __global__ __launch_bounds__(512 / VT, q128_per_cu(PROD, F32) * 2 / VT) void qua
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
               uint32_t w1, w2;
-              h2_split(acc[nt][t][8 * p + 2 * e], acc[nt][t][8 * p + 2 * e + 1], w1, w2);
+              cut_split(acc[nt][t][8 * p + 2 * e], acc[nt][t][8 * p + 2 * e + 1], w1, w2);
               rp[0][nt][2 * t + p][e] = w1;
               rp[1][nt][2 * t + p][e] = w2;
             }
