@@ -147,8 +147,12 @@ hipError_t launch_matvec_rows(int d, int64_t n, const float* W0, const float* W1
     return hipGetLastError();
   };
   using std::integral_constant;
-  const bool many = (int64_t)(d / 16) * ((nq + 3) / 4) * mats >= device_cu_count();
+  const int64_t wide = (int64_t)(d / 16) * ((nq + 3) / 4) * mats, cus = device_cu_count();  // workgroups with R = 4
+  const bool many = wide >= cus;
   if (nq == 1) return many ? go(integral_constant<int, 1>{}, integral_constant<int, 4>{}) : go(integral_constant<int, 1>{}, integral_constant<int, 1>{});
+  // (one and a half workgroups per compute unit leave half of them with twice the work of the others: two rows per wavefront then. Four
+  // vectors, two matrices of 3072: 24.1 -> 22.8 us, 16 and 768: 9.7 -> 8.2; with two workgroups and more the staging counts: 8 and 3072 19 / 24)
+  if (many && wide < 2 * cus) return go(integral_constant<int, MV_Q>{}, integral_constant<int, 2>{});
   return many ? go(integral_constant<int, MV_Q>{}, integral_constant<int, 4>{}) : go(integral_constant<int, MV_Q>{}, integral_constant<int, 1>{});
 }
 
