@@ -98,7 +98,7 @@ def make_calls(tq, cfg, p, b):
 
 
 def few_queries(cfg):
-    """tq_score runs on the int8 matrix cores: masked sums of the query's digits (one instance, symmetric codebook)."""
+    """tq_score takes masked sums of the query's fixed-point digits (one instance, symmetric codebook)."""
     if cfg.d % 128:
         return False
     if cfg.d <= 512:
@@ -109,7 +109,8 @@ def few_queries(cfg):
 def routing(cfg, call: str):
     """How the library carries out the fp32 contractions of `call` on the 16-bit matrix cores: (products per fp32 product of
     the rotation or centroid part, the same of the sketch or sign part, in words), or None where the call runs on the fp32
-    or the int8 matrix cores.  Mirrors the library's choice for one instance and the workspace that it asks for."""
+    matrix instructions or on digits.  (Dequantisation of tables that are sums of signs runs on fp6 digits; it is priced as the pieces that
+    they took the place of.)  Mirrors the library's choice for one instance and the workspace that it asks for."""
     n, prod, bits = cfg.n * cfg.n_groups, cfg.kind == "prod", cfg.bits_mse
     bf16 = cfg.in_dtype == "bf16"
     # Alg. 2 of fp32 vectors whose residual is small keeps the rotation on the fp32 instructions
@@ -119,7 +120,7 @@ def routing(cfg, call: str):
             return None
         if cfg.d == 128:
             return 2 if bf16 else 3, 3, (f"fp16 MFMA, {'a bf16 vector as one exact piece' if bf16 else 'two pieces of x'} against two "
-                                         "of Pi (rotation); bf16 MFMA, two pieces of the residual against two of S Pi^T (signs only)")
+                                         "of Pi (rotation), two pieces of the residual against two of S Pi^T (signs only)")
         if cfg.d >= 512 or n <= 16384:
             if n <= 64 and cfg.d >= 512 and (n + 3) // 4 * cfg.d ** 2 * (2 if prod else 1) <= 150 * 512 ** 2:
                 return None
@@ -131,6 +132,9 @@ def routing(cfg, call: str):
         if cfg.d == 128 and n <= 8192:
             return None
         kind = "bf16" if cfg.d == 128 else "fp16"
+        if bits <= 2 and cfg.d % 128 == 0 and (prod or bits != 2 or n * cfg.d >= 1 << 20):
+            return 2 if bits == 1 else 3, 2, (f"scaled-format MFMA, signs of the planes as fp4 against {'four' if cfg.d == 128 else 'five'} fp6 "
+                                              f"digits of Pi^T and S^T (priced as {kind} pieces)")
         return 2 if bits == 1 else 3, 2, f"{kind} MFMA, two pieces of a centroid (a sign is one) against two of Pi^T and S^T"
     if few_queries(cfg) or (cfg.q_per_group <= 32 and cfg.d % 128 == 0 and cfg.d <= 1024):
         return None
@@ -160,8 +164,8 @@ def arithmetic(cfg):
         if r is not None:
             out[call] = r[2] + "; fp32 accumulation"
         elif call == "score" and few_queries(cfg):
-            unit = 19 if cfg.d == 128 else 20
-            out[call] = f"int8 MFMA on exact base-128 digits of rotated queries in 2^-{unit} fixed point, fp32 combination"
+            unit, digit = (19, "fp8 digits (base 32)") if cfg.d == 128 else (20, "fp6 digits (base 49)")
+            out[call] = f"scaled-format MFMA on exact {digit} of rotated queries in 2^-{unit} fixed point, fp32 combination"
         else:
             out[call] = "fp32"
     return out
@@ -274,10 +278,10 @@ def path_dtype(cfg):
     for name in ("quantize", "dequantize", "score"):
         pc = piece_products(cfg, name)
         if pc:
-            kinds = " and ".join(k for k in ("fp16", "bf16") if k + " MFMA" in routing(cfg, name)[2])
+            kinds = " and ".join(k for k in ("fp16", "bf16") if k + " MFMA" in routing(cfg, name)[2]) or "fp6 digits in place of"
             parts.append(f"{name}: {kinds} pieces of fp32 factors ({pc:g} products per fp32 product), f32 accumulate")
         elif name == "score" and few_queries(cfg):
-            parts.append("score: i8 digits of a fixed-point query, i32 accumulate")
+            parts.append(f"score: {'fp8' if cfg.d == 128 else 'fp6'} digits of a fixed-point query, exact f32 accumulate")
         else:
             parts.append(f"{name}: f32")
     return "; ".join(parts)

@@ -249,7 +249,7 @@ def main():
         report("score" + (f"+top{cfg.topk}" if cfg.topk else ""), cfg, timed(score, reps),
                2.0 * pairs * d * (2 if prod else 1) + 2.0 * nq * dd * (2 if prod else 1),
                n * code_b + out_b + 4 * nq * d, {"scores_per_s": None, "pairs": pairs},
-               # a few queries per code run on the int8 cores and read the codes once per four queries
+               # a few queries per code run on digits and masks and read the codes once per four queries
                bound="hbm" if cfg.q_per_group <= 16 and d > 128 else None)
 
     if on("attend") and not cfg.topk and cfg.q_per_group <= 32 and not big:
@@ -290,7 +290,7 @@ def main():
             f"{'prod' if vprod else 'mse'}{args.value_bits}"
         report(f"attend(v{vname})", cfg, timed(attend, reps),
                2.0 * pairs * d * ((2 if prod else 1) + (2 if vprod else 1)), n * (code_b + vcode_b) + 8 * nq * d,
-               {"pairs": pairs}, bound="hbm")  # the contractions run on the int8 cores; the codes are read once
+               {"pairs": pairs}, bound="hbm")  # the contractions run on digits and masks; the codes are read once
 
         if d == 128 and not cfg.d_hi and p.PiT is not None:
             # one decoding step on a cache laid out [head][capacity = n]: the last slot of every head is
