@@ -16,10 +16,11 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 
 // The operand of one rotated query ys [d] (LDS) for tq_score_stream.hip: 32 words per word group g, digit dg of its coordinates as 32 values
-// of 6 bits, the first four words at 4 dg, the other two at 16 + 2 dg.  Value 8 v + i is coordinate 32 g + 4 i + v, negated for v = 3.  A mask
+// of 6 bits, the first four words at 4 dg, the other two at 16 + 2 dg (24 words, here without the gap; written in bytes, which memory takes
+// one by one and LDS does not: 7.0 -> 6.6 us at d = 3072).  Value 8 v + i is coordinate 32 g + 4 i + v, negated for v = 3.  A mask
 // of bit b is 4 + 2 b, 2 + 2 b, 2 b or 1 - 2 b there (v = 0 .. 3); off_s[dg], zero before: what the parts without b come to.  A thread
 // for four coordinates, d / 4 <= blockDim.x.
-__device__ __forceinline__ void stream_digits(const float* ys, int d, float sc, uint32_t* img, int* off_s, int tid) {
+__device__ __forceinline__ void stream_digits(const float* ys, int d, float sc, uint32_t* img_s, int* off_s, int tid) {
   int off[4] = {0, 0, 0, 0};
   if (tid < d / 4) {  // eight threads of a group: four values = 24 bits of the 192 each
     const int g = tid >> 3, v = (tid >> 1) & 3, half = tid & 1;
@@ -41,7 +42,7 @@ __device__ __forceinline__ void stream_digits(const float* ys, int d, float sc, 
 #pragma unroll
       for (int k = 0; k < 3; ++k) {
         const int at = 6 * v + 3 * half + k;  // of the lane's 24 bytes
-        reinterpret_cast<uint8_t*>(img + g * 32 + (at < 16 ? dg * 4 : 16 + dg * 2 - 4))[at] = (uint8_t)(w[dg] >> (8 * k));
+        reinterpret_cast<uint8_t*>(img_s + g * 24 + (at < 16 ? dg * 4 : 16 + dg * 2 - 4))[at] = (uint8_t)(w[dg] >> (8 * k));
       }
   }
   // two sums to a word: a wavefront's are at most 64 x 4 x 56 each
@@ -169,6 +170,7 @@ __global__ __launch_bounds__(1024) void digitise_i8_kernel(const int d, const in
   __shared__ float red_mx[16];
   __shared__ long long red_tot[16];
   __shared__ int off_s[4];
+  __shared__ uint32_t img_s[4096 / 32 * 24];
   const int tid = threadIdx.x;
   if (tid < 4) off_s[tid] = 0;
   const int64_t q = blockIdx.x;
@@ -189,7 +191,7 @@ __global__ __launch_bounds__(1024) void digitise_i8_kernel(const int d, const in
   int e = 0;
   if (mx > 0.f) (void)frexpf(mx, &e);  // mx = f * 2^e, f in [0.5, 1)
   const float sc = ldexpf(1.f, 20 - e);
-  stream_digits(ys, d, sc, own, off_s, tid);  // everyone has read its floats
+  stream_digits(ys, d, sc, img_s, off_s, tid);
   int tot = 0;  // of a wavefront: 256 values of up to 2^20
 #pragma unroll
   for (int k = 0; k < 4; ++k) tot += __float2int_rn(v[k] * sc);
@@ -197,6 +199,7 @@ __global__ __launch_bounds__(1024) void digitise_i8_kernel(const int d, const in
   for (int off = 32; off >= 1; off >>= 1) tot += __shfl_xor(tot, off);
   if ((tid & 63) == 0) red_tot[tid >> 6] = tot;
   __syncthreads();
+  for (int i = tid; i < d / 32 * 24; i += blockDim.x) own[i / 24 * 32 + i % 24] = img_s[i];  // (everyone has read its floats)
   if (tid < 4) reinterpret_cast<float*>(own)[24 + tid] = (float)-off_s[tid];  // behind the first group's digits: where the sums start
   if (tid == 0) {
     long long t = 0;
