@@ -250,6 +250,7 @@ typedef struct tq_params {
  * want the plain fp32 evaluation. */
 #define TQ_FLAG_FP32_MFMA 1u
 #define TQ_FLAG_DEQUANT_IMAGES 2u  /* params.images: see tq_build_dequant_images */
+#define TQ_FLAG_SIGN_IMAGES 4u     /* with the last one: the digits that tq_build_dequant_images writes at multiples of 128 are there, too */
 
 /*
  * Fill the derived matrices from Pi and S on the device: PiT = Pi^T,
@@ -285,7 +286,8 @@ tq_status tq_build_images(const tq_params* p, void* images, void* stream);
  * bits, symmetric about zero).
  * Read from p->Pi and p->S.  They lie behind the
  * images above: `images` is a buffer of tq_images_bytes(d) + tq_dequant_images_bytes(d) bytes, and
- * TQ_FLAG_DEQUANT_IMAGES in params.flags says that params.images is such a buffer with both parts filled.  Without the flag tq_dequantize makes these tiles in the
+ * TQ_FLAG_DEQUANT_IMAGES in params.flags says that params.images is such a buffer with both parts filled, TQ_FLAG_SIGN_IMAGES
+ * that its second part has the digits (a buffer that was sized and filled without them stays valid under the first flag alone).  Without the first flag tq_dequantize makes these tiles in the
  * workspace in every call, where it has room (8 d^2 + 256 bytes, less at d = 128), or takes kernels that do without (at d = 128 above 24576 vectors), the same up to
  * rounding; tq_score likewise for more than 64 queries (tq_score_workspace_bytes counts the room). */
 size_t tq_dequant_images_bytes(int32_t d);

@@ -31,7 +31,7 @@ class TqParams(C.Structure):
         ("images", C.c_void_p),
     ]
 
-TQ_FLAG_FP32_MFMA, TQ_FLAG_DEQUANT_IMAGES = 1, 2
+TQ_FLAG_FP32_MFMA, TQ_FLAG_DEQUANT_IMAGES, TQ_FLAG_SIGN_IMAGES = 1, 2, 4
 
 
 _P = C.POINTER(TqParams)

@@ -143,7 +143,7 @@ class Params:
             _check(lib.tq_build_images(C.byref(self.c), _ptr(self.images), _stream()), "tq_build_images")
             if more:
                 _check(lib.tq_build_dequant_images(C.byref(self.c), _ptr(both), _stream()), "tq_build_dequant_images")
-                self.c.flags |= _lib.TQ_FLAG_DEQUANT_IMAGES
+                self.c.flags |= _lib.TQ_FLAG_DEQUANT_IMAGES | _lib.TQ_FLAG_SIGN_IMAGES
             self.c.images = self.images.data_ptr()
         return self
 

@@ -102,6 +102,11 @@ const void* dequant_image(const tq_params* p) {
   return p->d == 128 && p->images != nullptr ? static_cast<const char*>(p->images) + quant128_bf3_image_bytes() : nullptr;
 }
 
+bool sign_images(const tq_params* p) {
+  constexpr uint32_t both = TQ_FLAG_DEQUANT_IMAGES | TQ_FLAG_SIGN_IMAGES;
+  return p->images != nullptr && (p->flags & both) == both;
+}
+
 tq_status from_hip(hipError_t e) { return e == hipSuccess ? TQ_OK : TQ_ERR_HIP; }
 
 // Quant_prod of fp32 vectors on the bf16 matrix cores keeps the two leading pieces of x: the rotated vector is off
@@ -140,7 +145,7 @@ float* h2_image_scale(const void* images, int d, int which) {
   const char* const at = which >= 2 ? h2_image(images, d, 5) + 8 * (which - 2) : h2_image(images, d, 0) + 2 * h2_image_bytes(d, d) + 8 * which;
   return reinterpret_cast<float*>(const_cast<char*>(at));
 }
-// behind those, where codes are decoded as signs (tq_sign_gemm.hip): the digits of Pi^T and of S^T
+// with TQ_FLAG_SIGN_IMAGES behind those, where codes are decoded as signs (tq_sign_gemm.hip): the digits of Pi^T and of S^T
 char* sign_gemm_image(const void* images, int d, int which) {
   return const_cast<char*>(h2_image(images, d, 5)) + 256 + which * sign_gemm_image_bytes(d);
 }
@@ -571,8 +576,7 @@ tq_status tq_dequantize(const tq_params* p, const uint32_t* idx, const uint32_t*
   SignCoefs sc;
   if (p->d == 128 && !fp32_mfma_only(p) && (p->bits_mse > 0 || prod) && sign_table(p->bits_mse, make_codebook(p), &sc)) {
     const hipStream_t s = static_cast<hipStream_t>(stream);
-    const char* digits = p->images != nullptr && (p->flags & TQ_FLAG_DEQUANT_IMAGES) != 0
-                             ? static_cast<const char*>(p->images) + tq_images_bytes(128) : nullptr;
+    const char* digits = sign_images(p) && aligned16(p->images) ? static_cast<const char*>(p->images) + tq_images_bytes(128) : nullptr;
     if (p->images == nullptr && n <= kSignOwnDigitRows && p->Pi != nullptr && (!prod || p->S != nullptr)) {
       Workspace ws{static_cast<char*>(p->workspace), p->workspace_bytes, 0};
       if (char* const own = static_cast<char*>(ws.take((prod ? 2 : 1) * SIGN128_BYTES)); own != nullptr) {
@@ -606,7 +610,7 @@ tq_status tq_dequantize(const tq_params* p, const uint32_t* idx, const uint32_t*
     const int d = p->d;
     const char *pi = nullptr, *si = nullptr;
     if (const char* const img = h2_dequant_images(p); img != nullptr) {
-      pi = sign_gemm_image(img, d, 0), si = sign_gemm_image(img, d, 1);
+      if (sign_images(p)) pi = sign_gemm_image(img, d, 0), si = sign_gemm_image(img, d, 1);
     } else {
       Workspace ws{static_cast<char*>(p->workspace), p->workspace_bytes, 0};
       if (char* const own = static_cast<char*>(ws.take((prod ? 2 : 1) * sign_gemm_image_bytes(d))); own != nullptr) {

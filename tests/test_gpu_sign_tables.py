@@ -90,3 +90,23 @@ def test_long_codes(d, bits, prod, n):
         assert torch.equal(out, got)
     finally:
         p.build_images()
+
+
+@pytest.mark.parametrize("d,n", [(128, 100), (128, 8200), (256, 5000)])
+def test_images_without_digits(d, n):
+    """TQ_FLAG_DEQUANT_IMAGES alone: images that end before the digits (made so here: the buffer is cut there), and the kernels that do without."""
+    from paper_2504_19874_amd import _lib
+    p, codes, parts, norm = make(2, True, n, d)
+    out = torch.empty((n, d), device=T.DEV)
+    whole = p.images
+    sign_bytes = 2 * ((d // 64) * (d // 32) * 5 * 1536 + 512) if d == 128 else 8 * d * d
+    cut = torch.empty(int(tq.tq_images_bytes(d)) + int(_lib.load().tq_dequant_images_bytes(d)) - sign_bytes, dtype=torch.uint8, device=T.DEV)
+    cut.copy_(torch.as_strided(whole, (cut.numel(),), (1,)))
+    try:
+        p.images, p.c.images = cut, cut.data_ptr()
+        p.c.flags &= ~_lib.TQ_FLAG_SIGN_IMAGES
+        tq.tq_dequantize(p, *codes, T.dev(norm), out)
+    finally:
+        p.build_images()
+    assert p.c.flags & _lib.TQ_FLAG_SIGN_IMAGES
+    T.P.check_close(out.cpu().numpy(), reference(parts, True, norm), norm.astype(np.float64)[:, None] / np.sqrt(d), "coordinate")
