@@ -63,12 +63,17 @@ __device__ __forceinline__ v8i_t sign_operand(const SignFrag& f) {
   const v4 a = __builtin_bit_cast(v4, f.a), b = v4{(int)f.b.x, (int)f.b.y, 0, 0};
   return __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, -1, -1);
 }
-// the signs of 32 bits (bit set: +1) as fp4
-__device__ __forceinline__ v8i_t sign_bits(uint32_t w) {
-  const uint32_t n = ~w;
+// Minus the signs of 32 bits (bit set: +1) as fp4; two: 0x22222222 in a register that the compiler does not know (one v_and_or_b32 takes no two
+// constants: seven instructions, twelve otherwise).  The sums are all of the other sign, which their last factor puts right.
+__device__ __forceinline__ uint32_t sign_two() {
+  uint32_t two = 0x22222222u;
+  asm volatile("" : "+v"(two));
+  return two;
+}
+__device__ __forceinline__ v8i_t minus_sign_bits(uint32_t w, uint32_t two) {
   typedef int v4 __attribute__((ext_vector_type(4)));
-  const v4 v = {(int)(((n << 3) & 0x88888888u) | 0x22222222u), (int)(((n << 2) & 0x88888888u) | 0x22222222u),
-                (int)(((n << 1) & 0x88888888u) | 0x22222222u), (int)((n & 0x88888888u) | 0x22222222u)};
+  const v4 v = {(int)(((w << 3) & 0x88888888u) | two), (int)(((w << 2) & 0x88888888u) | two), (int)(((w << 1) & 0x88888888u) | two),
+                (int)((w & 0x88888888u) | two)};
   return __builtin_shufflevector(v, v, 0, 1, 2, 3, -1, -1, -1, -1);
 }
 // accumulator += signs x digit J, in units: 8 (fp6 holds eighths) 32^J

@@ -53,8 +53,8 @@ __global__ __launch_bounds__(256, 2) void sign128_dequant_kernel(const Sign128Ar
         frag[m][j][s].b = *reinterpret_cast<const uint2*>(f + 1024 + lane * 8);
       }
   const unsigned char* const units = a.image + sign_image_bytes(128) + (32 * ct + l) * 4;
-  const float pi_unit = BITS > 0 ? *reinterpret_cast<const float*>(units) : 0.f;
-  const float s_unit = PROD ? *reinterpret_cast<const float*>(units + SIGN128_BYTES) : 0.f;
+  const float pi_unit = BITS > 0 ? -*reinterpret_cast<const float*>(units) : 0.f;
+  const float s_unit = PROD ? -*reinterpret_cast<const float*>(units + SIGN128_BYTES) : 0.f;  // (minus: see minus_sign_bits)
   // the two factors in two parts each: rounded once they would be off for every code alike
   const double alpha_d = a.c.alpha * (double)pi_unit, beta_d = a.c.beta * (double)pi_unit;
   const float alpha = (float)alpha_d, beta = (float)beta_d, alpha_lo = (float)(alpha_d - (double)alpha), beta_lo = (float)(beta_d - (double)beta);
@@ -80,6 +80,7 @@ __global__ __launch_bounds__(256, 2) void sign128_dequant_kernel(const Sign128Ar
   const floatx16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
   const uint32_t row_bytes = (uint32_t)a.ldo * 4u;
   const uint32_t lane_off = 4u * (uint32_t)h * row_bytes + 4u * (uint32_t)l;
+  const uint32_t two = sign_two();
   int64_t blk = id >> 2;
   if (blk < blocks) load(blk);
   for (; blk < blocks; blk += step) {
@@ -88,8 +89,8 @@ __global__ __launch_bounds__(256, 2) void sign128_dequant_kernel(const Sign128Ar
     for (int s = 0; s < 2; ++s) {
       if constexpr (BITS > 0)
 #pragma unroll
-        for (int p = 0; p < BITS; ++p) sw[s][p] = sign_bits(w[s][p]);
-      if constexpr (PROD) sz[s] = sign_bits(z[s]);
+        for (int p = 0; p < BITS; ++p) sw[s][p] = minus_sign_bits(w[s][p], two);
+      if constexpr (PROD) sz[s] = minus_sign_bits(z[s], two);
     }
     float (&row_f)[2][32] = row_s[(threadIdx.x >> 6) & 3];
     row_f[0][l] = nu;

@@ -11,7 +11,7 @@
 //
 // Bound by the matrix instructions: at their rate in registers, which the chip's power sets (6.6 PFLOP/s with signs against digits), 20011
 // codes of 768, 2 + 1 bits, take 55 us, their stores 13.  Before -> now, us: that 106 -> 87, 1 + 1 bits 84 -> 57, 1 bit 50 -> 34; 3000 codes
-// of 1536, 2 + 1 bits 159 -> 75; 100000 of 384 218 -> 115; 20011 of 3072 1594 -> 1363.  Error against 64 bits, of a
+// of 1536, 2 + 1 bits 159 -> 75; 100000 of 384 218 -> 115; 20011 of 3072 1594 -> 1340.  Error against 64 bits, of a
 // coordinate's root mean square: d = 768, 2 + 1 bits 3.5e-7 -> 1.7e-7; 3072 6.9e-7 -> 3.2e-7.
 #include <type_traits>
 
@@ -130,6 +130,7 @@ __global__ __launch_bounds__(64 * WC, 2) void sign_gemm_kernel(const SignGemmArg
     for (int u = 0; u < 2; ++u)
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[t][u][r] = 0.f;
+  const uint32_t two = sign_two();
   // ten products of a digit: the next one's fragments are on their way from LDS during each
   auto compute = [&](int buf, const Pair& p) {
     auto fragments = [&](int i, SignFrag (&f)[2]) {  // i: digit + 5 step
@@ -148,7 +149,7 @@ __global__ __launch_bounds__(64 * WC, 2) void sign_gemm_kernel(const SignGemmArg
       if constexpr (i + 1 < 2 * SIGN_DIGITS) fragments(i + 1, f[(i + 1) & 1]);
       if constexpr (j == 0)
 #pragma unroll
-        for (int t = 0; t < TW; ++t) sg[t] = sign_bits(p.w[t][i / SIGN_DIGITS]);
+        for (int t = 0; t < TW; ++t) sg[t] = minus_sign_bits(p.w[t][i / SIGN_DIGITS], two);
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
       for (int u = 0; u < 2; ++u)
@@ -228,7 +229,7 @@ __global__ __launch_bounds__(64 * WC, 2) void sign_gemm_kernel(const SignGemmArg
   // ---- a lane has 16 codes of two neighbouring outputs, a half-wave stores 256 bytes of a row ----------------
   float per[2];
 #pragma unroll
-  for (int u = 0; u < 2; ++u) per[u] = BITS > 0 ? (float)(a.c.alpha * (double)pi_unit[u]) : s_unit[u];
+  for (int u = 0; u < 2; ++u) per[u] = -(BITS > 0 ? (float)(a.c.alpha * (double)pi_unit[u]) : s_unit[u]);  // (minus: see minus_sign_bits)
   const int m = tile_m * TO + 2 * l;
   typedef float f32x2 __attribute__((ext_vector_type(2)));
 #pragma unroll
