@@ -56,8 +56,9 @@ __host__ __device__ constexpr int score128_lds(int bits) { return 8 * stage_byte
 // (query q0 + lane / 16, key wave_key0 + 16 t + lane % 16), wave_key0 = (8 blockIdx.x + wave) * 16 TILES.
 // dyn_s: score128_lds(BITS) bytes, 8 staging regions, then the query preparation.  All of LDS may be reused after the workgroup's
 // next barrier.
-template <int BITS, bool PROD, int TILES, class Sink>
-__device__ __forceinline__ void score128_body(const ScoreI8Args& a, unsigned char* dyn_s, Sink& sink) {
+// meanwhile(): what the caller has to do that waits for nothing, while the first loads are on their way.
+template <int BITS, bool PROD, int TILES, class Sink, class Meanwhile>
+__device__ __forceinline__ void score128_body(const ScoreI8Args& a, unsigned char* dyn_s, Sink& sink, Meanwhile meanwhile) {
   constexpr int RT = SCORE128_ROUND_TILES < TILES ? SCORE128_ROUND_TILES : TILES;
   constexpr int ROWS = 16 * RT;               // rows staged per round
   constexpr int ROUNDS = TILES / RT;
@@ -134,6 +135,8 @@ __device__ __forceinline__ void score128_body(const ScoreI8Args& a, unsigned cha
 #pragma unroll
   for (int r = 0; r < AHEAD; ++r) issue_round(r);
   __builtin_amdgcn_sched_barrier(0);  // all of these are asked for here (left to itself the compiler requests a matrix entry when it is due)
+
+  meanwhile();
 
   // ---- 3. rotate / sketch this workgroup's four queries, 4. fixed point --------------------------
   prep.matvec(a, group, q0, part_s);
