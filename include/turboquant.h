@@ -75,6 +75,8 @@
  *   quantise, sketch, of which only signs are kept: two pieces of the residual and
  *     two of S Pi^T (a sign can differ from the exact one only where
  *     |<S_j, r>| < 1e-6 |S_j| |r|).
+ *   quantise at d = 128 with a table that holds a centroid beyond +-64 (the pieces of the
+ *     residual are made for tables of about the unit ball): fp32 instructions.
  *   tq_quantize_prod of fp32 vectors keeps the rotation on the fp32 instructions,
  *     whatever the batch size, where the residual is so small that the part of x
  *     left out would show in gamma (4-bit MSE stage up to d = 416, 3 bits up to
@@ -306,7 +308,9 @@ size_t tq_workspace_bytes(const tq_params* p, int64_t n, int64_t nq, int32_t top
  *   idx   device out, n * (bits_mse*d/32) words.
  *   norm  device out, n floats, or NULL.  Non-NULL: each row is divided by its
  *         L2 norm before rotation and the norm is stored (a zero row stays
- *         zero with norm 0).  NULL: rows are taken as unit-norm as given.
+ *         zero with norm 0).  NULL: rows are taken as unit-norm as given. (Longer
+ *         ones are quantised as they are, their sketch too; gamma overflows from
+ *         residuals of 1e17 on.)
  * A coordinate exactly on a cell boundary goes to the upper cell.
  */
 tq_status tq_quantize_mse(const tq_params* p, const void* x, int32_t dtype, int64_t n,

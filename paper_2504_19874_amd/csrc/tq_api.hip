@@ -263,13 +263,16 @@ tq_status quantize_common(const tq_params* p, const void* x, int32_t dtype, int6
   const size_t esz = dtype == TQ_F32 ? 4 : 2;
   const int words_per_row = (d / 32) * p->bits_mse;
 
+  const Codebook few_cb = make_codebook(p), few_cb_hi = make_codebook_hi(p);
+  const bool few128_takes = d == 128 && dtype == TQ_BF16 && !fp32_mfma_only(p) &&
+                            quant128_few_applicable(p->bits_mse, few_cb, p->d_hi != 0 ? &few_cb_hi : nullptr);
   if (scattered) {
     // rows scattered into a larger store (tq_append): the short-chain d = 128 kernel only
     if (d != 128 || n > kSmallQuantRows || !aligned16(x) || (ldx * esz) % 16 != 0) return TQ_ERR_UNSUPPORTED;
     if (p->d_hi != 0 && norm == nullptr) return TQ_ERR_INVALID_ARG;
-    if (dtype == TQ_BF16 && !fp32_mfma_only(p))
-      return from_hip(launch_quant128_few(p->bits_mse, prod, x, ldx, n, p->Pi, prod ? p->SPiT : nullptr, idx, qjl, gamma, norm, make_codebook(p),
-                                          p->d_hi / 32, make_codebook_hi(p), quant_image(p), stream, out_first, out_step));
+    if (few128_takes)
+      return from_hip(launch_quant128_few(p->bits_mse, prod, x, ldx, n, p->Pi, prod ? p->SPiT : nullptr, idx, qjl, gamma, norm, few_cb,
+                                          p->d_hi / 32, few_cb_hi, quant_image(p), stream, out_first, out_step));
     return from_hip(launch_quant128_small(p->bits_mse, prod, dtype == TQ_BF16, x, ldx, n, p->Pi,
                                           prod ? p->SPiT : nullptr, idx, qjl, gamma, norm, make_codebook(p),
                                           p->d_hi / 32, p->d_hi != 0 ? make_codebook_hi(p) : make_codebook(p), stream,
@@ -278,10 +281,10 @@ tq_status quantize_common(const tq_params* p, const void* x, int32_t dtype, int6
 
   // head dimension 128, a small batch of bf16 vectors
   auto few128 = [&] {
-    return from_hip(launch_quant128_few(p->bits_mse, prod, x, ldx, n, p->Pi, prod ? p->SPiT : nullptr, idx, qjl, gamma, norm, make_codebook(p),
-                                        p->d_hi / 32, make_codebook_hi(p), quant_image(p), stream));
+    return from_hip(launch_quant128_few(p->bits_mse, prod, x, ldx, n, p->Pi, prod ? p->SPiT : nullptr, idx, qjl, gamma, norm, few_cb,
+                                        p->d_hi / 32, few_cb_hi, quant_image(p), stream));
   };
-  const bool few128_serves = d == 128 && dtype == TQ_BF16 && n <= kFewQuantRows && !fp32_mfma_only(p) && aligned16(x) && ldx % 8 == 0;
+  const bool few128_serves = few128_takes && n <= kFewQuantRows && aligned16(x) && ldx % 8 == 0;
 
   if (p->d_hi != 0) {
     // two instances: the d = 128 kernels; both norms are always stored

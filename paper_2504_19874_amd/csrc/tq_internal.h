@@ -119,6 +119,7 @@ hipError_t launch_quant128_bf3(int bits, bool prod, bool f32, const void* X, int
 // Up to here it is faster than the kernel above whatever the bits (2 + 1 bits, 24576 / 32768 vectors: 10.5 / 12.8 us against 11.6 /
 // 11.7; 4 bits 9.7 / 12.0 against 14.2 / 14.2)
 constexpr int64_t kFewQuantRows = 24576;
+bool quant128_few_applicable(int bits, const Codebook& cb, const Codebook* cb_hi);
 hipError_t launch_quant128_few(int bits, bool prod, const void* X, int64_t ldx, int64_t n, const float* Pi, const float* SPiT, uint32_t* idx,
                                uint32_t* qjl, float* gamma, float* norm, const Codebook& cb, int gs_hi, const Codebook& cb_hi,
                                const void* image, hipStream_t s, int64_t out_first = 0, int64_t out_step = 1);

@@ -11,8 +11,23 @@ constexpr int PI_ELEMS = 2 * MAT_ELEMS;
 constexpr int W_ELEMS = 2 * MAT_ELEMS;
 
 // The residual is carried 64-fold, and so are the tables that it comes from: its two fp16 pieces then have room on both sides
-// (|64 e| up to 512 times what a unit vector gives, and 2^-30 |e| at the lower end).
+// (for a unit vector; 2^-30 |e| at the lower end).
 constexpr float Q128_RES = 64.f;
+// Tables that the kernels take: others (no unit vector comes near such centroids) go to the fp32 instructions
+constexpr float Q128_TABLE_MAX = 64.f;
+inline bool q128_table(const Codebook& cb, int bits) {
+  for (int i = 0; i < 1 << bits; ++i)
+    if (!(cb.c[i] >= -Q128_TABLE_MAX && cb.c[i] <= Q128_TABLE_MAX)) return false;
+  return true;
+}
+// Rows that are taken as given may be of any length: the power of two that brings a vector's 64-fold residual into the range of
+// fp16, 1 for every unit vector.  inv: accumulator -> 64-fold coordinate; an accumulator is a sum of 128 products of values
+// below 2^15, and a residual is at most a coordinate and a centroid.  (The sketch keeps signs only: no one undoes this.)
+__device__ __forceinline__ float q128_room(float inv) {
+  const float most = fmaf(inv, 0x1p37f, Q128_RES * Q128_TABLE_MAX);
+  const uint32_t e = __float_as_uint(most) >> 23;  // (NaN and infinity: 255)
+  return most <= 65000.f ? 1.f : __uint_as_float((268u - e) << 23);  // most in [2^(e - 127), 2^(e - 126)): below 2^15 then
+}
 inline Codebook q128_scaled(Codebook cb) {
   for (float& v : cb.c) v *= Q128_RES;
   for (float& v : cb.t) v *= Q128_RES;

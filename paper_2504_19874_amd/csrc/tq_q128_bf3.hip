@@ -312,6 +312,14 @@ __global__ __launch_bounds__(512 / VT, q128_per_cu(PROD, F32) * 2 / VT) void qua
     uint32_t word[VT][4][NB];
     float g2[VT] = {}, g2h[VT] = {}, nuh[VT] = {};  // MIXED: g2 / nu belong to instance lo
     u32x4 rp[2][VT][8];  // [piece][nt][step of stage 2]
+    // two instances are normalised each by what the rotation left of it: no residual is longer than a unit vector and a centroid
+    float room[VT];
+    bool long_rows = false;  // uniform
+#pragma unroll
+    for (int nt = 0; nt < VT; ++nt) {
+      room[nt] = MIXED ? 1.f : q128_room(inv[nt]);
+      if (PROD && !MIXED) long_rows = long_rows || __builtin_amdgcn_ballot_w64(room[nt] != 1.f) != 0;
+    }
     const int gs = MIXED ? a.gs_hi : 0;
     float inv_hi[VT] = {};
 #pragma unroll
@@ -371,6 +379,20 @@ __global__ __launch_bounds__(512 / VT, q128_per_cu(PROD, F32) * 2 / VT) void qua
       if constexpr (VT == 2) {
         tile(I1{}, I0{}); tile(I1{}, I1{}); tile(I1{}, I2{}); tile(I1{}, I3{});
       }
+    }
+    // rows taken as given, far longer than 1: split again, scaled (here, once a block: as a branch in every tile 131072 vectors take 1.3 % longer)
+    if (long_rows) {
+#pragma unroll
+      for (int nt = 0; nt < VT; ++nt)
+#pragma unroll
+        for (int t = 0; t < 4; ++t)
+#pragma unroll
+          for (int e = 0; e < 8; ++e) {
+            uint32_t w1, w2;
+            cut_split(room[nt] * acc[nt][t][2 * e], room[nt] * acc[nt][t][2 * e + 1], w1, w2);
+            rp[0][nt][2 * t + (e >> 2)][e & 3] = w1;
+            rp[1][nt][2 * t + (e >> 2)][e & 3] = w2;
+          }
     }
 
     // the vector this lane stores for.  VT = 2: tile nt = g (each half-wave writes one tile's rows); VT = 1: the one
@@ -508,12 +530,13 @@ hipError_t launch_one(const Q128Args& a, bool f32, hipStream_t s) {
 }  // namespace
 
 // bf16 rows of 128 values (fp32 rows too where there is one instance), 16-byte aligned with a row stride that keeps
-// them so; symmetric tables
+// them so; symmetric tables of the unit ball's size
 bool quant128_bf3_applicable(int bits, bool prod, bool f32, const void* X, int64_t ldx, const Codebook& cb, const Codebook* cb_hi) {
   if (f32 && cb_hi != nullptr) return false;
   if (bits < 0 || bits > (cb_hi != nullptr ? 3 : 4) || (bits == 0 && !prod && cb_hi == nullptr)) return false;
   // from 3 bits on the decision is taken on |y|: tables symmetric about zero (what tq_build_codebook produces)
   if (!codebook_symmetric(cb, bits) || (cb_hi != nullptr && !codebook_symmetric(*cb_hi, bits + 1))) return false;
+  if (!q128_table(cb, bits) || (cb_hi != nullptr && !q128_table(*cb_hi, bits + 1))) return false;
   return (reinterpret_cast<uintptr_t>(X) & 15u) == 0 && ldx % (f32 ? 4 : 8) == 0;
 }
 

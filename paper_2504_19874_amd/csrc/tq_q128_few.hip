@@ -271,6 +271,11 @@ __global__ __launch_bounds__(512, 4) void q128_few_kernel(const QuantFewArgs a) 
     g2 = over_vector(g2);
     if (kq == 0) g2_s[par][wave][col] = g2;
     {
+      if constexpr (!MIXED) {
+        const float room = q128_room(inv);  // the same in all wavefronts
+#pragma unroll
+        for (int r = 0; r < 4; ++r) e[r] *= room;
+      }
       uint32_t h0, h1, l0, l1;
       h2_split(e[0], e[1], h0, l0);
       h2_split(e[2], e[3], h1, l1);
@@ -332,7 +337,11 @@ hipError_t launch_bits(const QuantFewArgs& a, bool prod, hipStream_t s) {
 
 }  // namespace
 
-// rows of 128 bf16 values, 8-byte aligned with a row stride that keeps them so; any table
+bool quant128_few_applicable(int bits, const Codebook& cb, const Codebook* cb_hi) {
+  return q128_table(cb, bits) && (cb_hi == nullptr || q128_table(*cb_hi, bits + 1));
+}
+
+// rows of 128 bf16 values, 8-byte aligned with a row stride that keeps them so
 hipError_t launch_quant128_few(int bits, bool prod, const void* X, int64_t ldx, int64_t n, const float* Pi, const float* SPiT, uint32_t* idx,
                                uint32_t* qjl, float* gamma, float* norm, const Codebook& cb, int gs_hi, const Codebook& cb_hi,
                                const void* image, hipStream_t s, int64_t out_first, int64_t out_step) {
