@@ -231,7 +231,10 @@ typedef struct tq_params {
   const float* SPiT;      /* device d*d: S * Pi^T          (tq_quantize_prod)       */
   const float* centroids; /* host, 2^bits_mse floats (tq_build_codebook)            */
   const float* bounds;    /* host, 2^bits_mse - 1 floats                            */
-  void* workspace;        /* device scratch, see tq_workspace_bytes                 */
+  void* workspace;        /* device scratch, see tq_workspace_bytes; calls that share one
+                             must not overlap in time (two streams: two workspaces).
+                             At d = 128 tq_quantize_*, tq_append and tq_dequantize do
+                             not use it where all arrays are 16-byte aligned        */
   size_t workspace_bytes;
   /* split into two instances (see the head of this file); all zero / NULL = one instance */
   int32_t d_hi;               /* 0, or a multiple of 32 below d                         */
@@ -289,9 +292,10 @@ tq_status tq_build_images(const tq_params* p, void* images, void* stream);
  * Read from p->Pi and p->S.  They lie behind the
  * images above: `images` is a buffer of tq_images_bytes(d) + tq_dequant_images_bytes(d) bytes, and
  * TQ_FLAG_DEQUANT_IMAGES in params.flags says that params.images is such a buffer with both parts filled, TQ_FLAG_SIGN_IMAGES
- * that its second part has the digits (a buffer that was sized and filled without them stays valid under the first flag alone).  Without the first flag tq_dequantize makes these tiles in the
- * workspace in every call, where it has room (8 d^2 + 256 bytes, less at d = 128), or takes kernels that do without (at d = 128 above 24576 vectors), the same up to
- * rounding; tq_score likewise for more than 64 queries (tq_score_workspace_bytes counts the room). */
+ * that its second part has the digits (a buffer that was sized and filled without them stays valid under the first flag alone).
+ * Without the first flag tq_dequantize makes these tiles in the workspace in every call, where it has room (8 d^2 + 256 bytes), or takes kernels
+ * that do without, the same up to rounding; at d = 128 it leaves the workspace alone (all arrays 16-byte aligned; params.images null and up to 24576 vectors: the
+ * kernel makes the digits itself, to the same bits; above that, or with images that have none, kernels that do without); tq_score likewise for more than 64 queries (tq_score_workspace_bytes counts the room). */
 size_t tq_dequant_images_bytes(int32_t d);
 tq_status tq_build_dequant_images(const tq_params* p, void* images, void* stream);
 

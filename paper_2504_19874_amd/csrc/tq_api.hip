@@ -573,22 +573,18 @@ tq_status tq_dequantize(const tq_params* p, const uint32_t* idx, const uint32_t*
                                       kappa_of(p->d - p->d_hi), make_codebook(p), p->d_hi / 32,
                                       kappa_of(p->d_hi), make_codebook_hi(p), static_cast<hipStream_t>(stream)));
   }
-  // d = 128, a table that is a sum of signs: digits of Pi^T and S^T from the images, or, for few codes, made here in the
-  // workspace.  That takes 3 us, more where they evict the matrices (us, 3 bits in all / 2 without a sketch, kernels below -> made here -> from
-  // images: 512 codes 9.2 / 6.8 -> 7.0 / 6.4 -> 3.3 / 3.3, 16384 11.1 / 7.7 -> 9.9 / 7.9 -> 5.9 / 4.1, 65536 14.1 / 11.1 -> 15.2 / 13.9 -> 11.3 / 9.0)
+  // d = 128, a table that is a sum of signs: digits of Pi^T and S^T from the images, or, for few codes, made by every workgroup for
+  // itself, which takes 1.2 us a matrix and no memory (us, 3 bits in all / 2 without a sketch, kernels below -> made here -> from images: 8 codes
+  // 8.3 / 5.9 -> 7.2 / 4.6 -> 3.4 / 3.3, 512 9.2 / 6.8 -> 7.3 / 4.8 -> 3.3 / 3.3, 16384 11.0 / 8.2 -> 9.6 / 6.7 -> 5.9 / 4.1, 24576 11.2 / 8.3 -> 10.2 / 7.2 (1 bit
+  // without a sketch: 6.9 -> 7.0); above, more workgroups would make them, and made once in a launch of their own they need memory:
+  // 65536 14.1 / 11.1 that way 15.2 / 13.9, from images 11.3 / 9.0)
   SignCoefs sc;
   if (p->d == 128 && !fp32_mfma_only(p) && (p->bits_mse > 0 || prod) && sign_table(p->bits_mse, make_codebook(p), &sc)) {
     const hipStream_t s = static_cast<hipStream_t>(stream);
     const char* digits = sign_images(p) && aligned16(p->images) ? static_cast<const char*>(p->images) + tq_images_bytes(128) : nullptr;
-    if (p->images == nullptr && n <= kSignOwnDigitRows && p->Pi != nullptr && (!prod || p->S != nullptr)) {
-      Workspace ws{static_cast<char*>(p->workspace), p->workspace_bytes, 0};
-      if (char* const own = static_cast<char*>(ws.take((prod ? 2 : 1) * SIGN128_BYTES)); own != nullptr) {
-        if (launch_sign128_images(p->Pi, prod ? p->S : nullptr, own, s) != hipSuccess) return TQ_ERR_HIP;
-        digits = own;
-      }
-    }
-    if (digits != nullptr)
-      return from_hip(launch_sign128_dequant(p->bits_mse, prod, idx, qjl, gamma, norm, digits, x_out, ldo, n, kappa_of(128), sc, s));
+    const bool own = p->images == nullptr && n <= kSignOwnDigitRows && p->Pi != nullptr && (!prod || p->S != nullptr);
+    if (digits != nullptr || own)
+      return from_hip(launch_sign128_dequant(p->bits_mse, prod, idx, qjl, gamma, norm, digits, p->Pi, p->S, x_out, ldo, n, kappa_of(128), sc, s));
   }
   // large batches at d = 128: decoded codes straight into bf16 MFMA operands, pieces of Pi^T / S^T in LDS
   if (p->d == 128 && n > kBf3DequantRows && !fp32_mfma_only(p) && dequant128_bf3_applicable(p->bits_mse, prod, make_codebook(p), x_out, ldo))

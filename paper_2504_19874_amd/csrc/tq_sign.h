@@ -96,7 +96,9 @@ hipError_t launch_sign_gemm(int bits, bool prod, const void* pi_image, const voi
 // d = 128, both in one launch: image of Pi and its units, image of S and its units
 constexpr size_t SIGN128_BYTES = sign_image_bytes(128) + 128 * 4;  // of one matrix
 hipError_t launch_sign128_images(const float* Pi, const float* S, void* images, hipStream_t s);
+// images null: every workgroup makes its digits itself, the same ones, from Pi and S
 hipError_t launch_sign128_dequant(int bits, bool prod, const uint32_t* idx, const uint32_t* qjl, const float* gamma, const float* norm,
-                                  const void* images, float* out, int64_t ldo, int64_t n, float kappa, const SignCoefs& c, hipStream_t s);
+                                  const void* images, const float* Pi, const float* S, float* out, int64_t ldo, int64_t n, float kappa,
+                                  const SignCoefs& c, hipStream_t s);
 
 }  // namespace tq

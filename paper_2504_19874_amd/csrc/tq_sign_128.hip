@@ -21,15 +21,48 @@ struct Sign128Args {
   const uint32_t* qjl;
   const float* gamma;
   const float* norm;  // nullable
-  const unsigned char* image;
+  const unsigned char* image;  // OWN: not looked at
+  const float* Pi;             // OWN: the matrices themselves
+  const float* S;
   float* out;
   int64_t ldo, n;
   float kappa;
   SignCoefs c;
 };
 
-// DIG: the leading digits that are used
-template <int BITS, bool PROD, int DIG>
+// The largest magnitude of 16 values (NaN stays) and of a column, from those of the 8 parts that its 128 entries are read in
+__device__ __forceinline__ float largest16(const float (&v)[16]) {
+  float mx = 0.f;
+#pragma unroll
+  for (int e = 0; e < 16; ++e) mx = fabsf(v[e]) <= mx ? mx : fabsf(v[e]);
+  return mx;
+}
+__device__ __forceinline__ float largest_part(const float (&max_s)[8][32], int l) {
+  float mx = max_s[0][l];
+#pragma unroll
+  for (int k = 1; k < 8; ++k) {
+    const float o = max_s[k][l];
+    mx = o <= mx || mx != mx ? mx : o;
+  }
+  return mx;
+}
+// half of a lane's 32 values of a digit: words 0..3 of a lane lie together, words 4 and 5 behind those of all lanes
+__device__ __forceinline__ void put_digit(unsigned char* f, int lane, int half, const uint32_t (&w)[3]) {
+  uint32_t* const lo = reinterpret_cast<uint32_t*>(f + lane * 16);
+  if (half == 0) {
+    lo[0] = w[0], lo[1] = w[1], lo[2] = w[2];
+  } else {
+    lo[3] = w[0];
+    *reinterpret_cast<uint2*>(f + 1024 + lane * 8) = make_uint2(w[1], w[2]);
+  }
+}
+// (an entry that is not finite makes its whole column NaN, as it does in a sum of pieces)
+__device__ __forceinline__ float column_unit(float largest) { return largest <= 3.4e38f ? sign_unit(largest) : __builtin_nanf(""); }
+
+// DIG: the leading digits that are used.  OWN: no images; the four wavefronts of a workgroup own the same outputs, each makes a quarter
+// of their digits from the matrices, the same ones as sign128_image_kernel, and they cross through LDS: nothing outside the call's
+// own output is written, so that calls on several streams may share their parameters.
+template <int BITS, bool PROD, int DIG, bool OWN>
 __global__ __launch_bounds__(256, 2) void sign128_dequant_kernel(const Sign128Args a) {
   __shared__ __attribute__((aligned(16))) float row_s[4][2][32];  // by wavefront: the factors of its block's codes
   constexpr int J0 = SIGN_DIGITS - DIG;
@@ -37,24 +70,64 @@ __global__ __launch_bounds__(256, 2) void sign128_dequant_kernel(const Sign128Ar
   typedef uint32_t w2 __attribute__((ext_vector_type(2), aligned(4)));
   typedef uint32_t w4 __attribute__((ext_vector_type(4), aligned(4)));
   const int lane = threadIdx.x & 63, l = lane & 31, h = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const int id = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6)));
-  const int ct = id & 3;
+  const int ct = OWN ? blockIdx.x & 3 : id & 3;
   const int64_t blocks = (a.n + 31) / 32, step = (gridDim.x * (blockDim.x >> 6)) >> 2;
 
   SignFrag frag[MATS][SIGN_DIGITS][2];
+  float pi_unit = 0.f, s_unit = 0.f;  // (minus: see minus_sign_bits)
+  if constexpr (OWN) {
+    __shared__ __attribute__((aligned(16))) unsigned char own_s[MATS][2][DIG][SIGN_FRAG_BYTES];
+    __shared__ float max_s[MATS][8][32];
+    const int st = wave >> 1, half = wave & 1;
+    float v[MATS][16];
 #pragma unroll
-  for (int m = 0; m < MATS; ++m)
+    for (int m = 0; m < MATS; ++m) {
+      const float* const col = (BITS > 0 && m == 0 ? a.Pi : a.S) + 32 * ct + l;
 #pragma unroll
-    for (int j = J0; j < SIGN_DIGITS; ++j)
+      for (int e = 0; e < 16; ++e) v[m][e] = col[(32 * (2 * h + st) + 4 * (e & 7) + 2 * half + (e >> 3)) * 128];
+    }
 #pragma unroll
-      for (int s = 0; s < 2; ++s) {
-        const unsigned char* const f = a.image + (BITS > 0 && m == 0 ? 0 : SIGN128_BYTES) + ((s * 4 + ct) * SIGN_DIGITS + j) * SIGN_FRAG_BYTES;
-        frag[m][j][s].a = *reinterpret_cast<const u32x4*>(f + lane * 16);
-        frag[m][j][s].b = *reinterpret_cast<const uint2*>(f + 1024 + lane * 8);
+    for (int m = 0; m < MATS; ++m) max_s[m][2 * wave + h][l] = largest16(v[m]);
+    __syncthreads();
+#pragma unroll
+    for (int m = 0; m < MATS; ++m) {
+      const float mx = largest_part(max_s[m], l);
+      (BITS > 0 && m == 0 ? pi_unit : s_unit) = -column_unit(mx);
+#pragma unroll
+      for (int j = J0; j < SIGN_DIGITS; ++j) {
+        uint32_t w[3];
+        sign_digit(v[m], sign_unit(mx), j, w);
+        put_digit(own_s[m][st][j - J0], lane, half, w);
       }
-  const unsigned char* const units = a.image + sign_image_bytes(128) + (32 * ct + l) * 4;
-  const float pi_unit = BITS > 0 ? -*reinterpret_cast<const float*>(units) : 0.f;
-  const float s_unit = PROD ? -*reinterpret_cast<const float*>(units + SIGN128_BYTES) : 0.f;  // (minus: see minus_sign_bits)
+    }
+    __syncthreads();
+#pragma unroll
+    for (int m = 0; m < MATS; ++m)
+#pragma unroll
+      for (int j = J0; j < SIGN_DIGITS; ++j)
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+          const unsigned char* const f = own_s[m][s][j - J0];
+          frag[m][j][s].a = *reinterpret_cast<const u32x4*>(f + lane * 16);
+          frag[m][j][s].b = *reinterpret_cast<const uint2*>(f + 1024 + lane * 8);
+        }
+  } else {
+#pragma unroll
+    for (int m = 0; m < MATS; ++m)
+#pragma unroll
+      for (int j = J0; j < SIGN_DIGITS; ++j)
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+          const unsigned char* const f = a.image + (BITS > 0 && m == 0 ? 0 : SIGN128_BYTES) + ((s * 4 + ct) * SIGN_DIGITS + j) * SIGN_FRAG_BYTES;
+          frag[m][j][s].a = *reinterpret_cast<const u32x4*>(f + lane * 16);
+          frag[m][j][s].b = *reinterpret_cast<const uint2*>(f + 1024 + lane * 8);
+        }
+    const unsigned char* const units = a.image + sign_image_bytes(128) + (32 * ct + l) * 4;
+    if constexpr (BITS > 0) pi_unit = -*reinterpret_cast<const float*>(units);
+    if constexpr (PROD) s_unit = -*reinterpret_cast<const float*>(units + SIGN128_BYTES);
+  }
   // the two factors in two parts each: rounded once they would be off for every code alike
   const double alpha_d = a.c.alpha * (double)pi_unit, beta_d = a.c.beta * (double)pi_unit;
   const float alpha = (float)alpha_d, beta = (float)beta_d, alpha_lo = (float)(alpha_d - (double)alpha), beta_lo = (float)(beta_d - (double)beta);
@@ -81,7 +154,7 @@ __global__ __launch_bounds__(256, 2) void sign128_dequant_kernel(const Sign128Ar
   const uint32_t row_bytes = (uint32_t)a.ldo * 4u;
   const uint32_t lane_off = 4u * (uint32_t)h * row_bytes + 4u * (uint32_t)l;
   const uint32_t two = sign_two();
-  int64_t blk = id >> 2;
+  int64_t blk = OWN ? (int64_t)(blockIdx.x >> 2) * 4 + wave : id >> 2;
   if (blk < blocks) load(blk);
   for (; blk < blocks; blk += step) {
     v8i_t sw[2][NPL], sz[2];
@@ -158,53 +231,43 @@ __global__ __launch_bounds__(256, 2) void sign128_dequant_kernel(const Sign128Ar
 }
 
 // A workgroup per matrix, tile of 32 outputs and digit; a wavefront per step and half of a lane's 32 values (3 of a fragment's
-// 6 words).  A call without images makes these first, so it is latency that counts: all loads at once, a few hundred instructions.
+// 6 words).
 __global__ __launch_bounds__(256) void sign128_image_kernel(const float* Pi, const float* S, unsigned char* image) {
   __shared__ float max_s[8][32];
   const int j = blockIdx.x % SIGN_DIGITS, ct = (blockIdx.x / SIGN_DIGITS) & 3, m = blockIdx.x / (4 * SIGN_DIGITS);
   const int tid = threadIdx.x, lane = tid & 63, st = tid >> 7, half = (tid >> 6) & 1, l = lane & 31, h = lane >> 5, g = 2 * h + st;
   const float* const col = (m == 0 ? Pi : S) + 32 * ct + l;
-  float v[16], mx = 0.f;
+  float v[16];
 #pragma unroll
   for (int e = 0; e < 16; ++e) v[e] = col[(32 * g + 4 * (e & 7) + 2 * half + (e >> 3)) * 128];
-#pragma unroll
-  for (int e = 0; e < 16; ++e) mx = fabsf(v[e]) <= mx ? mx : fabsf(v[e]);  // (NaN stays)
-  max_s[2 * (tid >> 6) + h][l] = mx;
+  max_s[2 * (tid >> 6) + h][l] = largest16(v);
   __syncthreads();
-#pragma unroll
-  for (int k = 0; k < 8; ++k) {
-    const float o = max_s[k][l];
-    mx = o <= mx || mx != mx ? mx : o;
-  }
-  const float unit = sign_unit(mx);
+  const float mx = largest_part(max_s, l);
   image += m * SIGN128_BYTES;
-  // (an entry that is not finite makes its whole column NaN, as it does in a sum of pieces)
-  if (j == 0 && tid < 32) reinterpret_cast<float*>(image + sign_image_bytes(128))[32 * ct + l] = mx <= 3.4e38f ? unit : __builtin_nanf("");
+  if (j == 0 && tid < 32) reinterpret_cast<float*>(image + sign_image_bytes(128))[32 * ct + l] = column_unit(mx);
   uint32_t w[3];
-  sign_digit(v, unit, j, w);
-  // words 0..3 of a lane lie together, words 4 and 5 behind those of all lanes
-  unsigned char* const f = image + ((st * 4 + ct) * SIGN_DIGITS + j) * SIGN_FRAG_BYTES;
-  uint32_t* const lo = reinterpret_cast<uint32_t*>(f + lane * 16);
-  if (half == 0) {
-    lo[0] = w[0], lo[1] = w[1], lo[2] = w[2];
-  } else {
-    lo[3] = w[0];
-    *reinterpret_cast<uint2*>(f + 1024 + lane * 8) = make_uint2(w[1], w[2]);
-  }
+  sign_digit(v, sign_unit(mx), j, w);
+  put_digit(image + ((st * 4 + ct) * SIGN_DIGITS + j) * SIGN_FRAG_BYTES, lane, half, w);
 }
 
 // Four of the five digits (20 bits: 2^-18.6 of an entry in the root mean square) where two bf16 pieces of both factors served before
 // (2^-17.8 of a term), all five in place of the fp32 instructions.
+template <int BITS, bool PROD, bool OWN>
+hipError_t launch_digits(const Sign128Args& a, hipStream_t s) {
+  // eight wavefronts per compute unit and four per block of codes; while there are fewer, each is a workgroup (OWN: four that share
+  // their digits, always)
+  const int64_t blocks = (a.n + 31) / 32, cu = device_cu_count();
+  const int waves = !OWN && blocks * 4 <= cu ? 1 : 4;
+  const int64_t groups = OWN ? (blocks + 3) / 4 * 4 : blocks * 4 / waves, most = 8 * cu / waves / 4 * 4;
+  const dim3 grid((unsigned)(groups < most ? groups : most)), block(64 * waves);
+  if (a.n > kBf3DequantRows) hipLaunchKernelGGL((sign128_dequant_kernel<BITS, PROD, 4, OWN>), grid, block, 0, s, a);
+  else hipLaunchKernelGGL((sign128_dequant_kernel<BITS, PROD, 5, OWN>), grid, block, 0, s, a);
+  return hipGetLastError();
+}
+
 template <int BITS, bool PROD>
 hipError_t launch_one(const Sign128Args& a, hipStream_t s) {
-  // eight wavefronts per compute unit and four per block of codes; while there are fewer, each is a workgroup
-  const int64_t blocks = (a.n + 31) / 32, cu = device_cu_count();
-  const int waves = blocks * 4 <= cu ? 1 : 4;
-  const int64_t groups = blocks * 4 / waves, most = 8 * cu / waves;
-  const dim3 grid((unsigned)(groups < most ? groups : most)), block(64 * waves);
-  if (a.n > kBf3DequantRows) hipLaunchKernelGGL((sign128_dequant_kernel<BITS, PROD, 4>), grid, block, 0, s, a);
-  else hipLaunchKernelGGL((sign128_dequant_kernel<BITS, PROD, 5>), grid, block, 0, s, a);
-  return hipGetLastError();
+  return a.image != nullptr ? launch_digits<BITS, PROD, false>(a, s) : launch_digits<BITS, PROD, true>(a, s);
 }
 
 }  // namespace
@@ -228,10 +291,12 @@ hipError_t launch_sign128_images(const float* Pi, const float* S, void* images, 
 }
 
 hipError_t launch_sign128_dequant(int bits, bool prod, const uint32_t* idx, const uint32_t* qjl, const float* gamma, const float* norm,
-                                  const void* images, float* out, int64_t ldo, int64_t n, float kappa, const SignCoefs& c, hipStream_t s) {
+                                  const void* images, const float* Pi, const float* S, float* out, int64_t ldo, int64_t n, float kappa,
+                                  const SignCoefs& c, hipStream_t s) {
   if (n <= 0) return hipSuccess;
+  if (images == nullptr && ((bits > 0 && Pi == nullptr) || (prod && S == nullptr))) return hipErrorInvalidValue;
   if (ldo < 128 || ldo > (1 << 22)) return hipErrorInvalidValue;  // 32 rows are addressed with 32-bit byte offsets
-  const Sign128Args a{idx, qjl, gamma, norm, static_cast<const unsigned char*>(images), out, ldo, n, kappa, c};
+  const Sign128Args a{idx, qjl, gamma, norm, static_cast<const unsigned char*>(images), Pi, S, out, ldo, n, kappa, c};
   switch (bits * 2 + (prod ? 1 : 0)) {
     case 1: return launch_one<0, true>(a, s);
     case 2: return launch_one<1, false>(a, s);

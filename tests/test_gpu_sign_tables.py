@@ -110,3 +110,24 @@ def test_images_without_digits(d, n):
         p.build_images()
     assert p.c.flags & _lib.TQ_FLAG_SIGN_IMAGES
     T.P.check_close(out.cpu().numpy(), reference(parts, True, norm), norm.astype(np.float64)[:, None] / np.sqrt(d), "coordinate")
+
+
+@pytest.mark.parametrize("bits,prod,n", [(0, True, 5), (1, False, 4097), (2, True, 300), (2, False, 16000), (2, True, 24576), (2, True, 40000), (3, True, 1000)])
+def test_workspace_is_left_alone_at_128(bits, prod, n):
+    """Two streams may dequantise with one parameter set at d = 128: without images nothing that they share is written."""
+    p, codes, parts, norm = make(bits, prod, n)
+    out = torch.empty((n, D), device=T.DEV)
+    try:
+        p.drop_images().reserve(n)
+        p.workspace.fill_(0x5a)
+        tq.tq_dequantize(p, *codes, T.dev(norm), out)
+        assert bool((p.workspace == 0x5a).all())
+        keep = p.c.workspace, p.c.workspace_bytes
+        p.c.workspace, p.c.workspace_bytes = 0, 0  # nor needed
+        again = torch.empty_like(out)
+        tq.tq_dequantize(p, *codes, T.dev(norm), again)
+        p.c.workspace, p.c.workspace_bytes = keep
+        assert torch.equal(out, again)
+    finally:
+        p.build_images()
+    T.P.check_close(out.cpu().numpy(), reference(parts, prod, norm), norm.astype(np.float64)[:, None] / np.sqrt(D), "coordinate")
