@@ -298,6 +298,10 @@ tq_status tq_build_images(const tq_params* p, void* images, void* stream);
  * kernel makes the digits itself, to the same bits; above that, or with images that have none, kernels that do without); tq_score likewise for more than 64 queries (tq_score_workspace_bytes counts the room). */
 size_t tq_dequant_images_bytes(int32_t d);
 tq_status tq_build_dequant_images(const tq_params* p, void* images, void* stream);
+/* The same buffer for the calls of one parameter set alone: without the digits that its table (p->centroids) refuses in any case, and without
+ * those of S where there is none (p->S NULL); both flags go with it.  No larger than the buffer above, and not to be used by a set with another table. */
+size_t tq_dequant_images_bytes_for(const tq_params* p);
+tq_status tq_build_dequant_images_for(const tq_params* p, void* images, void* stream);
 
 /* Device scratch large enough for any call with up to n vectors (per call),
  * nq queries and this topk under these params: an upper bound that counts a

@@ -46,6 +46,8 @@ SIGNATURES = {
     "tq_build_images": (C.c_int, [_P, _vp, _vp]),
     "tq_dequant_images_bytes": (C.c_size_t, [_i32]),
     "tq_build_dequant_images": (C.c_int, [_P, _vp, _vp]),
+    "tq_dequant_images_bytes_for": (C.c_size_t, [_P]),
+    "tq_build_dequant_images_for": (C.c_int, [_P, _vp, _vp]),
     "tq_prefix_code_build": (C.c_int, [_i32, _vp, _vp, _vp, C.POINTER(C.c_double)]),
     "tq_entropy_encode": (C.c_int, [_i32, _i32, _vp, _vp, _vp, _i64, _vp, C.c_size_t, C.POINTER(C.c_size_t), _vp]),
     "tq_entropy_decode": (C.c_int, [_i32, _i32, _vp, _vp, C.c_size_t, C.c_uint64, _i64, _vp]),

@@ -133,16 +133,16 @@ class Params:
         self.build_images()
 
     def build_images(self):
-        """The matrices in the form the kernels keep on chip (tq_build_images, tq_build_dequant_images).
+        """The matrices in the form the kernels keep on chip (tq_build_images, tq_build_dequant_images_for).
         `drop_images` goes back to splitting them in every launch (same results)."""
         lib = _lib.load()
-        need, more = int(lib.tq_images_bytes(self.d)), int(lib.tq_dequant_images_bytes(self.d))
+        need, more = int(lib.tq_images_bytes(self.d)), int(lib.tq_dequant_images_bytes_for(C.byref(self.c)))
         if need:
             both = torch.empty(need + more, dtype=torch.uint8, device=self.device)
             self.images = both[:need]  # the dequantiser's lie behind
             _check(lib.tq_build_images(C.byref(self.c), _ptr(self.images), _stream()), "tq_build_images")
             if more:
-                _check(lib.tq_build_dequant_images(C.byref(self.c), _ptr(both), _stream()), "tq_build_dequant_images")
+                _check(lib.tq_build_dequant_images_for(C.byref(self.c), _ptr(both), _stream()), "tq_build_dequant_images_for")
                 self.c.flags |= _lib.TQ_FLAG_DEQUANT_IMAGES | _lib.TQ_FLAG_SIGN_IMAGES
             self.c.images = self.images.data_ptr()
         return self

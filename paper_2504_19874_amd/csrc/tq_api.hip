@@ -81,13 +81,18 @@ Codebook make_codebook_hi(const tq_params* p) {
   return cb;
 }
 
-Codebook make_codebook(const tq_params* p) {
+// (the bounds are left out)
+Codebook make_codebook_of(int bits, const float* centroids) {
   Codebook cb;
   std::memset(&cb, 0, sizeof(cb));
-  cb.bits = p->bits_mse;
-  const int K = 1 << p->bits_mse;
-  for (int k = 0; k < K; ++k) cb.c[k] = p->centroids[k];
-  for (int k = 0; k + 1 < K; ++k) cb.t[k] = p->bounds[k];
+  cb.bits = bits;
+  for (int k = 0; k < 1 << bits; ++k) cb.c[k] = centroids[k];
+  return cb;
+}
+
+Codebook make_codebook(const tq_params* p) {
+  Codebook cb = make_codebook_of(p->bits_mse, p->centroids);
+  for (int k = 0; k + 1 < 1 << p->bits_mse; ++k) cb.t[k] = p->bounds[k];
   return cb;
 }
 
@@ -401,6 +406,43 @@ tq_status quantize_common(const tq_params* p, const void* x, int32_t dtype, int6
   return TQ_OK;
 }
 
+// The digits of tq_dequantize (tq_sign.h) that calls with these parameters can come to multiply: of no matrix, of Pi, of Pi and S
+int digit_matrices(const tq_params* p) {
+  SignCoefs c;
+  if (p->d_hi != 0 || p->bits_mse < 0 || p->bits_mse > 2 || (p->bits_mse == 0 && p->S == nullptr)) return 0;
+  if (p->centroids != nullptr && !sign_table(p->bits_mse, make_codebook_of(p->bits_mse, p->centroids), &c)) return 0;
+  return p->S != nullptr ? 2 : 1;
+}
+
+// behind tq_images_bytes(d); d = 128: digits alone
+size_t dequant_images_bytes(int32_t d, int matrices) {
+  if (d <= 0 || d % 32 != 0 || d > 16384) return 0;
+  if (d == 128) return matrices * SIGN128_BYTES;
+  return 3 * h2_image_bytes(d, d) + 256 + (sign_gemm_images(d) ? matrices * sign_gemm_image_bytes(d) : 0);
+}
+
+tq_status build_dequant_images(const tq_params* p, void* images, int matrices, void* stream) {
+  if (p == nullptr || p->d <= 0) return TQ_ERR_INVALID_ARG;
+  if (dequant_images_bytes(p->d, matrices) == 0) return TQ_OK;
+  if (images == nullptr || p->Pi == nullptr) return TQ_ERR_INVALID_ARG;
+  if (!aligned16(images)) return TQ_ERR_UNSUPPORTED;
+  const hipStream_t s = static_cast<hipStream_t>(stream);
+  const int d = p->d;
+  if (d == 128) return from_hip(launch_sign128_images(p->Pi, p->S, static_cast<char*>(images) + tq_images_bytes(d), s));
+  auto image = [&](int which) { return const_cast<char*>(h2_image(images, d, which)); };
+  if (launch_code_image(p->Pi, d, image(IMG_CODE_PI), h2_image_scale(images, d, IMG_CODE_PI), s) != hipSuccess ||
+      (p->S != nullptr && launch_code_image(p->S, d, image(IMG_CODE_S), h2_image_scale(images, d, IMG_CODE_S), s) != hipSuccess))
+    return TQ_ERR_HIP;
+  if (matrices > 0 && sign_gemm_images(d) &&
+      (launch_sign_gemm_image(p->Pi, d, sign_gemm_image(images, d, 0), s) != hipSuccess ||
+       (p->S != nullptr && launch_sign_gemm_image(p->S, d, sign_gemm_image(images, d, 1), s) != hipSuccess)))
+    return TQ_ERR_HIP;
+  // (an S that is not 16-byte aligned is refused wherever the last one is used)
+  if (p->S != nullptr && aligned16(p->S) && launch_h2_image(p->S, d, d, d, image(IMG_S), h2_image_scale(images, d, IMG_S), s) != hipSuccess)
+    return TQ_ERR_HIP;
+  return TQ_OK;
+}
+
 }  // namespace
 
 extern "C" {
@@ -449,33 +491,12 @@ tq_status tq_build_images(const tq_params* p, void* images, void* stream) {
   return TQ_OK;
 }
 
-size_t tq_dequant_images_bytes(int32_t d) {
-  if (d <= 0 || d % 32 != 0 || d > 16384) return 0;
-  if (d == 128) return 2 * SIGN128_BYTES;
-  return 3 * h2_image_bytes(d, d) + 256 + (sign_gemm_images(d) ? 2 * sign_gemm_image_bytes(d) : 0);
-}
+size_t tq_dequant_images_bytes(int32_t d) { return dequant_images_bytes(d, 2); }
+size_t tq_dequant_images_bytes_for(const tq_params* p) { return p == nullptr ? 0 : dequant_images_bytes(p->d, digit_matrices(p)); }
 
-tq_status tq_build_dequant_images(const tq_params* p, void* images, void* stream) {
-  if (p == nullptr || p->d <= 0) return TQ_ERR_INVALID_ARG;
-  if (tq_dequant_images_bytes(p->d) == 0) return TQ_OK;
-  if (images == nullptr || p->Pi == nullptr) return TQ_ERR_INVALID_ARG;
-  if (!aligned16(images)) return TQ_ERR_UNSUPPORTED;
-  const hipStream_t s = static_cast<hipStream_t>(stream);
-  const int d = p->d;
-  if (d == 128) {
-    return from_hip(launch_sign128_images(p->Pi, p->S, static_cast<char*>(images) + tq_images_bytes(d), s));
-  }
-  auto image = [&](int which) { return const_cast<char*>(h2_image(images, d, which)); };
-  if (launch_code_image(p->Pi, d, image(IMG_CODE_PI), h2_image_scale(images, d, IMG_CODE_PI), s) != hipSuccess ||
-      (p->S != nullptr && launch_code_image(p->S, d, image(IMG_CODE_S), h2_image_scale(images, d, IMG_CODE_S), s) != hipSuccess))
-    return TQ_ERR_HIP;
-  if (sign_gemm_images(d) && (launch_sign_gemm_image(p->Pi, d, sign_gemm_image(images, d, 0), s) != hipSuccess ||
-                              (p->S != nullptr && launch_sign_gemm_image(p->S, d, sign_gemm_image(images, d, 1), s) != hipSuccess)))
-    return TQ_ERR_HIP;
-  // (an S that is not 16-byte aligned is refused wherever the last one is used)
-  if (p->S != nullptr && aligned16(p->S) && launch_h2_image(p->S, d, d, d, image(IMG_S), h2_image_scale(images, d, IMG_S), s) != hipSuccess)
-    return TQ_ERR_HIP;
-  return TQ_OK;
+tq_status tq_build_dequant_images(const tq_params* p, void* images, void* stream) { return build_dequant_images(p, images, 2, stream); }
+tq_status tq_build_dequant_images_for(const tq_params* p, void* images, void* stream) {
+  return build_dequant_images(p, images, p == nullptr ? 0 : digit_matrices(p), stream);
 }
 
 tq_status tq_derive_params(int32_t d, const float* Pi, const float* S, float* PiT, float* ST,
@@ -581,7 +602,7 @@ tq_status tq_dequantize(const tq_params* p, const uint32_t* idx, const uint32_t*
   SignCoefs sc;
   if (p->d == 128 && !fp32_mfma_only(p) && (p->bits_mse > 0 || prod) && sign_table(p->bits_mse, make_codebook(p), &sc)) {
     const hipStream_t s = static_cast<hipStream_t>(stream);
-    const char* digits = sign_images(p) && aligned16(p->images) ? static_cast<const char*>(p->images) + tq_images_bytes(128) : nullptr;
+    const char* digits = sign_images(p) && aligned16(p->images) && (!prod || p->S != nullptr) ? static_cast<const char*>(p->images) + tq_images_bytes(128) : nullptr;
     const bool own = p->images == nullptr && n <= kSignOwnDigitRows && p->Pi != nullptr && (!prod || p->S != nullptr);
     if (digits != nullptr || own)
       return from_hip(launch_sign128_dequant(p->bits_mse, prod, idx, qjl, gamma, norm, digits, p->Pi, p->S, x_out, ldo, n, kappa_of(128), sc, s));

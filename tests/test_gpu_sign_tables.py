@@ -131,3 +131,39 @@ def test_workspace_is_left_alone_at_128(bits, prod, n):
     finally:
         p.build_images()
     T.P.check_close(out.cpu().numpy(), reference(parts, prod, norm), norm.astype(np.float64)[:, None] / np.sqrt(D), "coordinate")
+
+
+@pytest.mark.parametrize("d,bits,prod,matrices", [(256, 4, False, 0), (256, 3, True, 0), (256, 2, False, 1), (256, 1, True, 2), (128, 4, False, 0), (128, 2, False, 1),
+                                                  (128, 2, True, 2), (320, 2, True, 0)])
+def test_digits_only_where_a_call_can_take_them(d, bits, prod, matrices):
+    """A parameter set's images hold the digits of the matrices that its own table lets tq_dequantize multiply, and of no others."""
+    from paper_2504_19874_amd import _lib
+    p = T.setup(d, bits, prod)[0]
+    one = (d // 64) * (d // 32) * 5 * 1536 + 512 if d == 128 else 4 * d * d
+    most = int(_lib.load().tq_dequant_images_bytes(d)) - (2 * one if d % 128 == 0 else 0)
+    assert p.images.untyped_storage().nbytes() == int(tq.tq_images_bytes(d)) + most + matrices * one
+
+
+def test_images_for_any_table():
+    """tq_build_dequant_images fills the whole buffer, whatever the table of the parameter set it is called with: the images are those of
+    the matrices, and a set with another table may use them."""
+    import ctypes
+    from paper_2504_19874_amd import _lib
+    lib = _lib.load()
+    for d in (128, 256):
+        four, codes, parts, norm = make(2, True, 3000, d)
+        want, got = torch.empty((3000, d), device=T.DEV), torch.empty((3000, d), device=T.DEV)
+        tq.tq_dequantize(four, *codes, T.dev(norm), want)
+        other = T.setup(d, 4, True)[0]  # (the same Pi and S)
+        size = int(tq.tq_images_bytes(d)) + int(lib.tq_dequant_images_bytes(d))
+        whole = torch.zeros(size, dtype=torch.uint8, device=T.DEV)
+        stream = ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+        assert lib.tq_build_images(ctypes.byref(other.c), ctypes.c_void_p(whole.data_ptr()), stream) == 0
+        assert lib.tq_build_dequant_images(ctypes.byref(other.c), ctypes.c_void_p(whole.data_ptr()), stream) == 0
+        keep = four.c.images
+        try:
+            four.c.images = whole.data_ptr()
+            tq.tq_dequantize(four, *codes, T.dev(norm), got)
+        finally:
+            four.c.images = keep
+        assert torch.equal(got, want)
