@@ -532,11 +532,10 @@ size_t tq_workspace_bytes(const tq_params* p, int64_t n, int64_t nq, int32_t top
   if (p == nullptr || p->d <= 0 || n < 0 || nq < 0) return 0;
   const size_t d = (size_t)p->d;
   const size_t rows = (size_t)(n < kChunkRows / 2 ? n : kChunkRows / 2);
-  // the quantiser's pieces of the vectors and of the residual, two factors and the partial residual norms per vector
+  // the quantiser's pieces of the vectors and of the residual, two factors and the partial residual norms per vector (a handful of
+  // long vectors instead keeps the fp32 residual alone)
   size_t bytes = round_up(rows * (2 * d * sizeof(float) + 8 + (d + 63) / 64 * 4), 256) + 4096;
   if (n > 0 && p->images == nullptr) bytes += round_up(h2_own_images_bytes(p->d, p->S != nullptr), 256);
-  // a handful of long vectors: their rotated coordinates beside the residual (the matrix-vector route)
-  bytes += round_up((size_t)(n < kRowsQuantMax ? n : kRowsQuantMax) * d * sizeof(float), 256);
   bytes += 2 * round_up((size_t)nq * d * sizeof(float), 256);      // rotated / sketched queries
   bytes += round_up(score_i8_workspace_bytes(p->d, nq), 256);      // or their int8 digit images
   if (topk > 0) bytes += round_up((size_t)nq * (size_t)(n + 3) * sizeof(float), 256);  // scores when not returned
