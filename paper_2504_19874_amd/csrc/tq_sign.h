@@ -30,6 +30,9 @@ bool sign_table(int bits, const Codebook& cb, SignCoefs* c);
 
 __host__ __device__ constexpr size_t sign_image_bytes(int d) { return (size_t)(d / 64) * (d / 32) * SIGN_DIGITS * SIGN_FRAG_BYTES; }
 
+// the larger of two magnitudes, where NaN stays
+__device__ __forceinline__ float sign_larger(float m, float mx) { return m <= mx || mx != mx ? mx : m; }
+
 // What one unit of the last digit stands for in an output's column, from the column's largest magnitude: 16.5 32^4 units
 __device__ __forceinline__ float sign_unit(float largest) {
   const float u = largest * (1.00001f / 17301504.f);

@@ -30,20 +30,17 @@ struct Sign128Args {
   SignCoefs c;
 };
 
-// The largest magnitude of 16 values (NaN stays) and of a column, from those of the 8 parts that its 128 entries are read in
+// The largest magnitude of 16 values and of a column, from those of the 8 parts that its 128 entries are read in
 __device__ __forceinline__ float largest16(const float (&v)[16]) {
   float mx = 0.f;
 #pragma unroll
-  for (int e = 0; e < 16; ++e) mx = fabsf(v[e]) <= mx ? mx : fabsf(v[e]);
+  for (int e = 0; e < 16; ++e) mx = sign_larger(fabsf(v[e]), mx);
   return mx;
 }
 __device__ __forceinline__ float largest_part(const float (&max_s)[8][32], int l) {
   float mx = max_s[0][l];
 #pragma unroll
-  for (int k = 1; k < 8; ++k) {
-    const float o = max_s[k][l];
-    mx = o <= mx || mx != mx ? mx : o;
-  }
+  for (int k = 1; k < 8; ++k) mx = sign_larger(max_s[k][l], mx);
   return mx;
 }
 // half of a lane's 32 values of a digit: words 0..3 of a lane lie together, words 4 and 5 behind those of all lanes

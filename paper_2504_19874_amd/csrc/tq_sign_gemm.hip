@@ -270,8 +270,6 @@ hipError_t launch_one(const SignGemmArgs& a, hipStream_t s) {
   return launch_tile<BITS, PROD, 2, 4>(a, s);
 }
 
-__device__ __forceinline__ float larger(float m, float mx) { return m <= mx || mx != mx ? mx : m; }  // (NaN stays)
-
 // a workgroup for 64 rows and two tiles
 __global__ __launch_bounds__(256) void sign_gemm_largest_kernel(const float* __restrict__ W, const int d, unsigned char* image) {
   __shared__ float max_s[4][64];
@@ -281,12 +279,12 @@ __global__ __launch_bounds__(256) void sign_gemm_largest_kernel(const float* __r
 #pragma unroll
   for (int j = 0; j < 16; ++j) v[j] = fabsf(at[(int64_t)j * d]);
 #pragma unroll
-  for (int j = 0; j < 16; ++j) mx = larger(v[j], mx);
+  for (int j = 0; j < 16; ++j) mx = sign_larger(v[j], mx);
   max_s[part][c] = mx;
   __syncthreads();
   if (part != 0) return;
 #pragma unroll
-  for (int k = 1; k < 4; ++k) mx = larger(max_s[k][c], mx);
+  for (int k = 1; k < 4; ++k) mx = sign_larger(max_s[k][c], mx);
   reinterpret_cast<float*>(image + ((size_t)st * (d >> 5) + 2 * pair + (c & 1)) * SIGN_STEP_BYTES + LARGEST)[c >> 1] = mx;
 }
 
@@ -302,7 +300,7 @@ __global__ __launch_bounds__(64 * SIGN_DIGITS) void sign_gemm_image_kernel(const
 #pragma unroll
   for (int e = 0; e < 32; ++e) v[e] = col[(int64_t)(32 * g + 4 * (e & 7) + (e >> 3)) * d];
 #pragma unroll 4
-  for (int k = 0; k < S; ++k) mx = larger(reinterpret_cast<const float*>(tile + k * step_bytes + LARGEST)[l], mx);
+  for (int k = 0; k < S; ++k) mx = sign_larger(reinterpret_cast<const float*>(tile + k * step_bytes + LARGEST)[l], mx);
   int e2;
   (void)frexpf(fmaxf(sign_unit(mx), 1e-20f), &e2);  // the unit 2^e2: the digits below are exact in fp32
   // (an entry that is not finite makes its whole output NaN, as it does in a sum of pieces)

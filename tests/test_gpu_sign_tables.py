@@ -167,3 +167,71 @@ def test_images_for_any_table():
         finally:
             four.c.images = keep
         assert torch.equal(got, want)
+
+
+def run(p, codes, norm, n, d):
+    out = torch.empty((n, d), device=T.DEV)
+    tq.tq_dequantize(p, *codes, T.dev(norm), out)
+    return out.cpu().numpy()
+
+
+@pytest.mark.parametrize("d,bits,prod,n", [(128, 0, True, 70), (128, 2, True, 300), (128, 1, False, 8200), (128, 2, True, 9000), (256, 1, True, 65), (640, 2, True, 300),
+                                           (256, 0, True, 5000)])
+@pytest.mark.parametrize("images", [True, False])
+def test_factors_that_are_not_finite(d, bits, prod, n, images):
+    """A code's own coordinates are not finite then, and nothing else is touched by it."""
+    p, codes, parts, norm = make(bits, prod, n, d)
+    try:
+        if not images:
+            p.drop_images().reserve(n)
+        want = run(p, codes, norm, n, d)
+        bad = np.zeros(n, dtype=bool)
+        norm = norm.copy()
+        for k, v in enumerate((np.inf, np.nan, -np.inf)):
+            norm[7 + 20 * k] = v
+            bad[7 + 20 * k] = True
+            if prod:
+                codes[2][5 + 20 * k] = float(v)
+                bad[5 + 20 * k] = True
+        got = run(p, codes, norm, n, d)
+    finally:
+        p.build_images()
+    assert np.isfinite(want).all() and not np.isfinite(got[bad]).any()
+    assert np.array_equal(got[~bad], want[~bad])
+
+
+@pytest.mark.parametrize("d,bits,prod,n", [(128, 2, True, 300), (128, 0, True, 40), (128, 1, False, 9000), (256, 2, True, 700), (384, 1, True, 65), (256, 0, True, 100)])
+@pytest.mark.parametrize("value", [np.inf, -np.inf, np.nan, 0.0])
+@pytest.mark.parametrize("images", [True, False])
+def test_columns_that_are_not_finite_or_zero(d, bits, prod, n, value, images):
+    """An entry of Pi or S that is not finite makes that output of every code not finite, and a column of zeros leaves it to the other
+    matrix; the other outputs do not change."""
+    p0, codes, (idx, z, gamma, Pi, S, c), norm = make(bits, prod, n, d)
+    want = run(p0, codes, norm, n, d)
+    Pi, S = Pi.copy(), S.copy() if prod else None
+    hit = np.zeros(d, dtype=bool)
+    for M, cols in ((Pi if bits else None, (3, 70)), (S, (9, 70))):
+        if M is not None:
+            for k in cols:
+                if value == 0.0:
+                    M[:, k] = 0.0
+                else:
+                    M[(5 * k) % d, k] = value
+                hit[k] = True
+    p = tq.Params(d, bits, torch.from_numpy(Pi), torch.from_numpy(S) if prod else None, p0.centroids, p0.bounds)
+    if not images:
+        p.drop_images().reserve(n)
+    got = run(p, codes, norm, n, d)
+    assert np.array_equal(got[:, ~hit], want[:, ~hit])
+    if value != 0.0:
+        assert not np.isfinite(got[:, hit]).any()
+        return
+    exact = reference((idx, z, gamma, Pi, S, c), prod, norm)
+    assert np.all(got[:, 70] == 0.0)
+    close(got[:, hit], exact[:, hit], norm, n)
+
+
+@pytest.mark.parametrize("bits,prod,n", [(2, True, 70), (1, True, 513), (0, True, 100), (2, False, 400)])
+def test_the_longest_stored_vectors(bits, prod, n):
+    """d = 3072, where an entry of S is 55 times one of Pi and the sums of the two are joined in units of the one."""
+    test_long_codes(3072, bits, prod, n)
