@@ -56,8 +56,11 @@
  * (22 bits: what is left out is below 2^-22 of the value, 2^-24.5 in the root
  * mean square, or below 2^-39 of the row's largest value), or base-128 digits
  * of a fixed-point value with 2^-19 (d = 128) or 2^-20 relative spacing:
- *   quantise, rotation, more than 8192 vectors at d = 128: two fp16 pieces of Pi
- *     and of an fp32 x (a bf16 x is one exact piece).
+ *   quantise, rotation at d = 128, more than 8192 vectors, and bf16 vectors in any number:
+ *     two fp16 pieces of Pi and of an fp32 x (a bf16 x is one exact piece).  Up to 8192 bf16
+ *     vectors against the fp32 instructions, of 7.9e8 coordinates at 4 bits 224 on the other
+ *     side of a boundary against 320; gamma at 3 + 1 bits off by 0.9e-7 against 1.1e-7, signs
+ *     0.24 of 10^6 against 0.29.
  *   quantise, rotation, every d other than 128: two fp16 pieces of Pi where
  *     d >= 512 or n <= 16384 and params.workspace holds the pieces of the vectors
  *     (tq_workspace_bytes counts them; codebooks of 3 and 4 bits have to be symmetric
@@ -89,10 +92,14 @@
  *     a centroid and of an entry of Pi^T or S^T, a sign as one exact piece (error
  *     below 4e-5 of a coordinate's typical size);
  *   dequantise, a table of up to two bits that is symmetric about zero: sums of signs
- *     times the 25 leading bits of an entry (of its column's largest), where the result is
- *     closer than that of the fp32 instructions; at d = 128 (with the images of
- *     tq_build_dequant_images or up to 24576 vectors) 20 bits above 8192 vectors; at d = 256,
- *     384, 512, ... from 2^20 coordinates on for two bits without a sketch, always for the rest;
+ *     times the 25 leading bits of an entry (of its column's largest), at d = 128 (with the
+ *     images of tq_build_dequant_images, or without any up to 24576 vectors) and above 8192
+ *     vectors 20 of them; at d = 256, 384, 512, ... from 2^20 coordinates on for two bits
+ *     without a sketch, always for the rest.  Error in units of a coordinate's root mean
+ *     square, of the fp32 instructions -> of these: d = 128 0.9 - 1.2e-7 -> 0.8e-7 (above 8192
+ *     vectors 1.55e-6, where two bf16 pieces are 2.5 - 3.9e-6), d = 768 5 - 8e-7 -> 1.3 -
+ *     1.7e-7, d = 3072 1.0 - 1.6e-6 -> 2.2 - 3.1e-7.  An entry of Pi or S that is not finite
+ *     makes that output of every vector NaN;
  *   scoring, Pi q and S q: plain fp32 for up to 64 queries in all; more of them at d
  *     other than 128 from two fp16 pieces of the query and of Pi and S each, where the
  *     workspace has the room that tq_score_workspace_bytes counts (0.62 of the
@@ -104,7 +111,7 @@
  *   scoring, few queries: fixed-point digits (up to 32 per group at d <= 1024, up to 16
  *     per group at d <= 4096 (64 in all beyond d = 512), d a multiple of 128,
  *     codebook symmetric about zero).
- * Smaller batches of fp32 vectors, and of codes, at d = 128 run on the fp32 matrix
+ * Smaller batches of fp32 vectors, and of codes of other tables, at d = 128 run on the fp32 matrix
  * instructions.  All paths meet
  * the same tolerances (indices equal to an fp32 evaluation except within 1e-5 of a
  * cell boundary; values and scores within 1e-4 relative).  With TQ_FLAG_FP32_MFMA

@@ -1,0 +1,131 @@
+"""What the arithmetic on pieces and digits leaves of fp32, against 64-bit sums on the GPU: no further from them than the fp32 matrix
+instructions where these served before, and within twice the errors that the header states."""
+import math
+
+import numpy as np
+import pytest
+import torch
+
+from tests import test_gpu_parity as T
+
+pytestmark = pytest.mark.gpu
+
+tq = pytest.importorskip("paper_2504_19874_amd")
+
+D = 128
+
+
+def unpack(words, bits, d):
+    w = words.view(words.shape[0], d // 32, bits, 1)
+    b = (w >> torch.arange(32, device=T.DEV, dtype=torch.int32)) & 1
+    return (b << torch.arange(bits, device=T.DEV, dtype=torch.int32).view(1, 1, bits, 1)).sum(2).view(words.shape[0], d)
+
+
+def table(a):
+    return torch.tensor(np.asarray(a).reshape(-1), device=T.DEV, dtype=torch.float64)
+
+
+# ------------------------------------------------------------------ quantisation of few bf16 vectors
+
+
+def rows(g, kind, n):
+    x = torch.randn(n, D, generator=g, device=T.DEV)
+    if kind == "outliers":
+        x[:, torch.randperm(D, generator=g, device=T.DEV)[:4]] *= 20
+    if kind == "centres":
+        c = torch.randn(256, D, generator=g, device=T.DEV)
+        x = 0.3 * x + c[torch.randint(256, (n,), generator=g, device=T.DEV)]
+    return x.to(torch.bfloat16)
+
+
+def errors(p, x, bits, prod, Pi, W, c, t):
+    """Wrong indices and signs, and the summed squares of gamma's and the norm's relative errors."""
+    n = x.shape[0]
+    idx = torch.zeros((n, max(1, p.idx_words)), dtype=torch.int32, device=T.DEV)
+    qjl = torch.zeros((n, p.qjl_words), dtype=torch.int32, device=T.DEV)
+    gamma, norm = torch.zeros(n, device=T.DEV), torch.zeros(n, device=T.DEV)
+    if prod:
+        tq.tq_quantize_prod(p, x, idx, qjl, gamma, norm)
+    else:
+        tq.tq_quantize_mse(p, x, idx, norm)
+    xd = x.double()
+    nu = xd.norm(dim=1)
+    y = (xd / nu[:, None]) @ Pi.T
+    out = [0.0, 0.0, 0.0, float(((norm.double() - nu) / nu).pow(2).sum())]
+    got = unpack(idx, bits, D)
+    out[0] = float((got != torch.bucketize(y, t, right=True)).sum())
+    if prod:
+        e = y - c[got.long()]
+        size = e.norm(dim=1)
+        out[1] = float((unpack(qjl, 1, D) != (e @ W.T >= 0)).sum())
+        out[2] = float(((gamma.double() - size) / size).pow(2).sum())
+    return np.array(out)
+
+
+@pytest.mark.parametrize("kind", ["outliers", "normal", "centres"])
+@pytest.mark.parametrize("bits,prod,n", [(4, False, 8192), (3, True, 8192), (2, True, 512), (1, True, 4096)])
+def test_few_vectors_no_further_off_than_the_fp32_instructions(kind, bits, prod, n):
+    """Two fp16 pieces hold 22 bits of an entry of Pi, but a sum meets a quarter of the roundings."""
+    p, Pi, S, c32, t32 = T.setup(D, bits, prod)
+    Pi = T.dev(Pi).double()
+    W = T.dev(S).double() @ Pi.T if prod else None
+    g = torch.Generator(device=T.DEV)
+    g.manual_seed(bits + n)
+    pieces, fp32 = np.zeros(4), np.zeros(4)
+    for _ in range((1 << 19) // n):  # 6.7e7 coordinates
+        x = rows(g, kind, n)
+        try:
+            pieces += errors(p, x, bits, prod, Pi, W, table(c32), table(t32))
+            p.fp32_mfma = True
+            fp32 += errors(p, x, bits, prod, Pi, W, table(c32), table(t32))
+        finally:
+            p.fp32_mfma = False
+    # counts of rare events: two standard deviations of their own number
+    assert np.all(pieces[:2] <= fp32[:2] + 2 * np.sqrt(fp32[:2] + 1)), (pieces, fp32)
+    assert np.all(pieces[2:] <= 1.02 * fp32[2:]), (pieces, fp32)
+
+
+# ------------------------------------------------------------------ dequantisation of sums of signs
+
+
+def restore_error(p, d, bits, prod, n, Pi, S, c32):
+    """Error in units of a coordinate's root mean square: (root mean square, largest)."""
+    g = torch.Generator(device=T.DEV)
+    g.manual_seed(n + bits)
+    word = lambda k: torch.empty((n, k), dtype=torch.int32, device=T.DEV).random_(-2**31, 2**31 - 1, generator=g)  # noqa: E731
+    idx, qjl = word(max(1, p.idx_words)), word(p.qjl_words)
+    gamma, norm = 0.2 + 0.3 * torch.rand(n, generator=g, device=T.DEV), 0.5 + torch.rand(n, generator=g, device=T.DEV)
+    out = torch.empty((n, d), device=T.DEV)
+    p.reserve(n)
+    tq.tq_dequantize(p, idx if bits else None, qjl if prod else None, gamma if prod else None, norm, out)
+    want = table(c32)[unpack(idx, bits, d).long()] @ Pi if bits else 0.0
+    if prod:
+        want = want + math.sqrt(math.pi / 2) / d * gamma.double()[:, None] * ((2.0 * unpack(qjl, 1, d) - 1).double() @ S)
+    e = (out.double() / norm.double()[:, None] - want) / want.pow(2).mean().sqrt()
+    return float(e.pow(2).mean().sqrt()), float(e.abs().max())
+
+
+# (d, codes): the error that is stated for it, root mean square
+STATED = {(128, 8): 0.8e-7, (128, 8192): 0.8e-7, (128, 8193): 1.55e-6, (128, 60000): 1.55e-6, (256, 5000): 1.2e-7, (768, 3000): 1.7e-7,
+          (1536, 700): 2.2e-7, (3072, 400): 3.1e-7}
+
+
+@pytest.mark.parametrize("bits,prod", [(0, True), (1, False), (1, True), (2, False), (2, True)])
+@pytest.mark.parametrize("d,n", list(STATED))
+def test_signs_against_digits(d, n, bits, prod):
+    from paper_2504_19874_amd import _lib
+    p, Pi, S, c32, _ = T.setup(d, bits, prod)
+    Pi, S = T.dev(Pi).double(), T.dev(S).double() if prod else None
+    rms, most = restore_error(p, d, bits, prod, n, Pi, S, c32)
+    # errors of a few million coordinates, none of them an outlier: up to about 15 times their root mean square (where a code's
+    # kinds of sign add up to a long vector)
+    assert rms <= 2 * STATED[d, n] and most <= 30 * STATED[d, n], (rms, most)
+    flags = p.c.flags
+    try:
+        p.c.flags = flags & ~_lib.TQ_FLAG_SIGN_IMAGES  # the kernels of the other tables
+        before = restore_error(p, d, bits, prod, n, Pi, S, c32)
+        p.c.flags = flags | _lib.TQ_FLAG_FP32_MFMA
+        fp32 = restore_error(p, d, bits, prod, n, Pi, S, c32)
+    finally:
+        p.c.flags = flags
+    assert rms <= before[0] and (rms <= fp32[0] or (d == 128 and n > 8192)), (rms, before, fp32)
