@@ -16,7 +16,9 @@ that takes the largest share of the step.  A contraction that the library
 feeds to the 16-bit matrix cores as pieces of its fp32 factors is priced
 against their peak on its algorithmic flops (`frac`); the share of the
 peak that the executed piece products reach (`executed_frac`) and the
-fp32-equivalent rate are given beside it, and `fp32_mfma_reference` times the
+fp32-equivalent rate are given beside it.  Dequantisation that multiplies signs
+and fp6 digits is priced against the peak of that format by what it executes,
+or against HBM where its bytes take longer there.  `fp32_mfma_reference` times the
 same calls with TQ_FLAG_FP32_MFMA (every contraction on fp32 MFMA).
 `d1536` is the same step on the d = 1536 configuration (C4: 10^6 database
 vectors, 1000 queries, top-10), a few timed steps after the headline region.
@@ -37,6 +39,7 @@ if ROOT not in sys.path:
 
 PEAK_FP32_MFMA_TFLOPS = 157.3
 PEAK_BF16_MFMA_TFLOPS = 2500.0
+PEAK_FP6_MFMA_TFLOPS = 10000.0  # fp4 and fp6 operands
 PEAK_HBM_GBS = 8000.0
 
 
@@ -106,17 +109,28 @@ def few_queries(cfg):
     return cfg.nq <= 64 and cfg.d <= 4096 and cfg.q_per_group <= (32 if cfg.d <= 1024 else 16)
 
 
+def sign_digits(cfg):
+    """fp6 digits of an entry of Pi^T and S^T that tq_dequantize multiplies with the signs of the codes' planes; 0 where the table is no
+    sum of signs and it multiplies pieces of centroids."""
+    n, prod, bits = cfg.n * cfg.n_groups, cfg.kind == "prod", cfg.bits_mse
+    if bits > 2 or cfg.d_hi or cfg.d % 128 or not (prod or bits):
+        return 0
+    if cfg.d == 128:
+        return 5 if n <= 8192 else 4
+    return 5 if prod or bits != 2 or n * cfg.d >= 1 << 20 else 0
+
+
 def routing(cfg, call: str):
     """How the library carries out the fp32 contractions of `call` on the 16-bit matrix cores: (products per fp32 product of
     the rotation or centroid part, the same of the sketch or sign part, in words), or None where the call runs on the fp32
-    matrix instructions or on digits.  (Dequantisation of tables that are sums of signs runs on fp6 digits; it is priced as the pieces that
-    they took the place of.)  Mirrors the library's choice for one instance and the workspace that it asks for."""
+    matrix instructions or on digits.  (Dequantisation on digits has the numbers of the pieces that these take the place of; what it
+    executes is in `call_roofline`.)  Mirrors the library's choice for one instance and the workspace that it asks for."""
     n, prod, bits = cfg.n * cfg.n_groups, cfg.kind == "prod", cfg.bits_mse
     bf16 = cfg.in_dtype == "bf16"
     # Alg. 2 of fp32 vectors whose residual is small keeps the rotation on the fp32 instructions
     small_residual = prod and not bf16 and (1.0, 0.60, 0.342, 0.183, 0.097)[bits] * cfg.d ** 0.5 < 2.0
     if call == "quantize":
-        if small_residual or (cfg.d == 128 and n <= 8192):
+        if small_residual or (cfg.d == 128 and n <= 8192 and not bf16):
             return None
         if cfg.d == 128:
             return 2 if bf16 else 3, 3, (f"fp16 MFMA, {'a bf16 vector as one exact piece' if bf16 else 'two pieces of x'} against two "
@@ -132,9 +146,9 @@ def routing(cfg, call: str):
         if cfg.d == 128 and n <= 8192:
             return None
         kind = "bf16" if cfg.d == 128 else "fp16"
-        if bits <= 2 and cfg.d % 128 == 0 and (prod or bits != 2 or n * cfg.d >= 1 << 20):
+        if sign_digits(cfg):
             return 2 if bits == 1 else 3, 2, (f"scaled-format MFMA, signs of the planes as fp4 against {'four' if cfg.d == 128 else 'five'} fp6 "
-                                              f"digits of Pi^T and S^T (priced as {kind} pieces)")
+                                              f"digits of Pi^T and S^T (in place of {kind} pieces)")
         return 2 if bits == 1 else 3, 2, f"{kind} MFMA, two pieces of a centroid (a sign is one) against two of Pi^T and S^T"
     if few_queries(cfg) or (cfg.q_per_group <= 32 and cfg.d % 128 == 0 and cfg.d <= 1024):
         return None
@@ -145,8 +159,8 @@ def routing(cfg, call: str):
 
 
 def piece_products(cfg, call: str):
-    """Piece products that the matrix cores execute per fp32 product of `call`, over both of its parts; 0 where it does not
-    run on pieces."""
+    """Piece products that the matrix cores execute per fp32 product of `call`, over both of its parts (dequantisation on digits: of the
+    pieces in whose place they are); 0 where it does not run on pieces."""
     r = routing(cfg, call)
     if r is None:
         return 0.0
@@ -166,6 +180,8 @@ def arithmetic(cfg):
         elif call == "score" and few_queries(cfg):
             unit, digit = (19, "fp8 digits (base 32)") if cfg.d == 128 else (20, "fp6 digits (base 49)")
             out[call] = f"scaled-format MFMA on exact {digit} of rotated queries in 2^-{unit} fixed point, fp32 combination"
+        elif call == "dequantize" and sign_digits(cfg):
+            out[call] = "signs of the planes as fp4 against five fp6 digits of Pi^T and S^T (25 bits); fp32 accumulation"
         else:
             out[call] = "fp32"
     return out
@@ -254,8 +270,21 @@ def call_roofline(cfg, name: str, ms: float):
     few_q = name == "score" and not pieces  # few queries per code: integer digits or fp32 lanes, graded against HBM
     peak_tf = PEAK_BF16_MFMA_TFLOPS if pieces else PEAK_FP32_MFMA_TFLOPS
     t_mfma, t_hbm = flops / (peak_tf * 1e12), nbytes / (PEAK_HBM_GBS * 1e9)
+    digits = sign_digits(cfg) if name == "dequantize" else 0
     kernel = f"tq_{name}" + ("_prod" if name == "quantize" and cfg.kind == "prod" else "_mse" if name == "quantize" else "")
-    if few_q or t_hbm > t_mfma and not pieces:
+    if digits:
+        # every plane and the sketch are signs: one product of a sign and a digit each, 2 n d^2 operations
+        executed = 2.0 * cfg.n * cfg.n_groups * cfg.d ** 2 * (cfg.bits_mse + (cfg.kind == "prod")) * digits
+        t_mfma = executed / (PEAK_FP6_MFMA_TFLOPS * 1e12)
+        if t_hbm > t_mfma:
+            r = {"bound": "hbm", "achieved": nbytes / sec / 1e9, "peak": PEAK_HBM_GBS, "unit": "GB/s",
+                 "frac": nbytes / sec / 1e9 / PEAK_HBM_GBS}
+        else:
+            r = {"bound": "mfma", "achieved": flops / sec / 1e12, "peak": PEAK_FP6_MFMA_TFLOPS, "unit": "TFLOP/s",
+                 "frac": flops / sec / 1e12 / PEAK_FP6_MFMA_TFLOPS, "hbm_frac": nbytes / sec / 1e9 / PEAK_HBM_GBS}
+        r.update({"dtype": "signs against fp6 digits of fp32 entries, fp32 accumulate", "digits": digits,
+                  "executed_frac": executed / sec / 1e12 / PEAK_FP6_MFMA_TFLOPS, "of_fp32_mfma_peak": flops / sec / 1e12 / PEAK_FP32_MFMA_TFLOPS})
+    elif few_q or t_hbm > t_mfma and not pieces:
         r = {"bound": "hbm", "achieved": nbytes / sec / 1e9, "peak": PEAK_HBM_GBS, "unit": "GB/s",
              "frac": nbytes / sec / 1e9 / PEAK_HBM_GBS}
     else:
@@ -279,7 +308,10 @@ def path_dtype(cfg):
         pc = piece_products(cfg, name)
         if pc:
             kinds = " and ".join(k for k in ("fp16", "bf16") if k + " MFMA" in routing(cfg, name)[2]) or "fp6 digits in place of"
-            parts.append(f"{name}: {kinds} pieces of fp32 factors ({pc:g} products per fp32 product), f32 accumulate")
+            per = f"{sign_digits(cfg)} digits an entry" if name == "dequantize" and sign_digits(cfg) else f"{pc:g} products per fp32 product"
+            parts.append(f"{name}: {kinds} pieces of fp32 factors ({per}), f32 accumulate")
+        elif name == "dequantize" and sign_digits(cfg):
+            parts.append("dequantize: fp6 digits of fp32 factors, f32 accumulate")
         elif name == "score" and few_queries(cfg):
             parts.append(f"score: {'fp8' if cfg.d == 128 else 'fp6'} digits of a fixed-point query, exact f32 accumulate")
         else:
