@@ -51,11 +51,12 @@
  *
  * Arithmetic.  Every contraction has fp32 operands and an fp32 (or int32)
  * accumulator; the bucket decision is an fp32 comparison.  Where it is faster
- * the fp32 factors are fed to the 16-bit or int8 matrix cores as pieces: bf16
+ * the fp32 factors are fed to the matrix cores as narrower pieces: bf16
  * pieces of 8 significant bits each, two fp16 pieces under a power-of-two scale
  * (22 bits: what is left out is below 2^-22 of the value, 2^-24.5 in the root
- * mean square, or below 2^-39 of the row's largest value), or base-128 digits
- * of a fixed-point value with 2^-19 (d = 128) or 2^-20 relative spacing:
+ * mean square, or below 2^-39 of the row's largest value), or fp6, fp8 or int8 digits
+ * of a fixed-point value: of a query with 2^-19 (d = 128) or 2^-20 relative spacing,
+ * of an entry of Pi or S with 25 or 20 bits:
  *   quantise, rotation at d = 128, more than 8192 vectors, and bf16 vectors in any number:
  *     two fp16 pieces of Pi and of an fp32 x (a bf16 x is one exact piece).  Up to 8192 bf16
  *     vectors against the fp32 instructions, of 7.9e8 coordinates at 4 bits 224 on the other
@@ -367,7 +368,7 @@ tq_status tq_dequantize(const tq_params* p, const uint32_t* idx, const uint32_t*
  *            topk > n_per_group the surplus entries are index -1, value -inf.
  *            NaN scores are never returned.
  * Workspace (tq_score_workspace_bytes gives what a call makes use of): the
- * rotated queries or their int8 digit images, and for top-k without a score
+ * rotated queries or their digit images, and for top-k without a score
  * buffer either topk candidates per query and per range of codes (many queries
  * per code, topk <= 16: the selection runs inside the scoring kernel and no
  * score matrix exists anywhere) or a score matrix [nq][n_per_group] (other
@@ -389,7 +390,7 @@ tq_status tq_score(const tq_params* p, const float* q, int64_t ldq, int32_t n_gr
  * workspace: code under HIP graph capture, tight serving loops, harnesses
  * that forbid hipMalloc.  Same arguments, results and error codes as tq_score,
  * but p->workspace is ignored: the scratch memory (rotated queries or their
- * int8 digit images, and the score matrix when scores == NULL) is a static
+ * digit images, and the score matrix when scores == NULL) is a static
  * device array inside the library, tq_score_static_scratch_bytes() bytes
  * (16 MiB) on every GPU the library has run on, held until the process ends.
  * The call allocates and frees nothing and calls no allocating routine.

@@ -537,7 +537,7 @@ size_t tq_workspace_bytes(const tq_params* p, int64_t n, int64_t nq, int32_t top
   size_t bytes = round_up(rows * (2 * d * sizeof(float) + 8 + (d + 63) / 64 * 4), 256) + 4096;
   if (n > 0 && p->images == nullptr) bytes += round_up(h2_own_images_bytes(p->d, p->S != nullptr), 256);
   bytes += 2 * round_up((size_t)nq * d * sizeof(float), 256);      // rotated / sketched queries
-  bytes += round_up(score_i8_workspace_bytes(p->d, nq), 256);      // or their int8 digit images
+  bytes += round_up(score_i8_workspace_bytes(p->d, nq), 256);      // or their digit images
   if (topk > 0) bytes += round_up((size_t)nq * (size_t)(n + 3) * sizeof(float), 256);  // scores when not returned
   // partial top-k lists of a few long rows: at most 4096 (score, index) pairs for each of at most 128 rows
   if (topk > 0) bytes += 2 * round_up((size_t)(nq < 128 ? nq : 128) * 4096 * sizeof(float), 256);
@@ -726,7 +726,7 @@ bool rotate_h2(const tq_params* p, const float* q, int64_t ldq, int64_t nq, floa
 // tq_score_workspace_bytes reports it, so the two cannot drift apart.
 struct ScorePlan {
   enum Route { R_SPLIT_I8, R_I8, R_SMALL, R_BF3, R_GEMM } route;
-  size_t img_bytes;     // int8 digit images of the rotated queries (R_SPLIT_I8, R_I8)
+  size_t img_bytes;     // digit images of the rotated queries (R_SPLIT_I8, R_I8)
   size_t q_bytes;       // one [nq][d] fp32 matrix of rotated queries (other routes; a second one for prod)
   int64_t ld_scores;    // row stride of a score matrix in scratch memory
   size_t scores_bytes;  // that matrix: only when scores == NULL and top-k is not taken inside the scoring kernel
@@ -871,7 +871,7 @@ tq_status score_impl(const tq_params* p, Workspace ws, const float* q, int64_t l
                               kappa_of(p->d_hi), make_codebook(p), make_codebook_hi(p), s) != hipSuccess)
       return TQ_ERR_HIP;
   } else if (pl.route == ScorePlan::R_I8) {
-    // masked sums of fixed-point query digits on the int8 matrix cores (at d = 128 one kernel; otherwise a
+    // masked sums of fixed-point query digits on the scaled-format matrix instruction (at d = 128 one kernel; otherwise a
     // preparation kernel rotates the queries and writes their digits)
     if (launch_score_i8(p->bits_mse, prod, p->Pi, p->S, p->PiT, p->ST, q, ldq, img, idx, qjl, gamma, norm, scores, ld_scores,
                         n_per_group, d, n_groups, q_per_group, kappa_of(d), make_codebook(p), s) != hipSuccess)

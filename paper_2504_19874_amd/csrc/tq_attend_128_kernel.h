@@ -15,8 +15,8 @@
 // therefore takes the words of 16 keys (one coordinate group, one plane) and transposes the
 // 16 x 32 bit block in registers (two 16 x 16 transposes side by side in the halves of a 32-bit
 // register); the transposed words go through LDS to the lanes that need them as B operands, which
-// expand 16 bits (16 keys of one coordinate) to 16 bytes through a 256-entry table, as the scoring
-// kernels do.
+// expand 16 bits (16 keys of one coordinate) to 16 bytes through a 256-entry table of 64 KB (the scoring
+// body takes bits as fp4 operands where they are; the weights' digits here are bytes).
 //
 // Workgroup of 8 wavefronts = 128 TILES keys of one group, 4 queries; a wavefront owns 16 TILES consecutive
 // keys (256, or 64 where 2048 keys per workgroup would leave compute units without one: attend128_tiles) and takes

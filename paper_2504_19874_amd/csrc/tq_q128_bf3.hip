@@ -62,7 +62,8 @@ struct Q128Args {
 };
 
 // h2_split with the leading piece cut off, not rounded: a mask in place of a conversion back, which the vector units take
-// longer for (131072 vectors, bf16, 3 + 1 bits 28.0 -> 27.3 us; as v_fma_mix_f32 30.0).  The lo piece then has one bit less; the signs are the same.
+// longer for (131072 vectors, bf16, 3 + 1 bits 28.0 -> 27.3 us; as v_fma_mix_f32 30.0).  The lo piece then has one bit less; the signs are the same.  (This and the longer
+// ring below pay for the second fp16 piece: the call takes what it took with bf16 pieces in the sketch, 24.8 us then, 25.2 now at 2 + 1 bits.)
 __device__ __forceinline__ void cut_split(float a, float b, uint32_t& hi, uint32_t& lo) {
   typedef float f2 __attribute__((ext_vector_type(2)));
   const float ha = __uint_as_float(__float_as_uint(a) & 0xffffe000u), hb = __uint_as_float(__float_as_uint(b) & 0xffffe000u);

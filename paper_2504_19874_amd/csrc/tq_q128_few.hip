@@ -10,7 +10,8 @@
 // these 256 and 384.  bf16 vectors, 2 + 1 bits, us a call:
 // 8 vectors 6.7 -> 3.8, 4096 7.5 -> 4.5, 8192 10.4 -> 6.0, 16384 11.6 -> 8.2 (there against the large-batch kernel); 64 channels at 2 + 1
 // and 64 at 1 + 1 bits, 4936 10.6 -> 6.2; 4 bits, 512 5.0 -> 3.6.  What is left is mostly the launch and two round trips.
-// Signs on the other side of zero than in 64 bits: 0.10 of 10^6, indices 7.7e-8 sigma off in the mean (fp32 instructions 0.13 and 1.1e-7).
+// Against 64-bit arithmetic, no further off than the fp32 instructions, whose sums meet more roundings (pieces / fp32): of 7.9e8
+// coordinates at 4 bits 224 / 320 on the other side of a boundary; signs at 2 + 1 bits 0.13 / 0.16 of 10^6, gamma 0.65 - 0.69e-7 / 0.73 - 0.82e-7.
 //
 // Where blocks leave compute units idle, a block is given to up to eight workgroups: each multiplies what the residual needs
 // and finishes 16 (32, 64) coordinates of it, so that the matrix of the sketch is fetched by several units, a part each (and for

@@ -30,7 +30,7 @@ __host__ __device__ inline uint32_t mask_digit_code(int d) {
   return (m <= 16 ? m : 8 + (m >> 1)) | (d < 0 ? 32u : 0u);
 }
 
-// The same as bytes, for masks with values 2^k: the four balanced base-128 digits of Q 2^(7 - k) (negated for k = 7, where the mask byte reads as -128), |Q| <= 2^20:
+// The same as bytes, for masks with values 2^k (the host test of stream_digits_sum makes its sums from these; no kernel does): the four balanced base-128 digits of Q 2^(7 - k) (negated for k = 7, where the mask byte reads as -128), |Q| <= 2^20:
 // the first three in [-64, 63], the last in [-64, 64].
 __host__ __device__ inline void stream_digits_of(int Q, int k, int (&dig)[4]) {
   int v = k == 7 ? -Q : Q * (1 << (7 - k));

@@ -1,8 +1,8 @@
 // Few queries per code at d = 128 (attention logits against a quantised key
 // cache, Sec. 4.3): one kernel does everything.  The arithmetic is that of
-// tq_score_i8.hip (masked sums of fixed-point query digits on
-// v_mfma_i32_16x16x64_i8, Walsh terms of a symmetric codebook); what differs is
-// how the data gets to the matrix cores.
+// tq_score_stream.hip (masked sums of fixed-point query digits on the scaled-format
+// matrix instruction, Walsh terms of a symmetric codebook), with fp8 digits of base 32
+// for fp6 ones of base 49; what differs is how the data gets to the matrix cores.
 //
 // Measured with cycle stamps inside the kernel: what a workgroup waits for is
 // not the MFMAs but its own loads.  When every compute unit asks for its 240 KB

@@ -1,11 +1,11 @@
 // Dequantisation of codes whose centroid table is a sum of signs, on the scaled-format matrix instruction
-// (tq_sign_gemm.hip: any d that is a multiple of 64 from 192 on; tq_sign_128.hip: d = 128).
+// (tq_sign_gemm.hip: multiples of 128 from 256 on; tq_sign_128.hip: d = 128).
 //
 // A table of one bit is +-c, and one of two bits that is symmetric about zero is linear in the signs of its two planes,
 //     c[idx] = alpha s_1 + beta s_0,   alpha = (c_2 + c_3) / 2,  beta = (c_3 - c_2) / 2,   s_p = +-1 by plane p,
 // and the sketch is signs to begin with.  So the whole decoding is x~ = nu (alpha Pi^T s_1 + beta Pi^T s_0 + kappa gamma S^T z):
-// products of signs with fixed matrices.  A sign is an fp4 value, eight of which come out of a word of bits in two
-// instructions; an entry of a matrix is five balanced base-32 digits (25 bits of the largest entry that leads to the same output), integers
+// products of signs with fixed matrices.  A sign is an fp4 value, and a word of bits becomes 32 of them in seven
+// instructions (minus_sign_bits); an entry of a matrix is five balanced base-32 digits (25 bits of the largest entry that leads to the same output), integers
 // of up to 16, which fp6 holds exactly; and v_mfma_f32_32x32x64_f8f6f4 multiplies the two at four times the rate of fp16, the
 // digits' weights in its scale operand.  Five digits of one sign take 5/8 of the matrix time of two fp16 pieces, a
 // two-bit centroid 10/12 of its three products, and next to nothing is left of the decoding's vector instructions.

@@ -1,7 +1,7 @@
 // DeQuant at d = 128 of codes whose table is a sum of signs (tq_sign.h).
 //
 // A wavefront owns 32 output coordinates and keeps its digits of both matrices in registers (60 each, copied from the
-// image at the start); it walks blocks of 32 codes, whose words it reads as they lie: no LDS, no barrier, and few codes are simply
+// image at the start, or made there, see OWN); it walks blocks of 32 codes, whose words it reads as they lie: no LDS, no barrier, and few codes are simply
 // few wavefronts.  One accumulator per kind of sign, the small digits first, joined with the codes' factors in the end: a sum meets two
 // roundings at its full size where pieces met ten times as many.
 //
@@ -255,7 +255,7 @@ hipError_t launch_digits(const Sign128Args& a, hipStream_t s) {
   // their digits, always)
   const int64_t blocks = (a.n + 31) / 32, cu = device_cu_count();
   const int waves = !OWN && blocks * 4 <= cu ? 1 : 4;
-  const int64_t groups = OWN ? (blocks + 3) / 4 * 4 : blocks * 4 / waves, most = 8 * cu / waves / 4 * 4;
+  const int64_t groups = OWN ? (blocks + 3) / 4 * 4 : blocks * 4 / waves, most = (8 * cu / waves + 3) / 4 * 4;
   const dim3 grid((unsigned)(groups < most ? groups : most)), block(64 * waves);
   if (a.n > kBf3DequantRows) hipLaunchKernelGGL((sign128_dequant_kernel<BITS, PROD, 4, OWN>), grid, block, 0, s, a);
   else hipLaunchKernelGGL((sign128_dequant_kernel<BITS, PROD, 5, OWN>), grid, block, 0, s, a);
