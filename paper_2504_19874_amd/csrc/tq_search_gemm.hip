@@ -51,16 +51,16 @@ struct SearchGemmArgs {
   int qblocks, ranges, tiles, per_xcd;
 };
 
-// Four coordinates (bit position 4 half + k of the four bytes) as two words of the contraction
-template <int BITS>
+// Four coordinates (bit position 4 HALF + k of the four bytes) as two words of the contraction
+template <int BITS, int HALF>
 struct QuadDecoder {
   uint32_t u[BITS > 1 ? BITS - 1 : 1], n;
-  __device__ __forceinline__ QuadDecoder(const uint32_t* w, int half) {
+  __device__ __forceinline__ QuadDecoder(const uint32_t* w) {
     if constexpr (BITS > 1) {
 #pragma unroll
-      for (int p = 0; p < BITS - 1; ++p) u[p] = ~(w[p] ^ w[BITS - 1]) >> (4 * half);
+      for (int p = 0; p < BITS - 1; ++p) u[p] = ~(w[p] ^ w[BITS - 1]) >> (4 * HALF);
     }
-    n = ~w[BITS - 1] >> (4 * half);
+    n = ~w[BITS - 1] >> (4 * HALF);
   }
   __device__ __forceinline__ void quad(int k, const CodeTable& tab, uint32_t& a, uint32_t& b) const {
     if constexpr (BITS == 1) {
@@ -81,7 +81,7 @@ struct QuadDecoder {
 
 template <int TW, int WM, int WN>
 struct SearchCfg {
-  static constexpr int UW = WM;  // so that every thread decodes half a group of one code per step
+  static constexpr int UW = WM;  // so that every thread decodes a group of one code in two steps
   static constexpr int THREADS = 64 * WM * WN, TM = WM * TW * 32, TN = WN * UW * 32;
   static constexpr int A_BYTES = TM * 64, B_BYTES = TN * 64, NS = 4;
   static constexpr int LOADERS = A_BYTES / 1024 < WM * WN ? A_BYTES / 1024 : WM * WN;  // wavefronts that load query pieces
@@ -153,31 +153,58 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void search_gemm_kernel(const Sear
     if (a_step == n_steps) a_step = 0, gA = gS;
   };
 
-  // ---- codes: the words of step after step, tile after tile ----------------------------------------------
-  const int code = tid % TN, half = __builtin_amdgcn_readfirstlane(tid / TN);
-  auto code_row = [&](int tile) {  // codes past the end: the last one again
-    const int64_t i = (int64_t)tile * TN + code;
+  // ---- codes: the words of four steps at a time, tile after tile ------------------------------------------
+  // Two neighbouring lanes share a code: one has the groups of even steps, the other those of odd ones, each decoded over
+  // two steps.  A lane's two groups of a round are asked for together, so that a line of codes is met once in four steps:
+  // 256 codes are as many lines as the cache beside the compute unit has, and words asked for step by step came from L2 once
+  // for every step and half group, 646 requests a step with the queries' 128 (d = 1536, 4 bits, 10^6 codes, 1000 queries,
+  // the whole search: 3.49 -> 3.23 ms; d = 3072, 3 bits 1.17 times faster).
+  const int code = tid >> 1, odd = tid & 1;
+  auto code_row = [&](int tile, int c) {  // codes past the end: the last one again
+    const int64_t i = (int64_t)tile * TN + c;
     return (i < a.n ? i : a.n - 1) * (FIND ? 1 : a.code_step);
   };
   const uint32_t *wi = nullptr, *wz = nullptr;
   int w_step = 0, w_tile = tile0;
   auto point = [&] {
-    const int64_t row = code_row(w_tile);
-    if (HAVE_P) wi = a.idx + row * G * BITS;
-    if (HAVE_S) wz = a.qjl + row * G;
+    const int64_t row = code_row(w_tile, code);
+    if (HAVE_P) wi = a.idx + (row * G + odd) * BITS;
+    if (HAVE_S) wz = a.qjl + row * G + odd;
   };
   point();
-  uint32_t words[NS][NW];
-  auto load_step = [&](uint32_t (&w)[NW], auto in_s) {  // in_s: the step under way is one of the sketch (this one may not be)
-    if (HAVE_S && (decltype(in_s)::value || HAVE_P) && (!HAVE_P || w_step < n_s)) w[0] = wz[w_step];
-    else if constexpr (HAVE_P) load_plane_words<BITS>(wi + (w_step - n_s) * BITS, w);
-    if (++w_step == n_steps) {
+  uint32_t words[2][NW], next_words[2][NW];  // [pair of steps]
+  auto load_round = [&] {
+    if (HAVE_S && (!HAVE_P || w_step < n_s)) {
+#pragma unroll
+      for (int j = 0; j < 2; ++j) next_words[j][0] = wz[w_step + 2 * j];
+    } else if constexpr (HAVE_P) {
+      uint32_t w0[NW], w1[NW];  // (loaded into the array itself, one of the two branches would leave it in memory)
+      load_plane_words<BITS>(wi + (w_step - n_s) * BITS, w0);
+      load_plane_words<BITS>(wi + (w_step - n_s + 2) * BITS, w1);
+#pragma unroll
+      for (int p = 0; p < NW; ++p) next_words[0][p] = w0[p], next_words[1][p] = w1[p];
+    }
+    w_step += NS;
+    if (w_step == n_steps) {
       w_step = 0;
       ++w_tile;
       point();
     }
   };
-  const uint32_t b_at = h2_place<1>(code, 2 * half);
+  auto advance = [&] {
+    // (moves that the compiler can not put off to the end of its loop, where it would wait for the loads behind them)
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int p = 0; p < NW; ++p) asm volatile("v_mov_b32 %0, %1" : "=v"(words[j][p]) : "v"(next_words[j][p]));
+    __builtin_amdgcn_sched_barrier(0);
+    load_round();
+  };
+  // the two store into the buffers of both steps of a pair at once: the odd one has its two halves exchanged, for the banks
+  const uint32_t b_at = h2_place<1>(code, 2 * odd) + odd * C::B_BYTES;
+  auto store_codes = [&](int pair, int chunk, const uint32_t* v) {
+    *reinterpret_cast<uint4*>(lds + NS * C::A_BYTES + 2 * pair * C::B_BYTES + (b_at ^ (16 * chunk))) = make_uint4(v[0], v[1], v[2], v[3]);
+  };
 
   const unsigned char *pa[2], *pb[2];
 #pragma unroll
@@ -199,7 +226,7 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void search_gemm_kernel(const Sear
   float next_nu = 1.f, next_kg = 0.f;
   auto request_scalars = [&](int tile) {
     if (tid < TN) {
-      const int64_t r = code_row(tile);
+      const int64_t r = code_row(tile, tid);
       next_nu = a.norm != nullptr ? a.norm[r] : 1.f;
       next_kg = HAVE_S ? a.gamma[r] : 0.f;
     }
@@ -222,16 +249,14 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void search_gemm_kernel(const Sear
   constexpr int NR = TW + UW, NM = TW * UW;
   auto read_one = [&](Frag& f, int buf, int s, int i) {
     if (i < TW) f.a[i] = *reinterpret_cast<const f16x8*>(pa[s] + buf * C::A_BYTES + i * 2048);
-    else f.b[i - TW] = *reinterpret_cast<const f16x8*>(pb[s] + buf * C::B_BYTES + (i - TW) * 2048);
+    else f.b[i - TW] = *reinterpret_cast<const f16x8*>(pb[s ^ (buf & 1)] + buf * C::B_BYTES + (i - TW) * 2048);
   };
   Frag f0, f1;
-  // next_p: the step after this one belongs to the centroid segment
-  auto step = [&](auto buf_c, auto in_s, auto next_p) __attribute__((always_inline)) {  // (called, it would keep the accumulators in memory)
+  // of_p: the pair of steps that is decoded meanwhile (the one after this step's pair) belongs to the centroid segment
+  auto step = [&](auto buf_c, auto of_p) __attribute__((always_inline)) {  // (called, it would keep the accumulators in memory)
     constexpr int buf = decltype(buf_c)::value, nbuf = (buf + 1) % NS;
-    constexpr int NBITS = decltype(next_p)::value ? NW : 1;
-    load_step(words[buf], in_s);
-    const QuadDecoder<NBITS> dec(words[nbuf], half);
-    unsigned char* const bb = lds + NS * C::A_BYTES + nbuf * C::B_BYTES;
+    constexpr int half = buf & 1, pair = (buf / 2 + 1) % 2;  // half of the group, and which pair of the round
+    const QuadDecoder<decltype(of_p)::value ? NW : 1, half> dec(words[pair]);
     uint32_t v[8];
     auto from = [](int i) { return 2 * i * NR / NM < NR ? 2 * i * NR / NM : NR; };  // reads go into the first half of a half-step
     __builtin_amdgcn_sched_barrier(0);
@@ -243,29 +268,32 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void search_gemm_kernel(const Sear
 #pragma unroll
       for (int k = 4 * i / NM; k < 4 * (i + 1) / NM; ++k) {
         dec.quad(k, a.tab, v[2 * k], v[2 * k + 1]);
-        if (k == 1) *reinterpret_cast<uint4*>(bb + b_at) = make_uint4(v[0], v[1], v[2], v[3]);
-        if (k == 3) *reinterpret_cast<uint4*>(bb + (b_at ^ 16)) = make_uint4(v[4], v[5], v[6], v[7]);
+        if (k & 1) store_codes(pair, 2 * half + k / 2, v + 2 * (k - 1));
       }
       __builtin_amdgcn_sched_barrier(0);
     }
     __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0), so that the compiler knows the fragments have arrived
     // everyone has read this step; the next one is there (younger than its query pieces: the loads of the two steps after
-    // it and the words requested since)
-    h2_wait_barrier<(NS - 2) * AL + NS - 1>();
+    // it and, in the second pair, the words requested in front of those of step 1)
+    h2_wait_barrier<(NS - 2) * AL + (buf >= 2 ? 2 : 0)>();
 #pragma unroll
     for (int i = 0; i < NM; ++i) {
       acc[i / UW][i % UW] = __builtin_amdgcn_mfma_f32_32x32x16_f16(f1.a[i / UW], f1.b[i % UW], acc[i / UW][i % UW], 0, 0, 0);
 #pragma unroll
       for (int r = from(i); r < from(i + 1); ++r) read_one(f0, nbuf, 0, r);
-      if (i == NM - 1) dma(buf);
+      if (i == NM - 1) {
+        // (the words are waited for with all that is under way: in front of this step's loads, which would be the youngest)
+        if constexpr (buf == 1) advance();
+        dma(buf);
+      }
       __builtin_amdgcn_sched_barrier(0);
     }
   };
-  auto round = [&](auto in_s, auto next_p, auto last_next_p) __attribute__((always_inline)) {
-    step(std::integral_constant<int, 0>{}, in_s, next_p);
-    step(std::integral_constant<int, 1>{}, in_s, next_p);
-    step(std::integral_constant<int, 2>{}, in_s, next_p);
-    step(std::integral_constant<int, 3>{}, in_s, last_next_p);
+  auto round = [&](auto this_p, auto next_p) __attribute__((always_inline)) {
+    step(std::integral_constant<int, 0>{}, this_p);
+    step(std::integral_constant<int, 1>{}, this_p);
+    step(std::integral_constant<int, 2>{}, next_p);
+    step(std::integral_constant<int, 3>{}, next_p);
   };
 
   // ---- candidates ------------------------------------------------------------------------------------------
@@ -290,8 +318,8 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void search_gemm_kernel(const Sear
 
   // ---- before the first tile -------------------------------------------------------------------------------
   request_scalars(tile0);
-#pragma unroll
-  for (int i = 0; i < NS; ++i) load_step(words[i], std::bool_constant<HAVE_S>{});
+  load_round();
+  advance();
 #pragma unroll
   for (int i = 0; i < NS; ++i) dma(i);
   for (int m = tid; m < TM; m += C::THREADS) {
@@ -308,15 +336,17 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void search_gemm_kernel(const Sear
   }
   store_scalars(tile0);
   if (tid < 4) found_n[tid] = 0;
-  {
-    const QuadDecoder<HAVE_S ? 1 : NW> dec(words[0], half);
+  auto decode_half = [&](auto half_c) {  // of the first pair of steps
+    constexpr int half = decltype(half_c)::value;
+    const QuadDecoder<HAVE_S ? 1 : NW, half> dec(words[0]);
     uint32_t v[8];
 #pragma unroll
     for (int k = 0; k < 4; ++k) dec.quad(k, a.tab, v[2 * k], v[2 * k + 1]);
-    unsigned char* const bb = lds + NS * C::A_BYTES;
-    *reinterpret_cast<uint4*>(bb + b_at) = make_uint4(v[0], v[1], v[2], v[3]);
-    *reinterpret_cast<uint4*>(bb + (b_at ^ 16)) = make_uint4(v[4], v[5], v[6], v[7]);
-  }
+    store_codes(0, 2 * half, v);
+    store_codes(0, 2 * half + 1, v + 4);
+  };
+  decode_half(std::integral_constant<int, 0>{});
+  decode_half(std::integral_constant<int, 1>{});
   h2_wait_barrier<0>();
 #pragma unroll
   for (int i = 0; i < NR; ++i) read_one(f0, 0, 0, i);
@@ -324,13 +354,13 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void search_gemm_kernel(const Sear
   for (int tile = tile0; tile < tile1; ++tile) {
     request_scalars(tile + 1 < tile1 ? tile + 1 : tile);
     clear();
-    // (a tile's last step decodes the first step of the next one: of the sketch where there is one)
+    // (a tile's last pair of steps decodes the first pair of the next one: of the sketch where there is one)
     if constexpr (HAVE_S && !HAVE_P) {
-      for (int st = 0; st < n_s; st += NS) round(std::true_type{}, std::false_type{}, std::false_type{});
+      for (int st = 0; st < n_s; st += NS) round(std::false_type{}, std::false_type{});
     } else {
       if constexpr (HAVE_S) {
-        for (int st = NS; st < n_s; st += NS) round(std::true_type{}, std::false_type{}, std::false_type{});
-        round(std::true_type{}, std::false_type{}, std::true_type{});
+        for (int st = NS; st < n_s; st += NS) round(std::false_type{}, std::false_type{});
+        round(std::false_type{}, std::true_type{});
         int sl = l32;
         asm volatile("" : "+v"(sl));
         const float* const fs = code_s + (tile & 1) * C::CODE_F * TN + wn * UW * 32 + sl;
@@ -343,8 +373,8 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void search_gemm_kernel(const Sear
             for (int r = 0; r < 16; ++r) acc[t][u][r] *= f;
         }
       }
-      for (int st = HAVE_S ? NS : 0; st < G; st += NS) round(std::false_type{}, std::true_type{}, std::true_type{});
-      if constexpr (HAVE_S) round(std::false_type{}, std::true_type{}, std::false_type{});
+      for (int st = HAVE_S ? NS : 0; st < G; st += NS) round(std::true_type{}, std::true_type{});
+      if constexpr (HAVE_S) round(std::true_type{}, std::false_type{});
     }
 
     // ---- comparisons: a lane has 16 queries of one code per 32 x 32 tile ------------------------------------
