@@ -14,8 +14,8 @@
 //     lane loads (1 KB per instruction) and parks them in a private LDS region;
 //     the tiles later pick their words out of LDS in operand order,
 //   * the workgroup prepares its own four queries while those loads are in
-//     flight (y = Pi q and S q from the transposed matrices, column per thread,
-//     query coordinates through scalar registers; then digits into LDS).  That
+//     flight (y = Pi q and S q from the transposed matrices, column per thread;
+//     then digits into LDS).  That
 //     re-reads 128 KB of matrices per workgroup, which is cheaper than the
 //     launch-and-latency chain of a preparation kernel in front,
 //   * the masked sums are taken on v_mfma_f32_16x16x128_f8f6f4, all 128 coordinates of a key at once: a stored word ANDed
@@ -49,7 +49,7 @@ constexpr int SCORE128_ROUND_TILES = 4, SCORE128_ROUNDS_AHEAD = 2;
 __host__ __device__ constexpr int stage_bytes(int bits) { return 16 * SCORE128_ROUND_TILES * (16 * bits + 16 + 4 + 4); }
 
 // staging regions, partial sums of the query preparation (8 KB), one 2 KB digit image per masked sum, scalars
-__host__ __device__ constexpr int score128_lds(int bits) { return 8 * stage_bytes(bits) + 2 * 2 * 4 * 128 * 4 + i8_terms(bits, true) * 2048 + 2 * 4 * 4 * 4; }
+__host__ __device__ constexpr int score128_lds(int bits) { return 8 * stage_bytes(bits) + I8_PART_FLOATS * 4 + i8_terms(bits, true) * 2048 + 2 * 4 * 4 * 4; }
 
 // The whole kernel as a function of where a finished score goes: sink(t, score, key_live) is
 // called once per tile t (TILES tiles of 16 keys per wavefront) by every lane with the score of
@@ -84,12 +84,12 @@ __device__ __forceinline__ void score128_body(const ScoreI8Args& a, unsigned cha
 
   unsigned char* const stage = dyn_s + wave * stage_bytes(BITS);
   float* const part_s = reinterpret_cast<float*>(dyn_s + 8 * stage_bytes(BITS));        // [2][2][4][128]
-  unsigned char* const dig_s = reinterpret_cast<unsigned char*>(part_s + 2 * 2 * 4 * 128);  // [term][4][4][128]
+  unsigned char* const dig_s = reinterpret_cast<unsigned char*>(part_s + I8_PART_FLOATS);  // [term][4][4][128]
   float* const scal_s = reinterpret_cast<float*>(dig_s + i8_terms(BITS, true) * 2048);  // [2][4][4]
 
   // ---- 1. this thread's column of the transposed matrix: 64 values of k ---------------------
   I8Prep<(BITS > 0), PROD> prep;
-  prep.load(a, wave, tid);
+  prep.load(a, group, q0, wave, tid);
 
   // ---- 2. the codes of this wavefront's keys, as contiguous 16-byte pieces ---------------------
   // Pieces past the end of the arrays are clamped onto the last one (never used: the
@@ -139,10 +139,14 @@ __device__ __forceinline__ void score128_body(const ScoreI8Args& a, unsigned cha
   meanwhile();
 
   // ---- 3. rotate / sketch this workgroup's four queries, 4. fixed point --------------------------
-  prep.matvec(a, group, q0, part_s);
+  // (each phase by itself: mixed into each other by the compiler, they wait for one another's operands)
+  __builtin_amdgcn_sched_barrier(0);
+  prep.matvec(part_s);
+  __builtin_amdgcn_sched_barrier(0);
   __syncthreads();
   i8_digitise_terms<BITS, PROD>(a, q0, wave, lane, part_s, dig_s, scal_s);
   __syncthreads();  // digits and scalars are in LDS
+  __builtin_amdgcn_sched_barrier(0);
 
   // ---- 5. A operands: lane = row + 16 kq, row = 4 * query + digit; one image per masked sum --------
   const int a_query = col >> 2, a_digit = col & 3;

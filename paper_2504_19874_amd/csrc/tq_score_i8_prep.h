@@ -4,8 +4,11 @@
 //
 //   load      wavefront w requests its thread's column of matrix w / 4 (0: Pi^T, 1: S^T), half
 //             (w / 2) % 2 of k, column j = tid % 128: 64 values, to be issued before anything else
-//   matvec    y_j partial sums for the four queries (query coordinates through scalar
-//             registers) -> part_s[matrix][half][query][j]
+//   matvec    y_j partial sums for the four queries -> part_s[matrix][half][query][j].  The queries' coordinates lie in registers of
+//             every row of 16 lanes and are broadcast by the multiplication itself.  Through scalar registers, of which they take more
+//             than there are, they were three trips to memory in a row behind everything else that had been asked for: 1.4 us of
+//             a read-out over 1024 keys (19.1 -> 18.3 us with its two appends; 8 x 65536 keys scored: 11.2 -> 10.9).  The matrices as
+//             8 bytes per lane in half as many loads: 0.5 us slower with a sketch
 //   (barrier)
 //   digitise  wavefront w takes (matrix w / 4, query w % 4): power-of-two scale with |Q| <= 2^19,
 //             digits -> dig_s[matrix][query][digit][j] (digit 3 = 0), scalars -> scal_s[matrix][query]
@@ -24,7 +27,8 @@ namespace tq {
 // coordinate c in a digit row whose lanes read 16 bytes at 16 kq and 16 at 64 + 16 kq.
 __host__ __device__ constexpr int mask_slot(int c) { return (c & ~31) + 8 * (c & 3) + ((c >> 2) & 7); }
 
-constexpr int I8_PREP_BYTES = 2 * 2 * 4 * 128 * 4 + 2 * 4 * 4 * 128 + 2 * 4 * 4 * 4;  // partial sums, digits, scalars
+constexpr int I8_PART_FLOATS = 2 * 2 * 4 * 128;
+constexpr int I8_PREP_BYTES = I8_PART_FLOATS * 4 + 2 * 4 * 4 * 128 + 2 * 4 * 4 * 4;  // partial sums, digits, scalars
 
 // max / sum over the 64 lanes: four DPP steps inside each row of 16, then the four rows
 // through scalar registers
@@ -52,13 +56,16 @@ __device__ __forceinline__ int wave_sum(int v) {
          __builtin_amdgcn_readlane(v, 48);
 }
 
+typedef float f32x4_prep __attribute__((ext_vector_type(4), aligned(4)));  // (the queries are the caller's)
+
 template <bool HAVE_R, bool PROD>
 struct I8Prep {
   float wv[64];
+  f32x4_prep q[4];  // coordinates 4 i .. 4 i + 3 of the half of k, in lane i of every row of 16
   int mat, kh, j;
   bool work;
 
-  __device__ __forceinline__ void load(const ScoreI8Args& a, int wave, int tid) {
+  __device__ __forceinline__ void load(const ScoreI8Args& a, int group, int q0, int wave, int tid) {
     mat = wave >> 2;
     kh = (wave >> 1) & 1;
     j = tid & 127;
@@ -66,23 +73,41 @@ struct I8Prep {
     if (work) {
       const float* WT = (mat ? a.ST : a.PiT) + (64 * kh) * 128 + j;
 #pragma unroll
-      for (int k = 0; k < 64; ++k) wv[k] = WT[k * 128];
+      for (int k = 0; k < 40; ++k) wv[k] = WT[k * 128];
+      // (here: in front of the matrix they hold up what comes from a nearer cache, 11.5 us in place of 10.9, behind it the products)
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int qi = 0; qi < 4; ++qi) {
+        const int64_t r = (int64_t)group * a.q_per_group + (q0 + qi < a.q_per_group ? q0 + qi : q0);
+        q[qi] = *reinterpret_cast<const f32x4_prep*>(a.x + r * a.ldx + 64 * kh + 4 * (tid & 15));
+      }
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int k = 40; k < 64; ++k) wv[k] = WT[k * 128];
     }
   }
 
-  __device__ __forceinline__ void matvec(const ScoreI8Args& a, int group, int q0, float* part_s) {
+  // k = 4 I .. 4 I + 3: a query's coordinate from lane I of the row, in one instruction with its product.  (The compiler makes two of
+  // it.  It does not look inside: s_nop is the distance that a register moved just before needs from its use by other lanes.)
+  template <int I>
+  __device__ __forceinline__ void matvec_step(float (&acc)[4]) {
+#define TQ_FMAC(ACC, Q, W) "\n\tv_fmac_f32_dpp %" #ACC ", %" #Q ", %" #W " row_newbcast:%24 row_mask:0xf bank_mask:0xf"
+    asm("s_nop 1"
+        TQ_FMAC(0, 4, 20) TQ_FMAC(1, 8, 20) TQ_FMAC(2, 12, 20) TQ_FMAC(3, 16, 20)
+        TQ_FMAC(0, 5, 21) TQ_FMAC(1, 9, 21) TQ_FMAC(2, 13, 21) TQ_FMAC(3, 17, 21)
+        TQ_FMAC(0, 6, 22) TQ_FMAC(1, 10, 22) TQ_FMAC(2, 14, 22) TQ_FMAC(3, 18, 22)
+        TQ_FMAC(0, 7, 23) TQ_FMAC(1, 11, 23) TQ_FMAC(2, 15, 23) TQ_FMAC(3, 19, 23)
+        : "+v"(acc[0]), "+v"(acc[1]), "+v"(acc[2]), "+v"(acc[3])
+        : "v"(q[0][0]), "v"(q[0][1]), "v"(q[0][2]), "v"(q[0][3]), "v"(q[1][0]), "v"(q[1][1]), "v"(q[1][2]), "v"(q[1][3]), "v"(q[2][0]),
+          "v"(q[2][1]), "v"(q[2][2]), "v"(q[2][3]), "v"(q[3][0]), "v"(q[3][1]), "v"(q[3][2]), "v"(q[3][3]), "v"(wv[4 * I]),
+          "v"(wv[4 * I + 1]), "v"(wv[4 * I + 2]), "v"(wv[4 * I + 3]), "n"(I));
+#undef TQ_FMAC
+    if constexpr (I + 1 < 16) matvec_step<I + 1>(acc);
+  }
+  __device__ __forceinline__ void matvec(float* part_s) {
     if (!work) return;
-    const float* xq[4];  // uniform addresses: the query coordinates arrive in scalar registers
-#pragma unroll
-    for (int qi = 0; qi < 4; ++qi) {
-      const int64_t r = (int64_t)group * a.q_per_group + (q0 + qi < a.q_per_group ? q0 + qi : q0);
-      xq[qi] = a.x + r * a.ldx + 64 * kh;
-    }
     float acc[4] = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int k = 0; k < 64; ++k)
-#pragma unroll
-      for (int qi = 0; qi < 4; ++qi) acc[qi] = fmaf(wv[k], xq[qi][k], acc[qi]);
+    matvec_step<0>(acc);
 #pragma unroll
     for (int qi = 0; qi < 4; ++qi) part_s[((mat * 2 + kh) * 4 + qi) * 128 + j] = acc[qi];
   }

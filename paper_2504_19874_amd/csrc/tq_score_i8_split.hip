@@ -33,7 +33,7 @@ __global__ __launch_bounds__(512) void score_i8_split_kernel(const ScoreI8Args a
   __shared__ __attribute__((aligned(16))) uint2 expand_s[256 * I8_COPIES];  // [256][32]: byte -> one byte per bit
   extern __shared__ __attribute__((aligned(16))) unsigned char prep_s[];   // FUSED: partial sums, digits, scalars
   float* const part_s = reinterpret_cast<float*>(prep_s);                               // [2][2][4][128]
-  signed char* const dig_s = reinterpret_cast<signed char*>(part_s + 2 * 2 * 4 * 128);  // [2][4][4][128]
+  signed char* const dig_s = reinterpret_cast<signed char*>(part_s + I8_PART_FLOATS);  // [2][4][4][128]
   float* const scal_s = reinterpret_cast<float*>(dig_s + 2 * 4 * 4 * 128);              // [2][4][4]
   constexpr int NP = BITS + 1;            // planes of instance hi
   constexpr int NMH = (1 << NP) - 1;      // plane subsets of hi
@@ -59,7 +59,7 @@ __global__ __launch_bounds__(512) void score_i8_split_kernel(const ScoreI8Args a
   const v4i zero = v4i{0, 0, 0, 0};
   I8Prep<true, PROD> prep;
   if (FUSED) {
-    prep.load(a, wave, tid);  // this thread's column of the transposed matrix, before anything else
+    prep.load(a, group, q0, wave, tid);  // this thread's column of the transposed matrix, before anything else
   } else {
 #pragma unroll
     for (int s = 0; s < 2; ++s) {
@@ -113,7 +113,7 @@ __global__ __launch_bounds__(512) void score_i8_split_kernel(const ScoreI8Args a
     }
   }
   if (FUSED) {
-    prep.matvec(a, group, q0, part_s);
+    prep.matvec(part_s);
     __syncthreads();
     prep.digitise(a, q0, wave, lane, 32 * gs, part_s, dig_s, scal_s);
   }
