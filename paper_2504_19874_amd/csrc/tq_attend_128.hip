@@ -11,6 +11,15 @@ int64_t long_limit(int n_groups, int q_per_group) {  // keys per group up to whi
   const int64_t others = (int64_t)n_groups * ((q_per_group + 3) / 4);
   return others > 0 ? device_cu_count() / 2 / others * (128 * AT_TILES) : 0;
 }
+
+bool coefficients(const Codebook& cb, AttendCoefs* out) {
+  if (!i8_coefficients(cb.bits, cb, out->c)) return false;
+  double mean = 0.0;  // (0 and nothing else for a table symmetric about zero: the sums are exact)
+  for (int i = 0; i < (1 << cb.bits); ++i) mean += cb.c[i];
+  out->c[0] = (float)(mean / (1 << cb.bits));
+  for (int v = 1; v < 16; ++v) out->c[v] = -out->c[v];
+  return true;
+}
 }  // namespace
 int attend128_tiles(int64_t n, int n_groups, int q_per_group) { return n <= long_limit(n_groups, q_per_group) ? AT_TILES_SHORT : AT_TILES; }
 int attend128_max_chunks(int64_t n, int n_groups, int q_per_group) {
@@ -40,9 +49,9 @@ hipError_t launch_attend128(int kb, bool kprod, const ScoreI8Args* ka, bool vpro
   if (ka == nullptr) kb = -1;
   AttendCoefs cf, cfh;
   std::memset(&cfh, 0, sizeof(cfh));
-  if (a.d != 128 || !i8_coefficients(a.cb.bits, a.cb, cf.c)) return hipErrorInvalidValue;
+  if (a.d != 128 || !coefficients(a.cb, &cf)) return hipErrorInvalidValue;
   if (a.gs_hi > 0) {
-    if (vprod || !i8_coefficients(a.cb_hi.bits, a.cb_hi, cfh.c)) return hipErrorInvalidValue;
+    if (vprod || !coefficients(a.cb_hi, &cfh)) return hipErrorInvalidValue;
     switch (a.cb.bits) {
       case 1: return launch_attend128_s1(kb, kprod, k, a, cf, cfh, n_groups, s);
       case 2: return launch_attend128_s2(kb, kprod, k, a, cf, cfh, n_groups, s);

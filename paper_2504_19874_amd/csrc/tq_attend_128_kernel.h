@@ -1,26 +1,31 @@
 // Attention read-out at d = 128 (see tq_attend.hip for the decomposition): the softmax-weighted
-// sum of decoded value codes on the integer matrix cores.
+// sum of decoded value codes on the matrix cores.
 //
-// With a centroid table symmetric about zero, c[idx] = coef[0] + sum over the odd-sized plane
-// subsets S of coef[S] * x_S(idx), x_S = XOR of the index bits in S (tq_score_i8.hip).  So for
+// A centroid table symmetric about its mean is a sum of signs, c[idx] = w0 + sum over the odd-sized plane
+// subsets S of h[S] * s_S(idx), s_S = -1 / +1 as the XOR of the index bits in S is 0 / 1 (tq_score_i8.hip).  So for
 // every query q and coordinate j
-//     sum_i w_qi c[idx_ij] = coef[0] * sum_i w_qi + sum_S coef[S] * sum_i w_qi x_S(idx_ij):
-// sums of weights over the KEYS selected by a bit mask.  The sign term of Alg. 2 is one more
+//     sum_i w_qi c[idx_ij] = w0 * sum_i w_qi + sum_S h[S] * sum_i w_qi s_S(idx_ij):
+// sums of weights over the KEYS with signs from the code's bits.  The sign term of Alg. 2 is one more
 // such sum, over the sign bits with the weights exp(logit - m) * nu_i * gamma_i (VPROD).  The weights w_qi = exp(logit - m) * nu_i
-// are scaled by a power of two to 26-bit integers and split into four balanced base-256 digits;
-// one v_mfma_i32_16x16x64_i8 multiplies the 16 rows (4 queries x 4 digits) with 64 keys x 16
-// coordinates of 0/1 bytes.
+// are scaled by a power of two to 28-bit integers.  A nibble n of one, as a byte, IS the fp8 number n 2^-9 (e4m3: 0..7 are the
+// subnormals, 8..15 go on evenly), so the eight base-16 digits of a weight cost two ANDs and no conversion, and a bit becomes an fp4
+// operand of either sign where it stands in its word (0.5 with the bit shifted to the sign: seven instructions for 32 keys).  One
+// v_mfma_scale_f32_32x32x64_f8f6f4 multiplies 32 rows (4 queries x 8 digits) with 64 keys x 32 coordinates; all sums of digits are
+// exact (below 2^12 in steps of 1/2).
 //
 // The contraction runs over keys, but a code word holds 32 COORDINATES of one key.  Each lane
-// therefore takes the words of 16 keys (one coordinate group, one plane) and transposes the
-// 16 x 32 bit block in registers (two 16 x 16 transposes side by side in the halves of a 32-bit
-// register); the transposed words go through LDS to the lanes that need them as B operands, which
-// expand 16 bits (16 keys of one coordinate) to 16 bytes through a 256-entry table of 64 KB (the scoring
-// body takes bits as fp4 operands where they are; the weights' digits here are bytes).
+// therefore takes the words of 32 keys (one coordinate group, one plane) and transposes the
+// 32 x 32 bit block in registers; the transposed words go through LDS to the lanes that need them as operands.
 //
 // Workgroup of 8 wavefronts = 128 TILES keys of one group, 4 queries; a wavefront owns 16 TILES consecutive
 // keys (256, or 64 where 2048 keys per workgroup would leave compute units without one: attend128_tiles) and takes
-// 128 (64) per pass.  Per pass and wavefront: 2 (1) k-blocks of 64 keys x 8 coordinate blocks x terms MFMAs.
+// up to 256 per pass (at_pass_keys: what LDS holds).  Everything between the scoring and the joining is a wavefront's own.
+//
+// 8 heads, 4 queries each, keys of 2 + 1 bits, values of 2, a step with its two appends: 65536 keys 29.0 -> 27.4 us, 1024 19.1 ->
+// 18.1; keys and values of 4 bits, 53970 keys 61 -> 41.  Before: four base-256 digits on the integer instructions, whose byte operands
+// came through a table of 64 KB in LDS, passes of 128 keys with two barriers each, and every lane fetching its own code words.  What
+// bounds the 17 us after the launch: key codes until 10 (see the scoring body), then vector instructions (transposition, weights) and 2 us of matrix
+// instructions, which with an fp8 operand take 64 cycles.
 //
 // FUSED: the logits come from the d = 128 scoring kernel run in place (tq_score_i8_128_body.h: the
 // lane of (query, key) keeps its score in a register), so neither a score nor a dequantised
@@ -34,24 +39,35 @@
 
 namespace tq {
 
-__host__ __device__ constexpr int at_pass_keys(int tiles) { return tiles >= 8 ? 128 : 64; }    // keys a wavefront handles per pass
-__host__ __device__ constexpr int at_wd_bytes(int tiles) { return 8 * 4 * 4 * at_pass_keys(tiles); }        // weight digits [wave][query][digit][key]
-__host__ __device__ constexpr int at_xch_bytes(int tiles) { return 8 * (at_pass_keys(tiles) / 16) * 64 * 4; }  // per plane: [wave][block of 16 keys][64 words]
-constexpr int AT_FSUM_BYTES = 8 * 4 * 128 * 4;  // [wave][query][coordinate], over the exchange area in the end
+// keys a wavefront handles per pass, its planes in words being NPL: all of its own where LDS and the 64 lanes (a block of 32 keys, a
+// coordinate group and a plane each) allow it.  two: a second set of weight digits (the signs of Alg. 2, or instance hi)
+__host__ __device__ constexpr int at_pass_keys(int tiles, int npl, bool two) { return tiles < 8 ? 64 : npl <= 2 && !two ? 256 : 128; }
+__host__ __device__ constexpr int at_planes(int vb, bool two) { return vb + (two ? 1 : 0); }
+// digits of a wavefront: [query][digit][key], a byte each; 16 more per row, so that the rows of a read are in different banks
+__host__ __device__ constexpr int at_row_bytes(int pass) { return pass + 16; }
+__host__ __device__ constexpr int at_wd_bytes(int pass) { return 32 * at_row_bytes(pass); }
+// transposed words of a plane: [pair of blocks of 32 keys][block][coordinate]; the second block of a pair 32 words behind the first, so
+// that the half-waves, which read one each, are in different halves of the banks
+constexpr int AT_BLOCK_WORDS = 128 + 32, AT_PAIR_WORDS = AT_BLOCK_WORDS + 128;
+__host__ __device__ constexpr int at_plane_words(int pass) { return pass / 64 * AT_PAIR_WORDS; }
+constexpr int AT_FSUM_BYTES = 8 * 4 * 128 * 4;  // [wave][query][coordinate], over the digits in the end
 constexpr int AT_RED_FLOATS = 3 * 8 * 4;  // [maxima | norm maxima | sums][wave][4]
 
-// dynamic LDS: digits, exchange area (or, before them in time, what the scoring body needs), then the
-// reduction scratch, which is written while other wavefronts may still be scoring
-// (two: a second set of weight digits and one more plane: the signs of Alg. 2, or the top plane of instance hi)
-__host__ __device__ constexpr int attend128_work_bytes(int kb, int vb, bool two, bool fused, int tiles) {
-  const int xch = (vb + (two ? 1 : 0)) * at_xch_bytes(tiles);
-  const int own = (two ? 2 : 1) * at_wd_bytes(tiles) + (xch > AT_FSUM_BYTES ? xch : AT_FSUM_BYTES);
-  return fused && score128_lds(kb) > own ? score128_lds(kb) : own;
+// dynamic LDS: what the scoring body needs, then the digits and at last the sums; words; the reduction scratch, which like the words is
+// written while other wavefronts may still be scoring
+__host__ __device__ constexpr int attend128_first_bytes(int kb, int vb, bool two, bool fused, int tiles) {
+  const int sets = two ? 2 : 1, wd = sets * 8 * at_wd_bytes(at_pass_keys(tiles, at_planes(vb, two), two));
+  const int own = wd > sets * AT_FSUM_BYTES ? wd : sets * AT_FSUM_BYTES;
+  return fused && score128_lds(kb) > own ? (score128_lds(kb) + 15) / 16 * 16 : own;
+}
+__host__ __device__ constexpr int attend128_words_bytes(int vb, bool two, int tiles) {
+  return 8 * at_planes(vb, two) * at_plane_words(at_pass_keys(tiles, at_planes(vb, two), two)) * 4;
 }
 __host__ __device__ constexpr int attend128_lds(int kb, int vb, bool two, bool fused, int tiles) {
-  return attend128_work_bytes(kb, vb, two, fused, tiles) + AT_RED_FLOATS * 4;
+  return attend128_first_bytes(kb, vb, two, fused, tiles) + attend128_words_bytes(vb, two, tiles) + AT_RED_FLOATS * 4;
 }
 
+// [0]: the table's mean w0; [S]: what belongs to a plane subset of odd size, -2 h[S] (the operands are halves, and minus where the bit is set)
 struct AttendCoefs {
   float c[16];
 };
@@ -72,26 +88,31 @@ __device__ __forceinline__ float row_sum(float v) {
   return v;
 }
 
-// x[i] bit c (16 rows, 32 columns)  ->  x[c'] bit t = old x[t] bit c' and x[c'] bit 16 + t = old x[t] bit 16 + c':
-// two 16 x 16 transposes, one in each half of the registers
-__device__ __forceinline__ void transpose16x32(uint32_t (&x)[16]) {
-#define TQ_SWAP_STAGE(J, M)                                      \
-  _Pragma("unroll") for (int k = 0; k < 16; ++k) if (!(k & J)) { \
-    const uint32_t a = x[k], b = x[k + J];                       \
-    x[k + J] = ((a >> J) & M) | (b & ~M);                        \
-    x[k] = (a & ~(M << J)) | ((b << J) & (M << J));              \
+// nibble a of x[4 i + b] <-> nibble i of x[4 a + b]: four coordinates stay together
+__device__ __forceinline__ void transpose_nibbles(uint32_t (&x)[32]) {
+#pragma unroll
+  for (int k = 0; k < 16; ++k) {
+    const uint32_t a = x[k], b = x[k + 16];
+    x[k + 16] = __builtin_amdgcn_perm(b, a, 0x07060302u);
+    x[k] = __builtin_amdgcn_perm(b, a, 0x05040100u);
   }
 #pragma unroll
-  for (int k = 0; k < 8; ++k) {  // whole bytes
+  for (int k = 0; k < 32; ++k) {
+    if (k & 8) continue;
     const uint32_t a = x[k], b = x[k + 8];
     x[k + 8] = __builtin_amdgcn_perm(b, a, 0x07030501u);
     x[k] = __builtin_amdgcn_perm(b, a, 0x06020400u);
   }
-  TQ_SWAP_STAGE(4, 0x0F0F0F0Fu)
-  TQ_SWAP_STAGE(2, 0x33333333u)
-  TQ_SWAP_STAGE(1, 0x55555555u)
-#undef TQ_SWAP_STAGE
+#pragma unroll
+  for (int k = 0; k < 32; ++k) {
+    if (k & 4) continue;
+    const uint32_t a = x[k], b = x[k + 4];
+    x[k + 4] = ((a >> 4) & 0x0F0F0F0Fu) | (b & 0xF0F0F0F0u);
+    x[k] = (a & 0x0F0F0F0Fu) | ((b << 4) & 0xF0F0F0F0u);
+  }
 }
+
+typedef float f32x16 __attribute__((ext_vector_type(16)));
 
 // ka: arguments of the scoring body (FUSED only); a: value codes, partial results, and with !FUSED the score matrix
 // VKIND, the kind of value code: 0 = Alg. 1; 1 = Alg. 2 (one more plane: the signs, with weights ... * gamma);
@@ -101,53 +122,101 @@ template <int KB, bool KPROD, int VB, int VKIND, bool FUSED, int TILES>
 __global__ __launch_bounds__(512) void attend128_kernel(const ScoreI8Args ka, const AttendArgs a, const AttendCoefs cf,
                                                         const AttendCoefs cfh) {
   constexpr bool VPROD = VKIND == 1, VSPLIT = VKIND == 2, TWO = VKIND != 0;  // TWO: a second set of weights
-  __shared__ __attribute__((aligned(16))) uint2 expand_s[256 * I8_COPIES];  // byte -> one byte per bit, 32 copies
+  {  // the arguments' lines all at once: a line that is met later is a trip of its own then (0.2 - 0.4 us)
+    const uint32_t* const args = reinterpret_cast<const uint32_t*>((uintptr_t)__builtin_amdgcn_kernarg_segment_ptr());
+    constexpr int LINES = (sizeof(ScoreI8Args) + sizeof(AttendArgs) + 2 * sizeof(AttendCoefs) + 63) / 64;
+    uint32_t first[LINES];
+#pragma unroll
+    for (int i = 0; i < LINES; ++i) first[i] = args[16 * i];
+#pragma unroll
+    for (int i = 0; i < LINES; ++i) asm volatile("" ::"s"(first[i]));
+  }
   extern __shared__ __attribute__((aligned(16))) unsigned char dyn_s[];
-  constexpr int NPL = VB + (TWO ? 1 : 0);  // bit planes of a value code: index planes, then the signs of Alg. 2 / the top plane of instance hi
+  constexpr int NPL = at_planes(VB, TWO);  // bit planes of a value code: index planes, then the signs of Alg. 2 / the top plane of instance hi
+  constexpr int WAVE_KEYS = 16 * TILES, PASS_KEYS = at_pass_keys(TILES, NPL, TWO), PASSES = WAVE_KEYS / PASS_KEYS;
+  constexpr int PT = PASS_KEYS / 16, PB = PASS_KEYS / 32, KK = PASS_KEYS / 64;  // tiles, blocks of 32 keys, k-blocks of 64 keys per pass
   constexpr int NVB = VB > 0 ? VB : 1;
-  constexpr int WAVE_KEYS = 16 * TILES, PASS_KEYS = at_pass_keys(TILES), PASSES = WAVE_KEYS / PASS_KEYS;
-  constexpr int PT = PASS_KEYS / 16, KK = PASS_KEYS / 64;  // tiles (= blocks of 16 keys), k-blocks of 64 keys per pass
-  constexpr int WD_BYTES = at_wd_bytes(TILES), XCH_WORDS = at_xch_bytes(TILES) / 4;
-  constexpr int NPH = 16 / PT;                     // planes the wavefront transposes at a time
-  constexpr int ROUNDS = (NPL + NPH - 1) / NPH;    // planes a transposing lane takes: ph, ph + NPH, ...
+  constexpr int ROW = at_row_bytes(PASS_KEYS), WD_BYTES = at_wd_bytes(PASS_KEYS), PLANE_WORDS = at_plane_words(PASS_KEYS);
+  static_assert(4 * PB * NPL <= 64, "a block, a group and a plane per lane");
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int col = lane & 15;  // key within a tile; B column (coordinate within a block of 16); A row (query, digit)
-  const int kc = lane >> 4;   // query of this lane's logits and sums; k-chunk (16 keys of a k-block)
+  const int col = lane & 15;  // key within a tile
+  const int kc = lane >> 4;   // query of this lane's logits
+  const int l32 = lane & 31, h = lane >> 5;  // matrix instructions: row (query, digit) or column (coordinate of a group), half of the 64 keys
   const int chunk = blockIdx.x, group = blockIdx.y, q0 = blockIdx.z * 4;
-  constexpr int WD_ALL = (TWO ? 2 : 1) * WD_BYTES;
-  static_assert(!VPROD || WD_ALL >= AT_FSUM_BYTES, "the sums of the sign term lie over the digits");
-  unsigned char* const wd = dyn_s + wave * (4 * 4 * PASS_KEYS);  // digits of exp(.) nu; + WD_BYTES: of exp(.) nu gamma
-  uint32_t* const xch = reinterpret_cast<uint32_t*>(dyn_s + WD_ALL) + wave * (PT * 64);  // + plane * XCH_WORDS
-  float* const fsum_s = reinterpret_cast<float*>(dyn_s + WD_ALL);  // [8][4][128], over the exchange area
-  float* const fsumz_s = reinterpret_cast<float*>(dyn_s);          // the same for the sign sums, over the digits
-  float* const red_s = reinterpret_cast<float*>(dyn_s + attend128_work_bytes(KB, VB, TWO, FUSED, TILES));  // [3][8][4]
+  constexpr int FIRST = attend128_first_bytes(KB, VB, TWO, FUSED, TILES);
+  unsigned char* const wd = dyn_s + wave * WD_BYTES;  // digits of exp(.) nu; + 8 WD_BYTES: of exp(.) nu gamma / nu_hi
+  uint32_t* const words = reinterpret_cast<uint32_t*>(dyn_s + FIRST) + wave * (NPL * PLANE_WORDS);  // + plane * PLANE_WORDS
+  float* const fsum_s = reinterpret_cast<float*>(dyn_s);  // [8][4][128], over the digits
+  float* const fsumz_s = fsum_s + AT_FSUM_BYTES / 4;      // the same for the sign sums
+  float* const red_s = reinterpret_cast<float*>(dyn_s + FIRST + attend128_words_bytes(VB, TWO, TILES));  // [3][8][4]
 
   const int64_t gbase = (int64_t)group * a.group_stride;
   const int64_t wave_key0 = ((int64_t)chunk * 8 + wave) * WAVE_KEYS;
-  // transposing role: block kb of 16 keys, coordinate group tg, planes ph, ph + NPH, ...
-  const int kb = lane & (PT - 1), tg = (lane / PT) & 3, ph = lane / (4 * PT);
+  // transposing role: block kb of 32 keys, coordinate group tg, a plane.  Nibble i of the transposed word 4 a + b is to be key 8 b + i
+  // (word t of the lane: key 8 (t % 4) + t / 4): eight consecutive keys, as the digits lie, make one dword of an operand, the bit of
+  // the nibble being the coordinate's.
+  const int kb = lane & (PB - 1), tg = (lane / PB) & 3, plane = lane / (4 * PB);
 
-  uint32_t vw[ROUNDS][16];
+  uint32_t vw[32];
+  const bool full = wave_key0 + WAVE_KEYS <= a.n;  // uniform: no key of this wavefront is past the end
+  // the 16-byte pieces of the wavefront's rows, as they lie in memory; through its words' place in LDS to the lanes that transpose them
+  // (lanes that fetch their own words touch every line four times: scoring ended 2 us later).  Two instances: rows are no whole pieces.
+  typedef uint32_t piece __attribute__((ext_vector_type(4), aligned(4)));  // (the arrays are the caller's)
+  constexpr int IP = VSPLIT ? 0 : PASS_KEYS * VB / 64, ZP = VPROD ? PASS_KEYS / 64 : 0;  // pieces per lane: index planes, signs
+  constexpr int Z_AT = PASS_KEYS * VB * 4 + PB * VB * 4;  // words of the index planes with 4 VB more per block of 32 keys (banks)
+  piece pi[IP > 0 ? IP : 1], pz[ZP > 0 ? ZP : 1];
   auto load_codes = [&](int ps) {
-    const int64_t k0 = wave_key0 + ps * PASS_KEYS + 16 * kb;
+    if constexpr (!VSPLIT) {
+      const int64_t row0 = wave_key0 + ps * PASS_KEYS, rows = a.n - row0;  // keys past the end have weight 0: the last piece again
+      auto get = [&](const uint32_t* src, int per_row, int p) {
+        const int64_t last = rows * per_row - 1;
+        const int64_t at = full || p <= last ? p : last;
+        return *reinterpret_cast<const piece*>(src + ((gbase + row0) * per_row + at) * 4);
+      };
 #pragma unroll
-    for (int r = 0; r < ROUNDS; ++r) {
-      const int plane = ph + NPH * r;
-      // an odd number of planes: the last round has work for half the lanes only
+      for (int i = 0; i < IP; ++i) pi[i] = get(a.idx, VB, i * 64 + lane);
 #pragma unroll
-      for (int i = 0; i < 16; ++i) {
-        const int64_t key = k0 + i;
-        const int64_t row = gbase + (key < a.n ? key : a.n - 1);  // clamped: such keys have weight 0
-        if (VSPLIT) {
-          const bool thi = tg < a.gs_hi;
-          const int wpr = 4 * VB + a.gs_hi, woff = thi ? tg * (VB + 1) : a.gs_hi + tg * VB;
-          vw[r][i] = plane < VB + (thi ? 1 : 0) ? a.idx[row * wpr + woff + plane] : 0u;  // no such plane: all-zero mask
-        } else {
-          vw[r][i] = plane < VB ? a.idx[row * (4 * VB) + tg * VB + plane] : (VPROD && plane == VB) ? a.qjl[row * 4 + tg] : 0u;
-        }
+      for (int i = 0; i < ZP; ++i) pz[i] = get(a.qjl, 1, i * 64 + lane);
+    } else {
+      const int64_t k0 = wave_key0 + ps * PASS_KEYS + 32 * kb;
+      const bool thi = tg < a.gs_hi;
+      const int wpr = 4 * VB + a.gs_hi, off = (thi ? tg * (VB + 1) : a.gs_hi + tg * VB) + plane;
+      const uint32_t* const src = a.idx + (gbase + (k0 < a.n ? k0 : a.n - 1)) * wpr + off;
+      const int last = k0 < a.n ? (int)(a.n - 1 - k0 < 31 ? a.n - 1 - k0 : 31) : 0;
+      // (asked for in the order of the keys: neighbours share a line)
+#pragma unroll
+      for (int k = 0; k < 32; ++k) vw[4 * (k & 7) + (k >> 3)] = plane < VB + (thi ? 1 : 0) ? src[(k < last ? k : last) * wpr] : 0u;  // no such plane: zeros
+    }
+  };
+  auto take_codes = [&] {
+    if constexpr (!VSPLIT) {
+#pragma unroll
+      for (int i = 0; i < IP; ++i) {
+        const int p = i * 64 + lane;
+        *reinterpret_cast<u32x4*>(words + 4 * (p + p / (32 * NVB) * NVB)) = pi[i];
       }
+#pragma unroll
+      for (int i = 0; i < ZP; ++i) {
+        const int p = i * 64 + lane;
+        *reinterpret_cast<u32x4*>(words + Z_AT + 4 * (p + p / 32)) = pz[i];
+      }
+      const bool sign = VPROD && plane == VB;
+      const int step = sign ? 4 : 4 * VB;  // words from one key's to the next key's
+      const uint32_t* const src = words + (sign ? Z_AT + tg : tg * VB + (plane < NPL ? plane : 0)) + kb * 33 * step;
+#pragma unroll
+      for (int k = 0; k < 32; ++k) vw[4 * (k & 7) + (k >> 3)] = src[k * step];
+    }
+  };
+  auto put_words = [&] {
+    take_codes();
+    transpose_nibbles(vw);
+    if (4 * PB * NPL == 64 || plane < NPL) {
+      // the 16-byte pieces of a row of 32 words in an order of the lane's own: a store meets every bank equally often
+      uint32_t* const row = words + plane * PLANE_WORDS + (kb >> 1) * AT_PAIR_WORDS + (kb & 1) * AT_BLOCK_WORDS + tg * 32;
+#pragma unroll
+      for (int c = 0; c < 8; ++c) *reinterpret_cast<uint4*>(row + 4 * (c ^ (lane & 7))) = make_uint4(vw[4 * c], vw[4 * c + 1], vw[4 * c + 2], vw[4 * c + 3]);
     }
   };
 
@@ -168,35 +237,29 @@ __global__ __launch_bounds__(512) void attend128_kernel(const ScoreI8Args ka, co
   }
   // the first pass's value codes travel while the keys are scored, where the registers allow it
   constexpr bool EARLY = !FUSED || KB + (KPROD ? 1 : 0) <= 4;
-  if (EARLY) load_codes(0);
-
   // ---- logits: lane (kc, col) holds those of (query q0 + kc, key wave_key0 + 16 t + col), t < TILES ----
   // (kept in units of log 2, so that the weights are one v_exp_f32 each)
   float lg[TILES];
   const float scale2 = a.scale * 1.44269504088896341f;
 #pragma unroll
   for (int t = 0; t < TILES; ++t) lg[t] = -INFINITY;
-  // the expansion table of the read-out, while the key codes and the matrices are on their way (behind the scoring it was 0.2 us of a call)
-  auto fill_table = [&] {
-    const uint32_t lo = (((uint32_t)tid >> 5) * 0x00204081u) & 0x01010101u;
-#pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      const uint32_t hi = ((uint32_t)i * 0x00204081u) & 0x01010101u;
-      expand_s[tid + 512 * i] = make_uint2(lo, hi);
-    }
-  };
   if (FUSED) {
     auto sink = [&](int t, float score, bool key_live) { lg[t] = key_live ? scale2 * score : -INFINITY; };
-    score128_body<KB, KPROD, TILES>(ka, dyn_s, sink, fill_table);
+    // (the value codes behind the first key codes and the matrices, which are due earlier)
+    score128_body<KB, KPROD, TILES>(ka, dyn_s, sink, [&] {
+      if (EARLY) load_codes(0);
+    });
+  __builtin_amdgcn_sched_barrier(0);
   } else {
-    fill_table();
     const int64_t qrow = (int64_t)group * a.q_per_group + (q0 + kc < a.q_per_group ? q0 + kc : q0);
     const float* srow = a.scores + qrow * a.lds + wave_key0 + col;
 #pragma unroll
     for (int t = 0; t < TILES; ++t)
       if (wave_key0 + 16 * t + col < a.n) lg[t] = scale2 * srow[16 * t];
   }
-  if (!EARLY) load_codes(0);
+  if (!EARLY || !FUSED) load_codes(0);
+  __builtin_amdgcn_sched_barrier(0);
+  put_words();  // (in front of the barrier that waits for the last wavefront's scores)
 
   // ---- chunk maxima: logits per query, value norm ---------------------------------------------
   {
@@ -205,11 +268,11 @@ __global__ __launch_bounds__(512) void attend128_kernel(const ScoreI8Args ka, co
     for (int t = 1; t < TILES; ++t) v = fmaxf(v, lg[t]);
     v = row_max(v);
     if (col == 0) red_s[wave * 4 + kc] = v;
-    float nv = nuv[0], gv = ngv[0];
+    float nv = fabsf(nuv[0]), gv = fabsf(ngv[0]);
 #pragma unroll
     for (int e = 1; e < NE; ++e) {
-      nv = fmaxf(nv, nuv[e]);
-      gv = fmaxf(gv, ngv[e]);
+      nv = fmaxf(nv, fabsf(nuv[e]));
+      gv = fmaxf(gv, fabsf(ngv[e]));
     }
     const float nm = wave_max(nv);
     if (lane == 1) red_s[32 + wave * 4] = nm;
@@ -219,6 +282,7 @@ __global__ __launch_bounds__(512) void attend128_kernel(const ScoreI8Args ka, co
     }
   }
   __syncthreads();  // also: every wavefront is done with the scoring body's LDS
+  __builtin_amdgcn_sched_barrier(0);
   float m = -INFINITY, numax = 0.f, ngmax = 0.f;
 #pragma unroll
   for (int w = 0; w < 8; ++w) {
@@ -229,149 +293,172 @@ __global__ __launch_bounds__(512) void attend128_kernel(const ScoreI8Args ka, co
   int enu = 0, eng = 0;
   if (numax > 0.f) (void)frexpf(numax, &enu);  // numax = f * 2^enu, f in [0.5, 1)
   if (ngmax > 0.f) (void)frexpf(ngmax, &eng);
-  const float wscale = ldexpf(1.f, 26 - enu);  // weights exp(logit - m) * nu * wscale <= 2^26
-  const float zscale = ldexpf(1.f, 26 - eng);
+  // |weights exp(logit - m) * nu * wscale| <= 2^28
+#pragma unroll
+  for (int e = 0; e < NE; ++e) nuv[e] *= ldexpf(1.f, 28 - enu), ngv[e] *= ldexpf(1.f, 28 - eng);
+  auto rounded = [](float v) {  // to the nearest integer, in one instruction
+    int i;
+    asm("v_cvt_rpi_i32_f32 %0, %1" : "=v"(i) : "v"(v));
+    return i;
+  };
 
-  const uint32_t copy_off = (uint32_t)(lane & (I8_COPIES - 1)) * 8u;
-  const char* const table = reinterpret_cast<const char*>(expand_s);
-  auto expand16 = [&](uint32_t w, int h) -> v4i {  // bits [16 h, 16 h + 16) of w -> 16 bytes of 0/1
-    const uint32_t o0 = __builtin_amdgcn_perm(w, copy_off, h ? 0x0c0c0600u : 0x0c0c0400u);
-    const uint32_t o1 = __builtin_amdgcn_perm(w, copy_off, h ? 0x0c0c0700u : 0x0c0c0500u);
-    const uint2 lo = *reinterpret_cast<const uint2*>(table + o0);
-    const uint2 hi = *reinterpret_cast<const uint2*>(table + o1);
-    return v4i{(int)lo.x, (int)lo.y, (int)hi.x, (int)hi.y};
-  };
-  auto digits_sum = [&](const v4i& acc) -> float {  // D0 + 2^8 D1 + 2^16 D2 + 2^24 D3; |D0 .. D2| <= 2^14
-    return fmaf((float)acc[3], 16777216.f, (float)(acc[0] + (acc[1] << 8) + (acc[2] << 16)));
-  };
-  // A weight of at most 26 bits as four balanced base-256 digits (the first three of -128 .. 127, which is the integer's bytes
-  // after adding 128 to each and taking it off again), and of these, by a transposition among the four lanes of a quad, digit
-  // lane % 4 of the quad's four keys in one word: one store in place of a byte per digit, and a third of the instructions.
+  // The eight base-16 digits of a weight (the top one with a sign), transposed among the four lanes of a quad: lane i gets digits 2 i and
+  // 2 i + 1 of the quad's four keys in a word each.
   const uint32_t sel1 = lane & 1 ? 0x03070105u : 0x06020400u, sel2 = lane & 2 ? 0x03020706u : 0x05040100u;
-  auto four_digits = [&](uint32_t Q) -> uint32_t {
-    uint32_t w = (Q + 0x00808080u) ^ 0x00808080u;
-    w = __builtin_amdgcn_perm((uint32_t)dpp_move<0xB1>((int)w), w, sel1);
-    return __builtin_amdgcn_perm((uint32_t)dpp_move<0x4E>((int)w), w, sel2);
+  auto quad_transpose = [&](uint32_t w) -> uint32_t {
+    w = __builtin_amdgcn_perm((uint32_t)__builtin_amdgcn_mov_dpp((int)w, 0xB1, 0xF, 0xF, true), w, sel1);
+    return __builtin_amdgcn_perm((uint32_t)__builtin_amdgcn_mov_dpp((int)w, 0x4E, 0xF, 0xF, true), w, sel2);
+  };
+  auto put_digits = [&](unsigned char* o, int Q) {
+    *reinterpret_cast<uint32_t*>(o) = quad_transpose((uint32_t)Q & 0x0F0F0F0Fu);
+    *reinterpret_cast<uint32_t*>(o + 4 * ROW) = quad_transpose((uint32_t)(Q >> 4) & 0x810F0F0Fu);  // |Q| <= 2^28: the top digit is -1, 0 or 1
   };
 
-  float f[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};  // coordinate 16 cb + col of query kc
-  float ftot = 0.f;                                         // sum of the integer weights of query kc
-  float fz[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};  // VPROD: the same two for the weights of the sign term
-  float fztot = 0.f;
+  // the half-waves hold the digits 0, 2, 4, 6 and 1, 3, 5, 7 of the sums
+  const float hf = h ? 16.f : 1.f;
+  float f[4][4], fz[4][4];  // [coordinate group][query]: coordinate 32 g + l32; VPROD: the sums of the sign term
+#pragma unroll
+  for (int g = 0; g < 4; ++g)
+#pragma unroll
+    for (int k = 0; k < 4; ++k) f[g][k] = fz[g][k] = 0.f;
   float lsum = 0.f;
-  const v4i ones = v4i{0x01010101, 0x01010101, 0x01010101, 0x01010101};
+  // words with coordinate 32 g + l32 for the 32 keys 64 kk + 32 h ..: see put_words
+  uint32_t read_at[4];
+#pragma unroll
+  for (int x = 0; x < 4; ++x) read_at[x] = h * AT_BLOCK_WORDS + 4 * (((l32 >> 2) ^ h) ^ (2 * x));
+  // a wavefront's digits and words are its own, and LDS takes a wavefront's instructions in order
+  auto wave_sync = [] {
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_wave_barrier();
+  };
+  // 32 keys as fp4 operands +-0.5: minus where the bit is set
+  uint32_t halves = 0x11111111u;  // in a register that the compiler does not know: one v_and_or_b32 takes no two constants
+  asm volatile("" : "+v"(halves));
+  const int to_top = 3 - (l32 & 3);
+  auto signs = [halves, to_top](const u32x4& w) -> v8i {
+    auto of = [halves, to_top](uint32_t v) { return (int)(((v << to_top) & 0x88888888u) | halves); };
+    const v4i b = v4i{of(w[0]), of(w[1]), of(w[2]), of(w[3])};
+    return __builtin_shufflevector(b, b, 0, 1, 2, 3, -1, -1, -1, -1);  // fp4: four registers
+  };
 
 #pragma unroll
   for (int ps = 0; ps < PASSES; ++ps) {
-    // weights of this lane's (query, key) pairs -> four base-256 digits
+    if (ps > 0) put_words();
+    if (ps + 1 < PASSES) load_codes(ps + 1);
+    // weights of this lane's (query, key) pairs -> digits
 #pragma unroll
     for (int tt = 0; tt < PT; ++tt) {
       const int t = PT * ps + tt;
       const float nu = __int_as_float(__builtin_amdgcn_ds_bpermute(4 * (16 * (t & 3) + col), __float_as_int(nuv[t >> 2])));
       const float p = __builtin_amdgcn_exp2f(lg[t] - m);  // 0 for keys past the end (logit -inf)
       lsum += p;
-      uint32_t* const o = reinterpret_cast<uint32_t*>(wd + (kc * 4 + (col & 3)) * PASS_KEYS + 16 * tt + (col & 12));
-      *o = four_digits((uint32_t)__float2int_rn(p * nu * wscale));
+      unsigned char* const o = wd + (8 * kc + (col & 3)) * ROW + 16 * tt + (col & 12);
+      put_digits(o, rounded(p * nu));
       if (TWO) {
         const float ng = __int_as_float(__builtin_amdgcn_ds_bpermute(4 * (16 * (t & 3) + col), __float_as_int(ngv[t >> 2])));
-        o[WD_BYTES / 4] = four_digits((uint32_t)__float2int_rn(p * ng * zscale));
+        put_digits(o + 8 * WD_BYTES, rounded(p * ng));
       }
     }
-    // value code words: 16 keys x 32 coordinates -> 32 coordinates x 16 keys
-#pragma unroll
-    for (int r = 0; r < ROUNDS; ++r) {
-      const int plane = ph + NPH * r;
-      transpose16x32(vw[r]);
-      if (plane < NPL) {
-        // word c: low half = coordinate 32 tg + c, high half = coordinate 32 tg + 16 + c.  Odd key blocks swap
-        // the halves of a row of 32 words, which keeps the reads below free of bank conflicts.
-        uint4* dst = reinterpret_cast<uint4*>(xch + plane * XCH_WORDS + kb * 64 + ((tg ^ (kb & 1)) * 16));
-#pragma unroll
-        for (int c = 0; c < 4; ++c) dst[c] = make_uint4(vw[r][4 * c], vw[r][4 * c + 1], vw[r][4 * c + 2], vw[r][4 * c + 3]);
-      }
-    }
-    if (ps + 1 < PASSES) load_codes(ps + 1);
-    __syncthreads();
+    wave_sync();
 
-    v4i aop[KK], zop[KK];
+  __builtin_amdgcn_sched_barrier(0);
+    // an fp8 operand's 32 values of a lane are k = 16 h .. and 32 + 16 h .., an fp4 operand's k = 32 h ..
+    v8i aop[KK], zop[KK];
+    auto digits_of = [&](const unsigned char* w, int kk) -> v8i {
+      const unsigned char* const r = w + l32 * ROW + kk * 64 + 16 * h;
+      const v4i lo = *reinterpret_cast<const v4i*>(r), hi = *reinterpret_cast<const v4i*>(r + 32);
+      return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+    };
 #pragma unroll
     for (int kk = 0; kk < KK; ++kk) {
-      aop[kk] = *reinterpret_cast<const v4i*>(wd + col * PASS_KEYS + kk * 64 + kc * 16);
-      if (TWO) zop[kk] = *reinterpret_cast<const v4i*>(wd + WD_BYTES + col * PASS_KEYS + kk * 64 + kc * 16);
+      aop[kk] = digits_of(wd, kk);
+      if (VSPLIT) zop[kk] = digits_of(wd + 8 * WD_BYTES, kk);
     }
-    {
-      v4i tot = v4i{0, 0, 0, 0}, ztot = v4i{0, 0, 0, 0};
+    auto words_of = [&](int pl, int g, int kk) {
+      return *reinterpret_cast<const u32x4*>(words + pl * PLANE_WORDS + kk * AT_PAIR_WORDS + g * 32 + read_at[((2 * kk + PB * g) & 7) / 2]);
+    };
+    // sums of a coordinate group with these weights and signs, added to o with a factor
+    auto add_sums = [&](const v8i (&wop)[KK], auto sign_of, float factor, float (&o)[4]) {
+      f32x16 acc;
 #pragma unroll
-      for (int kk = 0; kk < KK; ++kk) {
-        tot = __builtin_amdgcn_mfma_i32_16x16x64_i8(aop[kk], ones, tot, 0, 0, 0);
-        if (TWO) ztot = __builtin_amdgcn_mfma_i32_16x16x64_i8(zop[kk], ones, ztot, 0, 0, 0);
-      }
-      ftot += digits_sum(tot);
-      if (TWO) fztot += digits_sum(ztot);
-    }
+      for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+#pragma unroll
+      for (int kk = 0; kk < KK; ++kk)  // (the scale 2^9 makes a digit the integer it stands for)
+        acc = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(wop[kk], sign_of(kk), acc, 0, 4, 0, 136, 0, 127);
+#pragma unroll
+      for (int k = 0; k < 4; ++k)
+        o[k] = fmaf(factor, fmaf(fmaf(acc[4 * k + 3], 256.f, acc[4 * k + 2]), 65536.f, fmaf(acc[4 * k + 1], 256.f, acc[4 * k])), o[k]);
+    };
 #pragma unroll
     for (int g = 0; g < 4; ++g) {
-      constexpr int NPW = VSPLIT ? VB + 1 : NVB;  // index planes read (instance lo: the top one is all zero)
-      uint32_t pw[KK][NPW], pz[KK];
+      __builtin_amdgcn_sched_barrier(0);  // one group's sums at a time (registers)
+      constexpr int NPI = VSPLIT ? VB + 1 : NVB;  // index planes (instance lo: the top one is all zero)
+      u32x4 pw[KK][NPI];
 #pragma unroll
-      for (int kk = 0; kk < KK; ++kk) {
-        pz[kk] = 0u;
+      for (int kk = 0; kk < KK; ++kk)
 #pragma unroll
-        for (int pl = 0; pl < (VSPLIT ? VB + 1 : VB); ++pl)
-          pw[kk][pl] = xch[pl * XCH_WORDS + (4 * kk + kc) * 64 + ((g ^ (kc & 1)) * 16) + col];
-        if (VPROD) pz[kk] = xch[VB * XCH_WORDS + (4 * kk + kc) * 64 + ((g ^ (kc & 1)) * 16) + col];
-      }
-      // masked sums of one coordinate group: plane subsets of odd size, weights and table of the group's instance
-      auto terms = [&](auto planes_c, const v4i (&wop)[KK], const AttendCoefs& tab) {
+        for (int pl = 0; pl < (VSPLIT ? VB + 1 : VB); ++pl) pw[kk][pl] = words_of(pl, g, kk);
+      // signs of one coordinate group: plane subsets of odd size, weights and table of the group's instance
+      auto terms = [&](auto planes_c, const v8i (&wop)[KK], const AttendCoefs& tab) {
         constexpr int NP = decltype(planes_c)::value;
 #pragma unroll
         for (int mset = 1; mset < (1 << NP); ++mset) {
           if (!i8_term(mset)) continue;
-          uint32_t mk[KK];
-#pragma unroll
-          for (int kk = 0; kk < KK; ++kk) {
-            mk[kk] = 0u;
+          if (NPL > 2) __builtin_amdgcn_sched_barrier(0);  // one sum at a time
+          add_sums(wop, [&](int kk) {
+            u32x4 x = u32x4{0u, 0u, 0u, 0u};
 #pragma unroll
             for (int pl = 0; pl < NP; ++pl)
-              if (mset & (1 << pl)) mk[kk] ^= pw[kk][pl];
-          }
-#pragma unroll
-          for (int h = 0; h < 2; ++h) {
-            v4i acc = v4i{0, 0, 0, 0};
-#pragma unroll
-            for (int kk = 0; kk < KK; ++kk) acc = __builtin_amdgcn_mfma_i32_16x16x64_i8(wop[kk], expand16(mk[kk], h), acc, 0, 0, 0);
-            f[2 * g + h] = fmaf(tab.c[mset], digits_sum(acc), f[2 * g + h]);
-          }
+              if (mset & (1 << pl)) x ^= pw[kk][pl];
+            return signs(x);
+          }, hf * tab.c[mset], f[g]);
         }
       };
       if (VSPLIT && g < a.gs_hi) terms(std::integral_constant<int, VB + 1>{}, zop, cfh);  // uniform
       else terms(std::integral_constant<int, VB>{}, aop, cf);
-      if (VPROD) {
+    }
+    if constexpr (VPROD) {
 #pragma unroll
-        for (int h = 0; h < 2; ++h) {
-          v4i acc = v4i{0, 0, 0, 0};
+      for (int kk = 0; kk < KK; ++kk) zop[kk] = digits_of(wd + 8 * WD_BYTES, kk);
 #pragma unroll
-          for (int kk = 0; kk < KK; ++kk) acc = __builtin_amdgcn_mfma_i32_16x16x64_i8(zop[kk], expand16(pz[kk], h), acc, 0, 0, 0);
-          fz[2 * g + h] += digits_sum(acc);
-        }
+      for (int g = 0; g < 4; ++g) {
+        __builtin_amdgcn_sched_barrier(0);
+        add_sums(zop, [&](int kk) { return signs(words_of(VB, g, kk)); }, -2.f * hf, fz[g]);
       }
     }
-    __syncthreads();  // the digit and exchange areas are rewritten by the next pass / the final sums
+    if (cf.c[0] != 0.f || (VSPLIT && cfh.c[0] != 0.f)) {  // tables whose mean is not 0 (uniform; behind the sums, which it would tear apart)
+      float w[4] = {0.f, 0.f, 0.f, 0.f}, wh[4] = {0.f, 0.f, 0.f, 0.f};
+      add_sums(aop, [&](int) { return signs(u32x4{0u, 0u, 0u, 0u}); }, 2.f * hf * cf.c[0], w);
+      if constexpr (VSPLIT) add_sums(zop, [&](int) { return signs(u32x4{0u, 0u, 0u, 0u}); }, 2.f * hf * cfh.c[0], wh);
+#pragma unroll
+      for (int g = 0; g < 4; ++g)
+#pragma unroll
+        for (int k = 0; k < 4; ++k) f[g][k] += VSPLIT && g < a.gs_hi ? wh[k] : w[k];
+    }
+    wave_sync();
   }
+  __builtin_amdgcn_sched_barrier(0);
+  __syncthreads();  // the final sums go over the digits
+  __builtin_amdgcn_sched_barrier(0);
 
   // ---- join the wavefronts ------------------------------------------------------------------------
   lsum = row_sum(lsum);
   if (col == 0) red_s[64 + wave * 4 + kc] = lsum;
+  // the half-waves' parts of a sum together: half h then has those of queries k + 2 h
+  auto join = [&](float lo, float hi) {
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(lo), __float_as_uint(hi), false, false);
+    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+  };
 #pragma unroll
-  for (int cb = 0; cb < 8; ++cb) {
-    if (VSPLIT)  // each instance has its own table, weight total and weight scale
-      fsum_s[(wave * 4 + kc) * 128 + 16 * cb + col] = (cb >> 1) < a.gs_hi ? fmaf(cfh.c[0], fztot, f[cb]) * ldexpf(1.f, eng - 26)
-                                                                           : fmaf(cf.c[0], ftot, f[cb]) * ldexpf(1.f, enu - 26);
-    else
-      fsum_s[(wave * 4 + kc) * 128 + 16 * cb + col] = fmaf(cf.c[0], ftot, f[cb]);
-    // sum of w z over the keys, z = +-1 from the sign bits: twice the masked sum minus the sum of the weights
-    if (VPROD) fsumz_s[(wave * 4 + kc) * 128 + 16 * cb + col] = fmaf(2.f, fz[cb], -fztot);
-  }
+  for (int g = 0; g < 4; ++g)
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+      const int at = (wave * 4 + k + 2 * h) * 128 + 32 * g + l32;
+      float v = join(f[g][k], f[g][k + 2]);
+      if (VSPLIT) v *= ldexpf(1.f, (g < a.gs_hi ? eng : enu) - 28);  // each instance has its own weight scale
+      fsum_s[at] = v;
+      if (VPROD) fsumz_s[at] = join(fz[g][k], fz[g][k + 2]);
+    }
   __syncthreads();
   const int qi = tid >> 7, j = tid & 127;
   if (q0 + qi < a.q_per_group) {
@@ -382,8 +469,8 @@ __global__ __launch_bounds__(512) void attend128_kernel(const ScoreI8Args ka, co
       if (VPROD) accz += fsumz_s[(w * 4 + qi) * 128 + j];
     }
     float* o = a.part + (((int64_t)group * a.q_per_group + q0 + qi) * a.nchunks + chunk) * attend_part_stride(128);
-    o[4 + j] = VSPLIT ? acc : acc * ldexpf(1.f, enu - 26);
-    o[4 + 128 + j] = VPROD ? accz * ldexpf(1.f, eng - 26) : 0.f;
+    o[4 + j] = VSPLIT ? acc : acc * ldexpf(1.f, enu - 28);
+    o[4 + 128 + j] = VPROD ? accz * ldexpf(1.f, eng - 28) : 0.f;
     if (j == 0) {
       float l = 0.f, mq = -INFINITY;
 #pragma unroll
@@ -401,7 +488,7 @@ template <int KB, bool KPROD, int VB, int VKIND, bool FUSED, int TILES>
 hipError_t launch_attend128_tiles(const ScoreI8Args& ka, const AttendArgs& a, const AttendCoefs& cf, const AttendCoefs& cfh,
                                 int n_groups, hipStream_t s) {
   constexpr int lds = attend128_lds(KB, VB, VKIND != 0, FUSED, TILES);
-  static_assert(I8_TABLE_BYTES + lds <= 160 * 1024, "LDS budget");
+  static_assert(lds <= 160 * 1024, "LDS budget");
   static LdsLimit lds_limit;  // per instantiation: the limit is raised once per device
   if (const hipError_t e = raise_lds_limit(lds_limit, reinterpret_cast<const void*>(&attend128_kernel<KB, KPROD, VB, VKIND, FUSED, TILES>), lds); e != hipSuccess) return e;
   const dim3 grid(a.nchunks, n_groups, (a.q_per_group + 3) / 4);

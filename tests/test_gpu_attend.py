@@ -102,6 +102,43 @@ def test_attend_with_scores_from_a_scoring_call(d, kb, kprod, vb, vprod, n_group
     run_attend(d, kb, kprod, vb, vprod, n_groups, qpg, npg, False)
 
 
+EDGES = [
+    # value bits_mse, value prod, groups, queries per group, tokens per group: around the blocks of 32 and 64 keys, the passes of 128 and 256
+    # (values of one and two planes, three and more) and the ranges of a wavefront; with 128 groups a workgroup takes 2048 keys, else 512
+    (1, False, 1, 4, 31), (2, False, 1, 4, 33), (3, False, 1, 3, 63), (4, False, 1, 4, 65), (0, True, 1, 4, 127), (1, True, 1, 1, 129),
+    (2, True, 1, 4, 513), (2, False, 128, 1, 2080), (3, False, 128, 1, 2179), (1, True, 128, 2, 2305),
+]
+
+
+@pytest.mark.parametrize("vb,vprod,n_groups,qpg,npg", EDGES)
+def test_attend_at_the_edges_of_blocks_and_passes(vb, vprod, n_groups, qpg, npg):
+    run_attend(128, 2, True, vb, vprod, n_groups, qpg, npg, True)
+
+
+@pytest.mark.parametrize("table", [[0.02, 0.15], [-0.05, 0.03, 0.07, 0.15]])
+def test_attend_with_a_table_that_is_not_centred_and_norms_of_either_sign(table):
+    """A table symmetric about a mean other than zero is what the sums of signs take with one term more; weights are
+    negative where a norm is."""
+    d, npg = 128, 700
+    bits = len(table).bit_length() - 1
+    c32 = np.asarray(table, dtype=np.float32)
+    pk, Pik, Sk, ck = setup(d, 2, True, 100, 200)
+    Piv = o.rotation_from_gaussian(W.gaussian_matrix(d, 300))
+    pv = tq.Params(d, bits, torch.from_numpy(Piv), None, c32, ((c32[1:] + c32[:-1]) / 2).astype(np.float32))
+    rng = np.random.default_rng(5)
+    k_codes, k_dev = random_codes(rng, npg, d, 2, True, 0.3)
+    (idx, _, _, norm), v_dev = random_codes(rng, npg, d, bits, False, 1.0)
+    norm = norm * rng.choice([-1.0, 1.0], size=npg).astype(np.float32)
+    v_dev = (v_dev[0], None, None, dev(norm))
+    q = W.gaussian_queries(4, d, 3, unit=False)
+    scale = 1.0 / math.sqrt(d)
+    kt, vt = dequant(k_codes, Pik, Sk, ck), o.dequant_mse(idx, Piv, c32, norm)
+    out = torch.full((4, d), float("nan"), dtype=torch.float32, device=DEV)
+    tq.tq_attend(pk, pv, dev(q), 1, 4, k_dev, v_dev, npg, scale, out)
+    check_attend(out.cpu().numpy().astype(np.float64), o.attend(q, kt, vt, scale), q, scale, k_codes[3], vt,
+                 o.attend(q, kt, np.eye(npg), scale), d, 1, 4, npg)
+
+
 def run_attend(d, kb, kprod, vb, vprod, n_groups, qpg, npg, key_transposes):
     pk, Pik, Sk, ck = setup(d, kb, kprod, 100, 200)
     pv, Piv, Sv, cv = setup(d, vb, vprod, 300, 400)
