@@ -21,7 +21,7 @@
 #include <cmath>
 
 #include "tq_bf3.h"
-#include "tq_code_gemm.h"
+#include "tq_code_decode.h"
 #include "tq_search.h"
 #include "tq_select.h"
 
@@ -162,18 +162,30 @@ __global__ __launch_bounds__(256) void search_select_kernel(const SelectArgs a) 
   float mx = -__builtin_inff();
   float top[N];
 #pragma unroll
-  for (int i = 0; i < N; ++i) {
-    top[i] = __builtin_nanf("");
-    if (i * 256 < total) {  // uniform
-      const int c = i * 256 + tid;
-      if (c < total) {
-        const int64_t row = a.list_i[q * CAP + c];
-        const float nu = a.norm != nullptr ? a.norm[row] : 1.f;
-        float eps = fabsf(nu) * e1;
-        if (PROD) eps = fmaf(fabsf(nu * (a.kappa * a.gamma[row])), e2, eps);
-        top[i] = a.list_u[q * CAP + c];
-        mx = fmaxf(mx, fmaf(-2.f, eps, top[i]));
-      }
+  for (int i0 = 0; i0 < N; i0 += 4) {
+#pragma unroll
+    for (int i = i0; i < i0 + 4; ++i) top[i] = __builtin_nanf("");
+    if (i0 * 256 >= total) continue;  // uniform
+    // (four of a thread's at a time: one by one they are two trips to memory each)
+    int64_t row[4];
+    float nu[4], ga[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int c = (i0 + i) * 256 + tid, cc = c < total ? c : total - 1;
+      row[i] = a.list_i[q * CAP + cc];
+      top[i0 + i] = a.list_u[q * CAP + cc];
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      nu[i] = a.norm != nullptr ? a.norm[row[i]] : 1.f;
+      ga[i] = PROD ? a.gamma[row[i]] : 0.f;
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      float eps = fabsf(nu[i]) * e1;
+      if (PROD) eps = fmaf(fabsf(nu[i] * (a.kappa * ga[i])), e2, eps);
+      if ((i0 + i) * 256 + tid >= total) top[i0 + i] = __builtin_nanf("");
+      mx = fmaxf(mx, fmaf(-2.f, eps, top[i0 + i]));
     }
   }
   const float bar = kth_of_maxima(mx, k, keys, &bar_s, tid);
@@ -198,12 +210,19 @@ __global__ __launch_bounds__(256) void search_select_kernel(const SelectArgs a) 
     floatx16 acc1, acc2;
 #pragma unroll
     for (int r = 0; r < 16; ++r) acc1[r] = acc2[r] = 0.f;
-    uint32_t w[NB], z = 0u, wn[NB], zn = 0u;
+    // The words of four groups at a time, four to eight ahead of their use: a lane's row is somewhere in memory.  (With one group ahead and
+    // the list above entry by entry: d = 3072, 4 bits, 203163 codes, 70 queries 105 us, 86 so, the whole search 515 -> 444; bound by
+    // the decoding of a wavefront.  Four that decode for one that multiplies, through LDS: the same; eight per query: 72 us there, but 44
+    // for 27 at d = 512 and 972 queries.)
+    constexpr int AHEAD = 4;  // d is a multiple of 128
+    uint32_t w[AHEAD][NB], z[AHEAD], wn[AHEAD][NB], zn[AHEAD];
     auto load = [&](int g) {
-      const int gg = g < gw ? g : gw - 1;
+      const int gg = g < gw ? g : gw - AHEAD;
 #pragma unroll
-      for (int pl = 0; pl < BITS; ++pl) wn[pl] = wi[gg * BITS + pl];
-      if (PROD) zn = wz[gg];
+      for (int u = 0; u < AHEAD; ++u) {
+        if constexpr (BITS > 0) load_plane_words<BITS>(wi + (gg + u) * BITS, wn[u]);
+        if (PROD) zn[u] = wz[gg + u];
+      }
     };
     auto signs = [&](uint32_t bits) -> bf16x8 {
       uint32_t v[4];
@@ -213,44 +232,51 @@ __global__ __launch_bounds__(256) void search_select_kernel(const SelectArgs a) 
       return *reinterpret_cast<const bf16x8*>(&o);
     };
     load(0);
-    for (int g = 0; g < gw; ++g) {
+    for (int g0 = 0; g0 < gw; g0 += AHEAD) {
 #pragma unroll
-      for (int pl = 0; pl < BITS; ++pl) w[pl] = wn[pl];
-      z = zn;
-      load(g + 1);
+      for (int u = 0; u < AHEAD; ++u) {
 #pragma unroll
-      for (int half = 0; half < 2; ++half) {
-        const int off = 16 * half + 8 * h, at = 32 * g + off;
-        auto piece = [&](int seg, int pc) { return *reinterpret_cast<const bf16x8*>(qp + (seg * 2 + pc) * d + at); };
-        if (BITS == 1) {
-          const bf16x8 f = signs(w[0] >> off);
-          acc1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(piece(0, 1), f, acc1, 0, 0, 0);
-          acc1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(piece(0, 0), f, acc1, 0, 0, 0);
-        } else if (BITS > 1) {
-          uint32_t lv[2];
+        for (int pl = 0; pl < BITS; ++pl) w[u][pl] = wn[u][pl];
+        z[u] = PROD ? zn[u] : 0u;
+      }
+      load(g0 + AHEAD);
 #pragma unroll
-          for (int e = 0; e < 2; ++e) {
-            lv[e] = 0u;
+      for (int u = 0; u < AHEAD; ++u) {
+        const int g = g0 + u;
 #pragma unroll
-            for (int pl = 0; pl < BITS; ++pl) lv[e] |= ((((w[pl] >> (off + 4 * e)) & 0xFu) * 0x00204081u) & 0x01010101u) << pl;
+        for (int half = 0; half < 2; ++half) {
+          const int off = 16 * half + 8 * h, at = 32 * g + off;
+          auto piece = [&](int seg, int pc) { return *reinterpret_cast<const bf16x8*>(qp + (seg * 2 + pc) * d + at); };
+          if (BITS == 1) {
+            const bf16x8 f = signs(w[u][0] >> off);
+            acc1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(piece(0, 1), f, acc1, 0, 0, 0);
+            acc1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(piece(0, 0), f, acc1, 0, 0, 0);
+          } else if (BITS > 1) {
+            uint32_t lv[2];
+#pragma unroll
+            for (int e = 0; e < 2; ++e) {
+              lv[e] = 0u;
+#pragma unroll
+              for (int pl = 0; pl < BITS; ++pl) lv[e] |= ((((w[u][pl] >> (off + 4 * e)) & 0xFu) * 0x00204081u) & 0x01010101u) << pl;
+            }
+            u32x4 v1, v2;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+              const uint2 lo = table_s[(lv[e >> 1] >> (16 * (e & 1))) & 0xFFu], hi = table_s[(lv[e >> 1] >> (16 * (e & 1) + 8)) & 0xFFu];
+              v1[e] = __builtin_amdgcn_perm(hi.x, lo.x, 0x05040100u);
+              v2[e] = __builtin_amdgcn_perm(hi.x, lo.x, 0x07060302u);
+            }
+            const bf16x8 f1 = *reinterpret_cast<const bf16x8*>(&v1), f2 = *reinterpret_cast<const bf16x8*>(&v2);
+            const bf16x8 a1 = piece(0, 0);
+            acc1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(piece(0, 1), f1, acc1, 0, 0, 0);
+            acc1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a1, f2, acc1, 0, 0, 0);
+            acc1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a1, f1, acc1, 0, 0, 0);
           }
-          u32x4 v1, v2;
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            const uint2 lo = table_s[(lv[e >> 1] >> (16 * (e & 1))) & 0xFFu], hi = table_s[(lv[e >> 1] >> (16 * (e & 1) + 8)) & 0xFFu];
-            v1[e] = __builtin_amdgcn_perm(hi.x, lo.x, 0x05040100u);
-            v2[e] = __builtin_amdgcn_perm(hi.x, lo.x, 0x07060302u);
+          if (PROD) {
+            const bf16x8 f = signs(z[u] >> off);
+            acc2 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(piece(SEGS - 1, 1), f, acc2, 0, 0, 0);
+            acc2 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(piece(SEGS - 1, 0), f, acc2, 0, 0, 0);
           }
-          const bf16x8 f1 = *reinterpret_cast<const bf16x8*>(&v1), f2 = *reinterpret_cast<const bf16x8*>(&v2);
-          const bf16x8 a1 = piece(0, 0);
-          acc1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(piece(0, 1), f1, acc1, 0, 0, 0);
-          acc1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a1, f2, acc1, 0, 0, 0);
-          acc1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a1, f1, acc1, 0, 0, 0);
-        }
-        if (PROD) {
-          const bf16x8 f = signs(z >> off);
-          acc2 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(piece(SEGS - 1, 1), f, acc2, 0, 0, 0);
-          acc2 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(piece(SEGS - 1, 0), f, acc2, 0, 0, 0);
         }
       }
     }
