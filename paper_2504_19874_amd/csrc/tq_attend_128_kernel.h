@@ -122,15 +122,7 @@ template <int KB, bool KPROD, int VB, int VKIND, bool FUSED, int TILES>
 __global__ __launch_bounds__(512) void attend128_kernel(const ScoreI8Args ka, const AttendArgs a, const AttendCoefs cf,
                                                         const AttendCoefs cfh) {
   constexpr bool VPROD = VKIND == 1, VSPLIT = VKIND == 2, TWO = VKIND != 0;  // TWO: a second set of weights
-  {  // the arguments' lines all at once: a line that is met later is a trip of its own then (0.2 - 0.4 us)
-    const uint32_t* const args = reinterpret_cast<const uint32_t*>((uintptr_t)__builtin_amdgcn_kernarg_segment_ptr());
-    constexpr int LINES = (sizeof(ScoreI8Args) + sizeof(AttendArgs) + 2 * sizeof(AttendCoefs) + 63) / 64;
-    uint32_t first[LINES];
-#pragma unroll
-    for (int i = 0; i < LINES; ++i) first[i] = args[16 * i];
-#pragma unroll
-    for (int i = 0; i < LINES; ++i) asm volatile("" ::"s"(first[i]));
-  }
+  fetch_arguments<sizeof(ScoreI8Args) + sizeof(AttendArgs) + 2 * sizeof(AttendCoefs)>();
   extern __shared__ __attribute__((aligned(16))) unsigned char dyn_s[];
   constexpr int NPL = at_planes(VB, TWO);  // bit planes of a value code: index planes, then the signs of Alg. 2 / the top plane of instance hi
   constexpr int WAVE_KEYS = 16 * TILES, PASS_KEYS = at_pass_keys(TILES, NPL, TWO), PASSES = WAVE_KEYS / PASS_KEYS;

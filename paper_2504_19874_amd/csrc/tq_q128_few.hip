@@ -58,6 +58,7 @@ constexpr int ROW_LD = 136;  // fp16 values per row in LDS: consecutive rows sta
 
 template <int BITS, bool PROD, bool MIXED>
 __global__ __launch_bounds__(512, 4) void q128_few_kernel(const QuantFewArgs a) {
+  if (!MIXED) fetch_arguments<sizeof(QuantFewArgs)>();
   __shared__ __attribute__((aligned(16))) unsigned short x_s[2][16 * ROW_LD];              // by parity of the block
   __shared__ __attribute__((aligned(16))) unsigned short e_s[PROD ? 2 : 1][PROD ? 16 * ROW_LD : 8];  // pieces of the residual, columns permuted
   __shared__ float nu_s[2][16], unit_s[2][16];  // norm; scaled value -> value (of the unit vector, unless MIXED)

@@ -6,6 +6,7 @@ namespace tq {
 
 template <int BITS, bool PROD, int TILES>
 __global__ __launch_bounds__(512) void score_i8_128_kernel(const ScoreI8Args a) {
+  fetch_arguments<sizeof(ScoreI8Args)>();
   extern __shared__ __attribute__((aligned(16))) unsigned char dyn_s[];
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
