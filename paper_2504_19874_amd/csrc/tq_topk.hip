@@ -9,8 +9,12 @@
 // threads' best PAIRS is the bar instead: pairs are never equal, so at most k threads have any that reach it.  A few long rows (one query against a million codes) are cut into chunks, one
 // workgroup each, whose lists topk_merge_kernel joins in the same way.
 // (Before: a sorted list per thread, k rounds of arg-max to join them.  4 rows of 10^6 scores, k = 10: 35 + 30 us for the
-// chunks and the merge, 11.5 + 7.5 here; 16 rows, k = 64: 1.2 ms in all, 70 us here.)
+// chunks and the merge, 6.7 + 5.0 here; 2 rows of 300000, k = 64: 11.9 + 12.1.)
+// What such a launch costs is a chain of latencies, so the comparisons are shared out: those of a few pairs over up to sixteen lanes each, those
+// of the maxima over four (4 rows as above: 11.3 + 9.0 without).
 #include "tq_select.h"
+
+#include <type_traits>
 
 namespace tq {
 namespace {
@@ -105,13 +109,15 @@ __device__ int take_segment(TopkLds& s, const float (&v)[N], Pair pair, int k, i
     n = s.count;
   }
   if (n == kept) return kept;  // uniform; nothing passed
-  for (int c = tid; c < n; c += 256) {
+  const int lanes = n <= 16 ? 16 : n <= 32 ? 8 : n <= 64 ? 4 : n <= 128 ? 2 : 1;  // that share a pair's comparisons
+  for (int c = tid / lanes; c < n; c += 256) {  // one round, or one lane each
     const float cv = s.v[c];
     const int ci = s.i[c];
     int rank = 0;
-#pragma unroll 4
-    for (int o = 0; o < n; ++o) rank += better(s.v[o], s.i[o], cv, ci) ? 1 : 0;
-    if (rank < k) {
+#pragma unroll 8
+    for (int o = tid & (lanes - 1); o < n; o += lanes) rank += better(s.v[o], s.i[o], cv, ci) ? 1 : 0;
+    rank = sum_of_lanes(rank, lanes);
+    if (rank < k) {  // the lanes of a pair write the same
       s.best_v[rank] = cv;
       s.best_i[rank] = ci;
     }
@@ -172,7 +178,10 @@ __global__ __launch_bounds__(256) void topk_kernel(const float* __restrict__ sco
   write_best(s, kept, k, chunk_len > 0 ? 0x7fffffff : -1, out_idx + out_row * k, out_val != nullptr ? out_val + out_row * k : nullptr, tid);
 }
 
-// One workgroup per row: the k best of its cands <= 4096 (score, index) pairs (index INT_MAX: no pair).
+// One workgroup per row: the k best of its cands <= 256 N pairs of score and index (index INT_MAX: no pair).
+// They are sorted lists of k one behind the other, so a thread takes its pairs from ever other places of the lists: the threads' maxima are
+// then alike, and few pairs beside the k best reach the k-th largest of them.  (37 lists of 64, a thread's pairs all of one place: 81 us.)
+template <int N>
 __global__ __launch_bounds__(256) void topk_merge_kernel(const float* __restrict__ part_val, const int32_t* __restrict__ part_idx,
                                                          const int cands, const int k, int32_t* __restrict__ out_idx,
                                                          float* __restrict__ out_val, const int32_t* __restrict__ flags) {
@@ -181,17 +190,17 @@ __global__ __launch_bounds__(256) void topk_merge_kernel(const float* __restrict
   TopkLds& s = *reinterpret_cast<TopkLds*>(smem_raw);
   const int tid = threadIdx.x;
   const int64_t row = blockIdx.x;
-  constexpr int N = 16;
   float v[N];
+  auto place = [&](int e) { return e * 256 + ((tid + 37 * e) & 255); };  // 256 + 37 = 293, a prime: no k up to 64 divides it
 #pragma unroll
   for (int e = 0; e < N; ++e) {
-    const int c = e * 256 + tid, cc = c < cands ? c : cands - 1;
+    const int c = place(e), cc = c < cands ? c : cands - 1;
     const float w = part_val[row * cands + cc];
     v[e] = c < cands && part_idx[row * cands + cc] != 0x7fffffff ? w : __builtin_nanf("");
   }
   const int kept = take_segment(s, v, [&](int e, float& pv, int& pi) {
-    pv = part_val[row * cands + e * 256 + tid];
-    pi = part_idx[row * cands + e * 256 + tid];
+    pv = part_val[row * cands + place(e)];
+    pi = part_idx[row * cands + place(e)];
   }, k, 0, tid);
   write_best(s, kept, k, -1, out_idx + row * k, out_val != nullptr ? out_val + row * k : nullptr, tid);
 }
@@ -199,11 +208,12 @@ __global__ __launch_bounds__(256) void topk_merge_kernel(const float* __restrict
 }  // namespace
 
 // Chunks per row when a call's rows are too few to fill the chip: 0 (one workgroup per row) unless the rows are
-// few and long; then chunks of a segment or more, about four workgroups per compute unit in all, and no more
-// pairs per row than the joining kernel takes (4096).  (A segment exactly where there could be more: cut into 122 parts, a row of 10^6 is a
+// few and longer than two segments; then chunks of a segment or more, about four workgroups per compute unit in all, and no more
+// pairs per row than the joining kernel takes (4096).  (A workgroup takes 3 - 5 us per segment, more for k = 64, the joining 4.5 - 8: one row of 50000, k = 10:
+// 23.3 us in one workgroup, 4.5 + 4.4 in seven; 5 of 30000, k = 16: 20.2 and 6.9 + 7.1; 10 of 20000, k = 64: 37.3 and 12.1 + 8.5.)  (A segment exactly where there could be more: cut into 122 parts, a row of 10^6 is a
 // segment and eight columns each, two passes; 4 rows, k = 10: 13.6 -> 10.8 us.)
 int topk_chunks(int64_t rows, int64_t n, int k) {
-  if (k < 1 || rows < 1 || rows > 128 || n < 65536) return 0;
+  if (k < 1 || rows < 1 || rows > 128 || n <= 2 * SEG) return 0;
   int64_t c = (4 * (int64_t)device_cu_count() + rows - 1) / rows;
   if (c > (n + SEG - 1) / SEG) c = (n + SEG - 1) / SEG;
   if (c > 4096 / k) c = 4096 / k;
@@ -237,10 +247,16 @@ hipError_t launch_topk_merge(const float* part_val, const int32_t* part_idx, int
                              int32_t* out_idx, float* out_val, hipStream_t s, const int32_t* flags) {
   if (rows == 0) return hipSuccess;
   if (ranges < 1 || k < 1 || k > 64 || (int64_t)ranges * k > 4096 || rows > 0x7fffffff) return hipErrorInvalidValue;
-  static LdsLimit lds_limit;
-  if (const hipError_t e = raise_lds_limit(lds_limit, reinterpret_cast<const void*>(&topk_merge_kernel), (int)sizeof(TopkLds)); e != hipSuccess) return e;
-  hipLaunchKernelGGL(topk_merge_kernel, dim3((unsigned)rows), dim3(256), sizeof(TopkLds), s, part_val, part_idx, ranges * k, k, out_idx, out_val, flags);
-  return hipGetLastError();
+  auto go = [&](auto n_c) {
+    constexpr int N = decltype(n_c)::value;
+    static LdsLimit lds_limit;
+    if (const hipError_t e = raise_lds_limit(lds_limit, reinterpret_cast<const void*>(&topk_merge_kernel<N>), (int)sizeof(TopkLds)); e != hipSuccess) return e;
+    hipLaunchKernelGGL((topk_merge_kernel<N>), dim3((unsigned)rows), dim3(256), sizeof(TopkLds), s, part_val, part_idx, ranges * k, k, out_idx, out_val, flags);
+    return hipGetLastError();
+  };
+  if (ranges * k <= 1024) return go(std::integral_constant<int, 4>{});
+  if (ranges * k <= 2048) return go(std::integral_constant<int, 8>{});
+  return go(std::integral_constant<int, 16>{});
 }
 
 }  // namespace tq

@@ -21,11 +21,11 @@ def rows(kind, n):
             }[kind].astype(np.float32)
 
 
-def call(p, q, c, n, topk):
-    scores = torch.zeros((2, n), device=T.DEV)
-    top = torch.zeros((2, topk), dtype=torch.int32, device=T.DEV), torch.zeros((2, topk), device=T.DEV)
-    p.reserve_score(1, 2, n, False, True, topk)
-    run = lambda: tq.tq_score(p, q, 1, 2, c["idx"], None, None, c["norm"], n, scores, topk, *top)  # noqa: E731
+def call(p, q, c, n, topk, nq=2):
+    scores = torch.zeros((nq, n), device=T.DEV)
+    top = torch.zeros((nq, topk), dtype=torch.int32, device=T.DEV), torch.zeros((nq, topk), device=T.DEV)
+    p.reserve_score(1, nq, n, False, True, topk)
+    run = lambda: tq.tq_score(p, q, 1, nq, c["idx"], None, None, c["norm"], n, scores, topk, *top)  # noqa: E731
     run()
     return scores, top, run
 
@@ -39,7 +39,7 @@ def case(kind, n):
 
 
 @pytest.mark.parametrize("topk", [1, 10, 64])
-@pytest.mark.parametrize("n", [8192, 50001, 300000])  # one segment, a workgroup's several, chunks and their joining
+@pytest.mark.parametrize("n", [8192, 50001, 300000])  # one segment, chunks and their joining
 @pytest.mark.parametrize("kind", ["rising", "falling", "equal", "ties at the end", "zeros", "steps", "period", "infinite"])
 def test_many_candidates(kind, n, topk):
     p, c = case(kind, n)
@@ -52,9 +52,24 @@ def test_many_candidates(kind, n, topk):
         assert np.array_equal(tv[r].cpu().numpy(), s[r][want])
 
 
+@pytest.mark.parametrize("nq,n", [(2, 16384), (2, 16385), (128, 16385), (129, 40001),  # two segments; chunks from there; several segments of a workgroup
+                                  (2, 16 * 8192), (2, 16 * 8192 + 1), (2, 33 * 8192 - 5)])  # of 64: 1024, 1088 and 2112 pairs to be joined
+@pytest.mark.parametrize("topk", [16, 17, 64])  # bars from the maxima of four threads, of one
+@pytest.mark.parametrize("kind", ["drawn", "rising", "equal", "period", "infinite"])
+def test_chunks_and_bars(kind, nq, n, topk):
+    p, c = case(kind, n)
+    q = W.gaussian_queries(nq, 128, 5, unit=False)
+    scores, (ti, tv), _ = call(p, T.dev(q), c, n, topk, nq)
+    s = scores.cpu().numpy()
+    for r in range(0, nq, 1 if nq < 10 else 37):
+        want = np.argsort(-s[r], kind="stable")[:topk]  # equal scores by lower index
+        assert np.array_equal(ti[r].cpu().numpy(), want)
+        assert np.array_equal(tv[r].cpu().numpy(), s[r][want])
+
+
 @pytest.mark.parametrize("kind", ["rising", "equal", "ties at the end", "steps"])
 def test_their_cost_is_bounded(kind):
-    """50001 scores per row in one workgroup: within ten times a row of drawn scores (the quadratic ranking of whole segments
+    """50001 scores per row: within ten times a row of drawn scores (the quadratic ranking of whole segments
     that this guards against takes thousands of times as long)."""
     def us(kind):
         p, c = case(kind, 50001)
