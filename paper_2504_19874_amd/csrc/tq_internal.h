@@ -51,6 +51,23 @@ __device__ __forceinline__ void fetch_arguments() {
   for (int i = 0; i < LINES; ++i) asm volatile("" ::"s"(first[i]));
 }
 
+// op over the 64 lanes' values, in every lane, combined as by a butterfly over lane distances 32, 16 .. 1: once the halves are alike, a
+// rotation by half a period is the exchange.  Vector instructions throughout (a trip through the LDS crossbar per distance takes 100 cycles more).
+template <class T, class Op>
+__device__ __forceinline__ T over_wavefront(T v, Op op) {
+  static_assert(sizeof(T) == 4, "one register");
+  const auto bits = [](T x) { return __builtin_bit_cast(uint32_t, x); };
+  const auto val = [](uint32_t x) { return __builtin_bit_cast(T, x); };
+  const auto a = __builtin_amdgcn_permlane32_swap(bits(v), bits(v), false, false);
+  v = op(val(a[0]), val(a[1]));
+  const auto b = __builtin_amdgcn_permlane16_swap(bits(v), bits(v), false, false);
+  v = op(val(b[0]), val(b[1]));
+  v = op(v, val((uint32_t)__builtin_amdgcn_update_dpp(0, (int)bits(v), 0x128, 0xf, 0xf, true)));  // row_ror:8
+  v = op(v, val((uint32_t)__builtin_amdgcn_update_dpp(0, (int)bits(v), 0x124, 0xf, 0xf, true)));
+  v = op(v, val((uint32_t)__builtin_amdgcn_update_dpp(0, (int)bits(v), 0x122, 0xf, 0xf, true)));
+  return op(v, val((uint32_t)__builtin_amdgcn_update_dpp(0, (int)bits(v), 0x121, 0xf, 0xf, true)));
+}
+
 // ---------------------------------------------------------------------------
 // The one contraction kernel.  It computes, for a block of "vectors" i (the
 // N side) and a block of "rows" m (the M side),

@@ -47,11 +47,9 @@ __device__ __forceinline__ void stream_digits(const float* ys, int d, float sc, 
   }
   // two sums to a word: a wavefront's are at most 64 x 4 x 56 each
   int o01 = off[0] + off[1] * 65536, o23 = off[2] + off[3] * 65536;
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) {
-    o01 += __shfl_xor(o01, o);
-    o23 += __shfl_xor(o23, o);
-  }
+  const auto add = [](int x, int y) { return x + y; };
+  o01 = over_wavefront(o01, add);
+  o23 = over_wavefront(o23, add);
   if ((tid & 63) < 4) {
     const int both = (tid & 2) != 0 ? o23 : o01, low = (int)(int16_t)both;
     atomicAdd(off_s + (tid & 3), (tid & 1) != 0 ? (both - low) >> 16 : low);
@@ -182,8 +180,7 @@ __global__ __launch_bounds__(1024) void digitise_i8_kernel(const int d, const in
     *reinterpret_cast<f32x4*>(ys + 4 * tid) = v;
   }
   float mx = fmaxf(fmaxf(fabsf(v[0]), fabsf(v[1])), fmaxf(fabsf(v[2]), fabsf(v[3])));
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off));
+  mx = over_wavefront(mx, [](float x, float y) { return fmaxf(x, y); });
   if ((tid & 63) == 0) red_mx[tid >> 6] = mx;
   __syncthreads();
   mx = red_mx[0];
@@ -195,8 +192,7 @@ __global__ __launch_bounds__(1024) void digitise_i8_kernel(const int d, const in
   int tot = 0;  // of a wavefront: 256 values of up to 2^20
 #pragma unroll
   for (int k = 0; k < 4; ++k) tot += __float2int_rn(v[k] * sc);
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) tot += __shfl_xor(tot, off);
+  tot = over_wavefront(tot, [](int x, int y) { return x + y; });
   if ((tid & 63) == 0) red_tot[tid >> 6] = tot;
   __syncthreads();
   for (int i = tid; i < d / 32 * 24; i += blockDim.x) own[i / 24 * 32 + i % 24] = img_s[i];  // (everyone has read its floats)

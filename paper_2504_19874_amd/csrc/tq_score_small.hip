@@ -15,6 +15,7 @@
 // kernel and sit in LDS laid out [k/4][query][k%4], so one 16-byte read gives a
 // lane the values of its query (lane%4) for four consecutive coordinates.
 #include "tq_internal.h"
+#include "tq_h2.h"
 
 #include <type_traits>
 
@@ -65,59 +66,86 @@ __global__ __launch_bounds__(256) void matvec_small_kernel(const int d, const in
 
 // Long vectors: a wavefront takes R rows of the matrix at a time, 16 bytes per lane and load, against Q vectors that the
 // workgroup has staged in LDS.  Bound by the matrix coming from memory; R = 4 shares the staging and the LDS reads over four
-// rows where that still gives the chip enough workgroups.  (Four vectors, two matrices of 3072 x 3072, 75 MB: 57 us with
-// one row per wavefront and the vectors staged a float at a time, 18.5 here; one vector, 1536 x 1536: 7.2 us -> 2.2 - 3.2.)
+// rows where that still gives the chip enough workgroups.  The vectors go to LDS by direct loads, and the beginning of the rows is on
+// its way before they are waited for; then two chunks of a row are loaded ahead (one with R = 4: two take 13.2 us instead of 11.8 for 50 vectors and 768
+// x 768).  (Four vectors, two matrices of 3072 x 3072, 75 MB: 57 us with one row per wavefront and the vectors staged a float at a time, 21.7
+// with vectors staged through registers one after the other and nothing ahead, 18.3 here; twelve of them 32.7 -> 26.3; five, 1536: 9.5 -> 7.5.)
 template <int Q, int R>
 __global__ __launch_bounds__(256) void matvec_rows_kernel(const int d, const int nq, const float* __restrict__ W0,
                                                           const float* __restrict__ W1, const float* __restrict__ x,
                                                           const int64_t ldx, float* __restrict__ out0,
                                                           float* __restrict__ out1, const int64_t ldo, const int x_bf16) {
   extern __shared__ __attribute__((aligned(16))) float xs[];  // [Q][d]
-  const int tid = threadIdx.x, lane = tid & 63;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int q0 = blockIdx.y * Q;
-#pragma unroll
-  for (int r = 0; r < Q; ++r) {
-    const int64_t row = q0 + r < nq ? q0 + r : nq - 1;  // past the end: the last one again, not stored
-    if (x_bf16) {
-      const uint2* src = reinterpret_cast<const uint2*>(reinterpret_cast<const uint16_t*>(x) + row * ldx);
-      for (int k4 = tid; k4 < d / 4; k4 += 256) {
-        const uint2 w = src[k4];
-        reinterpret_cast<float4*>(xs + r * d)[k4] = make_float4(__uint_as_float(w.x << 16), __uint_as_float(w.x & 0xffff0000u),
-                                                                __uint_as_float(w.y << 16), __uint_as_float(w.y & 0xffff0000u));
-      }
-    } else {
-      const float4* src = reinterpret_cast<const float4*>(x + row * ldx);
-#pragma unroll 4
-      for (int k4 = tid; k4 < d / 4; k4 += 256) reinterpret_cast<float4*>(xs + r * d)[k4] = src[k4];
-    }
-  }
   const int j0 = (blockIdx.x * 4 + (tid >> 6)) * R;
   const bool live = j0 < d;  // d is a multiple of 4 R: whole wavefronts
   const float4* w4 = reinterpret_cast<const float4*>((blockIdx.z == 0 ? W0 : W1) + (int64_t)(live ? j0 : 0) * d);
+  const int n4 = d / 4;
+  const uint32_t xs_lds = h2_lds_address(xs);
+  constexpr int U = R == 4 ? 1 : 2;  // chunks of 64 x 16 bytes per row that are loaded ahead
+  float4 w[U][R];
+  auto load = [&](float4 (&o)[U][R], int k0) {  // past the rows' end: their last values again
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int i = 0; i < R; ++i) o[u][i] = w4[i * n4 + min(k0 + 64 * u + lane, n4 - 1)];
+  };
+  // the vectors' way to LDS first, all of it, then the beginning of the matrix: both are under way together
+  if (!x_bf16) {
+#pragma unroll
+    for (int r = 0; r < Q; ++r) {
+      const float* const src = x + (q0 + r < nq ? q0 + r : nq - 1) * ldx;  // past the end: the last one again, not stored
+      for (int k = wave * 64; k < n4; k += 256)
+        if (k + lane < n4) h2_dma(src, (uint32_t)(k + lane) * 16, xs_lds + (uint32_t)(r * d + 4 * k) * 4);
+    }
+  }
+  load(w, 0);
+  if (x_bf16) {
+#pragma unroll
+    for (int r = 0; r < Q; ++r) {
+      const uint2* src = reinterpret_cast<const uint2*>(reinterpret_cast<const uint16_t*>(x) + (q0 + r < nq ? q0 + r : nq - 1) * ldx);
+      for (int k4 = tid; k4 < n4; k4 += 256) {
+        const uint2 v = src[k4];
+        reinterpret_cast<float4*>(xs + r * d)[k4] = make_float4(__uint_as_float(v.x << 16), __uint_as_float(v.x & 0xffff0000u),
+                                                                __uint_as_float(v.y << 16), __uint_as_float(v.y & 0xffff0000u));
+      }
+    }
+  }
   float acc[R][Q];
 #pragma unroll
   for (int i = 0; i < R; ++i)
 #pragma unroll
     for (int r = 0; r < Q; ++r) acc[i][r] = 0.f;
-  __syncthreads();
-#pragma unroll 2
-  for (int k4 = lane; k4 < d / 4; k4 += 64) {
-    float4 w[R];
 #pragma unroll
-    for (int i = 0; i < R; ++i) w[i] = w4[i * (d / 4) + k4];
+  for (int u = 0; u < U; ++u)
 #pragma unroll
-    for (int r = 0; r < Q; ++r) {
-      const float4 v = reinterpret_cast<const float4*>(xs + r * d)[k4];
+    for (int i = 0; i < R; ++i) asm volatile("" : "+v"(w[u][i].x), "+v"(w[u][i].y), "+v"(w[u][i].z), "+v"(w[u][i].w));
+  h2_wait_barrier<0>();
+  for (int k0 = 0; k0 < n4; k0 += 64 * U) {
+    float4 next[U][R];
+    if (k0 + 64 * U < n4) load(next, k0 + 64 * U);
 #pragma unroll
-      for (int i = 0; i < R; ++i) acc[i][r] = fmaf(w[i].x, v.x, fmaf(w[i].y, v.y, fmaf(w[i].z, v.z, fmaf(w[i].w, v.w, acc[i][r]))));
+    for (int u = 0; u < U; ++u) {
+      const int k4 = k0 + 64 * u + lane;
+      if (k4 < n4)
+#pragma unroll
+        for (int r = 0; r < Q; ++r) {
+          const float4 v = reinterpret_cast<const float4*>(xs + r * d)[k4];
+#pragma unroll
+          for (int i = 0; i < R; ++i)
+            acc[i][r] = fmaf(w[u][i].x, v.x, fmaf(w[u][i].y, v.y, fmaf(w[u][i].z, v.z, fmaf(w[u][i].w, v.w, acc[i][r]))));
+        }
     }
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int i = 0; i < R; ++i) w[u][i] = next[u][i];
   }
 #pragma unroll
-  for (int off = 32; off >= 1; off >>= 1)
+  for (int i = 0; i < R; ++i)
 #pragma unroll
-    for (int i = 0; i < R; ++i)
-#pragma unroll
-      for (int r = 0; r < Q; ++r) acc[i][r] += __shfl_xor(acc[i][r], off);
+    for (int r = 0; r < Q; ++r) acc[i][r] = over_wavefront(acc[i][r], [](float x, float y) { return x + y; });
   if (!live) return;
   float* const out = blockIdx.z == 0 ? out0 : out1;
 #pragma unroll
