@@ -882,7 +882,7 @@ tq_status score_impl(const tq_params* p, Workspace ws, const float* q, int64_t l
     if (rot != nullptr) {
       if (!rotate_h2(p, q, ldq, nq, qr, qs, rot, s)) return TQ_ERR_HIP;
     } else if (nq <= kMatvecQueries && d <= 4096) {
-      if (launch_matvec_small(d, (int)nq, p->Pi, prod ? p->S : nullptr, q, ldq, qr, qs, s) != hipSuccess)
+      if (launch_matvec_rows(d, nq, p->Pi, prod ? p->S : nullptr, q, ldq, qr, qs, d, false, s) != hipSuccess)
         return TQ_ERR_HIP;
     } else {
       GemmArgs a;

@@ -175,9 +175,7 @@ hipError_t launch_quant_rows(int bits, bool bf16, const void* x, int64_t ldx, in
 hipError_t launch_dequant_rows(int bits, bool prod, int d, int64_t n, const uint32_t* idx, const uint32_t* qjl,
                                const float* gamma, const float* norm, const float* PiT, const float* ST, const Codebook& cb,
                                float kappa, float* out, int64_t ldo, hipStream_t s);
-hipError_t launch_matvec_small(int d, int nq, const float* W0, const float* W1, const float* x,
-                               int64_t ldx, float* out0, float* out1, hipStream_t stream);
-// the same by the kernel for long vectors, d a multiple of 32 up to 4096: rows of out0 / out1 ldo apart
+// a handful of vectors times W0 (and W1, unless null), d a multiple of 32 up to 4096: rows of out0 / out1 ldo apart
 hipError_t launch_matvec_rows(int d, int64_t n, const float* W0, const float* W1, const float* x, int64_t ldx, float* out0,
                               float* out1, int64_t ldo, bool bf16, hipStream_t s);
 hipError_t launch_score_small(int bits, bool prod, const float* qr, const float* qs, const uint32_t* idx,

@@ -23,53 +23,16 @@ namespace tq {
 
 typedef float floatx4 __attribute__((ext_vector_type(4)));
 
-// ---------------------------------------------------------------------------
-// out[q][j] = sum_k W[j][k] x[q][k] for a handful of queries.  One thread per
-// output (q, j), j fastest; a workgroup stages its queries in LDS and every
-// thread walks its own row of W with 16-byte loads (each 128-byte line of W is
-// consumed by the thread that fetched it).  blockIdx.z selects (W0, out0) or
-// (W1, out1); blockIdx.y a block of 4 queries; blockIdx.x a block of 64 rows j.
-// ---------------------------------------------------------------------------
-constexpr int MV_Q = 4;
+constexpr int MV_Q = 4;  // vectors of a workgroup
 
-__global__ __launch_bounds__(256) void matvec_small_kernel(const int d, const int nq,
-                                                           const float* __restrict__ W0,
-                                                           const float* __restrict__ W1,
-                                                           const float* __restrict__ x, const int64_t ldx,
-                                                           float* __restrict__ out0,
-                                                           float* __restrict__ out1) {
-  extern __shared__ __attribute__((aligned(16))) float xs[];  // [MV_Q][d]
-  const int tid = threadIdx.x;
-  const int q0 = blockIdx.y * MV_Q;
-  for (int e = tid; e < MV_Q * d; e += 256) {
-    const int r = e / d, k = e - r * d;
-    xs[e] = (q0 + r < nq) ? x[(int64_t)(q0 + r) * ldx + k] : 0.f;
-  }
-  __syncthreads();
-  const int j = blockIdx.x * 64 + (tid & 63);
-  const int r = tid >> 6;  // query within the block of 4: one per wavefront
-  if (j >= d || q0 + r >= nq) return;
-  const float4* w4 = reinterpret_cast<const float4*>((blockIdx.z == 0 ? W0 : W1) + (int64_t)j * d);
-  const float4* x4 = reinterpret_cast<const float4*>(xs + r * d);
-  float a0 = 0.f, a1 = 0.f, a2 = 0.f, a3 = 0.f;
-#pragma unroll 8
-  for (int k4 = 0; k4 < d / 4; ++k4) {
-    const float4 w = w4[k4];
-    const float4 v = x4[k4];
-    a0 = fmaf(w.x, v.x, a0);
-    a1 = fmaf(w.y, v.y, a1);
-    a2 = fmaf(w.z, v.z, a2);
-    a3 = fmaf(w.w, v.w, a3);
-  }
-  (blockIdx.z == 0 ? out0 : out1)[(int64_t)(q0 + r) * d + j] = (a0 + a1) + (a2 + a3);
-}
-
-// Long vectors: a wavefront takes R rows of the matrix at a time, 16 bytes per lane and load, against Q vectors that the
+// out[q][j] = sum_k W[j][k] x[q][k] for a handful of vectors; blockIdx.z selects (W0, out0) or (W1, out1), blockIdx.y a block of Q vectors.
+// A wavefront takes R rows of the matrix at a time, 16 bytes per lane and load, against Q vectors that the
 // workgroup has staged in LDS.  Bound by the matrix coming from memory; R = 4 shares the staging and the LDS reads over four
 // rows where that still gives the chip enough workgroups.  The vectors go to LDS by direct loads, and the beginning of the rows is on
 // its way before they are waited for; then two chunks of a row are loaded ahead (one with R = 4: two take 13.2 us instead of 11.8 for 50 vectors and 768
 // x 768).  (Four vectors, two matrices of 3072 x 3072, 75 MB: 57 us with one row per wavefront and the vectors staged a float at a time, 21.7
-// with vectors staged through registers one after the other and nothing ahead, 18.3 here; twelve of them 32.7 -> 26.3; five, 1536: 9.5 -> 7.5.)
+// with vectors staged through registers one after the other and nothing ahead, 18.3 here; twelve of them 32.7 -> 26.3; five, 1536: 9.5 -> 7.5; 60 vectors
+// of 384 15.0 us with a thread per row of the matrix, 5.1 here, of 128 6.2 and 3.4.)
 template <int Q, int R>
 __global__ __launch_bounds__(256) void matvec_rows_kernel(const int d, const int nq, const float* __restrict__ W0,
                                                           const float* __restrict__ W1, const float* __restrict__ x,
@@ -281,18 +244,6 @@ hipError_t launch_dequant_rows(int bits, bool prod, int d, int64_t n, const uint
     case 4: return dequant_rows_bits<4>(prod, d, (int)n, idx, qjl, gamma, norm, PiT, ST, cb, kappa, out, ldo, s);
     default: return hipErrorInvalidValue;
   }
-}
-
-hipError_t launch_matvec_small(int d, int nq, const float* W0, const float* W1, const float* x,
-                               int64_t ldx, float* out0, float* out1, hipStream_t stream) {
-  if (nq == 0) return hipSuccess;
-  if (d % 4 != 0 || (size_t)MV_Q * d * sizeof(float) > 65536) return hipErrorInvalidValue;
-  if (d >= 512) {
-    return launch_matvec_rows(d, nq, W0, W1, x, ldx, out0, out1, d, false, stream);
-  }
-  hipLaunchKernelGGL(matvec_small_kernel, dim3((d + 63) / 64, (nq + MV_Q - 1) / MV_Q, W1 != nullptr ? 2 : 1),
-                     dim3(256), (size_t)MV_Q * d * sizeof(float), stream, d, nq, W0, W1, x, ldx, out0, out1);
-  return hipGetLastError();
 }
 
 // ---------------------------------------------------------------------------

@@ -55,8 +55,7 @@ __global__ __launch_bounds__(256) void search_prepare_kernel(const int d, const 
     if (r != nullptr) mx = fmaxf(mx, fabsf(r[k]));
     if (z != nullptr) mx = fmaxf(mx, fabsf(z[k]) * s_fac);
   }
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off));
+  mx = over_wavefront(mx, [](float x, float y) { return fmaxf(x, y); });
   if (lane == 0) red_mx[tid >> 6] = mx;
   __syncthreads();
   mx = fmaxf(fmaxf(red_mx[0], red_mx[1]), fmaxf(red_mx[2], red_mx[3]));
@@ -82,9 +81,7 @@ __global__ __launch_bounds__(256) void search_prepare_kernel(const int d, const 
     if (z != nullptr) *reinterpret_cast<uint2*>(s_pieces + (q * d) / 2 + g * 16 + k * 2) = pieces(z, s * s_fac, si * f.s_rel, sum[2], sum[3]);
   }
 #pragma unroll
-  for (int off = 32; off >= 1; off >>= 1)
-#pragma unroll
-    for (int i = 0; i < 4; ++i) sum[i] += __shfl_xor(sum[i], off);
+  for (int i = 0; i < 4; ++i) sum[i] = over_wavefront(sum[i], [](float x, float y) { return x + y; });
   if (lane == 0)
 #pragma unroll
     for (int i = 0; i < 4; ++i) red[tid >> 6][i] = sum[i];
