@@ -617,14 +617,21 @@ tq_status tq_dequantize(const tq_params* p, const uint32_t* idx, const uint32_t*
                                       kappa_of(p->d), make_codebook(p), 0, 0.f, make_codebook(p),
                                       static_cast<hipStream_t>(stream)));
   }
+  // A table that is a sum of signs, by its digits.  A few long codes by matrix-vector products in fp32, unless there is a sketch and d >= 1024: else digits
+  // are a little further from 64 bits (of a coordinate's root mean square, products / digits: d = 512, 2 bits 0.8 / 1.3e-7; 768, 2 + 1 bits 1.18 / 1.25e-7; 1536, 2 + 1 bits
+  // 1.46 / 1.27e-7).  The first of those, too, where they take less time (us, 1536, 2 + 1 bits, 1 code 7.2 / 8.0, 2 8.6 / 8.1; 1024, 1 + 1 bits, 4 5.1 / 6.3,
+  // 8 6.6 / 6.5; 3072, 1 + 1 bits, 1 16.4 / 13.3).
+  const bool has_digits = h2_dequant_images(p) != nullptr && sign_images(p);
+  const bool by_digits = !fp32_mfma_only(p) && sign_gemm_serves(p->bits_mse, prod, p->d, n, has_digits) && (p->bits_mse > 0 || prod) && p->Pi != nullptr &&
+                         (!prod || p->S != nullptr) && sign_table(p->bits_mse, make_codebook(p), &sc);
+  const bool first_few = !by_digits || !has_digits || !prod || p->d < 1024 || n * p->d * p->d <= 4500000;
   // a handful of long vectors: matrix-vector products (the matrices are read once per block of 4 vectors, 2 with a
   // sketch; the same bound as for the quantiser's route)
-  if (p->d < 4096 && !fp32_mfma_only(p) && rows_route_serves(prod ? 2 * n : n, p->d, prod ? 2 : 1, 300))
+  if (first_few && p->d < 4096 && !fp32_mfma_only(p) && rows_route_serves(prod ? 2 * n : n, p->d, prod ? 2 : 1, 300))
     return from_hip(launch_dequant_rows(p->bits_mse, prod, p->d, n, idx, qjl, gamma, norm, p->PiT, p->ST, make_codebook(p),
                                         kappa_of(p->d), x_out, ldo, static_cast<hipStream_t>(stream)));
   // many codes of a table that is a sum of signs: digits of Pi^T and S^T, from the images or made here where the workspace holds them
-  if (!fp32_mfma_only(p) && sign_gemm_serves(p->bits_mse, prod, p->d, n) && (p->bits_mse > 0 || prod) && p->Pi != nullptr &&
-      (!prod || p->S != nullptr) && sign_table(p->bits_mse, make_codebook(p), &sc)) {
+  if (by_digits) {
     const hipStream_t s = static_cast<hipStream_t>(stream);
     const int d = p->d;
     const char *pi = nullptr, *si = nullptr;

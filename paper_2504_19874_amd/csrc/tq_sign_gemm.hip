@@ -262,12 +262,192 @@ hipError_t launch_tile(SignGemmArgs a, hipStream_t s) {
   return hipGetLastError();
 }
 
+// Up to one workgroup of sign_few_kernel per compute unit, two where there is more than one stream of products; us, sign_gemm_kernel / here: 2 + 1 bits d = 256
+// 1 code 10.0 / 3.8, 2000 11.0 / 6.0; 768 64 22.8 / 8.0, 1000 24.0 / 15.7, 1500 (2.25 workgroups) 24.4 / 22.8; 1536 200 41.8 / 12.6; 3072, 1 + 1 bits, 64
+// 52.2 / 24.3, 400 (2.6) 52.9 / 58.9; one stream d = 512 1000 8.1 / 5.6, 1500 (1.5) 8.3 / 9.5.  Two bits without a sketch, against tq_code_gemm.hip: 1536
+// 200 29.4 / 8.8, 1000 (3) 31.8 / 23.9, 1500 (4.5) 35.0 / 38.5.
+bool few_serves(int bits, bool prod, int d, int64_t n) {
+  return (d / 32) * ((n + 63) / 64) <= (int64_t)(bits + (prod ? 1 : 0) > 1 ? 2 : 1) * device_cu_count();
+}
+
 template <int BITS, bool PROD>
 hipError_t launch_one(const SignGemmArgs& a, hipStream_t s) {
   // 512 codes per workgroup where that gives three quarters of the chip's two per compute unit, else 256 (20011 codes of 768 87 / 93 us; 3000 of
   // 1536 93 / 75)
+  if (a.n <= 32) return launch_few<BITS, PROD, 1>(a, s);
+  if (few_serves(BITS, PROD, a.d, a.n)) return launch_few<BITS, PROD, 2>(a, s);
   if ((int64_t)(a.d / 64) * ((a.n + 511) / 512) * 2 >= 3 * device_cu_count()) return launch_tile<BITS, PROD, 4, 4>(a, s);
   return launch_tile<BITS, PROD, 2, 4>(a, s);
+}
+
+// Few codes: a tile of 32 outputs and up to 64 codes per workgroup, the contraction split over its eight wavefronts.  Each takes every eighth step, digits
+// straight into registers and one step ahead, and keeps a sum of its own per stream; the eight meet in LDS.  Bound by latency: a wavefront has d / 512 steps, and
+// the matrices come once from memory for all of the chip, d <= 1536 within three trips (sign_gemm_kernel goes through the whole contraction step by step in d / 64
+// workgroups: 64 codes of 1536, 2 + 1 bits, 41.7 us, here 13.0; few_serves has more).  Error of a coordinate's root mean square against 64 bits, d = 1536, 300 codes,
+// sign_gemm_kernel / here: 2 + 1 bits 2.2e-7 / 1.3e-7, 1 bit 1.7e-7 / 1.2e-7; 2 bits, tq_code_gemm.hip / here: 4.4e-7 / 1.3e-7.
+template <int BITS, bool PROD, int TW>
+__global__ __launch_bounds__(512, 2) void sign_few_kernel(const SignGemmArgs a) {
+  constexpr int NW = 8, TC = TW * 32, KINDS = (BITS > 0 ? 1 : 0) + (PROD ? 1 : 0);
+  extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
+  float* const sum_s = reinterpret_cast<float*>(lds);  // [kind][wavefront][TW][16][64]
+  // two neighbouring tiles, whose outputs alternate, on one XCD
+  const int k8 = (int)blockIdx.x / XCDS, item = (k8 >> 1) * XCDS + (int)blockIdx.x % XCDS, pairs = a.tiles_m >> 1;
+  if (item >= pairs * a.tiles_n) return;
+  const int tile = 2 * (item % pairs) + (k8 & 1);
+  const int tid = threadIdx.x, lane = tid & 63, l = lane & 31, h = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int S = a.d >> 6, G = a.d >> 5;
+  const int64_t n0 = (int64_t)(item / pairs) * TC;
+  const int rows = (int)(a.n - n0 < TC ? a.n - n0 : TC);
+  const size_t step_bytes = (size_t)G * SIGN_STEP_BYTES;
+  const uint32_t* at_idx[TW];
+  const uint32_t* at_qjl[TW];
+#pragma unroll
+  for (int t = 0; t < TW; ++t) {
+    const int r = t * 32 + l;
+    const int64_t first = (n0 + (r < rows ? r : rows - 1)) * G + h * S;  // past the end: not stored
+    at_idx[t] = BITS > 0 ? a.idx + first * BITS : nullptr;
+    at_qjl[t] = PROD ? a.qjl + first : nullptr;
+  }
+  struct Step {
+    SignFrag z[PROD ? SIGN_DIGITS : 1], p[BITS > 0 ? SIGN_DIGITS : 1];
+    uint32_t zw[TW], pw[TW][BITS > 0 ? BITS : 1];
+  };
+  auto digits = [&](const unsigned char* image, int s, SignFrag (&o)[SIGN_DIGITS]) {
+    const unsigned char* const at = image + s * step_bytes + (size_t)tile * SIGN_STEP_BYTES;
+#pragma unroll
+    for (int j = 0; j < SIGN_DIGITS; ++j) {
+      o[j].a = *reinterpret_cast<const u32x4*>(at + j * SIGN_FRAG_BYTES + lane * 16);
+      o[j].b = *reinterpret_cast<const uint2*>(at + j * SIGN_FRAG_BYTES + 1024 + lane * 8);
+    }
+  };
+  auto load_sketch = [&](Step& f, int s) {
+    if constexpr (PROD) {
+#pragma unroll
+      for (int t = 0; t < TW; ++t) f.zw[t] = at_qjl[t][s];
+      digits(a.s, s, f.z);
+    }
+  };
+  auto load_planes = [&](Step& f, int s) {
+    if constexpr (BITS > 0) {
+#pragma unroll
+      for (int t = 0; t < TW; ++t)
+#pragma unroll
+        for (int b = 0; b < BITS; ++b) f.pw[t][b] = at_idx[t][s * BITS + b];
+      digits(a.pi, s, f.p);
+    }
+  };
+  floatx16 accz[TW], accp[BITS > 0 ? BITS : 1][TW];
+#pragma unroll
+  for (int t = 0; t < TW; ++t)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      accz[t][r] = 0.f;
+#pragma unroll
+      for (int b = 0; b < BITS; ++b) accp[b][t][r] = 0.f;
+    }
+  const uint32_t two = sign_two();
+  auto products = [&](const v8i_t& sg, const SignFrag (&f)[SIGN_DIGITS], floatx16& acc) {
+    acc = sign_mfma<0>(sg, sign_operand(f[0]), acc);
+    acc = sign_mfma<1>(sg, sign_operand(f[1]), acc);
+    acc = sign_mfma<2>(sg, sign_operand(f[2]), acc);
+    acc = sign_mfma<3>(sg, sign_operand(f[3]), acc);
+    acc = sign_mfma<4>(sg, sign_operand(f[4]), acc);
+  };
+  auto sketch = [&](const Step& f) {
+    if constexpr (PROD)
+#pragma unroll
+      for (int t = 0; t < TW; ++t) products(minus_sign_bits(f.zw[t], two), f.z, accz[t]);
+  };
+  auto planes = [&](const Step& f) {
+    if constexpr (BITS > 0)
+#pragma unroll
+      for (int b = 0; b < BITS; ++b)
+#pragma unroll
+        for (int t = 0; t < TW; ++t) products(minus_sign_bits(f.pw[t][b], two), f.p, accp[b][t]);
+  };
+  const size_t unit_at = (size_t)tile * SIGN_STEP_BYTES + UNITS + l * 4;
+  const float pi_unit = BITS > 0 ? *reinterpret_cast<const float*>(a.pi + unit_at) : 1.f;
+  const float s_unit = PROD ? *reinterpret_cast<const float*>(a.s + unit_at) : 1.f;
+  if (wave < S) {
+    // past the last step: it once more, not multiplied
+    if constexpr (PROD && BITS > 0 && TW == 2) {  // one kind of sign ahead: registers
+      Step f;
+      load_sketch(f, wave);
+      load_planes(f, wave);
+      for (int s = wave; s < S; s += NW) {
+        const int next = s + NW < S ? s + NW : s;
+        __builtin_amdgcn_sched_barrier(0);
+        sketch(f);
+        __builtin_amdgcn_sched_barrier(0);
+        load_sketch(f, next);
+        __builtin_amdgcn_sched_barrier(0);
+        planes(f);
+        __builtin_amdgcn_sched_barrier(0);
+        load_planes(f, next);
+      }
+    } else {
+      Step f0, f1;
+      auto load = [&](Step& f, int s) {
+        load_sketch(f, s < S ? s : s - NW);
+        load_planes(f, s < S ? s : s - NW);
+        __builtin_amdgcn_sched_barrier(0);
+      };
+      load(f0, wave);
+      for (int s = wave;; s += 2 * NW) {
+        load(f1, s + NW);
+        sketch(f0);
+        planes(f0);
+        __builtin_amdgcn_sched_barrier(0);
+        if (s + NW >= S) break;
+        load(f0, s + 2 * NW);
+        sketch(f1);
+        planes(f1);
+        __builtin_amdgcn_sched_barrier(0);
+        if (s + 2 * NW >= S) break;
+      }
+    }
+  }
+  // ---- (minus: see minus_sign_bits) ----
+  const float upper = -(float)(a.c.alpha * (double)pi_unit), lower = -(float)(a.c.beta * (double)pi_unit);
+  auto put = [&](int kind, int t, int r, float v) { sum_s[(((kind * NW + wave) * TW + t) * 16 + r) * 64 + lane] = v; };
+#pragma unroll
+  for (int t = 0; t < TW; ++t)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      if constexpr (BITS == 1) put(0, t, r, upper * accp[0][t][r]);
+      if constexpr (BITS == 2) put(0, t, r, fmaf(upper, accp[1][t][r], lower * accp[0][t][r]));
+      if constexpr (PROD) put(KINDS - 1, t, r, -s_unit * accz[t][r]);
+    }
+  __syncthreads();
+  const int m = 64 * (tile >> 1) + (tile & 1) + 2 * l;
+  for (int e = wave; e < TW * 16; e += NW) {
+    const int t = e >> 4, r = e & 15, c = 32 * t + 8 * (r >> 2) + 4 * h + (r & 3);
+    float v[KINDS];
+#pragma unroll
+    for (int kind = 0; kind < KINDS; ++kind) {
+      v[kind] = sum_s[(kind * NW * TW * 16 + e) * 64 + lane];
+#pragma unroll
+      for (int w = 1; w < NW; ++w) v[kind] += sum_s[((kind * NW + w) * TW * 16 + e) * 64 + lane];
+    }
+    if (c < rows) {
+      const float nu = a.norm != nullptr ? a.norm[n0 + c] : 1.f, kg = PROD ? a.kappa * a.gamma[n0 + c] : 0.f;
+      const float sum = !PROD ? v[0] : BITS > 0 ? fmaf(kg, v[KINDS - 1], v[0]) : kg * v[0];
+      a.out[(n0 + c) * a.ldo + m] = nu * sum;
+    }
+  }
+}
+
+template <int BITS, bool PROD, int TW>
+hipError_t launch_few(SignGemmArgs a, hipStream_t s) {
+  constexpr int LDS = ((BITS > 0 ? 1 : 0) + (PROD ? 1 : 0)) * 8 * TW * 16 * 64 * 4;
+  a.tiles_m = a.d / 32;  // even
+  a.tiles_n = (int)((a.n + 32 * TW - 1) / (32 * TW));
+  static LdsLimit lds_limit;  // per instantiation: the limit is raised once per device
+  if (const hipError_t e = raise_lds_limit(lds_limit, reinterpret_cast<const void*>(&sign_few_kernel<BITS, PROD, TW>), LDS); e != hipSuccess) return e;
+  const dim3 grid((a.tiles_m / 2 * a.tiles_n + XCDS - 1) / XCDS * 2 * XCDS);
+  hipLaunchKernelGGL((sign_few_kernel<BITS, PROD, TW>), grid, dim3(512), LDS, s, a);
+  return hipGetLastError();
 }
 
 // a workgroup for 64 rows and two tiles
@@ -330,9 +510,10 @@ __global__ __launch_bounds__(64 * SIGN_DIGITS) void sign_gemm_image_kernel(const
 bool sign_gemm_images(int d) { return d >= 256 && d % 128 == 0; }
 
 // Two bits without a sketch are two streams, ten products of a digit, where fp16 pieces take three products of twice the steps' length each:
-// below 2^20 coordinates these have the smaller tiles (768 coordinates: 100 codes 14.9 us, 16.4 here; 1000 16.8, 17.0; 3000 24.2, 18.1).
-// Everything else is faster here from the first code on (1 + 1 bits: 65 codes of 256 8.8 -> 8.1, of 3072 97 -> 53).
-bool sign_gemm_serves(int bits, bool prod, int d, int64_t n) { return sign_gemm_images(d) && (prod || bits != 2 || n * d >= 1 << 20); }
+// between few codes and 2^20 coordinates these have the smaller tiles (768 coordinates: 1000 codes 16.8 us, 17.0 with sign_gemm_kernel; 3000 24.2, 18.1).
+bool sign_gemm_serves(int bits, bool prod, int d, int64_t n, bool digits) {
+  return sign_gemm_images(d) && (prod || bits != 2 || (digits && few_serves(bits, prod, d, n)) || n * d >= 1 << 20);
+}
 
 hipError_t launch_sign_gemm_image(const float* W, int d, void* image, hipStream_t s) {
   if (d < 256 || d % 128 != 0) return hipErrorInvalidValue;

@@ -47,6 +47,13 @@ def test_the_sketch_comes_from_s(d, bits, nq):
     P.check_close(run(p, q, codes, n).cpu().numpy(), want, scale, "score")
 
 
+# rows shorter than a wavefront's load, not a multiple of one, of two; blocks of four queries with one to four of them
+@pytest.mark.parametrize("d,bits,nq", [(32, 1, 64), (96, 1, 33), (224, 0, 61), (288, 2, 42), (384, 2, 64), (544, 1, 35)])
+def test_a_wavefront_per_row(d, bits, nq):
+    p, q, codes, n, want, scale = problem(d, bits, nq, d + nq)
+    P.check_close(run(p, q, codes, n).cpu().numpy(), want, scale, "score")
+
+
 @pytest.mark.parametrize("d,bits,nq", [(256, 1, 65), (1024, 0, 130)])
 def test_images_change_no_bit(d, bits, nq):
     """The matrices' pieces from the images, or made in a workspace of the size that is asked for without them."""

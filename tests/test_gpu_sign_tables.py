@@ -92,6 +92,19 @@ def test_long_codes(d, bits, prod, n):
         p.build_images()
 
 
+# up to 32 codes of a workgroup and up to 64, the last of several, the ends of the range (256 compute units); fewer steps than wavefronts, a remainder of them
+@pytest.mark.parametrize("d,bits,prod,n", [(256, 2, False, 1), (256, 2, True, 32), (256, 0, True, 33), (384, 1, True, 31), (384, 2, False, 65), (512, 1, False, 1024), (512, 1, False, 1025),
+                                           (640, 1, True, 64), (640, 2, True, 1600), (1152, 2, False, 129), (1536, 2, True, 1), (1536, 2, True, 2), (1024, 1, True, 4), (1024, 1, True, 5), (768, 2, True, 64)])
+def test_few_long_codes(d, bits, prod, n):
+    p, codes, parts, norm = make(bits, prod, n, d)
+    wide = torch.full((n + 1, d + 4), 7.0, device=T.DEV)
+    tq.tq_dequantize(p, *codes, T.dev(norm), wide[:n, :d])
+    assert bool((wide[:n, d:] == 7).all()) and bool((wide[n] == 7).all())
+    # as above, and the eight wavefronts' sums are added
+    scale = norm.astype(np.float64)[:, None] / np.sqrt(d)
+    assert np.abs((wide[:n, :d].cpu().numpy() - reference(parts, prod, norm)) / scale).max() < (5 * d / 64 * (bits + prod) + 8) * 6 * 2.0**-24
+
+
 @pytest.mark.parametrize("d,n", [(128, 100), (128, 8200), (256, 5000)])
 def test_images_without_digits(d, n):
     """TQ_FLAG_DEQUANT_IMAGES alone: images that end before the digits (made so here: the buffer is cut there), and the kernels that do without."""
