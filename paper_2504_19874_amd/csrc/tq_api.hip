@@ -43,10 +43,15 @@ constexpr int64_t kRowsQuantMax = 64;  // at most this many long vectors take th
 // 2.0e-6 on the contraction, 2.4e-7 for bf16 vectors).  Measured, this route, and the contraction at the next larger size, in us:
 //   Alg. 1  d = 1024: 64 vectors 9.5, 65 12.0; 1536: 32 9.7, 64 15.7, 65 14.9; 3072: 8 13.9, 16 16.7, 24 22.7; 4096: 8 23.4, 12 29.5
 //   Alg. 2  d = 1024: 64 18.6, 65 21.7; 1536: 32 19.8, 48 29.6; 3072: 8 28.6, 12 43.5; 4096: 4 44.5, 8 54.4
-// (The dequantiser's route reads both matrices in one kernel and has no second stage; its bound is twice as wide.)
 bool rows_route_serves(int64_t n, int d, int matrices, int64_t limit = 150) {
   return n <= kRowsQuantMax && d >= 512 && d <= 4096 && ((n + 3) / 4) * (int64_t)d * d * matrices <= limit * 512 * 512;
 }
+
+// The dequantiser's (tq_score_small.hip: both matrices in one kernel, decoding and products by vector instructions), against the kernels on the matrix cores,
+// us: 4 bits d = 64 1 code 3.5 / 5.2, 256 4.9 / 5.9; 128 1 3.4 / 6.4, 256 6.5 / 7.3; 256 256 5.9 / 8.5; 512 256 9.5 / 12.6; 768 256 15.1 / 16.9; 1024 192
+// 18.3 / 20.8, 256 22.6 / 22.1; 1536 128 26.4 / 30.4, 192 37.3 / 30.6; 3072 32 31 / 56 (48 codes), 64 58.5 / 55.8; 3 + 1 bits 384 256 12.8 / 15.0; 768 256 23.0 / 30.6; 1536 128
+// 43.7 / 56.6, 192 63.8 / 56.8; 3072 32 94 / 108, 64 237 / 109.
+bool dequant_rows_serves(int64_t n, int d) { return n <= 256 && d < 4096 && n * d <= (d <= 2048 ? 128 * 1536 : 32 * 3072); }
 
 inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 inline size_t round_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
@@ -606,6 +611,12 @@ tq_status tq_dequantize(const tq_params* p, const uint32_t* idx, const uint32_t*
     if (digits != nullptr || own)
       return from_hip(launch_sign128_dequant(p->bits_mse, prod, idx, qjl, gamma, norm, digits, p->Pi, p->S, x_out, ldo, n, kappa_of(128), sc, s));
   }
+  const bool few_rows = !fp32_mfma_only(p) && dequant_rows_serves(n, p->d);
+  auto by_rows = [&] {
+    return from_hip(launch_dequant_rows(p->bits_mse, prod, p->d, n, idx, qjl, gamma, norm, p->PiT, p->ST, make_codebook(p), kappa_of(p->d), x_out, ldo,
+                                        static_cast<hipStream_t>(stream)));
+  };
+  if (p->d == 128 && few_rows) return by_rows();
   // large batches at d = 128: decoded codes straight into bf16 MFMA operands, pieces of Pi^T / S^T in LDS
   if (p->d == 128 && n > kBf3DequantRows && !fp32_mfma_only(p) && dequant128_bf3_applicable(p->bits_mse, prod, make_codebook(p), x_out, ldo))
     return from_hip(launch_dequant128_bf3(p->bits_mse, prod, idx, qjl, gamma, norm, p->PiT, p->ST, x_out, ldo, n,
@@ -617,19 +628,13 @@ tq_status tq_dequantize(const tq_params* p, const uint32_t* idx, const uint32_t*
                                       kappa_of(p->d), make_codebook(p), 0, 0.f, make_codebook(p),
                                       static_cast<hipStream_t>(stream)));
   }
-  // A table that is a sum of signs, by its digits.  A few long codes by matrix-vector products in fp32, unless there is a sketch and d >= 1024: else digits
-  // are a little further from 64 bits (of a coordinate's root mean square, products / digits: d = 512, 2 bits 0.8 / 1.3e-7; 768, 2 + 1 bits 1.18 / 1.25e-7; 1536, 2 + 1 bits
-  // 1.46 / 1.27e-7).  The first of those, too, where they take less time (us, 1536, 2 + 1 bits, 1 code 7.2 / 8.0, 2 8.6 / 8.1; 1024, 1 + 1 bits, 4 5.1 / 6.3,
-  // 8 6.6 / 6.5; 3072, 1 + 1 bits, 1 16.4 / 13.3).
-  const bool has_digits = h2_dequant_images(p) != nullptr && sign_images(p);
-  const bool by_digits = !fp32_mfma_only(p) && sign_gemm_serves(p->bits_mse, prod, p->d, n, has_digits) && (p->bits_mse > 0 || prod) && p->Pi != nullptr &&
+  // A few codes by matrix-vector products in fp32.  Of a table that is a sum of signs only a few long ones, the others by digits, whether the matrices' are there or made
+  // in the call: from the least codes on these take about the same time (us, products / digits: 256, 2 + 1 bits, 16 codes 3.5 / 3.9; 768 32 6.2 / 6.6; 1536 4 7.9 / 8.2, 16 9.7 /
+  // 8.9; 2 bits 64 14.7 / 8.1), but without a sketch, or with one below d = 1024, they are a little further from 64 bits (of a coordinate's root mean square, d = 512, 2 bits,
+  // 0.8 / 1.3e-7; 768, 2 + 1 bits 1.18 / 1.25e-7; 1536, 2 + 1 bits 1.46 / 1.27e-7).
+  const bool by_digits = !fp32_mfma_only(p) && sign_gemm_serves(p->bits_mse, prod, p->d, n) && (p->bits_mse > 0 || prod) && p->Pi != nullptr &&
                          (!prod || p->S != nullptr) && sign_table(p->bits_mse, make_codebook(p), &sc);
-  const bool first_few = !by_digits || !has_digits || !prod || p->d < 1024 || n * p->d * p->d <= 4500000;
-  // a handful of long vectors: matrix-vector products (the matrices are read once per block of 4 vectors, 2 with a
-  // sketch; the same bound as for the quantiser's route)
-  if (first_few && p->d < 4096 && !fp32_mfma_only(p) && rows_route_serves(prod ? 2 * n : n, p->d, prod ? 2 : 1, 300))
-    return from_hip(launch_dequant_rows(p->bits_mse, prod, p->d, n, idx, qjl, gamma, norm, p->PiT, p->ST, make_codebook(p),
-                                        kappa_of(p->d), x_out, ldo, static_cast<hipStream_t>(stream)));
+  if (by_digits ? p->d < 4096 && rows_route_serves(prod ? 2 * n : n, p->d, prod ? 2 : 1, 300) : few_rows) return by_rows();
   // many codes of a table that is a sum of signs: digits of Pi^T and S^T, from the images or made here where the workspace holds them
   if (by_digits) {
     const hipStream_t s = static_cast<hipStream_t>(stream);

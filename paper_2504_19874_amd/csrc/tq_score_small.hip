@@ -148,87 +148,142 @@ hipError_t launch_matvec_rows(int d, int64_t n, const float* W0, const float* W1
 }
 
 // DeQuant of Alg. 1 / Alg. 2 for a handful of long vectors: x~[k] = nu (sum_j Pi^T[k][j] c[idx_j] + kappa gamma
-// sum_j S^T[k][j] z_j), one wavefront per output coordinate k (a row of Pi^T and of S^T, 1 KB per load), the decoded
-// codes of Q vectors in LDS (4 for Alg. 1; 2 for Alg. 2, whose sign vector sits beside them).
-template <int BITS, bool PROD>
+// sum_j S^T[k][j] z_j), R output coordinates k per wavefront (rows of Pi^T and of S^T, 1 KB per load), the decoded
+// codes of Q vectors in LDS (Alg. 2: their sign vectors behind them).  A thread decodes four neighbouring coordinates at a time; the rows' beginning is on
+// its way meanwhile.  Many codes are bound by the decoding, which every workgroup does for itself: more rows per wavefront then.  (A row per wavefront, decoded
+// a coordinate at a time, before -> now, us: 1536, 4 bits, 1 code 7.4 -> 5.6, 16 18.2 -> 8.9, 64 53.4 -> 14.7; 3072, 4 bits, 16 100 -> 16.9; 768, 3 + 1
+// bits, 32 11.8 -> 6.2.)
+template <int BITS, bool PROD, int Q, int R>
 __global__ __launch_bounds__(256) void dequant_rows_kernel(const int d, const int n, const uint32_t* __restrict__ idx,
                                                            const uint32_t* __restrict__ qjl, const float* __restrict__ gamma,
                                                            const float* __restrict__ norm, const float* __restrict__ PiT,
                                                            const float* __restrict__ ST, const Codebook cb, const float kappa,
                                                            float* __restrict__ out, const int64_t ldo) {
-  constexpr int Q = PROD ? 2 : 4;
+  constexpr int NB = BITS > 0 ? BITS : 1;
   extern __shared__ __attribute__((aligned(16))) float ys[];  // [Q][d], then (PROD) [Q][d] of +-kappa gamma
   __shared__ float cent_s[16];
   float* const zs = ys + Q * d;
   const int tid = threadIdx.x, lane = tid & 63;
   const int q0 = blockIdx.y * Q;
-  if (tid < 16) cent_s[tid] = cb.c[tid];
-  __syncthreads();
-  const int groups = d >> 5;
-  for (int e = tid; e < Q * d; e += 256) {
-    const int r = e / d, k = e - r * d;
-    const int64_t row = q0 + r;
-    float y = 0.f, z = 0.f;
-    if (row < n) {
-      int code = 0;
+  const int j0 = (blockIdx.x * 4 + (tid >> 6)) * R;
+  const bool live = j0 < d;  // d is a multiple of 4 R: whole wavefronts
+  const int n4 = d >> 2, groups = d >> 5;
+  const float4* const w4 = reinterpret_cast<const float4*>(PiT + (int64_t)(live ? j0 : 0) * d);
+  const float4* const s4 = PROD ? reinterpret_cast<const float4*>(ST + (int64_t)(live ? j0 : 0) * d) : nullptr;
+  float4 w[R], sv[PROD ? R : 1];
+  auto load = [&](float4 (&wo)[R], float4 (&so)[PROD ? R : 1], int k4) {  // past the rows' end: their last values again
 #pragma unroll
-      for (int pl = 0; pl < BITS; ++pl) code |= (int)((idx[row * (int64_t)(groups * BITS) + (k >> 5) * BITS + pl] >> (k & 31)) & 1u) << pl;
-      y = cent_s[code];
-      if (PROD) {
-        const float kg = kappa * gamma[row];
-        z = ((qjl[row * groups + (k >> 5)] >> (k & 31)) & 1u) ? kg : -kg;
-      }
+    for (int i = 0; i < R; ++i) {
+      wo[i] = w4[i * n4 + min(k4, n4 - 1)];
+      if constexpr (PROD) so[i] = s4[i * n4 + min(k4, n4 - 1)];
     }
-    ys[e] = y;
-    if (PROD) zs[e] = z;
-  }
-  __syncthreads();
-  const int j = blockIdx.x * 4 + (tid >> 6);
-  if (j >= d) return;  // the whole wavefront
-  const float4* w4 = reinterpret_cast<const float4*>(PiT + (int64_t)j * d);
-  const float4* s4 = PROD ? reinterpret_cast<const float4*>(ST + (int64_t)j * d) : nullptr;
-  float acc[Q];
+  };
+  if (tid < 16) cent_s[tid] = cb.c[tid];
+  float kg[Q];
 #pragma unroll
-  for (int r = 0; r < Q; ++r) acc[r] = 0.f;
-  for (int k4 = lane; k4 < d / 4; k4 += 64) {
-    const float4 w = w4[k4];
-    float4 sv = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (PROD) sv = s4[k4];
+  for (int r = 0; r < Q; ++r) kg[r] = PROD ? kappa * gamma[min(q0 + r, n - 1)] : 0.f;  // past the end: the last code again, not stored
+  uint32_t word[Q][NB], sign[Q];
+  auto fetch = [&](int e) {  // of four coordinates: their bits of the planes' words from bit 0 on
 #pragma unroll
     for (int r = 0; r < Q; ++r) {
-      const float4 v = reinterpret_cast<const float4*>(ys + r * d)[k4];
-      acc[r] = fmaf(w.x, v.x, fmaf(w.y, v.y, fmaf(w.z, v.z, fmaf(w.w, v.w, acc[r]))));
-      if (PROD) {
-        const float4 u = reinterpret_cast<const float4*>(zs + r * d)[k4];
-        acc[r] = fmaf(sv.x, u.x, fmaf(sv.y, u.y, fmaf(sv.z, u.z, fmaf(sv.w, u.w, acc[r]))));
+      const int64_t at = (int64_t)min(q0 + r, n - 1) * groups + (e >> 3);
+#pragma unroll
+      for (int pl = 0; pl < BITS; ++pl) word[r][pl] = idx[at * BITS + pl] >> 4 * (e & 7);
+      if constexpr (PROD) sign[r] = qjl[at] >> 4 * (e & 7);
+    }
+  };
+  fetch(min(tid, n4 - 1));
+  load(w, sv, lane);
+  __syncthreads();  // the table
+  for (int e = tid; e < n4;) {
+#pragma unroll
+    for (int r = 0; r < Q; ++r) {
+      float y[4];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        uint32_t code = 0;
+#pragma unroll
+        for (int pl = 0; pl < BITS; ++pl) code |= (word[r][pl] >> k & 1u) << pl;
+        y[k] = cent_s[code];
       }
+      reinterpret_cast<float4*>(ys + r * d)[e] = make_float4(y[0], y[1], y[2], y[3]);
+      if constexpr (PROD)
+        reinterpret_cast<float4*>(zs + r * d)[e] = make_float4((sign[r] & 1u) ? kg[r] : -kg[r], (sign[r] & 2u) ? kg[r] : -kg[r],
+                                                               (sign[r] & 4u) ? kg[r] : -kg[r], (sign[r] & 8u) ? kg[r] : -kg[r]);
+    }
+    e += 256;
+    if (e < n4) fetch(e);
+  }
+  __syncthreads();
+  if (!live) return;  // the whole wavefront
+  float acc[R][Q];
+#pragma unroll
+  for (int i = 0; i < R; ++i)
+#pragma unroll
+    for (int r = 0; r < Q; ++r) acc[i][r] = 0.f;
+  for (int k0 = 0; k0 < n4; k0 += 64) {
+    float4 wn[R], sn[PROD ? R : 1];
+    if (k0 + 64 < n4) load(wn, sn, k0 + 64 + lane);
+    const int k4 = k0 + lane;
+    if (k4 < n4)
+#pragma unroll
+      for (int r = 0; r < Q; ++r) {
+        const float4 v = reinterpret_cast<const float4*>(ys + r * d)[k4];
+        float4 u = make_float4(0.f, 0.f, 0.f, 0.f);
+        if constexpr (PROD) u = reinterpret_cast<const float4*>(zs + r * d)[k4];
+#pragma unroll
+        for (int i = 0; i < R; ++i) {
+          acc[i][r] = fmaf(w[i].x, v.x, fmaf(w[i].y, v.y, fmaf(w[i].z, v.z, fmaf(w[i].w, v.w, acc[i][r]))));
+          if constexpr (PROD) acc[i][r] = fmaf(sv[i].x, u.x, fmaf(sv[i].y, u.y, fmaf(sv[i].z, u.z, fmaf(sv[i].w, u.w, acc[i][r]))));
+        }
+      }
+#pragma unroll
+    for (int i = 0; i < R; ++i) {
+      w[i] = wn[i];
+      if constexpr (PROD) sv[i] = sn[i];
     }
   }
 #pragma unroll
-  for (int off = 32; off >= 1; off >>= 1)
+  for (int i = 0; i < R; ++i)
 #pragma unroll
-    for (int r = 0; r < Q; ++r) acc[r] += __shfl_xor(acc[r], off);
-  if (lane < Q && q0 + lane < n) {
-    float v = acc[0];
+    for (int r = 0; r < Q; ++r) acc[i][r] = over_wavefront(acc[i][r], [](float x, float y) { return x + y; });
+  float v = 0.f;
 #pragma unroll
-    for (int r = 1; r < Q; ++r) v = lane == r ? acc[r] : v;
-    const float nu = norm != nullptr ? norm[q0 + lane] : 1.f;
-    out[(int64_t)(q0 + lane) * ldo + j] = nu * v;
-  }
+  for (int i = 0; i < R; ++i)
+#pragma unroll
+    for (int r = 0; r < Q; ++r) v = lane == r * R + i ? acc[i][r] : v;
+  const int row = q0 + lane / R;
+  if (lane < R * Q && row < n) out[(int64_t)row * ldo + j0 + lane % R] = (norm != nullptr ? norm[row] : 1.f) * v;
 }
 
 template <int BITS>
 static hipError_t dequant_rows_bits(bool prod, int d, int n, const uint32_t* idx, const uint32_t* qjl, const float* gamma,
                                     const float* norm, const float* PiT, const float* ST, const Codebook& cb, float kappa,
                                     float* out, int64_t ldo, hipStream_t s) {
-  const int Q = prod ? 2 : 4;
-  const dim3 grid((d + 3) / 4, (n + Q - 1) / Q);
-  const size_t lds = (size_t)(prod ? 2 : 1) * Q * d * sizeof(float);
-  if (prod)
-    hipLaunchKernelGGL((dequant_rows_kernel<BITS, true>), grid, dim3(256), lds, s, d, n, idx, qjl, gamma, norm, PiT, ST, cb, kappa, out, ldo);
-  else
-    hipLaunchKernelGGL((dequant_rows_kernel<BITS, false>), grid, dim3(256), lds, s, d, n, idx, qjl, gamma, norm, PiT, ST, cb, kappa, out, ldo);
-  return hipGetLastError();
+  auto go = [&](auto prod_c, auto q_c, auto r_c) {
+    constexpr bool PROD = decltype(prod_c)::value;
+    constexpr int Q = decltype(q_c)::value, R = decltype(r_c)::value;
+    hipLaunchKernelGGL((dequant_rows_kernel<BITS, PROD, Q, R>), dim3((d + 4 * R - 1) / (4 * R), (n + Q - 1) / Q), dim3(256),
+                       (size_t)(PROD ? 2 : 1) * Q * d * sizeof(float), s, d, n, idx, qjl, gamma, norm, PiT, ST, cb, kappa, out, ldo);
+    return hipGetLastError();
+  };
+  using std::integral_constant;
+  // One row per wavefront up to `once` workgroups per compute unit, two up to `twice`, else four (the decoding is shared by all of a workgroup's; us with
+  // 1 / 2 / 4, 4 bits: 8 codes of 1024 5.0 / 5.5 / 6.4, 16 6.4 / 5.6 / 6.5, 32 9.9 / 7.2 / 6.8; 2 + 1 bits of 768: 4 4.0 / 4.5 / 5.6, 16 5.3 / 5.1 / 5.8; 32 of 1536,
+  // 3 + 1 bits, 27 / 17 / 13).  Eight codes per workgroup, four with a sketch, while 64 KB hold them (3072: 32 codes of 4 bits 31 us, with 96 KB 48).
+  const int64_t cus = device_cu_count();
+  auto rows = [&](auto prod_c, auto q_c, int64_t once, int64_t twice) {
+    const int64_t all = (int64_t)(d / 4) * ((n + decltype(q_c)::value - 1) / decltype(q_c)::value);
+    if (all <= once * cus) return go(prod_c, q_c, integral_constant<int, 1>{});
+    if (all <= twice * cus) return go(prod_c, q_c, integral_constant<int, 2>{});
+    return go(prod_c, q_c, integral_constant<int, 4>{});
+  };
+  if (prod) {
+    if (n <= 2 || d > 2048) return rows(std::true_type{}, integral_constant<int, 2>{}, 3, 6);
+    return rows(std::true_type{}, integral_constant<int, 4>{}, 2, 6);
+  }
+  if (n <= 4 || d > 2048) return rows(std::false_type{}, integral_constant<int, 4>{}, 3, 3);
+  return rows(std::false_type{}, integral_constant<int, 8>{}, 1, 2);
 }
 
 hipError_t launch_dequant_rows(int bits, bool prod, int d, int64_t n, const uint32_t* idx, const uint32_t* qjl,

@@ -91,7 +91,7 @@ __device__ __forceinline__ floatx16 sign_mfma(const v8i_t& signs, const v8i_t& d
 constexpr int SIGN_STEP_BYTES = 8192;
 __host__ __device__ constexpr size_t sign_gemm_image_bytes(int d) { return (size_t)(d / 64) * (d / 32) * SIGN_STEP_BYTES; }
 bool sign_gemm_images(int d);  // images of this form are kept at this d
-bool sign_gemm_serves(int bits, bool prod, int d, int64_t n, bool digits);  // digits: images of them are there, not to be made for the call
+bool sign_gemm_serves(int bits, bool prod, int d, int64_t n);
 hipError_t launch_sign_gemm_image(const float* W, int d, void* image, hipStream_t s);
 hipError_t launch_sign_gemm(int bits, bool prod, const void* pi_image, const void* s_image, int d, const uint32_t* idx, const uint32_t* qjl,
                             const float* gamma, const float* norm, int64_t n, float* out, int64_t ldo, float kappa, const SignCoefs& c, hipStream_t s);

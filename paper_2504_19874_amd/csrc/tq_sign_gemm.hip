@@ -511,8 +511,8 @@ bool sign_gemm_images(int d) { return d >= 256 && d % 128 == 0; }
 
 // Two bits without a sketch are two streams, ten products of a digit, where fp16 pieces take three products of twice the steps' length each:
 // between few codes and 2^20 coordinates these have the smaller tiles (768 coordinates: 1000 codes 16.8 us, 17.0 with sign_gemm_kernel; 3000 24.2, 18.1).
-bool sign_gemm_serves(int bits, bool prod, int d, int64_t n, bool digits) {
-  return sign_gemm_images(d) && (prod || bits != 2 || (digits && few_serves(bits, prod, d, n)) || n * d >= 1 << 20);
+bool sign_gemm_serves(int bits, bool prod, int d, int64_t n) {
+  return sign_gemm_images(d) && (prod || bits != 2 || few_serves(bits, prod, d, n) || n * d >= 1 << 20);
 }
 
 hipError_t launch_sign_gemm_image(const float* W, int d, void* image, hipStream_t s) {
