@@ -36,15 +36,19 @@ constexpr int64_t kChunkRows = 65536;  // rows per pass of the quantiser at most
 // Row strides of vectors (x, q) and of dequantised output: the kernels address a tile's rows with 32-bit byte
 // offsets from a 64-bit tile base (up to 256 rows of ld * 4 bytes)
 constexpr int64_t kMaxRowStride = int64_t(1) << 22;
-constexpr int64_t kRowsQuantMax = 64;  // at most this many long vectors take the matrix-vector route of the quantiser
-// That route reads every matrix once per block of four vectors, plain fp32 multiply-adds; the fp16 contraction once per
-// tile, and reads 17 bits of an fp32 vector.  The line between them, blocks x d^2 x matrices, lies at 4e7 elements, about where
-// the two take the same time: up to there vectors keep all their bits (mean error of a rotated coordinate 0.8 - 1.2e-7 sigma;
-// 2.0e-6 on the contraction, 2.4e-7 for bf16 vectors).  Measured, this route, and the contraction at the next larger size, in us:
-//   Alg. 1  d = 1024: 64 vectors 9.5, 65 12.0; 1536: 32 9.7, 64 15.7, 65 14.9; 3072: 8 13.9, 16 16.7, 24 22.7; 4096: 8 23.4, 12 29.5
-//   Alg. 2  d = 1024: 64 18.6, 65 21.7; 1536: 32 19.8, 48 29.6; 3072: 8 28.6, 12 43.5; 4096: 4 44.5, 8 54.4
-bool rows_route_serves(int64_t n, int d, int matrices, int64_t limit = 150) {
-  return n <= kRowsQuantMax && d >= 512 && d <= 4096 && ((n + 3) / 4) * (int64_t)d * d * matrices <= limit * 512 * 512;
+// Up to here vectors take the matrix-vector route of the quantiser.  It reads every matrix once per block of four vectors, plain fp32 multiply-adds; the
+// contraction on the matrix cores once per tile, and reads 17 bits of an fp32 vector.  The line between them, blocks x d^2, lies at 4e7 elements, at 64 vectors, and for short
+// ones at 65536 values (half with a sketch), about where the two take the same time: up to there vectors keep all their bits (mean error of a rotated coordinate
+// 0.8 - 1.2e-7 sigma; 2.0e-6 on the contraction, 2.4e-7 for bf16 vectors).  Measured, this route / the contraction, in us:
+//   Alg. 1  d = 64: 1 vector 3.3 / 6.4, 256 4.7 / 7.5; 256: 1 3.4 / 7.8, 256 7.8 / 8.9, 512 12.2 / 8.8; 512: 128 8.3 / 10.1, 192 10.7 / 10.1; 768: 64 8.5 / 11.6 (96); 1536: 64
+//           17.0 / 16.2; 3072: 16 15.7 / 22.0 (32), 32 26.7 / 22.0
+//   Alg. 2  d = 256: 1 6.1 / 11.3, 128 10.7 / 12.8, 192 12.7 / 12.5; 512: 64 11.4 / 16.0 (96); 1536: 32 19.5 / 29.9 (48), 64 30.7 / 30.8; 3072: 16 29.9 / 45.2, 32 51.3 / 49.6
+bool quant_rows_serves(int64_t n, int d, bool prod) {
+  return d <= 4096 && n <= 256 && (n <= 64 || n * d <= (prod ? 32768 : 65536)) && ((n + 3) / 4) * (int64_t)d * d <= 150 * 512 * 512;
+}
+// of a table that is a sum of signs, the dequantiser's (see there)
+bool rows_before_digits(int64_t n, int d, bool prod) {
+  return n <= (prod ? 32 : 64) && d >= 512 && d < 4096 && (((prod ? 2 : 1) * n + 3) / 4) * (int64_t)d * d * (prod ? 2 : 1) <= 300 * 512 * 512;
 }
 
 // The dequantiser's (tq_score_small.hip: both matrices in one kernel, decoding and products by vector instructions), against the kernels on the matrix cores,
@@ -348,7 +352,7 @@ tq_status quantize_common(const tq_params* p, const void* x, int32_t dtype, int6
 
   if (!prod) {
     // a handful of long vectors: a matrix-vector product per vector instead of the tiled contraction's serial k-loop
-    if (rows_route_serves(n, d, 1) && !fp32_mfma_only(p))
+    if (quant_rows_serves(n, d, false) && !fp32_mfma_only(p))
       return from_hip(launch_quant_rows(p->bits_mse, dtype == TQ_BF16, x, ldx, n, d, p->Pi, make_codebook(p), idx, norm, stream));
     if (h2_serves && quantize_h2(p, x, dtype == TQ_BF16, n, ldx, idx, nullptr, nullptr, norm, false, stream, &st)) return st;
     a.X = x;
@@ -359,7 +363,7 @@ tq_status quantize_common(const tq_params* p, const void* x, int32_t dtype, int6
   }
 
   // a handful of long vectors: the matrix-vector route (see above), the sketch included, when the workspace holds the residual
-  if (rows_route_serves(n, d, 2) && !fp32_mfma_only(p)) {
+  if (quant_rows_serves(n, d, true) && !fp32_mfma_only(p)) {
     Workspace ws2{static_cast<char*>(p->workspace), p->workspace_bytes, 0};
     if (float* const ew = static_cast<float*>(ws2.take((size_t)n * d * sizeof(float))); ew != nullptr)
       return from_hip(launch_quant_rows(p->bits_mse, dtype == TQ_BF16, x, ldx, n, d, p->Pi, make_codebook(p), idx, norm, stream,
@@ -634,7 +638,7 @@ tq_status tq_dequantize(const tq_params* p, const uint32_t* idx, const uint32_t*
   // 0.8 / 1.3e-7; 768, 2 + 1 bits 1.18 / 1.25e-7; 1536, 2 + 1 bits 1.46 / 1.27e-7).
   const bool by_digits = !fp32_mfma_only(p) && sign_gemm_serves(p->bits_mse, prod, p->d, n) && (p->bits_mse > 0 || prod) && p->Pi != nullptr &&
                          (!prod || p->S != nullptr) && sign_table(p->bits_mse, make_codebook(p), &sc);
-  if (by_digits ? p->d < 4096 && rows_route_serves(prod ? 2 * n : n, p->d, prod ? 2 : 1, 300) : few_rows) return by_rows();
+  if (by_digits ? rows_before_digits(n, p->d, prod) : few_rows) return by_rows();
   // many codes of a table that is a sum of signs: digits of Pi^T and S^T, from the images or made here where the workspace holds them
   if (by_digits) {
     const hipStream_t s = static_cast<hipStream_t>(stream);

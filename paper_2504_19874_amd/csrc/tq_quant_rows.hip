@@ -6,7 +6,8 @@
 // matrix rows and the vector together, the joining of the lanes.  One vector, d = 1536, 4 bits: the products alone 3.3 us and
 // a second kernel of one workgroup
 // that normalised, decided and packed 5.6; a call took 8.6 us and takes 4.3, most of it the host's (d = 3072: 18.6 -> 6.8; Alg. 2 at
-// 1 + 1 bits 27.3 -> 14.9; four vectors, d = 1536, 12.0 -> 5.8 and 20.4 -> 12.7).
+// 1 + 1 bits 27.3 -> 14.9; four vectors, d = 1536, 12.0 -> 5.8 and 20.4 -> 12.7, then, asked for together on their way to LDS, 5.6 and 11.4; eight at a
+// time instead 6.4 / 8.4 for eight vectors).
 #include "tq_d128_tile.h"
 #include "tq_score_i8_prep.h"
 
@@ -67,10 +68,13 @@ __global__ __launch_bounds__(256) void quant_rows_kernel(const RowsArgs a, const
   };
   load_w(0);
   if (Q > 1) {
+    for (int k4 = tid; k4 < n4; k4 += 256) {  // all vectors' loads under way together
+      float4 y[Q];
 #pragma unroll
-    for (int r = 0; r < Q; ++r)
-      for (int k4 = tid; k4 < n4; k4 += 256)
-        reinterpret_cast<float4*>(xs + r * a.d)[k4] = load_x(q0 + r < a.n ? q0 + r : a.n - 1, k4);  // past the end: not stored
+      for (int r = 0; r < Q; ++r) y[r] = load_x(q0 + r < a.n ? q0 + r : a.n - 1, k4);  // past the end: not stored
+#pragma unroll
+      for (int r = 0; r < Q; ++r) reinterpret_cast<float4*>(xs + r * a.d)[k4] = y[r];
+    }
     __syncthreads();
   }
   float acc[R][Q], ss[Q];
