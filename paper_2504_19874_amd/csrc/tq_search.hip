@@ -14,7 +14,7 @@
 // A list that overflows (thousands of equal scores) flags its query: the caller runs the kernels that look at everything,
 // which skip blocks of queries without a flag.
 //
-// 1000 queries, 10^6 codes, k = 10, d = 1536, 4 bits: 3.6 ms, 9.5 with every score from the exact kernel; 3.4 of it are
+// 1000 queries, 10^6 codes, k = 10, d = 1536, 4 bits: 3.2 ms, 9.5 with every score from the exact kernel; 3.07 of it are
 // the find kernel's.  500 queries, 30000 codes, k = 64, d = 512: 136 us (284 with 4096 codes in the sample: the gathering
 // overflowed).
 #include <algorithm>

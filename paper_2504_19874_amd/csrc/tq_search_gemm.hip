@@ -13,8 +13,8 @@
 // the end of the next tile, and the pairs stored at the end of the one after that (d = 128, 10^6 codes, 1000
 // queries: 605 us, was 1037 with a trip each).
 //
-// Bound by the matrix cores and, at 3 and 4 bits, by the decoding's vector instructions (10^6 codes, 1000 queries: d = 1536, 4 bits
-// 3.2 ms, 0.95 PFLOP/s; d = 3072, 1 + 1 bits 10.6 ms, 1.16; d = 128, 4 bits 0.48 ms, 0.53).  With the loading and the decoding
+// Bound by the power of the matrix cores and, at 3 and 4 bits, by the decoding's vector instructions (10^6 codes, 1000 queries: d = 1536, 4 bits
+// 3.07 ms, 1.0 PFLOP/s; d = 3072, 1 + 1 bits 9.1 ms, 1.35; d = 128, 4 bits 0.55 ms, 0.46; in registers 1.62).  With the loading and the decoding
 // given to four wavefronts each it was no faster at d = 3072 and slower elsewhere (registers).
 #include <cstring>
 

@@ -5,8 +5,8 @@
 // few wavefronts.  One accumulator per kind of sign, the small digits first, joined with the codes' factors in the end: a sum meets two
 // roundings at its full size where pieces met ten times as many.
 //
-// Bound by the stores (131072 codes: 67 MB, 15.6 us at the rate of a copy).  Per block and wavefront 10 - 30 matrix instructions and
-// about 170 others.  3 bits in all, one call, us, with the images, before -> now: 8 codes 8.5 -> 3.4, 4096 9.5 -> 4.2, 16384
+// Bound by the stores (131072 codes: 67 MB, 11.2 us alone) and the instructions together: per block and wavefront 10 - 30 matrix instructions and
+// about 170 others, which the stores cover in part (codes asked for two blocks ahead: 5 % slower).  3 bits in all, one call, us, with the images, before -> now: 8 codes 8.5 -> 3.4, 4096 9.5 -> 4.2, 16384
 // 10.3 -> 5.5, 131072 23.8 -> 19.3, 524288 84 -> 65; 2 bits without a sketch 131072 17.4 -> 14.1.  Error against 64 bits, of a
 // coordinate's root mean square: above 8192 codes 2.5 - 3.8e-6 -> 1.55e-6, up to them 0.92 - 1.17e-7 -> 0.69 - 0.78e-7.
 #include <type_traits>
