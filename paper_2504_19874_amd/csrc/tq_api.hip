@@ -52,10 +52,10 @@ bool rows_before_digits(int64_t n, int d, bool prod) {
 }
 
 // The dequantiser's (tq_score_small.hip: both matrices in one kernel, decoding and products by vector instructions), against the kernels on the matrix cores,
-// us: 4 bits d = 64 1 code 3.5 / 5.2, 256 4.9 / 5.9; 128 1 3.4 / 6.4, 256 6.5 / 7.3; 256 256 5.9 / 8.5; 512 256 9.5 / 12.6; 768 256 15.1 / 16.9; 1024 192
+// us: 4 bits d = 64 1 code 3.1 / 5.2, 512 5.2 / 5.9, 640 6.1 / 5.9; 128 1 3.1 / 6.4, 512 5.9 / 7.3, 1024 7.8 / 7.3; 256 512 8.1 / 8.5, 640 9.1 / 8.6; 384 (3 bits) 256 8.3 / 9.9, 384 10.8 / 10.0; 512 256 9.5 / 12.6; 768 256 15.1 / 16.9; 1024 192
 // 18.3 / 20.8, 256 22.6 / 22.1; 1536 128 26.4 / 30.4, 192 37.3 / 30.6; 3072 32 31 / 56 (48 codes), 64 58.5 / 55.8; 3 + 1 bits 384 256 12.8 / 15.0; 768 256 23.0 / 30.6; 1536 128
 // 43.7 / 56.6, 192 63.8 / 56.8; 3072 32 94 / 108, 64 237 / 109.
-bool dequant_rows_serves(int64_t n, int d) { return n <= 256 && d < 4096 && n * d <= (d <= 2048 ? 128 * 1536 : 32 * 3072); }
+bool dequant_rows_serves(int64_t n, int d) { return n <= (d <= 256 ? 512 : 256) && d < 4096 && n * d <= (d <= 2048 ? 128 * 1536 : 32 * 3072); }
 
 inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 inline size_t round_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
