@@ -327,6 +327,15 @@ tq_status quantize_common(const tq_params* p, const void* x, int32_t dtype, int6
     return from_hip(launch_quant128_bf3(p->bits_mse, prod, dtype == TQ_F32, x, ldx, n, p->Pi, prod ? p->SPiT : nullptr, idx, qjl, gamma,
                                         norm, make_codebook(p), 0, make_codebook(p), quant_image(p), stream));
 
+  // head dimension 128, a few fp32 vectors: matrix-vector products, all bits here and there (us, that kernel / these: 4 bits 1 vector 4.8 / 3.3, 256 6.4 / 5.5, 384 6.4 / 6.6; 2 + 1
+  // bits 1 7.1 / 6.2, 64 8.6 / 8.2, 128 8.7 / 9.4)
+  if (d == 128 && dtype == TQ_F32 && n <= (prod ? 64 : 256) && !fp32_mfma_only(p)) {
+    Workspace ws2{static_cast<char*>(p->workspace), p->workspace_bytes, 0};
+    float* const ew = prod ? static_cast<float*>(ws2.take((size_t)n * d * sizeof(float))) : nullptr;
+    if (!prod || ew != nullptr)
+      return from_hip(launch_quant_rows(p->bits_mse, false, x, ldx, n, d, p->Pi, make_codebook(p), idx, norm, stream, p->SPiT, ew, qjl, gamma));
+  }
+
   // head dimension 128: one fused kernel, parameters resident in LDS
   if (d == 128 && aligned16(x) && (ldx * esz) % 16 == 0) {
     return from_hip(launch_quant128(p->bits_mse, prod, dtype == TQ_BF16, x, ldx, n, p->Pi,
@@ -349,8 +358,13 @@ tq_status quantize_common(const tq_params* p, const void* x, int32_t dtype, int6
   a.pieces = pieces && !(prod && dtype == TQ_F32 && !two_piece_x_serves_prod(d, p->bits_mse));
   // below d = 512 a large batch is bound by the passes over memory that the fp16 contraction adds (pieces of the vectors and of
   // the residual), and the contraction that splits its vectors on the fly is the faster one (2 + 1 bits, 60000 / 8000 vectors: d = 256
-  // 87 against 147 us / 30 against 24; d = 384 169 against 197 / 40 against 32; d = 512 284 against 223)
-  const bool h2_serves = a.pieces && (d >= 512 || n <= 16384) && h2_codebook_serves(p->bits_mse, a.cb) && (!prod || aligned16(p->SPiT));
+  // 87 against 147 us / 30 against 24; d = 384 169 against 197 / 40 against 32; d = 512 284 against 223).  Without a sketch there is one pass less, and from three bits on
+  // that one's decisions cost more than the pass (4 bits, us, that one / this: d = 64 70000 fp32 vectors 41.6 / 30.8, 300000 109 / 133; 192 70000 85 / 61; 256 17000 bf16 31.4 / 23.9,
+  // 300000 277 / 242; 384 70000 163 / 133; 3 bits: 64 24000 12.8 / 10.0, 40000 14.3 / 14.9; 256 70000 62.0 / 49.6, 300000 205 / 213; 384 300000 379 / 359).
+  int64_t h2_most = 16384;
+  if (!prod && p->bits_mse == 4) h2_most = d >= 192 ? INT64_MAX : 131072;
+  if (!prod && p->bits_mse == 3) h2_most = d >= 320 ? INT64_MAX : d >= 192 ? 196608 : 32768;
+  const bool h2_serves = a.pieces && (d >= 512 || n <= h2_most) && h2_codebook_serves(p->bits_mse, a.cb) && (!prod || aligned16(p->SPiT));
   const NKind nk = dtype == TQ_F32 ? N_F32 : N_BF16;
 
   if (!prod) {

@@ -28,6 +28,20 @@ def test_short_vectors(d, bits, n, kind):
     T.test_quantize_mse(d, bits, n, kind)
 
 
+# d = 128, fp32: as many as go by products, and one more
+@pytest.mark.parametrize("bits,n,kind", [(4, 1, "f32"), (1, 63, "unit"), (2, 64, "f32"), (3, 65, "f32"), (4, 256, "unit"), (0, 31, "f32"), (3, 257, "f32")])
+def test_fp32_vectors_at_128(bits, n, kind):
+    T.test_quantize_prod(128, bits, n, kind)
+    T.test_quantize_mse(128, bits, n, kind)
+
+
+# three bits and more without a sketch: the contraction on fp16 pieces beyond 16384 vectors too
+@pytest.mark.parametrize("d,bits,n,kind", [(64, 3, 16385, "bf16"), (64, 3, 32769, "f32"), (64, 4, 20001, "f32"), (192, 3, 16400, "unit"), (256, 4, 17003, "bf16"), (384, 4, 16385, "f32"),
+                                           (256, 2, 16385, "f32")])
+def test_many_short_vectors(d, bits, n, kind):
+    T.test_quantize_mse(d, bits, n, kind)
+
+
 @pytest.mark.parametrize("d_hi,bits_lo,prod,n", [(64, 1, True, 513), (32, 3, True, 8209), (96, 0, False, 33), (96, 2, False, 24576)])
 def test_two_instances(d_hi, bits_lo, prod, n):
     S.test_quantize_split(d_hi, bits_lo, prod, n, True)
