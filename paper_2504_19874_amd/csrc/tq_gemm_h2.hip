@@ -85,10 +85,30 @@ __global__ __launch_bounds__(256) void split_rows_kernel(const void* x, int64_t 
       take(v[0]);
     }
   }
-  for (int m = 1; m < L; m <<= 1) {
-    ss += __shfl_xor(ss, m);
-    const uint32_t o = (uint32_t)__shfl_xor((int)mx, m);
+  // over the row's lanes, as by a butterfly over lane distances 1, 2 .. L / 2: once pairs and quads are alike, mirrored lanes hold what is to be exchanged
+  auto join = [&](uint32_t sum, uint32_t o) {
+    ss += __uint_as_float(sum);
     mx = mx > o ? mx : o;
+  };
+#define TQ_ROW_DPP(CTRL)                                                                              \
+  join((uint32_t)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(ss), CTRL, 0xf, 0xf, true), \
+       (uint32_t)__builtin_amdgcn_update_dpp(0, (int)mx, CTRL, 0xf, 0xf, true))
+  TQ_ROW_DPP(0xB1);  // lane ^ 1
+  TQ_ROW_DPP(0x4E);  // lane ^ 2
+  if (L >= 8) TQ_ROW_DPP(0x141);   // lane ^ 7
+  if (L >= 16) TQ_ROW_DPP(0x140);  // lane ^ 15
+#undef TQ_ROW_DPP
+  if (L >= 32) {
+    const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(ss), __float_as_uint(ss), false, false);
+    const auto b = __builtin_amdgcn_permlane16_swap(mx, mx, false, false);
+    ss = __uint_as_float(a[0]) + __uint_as_float(a[1]);
+    mx = b[0] > b[1] ? b[0] : b[1];
+  }
+  if (L >= 64) {
+    const auto a = __builtin_amdgcn_permlane32_swap(__float_as_uint(ss), __float_as_uint(ss), false, false);
+    const auto b = __builtin_amdgcn_permlane32_swap(mx, mx, false, false);
+    ss = __uint_as_float(a[0]) + __uint_as_float(a[1]);
+    mx = b[0] > b[1] ? b[0] : b[1];
   }
   float s, inv;
   h2_scale(mx, s, inv);
