@@ -514,7 +514,12 @@ hipError_t launch_any(const H2Args& a, const Codebook& cb, hipStream_t s) {
     case T128:  // indices only: eight wavefronts of 64 x 32 hide the decisions better than four of 64 x 64 (5 - 15 %)
       if constexpr (EK == 0) return launch_tile<EK, BITS, NPX, 2, 1, 2, 4, 4>(a, cb, s);
       else return launch_tile<EK, BITS, NPX, 2, 2, 2, 2, 4>(a, cb, s);
-    default: return launch_tile<EK, BITS, NPX, 1, 1, 2, 2, 4>(a, cb, s);
+    default:
+      // 32 vectors instead of 64 while that leaves compute units without a workgroup (a tile's bytes come through one of them), of long vectors while it leaves two
+      // fifths of them (us, 64 / 32: 512, 4 bits, 500 vectors 10.0 / 9.8; 768, 2 + 1 bits, 300 20.6 / 19.5; 1536, 2 + 1 bits, 130 32.1 / 29.7, 200 (168 workgroups)
+      // 32.5 / 33.6; 3072, 2 bits, 70 24.5 / 23.2, 100 (192) 24.6 / 27.6)
+      if ((int64_t)((a.d + 63) / 64) * ((a.n + 31) / 32) * 5 <= (int64_t)device_cu_count() * (a.d <= 1024 ? 5 : 3)) return launch_tile<EK, BITS, NPX, 1, 1, 2, 1, 4>(a, cb, s);
+      return launch_tile<EK, BITS, NPX, 1, 1, 2, 2, 4>(a, cb, s);
   }
 }
 

@@ -28,6 +28,13 @@ def test_short_vectors(d, bits, n, kind):
     T.test_quantize_mse(d, bits, n, kind)
 
 
+# tiles of 32 vectors: one and several, the last in part, the ends of the range (256 compute units)
+@pytest.mark.parametrize("d,bits,n,kind", [(512, 2, 65, "f32"), (512, 4, 1024, "bf16"), (512, 1, 1025, "unit"), (1088, 3, 288, "bf16unit"), (1088, 2, 257, "f32"), (2560, 1, 97, "bf16")])
+def test_tiles_of_32(d, bits, n, kind):
+    T.test_quantize_prod(d, bits, n, kind)
+    T.test_quantize_mse(d, bits, n, kind)
+
+
 # d = 128, fp32: as many as go by products, and one more
 @pytest.mark.parametrize("bits,n,kind", [(4, 1, "f32"), (1, 63, "unit"), (2, 64, "f32"), (3, 65, "f32"), (4, 256, "unit"), (0, 31, "f32"), (3, 257, "f32")])
 def test_fp32_vectors_at_128(bits, n, kind):
