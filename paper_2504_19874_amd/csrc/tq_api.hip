@@ -327,14 +327,11 @@ tq_status quantize_common(const tq_params* p, const void* x, int32_t dtype, int6
     return from_hip(launch_quant128_bf3(p->bits_mse, prod, dtype == TQ_F32, x, ldx, n, p->Pi, prod ? p->SPiT : nullptr, idx, qjl, gamma,
                                         norm, make_codebook(p), 0, make_codebook(p), quant_image(p), stream));
 
-  // head dimension 128, a few fp32 vectors: matrix-vector products, all bits here and there (us, that kernel / these: 4 bits 1 vector 4.8 / 3.3, 256 6.4 / 5.5, 384 6.4 / 6.6; 2 + 1
-  // bits 1 7.1 / 6.2, 64 8.6 / 8.2, 128 8.7 / 9.4)
-  if (d == 128 && dtype == TQ_F32 && n <= (prod ? 64 : 256) && !fp32_mfma_only(p)) {
-    Workspace ws2{static_cast<char*>(p->workspace), p->workspace_bytes, 0};
-    float* const ew = prod ? static_cast<float*>(ws2.take((size_t)n * d * sizeof(float))) : nullptr;
-    if (!prod || ew != nullptr)
-      return from_hip(launch_quant_rows(p->bits_mse, false, x, ldx, n, d, p->Pi, make_codebook(p), idx, norm, stream, p->SPiT, ew, qjl, gamma));
-  }
+  // head dimension 128, a few fp32 vectors without a sketch: matrix-vector products, all bits here and there (4 bits, us, the kernel
+  // below / these: 1 vector 4.8 / 3.3, 256 6.4 / 5.5, 384 6.4 / 6.6).  With a sketch they would need memory for the residual
+  // between two launches, the caller's workspace, which at this d is left alone; and they took longer (1 + 1 bits, 5 vectors 7.2 / 8.6).
+  if (d == 128 && dtype == TQ_F32 && !prod && n <= 256 && !fp32_mfma_only(p))
+    return from_hip(launch_quant_rows(p->bits_mse, false, x, ldx, n, d, p->Pi, make_codebook(p), idx, norm, stream));
 
   // head dimension 128: one fused kernel, parameters resident in LDS
   if (d == 128 && aligned16(x) && (ldx * esz) % 16 == 0) {

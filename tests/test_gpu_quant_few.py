@@ -42,6 +42,34 @@ def test_fp32_vectors_at_128(bits, n, kind):
     T.test_quantize_mse(128, bits, n, kind)
 
 
+@pytest.mark.parametrize("bits,n,bf16", [(2, 1, False), (1, 64, False), (2, 65, False), (3, 257, False), (0, 33, False), (2, 1, True), (3, 64, True), (1, 257, True)])
+def test_workspace_is_left_alone_at_128(bits, n, bf16):
+    """Two streams may quantise, or one of them score, with one parameter set at d = 128: nothing that they share is written, or needed."""
+    p = T.setup(128, bits, True)[0]
+    x = torch.randn(n, 128, generator=torch.Generator().manual_seed(n)).to(torch.bfloat16 if bf16 else torch.float32).to(T.DEV)
+    p.reserve(n).workspace.fill_(0x5a)
+    keep = p.c.workspace, p.c.workspace_bytes
+
+    def run(prod):
+        c = [torch.zeros((n, max(1, p.idx_words)), dtype=torch.int32, device=T.DEV), torch.zeros((n, p.qjl_words), dtype=torch.int32, device=T.DEV),
+             torch.zeros(n, device=T.DEV), torch.zeros(n, device=T.DEV)]
+        if prod:
+            tq.tq_quantize_prod(p, x, *c)
+        else:
+            tq.tq_quantize_mse(p, x, c[0], c[3])
+        return c
+
+    for prod in (False, True):
+        want = run(prod)
+        assert bool((p.workspace == 0x5a).all())
+        try:
+            p.c.workspace, p.c.workspace_bytes = 0, 0
+            again = run(prod)
+        finally:
+            p.c.workspace, p.c.workspace_bytes = keep
+        assert all(torch.equal(a, b) for a, b in zip(want, again))
+
+
 # three bits and more without a sketch: the contraction on fp16 pieces beyond 16384 vectors too
 @pytest.mark.parametrize("d,bits,n,kind", [(64, 3, 16385, "bf16"), (64, 3, 32769, "f32"), (64, 4, 20001, "f32"), (192, 3, 16400, "unit"), (256, 4, 17003, "bf16"), (384, 4, 16385, "f32"),
                                            (256, 2, 16385, "f32")])
