@@ -355,13 +355,9 @@ tq_status quantize_common(const tq_params* p, const void* x, int32_t dtype, int6
   a.pieces = pieces && !(prod && dtype == TQ_F32 && !two_piece_x_serves_prod(d, p->bits_mse));
   // below d = 512 a large batch is bound by the passes over memory that the fp16 contraction adds (pieces of the vectors and of
   // the residual), and the contraction that splits its vectors on the fly is the faster one (2 + 1 bits, 60000 / 8000 vectors: d = 256
-  // 87 against 147 us / 30 against 24; d = 384 169 against 197 / 40 against 32; d = 512 284 against 223).  Without a sketch there is one pass less, and from three bits on
-  // that one's decisions cost more than the pass (4 bits, us, that one / this: d = 64 70000 fp32 vectors 41.6 / 30.8, 300000 109 / 133; 192 70000 85 / 61; 256 17000 bf16 31.4 / 23.9,
-  // 300000 277 / 242; 384 70000 163 / 133; 3 bits: 64 24000 12.8 / 10.0, 40000 14.3 / 14.9; 256 70000 62.0 / 49.6, 300000 205 / 213; 384 300000 379 / 359).
-  int64_t h2_most = 16384;
-  if (!prod && p->bits_mse == 4) h2_most = d >= 192 ? INT64_MAX : 131072;
-  if (!prod && p->bits_mse == 3) h2_most = d >= 320 ? INT64_MAX : d >= 192 ? 196608 : 32768;
-  const bool h2_serves = a.pieces && (d >= 512 || n <= h2_most) && h2_codebook_serves(p->bits_mse, a.cb) && (!prod || aligned16(p->SPiT));
+  // 87 against 147 us / 30 against 24; d = 384 169 against 197 / 40 against 32; d = 512 284 against 223).  It also meets all 24 bits of Pi,
+  // so it stays where, without a sketch and at 3 and 4 bits, the fp16 contraction would take less time (d = 256, 4 bits, 300000 vectors 277 / 242).
+  const bool h2_serves = a.pieces && (d >= 512 || n <= 16384) && h2_codebook_serves(p->bits_mse, a.cb) && (!prod || aligned16(p->SPiT));
   const NKind nk = dtype == TQ_F32 ? N_F32 : N_BF16;
 
   if (!prod) {

@@ -85,6 +85,31 @@ def test_few_vectors_no_further_off_than_the_fp32_instructions(kind, bits, prod,
     assert np.all(pieces[2:] <= 1.02 * fp32[2:]), (pieces, fp32)
 
 
+# ------------------------------------------------------------------ quantisation below d = 512
+
+
+@pytest.mark.parametrize("d,bits,n,bf16", [(64, 3, 16385, True), (64, 4, 20001, False), (256, 4, 17003, True), (192, 3, 16400, False), (384, 4, 16385, False),
+                                           (384, 3, 40001, True), (256, 2, 16385, False), (256, 4, 200, False), (96, 3, 5, True)])
+def test_every_bit_of_pi(d, bits, n, bf16):
+    """More than 16384 vectors below d = 512 (and a few at any d) meet all 24 bits of an entry of Pi: of a unit vector that is one entry, here
+    on a cell's boundary or the next number below it.  One product and zeros: every sum is exact."""
+    rng = np.random.default_rng(d + bits)
+    half = np.sort(rng.uniform(0.02, 0.3, 1 << bits - 1).astype(np.float32))
+    bounds = np.concatenate([-half[1:][::-1], np.zeros(1, np.float32), half[1:]])
+    c = np.concatenate([-half[::-1], half])
+    at = rng.choice(bounds[bounds != 0], size=(d, d))
+    Pi = np.where(rng.random((d, d)) < 0.5, at, np.nextafter(at, np.float32(-1))).astype(np.float32)
+    p = tq.Params(d, bits, torch.from_numpy(Pi), None, c, bounds)
+    k = np.arange(n) % d
+    x = torch.zeros((n, d), device=T.DEV, dtype=torch.bfloat16 if bf16 else torch.float32)
+    x[torch.arange(n), torch.from_numpy(k)] = 1
+    idx = torch.zeros((n, p.idx_words), dtype=torch.int32, device=T.DEV)
+    p.reserve(n)
+    tq.tq_quantize_mse(p, x, idx, None)
+    want = torch.from_numpy(np.searchsorted(bounds, Pi, side="right")).to(T.DEV).T[torch.from_numpy(k).to(T.DEV)]
+    assert int((unpack(idx, bits, d) != want).sum()) == 0
+
+
 # ------------------------------------------------------------------ dequantisation of sums of signs
 
 

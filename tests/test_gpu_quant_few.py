@@ -70,7 +70,7 @@ def test_workspace_is_left_alone_at_128(bits, n, bf16):
         assert all(torch.equal(a, b) for a, b in zip(want, again))
 
 
-# three bits and more without a sketch: the contraction on fp16 pieces beyond 16384 vectors too
+# short vectors beyond 16384: the contraction that splits them on the fly
 @pytest.mark.parametrize("d,bits,n,kind", [(64, 3, 16385, "bf16"), (64, 3, 32769, "f32"), (64, 4, 20001, "f32"), (192, 3, 16400, "unit"), (256, 4, 17003, "bf16"), (384, 4, 16385, "f32"),
                                            (256, 2, 16385, "f32")])
 def test_many_short_vectors(d, bits, n, kind):
