@@ -167,9 +167,17 @@ char* sign_gemm_image(const void* images, int d, int which) {
 size_t h2_own_images_bytes(int d, bool prod) { return kH2ImageHeader + (prod ? 2 : 1) * h2_image_bytes(d, d); }
 
 constexpr int64_t kMatvecQueries = 64;  // up to here queries of any length are rotated by matrix-vector products
-// So are short ones up to 65536 values, and at d = 128, where the alternative is gemm_kernel, 1024.  (A search of 20000 codes, us, the alternative / this: d = 128, 70 queries
-// 54.6 / 43.8, 1000 90.3 / 83.6, with a sketch 115 / 99; 256 70 53.0 / 49.8, 200 57.5 / 55.9, 400 68 / 68; 384 200 63.7 / 62.8; 768 70 75.4 / 72.0, 150 81 / 80; 3072 70 151 / 175.)
-bool rotated_by_products(int64_t nq, int d) { return nq <= kMatvecQueries || (d <= 128 ? nq <= 1024 : nq * d <= 65536); }
+// So are short ones up to 65536 values, and at d = 128, where the alternative is gemm_kernel, 1024; with TQ_FLAG_FP32_MFMA these stay on the
+// fp32 matrix instructions.  A search of 20000 codes, us, the alternative / this:
+//   d = 128   70 queries 54.6 / 43.8, 1000 90.3 / 83.6 (with a sketch 115 / 99)
+//   d = 256   70 53.0 / 49.8, 200 57.5 / 55.9, 400 68 / 68
+//   d = 384   200 63.7 / 62.8
+//   d = 768   70 75.4 / 72.0, 150 81 / 80
+//   d = 3072  70 151 / 175
+bool rotated_by_products(const tq_params* p, int64_t nq) {
+  if (nq <= kMatvecQueries) return true;
+  return !fp32_mfma_only(p) && (p->d <= 128 ? nq <= 1024 : nq * p->d <= 65536);
+}
 
 // Pi q and S q of many queries on the fp16 matrix cores, from the images of Pi and S or from ones made here.  (The error of
 // a rotated coordinate is 0.62 of the fp32 instructions' at every d from 256 to 4096, 4.4e-7 against 7.0e-7 of its size at
@@ -904,7 +912,7 @@ tq_status score_impl(const tq_params* p, Workspace ws, const float* q, int64_t l
       return TQ_ERR_HIP;
   } else {
     // queries into the rotated basis and the sketch basis: Pi q and S q
-    const bool products = rotated_by_products(nq, d);
+    const bool products = rotated_by_products(p, nq);
     void* const rot = pl.rotate_bytes > 0 && !products ? ws.take(pl.rotate_bytes) : nullptr;
     if (rot != nullptr) {
       if (!rotate_h2(p, q, ldq, nq, qr, qs, rot, s)) return TQ_ERR_HIP;

@@ -54,6 +54,19 @@ def test_a_wavefront_per_row(d, bits, nq):
     P.check_close(run(p, q, codes, n).cpu().numpy(), want, scale, "score")
 
 
+@pytest.mark.parametrize("d,bits,few,many", [(128, 1, 70, 1100), (256, 2, 65, 300)])
+def test_the_fp32_instructions_for_any_number_above_64(d, bits, few, many):
+    """TQ_FLAG_FP32_MFMA: a query's scores do not depend on how many come with it."""
+    p, q, codes, n, want, scale = problem(d, bits, many, d)
+    try:
+        p.fp32_mfma = True
+        whole = run(p, q, codes, n)
+        assert torch.equal(run(p, q[:few], codes, n), whole[:few])
+    finally:
+        p.fp32_mfma = False
+    P.check_close(whole.cpu().numpy(), want, scale, "score")
+
+
 @pytest.mark.parametrize("d,bits,nq", [(256, 1, 65), (1024, 0, 130)])
 def test_images_change_no_bit(d, bits, nq):
     """The matrices' pieces from the images, or made in a workspace of the size that is asked for without them."""
