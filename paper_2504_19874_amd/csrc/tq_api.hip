@@ -570,7 +570,7 @@ size_t tq_workspace_bytes(const tq_params* p, int64_t n, int64_t nq, int32_t top
   if (topk > 0) bytes += 2 * round_up((size_t)(nq < 128 ? nq : 128) * 4096 * sizeof(float), 256);
   // candidates of a search by many queries, and their rotation
   if (topk > 0 && nq > 0 && n > 0) bytes += search_workspace_bytes(p->d, n, nq, topk) + 256;
-  if (nq > kMatvecQueries && p->d != 128) bytes += RotateSpace(p, nq, p->S != nullptr).total + 256;
+  if (!rotated_by_products(p, nq) && p->d != 128) bytes += RotateSpace(p, nq, p->S != nullptr).total + 256;
   return bytes + 256;
 }
 
@@ -795,7 +795,7 @@ ScorePlan plan_score(const tq_params* p, bool prod, int n_groups, int q_per_grou
   if (pl.route == ScorePlan::R_BF3 && topk > 0 && !scores_given && n_groups == 1 &&
       search_applicable(p->bits_mse, prod, p->d, n_per_group, q_per_group, topk, make_codebook(p)))
     pl.search_bytes = search_workspace_bytes(p->d, n_per_group, nq, topk);
-  if (pl.q_bytes > 0 && nq > kMatvecQueries && p->d != 128 && !fp32_mfma_only(p)) pl.rotate_bytes = RotateSpace(p, nq, prod).total;
+  if (pl.q_bytes > 0 && !rotated_by_products(p, nq) && p->d != 128 && !fp32_mfma_only(p)) pl.rotate_bytes = RotateSpace(p, nq, prod).total;
   return pl;
 }
 
@@ -912,11 +912,10 @@ tq_status score_impl(const tq_params* p, Workspace ws, const float* q, int64_t l
       return TQ_ERR_HIP;
   } else {
     // queries into the rotated basis and the sketch basis: Pi q and S q
-    const bool products = rotated_by_products(p, nq);
-    void* const rot = pl.rotate_bytes > 0 && !products ? ws.take(pl.rotate_bytes) : nullptr;
+    void* const rot = pl.rotate_bytes > 0 ? ws.take(pl.rotate_bytes) : nullptr;
     if (rot != nullptr) {
       if (!rotate_h2(p, q, ldq, nq, qr, qs, rot, s)) return TQ_ERR_HIP;
-    } else if (products && d <= 4096) {
+    } else if (rotated_by_products(p, nq) && d <= 4096) {
       if (launch_matvec_rows(d, nq, p->Pi, prod ? p->S : nullptr, q, ldq, qr, qs, d, false, s) != hipSuccess)
         return TQ_ERR_HIP;
     } else {

@@ -17,3 +17,19 @@ def test_few_vectors(d, n, prod):
     got = _lib.load().tq_workspace_bytes(C.byref(p), n, 0, 0)
     need = n * (8 * d + 8 + (d + 63) // 64 * 4)
     assert need <= got <= need + 8192
+
+
+@pytest.mark.parametrize("d,most,prod", [(64, 1024, True), (256, 256, False), (384, 170, True), (768, 85, False), (1536, 64, True), (4096, 64, False)])
+def test_no_room_to_split_queries_that_matrix_vector_products_rotate(d, most, prod):
+    """Up to 64 queries, and short ones up to 65536 values, need their rotation's result alone; from the next on pieces and two images, too."""
+    c, t = (C.c_float * 4)(-1, -0.5, 0.5, 1), (C.c_float * 3)(-0.75, 0, 0.75)
+    p = _lib.TqParams()
+    p.d, p.bits_mse, p.S = d, 2, 256 if prod else 0
+    p.centroids, p.bounds = C.addressof(c), C.addressof(t)
+    lib = _lib.load()
+    result = lambda nq: nq * d * 4 * (2 if prod else 1)  # noqa: E731
+    call = lambda nq: lib.tq_score_workspace_bytes(C.byref(p), 1, nq, 1 << 20, int(prod), 1, 0)  # noqa: E731
+    assert call(most) <= result(most) + 2048
+    assert call(most + 1) >= result(most + 1) + (most + 1) * d * 4 + (2 if prod else 1) * 4 * d * d
+    bound = lambda nq: lib.tq_workspace_bytes(C.byref(p), 0, nq, 0)  # noqa: E731
+    assert bound(most + 1) - bound(most) >= (most + 1) * d * 4 + (2 if prod else 1) * 4 * d * d
