@@ -770,13 +770,14 @@ struct ScorePlan {
   bool prod;
   size_t search_bytes;  // top-k of many queries by candidates (tq_search.hip); without room for it every score is looked at
   size_t rotate_bytes;  // many queries rotated on the fp16 matrix cores; without room for it on the fp32 ones
-  size_t total() const { return needed() + round_up(search_bytes, 256) + round_up(rotate_bytes, 256); }
+  size_t total() const { return needed() + (ranges > 0 ? 0 : lists()) + round_up(search_bytes, 256) + round_up(rotate_bytes, 256); }
+  // what the call cannot do without: the lists of a top-k over a score matrix are left out where there is no room (one workgroup per row then)
   size_t needed() const {
     const size_t a = 256;
-    size_t t = round_up(img_bytes, a) + (q_bytes ? round_up(q_bytes, a) * (prod ? 2 : 1) : 0) + round_up(scores_bytes, a) +
-               2 * round_up(part_bytes, a);
+    size_t t = round_up(img_bytes, a) + (q_bytes ? round_up(q_bytes, a) * (prod ? 2 : 1) : 0) + round_up(scores_bytes, a) + (ranges > 0 ? lists() : 0);
     return t + a;
   }
+  size_t lists() const { return 2 * round_up(part_bytes, 256); }
 };
 
 ScorePlan plan_route(const tq_params* p, bool prod, int n_groups, int q_per_group, int64_t n_per_group, bool scores_given,
@@ -881,7 +882,7 @@ tq_status score_impl(const tq_params* p, Workspace ws, const float* q, int64_t l
   const ScorePlan pl = plan_score(p, prod, n_groups, q_per_group, n_per_group, scores != nullptr, topk,
                                   aligned16(idx) && (!prod || aligned16(qjl)));
 
-  // all scratch memory is taken before the first launch
+  // the scratch memory that the call cannot do without is taken before the first launch
   void* img = pl.img_bytes ? ws.take(pl.img_bytes) : nullptr;
   float* qr = pl.q_bytes ? static_cast<float*>(ws.take(pl.q_bytes)) : nullptr;
   float* qs = pl.q_bytes && prod ? static_cast<float*>(ws.take(pl.q_bytes)) : nullptr;
@@ -891,13 +892,15 @@ tq_status score_impl(const tq_params* p, Workspace ws, const float* q, int64_t l
     scores = static_cast<float*>(ws.take(pl.scores_bytes));
     if (scores == nullptr) return TQ_ERR_WORKSPACE;
   }
-  float* part_val = pl.part_bytes ? static_cast<float*>(ws.take(pl.part_bytes)) : nullptr;
-  int32_t* part_idx = pl.part_bytes ? static_cast<int32_t*>(ws.take(pl.part_bytes)) : nullptr;
-  // the chunks of a top-k over a score matrix are an optimisation: without room for their lists, one workgroup per row
-  const int topk_chunks = (part_val != nullptr && part_idx != nullptr) ? pl.topk_chunks : 0;
-  if ((pl.img_bytes && img == nullptr) || (pl.q_bytes && (qr == nullptr || (prod && qs == nullptr))) ||
-      (pl.ranges > 0 && (part_val == nullptr || part_idx == nullptr)))
-    return TQ_ERR_WORKSPACE;
+  auto take_lists = [&](float*& val, int32_t*& idx_of) {
+    val = pl.part_bytes ? static_cast<float*>(ws.take(pl.part_bytes)) : nullptr;
+    idx_of = pl.part_bytes ? static_cast<int32_t*>(ws.take(pl.part_bytes)) : nullptr;
+    return val != nullptr && idx_of != nullptr;
+  };
+  float* part_val = nullptr;
+  int32_t* part_idx = nullptr;
+  if (pl.ranges > 0 && !take_lists(part_val, part_idx)) return TQ_ERR_WORKSPACE;
+  if ((pl.img_bytes && img == nullptr) || (pl.q_bytes && (qr == nullptr || (prod && qs == nullptr)))) return TQ_ERR_WORKSPACE;
 
   if (pl.route == ScorePlan::R_SPLIT_I8) {
     if (launch_score_i8_split(p->bits_mse, prod, p->Pi, p->S, p->PiT, p->ST, q, ldq, img, idx, qjl, gamma, norm, scores, ld_scores,
@@ -985,10 +988,11 @@ tq_status score_impl(const tq_params* p, Workspace ws, const float* q, int64_t l
       if (launch_gemm(N_CODE, E_STORE_N, p->bits_mse, a, n_groups, s) != hipSuccess) return TQ_ERR_HIP;
     }
   }
-  if (topk > 0 && topk_chunks > 0) {
-    if (launch_topk(scores, nq, n_per_group, ld_scores, topk, nullptr, nullptr, s, topk_chunks, part_val, part_idx) != hipSuccess)
+  // the chunks of a top-k over a score matrix are an optimisation: without room for their lists behind everything else, one workgroup per row
+  if (topk > 0 && pl.topk_chunks > 0 && take_lists(part_val, part_idx)) {
+    if (launch_topk(scores, nq, n_per_group, ld_scores, topk, nullptr, nullptr, s, pl.topk_chunks, part_val, part_idx) != hipSuccess)
       return TQ_ERR_HIP;
-    return from_hip(launch_topk_merge(part_val, part_idx, nq, topk_chunks, topk, topk_idx, topk_val, s));
+    return from_hip(launch_topk_merge(part_val, part_idx, nq, pl.topk_chunks, topk, topk_idx, topk_val, s));
   }
   if (topk > 0) return from_hip(launch_topk(scores, nq, n_per_group, ld_scores, topk, topk_idx, topk_val, s));
   return TQ_OK;

@@ -109,3 +109,26 @@ def test_static_scratch_rejects_what_does_not_fit():
     torch.cuda.synchronize()
     assert torch.equal(ti.cpu(), torch.arange(4, dtype=torch.int32).repeat(64, 1))  # zero queries: all scores 0, ties by index
     assert lib.tq_status_string(4) == b"TQ_ERR_WORKSPACE"
+
+
+@pytest.mark.parametrize("topk,n", [(64, 41500), (64, 40900)])
+def test_static_scratch_without_room_for_lists_of_chunks(topk, n):
+    """A score matrix that fits, the lists of its chunks do not: one workgroup per row, the same pairs."""
+    from paper_2504_19874_amd import _lib
+    lib = _lib.load()
+    groups, qpg = 25, 4
+    rng = np.random.default_rng(n)
+    c32, t32, _ = o.codebook_fp32(128, 2)
+    p = tq.Params(128, 2, torch.from_numpy(o.rotation_from_gaussian(W.gaussian_matrix(128, 100))), None, c32, t32)
+    t = dict(idx=torch.from_numpy(rng.integers(-2**31, 2**31 - 1, size=(groups * n, 8), dtype=np.int64).astype(np.int32)).cuda(), qjl=None, gamma=None, norm=None)
+    q = torch.from_numpy(W.gaussian_queries(groups * qpg, 128, 11, unit=False)).cuda()
+    out = [(torch.full((groups * qpg, topk), -7, dtype=torch.int32, device="cuda"), torch.zeros((groups * qpg, topk), device="cuda")) for _ in range(2)]
+    p.reserve_score(groups, qpg, n, False, False, topk)
+    lists = 2 * groups * qpg * topk * 4 * -(-n // 8192)  # a chunk is 8192 scores here
+    whole = int(p.c.workspace_bytes)
+    assert (whole > 16 << 20) == (n == 41500) and whole - lists < 16 << 20
+    assert _raw_call(lib.tq_score, p, q, groups, qpg, t, n, None, topk, *out[0]) == 0
+    p.c.workspace, p.c.workspace_bytes = 0, 0
+    assert _raw_call(lib.tq_score_static, p, q, groups, qpg, t, n, None, topk, *out[1]) == 0
+    torch.cuda.synchronize()
+    assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])
