@@ -262,15 +262,24 @@ static hipError_t dequant_rows_bits(bool prod, int d, int n, const uint32_t* idx
                                     float* out, int64_t ldo, hipStream_t s) {
   auto go = [&](auto prod_c, auto q_c, auto r_c) {
     constexpr bool PROD = decltype(prod_c)::value;
-    constexpr int Q = decltype(q_c)::value, R = decltype(r_c)::value;
-    hipLaunchKernelGGL((dequant_rows_kernel<BITS, PROD, Q, R>), dim3((d + 4 * R - 1) / (4 * R), (n + Q - 1) / Q), dim3(256),
-                       (size_t)(PROD ? 2 : 1) * Q * d * sizeof(float), s, d, n, idx, qjl, gamma, norm, PiT, ST, cb, kappa, out, ldo);
+    constexpr int Q = decltype(q_c)::value, R = decltype(r_c)::value, MOST = 64 * 1024;
+    const int lds = (PROD ? 2 : 1) * Q * d * (int)sizeof(float);
+    if (lds > MOST) return hipErrorInvalidValue;
+    if (lds == MOST) {  // d = 2048: above the default limit with the table
+      static LdsLimit limit;
+      if (const hipError_t e = raise_lds_limit(limit, reinterpret_cast<const void*>(&dequant_rows_kernel<BITS, PROD, Q, R>), MOST); e != hipSuccess) return e;
+    }
+    hipLaunchKernelGGL((dequant_rows_kernel<BITS, PROD, Q, R>), dim3((d + 4 * R - 1) / (4 * R), (n + Q - 1) / Q), dim3(256), lds, s, d, n, idx, qjl, gamma,
+                       norm, PiT, ST, cb, kappa, out, ldo);
     return hipGetLastError();
   };
   using std::integral_constant;
-  // One row per wavefront up to `once` workgroups per compute unit, two up to `twice`, else four (the decoding is shared by all of a workgroup's; us with
-  // 1 / 2 / 4, 4 bits: 8 codes of 1024 5.0 / 5.5 / 6.4, 16 6.4 / 5.6 / 6.5, 32 9.9 / 7.2 / 6.8; 2 + 1 bits of 768: 4 4.0 / 4.5 / 5.6, 16 5.3 / 5.1 / 5.8; 32 of 1536,
-  // 3 + 1 bits, 27 / 17 / 13).  Eight codes per workgroup, four with a sketch, while 64 KB hold them (3072: 32 codes of 4 bits 31 us, with 96 KB 48).
+  // One row per wavefront up to `once` workgroups per compute unit, two up to `twice`, else four (the decoding is shared by all of a
+  // workgroup's); us with 1 / 2 / 4:
+  //   4 bits, d = 1024      8 codes 5.0 / 5.5 / 6.4, 16 6.4 / 5.6 / 6.5, 32 9.9 / 7.2 / 6.8
+  //   2 + 1 bits, d = 768   4 4.0 / 4.5 / 5.6, 16 5.3 / 5.1 / 5.8
+  //   3 + 1 bits, d = 1536  32 27 / 17 / 13
+  // Eight codes per workgroup, four with a sketch, while 64 KB beside the table hold them (d = 3072, 32 codes of 4 bits: 31 us, with 96 KB 48).
   const int64_t cus = device_cu_count();
   auto rows = [&](auto prod_c, auto q_c, int64_t once, int64_t twice) {
     const int64_t all = (int64_t)(d / 4) * ((n + decltype(q_c)::value - 1) / decltype(q_c)::value);
@@ -290,7 +299,7 @@ hipError_t launch_dequant_rows(int bits, bool prod, int d, int64_t n, const uint
                                const float* gamma, const float* norm, const float* PiT, const float* ST, const Codebook& cb,
                                float kappa, float* out, int64_t ldo, hipStream_t s) {
   if (n == 0) return hipSuccess;
-  if (n > 65535 || d % 32 != 0 || (size_t)4 * d * sizeof(float) > 65536) return hipErrorInvalidValue;
+  if (n > 65535 || d % 32 != 0 || d > 4096) return hipErrorInvalidValue;
   switch (bits) {
     case 0: return dequant_rows_bits<0>(prod, d, (int)n, idx, qjl, gamma, norm, PiT, ST, cb, kappa, out, ldo, s);
     case 1: return dequant_rows_bits<1>(prod, d, (int)n, idx, qjl, gamma, norm, PiT, ST, cb, kappa, out, ldo, s);

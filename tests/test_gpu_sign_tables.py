@@ -109,7 +109,8 @@ def test_few_long_codes(d, bits, prod, n):
 # blocks of two, four and eight codes; the ends of the range and one beyond
 @pytest.mark.parametrize("d,bits,prod,n", [(32, 3, False, 1), (32, 4, True, 3), (64, 3, True, 9), (96, 4, False, 13), (128, 4, False, 512), (128, 3, True, 513), (160, 3, True, 31),
                                            (288, 4, False, 250), (544, 3, True, 66), (1056, 3, False, 61), (1056, 4, True, 186), (2080, 3, True, 5), (2080, 4, False, 47),
-                                           (2080, 4, False, 48), (64, 0, True, 100), (96, 2, True, 200), (1536, 2, True, 9)])
+                                           (2080, 4, False, 48), (2048, 3, False, 5), (2048, 4, False, 90), (2048, 4, True, 5), (2048, 3, True, 90), (2016, 4, False, 33), (2016, 3, True, 33),
+                                           (64, 0, True, 100), (96, 2, True, 200), (1536, 2, True, 9)])
 def test_few_codes_of_any_table(d, bits, prod, n):
     p, codes, parts, norm = make(bits, prod, n, d)
     wide = torch.full((n + 1, d + 4), 7.0, device=T.DEV)
