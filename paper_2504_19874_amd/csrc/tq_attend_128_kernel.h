@@ -285,6 +285,7 @@ __global__ __launch_bounds__(512) void attend128_kernel(const ScoreI8Args ka, co
   int enu = 0, eng = 0;
   if (numax > 0.f) (void)frexpf(numax, &enu);  // numax = f * 2^enu, f in [0.5, 1)
   if (ngmax > 0.f) (void)frexpf(ngmax, &eng);
+  enu = max(enu, -99), eng = max(eng, -99);  // below, the scale would not be finite: fewer than 28 bits of a weight there
   // |weights exp(logit - m) * nu * wscale| <= 2^28
 #pragma unroll
   for (int e = 0; e < NE; ++e) nuv[e] *= ldexpf(1.f, 28 - enu), ngv[e] *= ldexpf(1.f, 28 - eng);

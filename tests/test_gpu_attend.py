@@ -139,6 +139,28 @@ def test_attend_with_a_table_that_is_not_centred_and_norms_of_either_sign(table)
                  o.attend(q, kt, np.eye(npg), scale), d, 1, 4, npg)
 
 
+@pytest.mark.parametrize("vb,vprod", [(2, False), (4, False), (2, True)])
+@pytest.mark.parametrize("power", [-98, -99, -100, -101, -102, -106, 90])
+def test_attend_with_norms_far_from_one(vb, vprod, power):
+    """Value norms of about 2^power: the weights' common scale stays finite, and the result is that of norms about one times 2^power."""
+    d, npg = 128, 900
+    pk = setup(d, 2, True, 100, 200)[0]
+    pv = setup(d, vb, vprod, 300, 400)[0]
+    rng = np.random.default_rng(7)
+    _, k_dev = random_codes(rng, npg, d, 2, True, 0.3)
+    (_, _, _, norm), v_dev = random_codes(rng, npg, d, vb, vprod, 0.1)
+    norm = (norm / norm.max()).astype(np.float32)  # the largest: 1
+    q = dev(W.gaussian_queries(4, d, 3, unit=False))
+    out = []
+    for e in (0, power):
+        v = (v_dev[0], v_dev[1], v_dev[2], dev(np.ldexp(norm, e)))
+        out.append(torch.full((4, d), float("nan"), dtype=torch.float32, device=DEV))
+        tq.tq_attend(pk, pv, q, 1, 4, k_dev, v, npg, 1.0 / math.sqrt(d), out[-1])
+    want, got = out[0].double(), out[1].double() * 2.0**-power
+    # at the least 21 bits of a weight are left of 28, of a sum of a few hundred
+    assert float(((got - want).norm(dim=1) / want.norm(dim=1)).max()) < 2.0**-17
+
+
 def run_attend(d, kb, kprod, vb, vprod, n_groups, qpg, npg, key_transposes):
     pk, Pik, Sk, ck = setup(d, kb, kprod, 100, 200)
     pv, Piv, Sv, cv = setup(d, vb, vprod, 300, 400)
