@@ -515,10 +515,17 @@ hipError_t launch_any(const H2Args& a, const Codebook& cb, hipStream_t s) {
       if constexpr (EK == 0) return launch_tile<EK, BITS, NPX, 2, 1, 2, 4, 4>(a, cb, s);
       else return launch_tile<EK, BITS, NPX, 2, 2, 2, 2, 4>(a, cb, s);
     default:
-      // 32 vectors instead of 64 while that leaves compute units without a workgroup (a tile's bytes come through one of them), of long vectors while it leaves two
-      // fifths of them (us, 64 / 32: 512, 4 bits, 500 vectors 10.0 / 9.8; 768, 2 + 1 bits, 300 20.6 / 19.5; 1536, 2 + 1 bits, 130 32.1 / 29.7, 200 (168 workgroups)
-      // 32.5 / 33.6; 3072, 2 bits, 70 24.5 / 23.2, 100 (192) 24.6 / 27.6)
-      if ((int64_t)((a.d + 63) / 64) * ((a.n + 31) / 32) * 5 <= (int64_t)device_cu_count() * (a.d <= 1024 ? 5 : 3)) return launch_tile<EK, BITS, NPX, 1, 1, 2, 1, 4>(a, cb, s);
+      // 32 vectors instead of 64 while that leaves compute units without a workgroup (a tile's bytes come through one of them), of long vectors
+      // while it leaves two fifths of them and only where tiles of 64 would hold more empty places, or, beyond d = 2048, are of two pieces and all but full.  us, 64 / 32:
+      //   d = 512, 4 bits     500 10.0 / 9.8
+      //   d = 768, 2 + 1      300 20.6 / 19.5
+      //   d = 1536, 2 + 1     130 32.1 / 29.7, 200 (168 workgroups) 32.5 / 33.6; bf16 57 26.8 / 29.4, 64 27.5 / 29.8; 2 bits, bf16 97 13.3 / 14.0
+      //   d = 2048, 1 + 1     40 33.5 / 35.7, bf16 64 34.7 / 36.6
+      //   d = 3072, 2 bits    64 24.3 / 21.7, 70 24.5 / 23.2, 100 (192 workgroups) 24.6 / 27.6; 1 + 1 36 46.4 / 50.9, 40 46.8 / 51.0, 64 52.4 / 49.2
+      //   d = 4096, 1 + 1     bf16 33 57.6 / 66.8
+      if (const int last = (int)((a.n - 1) % 64); a.d <= 1024 || last < 32 || (NPX == 2 && a.d > 2048 && last >= 56))
+        if ((int64_t)((a.d + 63) / 64) * ((a.n + 31) / 32) * 5 <= (int64_t)device_cu_count() * (a.d <= 1024 ? 5 : 3))
+          return launch_tile<EK, BITS, NPX, 1, 1, 2, 1, 4>(a, cb, s);
       return launch_tile<EK, BITS, NPX, 1, 1, 2, 2, 4>(a, cb, s);
   }
 }

@@ -28,8 +28,9 @@ def test_short_vectors(d, bits, n, kind):
     T.test_quantize_mse(d, bits, n, kind)
 
 
-# tiles of 32 vectors: one and several, the last in part, the ends of the range (256 compute units)
-@pytest.mark.parametrize("d,bits,n,kind", [(512, 2, 65, "f32"), (512, 4, 1024, "bf16"), (512, 1, 1025, "unit"), (1088, 3, 288, "bf16unit"), (1088, 2, 257, "f32"), (2560, 1, 97, "bf16")])
+# tiles of 32 vectors: one and several, the last in part, the ends of the range (256 compute units); of long vectors one tile of 64 or two of 32
+@pytest.mark.parametrize("d,bits,n,kind", [(512, 2, 65, "f32"), (512, 4, 1024, "bf16"), (512, 1, 1025, "unit"), (1088, 3, 288, "bf16unit"), (1088, 2, 257, "f32"), (2560, 1, 97, "bf16"),
+                                           (2080, 2, 96, "f32"), (2080, 1, 56, "bf16"), (2080, 3, 57, "unit"), (2080, 2, 57, "bf16unit"), (2560, 1, 33, "f32")])
 def test_tiles_of_32(d, bits, n, kind):
     T.test_quantize_prod(d, bits, n, kind)
     T.test_quantize_mse(d, bits, n, kind)
