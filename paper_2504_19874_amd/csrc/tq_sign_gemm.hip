@@ -262,12 +262,16 @@ hipError_t launch_tile(SignGemmArgs a, hipStream_t s) {
   return hipGetLastError();
 }
 
-// Up to one workgroup of sign_few_kernel per compute unit, two where there is more than one stream of products; us, sign_gemm_kernel / here: 2 + 1 bits d = 256
-// 1 code 10.0 / 3.8, 2000 11.0 / 6.0; 768 64 22.8 / 8.0, 1000 24.0 / 15.7, 1500 (2.25 workgroups) 24.4 / 22.8; 1536 200 41.8 / 12.6; 3072, 1 + 1 bits, 64
-// 52.2 / 24.3, 400 (2.6) 52.9 / 58.9; one stream d = 512 1000 8.1 / 5.6, 1500 (1.5) 8.3 / 9.5.  Two bits without a sketch, against tq_code_gemm.hip: 1536
-// 200 29.4 / 8.8, 1000 (3) 31.8 / 23.9, 1500 (4.5) 35.0 / 38.5.
+// Up to one workgroup of sign_few_kernel per compute unit, two where there is more than one stream of products, which is not enough for one bit with a
+// sketch while the contraction is a step per wavefront or less.  us, sign_gemm_kernel / here:
+//   2 + 1 bits           d = 256 1 code 10.0 / 3.8, 2000 11.0 / 6.0; 768 64 22.8 / 8.0, 1000 24.0 / 15.7, 1500 (2.25 workgroups) 24.4 / 22.8; 1536 200 41.8 / 12.6
+//   1 + 1 bits           256 2048 (1 workgroup) 8.4 / 5.7, 2900 (1.4) 8.6 / 9.5, 4096 (2) 8.7 / 9.9; 512 1300 (1.3) 12.5 / 12.4, 2000 (2) 12.4 / 12.8; 768 1300 (2)
+//                        16.5 / 14.8; 3072 64 52.2 / 24.3, 400 (2.6) 52.9 / 58.9
+//   one stream           512 1000 8.1 / 5.6, 1500 (1.5) 8.3 / 9.5
+//   2 bits (tq_code_gemm.hip / here)  256 4096 (2) 8.8 / 7.8; 1536 200 29.4 / 8.8, 1000 (3) 31.8 / 23.9, 1500 (4.5) 35.0 / 38.5
 bool few_serves(int bits, bool prod, int d, int64_t n) {
-  return (d / 32) * ((n + 63) / 64) <= (int64_t)(bits + (prod ? 1 : 0) > 1 ? 2 : 1) * device_cu_count();
+  const int streams = bits + (prod ? 1 : 0), most = streams > 2 || streams == 2 && (!prod || d > 512) ? 2 : 1;
+  return (d / 32) * ((n + 63) / 64) <= (int64_t)most * device_cu_count();
 }
 
 template <int BITS, bool PROD>
