@@ -36,16 +36,27 @@ constexpr int64_t kChunkRows = 65536;  // rows per pass of the quantiser at most
 // Row strides of vectors (x, q) and of dequantised output: the kernels address a tile's rows with 32-bit byte
 // offsets from a 64-bit tile base (up to 256 rows of ld * 4 bytes)
 constexpr int64_t kMaxRowStride = int64_t(1) << 22;
-// Up to here vectors take the matrix-vector route of the quantiser.  It reads every matrix once per block of four vectors, plain fp32 multiply-adds; the
-// contraction on the matrix cores once per tile, and reads 17 bits of an fp32 vector.  The line between them, blocks x d^2, lies at 4e7 elements, at 64 vectors, and for short
-// ones at 65536 values (half with a sketch), about where the two take the same time: up to there vectors keep all their bits (mean error of a rotated coordinate
-// 0.8 - 1.2e-7 sigma; 2.0e-6 on the contraction, 2.4e-7 for bf16 vectors).  Measured, this route / the contraction, in us:
-//   Alg. 1  d = 64: 1 vector 3.3 / 6.4, 256 4.7 / 7.5; 256: 1 3.4 / 7.8, 256 7.8 / 8.9, 512 12.2 / 8.8; 512: 128 8.3 / 10.1, 192 10.7 / 10.1; 768: 64 8.5 / 11.6 (96); 1536: 64
-//           17.0 / 16.2; 3072: 16 15.7 / 22.0 (32), 32 26.7 / 22.0
-//   Alg. 2  d = 256: 1 6.1 / 11.3, 128 10.7 / 12.8, 192 12.7 / 12.5; 512: 64 11.4 / 16.0 (96); 1536: 32 19.5 / 29.9 (48), 64 30.7 / 30.8; 3072: 16 29.9 / 45.2, 32 51.3 / 49.6
+// Up to here vectors take the matrix-vector route of the quantiser.  It reads every matrix once per block of four vectors, plain fp32
+// multiply-adds; the contraction on the matrix cores once per tile, and reads 17 bits of an fp32 vector.  The line between them, blocks x d^2, lies
+// at 4e7 elements, at 64 vectors (with a sketch 52 of 1536), and for short ones at 65536 values (half with a sketch), about where the two take
+// the same time: up to there vectors keep all their bits (mean error of a rotated coordinate 0.8 - 1.2e-7 sigma; 2.0e-6 on the
+// contraction, 2.4e-7 for bf16 vectors).  us, this route / the contraction:
+//   Alg. 1  d = 64    1 vector 3.3 / 6.4, 256 4.7 / 7.5
+//           d = 256   1 3.4 / 7.8, 256 7.8 / 8.9, 512 12.2 / 8.8
+//           d = 512   128 8.3 / 10.1, 192 10.7 / 10.1
+//           d = 768   64 8.5 / 11.6 (96)
+//           d = 1536  64 15.6 / 15.8
+//           d = 3072  16 15.7 / 22.0 (32), 32 26.7 / 22.0
+//   Alg. 2  d = 256   1 6.1 / 11.3, 128 10.7 / 12.8, 192 12.7 / 12.5
+//           d = 512   64 11.4 / 16.0 (96)
+//           d = 1536  32 19.5 / 29.9 (48), 52 24.5 / 28.1, 56 28.2 / 28.0, 64 29.4 / 28.9; bf16 52 24.7 / 27.6, 56 29.4 / 27.0, 64 30.2 / 27.3
+//           d = 2048  36 31.1 / 33.6
+//           d = 3072  16 29.9 / 45.2, 32 51.3 / 49.6
 bool quant_rows_serves(int64_t n, int d, bool prod) {
-  return d <= 4096 && n <= 256 && (n <= 64 || n * d <= (prod ? 32768 : 65536)) && ((n + 3) / 4) * (int64_t)d * d <= 150 * 512 * 512;
+  if (d > 4096 || n > 256 || ((n + 3) / 4) * (int64_t)d * d > 150 * 512 * 512) return false;
+  return prod ? (n <= 64 && n * d <= 52 * 1536) || n * d <= 32768 : n <= 64 || n * d <= 65536;
 }
+
 // of a table that is a sum of signs, the dequantiser's (see there)
 bool rows_before_digits(int64_t n, int d, bool prod) {
   return n <= (prod ? 32 : 64) && d >= 512 && d < 4096 && (((prod ? 2 : 1) * n + 3) / 4) * (int64_t)d * d * (prod ? 2 : 1) <= 300 * 512 * 512;

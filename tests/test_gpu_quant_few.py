@@ -22,7 +22,8 @@ def test_blocks_and_shares(bits, n, kind):
 # matrix-vector products of short vectors: fewer values than lanes, not a multiple of them, blocks of four in part; the ends of the range with and without a
 # sketch, one beyond
 @pytest.mark.parametrize("d,bits,n,kind", [(32, 3, 1, "f32"), (32, 2, 256, "bf16"), (64, 4, 257, "unit"), (96, 3, 7, "bf16unit"), (160, 1, 65, "f32"), (256, 4, 128, "bf16"),
-                                           (256, 2, 129, "f32"), (256, 3, 256, "unit"), (384, 2, 85, "bf16"), (384, 3, 170, "f32"), (768, 1, 64, "unit"), (1536, 2, 61, "f32")])
+                                           (256, 2, 129, "f32"), (256, 3, 256, "unit"), (384, 2, 85, "bf16"), (384, 3, 170, "f32"), (768, 1, 64, "unit"), (1536, 2, 52, "f32"), (1536, 2, 53, "bf16"),
+                                           (1536, 3, 61, "f32")])
 def test_short_vectors(d, bits, n, kind):
     T.test_quantize_prod(d, bits, n, kind)
     T.test_quantize_mse(d, bits, n, kind)
