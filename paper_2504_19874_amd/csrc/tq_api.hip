@@ -57,16 +57,37 @@ bool quant_rows_serves(int64_t n, int d, bool prod) {
   return prod ? (n <= 64 && n * d <= 52 * 1536) || n * d <= 32768 : n <= 64 || n * d <= 65536;
 }
 
-// of a table that is a sum of signs, the dequantiser's (see there)
-bool rows_before_digits(int64_t n, int d, bool prod) {
+// The dequantiser's (tq_score_small.hip: both matrices in one kernel, decoding and products by vector instructions).  us, it / the kernels on the
+// matrix cores:
+//   4 bits      d = 64    1 code 3.1 / 5.2, 512 5.2 / 5.9, 640 6.1 / 5.9
+//               d = 128   1 3.1 / 6.4, 512 5.9 / 7.3, 1024 7.8 / 7.3
+//               d = 256   512 8.1 / 8.5, 640 9.1 / 8.6
+//               d = 384   (3 bits) 256 8.3 / 9.9, 384 10.8 / 10.0
+//               d = 512   256 9.5 / 12.6
+//               d = 768   256 15.1 / 16.9
+//               d = 1024  192 18.3 / 20.8, 256 22.6 / 22.1
+//               d = 1536  128 26.4 / 30.4, 192 37.3 / 30.6
+//               d = 3072  32 31 / 56 (48 codes), 64 58.5 / 55.8
+//   3 + 1 bits  d = 384   256 12.8 / 15.0
+//               d = 768   256 23.0 / 30.6
+//               d = 1536  128 43.7 / 56.6, 192 63.8 / 56.8
+//               d = 3072  32 94 / 108, 64 237 / 109
+bool dequant_rows_serves(int64_t n, int d) { return n <= (d <= 256 ? 512 : 256) && d < 4096 && n * d <= (d <= 2048 ? 128 * 1536 : 32 * 3072); }
+
+// Codes of a table that is a sum of signs: only a few long ones by these products, the others by digits, made in the call where they are not at
+// hand, which takes ten times as long.  us and error against 64 bits (1e-7 of a coordinate's root mean square), products / digits at hand:
+//   2 bits      d = 512   1 code 4.3 / 3.7, 32 4.9 / 4.2, 0.9 / 1.3
+//               d = 1536  1 5.4 / 5.0, 16 9.5 / 5.3, 1.15 / 1.24 (digits made in the call 27)
+//   2 + 1 bits  d = 512   1 4.4 / 5.1, 32 4.9 / 5.8, 1.1 / 1.3
+//               d = 768   32 5.7 / 6.4, 1.2 / 1.2
+//               d = 1024  16 5.5 / 6.7, 32 7.3 / 7.4, 1.3 / 1.1
+//               d = 1536  4 6.3 / 7.7, 16 8.2 / 8.1, 32 11.0 / 9.1, 1.5 / 1.25 (digits made in the call 50)
+//               d = 3072  1 13.5 / 13.2, 16 39.8 / 14.9, 1.9 / 1.5
+// So products where they are the closer ones, which is without a sketch and below d = 1024, and beyond it while they take less time.
+bool rows_before_digits(int64_t n, int d, int bits, bool prod, bool at_hand) {
+  if (at_hand && prod && bits > 0 && d >= 1024 && n * d * d >= 32 * 1024 * 1024) return false;
   return n <= (prod ? 32 : 64) && d >= 512 && d < 4096 && (((prod ? 2 : 1) * n + 3) / 4) * (int64_t)d * d * (prod ? 2 : 1) <= 300 * 512 * 512;
 }
-
-// The dequantiser's (tq_score_small.hip: both matrices in one kernel, decoding and products by vector instructions), against the kernels on the matrix cores,
-// us: 4 bits d = 64 1 code 3.1 / 5.2, 512 5.2 / 5.9, 640 6.1 / 5.9; 128 1 3.1 / 6.4, 512 5.9 / 7.3, 1024 7.8 / 7.3; 256 512 8.1 / 8.5, 640 9.1 / 8.6; 384 (3 bits) 256 8.3 / 9.9, 384 10.8 / 10.0; 512 256 9.5 / 12.6; 768 256 15.1 / 16.9; 1024 192
-// 18.3 / 20.8, 256 22.6 / 22.1; 1536 128 26.4 / 30.4, 192 37.3 / 30.6; 3072 32 31 / 56 (48 codes), 64 58.5 / 55.8; 3 + 1 bits 384 256 12.8 / 15.0; 768 256 23.0 / 30.6; 1536 128
-// 43.7 / 56.6, 192 63.8 / 56.8; 3072 32 94 / 108, 64 237 / 109.
-bool dequant_rows_serves(int64_t n, int d) { return n <= (d <= 256 ? 512 : 256) && d < 4096 && n * d <= (d <= 2048 ? 128 * 1536 : 32 * 3072); }
 
 inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 inline size_t round_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
@@ -661,13 +682,11 @@ tq_status tq_dequantize(const tq_params* p, const uint32_t* idx, const uint32_t*
                                       kappa_of(p->d), make_codebook(p), 0, 0.f, make_codebook(p),
                                       static_cast<hipStream_t>(stream)));
   }
-  // A few codes by matrix-vector products in fp32.  Of a table that is a sum of signs only a few long ones, the others by digits, whether the matrices' are there or made
-  // in the call: from the least codes on these take about the same time (us, products / digits: 256, 2 + 1 bits, 16 codes 3.5 / 3.9; 768 32 6.2 / 6.6; 1536 4 7.9 / 8.2, 16 9.7 /
-  // 8.9; 2 bits 64 14.7 / 8.1), but without a sketch, or with one below d = 1024, they are a little further from 64 bits (of a coordinate's root mean square, d = 512, 2 bits,
-  // 0.8 / 1.3e-7; 768, 2 + 1 bits 1.18 / 1.25e-7; 1536, 2 + 1 bits 1.46 / 1.27e-7).
+  // a few codes by matrix-vector products in fp32 (see rows_before_digits)
   const bool by_digits = !fp32_mfma_only(p) && sign_gemm_serves(p->bits_mse, prod, p->d, n) && (p->bits_mse > 0 || prod) && p->Pi != nullptr &&
                          (!prod || p->S != nullptr) && sign_table(p->bits_mse, make_codebook(p), &sc);
-  if (by_digits ? rows_before_digits(n, p->d, prod) : few_rows) return by_rows();
+  const bool digits_at_hand = h2_dequant_images(p) != nullptr && sign_images(p);
+  if (by_digits ? rows_before_digits(n, p->d, p->bits_mse, prod, digits_at_hand) : few_rows) return by_rows();
   // many codes of a table that is a sum of signs: digits of Pi^T and S^T, from the images or made here where the workspace holds them
   if (by_digits) {
     const hipStream_t s = static_cast<hipStream_t>(stream);

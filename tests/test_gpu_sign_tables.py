@@ -95,7 +95,7 @@ def test_long_codes(d, bits, prod, n):
 # up to 32 codes of a workgroup and up to 64, the last of several, the ends of the range (256 compute units); fewer steps than wavefronts, a remainder of them
 @pytest.mark.parametrize("d,bits,prod,n", [(256, 2, False, 1), (256, 2, True, 32), (256, 0, True, 33), (384, 1, True, 31), (384, 2, False, 65), (512, 1, False, 1024), (512, 1, False, 1025),
                                            (640, 1, True, 64), (640, 2, True, 1600), (1152, 2, False, 129), (1536, 2, True, 64), (1024, 1, True, 100), (768, 2, True, 33),
-                                           (256, 1, True, 2048), (256, 1, True, 2049), (512, 1, True, 1025), (640, 1, True, 1537)])
+                                           (256, 1, True, 2048), (256, 1, True, 2049), (512, 1, True, 1025), (640, 1, True, 1537), (1536, 2, True, 14), (1536, 2, True, 15), (2048, 1, True, 8)])
 def test_few_long_codes(d, bits, prod, n):
     p, codes, parts, norm = make(bits, prod, n, d)
     wide = torch.full((n + 1, d + 4), 7.0, device=T.DEV)
