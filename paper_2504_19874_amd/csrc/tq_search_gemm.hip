@@ -332,7 +332,7 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void search_gemm_kernel(const Sear
     query_s[3 * TM + m] = inv;
     query_s[4 * TM + m] = e1;
     query_s[5 * TM + m] = e2;
-    query_s[6 * TM + m] = bar;
+    query_s[6 * TM + m] = m < rows_m ? bar : __builtin_nanf("");  // past the last query: not reached by a score that is infinite either
   }
   store_scalars(tile0);
   if (tid < 4) found_n[tid] = 0;

@@ -133,6 +133,18 @@ def test_search_by_candidates_with_too_many_of_them(d, bits, prod):
         T._topk_both_ways(p, q, 1, nq, c, n, topk)
 
 
+@pytest.mark.parametrize("d,bits,prod,nq", [(128, 2, True, 100), (256, 4, False, 70)])
+def test_search_by_candidates_with_infinite_norms(d, bits, prod, nq):
+    """Scores that are infinite, or whose bound is, reach every bar: those of the places behind the last query are none."""
+    n, topk = 20000, 64
+    p = T.setup(d, bits, prod)[0]
+    c = T._random_codes(p, d, bits, prod, n, 5)
+    c["norm"][7::1013] = float("inf")
+    c["norm"][11::517] = -float("inf")
+    c["norm"][13::2001] = 3e38
+    T._topk_both_ways(p, T.dev(W.gaussian_queries(nq, d, 9, unit=False)), 1, nq, c, n, topk)
+
+
 @pytest.mark.parametrize("vprod,groups,qpg,npg", [(True, 2, 3, 1), (False, 2, 2, 8193), (True, 1, 1, 32768), (False, 1, 2, 32769)])
 def test_attend_joins_of_chunks(vprod, groups, qpg, npg):
     """One chunk, more than sixteen, the 64 that a wavefront's lanes hold, and one more."""
