@@ -413,7 +413,7 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void search_gemm_kernel(const Sear
         auto exact = [&](int u, int e, float sign) {  // score + sign * its error bound
           const float* const q = query_s + m + e;
           const float nu = cs[2 * TN + c0 + 32 * u], fac = cs[TN + c0 + 32 * u];
-          float eps = fabsf(nu) * q[4 * TM];
+          float eps = HAVE_P ? fabsf(nu) * q[4 * TM] : 0.f;  // (without centroids that factor is zero, and a norm may be infinite)
           if (HAVE_S) eps = fmaf(fabsf(nu * kg[u]), q[5 * TM], eps);
           return fmaf(acc[t][u][4 * k + e] * (nu * fac), q[3 * TM], sign * eps);
         };

@@ -133,7 +133,7 @@ def test_search_by_candidates_with_too_many_of_them(d, bits, prod):
         T._topk_both_ways(p, q, 1, nq, c, n, topk)
 
 
-@pytest.mark.parametrize("d,bits,prod,nq", [(128, 2, True, 100), (256, 4, False, 70)])
+@pytest.mark.parametrize("d,bits,prod,nq", [(128, 2, True, 100), (256, 4, False, 70), (128, 0, True, 129)])
 def test_search_by_candidates_with_infinite_norms(d, bits, prod, nq):
     """Scores that are infinite, or whose bound is, reach every bar: those of the places behind the last query are none."""
     n, topk = 20000, 64
