@@ -1,4 +1,4 @@
-"""Queries into the rotated and the sketch basis, on either side of the 64 that matrix-vector products take."""
+"""Queries into the rotated and the sketch basis, on either side of what matrix-vector products take: 64 of any length, 65536 values, 1024 at d = 128."""
 import numpy as np
 import pytest
 import torch
@@ -41,7 +41,8 @@ def run(p, q, codes, n):
     return s
 
 
-@pytest.mark.parametrize("d,bits,nq", [(256, 0, 64), (256, 0, 65), (768, 1, 300), (160, 2, 129), (1536, 0, 100), (128, 0, 90)])
+@pytest.mark.parametrize("d,bits,nq", [(256, 0, 64), (256, 0, 65), (768, 1, 300), (160, 2, 129), (1536, 0, 100), (128, 0, 90),
+                                       (256, 0, 256), (256, 0, 257), (160, 2, 409), (160, 2, 410), (128, 0, 1024), (128, 0, 1025), (1536, 0, 64), (1536, 1, 65)])
 def test_the_sketch_comes_from_s(d, bits, nq):
     p, q, codes, n, want, scale = problem(d, bits, nq, d + nq)
     P.check_close(run(p, q, codes, n).cpu().numpy(), want, scale, "score")
@@ -67,7 +68,7 @@ def test_the_fp32_instructions_for_any_number_above_64(d, bits, few, many):
     P.check_close(whole.cpu().numpy(), want, scale, "score")
 
 
-@pytest.mark.parametrize("d,bits,nq", [(256, 1, 65), (1024, 0, 130)])
+@pytest.mark.parametrize("d,bits,nq", [(256, 1, 257), (1024, 0, 130)])
 def test_images_change_no_bit(d, bits, nq):
     """The matrices' pieces from the images, or made in a workspace of the size that is asked for without them."""
     p, q, codes, n, want, scale = problem(d, bits, nq, d)
