@@ -85,23 +85,31 @@
  *     whatever the batch size, where the residual is so small that the part of x
  *     left out would show in gamma (4-bit MSE stage up to d = 416, 3 bits up to
  *     d = 96, 2 bits at d = 32).
- *   Up to 64 vectors at d >= 512, while ceil(n / 4) d^2 (twice that with a sketch)
- *     is at most 150 x 512^2 (and, with a sketch, params.workspace holds their
- *     residuals) are rotated by plain fp32 multiply-adds, one matrix-vector
- *     product per vector, and so are a handful of long vectors in tq_dequantize;
- *   dequantise, more than 8192 vectors at d = 128 and every other d: two pieces of
- *     a centroid and of an entry of Pi^T or S^T, a sign as one exact piece (error
+ *   quantise, a few vectors, by plain fp32 multiply-adds, one matrix-vector product per
+ *     vector: at d = 128 up to 256 fp32 vectors without a sketch; at every other d up to
+ *     4096 up to 64, and short ones up to 256 while they are at most 65536 values
+ *     (with a sketch 32768, long ones 79872), while ceil(n / 4) d^2 is at most
+ *     150 x 512^2 and, with a sketch, params.workspace holds their residuals;
+ *   dequantise, up to 512 vectors at d <= 256, up to 256 at larger d below 4096 while
+ *     they are at most 196608 values (98304 above d = 2048): plain fp32 multiply-adds
+ *     of decoded codes (tables that are sums of signs: see below);
+ *   dequantise, more than 8192 vectors at d = 128 and beyond these at every other d: two
+ *     pieces of a centroid and of an entry of Pi^T or S^T, a sign as one exact piece (error
  *     below 4e-5 of a coordinate's typical size);
  *   dequantise, a table of up to two bits that is symmetric about zero: sums of signs
  *     times the 25 leading bits of an entry (of its column's largest), at d = 128 (with the
  *     images of tq_build_dequant_images, or without any up to 24576 vectors) and above 8192
- *     vectors 20 of them; at d = 256, 384, 512, ... from 2^20 coordinates on for two bits
- *     without a sketch, always for the rest.  Error in units of a coordinate's root mean
+ *     vectors 20 of them; at d = 256, 384, 512, ... for two bits without a sketch where they
+ *     are few (32 values each of 64 vectors: up to two times the compute units) or 2^20
+ *     coordinates and more, always for the rest; a handful of vectors from d = 512 on (up
+ *     to 64, 32 with a sketch) takes the multiply-adds above instead where these are closer
+ *     to the exact sums or take less time.  Error in units of a coordinate's root mean
  *     square, of the fp32 instructions -> of these: d = 128 0.9 - 1.2e-7 -> 0.8e-7 (above 8192
  *     vectors 1.55e-6, where two bf16 pieces are 2.5 - 3.9e-6), d = 768 5 - 8e-7 -> 1.3 -
  *     1.7e-7, d = 3072 1.0 - 1.6e-6 -> 2.2 - 3.1e-7.  An entry of Pi or S that is not finite
  *     makes that output of every vector NaN;
- *   scoring, Pi q and S q: plain fp32 for up to 64 queries in all; more of them at d
+ *   scoring, Pi q and S q: plain fp32 for up to 64 queries in all, up to 1024 at
+ *     d <= 128 and for at most 65536 values at every d; more of them at d
  *     other than 128 from two fp16 pieces of the query and of Pi and S each, where the
  *     workspace has the room that tq_score_workspace_bytes counts (0.62 of the
  *     fp32 instructions' error), on the fp32 instructions elsewhere;
@@ -112,13 +120,13 @@
  *   scoring, few queries: fixed-point digits (up to 32 per group at d <= 1024, up to 16
  *     per group at d <= 4096 (64 in all beyond d = 512), d a multiple of 128,
  *     codebook symmetric about zero).
- * Smaller batches of fp32 vectors, and of codes of other tables, at d = 128 run on the fp32 matrix
- * instructions.  All paths meet
+ * Batches at d = 128 between these sizes (fp32 vectors: 257 or, with a sketch, 1 up to 8192; codes of
+ * other tables: 513 up to 8192) run on the fp32 matrix instructions.  All paths meet
  * the same tolerances (indices equal to an fp32 evaluation except within 1e-5 of a
  * cell boundary; values and scores within 1e-4 relative).  With TQ_FLAG_FP32_MFMA
  * in params.flags every contraction of tq_quantize_*, tq_dequantize and
  * many-query tq_score stays on the fp32 matrix
- * instructions.
+ * instructions (but for the rotation of up to 64 queries, plain fp32 multiply-adds).
  */
 #ifndef TURBOQUANT_H
 #define TURBOQUANT_H
@@ -282,7 +290,8 @@ tq_status tq_derive_params(int32_t d, const float* Pi, const float* S, float* Pi
  * every other d: Pi and S Pi^T as rows of two fp16 pieces (10 d^2 bytes), which tq_quantize_* and the rotation of many
  * queries multiply.  At those d the quantisers use them only together with a params.workspace that holds the pieces of
  * at least 256 vectors, or of all of them (tq_workspace_bytes(p, n, 0, 0) is enough; a smaller one means fewer vectors
- * per pass); without it, and for more than 16384 vectors below d = 512, the launch splits the matrices itself.
+ * per pass); without it, and for more than 16384 vectors below d = 512, the launch splits the matrices itself; a few
+ * vectors ("Arithmetic") and few queries are multiplied with the fp32 matrices.
  * tq_images_bytes: size of the buffer for dimension d (0: none is taken at this d, tq_build_images then does
  * nothing).  tq_build_images reads p->Pi and, when p->S is set, p->SPiT (at d = 128 also p->PiT and p->ST), device
  * memory as tq_derive_params left it, and writes `images` (device, 16-byte aligned, owned by the caller) on
@@ -303,7 +312,9 @@ tq_status tq_build_images(const tq_params* p, void* images, void* stream);
  * that its second part has the digits (a buffer that was sized and filled without them stays valid under the first flag alone).
  * Without the first flag tq_dequantize makes these tiles in the workspace in every call, where it has room (8 d^2 + 256 bytes), or takes kernels
  * that do without, the same up to rounding; at d = 128 it leaves the workspace alone (all arrays 16-byte aligned; params.images null and up to 24576 vectors: the
- * kernel makes the digits itself, to the same bits; above that, or with images that have none, kernels that do without); tq_score likewise for more than 64 queries (tq_score_workspace_bytes counts the room). */
+ * kernel makes the digits itself, to the same bits; above that, or with images that have none, kernels that do without); a few
+ * vectors ("Arithmetic") are multiplied with the fp32 matrices, or with digits where these are at hand; tq_score makes the pieces of S likewise for queries
+ * that are not rotated in plain fp32 (tq_score_workspace_bytes counts the room). */
 size_t tq_dequant_images_bytes(int32_t d);
 tq_status tq_build_dequant_images(const tq_params* p, void* images, void* stream);
 /* The same buffer for the calls of one parameter set alone: without the digits that its table (p->centroids) refuses in any case, and without
