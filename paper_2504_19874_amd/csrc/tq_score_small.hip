@@ -29,10 +29,11 @@ constexpr int MV_Q = 4;  // vectors of a workgroup
 // A wavefront takes R rows of the matrix at a time, 16 bytes per lane and load, against Q vectors that the
 // workgroup has staged in LDS.  Bound by the matrix coming from memory; R = 4 shares the staging and the LDS reads over four
 // rows where that still gives the chip enough workgroups.  The vectors go to LDS by direct loads, and the beginning of the rows is on
-// its way before they are waited for; then two chunks of a row are loaded ahead (one with R = 4: two take 13.2 us instead of 11.8 for 50 vectors and 768
-// x 768).  (Four vectors, two matrices of 3072 x 3072, 75 MB: 57 us with one row per wavefront and the vectors staged a float at a time, 21.7
-// with vectors staged through registers one after the other and nothing ahead, 18.3 here; twelve of them 32.7 -> 26.3; five, 1536: 9.5 -> 7.5; 60 vectors
-// of 384 15.0 us with a thread per row of the matrix, 5.1 here, of 128 6.2 and 3.4.)
+// its way before they are waited for; then two chunks of a row are loaded ahead (one with R = 4: two take 13.2 us instead of
+// 11.8 for 50 vectors and 768 x 768).  us, vectors staged through registers one after the other and nothing ahead -> here:
+//   3072, two matrices (75 MB)  4 vectors 21.9 -> 17.6 (57 with a row per wavefront, staged a float at a time), 12 33.3 -> 24.7
+//   1536, one matrix            5 9.5 -> 7.5
+//   384 / 128, one matrix       60 (a thread per row of the matrix) 15.0 / 6.2 -> 5.1 / 3.4
 template <int Q, int R>
 __global__ __launch_bounds__(256) void matvec_rows_kernel(const int d, const int nq, const float* __restrict__ W0,
                                                           const float* __restrict__ W1, const float* __restrict__ x,

@@ -6,8 +6,8 @@
 // score that high), found by ranking the maxima against each other, and only scores that reach it, little more than k, are
 // looked at again.  In later segments a score has to beat the k-th best pair, which a handful do.  The ones that pass are
 // appended to a list and ranked against it.  Where they are many (equal scores, a row that rises), the k-th best of the
-// threads' best PAIRS is the bar instead: pairs are never equal, so at most k threads have any that reach it.  A few long rows (one query against a million codes) are cut into chunks, one
-// workgroup each, whose lists topk_merge_kernel joins in the same way.
+// threads' best PAIRS is the bar instead: pairs are never equal, so at most k threads have any that reach it.  A few long rows
+// (one query against a million codes) are cut into chunks, one workgroup each, whose lists topk_merge_kernel joins in the same way.
 // (Before: a sorted list per thread, k rounds of arg-max to join them.  4 rows of 10^6 scores, k = 10: 35 + 30 us for the
 // chunks and the merge, 6.7 + 5.0 here; 2 rows of 300000, k = 64: 11.9 + 12.1.)
 // What such a launch costs is a chain of latencies, so the comparisons are shared out: those of a few pairs over up to sixteen lanes each, those
@@ -209,9 +209,12 @@ __global__ __launch_bounds__(256) void topk_merge_kernel(const float* __restrict
 
 // Chunks per row when a call's rows are too few to fill the chip: 0 (one workgroup per row) unless the rows are
 // few and longer than two segments; then chunks of a segment or more, about four workgroups per compute unit in all, and no more
-// pairs per row than the joining kernel takes (4096).  (A workgroup takes 3 - 5 us per segment, more for k = 64, the joining 4.5 - 8: one row of 50000, k = 10:
-// 23.3 us in one workgroup, 4.5 + 4.4 in seven; 5 of 30000, k = 16: 20.2 and 6.9 + 7.1; 10 of 20000, k = 64: 37.3 and 12.1 + 8.5.)  (A segment exactly where there could be more: cut into 122 parts, a row of 10^6 is a
-// segment and eight columns each, two passes; 4 rows, k = 10: 13.6 -> 10.8 us.)
+// pairs per row than the joining kernel takes (4096).  A segment exactly where there could be more: cut into 122 parts, a row of
+// 10^6 is a segment and eight columns each, two passes (4 rows, k = 10: 13.6 -> 10.8 us).  A workgroup takes 3 - 5 us per segment,
+// more for k = 64, the joining 4.5 - 8.  us, one workgroup per row / chunks + joining:
+//   1 row of 50000, k = 10    23.3 / 4.5 + 4.4
+//   5 rows of 30000, k = 16   20.2 / 6.9 + 7.1
+//   10 rows of 20000, k = 64  37.3 / 12.1 + 8.5
 int topk_chunks(int64_t rows, int64_t n, int k) {
   if (k < 1 || rows < 1 || rows > 128 || n <= 2 * SEG) return 0;
   int64_t c = (4 * (int64_t)device_cu_count() + rows - 1) / rows;
