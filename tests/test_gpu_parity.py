@@ -160,8 +160,8 @@ def test_quantize_mse(d, bits, n, kind):
 @pytest.mark.parametrize("d,bits,n,kind", [(1536, 4, 1, "unit"), (1536, 4, 8, "f32"), (3072, 2, 64, "bf16"), (512, 3, 5, "f32"),
                                           (1024, 1, 33, "bf16unit"), (768, 4, 64, "unit"), (4096, 2, 3, "f32"), (544, 0, 7, "f32")])
 def test_quantize_a_handful_of_long_vectors(d, bits, n, kind):
-    """Up to 64 vectors at d >= 512 with a workspace at hand: y = Pi x by the matrix-vector kernel, then norm, decision
-    and packing per vector; without a workspace the tiled contraction.  Both against the oracle."""
+    """Up to 64 vectors at d >= 512 by the matrix-vector kernel, which also decides and packs, with a workspace and without
+    one; the largest of them, beyond its limit, by the tiled contraction.  All against the oracle."""
     p, Pi, _, c32, t32 = setup(d, bits, False)
     x_or, x_dev, normalise = _quant_inputs(n, d, kind, 13 * d + bits)
     idx_or, nu_or, y_or = o.quant_mse(x_or, Pi, t32, normalise)
@@ -188,7 +188,7 @@ def test_quantize_a_handful_of_long_vectors(d, bits, n, kind):
 @pytest.mark.parametrize("d,bits_mse,n,kind", [(1536, 1, 1, "unit"), (3072, 1, 8, "f32"), (512, 3, 64, "bf16"), (1024, 0, 5, "f32"),
                                               (768, 4, 33, "unit"), (2048, 2, 2, "bf16unit"), (544, 2, 9, "f32")])
 def test_quantize_prod_of_a_handful_of_long_vectors(d, bits_mse, n, kind):
-    """Alg. 2 on the matrix-vector route (up to 64 vectors, d >= 512, workspace sized by tq_workspace_bytes)."""
+    """Alg. 2 on the matrix-vector route (a few vectors, d >= 512, workspace sized by tq_workspace_bytes)."""
     p, Pi, S, c32, t32 = setup(d, bits_mse, True)
     x_or, x_dev, normalise = _quant_inputs(n, d, kind, 17 * d + bits_mse)
     assert tq.tq_workspace_bytes(p, n, 0, 0) >= 2 * n * d * 4

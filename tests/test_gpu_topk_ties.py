@@ -30,6 +30,12 @@ def call(p, q, c, n, topk, nq=2):
     return scores, top, run
 
 
+def both_signs(nq):
+    """One query nq // 2 times, then its opposite."""
+    q = W.gaussian_queries(1, 128, 5, unit=False)
+    return T.dev(np.concatenate([q.repeat(nq // 2, 0), -q.repeat(nq - nq // 2, 0)]))
+
+
 def case(kind, n):
     p = T.setup(128, 2, False)[0]
     c = T._random_codes(p, 128, 2, False, 1, 3)
@@ -39,14 +45,13 @@ def case(kind, n):
 
 
 @pytest.mark.parametrize("topk", [1, 10, 64])
-@pytest.mark.parametrize("n", [8192, 50001, 300000])  # one segment, chunks and their joining
+@pytest.mark.parametrize("nq,n", [(2, 8192), (2, 50001), (2, 300000), (129, 50001)])  # one segment, chunks and their joining, a workgroup's several segments
 @pytest.mark.parametrize("kind", ["rising", "falling", "equal", "ties at the end", "zeros", "steps", "period", "infinite"])
-def test_many_candidates(kind, n, topk):
+def test_many_candidates(kind, nq, n, topk):
     p, c = case(kind, n)
-    q = W.gaussian_queries(1, 128, 5, unit=False)
-    scores, (ti, tv), _ = call(p, T.dev(np.concatenate([q, -q])), c, n, topk)
+    scores, (ti, tv), _ = call(p, both_signs(nq), c, n, topk, nq)
     s = scores.cpu().numpy()
-    for r in range(2):
+    for r in (0, nq // 2):
         want = np.argsort(-s[r], kind="stable")[:topk]  # equal scores by lower index
         assert np.array_equal(ti[r].cpu().numpy(), want)
         assert np.array_equal(tv[r].cpu().numpy(), s[r][want])
@@ -67,14 +72,14 @@ def test_chunks_and_bars(kind, nq, n, topk):
         assert np.array_equal(tv[r].cpu().numpy(), s[r][want])
 
 
+@pytest.mark.parametrize("nq", [2, 129])  # a segment per workgroup, seven
 @pytest.mark.parametrize("kind", ["rising", "equal", "ties at the end", "steps"])
-def test_their_cost_is_bounded(kind):
+def test_their_cost_is_bounded(kind, nq):
     """50001 scores per row: within ten times a row of drawn scores (the quadratic ranking of whole segments
     that this guards against takes thousands of times as long)."""
     def us(kind):
         p, c = case(kind, 50001)
-        q = W.gaussian_queries(1, 128, 5, unit=False)
-        _, _, run = call(p, T.dev(np.concatenate([q, -q])), c, 50001, 10)
+        _, _, run = call(p, both_signs(nq), c, 50001, 10, nq)
         e = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
         torch.cuda.synchronize()
         best = float("inf")
