@@ -185,7 +185,7 @@ __global__ __launch_bounds__(256) void search_select_kernel(const SelectArgs a) 
       mx = fmaxf(mx, fmaf(-2.f, eps, top[i0 + i]));
     }
   }
-  const float bar = kth_of_maxima(mx, k, keys, &bar_s, tid);
+  const float bar = kth_of_maxima<256>(mx, k, keys, &bar_s, tid);
   uint32_t pass = 0u;
 #pragma unroll
   for (int i = N - 1; i >= 0; --i) pass = pass + pass + (top[i] >= bar ? 1u : 0u);

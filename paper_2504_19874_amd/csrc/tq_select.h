@@ -1,4 +1,4 @@
-// The k best of a workgroup's scores, shared by the top-k kernels (256 threads).
+// The k best of a workgroup's scores, shared by the top-k kernels.
 #pragma once
 #include "tq_internal.h"
 
@@ -24,42 +24,47 @@ __device__ __forceinline__ int sum_of_lanes(int v, int lanes) {
   return v;
 }
 
-// a value that at least k of the workgroup's scores reach (-inf where there are fewer), close to the k-th largest: the k-th
-// largest of the threads' own maxima `mx` (-inf: none).  keys [256], bar: LDS.
+// a value that at least k of the workgroup's scores reach (-inf where there are fewer), close to the k-th largest: one that k, or an
+// eighth more, of 256 maxima `mx` of T threads (-inf: none) reach, of 64 for k <= 16 (neighbouring threads' maxima joined; of 8192 scores
+// 10.9 are expected to reach the 10th largest of 64, 10.2 that of 256).  keys [256], bar: LDS.  A wavefront halves the range between the
+// smallest and the largest of them, some five steps of a comparison or four and as many counts.  (Ranked against each other in
+// place of this: 600 instructions per wavefront for k > 16.)
+template <int T>
 __device__ __forceinline__ float kth_of_maxima(float mx, int k, uint32_t* keys, uint32_t* bar, int tid) {
+  const auto larger = [](uint32_t x, uint32_t y) { return x > y ? x : y; };
+  const auto smaller = [](uint32_t x, uint32_t y) { return x < y ? x : y; };
   uint32_t key = ordered(mx);
-  if (k <= 16) {
-    // of the 64 maxima of four threads: a sixteenth of the comparisons, and of 8192 scores 10.9 are expected to reach the bar for k = 10
-    // and 18.4 for k = 16 (10.2 and 16.5 with a thread's own maxima)
-    uint32_t o = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)key, 0xB1, 0xf, 0xf, true);
-    key = o > key ? o : key;
-    o = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)key, 0x4E, 0xf, 0xf, true);
-    key = o > key ? o : key;
-    if ((tid & 3) == 0) keys[tid >> 2] = key;
-    if (tid == 0) *bar = 0xffffffffu;
-    __syncthreads();
-    int above = 0;
-#pragma unroll
-    for (int t = 0; t < 4; ++t) {
-      const uint4 v = reinterpret_cast<const uint4*>(keys)[4 * (tid & 3) + t];
-      above += (v.x > key ? 1 : 0) + (v.y > key ? 1 : 0) + (v.z > key ? 1 : 0) + (v.w > key ? 1 : 0);
-    }
-    above = sum_of_lanes(above, 4);
-    if ((tid & 3) == 0 && above < k) atomicMin(bar, key);
-    __syncthreads();
-    return from_ordered(*bar);
-  }
-  keys[tid] = key;
-  if (tid == 0) *bar = 0xffffffffu;
+  const int lanes = k <= 16 ? T / 64 : T / 256;  // uniform
+  if (lanes >= 2) key = larger(key, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)key, 0xB1, 0xf, 0xf, true));
+  if (lanes >= 4) key = larger(key, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)key, 0x4E, 0xf, 0xf, true));
+  if (lanes >= 8) key = larger(key, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)key, 0x141, 0xf, 0xf, true));
+  if (lanes >= 16) key = larger(key, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)key, 0x140, 0xf, 0xf, true));
+  if ((tid & (lanes - 1)) == 0) keys[tid / lanes] = key;
   __syncthreads();
-  int above = 0;
-  const uint4* m4 = reinterpret_cast<const uint4*>(keys);
-#pragma unroll 8
-  for (int t = 0; t < 64; ++t) {
-    const uint4 o = m4[t];
-    above += (o.x > key ? 1 : 0) + (o.y > key ? 1 : 0) + (o.z > key ? 1 : 0) + (o.w > key ? 1 : 0);
+  if (tid < 64) {
+    constexpr uint32_t NONE = 0x007fffffu;  // ordered(-inf)
+    uint4 v = k <= 16 ? make_uint4(keys[tid], NONE, NONE, NONE) : reinterpret_cast<const uint4*>(keys)[tid];
+    const auto count = [&](uint32_t at) {
+      const auto lanes_of = [](bool b) { return __builtin_popcountll(__builtin_amdgcn_ballot_w64(b)); };
+      const int n = lanes_of(v.x >= at);
+      return k <= 16 ? n : (n + lanes_of(v.y >= at)) + (lanes_of(v.z >= at) + lanes_of(v.w >= at));
+    };
+    // (threads without a score aside: their part of the range would be halved away in some ten steps)
+    const auto some = [](uint32_t x) { return x > NONE ? x : 0xffffffffu; };
+    uint32_t lo = over_wavefront(k <= 16 ? some(v.x) : smaller(smaller(some(v.x), some(v.y)), smaller(some(v.z), some(v.w))), smaller);
+    uint32_t hi = over_wavefront(k <= 16 ? v.x : larger(larger(v.x, v.y), larger(v.z, v.w)), larger);
+    lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)lo);
+    hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)hi) + 1u;  // none reaches it (no score is as large as the largest integer)
+    int n = lo < hi ? count(lo) : 0;  // that reach lo
+    if (n < k) lo = NONE;
+    while (n > k + k / 8 && hi - lo > 1u) {
+      const uint32_t mid = lo + (hi - lo) / 2u;
+      const int m = count(mid);
+      if (m >= k) lo = mid, n = m;
+      else hi = mid;
+    }
+    if (tid == 0) *bar = lo;
   }
-  if (above < k) atomicMin(bar, key);  // the smallest of the k largest
   __syncthreads();
   return from_ordered(*bar);
 }

@@ -1,17 +1,17 @@
 // Per-query top-k over a row of scores (the "return top-10" step of the nearest-neighbour configurations).
 // Order: larger score first, equal scores by lower index; a NaN is never taken.
 //
-// A workgroup walks its part of a row in segments of 8192 scores, 32 per thread in registers, and keeps the k best pairs so
-// far in LDS.  The first segment has no bar yet: the k-th largest of the 256 threads' own maxima is one (k threads hold a
-// score that high), found by ranking the maxima against each other, and only scores that reach it, little more than k, are
-// looked at again.  In later segments a score has to beat the k-th best pair, which a handful do.  The ones that pass are
-// appended to a list and ranked against it.  Where they are many (equal scores, a row that rises), the k-th best of the
-// threads' best PAIRS is the bar instead: pairs are never equal, so at most k threads have any that reach it.  A few long rows
-// (one query against a million codes) are cut into chunks, one workgroup each, whose lists topk_merge_kernel joins in the same way.
-// (Before: a sorted list per thread, k rounds of arg-max to join them.  4 rows of 10^6 scores, k = 10: 35 + 30 us for the
-// chunks and the merge, 6.7 + 5.0 here; 2 rows of 300000, k = 64: 11.9 + 12.1.)
-// What such a launch costs is a chain of latencies, so the comparisons are shared out: those of a few pairs over up to sixteen lanes each, those
-// of the maxima over four (4 rows as above: 11.3 + 9.0 without).
+// A workgroup of 256 to 1024 threads walks its part of a row in segments of 16 scores per thread, in registers, and keeps the k best pairs so
+// far in LDS, as integers that compare like pairs.  The first segment has no bar yet: what k of 64 or 256 groups of threads' maxima reach is
+// one (kth_of_maxima), and only scores that reach it, little more than k, are looked at again.  In later segments a score has to beat
+// the k-th best pair, which a handful do.  The ones that pass go from the registers to a list (a place for all of a wavefront's is
+// asked for once; elements that pass in no lane are a branch) and are ranked against it.  Where they are many (equal scores, a row that
+// rises), the k-th best of the groups' best PAIRS is the bar instead: pairs are never equal, so at most k groups have any that
+// reach it.  A few long rows (one query against a million codes) are cut into chunks, one workgroup each, whose lists topk_merge_kernel
+// joins in the same way.
+// What such a launch costs is a chain of latencies: us, before (256 threads with 32 scores each, maxima ranked against each other,
+// what passes fetched again from memory) and now: 3 rows of 12279, k = 64, 17.3 -> 5.8; 4 of 12969, k = 10, 6.5 -> 4.7; 45 of 16000,
+// k = 64, 29.2 -> 6.1; 5 of 30000, k = 16, 13.4 -> 7.0; 4 of 10^6, k = 10, with the joining 9.9 -> 9.2; 14 of 84645, k = 64, 22.2 -> 11.2.
 #include "tq_select.h"
 
 #include <type_traits>
@@ -19,128 +19,138 @@
 namespace tq {
 namespace {
 
-constexpr int SEG = 8192;              // scores per segment
-constexpr int PER = SEG / 256;         // per thread
-constexpr int LIST = 64 + 64 * PER;    // the k best so far, and all that k threads hold
+constexpr int PER = 16;  // scores of a segment per thread
+constexpr int THREADS = 1024;                 // of a workgroup at most; a segment has 16384 scores then
+constexpr int SEG = THREADS * PER;
 // more than this many are not ranked against each other as they are (two rows of 50001 equal scores, whole segments ranked:
-// 144 ms; 54 us as it is, 39 for scores that differ, 163 for rising ones)
+// 144 ms)
 constexpr int MANY = 512;
 
-struct TopkLds {
-  float v[LIST];
-  int i[LIST];
-  float best_v[64];
-  int best_i[64];
-  uint32_t mx[256];
-  uint32_t bar;
-  int count;
-  unsigned long long pair_bar;
-  unsigned long long pairs[256];
-};
-
-// pairs in the order of better() as unsigned integers; 0 is below every one of them
-__device__ __forceinline__ unsigned long long pair_key(float v, int i) {
-  return (unsigned long long)ordered(v + 0.f) << 32 | (uint32_t)~i;  // + 0: a negative zero is equal to a positive one
+// a pair as an integer: larger ones come first.  Equal scores by index; zeros are equal, the sign of one in the lowest bit.
+typedef unsigned long long pair;
+__device__ __forceinline__ pair make_pair(float v, int i) {
+  return (pair)ordered(v + 0.f) << 32 | (uint32_t)(0x7fffffff - i) << 1 | (v == 0.f ? __float_as_uint(v) >> 31 : 0u);
+}
+__device__ __forceinline__ int pair_index(pair p) { return 0x7fffffff - (int)((uint32_t)p >> 1); }
+__device__ __forceinline__ float pair_score(pair p) {
+  const float v = from_ordered((uint32_t)(p >> 32));
+  return v == 0.f ? __uint_as_float((uint32_t)p << 31) : v;
 }
 
-// v[e]: this thread's scores of one segment, NaN where there is none; pair(e) fetches score and index of the e-th again (a
-// handful are asked for, and a register array cannot be indexed).  kept: pairs in best so far (uniform).  Afterwards best
-// holds the k best of all segments up to this one, and the number of them is returned.
-// (Straight code for 32 elements would be 12 KB of instructions that a 10 us kernel has to fetch first: it is kept short.)
-template <int N, class Pair>
-__device__ int take_segment(TopkLds& s, const float (&v)[N], Pair pair, int k, int kept, int tid) {
+// N scores per thread of T
+template <int T, int N>
+struct TopkLds {
+  static constexpr int LIST = 64 + 64 * N * (T / 256) > MANY ? 64 + 64 * N * (T / 256) : MANY;  // the k best so far, and all that k groups of T / 256 threads hold
+  pair list[LIST];
+  pair best[64];
+  pair groups[256];
+  pair pair_bar;
+  __attribute__((aligned(16))) uint32_t mx[256];
+  uint32_t bar;
+  int count;
+};
+
+// v[e]: this thread's scores of one segment, NaN where there is none; index_of(e): the e-th one's index.  kept: pairs in best so far
+// (uniform).  Afterwards best holds the k best of all segments up to this one, and the number of them is returned.
+template <int T, int N, class Index>
+__device__ int take_segment(TopkLds<T, N>& s, const float (&v)[N], Index index_of, int k, int kept, int tid) {
+  constexpr int LIST = TopkLds<T, N>::LIST;
   float bar;
+  if (tid == 0) s.count = kept;
   if (kept < k) {
     float mx = -__builtin_inff();
 #pragma unroll
     for (int e = 0; e < N; ++e) mx = fmaxf(mx, v[e]);  // ignores NaN
-    bar = kth_of_maxima(mx, k, s.mx, &s.bar, tid);
+    bar = kth_of_maxima<T>(mx, k, s.mx, &s.bar, tid);
   } else {
     // the next larger value: an equal score of a later segment has a later index and does not beat a kept one
-    bar = from_ordered(ordered(s.best_v[k - 1] + 0.f) + 1u);  // + 0: see pair_key
+    bar = from_ordered((uint32_t)(s.best[k - 1] >> 32) + 1u);
+    __syncthreads();
   }
-  if (tid < kept) {
-    s.v[tid] = s.best_v[tid];
-    s.i[tid] = s.best_i[tid];
-  }
-  if (tid == 0) s.count = kept;
-  __syncthreads();
-  uint32_t pass = 0u;
+  if (tid < kept) s.list[tid] = s.best[tid];
+  // a wavefront's places are asked for together; most of its elements pass in no lane
+  uint64_t pass[N];
+  int passed = 0;
 #pragma unroll
-  for (int e = N - 1; e >= 0; --e) pass = pass + pass + (v[e] >= bar ? 1u : 0u);
-  if (pass != 0u) {
-    int pos = atomicAdd(&s.count, __builtin_popcount(pass));
-    for (uint32_t left = pass; left != 0u; left &= left - 1u, ++pos)
-      if (pos < LIST) pair(__builtin_ctz(left), s.v[pos], s.i[pos]);
+  for (int e = 0; e < N; ++e) {
+    pass[e] = __builtin_amdgcn_ballot_w64(v[e] >= bar);
+    passed += __builtin_popcountll(pass[e]);
+  }
+  if (passed != 0) {  // uniform
+    int at = 0;
+    if ((tid & 63) == 0) at = atomicAdd(&s.count, passed);
+    at = __builtin_amdgcn_readfirstlane(at);
+#pragma unroll
+    for (int e = 0; e < N; ++e) {
+      if (pass[e] == 0u) continue;
+      const int pos = at + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(pass[e] >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)pass[e], 0u));
+      if (v[e] >= bar && pos < LIST) s.list[pos] = make_pair(v[e], index_of(e));
+      at += __builtin_popcountll(pass[e]);
+    }
   }
   __syncthreads();
   int n = s.count;
   if (n > MANY) {  // uniform
-    unsigned long long key = 0;
-    for (uint32_t left = pass; left != 0u; left &= left - 1u) {
-      float pv;
-      int pi;
-      pair(__builtin_ctz(left), pv, pi);
-      const unsigned long long o = pair_key(pv, pi);
-      key = o > key ? o : key;
-    }
-    s.pairs[tid] = key;
-    if (tid == 0) s.pair_bar = ~0ull;
+    pair key = 0;
+#pragma unroll
+    for (int e = 0; e < N; ++e)
+      if (v[e] >= bar) {
+        const pair o = make_pair(v[e], index_of(e));
+        key = o > key ? o : key;
+      }
+    if (tid < 256) s.groups[tid] = 0;
+    if (tid == 0) s.pair_bar = ~pair(0);
     __syncthreads();  // everyone has read the count, too
-    int above = 0;
-#pragma unroll 4
-    for (int t = 0; t < 256; ++t) above += s.pairs[t] > key ? 1 : 0;
-    if (above < k) atomicMin(&s.pair_bar, key);
+    atomicMax(&s.groups[tid / (T / 256)], key);
     if (tid == 0) s.count = kept;
     __syncthreads();
-    const unsigned long long pair_bar = s.pair_bar;
-    if (key >= pair_bar)
-      for (uint32_t left = pass; left != 0u; left &= left - 1u) {
-        float pv;
-        int pi;
-        pair(__builtin_ctz(left), pv, pi);
-        if (pair_key(pv, pi) >= pair_bar) {
-          const int pos = atomicAdd(&s.count, 1);  // below LIST: at most k threads come here with any
-          s.v[pos] = pv;
-          s.i[pos] = pi;
-        }
-      }
+    if (tid < 256) {
+      const pair own = s.groups[tid];
+      int above = 0;
+#pragma unroll 4
+      for (int t = 0; t < 256; ++t) above += s.groups[t] > own ? 1 : 0;
+      if (above < k) atomicMin(&s.pair_bar, own);
+    }
+    __syncthreads();
+    const pair pair_bar = s.pair_bar;
+    if (key >= pair_bar && key != 0)
+#pragma unroll
+      for (int e = 0; e < N; ++e)
+        if (v[e] >= bar)
+          if (const pair o = make_pair(v[e], index_of(e)); o >= pair_bar) s.list[atomicAdd(&s.count, 1)] = o;  // below LIST: at most k groups come here with any
     __syncthreads();
     n = s.count;
   }
   if (n == kept) return kept;  // uniform; nothing passed
-  const int lanes = n <= 16 ? 16 : n <= 32 ? 8 : n <= 64 ? 4 : n <= 128 ? 2 : 1;  // that share a pair's comparisons
-  for (int c = tid / lanes; c < n; c += 256) {  // one round, or one lane each
-    const float cv = s.v[c];
-    const int ci = s.i[c];
+  const int lanes = n * 16 <= T ? 16 : n * 8 <= T ? 8 : n * 4 <= T ? 4 : n * 2 <= T ? 2 : 1;  // that share a pair's comparisons
+  for (int c = tid / lanes; c < n; c += T / lanes) {  // one round, or one lane each
+    const pair own = s.list[c];
     int rank = 0;
-#pragma unroll 8
-    for (int o = tid & (lanes - 1); o < n; o += lanes) rank += better(s.v[o], s.i[o], cv, ci) ? 1 : 0;
+#pragma unroll 4
+    for (int o = tid & (lanes - 1); o < n; o += lanes) rank += s.list[o] > own ? 1 : 0;
     rank = sum_of_lanes(rank, lanes);
-    if (rank < k) {  // the lanes of a pair write the same
-      s.best_v[rank] = cv;
-      s.best_i[rank] = ci;
-    }
+    if (rank < k) s.best[rank] = own;  // the lanes of a pair write the same
   }
   __syncthreads();
   return n < k ? n : k;
 }
 
-__device__ __forceinline__ void write_best(const TopkLds& s, int kept, int k, int none, int32_t* out_idx, float* out_val, int tid) {
+template <int T, int N>
+__device__ __forceinline__ void write_best(const TopkLds<T, N>& s, int kept, int k, int none, int32_t* out_idx, float* out_val, int tid) {
   if (tid < k) {
-    out_idx[tid] = tid < kept ? s.best_i[tid] : none;
-    if (out_val != nullptr) out_val[tid] = tid < kept ? s.best_v[tid] : -__builtin_inff();
+    out_idx[tid] = tid < kept ? pair_index(s.best[tid]) : none;
+    if (out_val != nullptr) out_val[tid] = tid < kept ? pair_score(s.best[tid]) : -__builtin_inff();
   }
 }
 
 // chunk_len > 0: workgroup (row, chunk) takes columns [c0, c0 + chunk_len) of the row (chunk_len is a multiple of
 // 4, so a chunk is as aligned as the row) and writes k (value, index) pairs, -inf / INT_MAX where it has fewer
-__global__ __launch_bounds__(256) void topk_kernel(const float* __restrict__ scores, const int64_t n_row, const int64_t ld, const int k,
-                                                   const int vec4, int32_t* __restrict__ out_idx, float* __restrict__ out_val,
-                                                   const int64_t chunk_len, const int32_t* __restrict__ flags) {
+template <int T>
+__global__ __launch_bounds__(T) void topk_kernel(const float* __restrict__ scores, const int64_t n_row, const int64_t ld, const int k,
+                                                 const int vec4, int32_t* __restrict__ out_idx, float* __restrict__ out_val,
+                                                 const int64_t chunk_len, const int32_t* __restrict__ flags) {
   if (flags != nullptr && flags[blockIdx.x] == 0) return;
-  extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
-  TopkLds& s = *reinterpret_cast<TopkLds*>(smem_raw);
+  __shared__ TopkLds<T, PER> s;
   const int tid = threadIdx.x;
   const int64_t c0 = chunk_len > 0 ? (int64_t)blockIdx.y * chunk_len : 0;
   const int64_t n = chunk_len > 0 ? (n_row - c0 < chunk_len ? n_row - c0 : chunk_len) : n_row;
@@ -148,79 +158,73 @@ __global__ __launch_bounds__(256) void topk_kernel(const float* __restrict__ sco
   const int64_t out_row = chunk_len > 0 ? (int64_t)blockIdx.x * gridDim.y + blockIdx.y : blockIdx.x;
   const float NONE = __builtin_nanf("");
   float v[PER];
-  // element e of a thread: column 4 (tid + 256 (e / 4)) + e % 4 of the segment
+  // element e of a thread: column 4 (tid + T (e / 4)) + e % 4 of the segment, tid + T e of one that is not whole
   int kept = 0;
-  for (int64_t seg = 0; seg < n; seg += SEG) {
+  for (int64_t seg = 0; seg < n; seg += T * PER) {
     typedef float f32x4 __attribute__((ext_vector_type(4)));
-    if (vec4 && seg + SEG <= n) {  // uniform: all loads in flight together
+    const bool whole = vec4 && seg + T * PER <= n;  // uniform
+    if (whole) {
 #pragma unroll
       for (int u = 0; u < PER / 4; ++u) {
-        const f32x4 w = *reinterpret_cast<const f32x4*>(row + seg + 4 * (tid + 256 * u));
+        const f32x4 w = *reinterpret_cast<const f32x4*>(row + seg + 4 * (tid + T * u));
 #pragma unroll
         for (int e = 0; e < 4; ++e) v[4 * u + e] = w[e];
       }
     } else {
-      const int left = (int)(n - seg < SEG ? n - seg : SEG);
+      const int left = (int)(n - seg < T * PER ? n - seg : T * PER);
       const float* const src = row + seg;
 #pragma unroll
       for (int e = 0; e < PER; ++e) {
-        const int c = 4 * (tid + 256 * (e >> 2)) + (e & 3);
+        const int c = tid + T * e;  // (a few scores meet as many threads)
         const float w = src[c < left ? c : left - 1];
         v[e] = c < left ? w : NONE;
       }
     }
-    kept = take_segment(s, v, [&](int e, float& pv, int& pi) {
-      const int64_t c = seg + 4 * (tid + 256 * (e >> 2)) + (e & 3);
-      pv = row[c];
-      pi = (int)(c0 + c);
-    }, k, kept, tid);
+    const int first = (int)(c0 + seg) + (whole ? 4 * tid : tid);
+    kept = take_segment<T, PER>(s, v, [&](int e) { return first + T * (whole ? 4 * (e >> 2) : e) + (whole ? e & 3 : 0); }, k, kept, tid);
   }
   write_best(s, kept, k, chunk_len > 0 ? 0x7fffffff : -1, out_idx + out_row * k, out_val != nullptr ? out_val + out_row * k : nullptr, tid);
 }
 
-// One workgroup per row: the k best of its cands <= 256 N pairs of score and index (index INT_MAX: no pair).
+// One workgroup per row: the k best of its cands <= 4 T pairs of score and index (index INT_MAX: no pair).
 // They are sorted lists of k one behind the other, so a thread takes its pairs from ever other places of the lists: the threads' maxima are
 // then alike, and few pairs beside the k best reach the k-th largest of them.  (37 lists of 64, a thread's pairs all of one place: 81 us.)
-template <int N>
-__global__ __launch_bounds__(256) void topk_merge_kernel(const float* __restrict__ part_val, const int32_t* __restrict__ part_idx,
-                                                         const int cands, const int k, int32_t* __restrict__ out_idx,
-                                                         float* __restrict__ out_val, const int32_t* __restrict__ flags) {
+template <int T>
+__global__ __launch_bounds__(T) void topk_merge_kernel(const float* __restrict__ part_val, const int32_t* __restrict__ part_idx,
+                                                       const int cands, const int k, int32_t* __restrict__ out_idx,
+                                                       float* __restrict__ out_val, const int32_t* __restrict__ flags) {
+  constexpr int N = 4;
   if (flags != nullptr && flags[blockIdx.x] == 0) return;
-  extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
-  TopkLds& s = *reinterpret_cast<TopkLds*>(smem_raw);
+  __shared__ TopkLds<T, N> s;
   const int tid = threadIdx.x;
   const int64_t row = blockIdx.x;
   float v[N];
-  auto place = [&](int e) { return e * 256 + ((tid + 37 * e) & 255); };  // 256 + 37 = 293, a prime: no k up to 64 divides it
+  int idx[N];
 #pragma unroll
   for (int e = 0; e < N; ++e) {
-    const int c = place(e), cc = c < cands ? c : cands - 1;
+    const int c = e * T + ((tid + 37 * e) & (T - 1)), cc = c < cands ? c : cands - 1;  // 256 + 37 and 1024 + 37 are primes: no k up to 64 divides them
     const float w = part_val[row * cands + cc];
-    v[e] = c < cands && part_idx[row * cands + cc] != 0x7fffffff ? w : __builtin_nanf("");
+    idx[e] = part_idx[row * cands + cc];
+    v[e] = c < cands && idx[e] != 0x7fffffff ? w : __builtin_nanf("");
   }
-  const int kept = take_segment(s, v, [&](int e, float& pv, int& pi) {
-    pv = part_val[row * cands + place(e)];
-    pi = part_idx[row * cands + place(e)];
-  }, k, 0, tid);
+  const int kept = take_segment<T, N>(s, v, [&](int e) { return idx[e]; }, k, 0, tid);
   write_best(s, kept, k, -1, out_idx + row * k, out_val != nullptr ? out_val + row * k : nullptr, tid);
 }
 
 }  // namespace
 
 // Chunks per row when a call's rows are too few to fill the chip: 0 (one workgroup per row) unless the rows are
-// few and longer than two segments; then chunks of a segment or more, about four workgroups per compute unit in all, and no more
-// pairs per row than the joining kernel takes (4096).  A segment exactly where there could be more: cut into 122 parts, a row of
-// 10^6 is a segment and eight columns each, two passes (4 rows, k = 10: 13.6 -> 10.8 us).  A workgroup takes 3 - 5 us per segment,
-// more for k = 64, the joining 4.5 - 8.  us, one workgroup per row / chunks + joining:
-//   1 row of 50000, k = 10    23.3 / 4.5 + 4.4
-//   5 rows of 30000, k = 16   20.2 / 6.9 + 7.1
-//   10 rows of 20000, k = 64  37.3 / 12.1 + 8.5
+// few and longer than three segments; then chunks of equal lengths, a segment at most (down to 4096 scores in chunks of 256 threads: no
+// faster), and no more pairs per row than the joining kernel takes (4096).  A workgroup takes 4.7 us (k = 10) or 6 (64) for a segment and 2 for every further one, its lists joined 4.3 to 6.  us, one workgroup per
+// row / chunks + joining:
+//   10 rows of 20000, k = 64   8.2 / 10.8
+//   2 rows of 49000, k = 64   10.7 / 10.7
+//   2 rows of 56430, k = 10    9.6 /  8.4
+//   14 rows of 84645, k = 64  18.1 / 11.2
 int topk_chunks(int64_t rows, int64_t n, int k) {
-  if (k < 1 || rows < 1 || rows > 128 || n <= 2 * SEG) return 0;
-  int64_t c = (4 * (int64_t)device_cu_count() + rows - 1) / rows;
-  if (c > (n + SEG - 1) / SEG) c = (n + SEG - 1) / SEG;
+  if (k < 1 || rows < 1 || rows > 128 || n <= 3 * SEG) return 0;
+  int64_t c = (n + SEG - 1) / SEG;
   if (c > 4096 / k) c = 4096 / k;
-  if (c > 65535) c = 65535;
   return c >= 2 ? (int)c : 0;
 }
 
@@ -233,33 +237,37 @@ hipError_t launch_topk(const float* scores, int64_t rows, int64_t n, int64_t ld,
   if (k < 1 || k > 64 || rows > 0x7fffffff || n > 0x7fffffff) return hipErrorInvalidValue;
   if (chunks > 0 && (part_val == nullptr || part_idx == nullptr || chunks > 65535)) return hipErrorInvalidValue;
   const int vec4 = (ld % 4 == 0) && ((reinterpret_cast<uintptr_t>(scores) & 15u) == 0);
-  int64_t chunk_len = chunks > 0 ? ((n + chunks - 1) / chunks + 3) / 4 * 4 : 0;
-  if (chunks == (n + SEG - 1) / SEG) chunk_len = SEG;
+  const int64_t chunk_len = chunks > 0 ? ((n + chunks - 1) / chunks + 3) / 4 * 4 : 0;
   const dim3 grid((unsigned)rows, chunks > 0 ? (unsigned)chunks : 1u);
   if (chunks > 0) {
     out_idx = part_idx;
     out_val = part_val;
   }
-  static LdsLimit lds_limit;
-  if (const hipError_t e = raise_lds_limit(lds_limit, reinterpret_cast<const void*>(&topk_kernel), (int)sizeof(TopkLds)); e != hipSuccess) return e;
-  hipLaunchKernelGGL(topk_kernel, grid, dim3(256), sizeof(TopkLds), stream, scores, n, ld, k, vec4, out_idx, out_val, chunk_len, flags);
-  return hipGetLastError();
+  // As many threads as a row's first segment needs, but more rows at a time where there are more than the chip takes of the largest
+  // workgroups (us, 256 / 512 / 1024 threads: 1000 rows of 9766, k = 10, 10.9 / 12.7 / 17.0; 871 of 16000, k = 64, 23.1 / 19.9 / 23.3;
+  // 45 of 16000, k = 64, 17.0 / 9.5 / 6.1)
+  const bool crowd = rows > 2 * (int64_t)device_cu_count();
+  const int64_t len = chunks > 0 ? chunk_len : n;
+  auto go = [&](auto t_c) {
+    constexpr int T = decltype(t_c)::value;
+    hipLaunchKernelGGL((topk_kernel<T>), grid, dim3(T), 0, stream, scores, n, ld, k, vec4, out_idx, out_val, chunk_len, flags);
+    return hipGetLastError();
+  };
+  if (len <= 256 * PER || (crowd && k <= 16)) return go(std::integral_constant<int, 256>{});
+  if (len <= 512 * PER || crowd) return go(std::integral_constant<int, 512>{});
+  return go(std::integral_constant<int, THREADS>{});
 }
 
 hipError_t launch_topk_merge(const float* part_val, const int32_t* part_idx, int64_t rows, int ranges, int k,
                              int32_t* out_idx, float* out_val, hipStream_t s, const int32_t* flags) {
   if (rows == 0) return hipSuccess;
   if (ranges < 1 || k < 1 || k > 64 || (int64_t)ranges * k > 4096 || rows > 0x7fffffff) return hipErrorInvalidValue;
-  auto go = [&](auto n_c) {
-    constexpr int N = decltype(n_c)::value;
-    static LdsLimit lds_limit;
-    if (const hipError_t e = raise_lds_limit(lds_limit, reinterpret_cast<const void*>(&topk_merge_kernel<N>), (int)sizeof(TopkLds)); e != hipSuccess) return e;
-    hipLaunchKernelGGL((topk_merge_kernel<N>), dim3((unsigned)rows), dim3(256), sizeof(TopkLds), s, part_val, part_idx, ranges * k, k, out_idx, out_val, flags);
+  auto go = [&](auto t_c) {
+    constexpr int T = decltype(t_c)::value;
+    hipLaunchKernelGGL((topk_merge_kernel<T>), dim3((unsigned)rows), dim3(T), 0, s, part_val, part_idx, ranges * k, k, out_idx, out_val, flags);
     return hipGetLastError();
   };
-  if (ranges * k <= 1024) return go(std::integral_constant<int, 4>{});
-  if (ranges * k <= 2048) return go(std::integral_constant<int, 8>{});
-  return go(std::integral_constant<int, 16>{});
+  return ranges * k <= 1024 ? go(std::integral_constant<int, 256>{}) : go(std::integral_constant<int, 1024>{});
 }
 
 }  // namespace tq

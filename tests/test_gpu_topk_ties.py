@@ -72,6 +72,21 @@ def test_chunks_and_bars(kind, nq, n, topk):
         assert np.array_equal(tv[r].cpu().numpy(), s[r][want])
 
 
+@pytest.mark.parametrize("nq,n", [(2, 63), (2, 4096), (2, 4097), (2, 8193),  # fewer than k; a segment of 256 threads, of 512, of 1024
+                                  (2, 3 * 16384), (2, 3 * 16384 + 1), (513, 20001)])  # three segments, chunks from there, more rows than workgroups fit
+@pytest.mark.parametrize("topk", [16, 64])  # bars from 64 maxima, from 256
+@pytest.mark.parametrize("kind", ["drawn", "falling", "equal", "zeros", "infinite"])
+def test_segments_and_threads(kind, nq, n, topk):
+    p, c = case(kind, n)
+    scores, (ti, tv), _ = call(p, T.dev(W.gaussian_queries(nq, 128, 5, unit=False)), c, n, topk, nq)
+    s = scores.cpu().numpy()
+    for r in range(0, nq, max(1, nq // 3)):
+        want = np.argsort(-s[r], kind="stable")[:topk]
+        k = len(want)
+        assert np.array_equal(ti[r, :k].cpu().numpy(), want) and (ti[r, k:] == -1).all()
+        assert np.array_equal(tv[r, :k].cpu().numpy().view(np.int32), s[r][want].view(np.int32))  # the sign of a zero, too
+
+
 @pytest.mark.parametrize("nq", [2, 129])  # a segment per workgroup, seven
 @pytest.mark.parametrize("kind", ["rising", "equal", "ties at the end", "steps"])
 def test_their_cost_is_bounded(kind, nq):
