@@ -15,7 +15,7 @@
 // which skip blocks of queries without a flag.
 //
 // 1000 queries, 10^6 codes, k = 10, d = 1536, 4 bits: 3.2 ms, 9.5 with every score from the exact kernel; 3.07 of it are
-// the find kernel's.  500 queries, 30000 codes, k = 64, d = 512: 136 us (284 with 4096 codes in the sample: the gathering
+// the find kernel's.  500 queries, 30000 codes, k = 64, d = 512: 119 us (284 with 4096 codes in the sample: the gathering
 // overflowed).
 #include <algorithm>
 #include <cmath>
@@ -112,8 +112,9 @@ struct SelectArgs {
   Codebook cb;
 };
 
-template <int BITS, bool PROD>
-__global__ __launch_bounds__(256) void search_select_kernel(const SelectArgs a) {
+// grid nq, T threads
+template <int BITS, bool PROD, int T>
+__global__ __launch_bounds__(T) void search_select_kernel(const SelectArgs a) {
   constexpr int SEGS = (BITS > 0 ? 1 : 0) + (PROD ? 1 : 0);
   constexpr int NB = BITS > 0 ? BITS : 1;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
@@ -139,7 +140,7 @@ __global__ __launch_bounds__(256) void search_select_kernel(const SelectArgs a) 
   }
   if (tid == 0) n_s = 0;
   // the query's pieces, as the scoring kernel stages them
-  for (int e = tid; e < d / 4; e += 256) {
+  for (int e = tid; e < d / 4; e += T) {
     int seg = 0;
 #pragma unroll
     for (int m = 0; m < 2; ++m) {
@@ -154,7 +155,7 @@ __global__ __launch_bounds__(256) void search_select_kernel(const SelectArgs a) 
     }
   }
   // candidates: score + eps from the list, eps again from the code's scalars
-  constexpr int N = CAP / 256;
+  constexpr int N = CAP / T;
   const float e1 = a.e1[q], e2 = a.e2[q];
   float mx = -__builtin_inff();
   float top[N];
@@ -162,13 +163,13 @@ __global__ __launch_bounds__(256) void search_select_kernel(const SelectArgs a) 
   for (int i0 = 0; i0 < N; i0 += 4) {
 #pragma unroll
     for (int i = i0; i < i0 + 4; ++i) top[i] = __builtin_nanf("");
-    if (i0 * 256 >= total) continue;  // uniform
+    if (i0 * T >= total) continue;  // uniform
     // (four of a thread's at a time: one by one they are two trips to memory each)
     int64_t row[4];
     float nu[4], ga[4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      const int c = (i0 + i) * 256 + tid, cc = c < total ? c : total - 1;
+      const int c = (i0 + i) * T + tid, cc = c < total ? c : total - 1;
       row[i] = a.list_i[q * CAP + cc];
       top[i0 + i] = a.list_u[q * CAP + cc];
     }
@@ -181,25 +182,25 @@ __global__ __launch_bounds__(256) void search_select_kernel(const SelectArgs a) 
     for (int i = 0; i < 4; ++i) {
       float eps = fabsf(nu[i]) * e1;
       if (PROD) eps = fmaf(fabsf(nu[i] * (a.kappa * ga[i])), e2, eps);
-      if ((i0 + i) * 256 + tid >= total) top[i0 + i] = __builtin_nanf("");
+      if ((i0 + i) * T + tid >= total) top[i0 + i] = __builtin_nanf("");
       mx = fmaxf(mx, fmaf(-2.f, eps, top[i0 + i]));
     }
   }
-  const float bar = kth_of_maxima<256>(mx, k, keys, &bar_s, tid);
+  const float bar = kth_of_maxima<T>(mx, k, keys, &bar_s, tid);
   uint32_t pass = 0u;
 #pragma unroll
   for (int i = N - 1; i >= 0; --i) pass = pass + pass + (top[i] >= bar ? 1u : 0u);
   while (pass != 0u) {
     const int i = __builtin_ctz(pass);
     pass &= pass - 1u;
-    cand[atomicAdd(&n_s, 1)] = a.list_i[q * CAP + i * 256 + tid];
+    cand[atomicAdd(&n_s, 1)] = a.list_i[q * CAP + i * T + tid];
   }
   __syncthreads();
   const int n = n_s;
 
   // scores as tq_score_bf3.hip makes them: 32 candidates of a wavefront are the columns, every row is the query
   const int gw = d >> 5, h = lane >> 5;
-  for (int b = wave; b * 32 < n; b += 4) {
+  for (int b = wave; b * 32 < n; b += T / 64) {
     const int s = b * 32 + (lane & 31);
     const int64_t row = cand[s < n ? s : n - 1];
     const uint32_t* const wi = a.idx + row * ((int64_t)gw * BITS);
@@ -283,26 +284,13 @@ __global__ __launch_bounds__(256) void search_select_kernel(const SelectArgs a) 
     if (h == 0 && s < n) score[s] = nu * fmaf(kg, PROD ? acc2[0] : 0.f, c1 * acc1[0]);
   }
   __syncthreads();
-  for (int c = tid; c < n; c += 256) {
-    const float cv = score[c];
-    const int ci = cand[c];
-    int rank = cv == cv ? 0 : k;  // a NaN is not returned
-#pragma unroll 4
-    for (int o = 0; o < n; ++o) rank += better(score[o], cand[o], cv, ci) ? 1 : 0;
-    if (rank < k) {
-      a.out_idx[q * k + rank] = ci;
-      if (a.out_val != nullptr) a.out_val[q * k + rank] = cv;
-    }
-  }
-  // fewer candidates than wanted: the rest of the list says so (NaN scores leave gaps only behind real ones)
-  if (n < k) {
-    int real = 0;
-    for (int o = 0; o < n; ++o) real += score[o] == score[o] ? 1 : 0;
-    if (tid >= real && tid < k) {
-      a.out_idx[q * k + tid] = -1;
-      if (a.out_val != nullptr) a.out_val[q * k + tid] = -__builtin_inff();
-    }
-  }
+  // the k best of them, in the place of the query's pieces; a NaN is not returned
+  TopkLds<T, N>& best = *reinterpret_cast<TopkLds<T, N>*>(qp);
+  float v[N];
+#pragma unroll
+  for (int i = 0; i < N; ++i) v[i] = i * T + tid < n ? score[i * T + tid] : __builtin_nanf("");
+  const int kept = take_segment<T, N>(best, v, [&](int i) { return cand[i * T + tid]; }, k, 0, tid, n <= 64);
+  write_best(best, kept, k, -1, a.out_idx + q * k, a.out_val != nullptr ? a.out_val + q * k : nullptr, tid);
 }
 
 size_t align256(size_t v) { return (v + 255) / 256 * 256; }
@@ -353,14 +341,22 @@ int64_t block_queries(int d, int64_t n, int64_t nq, int topk) {
   return std::min(most, ((nq + blocks - 1) / blocks + 127) / 128 * 128);
 }
 
+template <int BITS, bool PROD, int T>
+hipError_t launch_select_t(const SelectArgs& a, int nq, hipStream_t s) {
+  const int pieces = ((BITS > 0 ? 1 : 0) + (PROD ? 1 : 0)) * 2 * a.d * 2, lds = CAP * 8 + std::max(pieces, (int)sizeof(TopkLds<T, CAP / T>));
+  static LdsLimit lds_limit;  // per instantiation: the limit is raised once per device
+  if (const hipError_t e = raise_lds_limit(lds_limit, reinterpret_cast<const void*>(&search_select_kernel<BITS, PROD, T>), 80 * 1024); e != hipSuccess)
+    return e;
+  hipLaunchKernelGGL((search_select_kernel<BITS, PROD, T>), dim3((unsigned)nq), dim3(T), lds, s, a);
+  return hipGetLastError();
+}
+
 template <int BITS, bool PROD>
 hipError_t launch_select(const SelectArgs& a, int nq, hipStream_t s) {
-  const int lds = CAP * 8 + ((BITS > 0 ? 1 : 0) + (PROD ? 1 : 0)) * 2 * a.d * 2;
-  static LdsLimit lds_limit;  // per instantiation: the limit is raised once per device
-  if (const hipError_t e = raise_lds_limit(lds_limit, reinterpret_cast<const void*>(&search_select_kernel<BITS, PROD>), 80 * 1024); e != hipSuccess)
-    return e;
-  hipLaunchKernelGGL((search_select_kernel<BITS, PROD>), dim3((unsigned)nq), dim3(256), lds, s, a);
-  return hipGetLastError();
+  // Eight wavefronts per query where a compute unit has no other (us, 4 / 8 / 16 of them: 44 queries of 1536, 1 bit, k = 64, 24 / 15.0 / 14.7;
+  // 200 of 768, 4 bits, k = 10, 17.0 / 14.9 / 19.3); long codes, whose decoding they would be in each other's way for, keep four (39 of
+  // 3072, 3 + 1 bits, k = 64: 54 / 65 / 66, 48 now).
+  return nq <= device_cu_count() && a.d <= 2048 ? launch_select_t<BITS, PROD, 512>(a, nq, s) : launch_select_t<BITS, PROD, 256>(a, nq, s);
 }
 
 hipError_t launch_block(const SearchArgs& a, const Codebook& cb, char* base, int32_t* flags, hipStream_t s) {

@@ -69,4 +69,129 @@ __device__ __forceinline__ float kth_of_maxima(float mx, int k, uint32_t* keys, 
   return from_ordered(*bar);
 }
 
+// more than this many are not ranked against each other as they are (two rows of 50001 equal scores, whole segments ranked:
+// 144 ms)
+constexpr int MANY = 512;
+
+// a pair as an integer: larger ones come first.  Equal scores by index; zeros are equal, the sign of one in the lowest bit.
+typedef unsigned long long pair;
+__device__ __forceinline__ pair make_pair(float v, int i) {
+  return (pair)ordered(v + 0.f) << 32 | (uint32_t)(0x7fffffff - i) << 1 | (v == 0.f ? __float_as_uint(v) >> 31 : 0u);
+}
+__device__ __forceinline__ int pair_index(pair p) { return 0x7fffffff - (int)((uint32_t)p >> 1); }
+__device__ __forceinline__ float pair_score(pair p) {
+  const float v = from_ordered((uint32_t)(p >> 32));
+  return v == 0.f ? __uint_as_float((uint32_t)p << 31) : v;
+}
+
+// N scores per thread of T
+template <int T, int N>
+struct TopkLds {
+  static constexpr int LIST = 64 + 64 * N * (T / 256) > MANY ? 64 + 64 * N * (T / 256) : MANY;  // the k best so far, and all that k groups of T / 256 threads hold
+  pair list[LIST];
+  pair best[64];
+  pair groups[256];
+  pair pair_bar;
+  __attribute__((aligned(16))) uint32_t mx[256];
+  uint32_t bar;
+  int count;
+};
+
+// v[e]: this thread's scores of one segment, NaN where there is none; index_of(e): the e-th one's index.  kept: pairs in best so far
+// (uniform).  Afterwards best holds the k best of all segments up to this one, and the number of them is returned.  few: so few scores in all
+// that a bar costs more than it saves.
+template <int T, int N, class Index>
+__device__ int take_segment(TopkLds<T, N>& s, const float (&v)[N], Index index_of, int k, int kept, int tid, bool few = false) {
+  constexpr int LIST = TopkLds<T, N>::LIST;
+  float bar;
+  if (tid == 0) s.count = kept;
+  if (few) {  // uniform
+    bar = -__builtin_inff();
+    __syncthreads();
+  } else if (kept < k) {
+    float mx = -__builtin_inff();
+#pragma unroll
+    for (int e = 0; e < N; ++e) mx = fmaxf(mx, v[e]);  // ignores NaN
+    bar = kth_of_maxima<T>(mx, k, s.mx, &s.bar, tid);
+  } else {
+    // the next larger value: an equal score of a later segment has a later index and does not beat a kept one
+    bar = from_ordered((uint32_t)(s.best[k - 1] >> 32) + 1u);
+    __syncthreads();
+  }
+  if (tid < kept) s.list[tid] = s.best[tid];
+  // a wavefront's places are asked for together; most of its elements pass in no lane
+  uint64_t pass[N];
+  int passed = 0;
+#pragma unroll
+  for (int e = 0; e < N; ++e) {
+    pass[e] = __builtin_amdgcn_ballot_w64(v[e] >= bar);
+    passed += __builtin_popcountll(pass[e]);
+  }
+  if (passed != 0) {  // uniform
+    int at = 0;
+    if ((tid & 63) == 0) at = atomicAdd(&s.count, passed);
+    at = __builtin_amdgcn_readfirstlane(at);
+#pragma unroll
+    for (int e = 0; e < N; ++e) {
+      if (pass[e] == 0u) continue;
+      const int pos = at + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(pass[e] >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)pass[e], 0u));
+      if (v[e] >= bar && pos < LIST) s.list[pos] = make_pair(v[e], index_of(e));
+      at += __builtin_popcountll(pass[e]);
+    }
+  }
+  __syncthreads();
+  int n = s.count;
+  if (n > MANY) {  // uniform
+    pair key = 0;
+#pragma unroll
+    for (int e = 0; e < N; ++e)
+      if (v[e] >= bar) {
+        const pair o = make_pair(v[e], index_of(e));
+        key = o > key ? o : key;
+      }
+    if (tid < 256) s.groups[tid] = 0;
+    if (tid == 0) s.pair_bar = ~pair(0);
+    __syncthreads();  // everyone has read the count, too
+    atomicMax(&s.groups[tid / (T / 256)], key);
+    if (tid == 0) s.count = kept;
+    __syncthreads();
+    if (tid < 256) {
+      const pair own = s.groups[tid];
+      int above = 0;
+#pragma unroll 4
+      for (int t = 0; t < 256; ++t) above += s.groups[t] > own ? 1 : 0;
+      if (above < k) atomicMin(&s.pair_bar, own);
+    }
+    __syncthreads();
+    const pair pair_bar = s.pair_bar;
+    if (key >= pair_bar && key != 0)
+#pragma unroll
+      for (int e = 0; e < N; ++e)
+        if (v[e] >= bar)
+          if (const pair o = make_pair(v[e], index_of(e)); o >= pair_bar) s.list[atomicAdd(&s.count, 1)] = o;  // below LIST: at most k groups come here with any
+    __syncthreads();
+    n = s.count;
+  }
+  if (n == kept) return kept;  // uniform; nothing passed
+  const int lanes = n * 16 <= T ? 16 : n * 8 <= T ? 8 : n * 4 <= T ? 4 : n * 2 <= T ? 2 : 1;  // that share a pair's comparisons
+  for (int c = tid / lanes; c < n; c += T / lanes) {  // one round, or one lane each
+    const pair own = s.list[c];
+    int rank = 0;
+#pragma unroll 4
+    for (int o = tid & (lanes - 1); o < n; o += lanes) rank += s.list[o] > own ? 1 : 0;
+    rank = sum_of_lanes(rank, lanes);
+    if (rank < k) s.best[rank] = own;  // the lanes of a pair write the same
+  }
+  __syncthreads();
+  return n < k ? n : k;
+}
+
+template <int T, int N>
+__device__ __forceinline__ void write_best(const TopkLds<T, N>& s, int kept, int k, int none, int32_t* out_idx, float* out_val, int tid) {
+  if (tid < k) {
+    out_idx[tid] = tid < kept ? pair_index(s.best[tid]) : none;
+    if (out_val != nullptr) out_val[tid] = tid < kept ? pair_score(s.best[tid]) : -__builtin_inff();
+  }
+}
+
 }  // namespace tq

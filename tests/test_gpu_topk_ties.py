@@ -122,3 +122,12 @@ def test_search_with_scalars_of_both_signs(d, bits, prod):
         if c[name] is not None:
             c[name] = c[name] * T.dev(rng.choice(np.float32([-1, 1]), size=n))
     T._topk_both_ways(p, q, 1, nq, c, n, 10)
+
+
+@pytest.mark.parametrize("d,nq", [(128, 256), (128, 257), (2048, 40), (2176, 40)])  # eight wavefronts per query, four; eight; four
+@pytest.mark.parametrize("topk", [1, 64])
+def test_selection_from_the_candidates(d, nq, topk):
+    n = 9000
+    p = T.setup(d, 2, True)[0]
+    q = T.dev(W.gaussian_queries(nq, d, 9, unit=False))
+    T._topk_both_ways(p, q, 1, nq, T._random_codes(p, d, 2, True, n, 4), n, topk)
