@@ -136,9 +136,12 @@ __global__ __launch_bounds__(256) void q128_image_kernel(const float* Pi, const 
 // vectors, 4 bits: 28.3 -> 25.3 us; two instances of 2 + 3 bits: 20.6 -> 18.9)
 constexpr int q128_per_cu(bool prod, bool f32) { return !prod && !f32 ? 2 : 1; }
 
-template <int BITS, bool PROD, bool MIXED, int VT, bool F32 = false>
+// EVEN (two instances with a sketch): of two coordinate groups each.  S Pi^T is block diagonal then, and a half of the output coordinates
+// meets half of the residual's: 48 matrix instructions in place of 96 (131072 vectors, 2 + 1 and 1 + 1 bits 25.2 -> 22.3 us, 524288 86 -> 75).
+template <int BITS, bool PROD, bool MIXED, int VT, bool F32 = false, bool EVEN = false>
 __global__ __launch_bounds__(512 / VT, q128_per_cu(PROD, F32) * 2 / VT) void quant128_bf3_kernel(const Q128Args a) {
   constexpr int NT = 512 / VT;  // threads
+  static_assert(!EVEN || (MIXED && PROD && VT == 1), "");
   // A operands in flight: six where the registers are there (131072 vectors, bf16, 2 + 1 bits 24.3 -> 23.8 us; fp32 30.9 -> 34.4)
   constexpr int RING = PROD && !F32 ? 6 : 4;
   constexpr int NB = (BITS > 0 ? BITS : 1) + (MIXED ? 1 : 0);  // plane words per tile, at most
@@ -449,26 +452,28 @@ __global__ __launch_bounds__(512 / VT, q128_per_cu(PROD, F32) * 2 / VT) void qua
       for (int pass = 0; pass < 2; ++pass) {
         floatx16 u[VT][2];
         {
-          auto w_piece = [&](int i) {  // read i of 32: step i / 4, pieces 1, 0, tile i % 2
+          constexpr int READS = EVEN ? 16 : 32;
+          const int s0 = EVEN ? 4 * pass : 0;
+          auto w_piece = [&](int i) {  // read i: step s0 + i / 4, pieces 1, 0, tile i % 2
             return *reinterpret_cast<const f16x8*>(W_s + (1 - ((i >> 1) & 1)) * MAT_ELEMS +
-                                                    q128_at(64 * pass + 32 * (i & 1) + vi, 16 * (i >> 2) + 8 * g));
+                                                    q128_at(64 * pass + 32 * (i & 1) + vi, 16 * (s0 + (i >> 2)) + 8 * g));
           };
           f16x8 ring[RING];
 #pragma unroll
           for (int i = 0; i < RING; ++i) ring[i] = w_piece(i);
 #pragma unroll
-          for (int i = 0; i < 32; ++i) {
-            const int s = i >> 2, pa = 1 - ((i >> 1) & 1), mt = i & 1;
+          for (int i = 0; i < READS; ++i) {
+            const int s = s0 + (i >> 2), pa = 1 - ((i >> 1) & 1), mt = i & 1;
 #pragma unroll
             for (int pb = 1 - pa; pb >= 0; --pb)
 #pragma unroll
               for (int nt = 0; nt < VT; ++nt)
                 u[nt][mt] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ring[i % RING], *reinterpret_cast<const f16x8*>(&rp[pb][nt][s]),
                                                                    i < 2 ? zero16 : u[nt][mt], 0, 0, 0);
-            if (i + RING < 32) ring[i % RING] = w_piece(i + RING);
-            // the next block's vectors: all sixteen loads during the first pass
-            if (pass == 0 && (i & 1) && (VT == 2 || !(i & 2)))
-              load_x(next_x[(i >> 1) & 1], (i >> 1) & HI, s);
+            if (i + RING < READS) ring[i % RING] = w_piece(i + RING);
+            // the next block's vectors: all sixteen (eight) loads during the first pass
+            if (EVEN ? pass == 0 && (i & 1) : pass == 0 && (i & 1) && (VT == 2 || !(i & 2)))
+              load_x(next_x[EVEN ? 0 : (i >> 1) & 1], EVEN ? 0 : (i >> 1) & HI, EVEN ? i >> 1 : s);
             __builtin_amdgcn_sched_barrier(0);
           }
         }
@@ -509,13 +514,13 @@ __global__ __launch_bounds__(512 / VT, q128_per_cu(PROD, F32) * 2 / VT) void qua
   }
 }
 
-template <int BITS, bool PROD, bool MIXED, int VT, bool F32>
+template <int BITS, bool PROD, bool MIXED, int VT, bool F32, bool EVEN = false>
 hipError_t launch_vt(const Q128Args& a, hipStream_t s) {
   constexpr int lds = (PI_ELEMS + (PROD ? W_ELEMS : 0)) * 2;
   static LdsLimit lds_limit;  // per instantiation: the limit is raised once per device
-  if (const hipError_t e = raise_lds_limit(lds_limit, reinterpret_cast<const void*>(&quant128_bf3_kernel<BITS, PROD, MIXED, VT, F32>), lds); e != hipSuccess) return e;
+  if (const hipError_t e = raise_lds_limit(lds_limit, reinterpret_cast<const void*>(&quant128_bf3_kernel<BITS, PROD, MIXED, VT, F32, EVEN>), lds); e != hipSuccess) return e;
   const int64_t blocks = (a.n + 255) / 256, most = device_cu_count() * q128_per_cu(PROD, F32);
-  hipLaunchKernelGGL((quant128_bf3_kernel<BITS, PROD, MIXED, VT, F32>), dim3((unsigned)(blocks < most ? blocks : most)), dim3(512 / VT), lds, s, a);
+  hipLaunchKernelGGL((quant128_bf3_kernel<BITS, PROD, MIXED, VT, F32, EVEN>), dim3((unsigned)(blocks < most ? blocks : most)), dim3(512 / VT), lds, s, a);
   return hipGetLastError();
 }
 
@@ -525,6 +530,9 @@ template <int BITS, bool PROD, bool MIXED>
 hipError_t launch_one(const Q128Args& a, bool f32, hipStream_t s) {
   if constexpr (!MIXED) {
     if (f32) return launch_vt<BITS, PROD, MIXED, 1, true>(a, s);
+  }
+  if constexpr (MIXED && PROD) {
+    if (a.gs_hi == 2) return launch_vt<BITS, PROD, MIXED, 1, false, true>(a, s);
   }
   return launch_vt<BITS, PROD, MIXED, 1, false>(a, s);
 }

@@ -9,7 +9,8 @@
 // rotated coordinates).  The fp32 instructions (tq_d128_small.hip) spend 2048 cycles of a SIMD per contraction of 16 vectors,
 // these 256 and 384.  bf16 vectors, 2 + 1 bits, us a call:
 // 8 vectors 6.7 -> 3.8, 4096 7.5 -> 4.5, 8192 10.4 -> 6.0, 16384 11.6 -> 8.2 (there against the large-batch kernel); 64 channels at 2 + 1
-// and 64 at 1 + 1 bits, 4936 10.6 -> 6.2; 4 bits, 512 5.0 -> 3.6.  What is left is mostly the launch and two round trips.
+// and 64 at 1 + 1 bits, 4936 10.6 -> 6.2,
+// 5.6 without the zero blocks of S Pi^T; 4 bits, 512 5.0 -> 3.6.  What is left is mostly the launch and two round trips.
 // Against 64-bit arithmetic, no further off than the fp32 instructions, whose sums meet more roundings (pieces / fp32): of 7.9e8
 // coordinates at 4 bits 224 / 320 on the other side of a boundary; signs at 2 + 1 bits 0.13 / 0.16 of 10^6, gamma 0.65 - 0.69e-7 / 0.73 - 0.82e-7.
 //
@@ -56,8 +57,11 @@ __device__ __forceinline__ floatx4 settled(floatx4 v) {
 
 constexpr int ROW_LD = 136;  // fp16 values per row in LDS: consecutive rows start 16 bytes further on in the banks
 
-template <int BITS, bool PROD, bool MIXED>
+// STEPS: k-steps of 32 coordinates that the sketch of a coordinate group meets.  4, or fewer for two instances (MIXED), whose S Pi^T is
+// block diagonal: as many as the larger instance has, the other instance's blocks are not fetched.
+template <int BITS, bool PROD, int STEPS>
 __global__ __launch_bounds__(512, 4) void q128_few_kernel(const QuantFewArgs a) {
+  constexpr bool MIXED = STEPS < 4;
   if (!MIXED) fetch_arguments<sizeof(QuantFewArgs)>();
   __shared__ __attribute__((aligned(16))) unsigned short x_s[2][16 * ROW_LD];              // by parity of the block
   __shared__ __attribute__((aligned(16))) unsigned short e_s[PROD ? 2 : 1][PROD ? 16 * ROW_LD : 8];  // pieces of the residual, columns permuted
@@ -85,7 +89,8 @@ __global__ __launch_bounds__(512, 4) void q128_few_kernel(const QuantFewArgs a) 
   };
   uint2 raw = load_x(blockIdx.x);
 
-  u32x4 pw[2][4], sw[2][4];  // [piece][step]
+  u32x4 pw[2][4], sw[2][4];  // [piece][step]; of sw the STEPS from s0 on
+  const int s0 = hi ? 0 : 4 - STEPS;
   float pi_inv;
   if (a.image != nullptr) {
     pi_inv = *reinterpret_cast<const float*>(a.image + PI_ELEMS + W_ELEMS);
@@ -96,8 +101,8 @@ __global__ __launch_bounds__(512, 4) void q128_few_kernel(const QuantFewArgs a) 
 #pragma unroll
         for (int p = 0; p < 2; ++p)
 #pragma unroll
-          for (int s = 0; s < 4; ++s)
-            (m == 0 ? pw : sw)[p][s] = *reinterpret_cast<const u32x4*>(row + (2 * m + p) * MAT_ELEMS + (((4 * s + kq) ^ col) << 3));
+          for (int s = 0; s < (m == 0 ? 4 : STEPS); ++s)
+            (m == 0 ? pw : sw)[p][s] = *reinterpret_cast<const u32x4*>(row + (2 * m + p) * MAT_ELEMS + (((4 * (m == 0 ? s : s0 + s) + kq) ^ col) << 3));
   } else {
     if (tid == 0) max_s = 0u;
     __syncthreads();
@@ -111,7 +116,7 @@ __global__ __launch_bounds__(512, 4) void q128_few_kernel(const QuantFewArgs a) 
       for (int s = 0; s < 4; ++s)
 #pragma unroll
         for (int g = 0; g < 2; ++g) {
-          const int at = 32 * s + 8 * kq + 4 * g;
+          const int at = 32 * (m == 0 || s >= STEPS ? s : s0 + s) + 8 * kq + 4 * g;
           v[s][g] = *reinterpret_cast<const f32x4*>(row + (m == 0 ? at : q128_w_col(at)));
         }
       float sc = pi_scale;
@@ -289,8 +294,8 @@ __global__ __launch_bounds__(512, 4) void q128_few_kernel(const QuantFewArgs a) 
     if (!own) continue;
     floatx4 u = {0.f, 0.f, 0.f, 0.f}, ul = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int s = 0; s < 4; ++s) {
-      const int at = col * ROW_LD + 32 * s + 8 * kq;
+    for (int s = 0; s < STEPS; ++s) {
+      const int at = col * ROW_LD + 32 * (s0 + s) + 8 * kq;
       const f16x8 eh = *reinterpret_cast<const f16x8*>(&e_s[0][at]), el = *reinterpret_cast<const f16x8*>(&e_s[PROD ? 1 : 0][at]);
       ul = __builtin_amdgcn_mfma_f32_16x16x32_f16(f16(sw[1][s]), eh, ul, 0, 0, 0);
       ul = __builtin_amdgcn_mfma_f32_16x16x32_f16(f16(sw[0][s]), el, ul, 0, 0, 0);
@@ -318,23 +323,26 @@ __global__ __launch_bounds__(512, 4) void q128_few_kernel(const QuantFewArgs a) 
   }
 }
 
-template <int BITS, bool PROD, bool MIXED>
+template <int BITS, bool PROD, int STEPS>
 hipError_t launch_few(const QuantFewArgs& a, hipStream_t s) {
   const int64_t blocks = (a.n + 15) / 16, cu = device_cu_count();
   int share = 1;  // workgroups per block
   while (share < 8 && blocks * share * 2 <= cu) share *= 2;
   const dim3 grid((unsigned)(blocks < 2 * cu ? blocks : 2 * cu), share);
-  hipLaunchKernelGGL((q128_few_kernel<BITS, PROD, MIXED>), grid, dim3(512), 0, s, a);
+  hipLaunchKernelGGL((q128_few_kernel<BITS, PROD, STEPS>), grid, dim3(512), 0, s, a);
   return hipGetLastError();
 }
 
 template <int BITS>
 hipError_t launch_bits(const QuantFewArgs& a, bool prod, hipStream_t s) {
   if (a.gs_hi > 0) {
-    if constexpr (BITS < 4) return prod ? launch_few<BITS, true, true>(a, s) : launch_few<BITS, false, true>(a, s);
+    if constexpr (BITS < 4) {
+      if (!prod) return launch_few<BITS, false, 3>(a, s);
+      return a.gs_hi == 2 ? launch_few<BITS, true, 2>(a, s) : launch_few<BITS, true, 3>(a, s);
+    }
     return hipErrorInvalidValue;
   }
-  return prod ? launch_few<BITS, true, false>(a, s) : launch_few<BITS, false, false>(a, s);
+  return prod ? launch_few<BITS, true, 4>(a, s) : launch_few<BITS, false, 4>(a, s);
 }
 
 }  // namespace

@@ -98,6 +98,32 @@ def test_quantize_split(d_hi, bits_lo, prod, n, bf16):
             P.check_signs(z_part, u_or, s_norm[None, :] * gamma_or[:, None])
 
 
+@pytest.mark.parametrize("images", [True, False])
+@pytest.mark.parametrize("n", [17, 16385])  # the kernel for few vectors, the one for many
+@pytest.mark.parametrize("d_hi", [32, 64, 96])
+def test_an_instance_alone_decides_its_signs(d_hi, n, images):
+    """The sketch of an instance meets its own residual and no other: the other instance's channels changed, its signs and norms stay."""
+    hi_ch, _, _, p = instances(d_hi, 1, True)
+    if not images:
+        p.drop_images()
+    hi, lo = o.split_channels(D, hi_ch)
+    _, x = keys(n, hi_ch, bf16=True)
+    out = []
+    for other in (None, hi, lo):
+        y = x.clone()
+        if other is not None:
+            y[:, torch.from_numpy(other).to(DEV)] *= -0.75  # (not larger, so that the vector's power of two stays)
+        c = [torch.zeros((n, w), dtype=t, device=DEV) for w, t in ((p.idx_words, torch.int32), (p.qjl_words, torch.int32), (2, torch.float32), (2, torch.float32))]
+        tq.tq_quantize_prod(p, y, *c)
+        out.append(c)
+    gs = d_hi // 32
+    base, hi_changed, lo_changed = out
+    assert torch.equal(base[1][:, gs:], hi_changed[1][:, gs:]) and not torch.equal(base[1][:, :gs], hi_changed[1][:, :gs])
+    assert torch.equal(base[1][:, :gs], lo_changed[1][:, :gs]) and not torch.equal(base[1][:, gs:], lo_changed[1][:, gs:])
+    for j in (2, 3):  # residual norms, norms
+        assert torch.allclose(base[j][:, 1], hi_changed[j][:, 1], rtol=1e-6, atol=0) and torch.allclose(base[j][:, 0], lo_changed[j][:, 0], rtol=1e-6, atol=0)
+
+
 @pytest.mark.parametrize("d_hi,bits_lo,prod", [(32, 2, True), (64, 1, False)])
 def test_append_split_equals_the_dense_call(d_hi, bits_lo, prod):
     """tq_append with two instances: rows scattered into a larger cache hold exactly what the dense quantiser
