@@ -1186,7 +1186,11 @@ tq_status tq_attend_cache(const tq_params* pk, const tq_params* pv, const float*
     a.scores = scores; a.lds = pl.ld_scores;
     a.idx = v_idx; a.qjl = v_qjl; a.gamma = v_gamma; a.norm = v_norm;
     a.part = part; a.nchunks = pl.nchunks; a.tiles = pl.tiles; a.n = n_per_group; a.group_stride = group_stride; a.d = pv->d; a.q_per_group = q_per_group;
-    a.scale = scale; a.cb = make_codebook(pv); a.gs_hi = pv->d_hi / 32; a.cb_hi = make_codebook_hi(pv);
+    a.scale = scale; a.gs_hi = pv->d_hi / 32;
+    const AttendTables tables = {make_codebook(pv), make_codebook_hi(pv)};
+    // a single chunk is rotated back by the workgroup that has summed it
+    const bool whole = pl.fast && pl.nchunks == 1 && pl.tiles == AT_TILES_SHORT;
+    a.out = whole ? out : nullptr; a.ldo = ldo; a.Pi = pv->Pi; a.S = v_prod ? pv->S : nullptr; a.kappa = kappa_of(pv->d);
     // keys the single-kernel d = 128 scoring path takes are scored inside the read-out kernel
     const bool k_prod = k_qjl != nullptr;
     ScoreI8Args ka;
@@ -1194,7 +1198,7 @@ tq_status tq_attend_cache(const tq_params* pk, const tq_params* pv, const float*
                        score128_args(pk->bits_mse, k_prod, pk->PiT, pk->ST, q, ldq, k_idx, k_qjl, k_gamma, k_norm,
                                      n_per_group, n_groups, q_per_group, kappa_of(128), make_codebook(pk), group_stride, &ka);
     if (fused) {
-      if (launch_attend128(pk->bits_mse, k_prod, &ka, v_prod, a, n_groups, s) != hipSuccess) return TQ_ERR_HIP;
+      if (launch_attend128(pk->bits_mse, k_prod, &ka, v_prod, a, tables, n_groups, s) != hipSuccess) return TQ_ERR_HIP;
     } else {
       // tq_score knows densely stored groups only
       if (group_stride != n_per_group) return TQ_ERR_UNSUPPORTED;
@@ -1204,10 +1208,11 @@ tq_status tq_attend_cache(const tq_params* pk, const tq_params* pv, const float*
       st = tq_score(&pk_inner, q, ldq, n_groups, q_per_group, k_idx, k_qjl, k_gamma, k_norm, n_per_group, scores,
                     pl.ld_scores, 0, nullptr, nullptr, stream);
       if (st != TQ_OK) return st;
-      if ((pl.fast ? launch_attend128(0, false, nullptr, v_prod, a, n_groups, s) : launch_attend_values(v_prod, a, n_groups, s)) !=
+      if ((pl.fast ? launch_attend128(0, false, nullptr, v_prod, a, tables, n_groups, s) : launch_attend_values(v_prod, a, tables.cb, n_groups, s)) !=
           hipSuccess)
         return TQ_ERR_HIP;
     }
+    if (whole) return TQ_OK;
   }
   return from_hip(launch_attend_combine(part, pl.nchunks, pv->d, nq, pv->Pi, v_prod ? pv->S : nullptr,
                                         kappa_of(pv->d), out, ldo, s));

@@ -24,8 +24,17 @@ struct AttendArgs {
   int d;
   int q_per_group;
   float scale;
-  Codebook cb;          // of the value codes (two instances: of instance lo)
   int gs_hi;            // two instances: coordinate groups of instance hi (0: one instance); norm is [n][2] then
+  // d = 128 kernel, one short chunk: the output itself, rotated back (nullptr: partial results to `part`, for launch_attend_combine)
+  float* out;
+  int64_t ldo;
+  const float* Pi;
+  const float* S;
+  float kappa;
+};
+// the tables of the value codes (two instances: cb of instance lo); apart, since the d = 128 kernel has no use for them
+struct AttendTables {
+  Codebook cb;
   Codebook cb_hi;
 };
 
@@ -39,11 +48,11 @@ int attend128_tiles(int64_t n, int n_groups, int q_per_group);
 int attend128_max_chunks(int64_t n, int n_groups, int q_per_group);  // of any call with at most n keys per group
 bool attend128_applicable(int d, bool prod, const Codebook& cb, const Codebook* cb_hi);
 struct ScoreI8Args;
-hipError_t launch_attend128(int kb, bool kprod, const ScoreI8Args* ka, bool vprod, const AttendArgs& a, int n_groups,
+hipError_t launch_attend128(int kb, bool kprod, const ScoreI8Args* ka, bool vprod, const AttendArgs& a, const AttendTables& t, int n_groups,
                             hipStream_t s);
 
 int attend_simple_chunks(int64_t n);
-hipError_t launch_attend_values(bool prod, const AttendArgs& a, int n_groups, hipStream_t s);
+hipError_t launch_attend_values(bool prod, const AttendArgs& a, const Codebook& cb, int n_groups, hipStream_t s);
 hipError_t launch_attend_combine(const float* part, int nchunks, int d, int64_t nq, const float* Pi, const float* S,
                                  float kappa, float* out, int64_t ldo, hipStream_t s);
 

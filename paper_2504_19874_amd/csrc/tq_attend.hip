@@ -36,7 +36,7 @@ __device__ __forceinline__ float block_reduce(float v, bool take_max, float* red
 }
 
 template <bool PROD>
-__global__ __launch_bounds__(256) void attend_values_kernel(const AttendArgs a) {
+__global__ __launch_bounds__(256) void attend_values_kernel(const AttendArgs a, const Codebook cb) {
   __shared__ float w_s[4][SIMPLE_CHUNK];                                // exp(logit - m) * nu
   __shared__ float wg_s[PROD ? 4 : 1][PROD ? SIMPLE_CHUNK : 1];         // ... * gamma
   __shared__ float red_s[4];
@@ -46,7 +46,7 @@ __global__ __launch_bounds__(256) void attend_values_kernel(const AttendArgs a) 
   const int64_t key0 = (int64_t)chunk * SIMPLE_CHUNK;
   const int nk = (int)(a.n - key0 < SIMPLE_CHUNK ? a.n - key0 : SIMPLE_CHUNK);
   const int64_t row0 = (int64_t)group * a.group_stride + key0;
-  if (tid < 16) cent_s[tid] = a.cb.c[tid];
+  if (tid < 16) cent_s[tid] = cb.c[tid];
 
   float m[4], l[4];
 #pragma unroll
@@ -68,15 +68,15 @@ __global__ __launch_bounds__(256) void attend_values_kernel(const AttendArgs a) 
   }
   __syncthreads();
 
-  const int wpr = a.d / 32 * a.cb.bits, zpr = a.d / 32;
+  const int wpr = a.d / 32 * cb.bits, zpr = a.d / 32;
   const int64_t prow = ((int64_t)group * a.q_per_group + q0) * a.nchunks + chunk;  // + qi * nchunks
   for (int j = tid; j < a.d; j += 256) {
     const int g = j >> 5, bit = j & 31;
     float acc[4] = {0.f, 0.f, 0.f, 0.f}, accz[4] = {0.f, 0.f, 0.f, 0.f};
     for (int k = 0; k < nk; ++k) {
-      const uint32_t* words = a.idx + (row0 + k) * wpr + g * a.cb.bits;
+      const uint32_t* words = a.idx + (row0 + k) * wpr + g * cb.bits;
       int level = 0;
-      for (int p = 0; p < a.cb.bits; ++p) level |= (int)((words[p] >> bit) & 1u) << p;
+      for (int p = 0; p < cb.bits; ++p) level |= (int)((words[p] >> bit) & 1u) << p;
       const float c = cent_s[level];
       float z = 0.f;
       if (PROD) z = ((a.qjl[(row0 + k) * zpr + g] >> bit) & 1u) ? 1.f : -1.f;
@@ -271,13 +271,13 @@ __global__ __launch_bounds__(256) void attend_combine_kernel(const float* part, 
 
 int attend_simple_chunks(int64_t n) { return (int)((n + SIMPLE_CHUNK - 1) / SIMPLE_CHUNK); }
 
-hipError_t launch_attend_values(bool prod, const AttendArgs& a, int n_groups, hipStream_t s) {
+hipError_t launch_attend_values(bool prod, const AttendArgs& a, const Codebook& cb, int n_groups, hipStream_t s) {
   if (a.nchunks == 0 || n_groups == 0 || a.q_per_group == 0) return hipSuccess;
   const dim3 grid(a.nchunks, n_groups, (a.q_per_group + 3) / 4);
   if (prod)
-    hipLaunchKernelGGL(attend_values_kernel<true>, grid, dim3(256), 0, s, a);
+    hipLaunchKernelGGL(attend_values_kernel<true>, grid, dim3(256), 0, s, a, cb);
   else
-    hipLaunchKernelGGL(attend_values_kernel<false>, grid, dim3(256), 0, s, a);
+    hipLaunchKernelGGL(attend_values_kernel<false>, grid, dim3(256), 0, s, a, cb);
   return hipGetLastError();
 }
 

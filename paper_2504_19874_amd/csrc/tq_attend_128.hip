@@ -40,7 +40,7 @@ bool attend128_applicable(int d, bool prod, const Codebook& cb, const Codebook* 
 
 // ka == nullptr: logits from a.scores; otherwise the scoring body runs in the same kernel on key codes of
 // kb index bits (kprod: with the sign sketch)
-hipError_t launch_attend128(int kb, bool kprod, const ScoreI8Args* ka, bool vprod, const AttendArgs& a, int n_groups,
+hipError_t launch_attend128(int kb, bool kprod, const ScoreI8Args* ka, bool vprod, const AttendArgs& a, const AttendTables& t, int n_groups,
                             hipStream_t s) {
   if (a.nchunks == 0 || n_groups == 0 || a.q_per_group == 0) return hipSuccess;
   ScoreI8Args none;
@@ -49,24 +49,24 @@ hipError_t launch_attend128(int kb, bool kprod, const ScoreI8Args* ka, bool vpro
   if (ka == nullptr) kb = -1;
   AttendCoefs cf, cfh;
   std::memset(&cfh, 0, sizeof(cfh));
-  if (a.d != 128 || !coefficients(a.cb, &cf)) return hipErrorInvalidValue;
+  if (a.d != 128 || !coefficients(t.cb, &cf)) return hipErrorInvalidValue;
   if (a.gs_hi > 0) {
-    if (vprod || !coefficients(a.cb_hi, &cfh)) return hipErrorInvalidValue;
-    switch (a.cb.bits) {
+    if (vprod || !coefficients(t.cb_hi, &cfh)) return hipErrorInvalidValue;
+    switch (t.cb.bits) {
       case 1: return launch_attend128_s1(kb, kprod, k, a, cf, cfh, n_groups, s);
       case 2: return launch_attend128_s2(kb, kprod, k, a, cf, cfh, n_groups, s);
       default: return hipErrorInvalidValue;
     }
   }
   if (vprod) {
-    switch (a.cb.bits) {
+    switch (t.cb.bits) {
       case 0: return launch_attend128_p0(kb, kprod, k, a, cf, cfh, n_groups, s);
       case 1: return launch_attend128_p1(kb, kprod, k, a, cf, cfh, n_groups, s);
       case 2: return launch_attend128_p2(kb, kprod, k, a, cf, cfh, n_groups, s);
       default: return hipErrorInvalidValue;
     }
   }
-  switch (a.cb.bits) {
+  switch (t.cb.bits) {
     case 1: return launch_attend128_v1(kb, kprod, k, a, cf, cfh, n_groups, s);
     case 2: return launch_attend128_v2(kb, kprod, k, a, cf, cfh, n_groups, s);
     case 3: return launch_attend128_v3(kb, kprod, k, a, cf, cfh, n_groups, s);

@@ -118,7 +118,9 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 // VKIND, the kind of value code: 0 = Alg. 1; 1 = Alg. 2 (one more plane: the signs, with weights ... * gamma);
 // 2 = two instances of Alg. 1 over a split of the coordinates (Sec. 4.3): groups g < a.gs_hi have VB + 1 index
 // planes, the table cfh and the weights exp(.) * nu_hi, the others VB planes, cf and exp(.) * nu_lo.
-template <int KB, bool KPROD, int VB, int VKIND, bool FUSED, int TILES>
+// FINISH: the keys are one chunk, and the workgroup rotates its sums back itself; the joining kernel is a launch of its own, 3.5 us (8 heads, 4
+// queries each, keys of 2 + 1 bits, values of 2, a step with its two appends: 100 tokens 17.5 -> 15.8 us, 512 18.0 -> 16.4).
+template <int KB, bool KPROD, int VB, int VKIND, bool FUSED, int TILES, bool FINISH>
 __global__ __launch_bounds__(512) void attend128_kernel(const ScoreI8Args ka, const AttendArgs a, const AttendCoefs cf,
                                                         const AttendCoefs cfh) {
   constexpr bool VPROD = VKIND == 1, VSPLIT = VKIND == 2, TWO = VKIND != 0;  // TWO: a second set of weights
@@ -250,6 +252,16 @@ __global__ __launch_bounds__(512) void attend128_kernel(const ScoreI8Args ka, co
       if (wave_key0 + 16 * t + col < a.n) lg[t] = scale2 * srow[16 * t];
   }
   if (!EARLY || !FUSED) load_codes(0);
+  // FINISH: four parts of 32 rows of Pi (S) by 128 threads each, due at the end
+  float wp[FINISH ? 32 : 1], ws[FINISH && VPROD ? 32 : 1];
+  if constexpr (FINISH) {
+    const int at = (tid >> 7) * (32 * 128) + (tid & 127);
+#pragma unroll
+    for (int u = 0; u < 32; ++u) wp[u] = a.Pi[at + u * 128];
+    if constexpr (VPROD)
+#pragma unroll
+      for (int u = 0; u < 32; ++u) ws[u] = a.S[at + u * 128];
+  }
   __builtin_amdgcn_sched_barrier(0);
   put_words();  // (in front of the barrier that waits for the last wavefront's scores)
 
@@ -454,46 +466,86 @@ __global__ __launch_bounds__(512) void attend128_kernel(const ScoreI8Args ka, co
     }
   __syncthreads();
   const int qi = tid >> 7, j = tid & 127;
-  if (q0 + qi < a.q_per_group) {
-    float acc = 0.f, accz = 0.f;
+  float acc = 0.f, accz = 0.f;
 #pragma unroll
-    for (int w = 0; w < 8; ++w) {
-      acc += fsum_s[(w * 4 + qi) * 128 + j];
-      if (VPROD) accz += fsumz_s[(w * 4 + qi) * 128 + j];
-    }
-    float* o = a.part + (((int64_t)group * a.q_per_group + q0 + qi) * a.nchunks + chunk) * attend_part_stride(128);
-    o[4 + j] = VSPLIT ? acc : acc * ldexpf(1.f, enu - 28);
-    o[4 + 128 + j] = VPROD ? accz * ldexpf(1.f, eng - 28) : 0.f;
-    if (j == 0) {
-      float l = 0.f, mq = -INFINITY;
+  for (int w = 0; w < 8; ++w) {
+    acc += fsum_s[(w * 4 + qi) * 128 + j];
+    if (VPROD) accz += fsumz_s[(w * 4 + qi) * 128 + j];
+  }
+  if (!VSPLIT) acc *= ldexpf(1.f, enu - 28);
+  if (VPROD) accz *= ldexpf(1.f, eng - 28);
+  const int64_t row = (int64_t)group * a.q_per_group + q0 + qi;
+  if constexpr (!FINISH) {
+    if (q0 + qi < a.q_per_group) {
+      float* o = a.part + (row * a.nchunks + chunk) * attend_part_stride(128);
+      o[4 + j] = acc;
+      o[4 + 128 + j] = accz;
+      if (j == 0) {
+        float l = 0.f, mq = -INFINITY;
 #pragma unroll
-      for (int w = 0; w < 8; ++w) {
-        l += red_s[64 + w * 4 + qi];
-        mq = fmaxf(mq, red_s[w * 4 + qi]);
+        for (int w = 0; w < 8; ++w) {
+          l += red_s[64 + w * 4 + qi];
+          mq = fmaxf(mq, red_s[w * 4 + qi]);
+        }
+        o[0] = mq * 0.693147180559945309f;  // back to natural units
+        o[1] = l;
       }
-      o[0] = mq * 0.693147180559945309f;  // back to natural units
-      o[1] = l;
     }
+  } else {
+  // (as the joining kernel does it, sums in the same order)
+  float* const y_s = reinterpret_cast<float*>(dyn_s + FIRST);  // [index term, sign term][coordinate][query], over the words
+  static_assert(attend128_words_bytes(VB, TWO, TILES) >= (VPROD ? 2 : 1) * 512 * 4, "LDS");
+  float l = 0.f;
+#pragma unroll
+  for (int w = 0; w < 8; ++w) l += red_s[64 + w * 4 + qi];
+  y_s[j * 4 + qi] = acc / l;
+  if (VPROD) y_s[512 + j * 4 + qi] = accz / l;
+  __syncthreads();
+#pragma unroll
+  for (int h16 = 0; h16 < 2; ++h16) {
+    float o[4] = {0.f, 0.f, 0.f, 0.f}, oz[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int u = 16 * h16; u < 16 * h16 + 16; ++u) {
+      const f32x4 y = *reinterpret_cast<const f32x4*>(y_s + (32 * qi + u) * 4);
+#pragma unroll
+      for (int k = 0; k < 4; ++k) o[k] = fmaf(wp[u], y[k], o[k]);
+      if constexpr (VPROD) {
+        const f32x4 z = *reinterpret_cast<const f32x4*>(y_s + 512 + (32 * qi + u) * 4);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) oz[k] = fmaf(ws[u], z[k], oz[k]);
+      }
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) fsum_s[((2 * qi + h16) * 4 + k) * 128 + j] = fmaf(a.kappa, oz[k], o[k]);
+  }
+  __syncthreads();
+  if (q0 + qi < a.q_per_group) {
+    float r = fsum_s[qi * 128 + j];
+#pragma unroll
+    for (int t = 1; t < 8; ++t) r += fsum_s[(t * 4 + qi) * 128 + j];
+    a.out[row * a.ldo + j] = r;
+  }
   }
 }
 
-template <int KB, bool KPROD, int VB, int VKIND, bool FUSED, int TILES>
+template <int KB, bool KPROD, int VB, int VKIND, bool FUSED, int TILES, bool FINISH>
 hipError_t launch_attend128_tiles(const ScoreI8Args& ka, const AttendArgs& a, const AttendCoefs& cf, const AttendCoefs& cfh,
                                 int n_groups, hipStream_t s) {
   constexpr int lds = attend128_lds(KB, VB, VKIND != 0, FUSED, TILES);
   static_assert(lds <= 160 * 1024, "LDS budget");
   static LdsLimit lds_limit;  // per instantiation: the limit is raised once per device
-  if (const hipError_t e = raise_lds_limit(lds_limit, reinterpret_cast<const void*>(&attend128_kernel<KB, KPROD, VB, VKIND, FUSED, TILES>), lds); e != hipSuccess) return e;
+  if (const hipError_t e = raise_lds_limit(lds_limit, reinterpret_cast<const void*>(&attend128_kernel<KB, KPROD, VB, VKIND, FUSED, TILES, FINISH>), lds); e != hipSuccess) return e;
   const dim3 grid(a.nchunks, n_groups, (a.q_per_group + 3) / 4);
-  hipLaunchKernelGGL((attend128_kernel<KB, KPROD, VB, VKIND, FUSED, TILES>), grid, dim3(512), lds, s, ka, a, cf, cfh);
+  hipLaunchKernelGGL((attend128_kernel<KB, KPROD, VB, VKIND, FUSED, TILES, FINISH>), grid, dim3(512), lds, s, ka, a, cf, cfh);
   return hipGetLastError();
 }
 
 template <int KB, bool KPROD, int VB, int VKIND, bool FUSED>
 hipError_t launch_attend128_one(const ScoreI8Args& ka, const AttendArgs& a, const AttendCoefs& cf, const AttendCoefs& cfh,
                                 int n_groups, hipStream_t s) {
-  return a.tiles == AT_TILES_SHORT ? launch_attend128_tiles<KB, KPROD, VB, VKIND, FUSED, AT_TILES_SHORT>(ka, a, cf, cfh, n_groups, s)
-                                   : launch_attend128_tiles<KB, KPROD, VB, VKIND, FUSED, AT_TILES>(ka, a, cf, cfh, n_groups, s);
+  if (a.out != nullptr) return launch_attend128_tiles<KB, KPROD, VB, VKIND, FUSED, AT_TILES_SHORT, true>(ka, a, cf, cfh, n_groups, s);
+  return a.tiles == AT_TILES_SHORT ? launch_attend128_tiles<KB, KPROD, VB, VKIND, FUSED, AT_TILES_SHORT, false>(ka, a, cf, cfh, n_groups, s)
+                                   : launch_attend128_tiles<KB, KPROD, VB, VKIND, FUSED, AT_TILES, false>(ka, a, cf, cfh, n_groups, s);
 }
 
 // all key variants for one kind of value code; kb < 0: logits from a.scores

@@ -115,6 +115,13 @@ def test_attend_at_the_edges_of_blocks_and_passes(vb, vprod, n_groups, qpg, npg)
     run_attend(128, 2, True, vb, vprod, n_groups, qpg, npg, True)
 
 
+@pytest.mark.parametrize("fused", [True, False])  # logits from the read-out kernel itself, from a scoring call
+@pytest.mark.parametrize("vb,vprod,qpg", [(2, False, 4), (0, True, 5), (2, True, 1), (4, False, 7)])
+@pytest.mark.parametrize("npg", [1, 511, 512, 513])  # one chunk, whose workgroup rotates its sums back itself, and two
+def test_attend_over_one_chunk(vb, vprod, qpg, npg, fused):
+    run_attend(128, 2, True, vb, vprod, 3, qpg, npg, fused)
+
+
 @pytest.mark.parametrize("table", [[0.02, 0.15], [-0.05, 0.03, 0.07, 0.15]])
 def test_attend_with_a_table_that_is_not_centred_and_norms_of_either_sign(table):
     """A table symmetric about a mean other than zero is what the sums of signs take with one term more; weights are
