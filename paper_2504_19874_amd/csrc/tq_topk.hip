@@ -93,15 +93,17 @@ __global__ __launch_bounds__(T) void topk_merge_kernel(const float* __restrict__
 }  // namespace
 
 // Chunks per row when a call's rows are too few to fill the chip: 0 (one workgroup per row) unless the rows are
-// few and longer than three segments; then chunks of equal lengths, a segment at most (down to 4096 scores in chunks of 256 threads: no
+// few and longer than three segments (two and a half for k > 16); then chunks of equal lengths, a segment at most (down to 4096 scores in chunks of 256 threads: no
 // faster), and no more pairs per row than the joining kernel takes (4096).  A workgroup takes 4.7 us (k = 10) or 6 (64) for a segment and 2 for every further one, its lists joined 4.3 to 6.  us, one workgroup per
 // row / chunks + joining:
 //   10 rows of 20000, k = 64   8.2 / 10.8
-//   2 rows of 49000, k = 64   10.7 / 10.7
+//   2 rows of 49000, k = 64   10.7 / 10.4;  60: 12.0 / 10.9;  2 of 33000 9.1 / 10.3
+//   2 rows of 49000, k = 10    8.0 /  8.1;  60: 8.5 / 8.7
+//   100 rows of 41500, k = 64 11.7 / 15.2 (what more rows than compute units for their chunks lose; 23.6 before)
 //   2 rows of 56430, k = 10    9.6 /  8.4
 //   14 rows of 84645, k = 64  18.1 / 11.2
 int topk_chunks(int64_t rows, int64_t n, int k) {
-  if (k < 1 || rows < 1 || rows > 128 || n <= 3 * SEG) return 0;
+  if (k < 1 || rows < 1 || rows > 128 || n <= (k <= 16 ? 3 * SEG : 5 * SEG / 2)) return 0;
   int64_t c = (n + SEG - 1) / SEG;
   if (c > 4096 / k) c = 4096 / k;
   return c >= 2 ? (int)c : 0;
