@@ -1110,7 +1110,7 @@ tq_status tq_score_static(const tq_params* p, const float* q, int64_t ldq, int32
 namespace {
 struct AttendPlan {
   bool fast;  // the d = 128 kernel on the integer matrix cores takes the value codes
-  int nchunks, max_chunks, tiles;
+  int nchunks, max_chunks, keys;
   int64_t ld_scores;
   size_t scores_bytes, part_bytes, score_ws_bytes;
 };
@@ -1120,10 +1120,11 @@ AttendPlan attend_plan(const tq_params* pk, const tq_params* pv, bool v_prod, in
   const Codebook v_hi = make_codebook_hi(pv);
   pl.fast = pv->centroids != nullptr && (pv->d_hi == 0 || pv->centroids_hi != nullptr) &&
             attend128_applicable(pv->d, v_prod, make_codebook(pv), pv->d_hi != 0 ? &v_hi : nullptr);
-  pl.tiles = attend128_tiles(n_per_group, n_groups, q_per_group);
-  pl.nchunks = pl.fast ? attend128_chunks(n_per_group, pl.tiles) : attend_simple_chunks(n_per_group);
+  const int planes = pv->bits_mse + (v_prod || pv->d_hi != 0 ? 1 : 0);
+  pl.keys = attend128_keys(n_per_group, n_groups, q_per_group, planes);
+  pl.nchunks = pl.fast ? attend128_chunks(n_per_group, pl.keys) : attend_simple_chunks(n_per_group);
   // what is reported covers every shorter cache too, whose chunks may be more
-  pl.max_chunks = pl.fast ? attend128_max_chunks(n_per_group, n_groups, q_per_group) : pl.nchunks;
+  pl.max_chunks = pl.fast ? attend128_max_chunks(n_per_group, n_groups, q_per_group, planes) : pl.nchunks;
   pl.ld_scores = (n_per_group + 3) / 4 * 4;
   pl.scores_bytes = round_up((size_t)nq * pl.ld_scores * sizeof(float), 256);
   pl.part_bytes = round_up((size_t)nq * pl.max_chunks * attend_part_stride(pv->d) * sizeof(float), 256);
@@ -1185,11 +1186,11 @@ tq_status tq_attend_cache(const tq_params* pk, const tq_params* pv, const float*
     AttendArgs a;
     a.scores = scores; a.lds = pl.ld_scores;
     a.idx = v_idx; a.qjl = v_qjl; a.gamma = v_gamma; a.norm = v_norm;
-    a.part = part; a.nchunks = pl.nchunks; a.tiles = pl.tiles; a.n = n_per_group; a.group_stride = group_stride; a.d = pv->d; a.q_per_group = q_per_group;
+    a.part = part; a.nchunks = pl.nchunks; a.keys = pl.keys; a.n = n_per_group; a.group_stride = group_stride; a.d = pv->d; a.q_per_group = q_per_group;
     a.scale = scale; a.gs_hi = pv->d_hi / 32;
     const AttendTables tables = {make_codebook(pv), make_codebook_hi(pv)};
     // a single chunk is rotated back by the workgroup that has summed it
-    const bool whole = pl.fast && pl.nchunks == 1 && pl.tiles == AT_TILES_SHORT;
+    const bool whole = pl.fast && pl.nchunks == 1 && pl.keys < AT_KEYS[2];
     a.out = whole ? out : nullptr; a.ldo = ldo; a.Pi = pv->Pi; a.S = v_prod ? pv->S : nullptr; a.kappa = kappa_of(pv->d);
     // keys the single-kernel d = 128 scoring path takes are scored inside the read-out kernel
     const bool k_prod = k_qjl != nullptr;

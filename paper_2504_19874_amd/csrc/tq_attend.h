@@ -18,7 +18,7 @@ struct AttendArgs {
   const float* norm;
   float* part;          // [n_groups * q_per_group][nchunks][attend_part_stride(d)]
   int nchunks;
-  int tiles;            // d = 128 kernel: AT_TILES or AT_TILES_SHORT
+  int keys;             // d = 128 kernel: of a chunk, see attend128_keys
   int64_t n;            // keys per group
   int64_t group_stride; // value code rows between the first tokens of consecutive groups (>= n)
   int d;
@@ -39,13 +39,12 @@ struct AttendTables {
 };
 
 // d = 128 on the integer matrix cores (tq_attend_128.hip)
-// A chunk of keys (a workgroup) is 128 TILES keys.  Short chunks where long ones would occupy at most half of the compute
-// units: what a workgroup does besides its keys is then done by more of them, but its keys take a quarter of the time
-// (8 heads of 1024 tokens, 4 queries each: 15.9 -> 10.6 us for the kernel).
-constexpr int AT_TILES = 16, AT_TILES_SHORT = 4;
-inline int attend128_chunks(int64_t n, int tiles) { return (int)((n + 128 * tiles - 1) / (128 * tiles)); }
-int attend128_tiles(int64_t n, int n_groups, int q_per_group);
-int attend128_max_chunks(int64_t n, int n_groups, int q_per_group);  // of any call with at most n keys per group
+// Keys of a chunk (a workgroup): 256 (four wavefronts of 64), 512 (eight of 64) or 2048 (eight of 256).
+constexpr int AT_KEYS[3] = {256, 512, 2048};
+inline int attend128_chunks(int64_t n, int keys) { return (int)((n + keys - 1) / keys); }
+// planes: of a value code, the signs of Alg. 2 or the top plane of instance hi among them
+int attend128_keys(int64_t n, int n_groups, int q_per_group, int planes);
+int attend128_max_chunks(int64_t n, int n_groups, int q_per_group, int planes);  // of any call with at most n keys per group
 bool attend128_applicable(int d, bool prod, const Codebook& cb, const Codebook* cb_hi);
 struct ScoreI8Args;
 hipError_t launch_attend128(int kb, bool kprod, const ScoreI8Args* ka, bool vprod, const AttendArgs& a, const AttendTables& t, int n_groups,

@@ -1,5 +1,6 @@
 // Attention read-out at d = 128 on the integer matrix cores: which kernel variant a call takes
 // (the kernel itself is in tq_attend_128_kernel.h).
+#include <algorithm>
 #include <cstring>
 
 #include "tq_attend_128_kernel.h"
@@ -7,9 +8,17 @@
 namespace tq {
 
 namespace {
-int64_t long_limit(int n_groups, int q_per_group) {  // keys per group up to which short chunks are taken
+// Keys per group up to which chunks of AT_KEYS[i] are taken, i = 0, 1.
+// Short chunks where long ones would occupy at most half of the compute units: what a workgroup does besides its keys is then done by more of
+// them, but its keys take a quarter of the time (8 heads of 1024 tokens, 4 queries each: 15.9 -> 10.6 us for the kernel).
+// Of four wavefronts instead of eight for values of three planes or more, while every compute unit has one workgroup at most (beyond, two
+// of them on a compute unit would fetch the matrices twice): their sums of signs then run on twice as many matrix cores.  A step, us,
+// eight / four wavefronts: values of 4 bits, 8 heads of 1741 tokens 21.2 / 20.2; of 2 bits, 8 of 1024 17.0 / 17.6.
+int64_t limit(int i, int n_groups, int q_per_group) {
   const int64_t others = (int64_t)n_groups * ((q_per_group + 3) / 4);
-  return others > 0 ? device_cu_count() / 2 / others * (128 * AT_TILES) : 0;
+  if (others == 0) return 0;
+  // (up to 64 chunks are joined by the quicker kernel)
+  return i == 0 ? std::min<int64_t>(device_cu_count() / others, 64) * AT_KEYS[0] : device_cu_count() / 2 / others * AT_KEYS[2];
 }
 
 bool coefficients(const Codebook& cb, AttendCoefs* out) {
@@ -21,11 +30,19 @@ bool coefficients(const Codebook& cb, AttendCoefs* out) {
   return true;
 }
 }  // namespace
-int attend128_tiles(int64_t n, int n_groups, int q_per_group) { return n <= long_limit(n_groups, q_per_group) ? AT_TILES_SHORT : AT_TILES; }
-int attend128_max_chunks(int64_t n, int n_groups, int q_per_group) {
-  const int64_t lim = long_limit(n_groups, q_per_group);
-  const int a = attend128_chunks(n < lim ? n : lim, AT_TILES_SHORT), b = attend128_chunks(n, AT_TILES);
-  return a > b ? a : b;
+int attend128_keys(int64_t n, int n_groups, int q_per_group, int planes) {
+  if (n > AT_KEYS[0] && n <= AT_KEYS[1] && n <= limit(1, n_groups, q_per_group)) return AT_KEYS[1];  // one chunk, which needs no joining
+  if (planes > 2 && n <= limit(0, n_groups, q_per_group)) return AT_KEYS[0];
+  return n <= limit(1, n_groups, q_per_group) ? AT_KEYS[1] : AT_KEYS[2];
+}
+int attend128_max_chunks(int64_t n, int n_groups, int q_per_group, int planes) {
+  int most = attend128_chunks(n, AT_KEYS[2]);
+  for (int i = planes > 2 ? 0 : 1; i < 2; ++i) {
+    const int64_t lim = limit(i, n_groups, q_per_group);
+    const int c = attend128_chunks(n < lim ? n : lim, AT_KEYS[i]);
+    most = c > most ? c : most;
+  }
+  return most;
 }
 
 // value codes the kernel covers: d = 128, tables symmetric about zero; codes of Alg. 1 with 1..4 index bits,

@@ -17,9 +17,11 @@
 // therefore takes the words of 32 keys (one coordinate group, one plane) and transposes the
 // 32 x 32 bit block in registers; the transposed words go through LDS to the lanes that need them as operands.
 //
-// Workgroup of 8 wavefronts = 128 TILES keys of one group, 4 queries; a wavefront owns 16 TILES consecutive
-// keys (256, or 64 where 2048 keys per workgroup would leave compute units without one: attend128_tiles) and takes
-// up to 256 per pass (at_pass_keys: what LDS holds).  Everything between the scoring and the joining is a wavefront's own.
+// Workgroup of WAVES (8, or 4) wavefronts = 16 WAVES TILES keys of one group, 4 queries; a wavefront owns 16 TILES consecutive
+// keys (256, or 64 where 2048 keys per workgroup would leave compute units without one: attend128_keys) and takes
+// up to 256 per pass (at_pass_keys: what LDS holds).  Between the scoring and the joining everything is a
+// wavefront's own with long ranges; with short ones the sums are shared out by coordinate group (at_grouped), and of eight wavefronts four
+// transpose (8 heads of 1024 tokens: 17.9 -> 17.2 us a step).
 //
 // 8 heads, 4 queries each, keys of 2 + 1 bits, values of 2, a step with its two appends: 65536 keys 29.0 -> 27.4 us, 1024 19.1 ->
 // 18.1; keys and values of 4 bits, 53970 keys 61 -> 41.  Before: four base-256 digits on the integer instructions, whose byte operands
@@ -43,6 +45,10 @@ namespace tq {
 // coordinate group and a plane each) allow it.  two: a second set of weight digits (the signs of Alg. 2, or instance hi)
 __host__ __device__ constexpr int at_pass_keys(int tiles, int npl, bool two) { return tiles < 8 ? 64 : npl <= 2 && !two ? 256 : 128; }
 __host__ __device__ constexpr int at_planes(int vb, bool two) { return vb + (two ? 1 : 0); }
+// Short ranges: a wavefront's 64 keys are one matrix instruction per term, and what comes after it (16 sums to four) would be most of the
+// work, so a wavefront takes one coordinate group for the keys of four wavefronts.  Not eight wavefronts with many planes: their registers
+// leave room for one workgroup per compute unit then (8 heads of 20000 tokens, values of 4 bits: 28.5 -> 30.5 us a step).
+__host__ __device__ constexpr bool at_grouped(int tiles, int waves, int npl) { return tiles < 8 && (waves == 4 || npl <= 2); }
 // digits of a wavefront: [query][digit][key], a byte each; 16 more per row, so that the rows of a read are in different banks
 __host__ __device__ constexpr int at_row_bytes(int pass) { return pass + 16; }
 __host__ __device__ constexpr int at_wd_bytes(int pass) { return 32 * at_row_bytes(pass); }
@@ -50,21 +56,21 @@ __host__ __device__ constexpr int at_wd_bytes(int pass) { return 32 * at_row_byt
 // that the half-waves, which read one each, are in different halves of the banks
 constexpr int AT_BLOCK_WORDS = 128 + 32, AT_PAIR_WORDS = AT_BLOCK_WORDS + 128;
 __host__ __device__ constexpr int at_plane_words(int pass) { return pass / 64 * AT_PAIR_WORDS; }
-constexpr int AT_FSUM_BYTES = 8 * 4 * 128 * 4;  // [wave][query][coordinate], over the digits in the end
+constexpr int AT_FSUM_BYTES = 8 * 4 * 128 * 4;  // [wave][query][coordinate], over the digits in the end (short ranges need less)
 constexpr int AT_RED_FLOATS = 3 * 8 * 4;  // [maxima | norm maxima | sums][wave][4]
 
 // dynamic LDS: what the scoring body needs, then the digits and at last the sums; words; the reduction scratch, which like the words is
 // written while other wavefronts may still be scoring
-__host__ __device__ constexpr int attend128_first_bytes(int kb, int vb, bool two, bool fused, int tiles) {
-  const int sets = two ? 2 : 1, wd = sets * 8 * at_wd_bytes(at_pass_keys(tiles, at_planes(vb, two), two));
+__host__ __device__ constexpr int attend128_first_bytes(int kb, int vb, bool two, bool fused, int tiles, int waves) {
+  const int sets = two ? 2 : 1, wd = sets * waves * at_wd_bytes(at_pass_keys(tiles, at_planes(vb, two), two));
   const int own = wd > sets * AT_FSUM_BYTES ? wd : sets * AT_FSUM_BYTES;
-  return fused && score128_lds(kb) > own ? (score128_lds(kb) + 15) / 16 * 16 : own;
+  return fused && score128_lds(kb, waves) > own ? (score128_lds(kb, waves) + 15) / 16 * 16 : own;
 }
-__host__ __device__ constexpr int attend128_words_bytes(int vb, bool two, int tiles) {
-  return 8 * at_planes(vb, two) * at_plane_words(at_pass_keys(tiles, at_planes(vb, two), two)) * 4;
+__host__ __device__ constexpr int attend128_words_bytes(int vb, bool two, int tiles, int waves) {
+  return waves * at_planes(vb, two) * at_plane_words(at_pass_keys(tiles, at_planes(vb, two), two)) * 4;
 }
-__host__ __device__ constexpr int attend128_lds(int kb, int vb, bool two, bool fused, int tiles) {
-  return attend128_first_bytes(kb, vb, two, fused, tiles) + attend128_words_bytes(vb, two, tiles) + AT_RED_FLOATS * 4;
+__host__ __device__ constexpr int attend128_lds(int kb, int vb, bool two, bool fused, int tiles, int waves) {
+  return attend128_first_bytes(kb, vb, two, fused, tiles, waves) + attend128_words_bytes(vb, two, tiles, waves) + AT_RED_FLOATS * 4;
 }
 
 // [0]: the table's mean w0; [S]: what belongs to a plane subset of odd size, -2 h[S] (the operands are halves, and minus where the bit is set)
@@ -119,9 +125,9 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 // 2 = two instances of Alg. 1 over a split of the coordinates (Sec. 4.3): groups g < a.gs_hi have VB + 1 index
 // planes, the table cfh and the weights exp(.) * nu_hi, the others VB planes, cf and exp(.) * nu_lo.
 // FINISH: the keys are one chunk, and the workgroup rotates its sums back itself; the joining kernel is a launch of its own, 3.5 us (8 heads, 4
-// queries each, keys of 2 + 1 bits, values of 2, a step with its two appends: 100 tokens 17.5 -> 15.8 us, 512 18.0 -> 16.4).
-template <int KB, bool KPROD, int VB, int VKIND, bool FUSED, int TILES, bool FINISH>
-__global__ __launch_bounds__(512) void attend128_kernel(const ScoreI8Args ka, const AttendArgs a, const AttendCoefs cf,
+// queries each, keys of 2 + 1 bits, values of 2, a step with its two appends: 100 tokens 17.9 -> 15.2 us, 512 18.2 -> 15.5).
+template <int KB, bool KPROD, int VB, int VKIND, bool FUSED, int TILES, int WAVES, bool FINISH>
+__global__ __launch_bounds__(64 * WAVES) void attend128_kernel(const ScoreI8Args ka, const AttendArgs a, const AttendCoefs cf,
                                                         const AttendCoefs cfh) {
   constexpr bool VPROD = VKIND == 1, VSPLIT = VKIND == 2, TWO = VKIND != 0;  // TWO: a second set of weights
   fetch_arguments<sizeof(ScoreI8Args) + sizeof(AttendArgs) + 2 * sizeof(AttendCoefs)>();
@@ -131,7 +137,7 @@ __global__ __launch_bounds__(512) void attend128_kernel(const ScoreI8Args ka, co
   constexpr int PT = PASS_KEYS / 16, PB = PASS_KEYS / 32, KK = PASS_KEYS / 64;  // tiles, blocks of 32 keys, k-blocks of 64 keys per pass
   constexpr int NVB = VB > 0 ? VB : 1;
   constexpr int ROW = at_row_bytes(PASS_KEYS), WD_BYTES = at_wd_bytes(PASS_KEYS), PLANE_WORDS = at_plane_words(PASS_KEYS);
-  static_assert(4 * PB * NPL <= 64, "a block, a group and a plane per lane");
+  static_assert(4 * PB * NPL <= 64 && (TILES >= 8 || 16 * NPL <= 64), "a block, a group and a plane per lane");
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -139,31 +145,37 @@ __global__ __launch_bounds__(512) void attend128_kernel(const ScoreI8Args ka, co
   const int kc = lane >> 4;   // query of this lane's logits
   const int l32 = lane & 31, h = lane >> 5;  // matrix instructions: row (query, digit) or column (coordinate of a group), half of the 64 keys
   const int chunk = blockIdx.x, group = blockIdx.y, q0 = blockIdx.z * 4;
-  constexpr int FIRST = attend128_first_bytes(KB, VB, TWO, FUSED, TILES);
-  unsigned char* const wd = dyn_s + wave * WD_BYTES;  // digits of exp(.) nu; + 8 WD_BYTES: of exp(.) nu gamma / nu_hi
+  constexpr int FIRST = attend128_first_bytes(KB, VB, TWO, FUSED, TILES, WAVES);
+  unsigned char* const wd = dyn_s + wave * WD_BYTES;  // digits of exp(.) nu; + WAVES WD_BYTES: of exp(.) nu gamma / nu_hi
   uint32_t* const words = reinterpret_cast<uint32_t*>(dyn_s + FIRST) + wave * (NPL * PLANE_WORDS);  // + plane * PLANE_WORDS
   float* const fsum_s = reinterpret_cast<float*>(dyn_s);  // [8][4][128], over the digits
   float* const fsumz_s = fsum_s + AT_FSUM_BYTES / 4;      // the same for the sign sums
-  float* const red_s = reinterpret_cast<float*>(dyn_s + FIRST + attend128_words_bytes(VB, TWO, TILES));  // [3][8][4]
+  float* const red_s = reinterpret_cast<float*>(dyn_s + FIRST + attend128_words_bytes(VB, TWO, TILES, WAVES));  // [3][8][4]
 
   const int64_t gbase = (int64_t)group * a.group_stride;
-  const int64_t wave_key0 = ((int64_t)chunk * 8 + wave) * WAVE_KEYS;
+  const int64_t wave_key0 = ((int64_t)chunk * WAVES + wave) * WAVE_KEYS;
   // transposing role: block kb of 32 keys, coordinate group tg, a plane.  Nibble i of the transposed word 4 a + b is to be key 8 b + i
   // (word t of the lane: key 8 (t % 4) + t / 4): eight consecutive keys, as the digits lie, make one dword of an operand, the bit of
   // the nibble being the coordinate's.
-  const int kb = lane & (PB - 1), tg = (lane / PB) & 3, plane = lane / (4 * PB);
+  constexpr bool GROUPED = at_grouped(TILES, WAVES, NPL), PAIRED = GROUPED && WAVES == 8;
+  // Eight wavefronts of short ranges: the first four, one per SIMD and the first to have their scores, transpose for two each, four blocks of 32 keys
+  constexpr int TB = PAIRED ? 4 : PB, TKEYS = 32 * TB;
+  const bool transposes = !PAIRED || wave < 4;  // uniform
+  const int64_t t_key0 = PAIRED ? (int64_t)chunk * (WAVES * WAVE_KEYS) + wave * TKEYS : wave_key0;
+  const int kb = lane & (TB - 1), tg = (lane / TB) & 3, plane = lane / (4 * TB);
 
   uint32_t vw[32];
-  const bool full = wave_key0 + WAVE_KEYS <= a.n;  // uniform: no key of this wavefront is past the end
+  const bool full = t_key0 + PASSES * TKEYS <= a.n;  // uniform: no key of this wavefront is past the end
   // the 16-byte pieces of the wavefront's rows, as they lie in memory; through its words' place in LDS to the lanes that transpose them
   // (lanes that fetch their own words touch every line four times: scoring ended 2 us later).  Two instances: rows are no whole pieces.
   typedef uint32_t piece __attribute__((ext_vector_type(4), aligned(4)));  // (the arrays are the caller's)
-  constexpr int IP = VSPLIT ? 0 : PASS_KEYS * VB / 64, ZP = VPROD ? PASS_KEYS / 64 : 0;  // pieces per lane: index planes, signs
-  constexpr int Z_AT = PASS_KEYS * VB * 4 + PB * VB * 4;  // words of the index planes with 4 VB more per block of 32 keys (banks)
+  constexpr int IP = VSPLIT ? 0 : TKEYS * VB / 64, ZP = VPROD ? TKEYS / 64 : 0;  // pieces per lane: index planes, signs
+  constexpr int Z_AT = TKEYS * VB * 4 + TB * VB * 4;  // words of the index planes with 4 VB more per block of 32 keys (banks)
   piece pi[IP > 0 ? IP : 1], pz[ZP > 0 ? ZP : 1];
   auto load_codes = [&](int ps) {
+    if (!transposes) return;
     if constexpr (!VSPLIT) {
-      const int64_t row0 = wave_key0 + ps * PASS_KEYS, rows = a.n - row0;  // keys past the end have weight 0: the last piece again
+      const int64_t row0 = t_key0 + ps * TKEYS, rows = a.n - row0;  // keys past the end have weight 0: the last piece again
       auto get = [&](const uint32_t* src, int per_row, int p) {
         const int64_t last = rows * per_row - 1;
         const int64_t at = full || p <= last ? p : last;
@@ -174,7 +186,7 @@ __global__ __launch_bounds__(512) void attend128_kernel(const ScoreI8Args ka, co
 #pragma unroll
       for (int i = 0; i < ZP; ++i) pz[i] = get(a.qjl, 1, i * 64 + lane);
     } else {
-      const int64_t k0 = wave_key0 + ps * PASS_KEYS + 32 * kb;
+      const int64_t k0 = t_key0 + ps * TKEYS + 32 * kb;
       const bool thi = tg < a.gs_hi;
       const int wpr = 4 * VB + a.gs_hi, off = (thi ? tg * (VB + 1) : a.gs_hi + tg * VB) + plane;
       const uint32_t* const src = a.idx + (gbase + (k0 < a.n ? k0 : a.n - 1)) * wpr + off;
@@ -184,31 +196,33 @@ __global__ __launch_bounds__(512) void attend128_kernel(const ScoreI8Args ka, co
       for (int k = 0; k < 32; ++k) vw[4 * (k & 7) + (k >> 3)] = plane < VB + (thi ? 1 : 0) ? src[(k < last ? k : last) * wpr] : 0u;  // no such plane: zeros
     }
   };
+  uint32_t* const t_words = PAIRED ? words + (transposes ? wave : 0) * (NPL * PLANE_WORDS) : words;  // of two wavefronts: 2 wave, 2 wave + 1
   auto take_codes = [&] {
     if constexpr (!VSPLIT) {
 #pragma unroll
       for (int i = 0; i < IP; ++i) {
         const int p = i * 64 + lane;
-        *reinterpret_cast<u32x4*>(words + 4 * (p + p / (32 * NVB) * NVB)) = pi[i];
+        *reinterpret_cast<u32x4*>(t_words + 4 * (p + p / (32 * NVB) * NVB)) = pi[i];
       }
 #pragma unroll
       for (int i = 0; i < ZP; ++i) {
         const int p = i * 64 + lane;
-        *reinterpret_cast<u32x4*>(words + Z_AT + 4 * (p + p / 32)) = pz[i];
+        *reinterpret_cast<u32x4*>(t_words + Z_AT + 4 * (p + p / 32)) = pz[i];
       }
       const bool sign = VPROD && plane == VB;
       const int step = sign ? 4 : 4 * VB;  // words from one key's to the next key's
-      const uint32_t* const src = words + (sign ? Z_AT + tg : tg * VB + (plane < NPL ? plane : 0)) + kb * 33 * step;
+      const uint32_t* const src = t_words + (sign ? Z_AT + tg : tg * VB + (plane < NPL ? plane : 0)) + kb * 33 * step;
 #pragma unroll
       for (int k = 0; k < 32; ++k) vw[4 * (k & 7) + (k >> 3)] = src[k * step];
     }
   };
   auto put_words = [&] {
+    if (!transposes) return;
     take_codes();
     transpose_nibbles(vw);
-    if (4 * PB * NPL == 64 || plane < NPL) {
+    if (4 * TB * NPL == 64 || plane < NPL) {
       // the 16-byte pieces of a row of 32 words in an order of the lane's own: a store meets every bank equally often
-      uint32_t* const row = words + plane * PLANE_WORDS + (kb >> 1) * AT_PAIR_WORDS + (kb & 1) * AT_BLOCK_WORDS + tg * 32;
+      uint32_t* const row = t_words + plane * PLANE_WORDS + (kb >> 1) * (PAIRED ? NPL * PLANE_WORDS : AT_PAIR_WORDS) + (kb & 1) * AT_BLOCK_WORDS + tg * 32;
 #pragma unroll
       for (int c = 0; c < 8; ++c) *reinterpret_cast<uint4*>(row + 4 * (c ^ (lane & 7))) = make_uint4(vw[4 * c], vw[4 * c + 1], vw[4 * c + 2], vw[4 * c + 3]);
     }
@@ -240,7 +254,7 @@ __global__ __launch_bounds__(512) void attend128_kernel(const ScoreI8Args ka, co
   if (FUSED) {
     auto sink = [&](int t, float score, bool key_live) { lg[t] = key_live ? scale2 * score : -INFINITY; };
     // (the value codes behind the first key codes and the matrices, which are due earlier)
-    score128_body<KB, KPROD, TILES>(ka, dyn_s, sink, [&] {
+    score128_body<KB, KPROD, TILES, WAVES>(ka, dyn_s, sink, [&] {
       if (EARLY) load_codes(0);
     });
   __builtin_amdgcn_sched_barrier(0);
@@ -252,15 +266,16 @@ __global__ __launch_bounds__(512) void attend128_kernel(const ScoreI8Args ka, co
       if (wave_key0 + 16 * t + col < a.n) lg[t] = scale2 * srow[16 * t];
   }
   if (!EARLY || !FUSED) load_codes(0);
-  // FINISH: four parts of 32 rows of Pi (S) by 128 threads each, due at the end
-  float wp[FINISH ? 32 : 1], ws[FINISH && VPROD ? 32 : 1];
+  // FINISH: parts of ROWS rows of Pi (S) by 128 threads each, due at the end
+  constexpr int ROWS = 256 / WAVES;
+  float wp[FINISH ? ROWS : 1], ws[FINISH && VPROD ? ROWS : 1];
   if constexpr (FINISH) {
-    const int at = (tid >> 7) * (32 * 128) + (tid & 127);
+    const int at = (tid >> 7) * (ROWS * 128) + (tid & 127);
 #pragma unroll
-    for (int u = 0; u < 32; ++u) wp[u] = a.Pi[at + u * 128];
+    for (int u = 0; u < ROWS; ++u) wp[u] = a.Pi[at + u * 128];
     if constexpr (VPROD)
 #pragma unroll
-      for (int u = 0; u < 32; ++u) ws[u] = a.S[at + u * 128];
+      for (int u = 0; u < ROWS; ++u) ws[u] = a.S[at + u * 128];
   }
   __builtin_amdgcn_sched_barrier(0);
   put_words();  // (in front of the barrier that waits for the last wavefront's scores)
@@ -289,7 +304,7 @@ __global__ __launch_bounds__(512) void attend128_kernel(const ScoreI8Args ka, co
   __builtin_amdgcn_sched_barrier(0);
   float m = -INFINITY, numax = 0.f, ngmax = 0.f;
 #pragma unroll
-  for (int w = 0; w < 8; ++w) {
+  for (int w = 0; w < WAVES; ++w) {
     m = fmaxf(m, red_s[w * 4 + kc]);
     numax = fmaxf(numax, red_s[32 + w * 4]);
     if (TWO) ngmax = fmaxf(ngmax, red_s[32 + w * 4 + 1]);
@@ -321,9 +336,11 @@ __global__ __launch_bounds__(512) void attend128_kernel(const ScoreI8Args ka, co
 
   // the half-waves hold the digits 0, 2, 4, 6 and 1, 3, 5, 7 of the sums
   const float hf = h ? 16.f : 1.f;
-  float f[4][4], fz[4][4];  // [coordinate group][query]: coordinate 32 g + l32; VPROD: the sums of the sign term
+  // GROUPED: wavefront w takes coordinate group w % 4 for the keys of four wavefronts, behind one barrier more
+  constexpr int NG = GROUPED ? 1 : 4;  // coordinate groups of a wavefront
+  float f[NG][4], fz[NG][4];           // [coordinate group][query]: coordinate 32 g + l32; VPROD: the sums of the sign term
 #pragma unroll
-  for (int g = 0; g < 4; ++g)
+  for (int g = 0; g < NG; ++g)
 #pragma unroll
     for (int k = 0; k < 4; ++k) f[g][k] = fz[g][k] = 0.f;
   float lsum = 0.f;
@@ -331,6 +348,8 @@ __global__ __launch_bounds__(512) void attend128_kernel(const ScoreI8Args ka, co
   uint32_t read_at[4];
 #pragma unroll
   for (int x = 0; x < 4; ++x) read_at[x] = h * AT_BLOCK_WORDS + 4 * (((l32 >> 2) ^ h) ^ (2 * x));
+  // GROUPED: in the words of wavefront kk of four
+  auto read_own = [&](int kk) { return h * AT_BLOCK_WORDS + 4 * (((l32 >> 2) ^ h) ^ (2 * ((((PAIRED ? 2 * (kk & 1) : 0) + TB * (wave & 3)) & 7) / 2))); };
   // a wavefront's digits and words are its own, and LDS takes a wavefront's instructions in order
   auto wave_sync = [] {
     asm volatile("" ::: "memory");
@@ -361,50 +380,62 @@ __global__ __launch_bounds__(512) void attend128_kernel(const ScoreI8Args ka, co
       put_digits(o, rounded(p * nu));
       if (TWO) {
         const float ng = __int_as_float(__builtin_amdgcn_ds_bpermute(4 * (16 * (t & 3) + col), __float_as_int(ngv[t >> 2])));
-        put_digits(o + 8 * WD_BYTES, rounded(p * ng));
+        put_digits(o + WAVES * WD_BYTES, rounded(p * ng));
       }
     }
-    wave_sync();
+    if constexpr (GROUPED) __syncthreads();
+    else wave_sync();
 
   __builtin_amdgcn_sched_barrier(0);
     // an fp8 operand's 32 values of a lane are k = 16 h .. and 32 + 16 h .., an fp4 operand's k = 32 h ..
-    v8i aop[KK], zop[KK];
     auto digits_of = [&](const unsigned char* w, int kk) -> v8i {
       const unsigned char* const r = w + l32 * ROW + kk * 64 + 16 * h;
       const v4i lo = *reinterpret_cast<const v4i*>(r), hi = *reinterpret_cast<const v4i*>(r + 32);
       return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
     };
+    // the k-blocks of this wavefront's sums: its own keys, or those of four wavefronts
+    constexpr int NK = GROUPED ? 4 : KK;
+    static_assert(!GROUPED || (KK == 1 && PASSES == 1), "");
+    const unsigned char* const wd0 = GROUPED ? dyn_s + (wave & ~3) * WD_BYTES : wd;
+    const uint32_t* const words0 = GROUPED ? words - (wave & 3) * (NPL * PLANE_WORDS) : words;
+    auto digits_at = [&](const unsigned char* w, int kk) { return GROUPED ? digits_of(w + kk * WD_BYTES, 0) : digits_of(w, kk); };
+    v8i aop[NK], zop[NK];
 #pragma unroll
-    for (int kk = 0; kk < KK; ++kk) {
-      aop[kk] = digits_of(wd, kk);
-      if (VSPLIT) zop[kk] = digits_of(wd + 8 * WD_BYTES, kk);
+    for (int kk = 0; kk < NK; ++kk) {
+      aop[kk] = digits_at(wd0, kk);
+      if (VSPLIT) zop[kk] = digits_at(wd0 + WAVES * WD_BYTES, kk);
     }
     auto words_of = [&](int pl, int g, int kk) {
-      return *reinterpret_cast<const u32x4*>(words + pl * PLANE_WORDS + kk * AT_PAIR_WORDS + g * 32 + read_at[((2 * kk + PB * g) & 7) / 2]);
+      if constexpr (GROUPED) {
+        const int gw = wave & 3;
+        return *reinterpret_cast<const u32x4*>(words0 + kk * (NPL * PLANE_WORDS) + pl * PLANE_WORDS + gw * 32 + read_own(kk));
+      } else {
+        return *reinterpret_cast<const u32x4*>(words0 + pl * PLANE_WORDS + kk * AT_PAIR_WORDS + g * 32 + read_at[((2 * kk + PB * g) & 7) / 2]);
+      }
     };
     // sums of a coordinate group with these weights and signs, added to o with a factor
-    auto add_sums = [&](const v8i (&wop)[KK], auto sign_of, float factor, float (&o)[4]) {
+    auto add_sums = [&](const v8i (&wop)[NK], auto sign_of, float factor, float (&o)[4]) {
       f32x16 acc;
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[r] = 0.f;
 #pragma unroll
-      for (int kk = 0; kk < KK; ++kk)  // (the scale 2^9 makes a digit the integer it stands for)
+      for (int kk = 0; kk < NK; ++kk)  // (the scale 2^9 makes a digit the integer it stands for)
         acc = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(wop[kk], sign_of(kk), acc, 0, 4, 0, 136, 0, 127);
 #pragma unroll
       for (int k = 0; k < 4; ++k)
         o[k] = fmaf(factor, fmaf(fmaf(acc[4 * k + 3], 256.f, acc[4 * k + 2]), 65536.f, fmaf(acc[4 * k + 1], 256.f, acc[4 * k])), o[k]);
     };
 #pragma unroll
-    for (int g = 0; g < 4; ++g) {
+    for (int g = 0; g < NG; ++g) {
       __builtin_amdgcn_sched_barrier(0);  // one group's sums at a time (registers)
       constexpr int NPI = VSPLIT ? VB + 1 : NVB;  // index planes (instance lo: the top one is all zero)
-      u32x4 pw[KK][NPI];
+      u32x4 pw[NK][NPI];
 #pragma unroll
-      for (int kk = 0; kk < KK; ++kk)
+      for (int kk = 0; kk < NK; ++kk)
 #pragma unroll
         for (int pl = 0; pl < (VSPLIT ? VB + 1 : VB); ++pl) pw[kk][pl] = words_of(pl, g, kk);
       // signs of one coordinate group: plane subsets of odd size, weights and table of the group's instance
-      auto terms = [&](auto planes_c, const v8i (&wop)[KK], const AttendCoefs& tab) {
+      auto terms = [&](auto planes_c, const v8i (&wop)[NK], const AttendCoefs& tab) {
         constexpr int NP = decltype(planes_c)::value;
 #pragma unroll
         for (int mset = 1; mset < (1 << NP); ++mset) {
@@ -419,14 +450,15 @@ __global__ __launch_bounds__(512) void attend128_kernel(const ScoreI8Args ka, co
           }, hf * tab.c[mset], f[g]);
         }
       };
-      if (VSPLIT && g < a.gs_hi) terms(std::integral_constant<int, VB + 1>{}, zop, cfh);  // uniform
+      const bool of_hi = VSPLIT && (GROUPED ? wave & 3 : g) < a.gs_hi;
+      if (of_hi) terms(std::integral_constant<int, VB + 1>{}, zop, cfh);  // uniform
       else terms(std::integral_constant<int, VB>{}, aop, cf);
     }
     if constexpr (VPROD) {
 #pragma unroll
-      for (int kk = 0; kk < KK; ++kk) zop[kk] = digits_of(wd + 8 * WD_BYTES, kk);
+      for (int kk = 0; kk < NK; ++kk) zop[kk] = digits_at(wd0 + WAVES * WD_BYTES, kk);
 #pragma unroll
-      for (int g = 0; g < 4; ++g) {
+      for (int g = 0; g < NG; ++g) {
         __builtin_amdgcn_sched_barrier(0);
         add_sums(zop, [&](int kk) { return signs(words_of(VB, g, kk)); }, -2.f * hf, fz[g]);
       }
@@ -436,9 +468,9 @@ __global__ __launch_bounds__(512) void attend128_kernel(const ScoreI8Args ka, co
       add_sums(aop, [&](int) { return signs(u32x4{0u, 0u, 0u, 0u}); }, 2.f * hf * cf.c[0], w);
       if constexpr (VSPLIT) add_sums(zop, [&](int) { return signs(u32x4{0u, 0u, 0u, 0u}); }, 2.f * hf * cfh.c[0], wh);
 #pragma unroll
-      for (int g = 0; g < 4; ++g)
+      for (int g = 0; g < NG; ++g)
 #pragma unroll
-        for (int k = 0; k < 4; ++k) f[g][k] += VSPLIT && g < a.gs_hi ? wh[k] : w[k];
+        for (int k = 0; k < 4; ++k) f[g][k] += VSPLIT && (GROUPED ? wave & 3 : g) < a.gs_hi ? wh[k] : w[k];
     }
     wave_sync();
   }
@@ -454,98 +486,113 @@ __global__ __launch_bounds__(512) void attend128_kernel(const ScoreI8Args ka, co
     const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(lo), __float_as_uint(hi), false, false);
     return __uint_as_float(r[0]) + __uint_as_float(r[1]);
   };
+  constexpr int PARTS = GROUPED ? WAVES / 4 : WAVES;  // sums to be added
 #pragma unroll
-  for (int g = 0; g < 4; ++g)
+  for (int g = 0; g < NG; ++g)
 #pragma unroll
     for (int k = 0; k < 2; ++k) {
-      const int at = (wave * 4 + k + 2 * h) * 128 + 32 * g + l32;
+      const int gw = GROUPED ? wave & 3 : g, at = ((GROUPED ? wave >> 2 : wave) * 4 + k + 2 * h) * 128 + 32 * gw + l32;
       float v = join(f[g][k], f[g][k + 2]);
-      if (VSPLIT) v *= ldexpf(1.f, (g < a.gs_hi ? eng : enu) - 28);  // each instance has its own weight scale
+      if (VSPLIT) v *= ldexpf(1.f, (gw < a.gs_hi ? eng : enu) - 28);  // each instance has its own weight scale
       fsum_s[at] = v;
       if (VPROD) fsumz_s[at] = join(fz[g][k], fz[g][k + 2]);
     }
   __syncthreads();
-  const int qi = tid >> 7, j = tid & 127;
+  constexpr int ROUNDS_Q = 8 / WAVES, QUERIES = WAVES / 2;  // 128 threads have a query's coordinates
+  const int j = tid & 127, part0 = tid >> 7;
+  float* const y_s = reinterpret_cast<float*>(dyn_s + FIRST);  // FINISH: [index term, sign term][query][coordinate], over the words
+#pragma unroll
+  for (int rq = 0; rq < ROUNDS_Q; ++rq) {
+  const int qi = part0 + rq * QUERIES;
   float acc = 0.f, accz = 0.f;
 #pragma unroll
-  for (int w = 0; w < 8; ++w) {
+  for (int w = 0; w < PARTS; ++w) {
     acc += fsum_s[(w * 4 + qi) * 128 + j];
     if (VPROD) accz += fsumz_s[(w * 4 + qi) * 128 + j];
   }
   if (!VSPLIT) acc *= ldexpf(1.f, enu - 28);
   if (VPROD) accz *= ldexpf(1.f, eng - 28);
   const int64_t row = (int64_t)group * a.q_per_group + q0 + qi;
+  auto summed = [&] {
+    float l = 0.f;
+#pragma unroll
+    for (int w = 0; w < WAVES; ++w) l += red_s[64 + w * 4 + qi];
+    return l;
+  };
   if constexpr (!FINISH) {
     if (q0 + qi < a.q_per_group) {
       float* o = a.part + (row * a.nchunks + chunk) * attend_part_stride(128);
       o[4 + j] = acc;
       o[4 + 128 + j] = accz;
       if (j == 0) {
-        float l = 0.f, mq = -INFINITY;
+        float mq = -INFINITY;
 #pragma unroll
-        for (int w = 0; w < 8; ++w) {
-          l += red_s[64 + w * 4 + qi];
-          mq = fmaxf(mq, red_s[w * 4 + qi]);
-        }
+        for (int w = 0; w < WAVES; ++w) mq = fmaxf(mq, red_s[w * 4 + qi]);
         o[0] = mq * 0.693147180559945309f;  // back to natural units
-        o[1] = l;
+        o[1] = summed();
       }
     }
   } else {
-  // (as the joining kernel does it, sums in the same order)
-  float* const y_s = reinterpret_cast<float*>(dyn_s + FIRST);  // [index term, sign term][coordinate][query], over the words
-  static_assert(attend128_words_bytes(VB, TWO, TILES) >= (VPROD ? 2 : 1) * 512 * 4, "LDS");
-  float l = 0.f;
+    const float l = summed();
+    static_assert(attend128_words_bytes(VB, TWO, TILES, WAVES) >= (VPROD ? 2 : 1) * 512 * 4, "LDS");
+    y_s[qi * 128 + j] = acc / l;
+    if (VPROD) y_s[512 + qi * 128 + j] = accz / l;
+  }
+  }
+  if constexpr (FINISH) {
+    __syncthreads();
+    // (a wavefront's rows are ROWS consecutive ones: the first of four values per lane of 16, of which ROWS / 4 count)
+    auto rotated = [&](const float (&w)[ROWS], const float* y, float (&o)[4]) {
+      f32x4_prep v[4];
 #pragma unroll
-  for (int w = 0; w < 8; ++w) l += red_s[64 + w * 4 + qi];
-  y_s[j * 4 + qi] = acc / l;
-  if (VPROD) y_s[512 + j * 4 + qi] = accz / l;
-  __syncthreads();
+      for (int k = 0; k < 4; ++k) {
+        v[k] = *reinterpret_cast<const f32x4*>(y + k * 128 + ROWS * part0 + 4 * (tid & (ROWS / 4 - 1)));
+        o[k] = 0.f;
+      }
+      matvec_rows<0, ROWS / 4>(o, v, w);
+    };
+    float o[4], oz[4] = {0.f, 0.f, 0.f, 0.f};
+    rotated(wp, y_s, o);
+    if constexpr (VPROD) rotated(ws, y_s + 512, oz);
 #pragma unroll
-  for (int h16 = 0; h16 < 2; ++h16) {
-    float o[4] = {0.f, 0.f, 0.f, 0.f}, oz[4] = {0.f, 0.f, 0.f, 0.f};
+    for (int k = 0; k < 4; ++k) fsum_s[(part0 * 4 + k) * 128 + j] = VPROD ? fmaf(a.kappa, oz[k], o[k]) : o[k];
+    __syncthreads();
 #pragma unroll
-    for (int u = 16 * h16; u < 16 * h16 + 16; ++u) {
-      const f32x4 y = *reinterpret_cast<const f32x4*>(y_s + (32 * qi + u) * 4);
+    for (int rq = 0; rq < ROUNDS_Q; ++rq) {
+      const int qi = part0 + rq * QUERIES;
+      if (q0 + qi < a.q_per_group) {
+        float r = fsum_s[qi * 128 + j];
 #pragma unroll
-      for (int k = 0; k < 4; ++k) o[k] = fmaf(wp[u], y[k], o[k]);
-      if constexpr (VPROD) {
-        const f32x4 z = *reinterpret_cast<const f32x4*>(y_s + 512 + (32 * qi + u) * 4);
-#pragma unroll
-        for (int k = 0; k < 4; ++k) oz[k] = fmaf(ws[u], z[k], oz[k]);
+        for (int t = 1; t < WAVES / 2; ++t) r += fsum_s[(t * 4 + qi) * 128 + j];
+        a.out[((int64_t)group * a.q_per_group + q0 + qi) * a.ldo + j] = r;
       }
     }
-#pragma unroll
-    for (int k = 0; k < 4; ++k) fsum_s[((2 * qi + h16) * 4 + k) * 128 + j] = fmaf(a.kappa, oz[k], o[k]);
-  }
-  __syncthreads();
-  if (q0 + qi < a.q_per_group) {
-    float r = fsum_s[qi * 128 + j];
-#pragma unroll
-    for (int t = 1; t < 8; ++t) r += fsum_s[(t * 4 + qi) * 128 + j];
-    a.out[row * a.ldo + j] = r;
-  }
   }
 }
 
-template <int KB, bool KPROD, int VB, int VKIND, bool FUSED, int TILES, bool FINISH>
+template <int KB, bool KPROD, int VB, int VKIND, bool FUSED, int TILES, int WAVES, bool FINISH>
 hipError_t launch_attend128_tiles(const ScoreI8Args& ka, const AttendArgs& a, const AttendCoefs& cf, const AttendCoefs& cfh,
                                 int n_groups, hipStream_t s) {
-  constexpr int lds = attend128_lds(KB, VB, VKIND != 0, FUSED, TILES);
+  constexpr int lds = attend128_lds(KB, VB, VKIND != 0, FUSED, TILES, WAVES);
   static_assert(lds <= 160 * 1024, "LDS budget");
   static LdsLimit lds_limit;  // per instantiation: the limit is raised once per device
-  if (const hipError_t e = raise_lds_limit(lds_limit, reinterpret_cast<const void*>(&attend128_kernel<KB, KPROD, VB, VKIND, FUSED, TILES, FINISH>), lds); e != hipSuccess) return e;
+  if (const hipError_t e = raise_lds_limit(lds_limit, reinterpret_cast<const void*>(&attend128_kernel<KB, KPROD, VB, VKIND, FUSED, TILES, WAVES, FINISH>), lds); e != hipSuccess) return e;
   const dim3 grid(a.nchunks, n_groups, (a.q_per_group + 3) / 4);
-  hipLaunchKernelGGL((attend128_kernel<KB, KPROD, VB, VKIND, FUSED, TILES, FINISH>), grid, dim3(512), lds, s, ka, a, cf, cfh);
+  hipLaunchKernelGGL((attend128_kernel<KB, KPROD, VB, VKIND, FUSED, TILES, WAVES, FINISH>), grid, dim3(64 * WAVES), lds, s, ka, a, cf, cfh);
   return hipGetLastError();
 }
 
 template <int KB, bool KPROD, int VB, int VKIND, bool FUSED>
 hipError_t launch_attend128_one(const ScoreI8Args& ka, const AttendArgs& a, const AttendCoefs& cf, const AttendCoefs& cfh,
                                 int n_groups, hipStream_t s) {
-  if (a.out != nullptr) return launch_attend128_tiles<KB, KPROD, VB, VKIND, FUSED, AT_TILES_SHORT, true>(ka, a, cf, cfh, n_groups, s);
-  return a.tiles == AT_TILES_SHORT ? launch_attend128_tiles<KB, KPROD, VB, VKIND, FUSED, AT_TILES_SHORT, false>(ka, a, cf, cfh, n_groups, s)
-                                   : launch_attend128_tiles<KB, KPROD, VB, VKIND, FUSED, AT_TILES, false>(ka, a, cf, cfh, n_groups, s);
+  switch (a.keys * 2 + (a.out != nullptr ? 1 : 0)) {
+    case 2 * 256: return launch_attend128_tiles<KB, KPROD, VB, VKIND, FUSED, 4, 4, false>(ka, a, cf, cfh, n_groups, s);
+    case 2 * 256 + 1: return launch_attend128_tiles<KB, KPROD, VB, VKIND, FUSED, 4, 4, true>(ka, a, cf, cfh, n_groups, s);
+    case 2 * 512: return launch_attend128_tiles<KB, KPROD, VB, VKIND, FUSED, 4, 8, false>(ka, a, cf, cfh, n_groups, s);
+    case 2 * 512 + 1: return launch_attend128_tiles<KB, KPROD, VB, VKIND, FUSED, 4, 8, true>(ka, a, cf, cfh, n_groups, s);
+    case 2 * 2048: return launch_attend128_tiles<KB, KPROD, VB, VKIND, FUSED, 16, 8, false>(ka, a, cf, cfh, n_groups, s);
+    default: return hipErrorInvalidValue;
+  }
 }
 
 // all key variants for one kind of value code; kb < 0: logits from a.scores

@@ -49,15 +49,16 @@ constexpr int SCORE128_ROUND_TILES = 4, SCORE128_ROUNDS_AHEAD = 2;
 __host__ __device__ constexpr int stage_bytes(int bits) { return 16 * SCORE128_ROUND_TILES * (16 * bits + 16 + 4 + 4); }
 
 // staging regions, partial sums of the query preparation (8 KB), one 2 KB digit image per masked sum, scalars
-__host__ __device__ constexpr int score128_lds(int bits) { return 8 * stage_bytes(bits) + I8_PART_FLOATS * 4 + i8_terms(bits, true) * 2048 + 2 * 4 * 4 * 4; }
+__host__ __device__ constexpr int score128_lds(int bits, int waves = 8) { return waves * stage_bytes(bits) + I8_PART_FLOATS * 4 + i8_terms(bits, true) * 2048 + 2 * 4 * 4 * 4; }
 
 // The whole kernel as a function of where a finished score goes: sink(t, score, key_live) is
 // called once per tile t (TILES tiles of 16 keys per wavefront) by every lane with the score of
-// (query q0 + lane / 16, key wave_key0 + 16 t + lane % 16), wave_key0 = (8 blockIdx.x + wave) * 16 TILES.
-// dyn_s: score128_lds(BITS) bytes, 8 staging regions, then the query preparation.  All of LDS may be reused after the workgroup's
+// (query q0 + lane / 16, key wave_key0 + 16 t + lane % 16), wave_key0 = (WAVES blockIdx.x + wave) * 16 TILES.
+// WAVES: 8, or 4 (one per SIMD, each with twice as much of the query preparation).
+// dyn_s: score128_lds(BITS, WAVES) bytes, staging regions, then the query preparation.  All of LDS may be reused after the workgroup's
 // next barrier.
 // meanwhile(): what the caller has to do that waits for nothing, while the first loads are on their way.
-template <int BITS, bool PROD, int TILES, class Sink, class Meanwhile>
+template <int BITS, bool PROD, int TILES, int WAVES = 8, class Sink, class Meanwhile>
 __device__ __forceinline__ void score128_body(const ScoreI8Args& a, unsigned char* dyn_s, Sink& sink, Meanwhile meanwhile) {
   constexpr int RT = SCORE128_ROUND_TILES < TILES ? SCORE128_ROUND_TILES : TILES;
   constexpr int ROWS = 16 * RT;               // rows staged per round
@@ -83,19 +84,25 @@ __device__ __forceinline__ void score128_body(const ScoreI8Args& a, unsigned cha
   const int q0 = blockIdx.z * 4;
 
   unsigned char* const stage = dyn_s + wave * stage_bytes(BITS);
-  float* const part_s = reinterpret_cast<float*>(dyn_s + 8 * stage_bytes(BITS));        // [2][2][4][128]
+  float* const part_s = reinterpret_cast<float*>(dyn_s + WAVES * stage_bytes(BITS));    // [2][2][4][128]
   unsigned char* const dig_s = reinterpret_cast<unsigned char*>(part_s + I8_PART_FLOATS);  // [term][4][4][128]
   float* const scal_s = reinterpret_cast<float*>(dig_s + i8_terms(BITS, true) * 2048);  // [2][4][4]
 
   // ---- 1. this thread's column of the transposed matrix: 64 values of k ---------------------
-  I8Prep<(BITS > 0), PROD> prep;
-  prep.load(a, group, q0, wave, tid);
+  static_assert(WAVES == 8 || WAVES == 4, "");
+  I8Prep<(BITS > 0), PROD> prep[8 / WAVES];
+  if constexpr (WAVES == 8) {
+    prep[0].load(a, group, q0, wave, tid);
+  } else {
+#pragma unroll
+    for (int half = 0; half < 2; ++half) prep[half].load_part(a, group, q0, wave >> 1, half, tid);
+  }
 
   // ---- 2. the codes of this wavefront's keys, as contiguous 16-byte pieces ---------------------
   // Pieces past the end of the arrays are clamped onto the last one (never used: the
   // scores of keys past the end are not stored).
   const int64_t gbase = (int64_t)group * a.group_stride;
-  const int64_t wave_key0 = ((int64_t)blockIdx.x * 8 + wave) * (16 * TILES);
+  const int64_t wave_key0 = ((int64_t)blockIdx.x * WAVES + wave) * (16 * TILES);
   const bool full = wave_key0 + 16 * TILES <= a.n;  // uniform: no key of this wavefront is past the end
   const int64_t wrow0 = gbase + wave_key0;
   u32x4 ci[ROUNDS][NI > 0 ? NI : 1], cq[ROUNDS][NQ > 0 ? NQ : 1];
@@ -141,10 +148,12 @@ __device__ __forceinline__ void score128_body(const ScoreI8Args& a, unsigned cha
   // ---- 3. rotate / sketch this workgroup's four queries, 4. fixed point --------------------------
   // (each phase by itself: mixed into each other by the compiler, they wait for one another's operands)
   __builtin_amdgcn_sched_barrier(0);
-  prep.matvec(part_s);
+#pragma unroll
+  for (int half = 0; half < 8 / WAVES; ++half) prep[half].matvec(part_s);
   __builtin_amdgcn_sched_barrier(0);
   __syncthreads();
-  i8_digitise_terms<BITS, PROD>(a, q0, wave, lane, part_s, dig_s, scal_s);
+#pragma unroll
+  for (int w = 0; w < 8; w += WAVES) i8_digitise_terms<BITS, PROD>(a, q0, w + wave, lane, part_s, dig_s, scal_s);
   __syncthreads();  // digits and scalars are in LDS
   __builtin_amdgcn_sched_barrier(0);
 

@@ -58,6 +58,25 @@ __device__ __forceinline__ int wave_sum(int v) {
 
 typedef float f32x4_prep __attribute__((ext_vector_type(4), aligned(4)));  // (the queries are the caller's)
 
+// acc[q] += sum over k = 4 I .. 4 N - 1 of w[k] * (coordinate k of vector q), which lane k / 4 of every row of 16 holds in q[q][k % 4]:
+// fetched from there in one instruction with its product.  (The compiler makes two of it.  It does not look inside: s_nop is the
+// distance that a register moved just before needs from its use by other lanes.)
+template <int I, int N>
+__device__ __forceinline__ void matvec_rows(float (&acc)[4], const f32x4_prep (&q)[4], const float (&wv)[4 * N]) {
+#define TQ_FMAC(ACC, Q, W) "\n\tv_fmac_f32_dpp %" #ACC ", %" #Q ", %" #W " row_newbcast:%24 row_mask:0xf bank_mask:0xf"
+  asm("s_nop 1"
+      TQ_FMAC(0, 4, 20) TQ_FMAC(1, 8, 20) TQ_FMAC(2, 12, 20) TQ_FMAC(3, 16, 20)
+      TQ_FMAC(0, 5, 21) TQ_FMAC(1, 9, 21) TQ_FMAC(2, 13, 21) TQ_FMAC(3, 17, 21)
+      TQ_FMAC(0, 6, 22) TQ_FMAC(1, 10, 22) TQ_FMAC(2, 14, 22) TQ_FMAC(3, 18, 22)
+      TQ_FMAC(0, 7, 23) TQ_FMAC(1, 11, 23) TQ_FMAC(2, 15, 23) TQ_FMAC(3, 19, 23)
+      : "+v"(acc[0]), "+v"(acc[1]), "+v"(acc[2]), "+v"(acc[3])
+      : "v"(q[0][0]), "v"(q[0][1]), "v"(q[0][2]), "v"(q[0][3]), "v"(q[1][0]), "v"(q[1][1]), "v"(q[1][2]), "v"(q[1][3]), "v"(q[2][0]),
+        "v"(q[2][1]), "v"(q[2][2]), "v"(q[2][3]), "v"(q[3][0]), "v"(q[3][1]), "v"(q[3][2]), "v"(q[3][3]), "v"(wv[4 * I]),
+        "v"(wv[4 * I + 1]), "v"(wv[4 * I + 2]), "v"(wv[4 * I + 3]), "n"(I));
+#undef TQ_FMAC
+  if constexpr (I + 1 < N) matvec_rows<I + 1, N>(acc, q, wv);
+}
+
 template <bool HAVE_R, bool PROD>
 struct I8Prep {
   float wv[64];
@@ -66,8 +85,11 @@ struct I8Prep {
   bool work;
 
   __device__ __forceinline__ void load(const ScoreI8Args& a, int group, int q0, int wave, int tid) {
-    mat = wave >> 2;
-    kh = (wave >> 1) & 1;
+    load_part(a, group, q0, wave >> 2, (wave >> 1) & 1, tid);
+  }
+  __device__ __forceinline__ void load_part(const ScoreI8Args& a, int group, int q0, int matrix, int half, int tid) {
+    mat = matrix;
+    kh = half;
     j = tid & 127;
     work = mat == 0 ? HAVE_R : PROD;  // uniform
     if (work) {
@@ -87,27 +109,10 @@ struct I8Prep {
     }
   }
 
-  // k = 4 I .. 4 I + 3: a query's coordinate from lane I of the row, in one instruction with its product.  (The compiler makes two of
-  // it.  It does not look inside: s_nop is the distance that a register moved just before needs from its use by other lanes.)
-  template <int I>
-  __device__ __forceinline__ void matvec_step(float (&acc)[4]) {
-#define TQ_FMAC(ACC, Q, W) "\n\tv_fmac_f32_dpp %" #ACC ", %" #Q ", %" #W " row_newbcast:%24 row_mask:0xf bank_mask:0xf"
-    asm("s_nop 1"
-        TQ_FMAC(0, 4, 20) TQ_FMAC(1, 8, 20) TQ_FMAC(2, 12, 20) TQ_FMAC(3, 16, 20)
-        TQ_FMAC(0, 5, 21) TQ_FMAC(1, 9, 21) TQ_FMAC(2, 13, 21) TQ_FMAC(3, 17, 21)
-        TQ_FMAC(0, 6, 22) TQ_FMAC(1, 10, 22) TQ_FMAC(2, 14, 22) TQ_FMAC(3, 18, 22)
-        TQ_FMAC(0, 7, 23) TQ_FMAC(1, 11, 23) TQ_FMAC(2, 15, 23) TQ_FMAC(3, 19, 23)
-        : "+v"(acc[0]), "+v"(acc[1]), "+v"(acc[2]), "+v"(acc[3])
-        : "v"(q[0][0]), "v"(q[0][1]), "v"(q[0][2]), "v"(q[0][3]), "v"(q[1][0]), "v"(q[1][1]), "v"(q[1][2]), "v"(q[1][3]), "v"(q[2][0]),
-          "v"(q[2][1]), "v"(q[2][2]), "v"(q[2][3]), "v"(q[3][0]), "v"(q[3][1]), "v"(q[3][2]), "v"(q[3][3]), "v"(wv[4 * I]),
-          "v"(wv[4 * I + 1]), "v"(wv[4 * I + 2]), "v"(wv[4 * I + 3]), "n"(I));
-#undef TQ_FMAC
-    if constexpr (I + 1 < 16) matvec_step<I + 1>(acc);
-  }
   __device__ __forceinline__ void matvec(float* part_s) {
     if (!work) return;
     float acc[4] = {0.f, 0.f, 0.f, 0.f};
-    matvec_step<0>(acc);
+    matvec_rows<0, 16>(acc, q, wv);
 #pragma unroll
     for (int qi = 0; qi < 4; ++qi) part_s[((mat * 2 + kh) * 4 + qi) * 128 + j] = acc[qi];
   }

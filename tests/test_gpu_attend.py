@@ -117,7 +117,7 @@ def test_attend_at_the_edges_of_blocks_and_passes(vb, vprod, n_groups, qpg, npg)
 
 @pytest.mark.parametrize("fused", [True, False])  # logits from the read-out kernel itself, from a scoring call
 @pytest.mark.parametrize("vb,vprod,qpg", [(2, False, 4), (0, True, 5), (2, True, 1), (4, False, 7)])
-@pytest.mark.parametrize("npg", [1, 511, 512, 513])  # one chunk, whose workgroup rotates its sums back itself, and two
+@pytest.mark.parametrize("npg", [1, 256, 257, 511, 512, 513, 1100])  # one chunk, whose workgroup rotates its sums back itself, and more
 def test_attend_over_one_chunk(vb, vprod, qpg, npg, fused):
     run_attend(128, 2, True, vb, vprod, 3, qpg, npg, fused)
 
