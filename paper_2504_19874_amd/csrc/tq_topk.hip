@@ -14,6 +14,7 @@
 // k = 64, 29.2 -> 6.1; 5 of 30000, k = 16, 13.4 -> 7.0; 4 of 10^6, k = 10, with the joining 9.9 -> 9.2; 14 of 84645, k = 64, 22.2 -> 11.2.
 #include "tq_select.h"
 
+#include <algorithm>
 #include <type_traits>
 
 namespace tq {
@@ -99,12 +100,17 @@ __global__ __launch_bounds__(T) void topk_merge_kernel(const float* __restrict__
 //   10 rows of 20000, k = 64   8.2 / 10.8
 //   2 rows of 49000, k = 64   10.7 / 10.4;  60: 12.0 / 10.9;  2 of 33000 9.1 / 10.3
 //   2 rows of 49000, k = 10    8.0 /  8.1;  60: 8.5 / 8.7
-//   100 rows of 41500, k = 64 11.7 / 15.2 (what more rows than compute units for their chunks lose; 23.6 before)
+//   100 rows of 41500, k = 64 11.5 / 13.9 (what more rows than compute units for their chunks lose; 23.6 before)
 //   2 rows of 56430, k = 10    9.6 /  8.4
 //   14 rows of 84645, k = 64  18.1 / 11.2
+// More segments than compute units: as many chunks as make two workgroups of 512 threads for each, all of them at work at once, so that a second
+// segment costs its 2 us only.  us, chunks of a segment / so (a workgroup per row):
+//   32 rows of 400000, k = 10  22.4 / 16.8 (42);  64 of 10^6 72.0 / 43.4 (91);  128 of 300000 47.4 / 29.5 (37)
+//   32 rows of 10^6, k = 64    50.6 / 34.3 (132);  128 of 200000 44.3 / 31.1 (37);  8 of 10^6, k = 10 12.5 / 10.9 (80)
 int topk_chunks(int64_t rows, int64_t n, int k) {
   if (k < 1 || rows < 1 || rows > 128 || n <= (k <= 16 ? 3 * SEG : 5 * SEG / 2)) return 0;
   int64_t c = (n + SEG - 1) / SEG;
+  if (const int64_t cus = device_cu_count(); rows * c > cus) c = std::min(c, 2 * cus / rows);
   if (c > 4096 / k) c = 4096 / k;
   return c >= 2 ? (int)c : 0;
 }
@@ -135,7 +141,7 @@ hipError_t launch_topk(const float* scores, int64_t rows, int64_t n, int64_t ld,
     return hipGetLastError();
   };
   if (len <= 256 * PER || (crowd && k <= 16)) return go(std::integral_constant<int, 256>{});
-  if (len <= 512 * PER || crowd) return go(std::integral_constant<int, 512>{});
+  if (len <= 512 * PER || crowd || (chunks > 0 && rows * chunks > device_cu_count())) return go(std::integral_constant<int, 512>{});
   return go(std::integral_constant<int, THREADS>{});
 }
 

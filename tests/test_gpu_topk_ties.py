@@ -73,7 +73,8 @@ def test_chunks_and_bars(kind, nq, n, topk):
 
 
 @pytest.mark.parametrize("nq,n", [(2, 63), (2, 4096), (2, 4097), (2, 8193),  # fewer than k; a segment of 256 threads, of 512, of 1024
-                                  (2, 3 * 16384), (2, 3 * 16384 + 1), (513, 20001)])  # three segments, chunks from there, more rows than workgroups fit
+                                  (2, 3 * 16384), (2, 3 * 16384 + 1), (513, 20001),  # three segments, chunks from there, more rows than workgroups fit
+                                  (65, 65537), (128, 70001)])  # more chunks than compute units: as many of 512 threads, fewer
 @pytest.mark.parametrize("topk", [16, 64])  # bars from 64 maxima, from 256
 @pytest.mark.parametrize("kind", ["drawn", "falling", "equal", "zeros", "infinite"])
 def test_segments_and_threads(kind, nq, n, topk):
