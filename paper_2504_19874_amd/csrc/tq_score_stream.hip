@@ -41,11 +41,13 @@ struct StreamArgs {
   int64_t n;
   int groups_d;  // d / 32
   int q_per_group;
+  int qblocks, shares;  // of queries, of keys
   int slots;  // blocks of keys whose scores a wavefront gathers in LDS
   float kappa;
   float coef[16];
 };
 
+constexpr int XCDS = 8;
 constexpr int kMaxLdsBytes = 159 * 1024;  // digits and gathered scores (scal_s besides)
 
 typedef int v8i __attribute__((ext_vector_type(8)));
@@ -121,14 +123,22 @@ __global__ __launch_bounds__(512, 2) void score_stream_kernel(const StreamArgs a
   using C = StreamCfg<BITS, PROD, QB>;
   constexpr int T = SHORT ? 1 : C::tiles(W), NV = C::NV, NT = C::NT;
   constexpr int NM = (1 << BITS) - 1;
+  fetch_arguments<sizeof(StreamArgs)>();
   // [step][W][matrix][query block][lane]: four words of a lane's 32 digits, then two
   extern __shared__ __attribute__((aligned(16))) u32x4 dig_s[];
   __shared__ float scal_s[4 * QB][4];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int col = lane & 15, kq = lane >> 4;
+  // the query blocks of one share of the keys follow each other on an XCD and share its L2
+  int share = blockIdx.x, q0 = 0;
+  if (a.qblocks > 1) {
+    const int logical = (int)(blockIdx.x % XCDS) * (int)(gridDim.x / XCDS) + (int)(blockIdx.x / XCDS);
+    share = logical / a.qblocks;
+    q0 = (logical - share * a.qblocks) * (4 * QB);
+    if (share >= a.shares) return;
+  }
   const int group = blockIdx.y;
-  const int q0 = blockIdx.z * (4 * QB);
   const int G = a.groups_d, steps = G / (4 * W);
   const int64_t gbase = (int64_t)group * a.n;
 
@@ -136,8 +146,8 @@ __global__ __launch_bounds__(512, 2) void score_stream_kernel(const StreamArgs a
   // 4 W step + W kq .. + W - 1
   const int64_t nblk = (a.n + 16 * T - 1) / (16 * T);
   const int waves = blockDim.x >> 6;
-  const int64_t stride = (int64_t)gridDim.x * waves;
-  int64_t blk = (int64_t)blockIdx.x * waves + wave;
+  const int64_t stride = (int64_t)a.shares * waves;
+  int64_t blk = (int64_t)share * waves + wave;
   // the digits of query qa of this workgroup, matrix v of the NV
   auto image = [&](int qa, int v) -> const uint32_t* {
     const int64_t q = (int64_t)group * a.q_per_group + (q0 + qa < a.q_per_group ? q0 + qa : a.q_per_group - 1);
@@ -335,7 +345,10 @@ hipError_t launch_t(StreamArgs a, int64_t gx, int qz, int threads, int per_cu, i
   a.slots = SHORT ? 0 : std::max(1, std::min(8, (kMaxLdsBytes / per_cu - digits) / slot));
   const int lds = digits + a.slots * slot;
   if (lds > kMaxLdsBytes) return hipErrorInvalidValue;  // (d <= 4096 and launch_bits' choice keep it below)
-  hipLaunchKernelGGL((score_stream_kernel<BITS, PROD, W, QB, SHORT>), dim3((unsigned)gx, n_groups, (unsigned)qz), dim3(threads), lds, s, a);
+  a.qblocks = qz;
+  a.shares = (int)gx;
+  const int64_t wgs = qz > 1 ? (gx * qz + XCDS - 1) / XCDS * XCDS : gx;
+  hipLaunchKernelGGL((score_stream_kernel<BITS, PROD, W, QB, SHORT>), dim3((unsigned)wgs, n_groups), dim3(threads), lds, s, a);
   return hipGetLastError();
 }
 
@@ -346,32 +359,49 @@ hipError_t launch_w(const StreamArgs& a, int n_groups, hipStream_t s) {
   const int qz = (a.q_per_group + 4 * QB - 1) / (4 * QB);
   const int64_t others = (int64_t)n_groups * qz, cus = device_cu_count();
   // one workgroup per compute unit (two where registers and LDS admit them), each walking its share of the keys; a list too
-  // short for that in wavefronts of one tile and workgroups of four (10^4 codes of 3072 coordinates, 2 queries, 3 + 1 bits: 20.9 us -> 16.6)
+  // short for that in wavefronts of one tile and workgroups of four (10^4 codes of 3072 coordinates, 2 queries, 3 + 1 bits: 20.9 us -> 16.6),
+  // if little more of these come to a compute unit than its LDS holds at once (16 queries of 3072, 1 + 1 bits, 20000 codes: 64 -> 54).  No more
+  // workgroups than there is room for: the last few made a second round (24 queries of 768, 2 bits, 300000 codes: 258 of them 59.9, 255 41.4).
   const int64_t nwg = (a.n + 128 * T - 1) / (128 * T);
-  if (nwg * others * 4 <= cus * 3) return launch_t<BITS, PROD, W, QB, true>(a, (a.n + 63) / 64, qz, 256, 1, n_groups, s);
+  const int64_t short_wgs = (a.n + 63) / 64 * others, digits = a.groups_d * C::NV * QB * 384;
+  if (nwg * others * 4 <= cus * 3 && short_wgs * 4 <= cus * 5 * std::min<int64_t>(4, kMaxLdsBytes / digits))
+    return launch_t<BITS, PROD, W, QB, true>(a, (a.n + 63) / 64, qz, 256, 1, n_groups, s);
   const int per_cu = C::NT * QB * T <= 4 && a.groups_d * C::NV * QB * 384 <= 72 * 1024 ? 2 : 1;
-  int64_t gx = (per_cu * cus + others - 1) / others;
+  int64_t gx = std::max<int64_t>(1, per_cu * cus / others);
   if (gx > nwg) gx = nwg;
   return launch_t<BITS, PROD, W, QB, false>(a, gx, qz, 512, per_cu, n_groups, s);
+}
+
+// word groups per step for rows of 128 m coordinates
+template <int BITS, bool PROD, int QB>
+constexpr int stream_words(int m) {
+  using C = StreamCfg<BITS, PROD, QB>;
+  for (int w : {12, 8, 6, 4, 3, 2})
+    if (C::takes(w) && (w == 6 || w == 12 ? m == w : m % w == 0)) return w;
+  return 1;
 }
 
 template <int BITS, bool PROD, int QB>
 hipError_t launch_qb(const StreamArgs& a, int n_groups, hipStream_t s) {
   using C = StreamCfg<BITS, PROD, QB>;
-  const int m = a.groups_d / 4;
-#define TQ_STREAM_W(W)          \
+  const int words = stream_words<BITS, PROD, QB>(a.groups_d / 4);
+#define TQ_STREAM_W(W)       \
   if constexpr (C::takes(W)) \
-    if (W == 6 || W == 12 ? m == W : m % W == 0) return launch_w<BITS, PROD, W, QB>(a, n_groups, s);
+    if (words == W) return launch_w<BITS, PROD, W, QB>(a, n_groups, s);
   TQ_STREAM_W(12) TQ_STREAM_W(8) TQ_STREAM_W(6) TQ_STREAM_W(4) TQ_STREAM_W(3) TQ_STREAM_W(2)
 #undef TQ_STREAM_W
   return launch_w<BITS, PROD, 1, QB>(a, n_groups, s);
 }
 
-// four queries per pass over the codes, or eight where there are more than four and their digits fit LDS beside a block's scores
+// four queries per pass over the codes, or eight where there are more than four and their digits fit LDS beside a block's scores; digits that
+// fill it only where two passes become one over a long list (us, four / eight, 3072 coordinates, 1 + 1 bits: 9 queries, 300000 codes 208 / 130;
+// 60000 77 / 63; 16 queries, 32768 codes 55 / 63; 5 queries, 60000 codes 50 / 59)
 template <int BITS, bool PROD>
 hipError_t launch_bits(const StreamArgs& a, int n_groups, hipStream_t s) {
   using C = StreamCfg<BITS, PROD, 2>;
-  const bool eight = a.q_per_group > 4 && a.groups_d * C::NV * 2 * 384 + 512 * 2 * C::T * 4 <= kMaxLdsBytes;
+  const int digits = a.groups_d * C::NV * 2 * 384, slot = 512 * 2 * C::tiles(stream_words<BITS, PROD, 2>(a.groups_d / 4)) * 4;
+  bool eight = a.q_per_group > 4 && digits + slot <= kMaxLdsBytes;
+  if (digits > 140 * 1024) eight = eight && a.q_per_group > 8 && a.n >= 49152;
   return eight ? launch_qb<BITS, PROD, 2>(a, n_groups, s) : launch_qb<BITS, PROD, 1>(a, n_groups, s);
 }
 

@@ -46,3 +46,18 @@ def test_one_call_and_pieces(d, bits, prod, n, nq):
         xt = o.dequant_mse(planes, Pi, c32, nrm)
     qh = q.cpu().numpy()
     T.P.check_close(wide[:, :k].cpu().numpy(), o.score(qh, xt), np.linalg.norm(qh.astype(np.float64), axis=1)[:, None] * nrm[None], "score")
+
+
+@pytest.mark.parametrize("d,bits,prod,n,groups,nq", [(256, 2, False, 30011, 1, 20), (512, 1, True, 9001, 3, 9), (768, 3, True, 50003, 1, 32), (256, 4, False, 130, 5, 33),
+                                                     (3072, 1, True, 49151, 1, 9), (3072, 1, True, 49152, 1, 9), (384, 2, True, 16001, 1, 61)])
+def test_blocks_of_queries(d, bits, prod, n, groups, nq):
+    """Several blocks of queries over the same codes, some of them not full, in grids that are no multiple of the XCDs: the bits of one query at a time."""
+    p = T.setup(d, bits, prod)[0]
+    c = T._random_codes(p, d, bits, prod, groups * n, d + n)
+    q = torch.randn(groups * nq, d, device=T.DEV, generator=torch.Generator(device=T.DEV).manual_seed(n))
+    p.reserve(1, groups * nq, 0)
+    out, one = torch.zeros((groups * nq, n), device=T.DEV), torch.zeros((groups, n), device=T.DEV)
+    tq.tq_score(p, q, groups, nq, c["idx"], c["qjl"], c["gamma"], c["norm"], n, out)
+    for i in (0, 3, 4, 7, 8, nq - 1):
+        tq.tq_score(p, q.view(groups, nq, d)[:, i].contiguous(), groups, 1, c["idx"], c["qjl"], c["gamma"], c["norm"], n, one)
+        assert torch.equal(out.view(groups, nq, n)[:, i], one)
