@@ -93,7 +93,7 @@ __global__ __launch_bounds__(256) void search_prepare_kernel(const int d, const 
     inv[q] = si;
     e1[q] = 1.01f * (t[1] + (f.c_rel + f.acc_rel) * (t[0] + t[1])) * f.c_norm;
     e2[q] = 1.01f * (t[3] + f.acc_rel * t[2]) * f.sqrt_d;
-    count[q] = 0;
+    count[q * COUNT_STEP] = 0;
     flags[q] = 0;
   }
 }
@@ -128,7 +128,7 @@ __global__ __launch_bounds__(T) void search_select_kernel(const SelectArgs a) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int64_t q = blockIdx.x;
   const int d = a.d, k = a.topk;
-  const int total = a.count[q];
+  const int total = a.count[q * COUNT_STEP];
   if (total > CAP) {
     if (tid == 0) a.flags[q] = 1;
     return;
@@ -326,7 +326,7 @@ struct SearchSpace {
     inv = take((size_t)nq * 4);
     e1 = take((size_t)nq * 4);
     e2 = take((size_t)nq * 4);
-    count = take((size_t)nq * 4);
+    count = take((size_t)nq * COUNT_STEP * 4);
     total = at;
   }
 };

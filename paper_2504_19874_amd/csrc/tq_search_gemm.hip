@@ -312,7 +312,7 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void search_gemm_kernel(const Sear
       pend_q = f[tid];
       pend_code = f[C::FOUND + tid];
       pend_top = __int_as_float(f[2 * C::FOUND + tid]);
-      pend_pos = atomicAdd(a.count + pend_q, 1);
+      pend_pos = atomicAdd(a.count + (int64_t)pend_q * COUNT_STEP, 1);
     }
   };
 
@@ -451,7 +451,7 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void search_gemm_kernel(const Sear
                   f[0] = q;
                   f[C::FOUND] = code_i;
                   f[2 * C::FOUND] = __float_as_int(top);
-                } else if (const int pos = atomicAdd(a.count + q, 1); pos < a.cap) {
+                } else if (const int pos = atomicAdd(a.count + (int64_t)q * COUNT_STEP, 1); pos < a.cap) {
                   a.list_u[(int64_t)q * a.cap + pos] = top;
                   a.list_i[(int64_t)q * a.cap + pos] = code_i;
                 }
