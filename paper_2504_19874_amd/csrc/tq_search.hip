@@ -284,11 +284,14 @@ __global__ __launch_bounds__(T) void search_select_kernel(const SelectArgs a) {
     if (h == 0 && s < n) score[s] = nu * fmaf(kg, PROD ? acc2[0] : 0.f, c1 * acc1[0]);
   }
   __syncthreads();
-  // the k best of them, in the place of the query's pieces; a NaN is not returned
-  TopkLds<T, N>& best = *reinterpret_cast<TopkLds<T, N>*>(qp);
+  // the k best of them, in the scores' place (three workgroups per compute unit for four where they have one behind the pieces: 1000 queries of
+  // 768, 3 bits, 30.0 us for 19.1); a NaN is not returned
+  TopkLds<T, N>& best = *reinterpret_cast<TopkLds<T, N>*>(score);
+  static_assert(sizeof(TopkLds<T, N>) <= CAP * 4, "room");
   float v[N];
 #pragma unroll
   for (int i = 0; i < N; ++i) v[i] = i * T + tid < n ? score[i * T + tid] : __builtin_nanf("");
+  __syncthreads();
   const int kept = take_segment<T, N>(best, v, [&](int i) { return cand[i * T + tid]; }, k, 0, tid, n <= 64);
   write_best(best, kept, k, -1, a.out_idx + q * k, a.out_val != nullptr ? a.out_val + q * k : nullptr, tid);
 }
@@ -343,7 +346,7 @@ int64_t block_queries(int d, int64_t n, int64_t nq, int topk) {
 
 template <int BITS, bool PROD, int T>
 hipError_t launch_select_t(const SelectArgs& a, int nq, hipStream_t s) {
-  const int pieces = ((BITS > 0 ? 1 : 0) + (PROD ? 1 : 0)) * 2 * a.d * 2, lds = CAP * 8 + std::max(pieces, (int)sizeof(TopkLds<T, CAP / T>));
+  const int pieces = ((BITS > 0 ? 1 : 0) + (PROD ? 1 : 0)) * 2 * a.d * 2, lds = CAP * 8 + pieces;
   static LdsLimit lds_limit;  // per instantiation: the limit is raised once per device
   if (const hipError_t e = raise_lds_limit(lds_limit, reinterpret_cast<const void*>(&search_select_kernel<BITS, PROD, T>), 80 * 1024); e != hipSuccess)
     return e;
