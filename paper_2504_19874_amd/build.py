@@ -20,7 +20,7 @@ CALL_LIB = os.path.join(HERE, "_tqcall.so")  # the per-call half of the Python b
 PROBE_LIB = os.path.join(HERE, "libtqprobe.so")  # measurement aid of bench_kernels, not part of the library
 OBJ = os.path.join(HERE, "_build")
 
-SOURCES = ["tq_api.hip", "tq_gemm.hip", "tq_gemm_h2.hip", "tq_quant_rows.hip", "tq_d128.hip", "tq_d128_small.hip", "tq_d128_small_dq.hip", "tq_score_small.hip", "tq_code_gemm.hip", "tq_search.hip", "tq_search_gemm.hip", "tq_score_i8.hip", "tq_score_stream.hip", "tq_score_i8_128.hip", "tq_score_i8_split.hip", "tq_score_bf3.hip", "tq_d128_bf3.hip", "tq_q128_bf3.hip", "tq_q128_few.hip", "tq_sign_128.hip", "tq_sign_gemm.hip", "tq_stage.hip", "tq_attend.hip", "tq_attend_128.hip", "tq_attend_128_v1.hip", "tq_attend_128_v2.hip", "tq_attend_128_v3.hip", "tq_attend_128_v4.hip", "tq_attend_128_p0.hip", "tq_attend_128_p1.hip", "tq_attend_128_p2.hip", "tq_attend_128_s1.hip", "tq_attend_128_s2.hip", "tq_topk.hip",
+SOURCES = ["tq_api.hip", "tq_gemm.hip", "tq_gemm_h2.hip", "tq_quant_rows.hip", "tq_d128.hip", "tq_d128_small.hip", "tq_d128_small_dq.hip", "tq_score_small.hip", "tq_code_gemm.hip", "tq_search.hip", "tq_search_gemm.hip", "tq_search_few.hip", "tq_score_i8.hip", "tq_score_stream.hip", "tq_score_i8_128.hip", "tq_score_i8_split.hip", "tq_score_bf3.hip", "tq_d128_bf3.hip", "tq_q128_bf3.hip", "tq_q128_few.hip", "tq_sign_128.hip", "tq_sign_gemm.hip", "tq_stage.hip", "tq_attend.hip", "tq_attend_128.hip", "tq_attend_128_v1.hip", "tq_attend_128_v2.hip", "tq_attend_128_v3.hip", "tq_attend_128_v4.hip", "tq_attend_128_p0.hip", "tq_attend_128_p1.hip", "tq_attend_128_p2.hip", "tq_attend_128_s1.hip", "tq_attend_128_s2.hip", "tq_topk.hip",
            "tq_codebook.cpp", "tq_rotation.cpp", "tq_entropy.cpp"]
 HIP_FLAGS = ["-O3", "--offload-arch=gfx950", "-fPIC", "-std=c++17",
              "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]

@@ -38,8 +38,11 @@ hipError_t launch_code_dequant(int bits, bool prod, const void* pit_image, const
 // way through memory (searches, us, counters side by side / so: 64 queries, k = 64, 400000 codes of 128, 3 bits, 154 / 71; 40 queries, k = 10, 300000 of 768
 // 140 / 105; 300 queries 189 / 170).
 constexpr int COUNT_STEP = 32;
+// Bytes between the pieces of 32 coordinates of all queries and those of the next 32.  A kernel's step takes these of a block of queries: side by
+// side they are whole lines on all channels of the L2; a query's coordinates side by side, they were half lines a multiple of 2 KB apart (d = 1024).
+__host__ __device__ constexpr uint32_t search_step_bytes(int nq) { return (uint32_t)(nq + (nq & 1)) * 64u; }
 struct CodeSearch {
-  const void* r_pieces;  // [nq][d] fp16, the contraction's order (code_position): Pi q scaled
+  const void* r_pieces;  // [d / 32][nq][32] fp16 (search_step_bytes), the contraction's order (code_position): Pi q scaled
   const void* s_pieces;  // S q scaled
   int nq;
   const float *inv, *e1, *e2, *bar;

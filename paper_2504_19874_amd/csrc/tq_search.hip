@@ -77,8 +77,9 @@ __global__ __launch_bounds__(256) void search_prepare_kernel(const int d, const 
       }
       return make_uint2(o[0], o[1]);
     };
-    if (r != nullptr) *reinterpret_cast<uint2*>(r_pieces + (q * d) / 2 + g * 16 + k * 2) = pieces(r, s, si, sum[0], sum[1]);
-    if (z != nullptr) *reinterpret_cast<uint2*>(s_pieces + (q * d) / 2 + g * 16 + k * 2) = pieces(z, s * s_fac, si * f.s_rel, sum[2], sum[3]);
+    const int64_t at = (int64_t)g * (search_step_bytes(gridDim.x) / 4) + q * 16 + k * 2;
+    if (r != nullptr) *reinterpret_cast<uint2*>(r_pieces + at) = pieces(r, s, si, sum[0], sum[1]);
+    if (z != nullptr) *reinterpret_cast<uint2*>(s_pieces + at) = pieces(z, s * s_fac, si * f.s_rel, sum[2], sum[3]);
   }
 #pragma unroll
   for (int i = 0; i < 4; ++i) sum[i] = over_wavefront(sum[i], [](float x, float y) { return x + y; });
@@ -319,8 +320,8 @@ struct SearchSpace {
       at += align256(bytes);
       return o;
     };
-    r = take((size_t)nq * d * 2);
-    s = take((size_t)nq * d * 2);
+    r = take((size_t)search_step_bytes((int)nq) * (d / 32));
+    s = take((size_t)search_step_bytes((int)nq) * (d / 32));
     sample = take((size_t)nq * ((sample_codes(n, topk) + 3) / 4 * 4) * 4);
     list_u = take((size_t)nq * CAP * 4);
     list_i = take((size_t)nq * CAP * 4);

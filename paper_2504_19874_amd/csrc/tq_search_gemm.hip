@@ -18,7 +18,7 @@
 // given to four wavefronts each it was no faster at d = 3072 and slower elsewhere (registers).
 #include <cstring>
 
-#include "tq_code_decode.h"
+#include "tq_search_gemm.h"
 
 #include <type_traits>
 
@@ -28,28 +28,6 @@ namespace {
 typedef float floatx16 __attribute__((ext_vector_type(16)));
 
 constexpr int XCDS = 8;
-
-struct SearchGemmArgs {
-  const unsigned char* R;  // pieces of the rotated and of the sketched queries
-  const unsigned char* S;
-  int M, d;
-  const uint32_t* idx;
-  const uint32_t* qjl;
-  const float* gamma;
-  const float* norm;
-  int64_t n, code_step;
-  float kappa, s_rel;
-  CodeTable tab;
-  const float *q_inv, *e1, *e2, *bar;
-  int bar_step;
-  float* sample;
-  int64_t ld_sample;
-  float* list_u;
-  int32_t* list_i;
-  int32_t* count;
-  int cap;
-  int qblocks, ranges, tiles, per_xcd;
-};
 
 // Four coordinates (bit position 4 HALF + k of the four bytes) as two words of the contraction
 template <int BITS, int HALF>
@@ -122,9 +100,9 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void search_gemm_kernel(const Sear
   const int n_s = HAVE_S ? G : 0, n_steps = n_s + (HAVE_P ? G : 0);
 
   // ---- query pieces: direct loads, round and round -----------------------------------------------------
-  const uint32_t row_a = (uint32_t)a.d * 2u;
-  const unsigned char* const gP = a.R + (int64_t)m0 * row_a;
-  const unsigned char* const gS = HAVE_S ? a.S + (int64_t)m0 * row_a : gP;
+  const uint32_t step_a = search_step_bytes(a.M);
+  const unsigned char* const gP = a.R + m0 * 64;
+  const unsigned char* const gS = HAVE_S ? a.S + m0 * 64 : gP;
   const unsigned char* gA = gS;
   uint32_t va[AL];
   {
@@ -132,7 +110,7 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void search_gemm_kernel(const Sear
 #pragma unroll
     for (int j = 0; j < AL; ++j) {
       const int r = 2 * ((wave * AL + j) * 8 + l8) + (slot >> 2);
-      va[j] = (uint32_t)min(r, rows_m - 1) * row_a + h2_chunk<1>(r, slot) * 16;
+      va[j] = (uint32_t)min(r, rows_m - 1) * 64 + h2_chunk<1>(r, slot) * 16;
     }
   }
   const uint32_t lds0 = h2_lds_address(lds);
@@ -148,7 +126,7 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void search_gemm_kernel(const Sear
 #pragma unroll
       for (int j = 0; j < AL; ++j) h2_dma(base, va[j], to + j * 1024);
     ++a_step;
-    gA += 64;
+    gA += step_a;
     if (HAVE_S && HAVE_P && a_step == n_s) gA = gP;
     if (a_step == n_steps) a_step = 0, gA = gS;
   };
@@ -517,6 +495,7 @@ hipError_t launch_code_search(int bits, bool prod, const CodeSearch& q, int d, c
   a.M = q.nq; a.d = d; a.idx = idx; a.qjl = qjl; a.gamma = gamma; a.norm = norm; a.n = n; a.kappa = kappa; a.tab = make_code_table(bits, cb);
   a.q_inv = q.inv; a.e1 = q.e1; a.e2 = q.e2; a.bar = q.bar; a.bar_step = q.bar_step; a.sample = q.sample; a.ld_sample = q.ld_sample;
   a.code_step = code_step; a.list_u = q.list_u; a.list_i = q.list_i; a.count = q.count; a.cap = q.cap; a.s_rel = q.s_rel;
+  if (search_few_serves(q.nq, d, n)) return launch_search_few(bits, prod, a, s);
   TQ_CODE_BITS(launch_one)
 }
 

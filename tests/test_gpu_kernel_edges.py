@@ -118,6 +118,17 @@ def test_search_by_candidates(d, bits, prod, nq, n, topk):
     T._topk_both_ways(p, T.dev(W.gaussian_queries(nq, d, 3, unit=False)), 1, nq, c, n, topk)
 
 
+@pytest.mark.parametrize("d,bits,prod,nq,n,topk", [
+    (128, 1, False, 32, 70001, 10), (128, 2, False, 97, 140033, 3), (256, 3, True, 96, 8321, 64), (384, 4, True, 128, 9999, 16),
+    (128, 4, True, 40, 66000, 64), (512, 0, True, 64, 16385, 1), (2048, 2, True, 145, 8192, 7), (3072, 1, False, 129, 10001, 10),
+    (256, 2, True, 641, 23041, 5),
+])
+def test_search_by_candidates_few_queries(d, bits, prod, nq, n, topk):
+    """Every block of 32 queries and kind of code of the kernel for few, several tiles to a workgroup, long codes; numbers of query blocks that
+    do not divide the chip."""
+    test_search_by_candidates(d, bits, prod, nq, n, topk)
+
+
 @pytest.mark.parametrize("d,bits,prod", [(128, 2, True), (256, 3, False)])
 def test_search_by_candidates_with_too_many_of_them(d, bits, prod):
     """Equal scores fill every query's list; rising ones defeat a bar from a sample; vectors of length zero tie at zero."""
