@@ -18,54 +18,6 @@ typedef float floatx16 __attribute__((ext_vector_type(16)));
 
 constexpr int XCDS = 8;
 
-// Constants that the compiler is not to see through: as literals of their own they would cost an instruction where they are a third operand
-struct LaneTable {
-  uint32_t hh[2], hl[2];  // bytes of the magnitudes' pieces, the high ones negated
-  uint32_t top16, top8, one16, ones, threes, low[2];
-  __device__ __forceinline__ explicit LaneTable(const CodeTable& t) {
-#pragma unroll
-    for (int i = 0; i < 2; ++i) hh[i] = t.hh[i] ^ 0x80808080u, hl[i] = t.hl[i];
-    top16 = 0x80008000u, top8 = 0x80808080u, one16 = 0x3C003C00u, ones = 0x11111111u, threes = 0x33333333u, low[0] = 0x03030303u, low[1] = 0x07070707u;
-    asm volatile("" : "+s"(top16), "+s"(top8), "+v"(one16), "+s"(ones), "+s"(threes), "+s"(low[0]), "+s"(low[1]));
-  }
-};
-
-// A lane's 16 values of a group of 32: of words moved right by twice its half, bit positions 0, 1, 4 and 5 of every byte are quads 4 half-step +
-// {0, 1}.  The low planes of two quads side by side (nibbles) are joined for both at once.  Vector instructions are paid in matrix time:
-// 45 / 39 / 34 / 17 of them a step at 4 / 3 / 2 / 1 bits, 75 / 58 / 43 / 25 plane by plane as in tq_code_decode.h.
-template <int BITS>
-struct LaneDecoder {
-  uint32_t s, even, odd;
-  __device__ __forceinline__ LaneDecoder(const uint32_t* w, const LaneTable& t) {
-    auto pick = [](uint32_t m, uint32_t a, uint32_t b) { return __builtin_amdgcn_bitop3_b32(m, a, b, 0xCA); };  // a where m, else b
-    s = w[BITS - 1];
-    even = odd = 0u;
-    if constexpr (BITS > 1) {
-      uint32_t x[BITS - 1];
-#pragma unroll
-      for (int p = 0; p < BITS - 1; ++p) x[p] = ~(w[p] ^ s);
-      if constexpr (BITS == 2) even = x[0], odd = x[0] >> 1;
-      if constexpr (BITS > 2) even = pick(t.ones, x[0], x[1] << 1), odd = pick(t.ones, x[0] >> 1, x[1]);
-      if constexpr (BITS > 3) even = pick(t.threes, even, x[2] << 2), odd = pick(t.threes, odd, x[2] << 1);
-    }
-  }
-  __device__ __forceinline__ void quad(int half, int j, const LaneTable& t, uint32_t& a, uint32_t& b) const {
-    const int k = 4 * half + j;
-    if constexpr (BITS == 1) {
-      a = __builtin_amdgcn_bitop3_b32(s << (15 - k), t.top16, t.one16, 0xAE);  // (~s & top) | one
-      b = __builtin_amdgcn_bitop3_b32(s << (7 - k), t.top16, t.one16, 0xAE);
-    } else {
-      const uint32_t n = j == 0 ? even : odd;
-      const uint32_t sel = (half == 0 ? n : n >> 4) & (BITS == 2 ? 0x01010101u : t.low[BITS - 3]);
-      const uint32_t up = BITS == 4 ? __builtin_amdgcn_perm(t.hh[1], t.hh[0], sel) : __builtin_amdgcn_perm(t.hh[0], t.hh[0], sel);
-      const uint32_t hi = __builtin_amdgcn_bitop3_b32(s << (7 - k), t.top8, up, 0x6A);  // (s & top) ^ up
-      const uint32_t lo = BITS == 4 ? __builtin_amdgcn_perm(t.hl[1], t.hl[0], sel) : __builtin_amdgcn_perm(t.hl[0], t.hl[0], sel);
-      a = __builtin_amdgcn_perm(hi, lo, 0x06020400u);
-      b = __builtin_amdgcn_perm(hi, lo, 0x07030501u);
-    }
-  }
-};
-
 // TW x 32 queries, a wavefront's 32 codes.  (Chunks of eight steps: no faster, and a lane has twice the words.)
 constexpr int WAVES = 4, CH = 4;
 template <int TW>
@@ -179,7 +131,7 @@ __global__ __launch_bounds__(64 * WAVES, 2) void search_few_kernel(const SearchG
   };
 
   floatx16 acc[TW];
-  const LaneTable tab(a.tab);
+  const PlaneTable tab(a.tab);
   constexpr int AHEAD = 2;
   const unsigned char* const pa[2] = {lds + h2_place<1>(l32, h), lds + h2_place<1>(l32, 2 + h)};
   // of_p: the chunk belongs to the centroid segment
@@ -204,8 +156,9 @@ __global__ __launch_bounds__(64 * WAVES, 2) void search_few_kernel(const SearchG
         f[i % (AHEAD + 1)][t] = *reinterpret_cast<const f16x8*>(pa[i & 1] + at + (i >> 1) * C::STEP_BYTES + t * 2048);
     };
     auto decode = [&](int i, int j) {  // one of the two quads of a half-step
-      const LaneDecoder<B> dec(words + (i >> 1) * B, tab);
-      dec.quad(i & 1, j, tab, v[i & 1][2 * j], v[i & 1][2 * j + 1]);
+      Planes<B> codes;
+      codes.set(words + (i >> 1) * B, tab);
+      codes.quad(4 * (i & 1) + j, tab, v[i & 1][2 * j], v[i & 1][2 * j + 1]);
     };
 #pragma unroll
     for (int i = 0; i < AHEAD; ++i) read(i);

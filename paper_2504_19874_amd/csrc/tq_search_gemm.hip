@@ -14,7 +14,7 @@
 // queries: 605 us, was 1037 with a trip each).
 //
 // Bound by the power of the matrix cores and, at 3 and 4 bits, by the decoding's vector instructions (10^6 codes, 1000 queries: d = 1536, 4 bits
-// 3.07 ms, 1.0 PFLOP/s; d = 3072, 1 + 1 bits 9.1 ms, 1.35; d = 128, 4 bits 0.55 ms, 0.46; in registers 1.62).  With the loading and the decoding
+// 2.93 ms, 1.05 PFLOP/s (3.05 with the planes joined position by position); d = 3072, 1 + 1 bits 9.1 ms, 1.35; d = 128, 4 bits 0.55 ms, 0.46; in registers 1.62).  With the loading and the decoding
 // given to four wavefronts each it was no faster at d = 3072 and slower elsewhere (registers).
 #include <cstring>
 
@@ -28,34 +28,6 @@ namespace {
 typedef float floatx16 __attribute__((ext_vector_type(16)));
 
 constexpr int XCDS = 8;
-
-// Four coordinates (bit position 4 HALF + k of the four bytes) as two words of the contraction
-template <int BITS, int HALF>
-struct QuadDecoder {
-  uint32_t u[BITS > 1 ? BITS - 1 : 1], n;
-  __device__ __forceinline__ QuadDecoder(const uint32_t* w) {
-    if constexpr (BITS > 1) {
-#pragma unroll
-      for (int p = 0; p < BITS - 1; ++p) u[p] = ~(w[p] ^ w[BITS - 1]) >> (4 * HALF);
-    }
-    n = ~w[BITS - 1] >> (4 * HALF);
-  }
-  __device__ __forceinline__ void quad(int k, const CodeTable& tab, uint32_t& a, uint32_t& b) const {
-    if constexpr (BITS == 1) {
-      a = ((n << (15 - k)) & 0x80008000u) | 0x3C003C00u;
-      b = ((n << (7 - k)) & 0x80008000u) | 0x3C003C00u;
-    } else {
-      uint32_t sel = 0u;
-#pragma unroll
-      for (int p = 0; p < BITS - 1; ++p) sel |= (k >= p ? u[p] >> (k - p) : u[p] << (p - k)) & (0x01010101u << p);
-      const uint32_t hi = (BITS == 4 ? __builtin_amdgcn_perm(tab.hh[1], tab.hh[0], sel) : __builtin_amdgcn_perm(tab.hh[0], tab.hh[0], sel)) ^
-                          ((n << (7 - k)) & 0x80808080u);
-      const uint32_t lo = BITS == 4 ? __builtin_amdgcn_perm(tab.hl[1], tab.hl[0], sel) : __builtin_amdgcn_perm(tab.hl[0], tab.hl[0], sel);
-      a = __builtin_amdgcn_perm(hi, lo, 0x06020400u);
-      b = __builtin_amdgcn_perm(hi, lo, 0x07030501u);
-    }
-  }
-};
 
 template <int TW, int WM, int WN>
 struct SearchCfg {
@@ -191,6 +163,9 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void search_gemm_kernel(const Sear
     pb[s] = lds + NS * C::A_BYTES + h2_place<1>(wn * UW * 32 + l32, s * 2 + h);
   }
   floatx16 acc[TW][UW];
+  const PlaneTable tab(a.tab);
+  constexpr int KEPT = BITS == 4 ? 4 : BITS == 3 ? 2 : BITS == 2 ? 1 : 0;
+  uint32_t kept[1 + KEPT];  // of a group's planes from its first step to its second
   auto clear = [&] {
 #pragma unroll
     for (int t = 0; t < TW; ++t)
@@ -234,7 +209,17 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void search_gemm_kernel(const Sear
   auto step = [&](auto buf_c, auto of_p) __attribute__((always_inline)) {  // (called, it would keep the accumulators in memory)
     constexpr int buf = decltype(buf_c)::value, nbuf = (buf + 1) % NS;
     constexpr int half = buf & 1, pair = (buf / 2 + 1) % 2;  // half of the group, and which pair of the round
-    const QuadDecoder<decltype(of_p)::value ? NW : 1, half> dec(words[pair]);
+    Planes<decltype(of_p)::value ? NW : 1> codes;
+    if constexpr (half == 0) {
+      codes.set(words[pair], tab);
+      kept[0] = codes.s;
+#pragma unroll
+      for (int i = 0; i < KEPT; ++i) kept[1 + i] = codes.n[i];
+    } else {
+      codes.s = kept[0];
+#pragma unroll
+      for (int i = 0; i < KEPT; ++i) codes.n[i] = kept[1 + i];
+    }
     uint32_t v[8];
     auto from = [](int i) { return 2 * i * NR / NM < NR ? 2 * i * NR / NM : NR; };  // reads go into the first half of a half-step
     __builtin_amdgcn_sched_barrier(0);
@@ -245,7 +230,7 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void search_gemm_kernel(const Sear
       for (int r = from(i); r < from(i + 1); ++r) read_one(f1, buf, 1, r);
 #pragma unroll
       for (int k = 4 * i / NM; k < 4 * (i + 1) / NM; ++k) {
-        dec.quad(k, a.tab, v[2 * k], v[2 * k + 1]);
+        codes.quad(4 * half + k, tab, v[2 * k], v[2 * k + 1]);
         if (k & 1) store_codes(pair, 2 * half + k / 2, v + 2 * (k - 1));
       }
       __builtin_amdgcn_sched_barrier(0);
@@ -316,10 +301,11 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void search_gemm_kernel(const Sear
   if (tid < 4) found_n[tid] = 0;
   auto decode_half = [&](auto half_c) {  // of the first pair of steps
     constexpr int half = decltype(half_c)::value;
-    const QuadDecoder<HAVE_S ? 1 : NW, half> dec(words[0]);
+    Planes<HAVE_S ? 1 : NW> codes;
+    codes.set(words[0], tab);
     uint32_t v[8];
 #pragma unroll
-    for (int k = 0; k < 4; ++k) dec.quad(k, a.tab, v[2 * k], v[2 * k + 1]);
+    for (int k = 0; k < 4; ++k) codes.quad(4 * half + k, tab, v[2 * k], v[2 * k + 1]);
     store_codes(0, 2 * half, v);
     store_codes(0, 2 * half + 1, v + 4);
   };
