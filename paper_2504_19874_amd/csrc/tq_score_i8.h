@@ -41,8 +41,6 @@ struct ScoreI8Args {
 constexpr int I8_MAX_D = 4096;
 // the terms the kernel evaluates: plane subsets of odd size (symmetric codebook)
 __host__ __device__ constexpr bool i8_term(int m) { return __builtin_popcount((unsigned)m) & 1; }
-constexpr int I8_COPIES = 32;
-constexpr int I8_TABLE_BYTES = 256 * I8_COPIES * 8;
 
 
 // the codes against digit images that are ready (tq_score_stream.hip)

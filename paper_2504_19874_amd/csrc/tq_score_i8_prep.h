@@ -1,6 +1,6 @@
 // In-kernel query preparation shared by the single-kernel d = 128 scoring kernels
 // (tq_score_i8_128.hip, tq_score_i8_split.hip): a workgroup of 8 wavefronts rotates / sketches
-// its own four queries from the transposed matrices and writes their balanced base-128 digits.
+// its own four queries from the transposed matrices and writes their digits.
 //
 //   load      wavefront w requests its thread's column of matrix w / 4 (0: Pi^T, 1: S^T), half
 //             (w / 2) % 2 of k, column j = tid % 128: 64 values, to be issued before anything else
@@ -10,9 +10,7 @@
 //             a read-out over 1024 keys (19.1 -> 18.3 us with its two appends; 8 x 65536 keys scored: 11.2 -> 10.9).  The matrices as
 //             8 bytes per lane in half as many loads: 0.5 us slower with a sketch
 //   (barrier)
-//   digitise  wavefront w takes (matrix w / 4, query w % 4): power-of-two scale with |Q| <= 2^19,
-//             digits -> dig_s[matrix][query][digit][j] (digit 3 = 0), scalars -> scal_s[matrix][query]
-//             [0: 1/scale, 1: sum of the rounded coordinates, 2: that sum over j < d_hi, 3: over the rest]
+//   digits    i8_digitise_terms, or what the two instances share (tq_score_i8_split.hip)
 //   (barrier)
 #pragma once
 #include "tq_score_i8.h"
@@ -28,7 +26,6 @@ namespace tq {
 __host__ __device__ constexpr int mask_slot(int c) { return (c & ~31) + 8 * (c & 3) + ((c >> 2) & 7); }
 
 constexpr int I8_PART_FLOATS = 2 * 2 * 4 * 128;
-constexpr int I8_PREP_BYTES = I8_PART_FLOATS * 4 + 2 * 4 * 4 * 128 + 2 * 4 * 4 * 4;  // partial sums, digits, scalars
 
 // max / sum over the 64 lanes: four DPP steps inside each row of 16, then the four rows
 // through scalar registers
@@ -115,48 +112,6 @@ struct I8Prep {
     matvec_rows<0, 16>(acc, q, wv);
 #pragma unroll
     for (int qi = 0; qi < 4; ++qi) part_s[((mat * 2 + kh) * 4 + qi) * 128 + j] = acc[qi];
-  }
-
-  __device__ __forceinline__ static void digitise(const ScoreI8Args& a, int q0, int wave, int lane, int d_hi,
-                                                  const float* part_s, signed char* dig_s, float* scal_s) {
-    const int m = wave >> 2, qi = wave & 3;
-    if (!(m == 0 ? HAVE_R : PROD)) return;
-    const bool live = q0 + qi < a.q_per_group;
-    float y[2];
-#pragma unroll
-    for (int u = 0; u < 2; ++u) {
-      const int c = lane + 64 * u;
-      y[u] = live ? part_s[((m * 2 + 0) * 4 + qi) * 128 + c] + part_s[((m * 2 + 1) * 4 + qi) * 128 + c] : 0.f;
-    }
-    const float mx = wave_max(fmaxf(fabsf(y[0]), fabsf(y[1])));
-    int e = 0;
-    if (mx > 0.f) (void)frexpf(mx, &e);  // mx = f * 2^e, f in [0.5, 1): |Q| <= 2^19
-    const float sc = ldexpf(1.f, 19 - e);
-    int Q[2];
-    Q[0] = __float2int_rn(y[0] * sc);
-    Q[1] = __float2int_rn(y[1] * sc);
-    const int tot = wave_sum(Q[0] + Q[1]);
-    const int tot_hi = wave_sum((lane < d_hi ? Q[0] : 0) + (lane + 64 < d_hi ? Q[1] : 0));
-#pragma unroll
-    for (int u = 0; u < 2; ++u) {
-      // balanced base 128: D0, D1 in [-64, 63], D2 in [-64, 64]
-      const int c = lane + 64 * u;
-      const int d0 = ((Q[u] + 64) & 127) - 64;
-      const int Q1 = (Q[u] - d0) >> 7;
-      const int d1 = ((Q1 + 64) & 127) - 64;
-      signed char* o = dig_s + (m * 4 + qi) * 4 * 128 + c;
-      o[0] = (signed char)d0;
-      o[128] = (signed char)d1;
-      o[256] = (signed char)((Q1 - d1) >> 7);
-      o[384] = 0;
-    }
-    if (lane == 0) {
-      const float inv = ldexpf(1.f, e - 19);
-      scal_s[(m * 4 + qi) * 4 + 0] = inv;
-      scal_s[(m * 4 + qi) * 4 + 1] = (float)tot * inv;
-      scal_s[(m * 4 + qi) * 4 + 2] = (float)tot_hi * inv;
-      scal_s[(m * 4 + qi) * 4 + 3] = (float)(tot - tot_hi) * inv;
-    }
   }
 };
 

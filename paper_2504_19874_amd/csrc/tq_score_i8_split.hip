@@ -7,11 +7,10 @@
 //     nu_hi * (mse_hi + kappa_hi gamma_hi qjl_hi) + nu_lo * (mse_lo + kappa_lo gamma_lo qjl_lo)
 // with the four inner sums taken over the instance's own coordinates only.
 //
-// Same arithmetic as tq_score_i8.hip (masked sums of fixed-point query digits on
-// v_mfma_i32_16x16x64_i8, Walsh terms of the symmetric codebooks).  In that
-// kernel's operand layout a lane's k-chunk IS one coordinate group, so "sum
-// over one instance only" is an A operand with the other instance's lanes
-// zeroed: every mask is expanded once and fed to two MFMAs, one per instance.
+// Masked sums of fixed-point query digits, Walsh terms of the symmetric codebooks.
+// "Sum over one instance only" is an A operand with the other instance's
+// coordinate groups zeroed: every mask is made once and fed to two matrix
+// instructions, one per instance.
 // Queries are prepared inside the kernel while the code words are in flight
 // (FUSED, needs the transposed matrices; see tq_score_i8_prep.h), or by
 // prep_i8_kernel beforehand; either leaves the per-instance sums of the rounded
@@ -26,130 +25,146 @@ struct SplitArgs {
   float coef_hi[16];  // Walsh form of the hi codebook; ScoreI8Args::coef is that of lo
 };
 
-constexpr int SPLIT_TILES = 8;  // tiles of 16 keys per wavefront
+typedef int v8i __attribute__((ext_vector_type(8)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 
-template <int BITS, bool PROD, bool FUSED>
-__global__ __launch_bounds__(512) void score_i8_split_kernel(const ScoreI8Args a, const SplitArgs sp) {
-  __shared__ __attribute__((aligned(16))) uint2 expand_s[256 * I8_COPIES];  // [256][32]: byte -> one byte per bit
-  extern __shared__ __attribute__((aligned(16))) unsigned char prep_s[];   // FUSED: partial sums, digits, scalars
-  float* const part_s = reinterpret_cast<float*>(prep_s);                               // [2][2][4][128]
-  signed char* const dig_s = reinterpret_cast<signed char*>(part_s + I8_PART_FLOATS);  // [2][4][4][128]
-  float* const scal_s = reinterpret_cast<float*>(dig_s + 2 * 4 * 4 * 128);              // [2][4][4]
-  constexpr int NP = BITS + 1;            // planes of instance hi
-  constexpr int NMH = (1 << NP) - 1;      // plane subsets of hi
-  constexpr int NML = (1 << BITS) - 1;    // plane subsets of lo (a prefix of hi's)
+// Tiles of 16 keys whose codes are asked for together, a round ahead of their use: with four, two workgroups have no room on a compute unit
+// (8 x 91627 keys, 4 queries each, 1 + 1 and 2 + 1 bits 21.2 us, 18.6 with two)
+constexpr int SPLIT_ROUND = 2;
+constexpr int SPLIT_LDS = I8_PART_FLOATS * 4 + 2 * 2048 + 2 * 4 * 4 * 4;  // partial sums, digits, scalars
+
+// What the two instances share: digits of the rounded coordinates Q of query qi's rotation (m = 0) or sketch (m = 1), and their sums
+// -> scal_s[m][qi][0: 1/scale, 2: sum over instance hi, 3: over lo].  Wavefront w takes (matrix w / 4, query w % 4).
+template <bool PROD>
+__device__ __forceinline__ void split_digitise(const ScoreI8Args& a, int q0, int wave, int lane, int d_hi, const float* part_s, unsigned char* dig_s,
+                                               float* scal_s) {
+  const int m = wave >> 2, qi = wave & 3;
+  if (m == 1 && !PROD) return;
+  const bool live = q0 + qi < a.q_per_group;
+  float y[2];
+#pragma unroll
+  for (int u = 0; u < 2; ++u) {
+    const int c = lane + 64 * u;
+    y[u] = live ? part_s[((m * 2 + 0) * 4 + qi) * 128 + c] + part_s[((m * 2 + 1) * 4 + qi) * 128 + c] : 0.f;
+  }
+  const float mx = wave_max(fmaxf(fabsf(y[0]), fabsf(y[1])));
+  int e = 0;
+  if (mx > 0.f) (void)frexpf(mx, &e);  // mx = f * 2^e, f in [0.5, 1): |Q| <= 2^19
+  const float sc = ldexpf(1.f, 19 - e);
+  const int Q[2] = {__float2int_rn(y[0] * sc), __float2int_rn(y[1] * sc)};
+  const int tot = wave_sum(Q[0] + Q[1]);
+  const int tot_hi = wave_sum((lane < d_hi ? Q[0] : 0) + (lane + 64 < d_hi ? Q[1] : 0));
+#pragma unroll
+  for (int u = 0; u < 2; ++u) put_mask_digits(dig_s, m, qi, lane + 64 * u, (float)Q[u]);
+  if (lane == 0) {
+    const float inv = ldexpf(1.f, e - 19);
+    scal_s[(m * 4 + qi) * 4 + 0] = inv;
+    scal_s[(m * 4 + qi) * 4 + 2] = (float)tot_hi * inv;
+    scal_s[(m * 4 + qi) * 4 + 3] = (float)(tot - tot_hi) * inv;
+  }
+}
+
+// The masked sums on v_mfma_f32_16x16x128_f8f6f4 as in tq_score_i8_128_body.h: a stored word ANDed with 0x11111111 << v is eight fp4 operands, the
+// digits are integers and every sum is exact, so the scores are those of the integer instructions bit for bit.  Bytes from a table of 64 KB in LDS,
+// written by every workgroup, left room for one workgroup on a compute unit, three in turn.  64 channels at 2 + 1 bits and 64 at 1 + 1, us: 8 x
+// 91627 keys, 4 queries each, 26.8 / 18.6 so, 8 x 65536 18.0 / 11.7, 8 x 16384 9.4 / 6.6; 16 x 131072, 8 queries, a bit more 144 / 85 (bound
+// by the codes' intake, as one parameter set is).
+template <int BITS, bool PROD, bool FUSED, int TILES>
+__global__ __launch_bounds__(512, 4) void score_i8_split_kernel(const ScoreI8Args a, const SplitArgs sp) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char dyn_s[];
+  float* const part_s = reinterpret_cast<float*>(dyn_s);                                      // [2][2][4][128]
+  unsigned char* const dig_s = reinterpret_cast<unsigned char*>(part_s + I8_PART_FLOATS);     // [2][4][4][128]
+  float* const scal_s = reinterpret_cast<float*>(dig_s + 2 * 2048);                           // [2][4][4]
+  constexpr int NP = BITS + 1;                     // planes of instance hi
+  constexpr int NMH = (1 << NP) - 1;               // plane subsets of hi
+  constexpr int NML = (1 << BITS) - 1;             // plane subsets of lo (a prefix of hi's)
+  constexpr int RT = SPLIT_ROUND, ROUNDS = TILES / RT;
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int col = lane & 15;   // key within a tile / row of A
-  const int kq = lane >> 4;    // k-chunk = coordinate group; also the query whose sums this lane receives
+  const int kq = lane >> 4;    // coordinate group of this lane's words; also the query whose sums this lane receives
   const int group = blockIdx.y;
   const int q0 = blockIdx.z * 4;
   const int gs = sp.gs_hi;
-  const bool g_hi = kq < gs;   // this lane's coordinate group belongs to instance hi
+  const bool g_hi = kq < gs;   // this lane's words belong to instance hi
 
-  // ---- A operands: digit images of this group's queries; one copy per instance ---------------
-  const int a_query = col >> 2, a_digit = col & 3;
-  const bool a_live = q0 + a_query < a.q_per_group;
-  const int64_t qrow = (int64_t)group * a.q_per_group + q0 + (a_live ? a_query : 0);
-  const bool out_live = q0 + kq < a.q_per_group;
-  const int64_t orow = (int64_t)group * a.q_per_group + q0 + (out_live ? kq : 0);
-  v4i ar[2][2], as_[2][2];  // [instance: 0 lo, 1 hi][k-step]
-  float r_inv = 0.f, r_sum_hi = 0.f, r_sum_lo = 0.f, s_inv = 0.f, s_sum_hi = 0.f, s_sum_lo = 0.f;
-  const v4i zero = v4i{0, 0, 0, 0};
   I8Prep<true, PROD> prep;
-  if (FUSED) {
-    prep.load(a, group, q0, wave, tid);  // this thread's column of the transposed matrix, before anything else
-  } else {
-#pragma unroll
-    for (int s = 0; s < 2; ++s) {
-      const uint4 r = a.img[((qrow * 2 + 0) * 2 + s) * 16 + a_digit * 4 + kq];
-      const uint4 z = PROD ? a.img[((qrow * 2 + 1) * 2 + s) * 16 + a_digit * 4 + kq] : make_uint4(0, 0, 0, 0);
-      const v4i rv = v4i{(int)r.x, (int)r.y, (int)r.z, (int)r.w}, zv = v4i{(int)z.x, (int)z.y, (int)z.z, (int)z.w};
-      ar[1][s] = g_hi ? rv : zero;
-      ar[0][s] = g_hi ? zero : rv;
-      as_[1][s] = g_hi ? zv : zero;
-      as_[0][s] = g_hi ? zero : zv;
-    }
-    r_inv = a.scal[(orow * 2 + 0) * 4];
-    r_sum_hi = a.scal[(orow * 2 + 0) * 4 + 2];
-    r_sum_lo = a.scal[(orow * 2 + 0) * 4 + 3];
-    if (PROD) {
-      s_inv = a.scal[(orow * 2 + 1) * 4];
-      s_sum_hi = a.scal[(orow * 2 + 1) * 4 + 2];
-      s_sum_lo = a.scal[(orow * 2 + 1) * 4 + 3];
-    }
-  }
+  if (FUSED) prep.load(a, group, q0, wave, tid);  // this thread's column of the transposed matrix, before anything else
 
-  // ---- code words of this wavefront's keys: plane words of the lane's own group --------------
+  // ---- code words of this wavefront's keys: plane words of the lane's own group, a round ahead ----
   const int wpr = 4 * BITS + gs;  // idx words per row
   const int woff = g_hi ? kq * NP : gs * NP + (kq - gs) * BITS;
   const int64_t gbase = (int64_t)group * a.n;
-  const int64_t wave_key0 = ((int64_t)blockIdx.x * 8 + wave) * (16 * SPLIT_TILES);
-  uint32_t pw[SPLIT_TILES][NP], zw[SPLIT_TILES];
-  float kgh[SPLIT_TILES], kgl[SPLIT_TILES], nuh[SPLIT_TILES], nul[SPLIT_TILES];
+  const int64_t wave_key0 = ((int64_t)blockIdx.x * 8 + wave) * (16 * TILES);
+  struct Round {
+    uint32_t pw[RT][NP], zw[RT];
+    float kgh[RT], kgl[RT], nuh[RT], nul[RT];
+  };
+  Round codes[2];
+  auto load_round = [&](int r, Round& c) {
 #pragma unroll
-  for (int t = 0; t < SPLIT_TILES; ++t) {
-    const int64_t key = wave_key0 + t * 16 + col;
-    const int64_t row = gbase + (key < a.n ? key : a.n - 1);  // clamped: results of such lanes are not stored
-    const uint32_t* pi = a.idx + row * wpr + woff;
+    for (int t = 0; t < RT; ++t) {
+      const int64_t key = wave_key0 + (r * RT + t) * 16 + col;
+      const int64_t row = gbase + (key < a.n ? key : a.n - 1);  // clamped: results of such lanes are not stored
+      const uint32_t* const pi = a.idx + row * wpr + woff;
 #pragma unroll
-    for (int pl = 0; pl < BITS; ++pl) pw[t][pl] = pi[pl];
-    pw[t][BITS] = g_hi ? pi[BITS] : 0u;  // a lo group has no such plane: an all-zero mask changes nothing
-    zw[t] = PROD ? a.qjl[row * 4 + kq] : 0u;
-    kgh[t] = PROD ? a.gamma[2 * row] : 0.f;
-    kgl[t] = PROD ? a.gamma[2 * row + 1] : 0.f;
-    nuh[t] = a.norm[2 * row];
-    nul[t] = a.norm[2 * row + 1];
-  }
-
-  // ---- the expansion table, 32 bank-private copies ---------------------------------------------
-  {
-    const uint32_t lo = (((uint32_t)tid >> 5) * 0x00204081u) & 0x01010101u;  // bit i of the nibble -> byte i
-#pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      const uint32_t hi = ((uint32_t)i * 0x00204081u) & 0x01010101u;
-      expand_s[tid + 512 * i] = make_uint2(lo, hi);
+      for (int pl = 0; pl < BITS; ++pl) c.pw[t][pl] = pi[pl];
+      c.pw[t][BITS] = g_hi ? pi[BITS] : 0u;  // a lo group has no such plane: an all-zero mask changes nothing
+      c.zw[t] = PROD ? a.qjl[row * 4 + kq] : 0u;
+      c.kgh[t] = PROD ? a.gamma[2 * row] : 0.f;
+      c.kgl[t] = PROD ? a.gamma[2 * row + 1] : 0.f;
+      c.nuh[t] = a.norm[2 * row];
+      c.nul[t] = a.norm[2 * row + 1];
     }
-  }
-  if (FUSED) {
+  };
+  load_round(0, codes[0]);
+  __builtin_amdgcn_sched_barrier(0);
+
+  // ---- digits and scalars of this workgroup's queries ------------------------------------------------
+  if constexpr (FUSED) {
     prep.matvec(part_s);
     __syncthreads();
-    prep.digitise(a, q0, wave, lane, 32 * gs, part_s, dig_s, scal_s);
+    split_digitise<PROD>(a, q0, wave, lane, 32 * gs, part_s, dig_s, scal_s);
+  } else {  // prepared by prep_i8_kernel, as base-128 digits
+    const int qi = tid >> 7, c = tid & 127;
+    const int64_t row = (int64_t)group * a.q_per_group + (q0 + qi < a.q_per_group ? q0 + qi : q0);
+    const signed char* const img = reinterpret_cast<const signed char*>(a.img);
+#pragma unroll
+    for (int m = 0; m < (PROD ? 2 : 1); ++m) {
+      auto digit = [&](int i) { return (int)img[(((row * 2 + m) * 2 + ((c >> 4) & 1)) * 16 + i * 4 + (c >> 5)) * 16 + (c & 15)]; };
+      put_mask_digits(dig_s, m, qi, c, (float)(digit(0) + 128 * digit(1) + 16384 * digit(2)));
+      if (c < 4) scal_s[(m * 4 + qi) * 4 + c] = a.scal[(row * 2 + m) * 4 + c];
+    }
   }
   __syncthreads();
-  if (FUSED) {
-#pragma unroll
-    for (int s = 0; s < 2; ++s) {
-      const int c0 = i8_coord0(s, kq);
-      const v4i rv = *reinterpret_cast<const v4i*>(dig_s + ((0 * 4 + a_query) * 4 + a_digit) * 128 + c0);
-      const v4i zv = PROD ? *reinterpret_cast<const v4i*>(dig_s + ((1 * 4 + a_query) * 4 + a_digit) * 128 + c0) : zero;
-      ar[1][s] = g_hi ? rv : zero;
-      ar[0][s] = g_hi ? zero : rv;
-      as_[1][s] = g_hi ? zv : zero;
-      as_[0][s] = g_hi ? zero : zv;
-    }
-    r_inv = scal_s[(0 * 4 + kq) * 4];
-    r_sum_hi = scal_s[(0 * 4 + kq) * 4 + 2];
-    r_sum_lo = scal_s[(0 * 4 + kq) * 4 + 3];
-    if (PROD) {
-      s_inv = scal_s[(1 * 4 + kq) * 4];
-      s_sum_hi = scal_s[(1 * 4 + kq) * 4 + 2];
-      s_sum_lo = scal_s[(1 * 4 + kq) * 4 + 3];
-    }
-  }
 
-  const uint32_t copy_off = (uint32_t)(lane & (I8_COPIES - 1)) * 8u;
-  const char* const table = reinterpret_cast<const char*>(expand_s);
-  auto expand16 = [&](uint32_t w, int h) -> v4i {  // bits [16 h, 16 h + 16) of w -> 16 bytes of 0/1
-    const uint32_t o0 = __builtin_amdgcn_perm(w, copy_off, h ? 0x0c0c0600u : 0x0c0c0400u);
-    const uint32_t o1 = __builtin_amdgcn_perm(w, copy_off, h ? 0x0c0c0700u : 0x0c0c0500u);
-    const uint2 lo = *reinterpret_cast<const uint2*>(table + o0);
-    const uint2 hi = *reinterpret_cast<const uint2*>(table + o1);
-    return v4i{(int)lo.x, (int)lo.y, (int)hi.x, (int)hi.y};
+  // ---- A operands: lane = row + 16 kq, row = 4 * query + digit; of an fp8 operand a lane has 16 bytes of one coordinate group and 16 of another
+  // (mask_slot), so that an instance's operand is the digits with the other instance's groups zeroed
+  const int a_query = col >> 2, a_digit = col & 3;
+  const v4i zero = v4i{0, 0, 0, 0};
+  v8i ar[2], az[2];  // [instance: 0 lo, 1 hi]
+  auto a_read = [&](int m, v8i (&o)[2]) {
+    const unsigned char* const row = dig_s + ((m * 4 + a_query) * 4 + a_digit) * 128 + 16 * kq;
+    const v4i d0 = *reinterpret_cast<const v4i*>(row), d1 = *reinterpret_cast<const v4i*>(row + 64);
+    const bool h0 = (kq >> 1) < gs, h1 = 2 + (kq >> 1) < gs;
+    o[1] = __builtin_shufflevector(h0 ? d0 : zero, h1 ? d1 : zero, 0, 1, 2, 3, 4, 5, 6, 7);
+    o[0] = __builtin_shufflevector(h0 ? zero : d0, h1 ? zero : d1, 0, 1, 2, 3, 4, 5, 6, 7);
   };
-  auto digits_sum = [&](const v4i& acc) -> float {  // D0 + 2^7 D1 + 2^14 D2
-    return (float)(acc[0] + acc[1] * 128 + acc[2] * 16384);
+  a_read(0, ar);
+  if (PROD) a_read(1, az);
+  const float r_inv = scal_s[kq * 4], r_sum_hi = scal_s[kq * 4 + 2], r_sum_lo = scal_s[kq * 4 + 3];
+  const float s_inv = PROD ? scal_s[(4 + kq) * 4] : 0.f, s_sum_hi = PROD ? scal_s[(4 + kq) * 4 + 2] : 0.f, s_sum_lo = PROD ? scal_s[(4 + kq) * 4 + 3] : 0.f;
+
+  auto masks = [&](uint32_t w) -> v8i {  // fp4: four registers
+    const v4i b = v4i{(int)(w & 0x11111111u), (int)(w & 0x22222222u), (int)(w & 0x44444444u), (int)((w >> 3) & 0x11111111u)};
+    return __builtin_shufflevector(b, b, 0, 1, 2, 3, -1, -1, -1, -1);
+  };
+  auto product = [&](const v8i& d, const v8i& b) -> f32x4 {
+    return __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(d, b, f32x4{0.f, 0.f, 0.f, 0.f}, 0, 4, 0, 127, 0, 127);
+  };
+  auto digits_sum = [&](const f32x4& acc) -> float {  // D0 + 2^5 D1 + 2^10 D2 + 2^15 D3, the inner sums exact
+    return fmaf(fmaf(acc[3], 32.f, acc[2]), 1024.f, fmaf(acc[1], 32.f, acc[0]));
   };
 
   // per-lane constants of the final combination
@@ -160,65 +175,66 @@ __global__ __launch_bounds__(512) void score_i8_split_kernel(const ScoreI8Args a
   for (int m = 1; m <= NML; ++m) crl[m - 1] = a.coef[m] * r_inv;
   const float base_hi = sp.coef_hi[0] * r_sum_hi, base_lo = a.coef[0] * r_sum_lo;
   const float zs = 2.f * s_inv;
-  float* const out0 = a.scores + ((int64_t)group * a.q_per_group + q0 + kq) * a.lds + wave_key0 + col;
+  const bool out_live = q0 + kq < a.q_per_group;
+  float* const out0 = a.scores + ((int64_t)group * a.q_per_group + (out_live ? q0 + kq : 0)) * a.lds + wave_key0 + col;
 
+  if (wave_key0 >= a.n) return;  // uniform over the wavefront; no barrier follows
+  // (a wavefront with any keys at all works through all of its tiles)
 #pragma unroll
-  for (int t = 0; t < SPLIT_TILES; ++t) {
-    if (wave_key0 + t * 16 >= a.n) break;  // uniform over the wavefront
-    v4i acch[NMH], accl[NML > 0 ? NML : 1], zh = {0, 0, 0, 0}, zl = {0, 0, 0, 0};
+  for (int r = 0; r < ROUNDS; ++r) {
+    const Round& c = codes[r & 1];
+    if (r + 1 < ROUNDS) load_round(r + 1, codes[(r + 1) & 1]);
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int m = 0; m < NMH; ++m) acch[m] = v4i{0, 0, 0, 0};
-#pragma unroll
-    for (int m = 0; m < (NML > 0 ? NML : 1); ++m) accl[m] = v4i{0, 0, 0, 0};
-#pragma unroll
-    for (int s = 0; s < 2; ++s) {
+    for (int t = 0; t < RT; ++t) {
+      float th = base_hi, tl = base_lo;
 #pragma unroll
       for (int m = 1; m <= NMH; ++m) {
         if (!i8_term(m)) continue;
         uint32_t w = 0u;
 #pragma unroll
         for (int pl = 0; pl < NP; ++pl)
-          if (m & (1 << pl)) w ^= pw[t][pl];
-        const v4i b = expand16(w, s);
-        acch[m - 1] = __builtin_amdgcn_mfma_i32_16x16x64_i8(ar[1][s], b, acch[m - 1], 0, 0, 0);
-        if (m <= NML) accl[m - 1] = __builtin_amdgcn_mfma_i32_16x16x64_i8(ar[0][s], b, accl[m - 1], 0, 0, 0);
+          if (m & (1 << pl)) w ^= c.pw[t][pl];
+        const v8i b = masks(w);
+        th = fmaf(crh[m - 1], digits_sum(product(ar[1], b)), th);
+        if (m <= NML) tl = fmaf(crl[m - 1], digits_sum(product(ar[0], b)), tl);
       }
       if (PROD) {
-        const v4i b = expand16(zw[t], s);
-        zh = __builtin_amdgcn_mfma_i32_16x16x64_i8(as_[1][s], b, zh, 0, 0, 0);
-        zl = __builtin_amdgcn_mfma_i32_16x16x64_i8(as_[0][s], b, zl, 0, 0, 0);
+        const v8i b = masks(c.zw[t]);
+        th = fmaf(sp.kappa_hi * c.kgh[t], fmaf(zs, digits_sum(product(az[1], b)), -s_sum_hi), th);
+        tl = fmaf(a.kappa * c.kgl[t], fmaf(zs, digits_sum(product(az[0], b)), -s_sum_lo), tl);
       }
+      float total = fmaf(c.nuh[t], th, c.nul[t] * tl);
+      // (formed here whether it is stored or not: behind a branch of its own this compiler loses sight of the waits that the registers of the
+      // matrix instructions above need)
+      asm volatile("" : "+v"(total));
+      if (out_live && wave_key0 + (r * RT + t) * 16 + col < a.n) out0[(r * RT + t) * 16] = total;
     }
-    float th = base_hi, tl = base_lo;
-#pragma unroll
-    for (int m = 1; m <= NMH; ++m)
-      if (i8_term(m)) th = fmaf(crh[m - 1], digits_sum(acch[m - 1]), th);
-#pragma unroll
-    for (int m = 1; m <= NML; ++m)
-      if (i8_term(m)) tl = fmaf(crl[m - 1], digits_sum(accl[m - 1]), tl);
-    if (PROD) {
-      th = fmaf(sp.kappa_hi * kgh[t], fmaf(zs, digits_sum(zh), -s_sum_hi), th);
-      tl = fmaf(a.kappa * kgl[t], fmaf(zs, digits_sum(zl), -s_sum_lo), tl);
-    }
-    const float total = fmaf(nuh[t], th, nul[t] * tl);
-    if (out_live && wave_key0 + t * 16 + col < a.n) out0[t * 16] = total;
   }
 }
 
-template <int BITS, bool PROD, bool FUSED>
+template <int BITS, bool PROD, bool FUSED, int TILES>
 static hipError_t launch_split_one(const ScoreI8Args& a, const SplitArgs& sp, int n_groups, hipStream_t s) {
-  const int64_t per_wg = 8 * 16 * SPLIT_TILES;
+  static_assert(SPLIT_LDS <= 64 * 1024, "no limit to raise");
+  const int64_t per_wg = 8 * 16 * TILES;
   const dim3 grid((unsigned)((a.n + per_wg - 1) / per_wg), n_groups, (a.q_per_group + 3) / 4);
-  constexpr int lds = FUSED ? I8_PREP_BYTES : 0;  // on top of the 64 KB table
-  static LdsLimit lds_limit;  // per instantiation: the limit is raised once per device
-  if (FUSED) if (const hipError_t e = raise_lds_limit(lds_limit, reinterpret_cast<const void*>(&score_i8_split_kernel<BITS, PROD, FUSED>), lds); e != hipSuccess) return e;
-  hipLaunchKernelGGL((score_i8_split_kernel<BITS, PROD, FUSED>), grid, dim3(512), lds, s, a, sp);
+  hipLaunchKernelGGL((score_i8_split_kernel<BITS, PROD, FUSED, TILES>), grid, dim3(512), SPLIT_LDS, s, a, sp);
   return hipGetLastError();
+}
+
+// Keys per workgroup as in tq_score_i8_128.hip: 2048, fewer while that leaves compute units without one (1024 of more keys than the chip takes at
+// once: 8 x 61687, 8 queries each, 19.3 -> 23.5 us)
+template <int BITS, bool PROD, bool FUSED>
+static hipError_t launch_split_tiles(const ScoreI8Args& a, const SplitArgs& sp, int n_groups, hipStream_t s) {
+  const int64_t others = (int64_t)n_groups * ((a.q_per_group + 3) / 4), cus = device_cu_count();
+  if (((a.n + 1023) / 1024) * others <= cus / 2) return launch_split_one<BITS, PROD, FUSED, 4>(a, sp, n_groups, s);
+  if (((a.n + 2047) / 2048) * others <= cus / 2) return launch_split_one<BITS, PROD, FUSED, 8>(a, sp, n_groups, s);
+  return launch_split_one<BITS, PROD, FUSED, 16>(a, sp, n_groups, s);
 }
 
 template <int BITS, bool PROD>
 static hipError_t launch_split(const ScoreI8Args& a, const SplitArgs& sp, int n_groups, bool fused, hipStream_t s) {
-  return fused ? launch_split_one<BITS, PROD, true>(a, sp, n_groups, s) : launch_split_one<BITS, PROD, false>(a, sp, n_groups, s);
+  return fused ? launch_split_tiles<BITS, PROD, true>(a, sp, n_groups, s) : launch_split_tiles<BITS, PROD, false>(a, sp, n_groups, s);
 }
 
 // c[v] = sum_S w_S chi_S(v) rewritten over masked sums (see tq_score_i8.hip):

@@ -202,6 +202,8 @@ def test_dequantize_split(d_hi, bits_lo, prod, n):
 @pytest.mark.parametrize("d_hi,bits_lo,prod,n_groups,qpg,npg,topk", [
     (32, 1, True, 8, 4, 1000, 0), (64, 1, True, 2, 5, 2100, 0), (32, 2, True, 1, 4, 130, 5), (96, 2, False, 2, 3, 300, 0),
     (32, 0, True, 1, 1, 77, 0), (64, 3, False, 1, 9, 1500, 4),
+    # 1024 and 2048 keys to a workgroup, with wavefronts that have some of their keys and none
+    (32, 1, True, 1, 200, 2100, 0), (96, 3, True, 2, 257, 2049, 0), (64, 0, False, 1, 520, 4000, 0), (64, 2, True, 2, 258, 1281, 0),
     # more than 32 queries per group (served by the same kernel, a block of four queries at a time)
     (64, 2, True, 2, 70, 900, 3),
 ])
