@@ -355,11 +355,13 @@ hipError_t launch_one(const SearchGemmArgs& a, hipStream_t s) {
 
 }  // namespace
 
-// Up to 128 queries; and long codes where tiles of 256 queries and codes would leave a quarter of the chip idle, whose steps follow each other
-// at the latency of a step (306 queries, 19628 codes of 3072, 1 bit, the whole search 170 us, 140 so).  Beyond, a code that is decoded once for 256
-// queries is cheaper (1000 queries' sample 57 us, 100 here; 200 queries, 500000 codes of 768 381 us, 420).
-bool search_few_serves(int M, int d, int64_t n) {
-  return M <= 128 || (d >= 2048 && (M + 255) / 256 * ((n + 255) / 256) * 4 <= 3 * (int64_t)device_cu_count());
+// Up to 128 queries; and long codes where tiles of 256 queries and codes would leave half of the chip idle, whose steps follow each other
+// at the latency of a step.  Beyond, a code that is decoded once for 256 queries is cheaper (1000 queries' sample 57 us, 100 here; 200 queries,
+// 500000 codes of 768 381 us, 420), and 3 and 4 bits without a sketch, whose steps all have the dearest decoding, from a quarter on.  The whole search, us, 250 queries
+// of 3072, through LDS / here: 28000 codes, 1 bit 140 / 134, 2 bits 167 / 163, 2 + 1 bits 299 / 276, 3 + 1 bits 307 / 288; 43000, 1 + 1 bits 311 / 325;
+// 4 bits: 10000 codes 163 / 161, 19000 177 / 182, 49000 214 / 250.
+bool search_few_serves(int bits, bool prod, int M, int d, int64_t n) {
+  return M <= 128 || (d >= 2048 && (M + 255) / 256 * ((n + 255) / 256) * (bits >= 3 && !prod ? 4 : 2) <= (int64_t)device_cu_count());
 }
 
 hipError_t launch_search_few(int bits, bool prod, const SearchGemmArgs& a, hipStream_t s) {

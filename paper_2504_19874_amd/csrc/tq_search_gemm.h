@@ -77,7 +77,7 @@ struct Planes {
 };
 
 // Few queries (tq_search_few.hip); the number of query blocks and ranges is its own
-bool search_few_serves(int M, int d, int64_t n);
+bool search_few_serves(int bits, bool prod, int M, int d, int64_t n);
 hipError_t launch_search_few(int bits, bool prod, const SearchGemmArgs& a, hipStream_t s);
 
 }  // namespace tq

@@ -481,7 +481,7 @@ hipError_t launch_code_search(int bits, bool prod, const CodeSearch& q, int d, c
   a.M = q.nq; a.d = d; a.idx = idx; a.qjl = qjl; a.gamma = gamma; a.norm = norm; a.n = n; a.kappa = kappa; a.tab = make_code_table(bits, cb);
   a.q_inv = q.inv; a.e1 = q.e1; a.e2 = q.e2; a.bar = q.bar; a.bar_step = q.bar_step; a.sample = q.sample; a.ld_sample = q.ld_sample;
   a.code_step = code_step; a.list_u = q.list_u; a.list_i = q.list_i; a.count = q.count; a.cap = q.cap; a.s_rel = q.s_rel;
-  if (search_few_serves(q.nq, d, n)) return launch_search_few(bits, prod, a, s);
+  if (search_few_serves(bits, prod, q.nq, d, n)) return launch_search_few(bits, prod, a, s);
   TQ_CODE_BITS(launch_one)
 }
 
