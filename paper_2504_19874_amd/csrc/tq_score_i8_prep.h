@@ -58,8 +58,9 @@ typedef float f32x4_prep __attribute__((ext_vector_type(4), aligned(4)));  // (t
 // acc[q] += sum over k = 4 I .. 4 N - 1 of w[k] * (coordinate k of vector q), which lane k / 4 of every row of 16 holds in q[q][k % 4]:
 // fetched from there in one instruction with its product.  (The compiler makes two of it.  It does not look inside: s_nop is the
 // distance that a register moved just before needs from its use by other lanes.)
-template <int I, int N>
-__device__ __forceinline__ void matvec_rows(float (&acc)[4], const f32x4_prep (&q)[4], const float (&wv)[4 * N]) {
+template <int I, int N, int M>
+__device__ __forceinline__ void matvec_rows(float (&acc)[4], const f32x4_prep (&q)[4], const float (&wv)[M]) {
+  static_assert(4 * N <= M, "");
 #define TQ_FMAC(ACC, Q, W) "\n\tv_fmac_f32_dpp %" #ACC ", %" #Q ", %" #W " row_newbcast:%24 row_mask:0xf bank_mask:0xf"
   asm("s_nop 1"
       TQ_FMAC(0, 4, 20) TQ_FMAC(1, 8, 20) TQ_FMAC(2, 12, 20) TQ_FMAC(3, 16, 20)

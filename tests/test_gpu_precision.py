@@ -154,3 +154,44 @@ def test_signs_against_digits(d, n, bits, prod):
     finally:
         p.c.flags = flags
     assert rms <= before[0] and (rms <= fp32[0] or (d == 128 and n > 8192)), (rms, before, fp32)
+
+
+# ------------------------------------------------------------------ attention read-out of one short chunk
+
+
+@pytest.mark.parametrize("bits,prod", [(2, False), (4, False), (0, True), (2, True)])
+@pytest.mark.parametrize("npg", [1, 100, 256, 512])
+def test_one_chunk_no_further_off_than_chunks_that_are_joined(npg, bits, prod):
+    """Up to 512 tokens the workgroup that has a query's sums rotates them back itself: chains of 16 products, as in the joining kernel, which
+    the same values come to in a call with more groups than the chip has compute units.  Queries of length zero: every weight is 1 / npg
+    exactly, and what is left of the error is the sums', the division's and the rotation's."""
+    pk = T.setup(D, 2, True)[0]
+    pv, Pi, S, c32, _ = T.setup(D, bits, prod)
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    part, groups = cus // 4, cus + cus // 4
+    n = groups * npg
+    g = torch.Generator(device=T.DEV)
+    g.manual_seed(npg + bits)
+    word = lambda k: torch.empty((n, k), dtype=torch.int32, device=T.DEV).random_(-2**31, 2**31 - 1, generator=g)  # noqa: E731
+    scalar = lambda: (0.3 * torch.randn(n, generator=g, device=T.DEV)).exp()  # noqa: E731
+    keys = word(pk.idx_words), word(pk.qjl_words), 0.3 * scalar(), scalar()
+    idx, qjl, gamma, norm = word(max(1, pv.idx_words)), word(pv.qjl_words), 0.3 * scalar(), scalar()
+    values = idx if bits else None, qjl if prod else None, gamma if prod else None, norm
+    q, joined, own = (torch.zeros((groups, D), device=T.DEV) for _ in range(3))
+    tq.tq_attend(pk, pv, q, groups, 1, keys, values, npg, 0.09, joined)
+    for g0 in range(0, groups, part):
+        cut = lambda ts: tuple(t if t is None else t[g0 * npg:(g0 + part) * npg] for t in ts)  # noqa: E731
+        tq.tq_attend(pk, pv, q[g0:g0 + part], part, 1, cut(keys), cut(values), npg, 0.09, own[g0:g0 + part])
+    mean = lambda t: t.view(groups, npg, D).mean(1)  # noqa: E731
+    want = mean(norm.double()[:, None] * table(c32)[unpack(idx, bits, D).long()]) @ T.dev(Pi).double() if bits else 0.0
+    if prod:
+        want = want + math.sqrt(math.pi / 2) / D * mean((norm.double() * gamma.double())[:, None] * (2.0 * unpack(qjl, 1, D) - 1).double()) @ T.dev(S).double()
+    error = lambda o: float((((o.double() - want).pow(2).sum(1) / want.pow(2).sum(1)).mean()).sqrt())  # noqa: E731
+    mine, theirs = error(own), error(joined)
+    print(f"{npg} tokens, {bits} bits{' and signs' if prod else ''}: {mine:.3e}, joined {theirs:.3e}")
+    # Values of three planes and more than 256 tokens: eight wavefronts' sums of 64 keys are added one after the other, of 256 keys in a call with
+    # many groups, so two here.  (2 + 3 + ... + 8) / 8 - 1 = 3.4 more squared roundings, each 2^-24 / sqrt(3) at most of the sum, 0.72 of that in the
+    # root mean square of mantissas from 1 to 2.
+    more = 3.4 * (0.72 * 2.0**-24 / math.sqrt(3)) ** 2 if npg > 256 and bits + prod > 2 else 0.0
+    # 40960 coordinates: two independent estimates of one error differ by 0.5 %
+    assert mine <= 1.02 * math.sqrt(theirs**2 + more), (mine, theirs)
