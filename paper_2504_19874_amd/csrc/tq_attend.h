@@ -41,6 +41,8 @@ struct AttendTables {
 // d = 128 on the integer matrix cores (tq_attend_128.hip)
 // Keys of a chunk (a workgroup): 256 (four wavefronts of 64), 512 (eight of 64) or 2048 (eight of 256).
 constexpr int AT_KEYS[3] = {256, 512, 2048};
+// Of a value code's planes: whether chunks of 256 keys are ever taken.  The kernels for them exist for such values only.
+__host__ __device__ constexpr bool attend128_takes_256(int planes) { return planes > 2; }
 inline int attend128_chunks(int64_t n, int keys) { return (int)((n + keys - 1) / keys); }
 // planes: of a value code, the signs of Alg. 2 or the top plane of instance hi among them
 int attend128_keys(int64_t n, int n_groups, int q_per_group, int planes);

@@ -32,12 +32,12 @@ bool coefficients(const Codebook& cb, AttendCoefs* out) {
 }  // namespace
 int attend128_keys(int64_t n, int n_groups, int q_per_group, int planes) {
   if (n > AT_KEYS[0] && n <= AT_KEYS[1] && n <= limit(1, n_groups, q_per_group)) return AT_KEYS[1];  // one chunk, which needs no joining
-  if (planes > 2 && n <= limit(0, n_groups, q_per_group)) return AT_KEYS[0];
+  if (attend128_takes_256(planes) && n <= limit(0, n_groups, q_per_group)) return AT_KEYS[0];
   return n <= limit(1, n_groups, q_per_group) ? AT_KEYS[1] : AT_KEYS[2];
 }
 int attend128_max_chunks(int64_t n, int n_groups, int q_per_group, int planes) {
   int most = attend128_chunks(n, AT_KEYS[2]);
-  for (int i = planes > 2 ? 0 : 1; i < 2; ++i) {
+  for (int i = attend128_takes_256(planes) ? 0 : 1; i < 2; ++i) {
     const int64_t lim = limit(i, n_groups, q_per_group);
     const int c = attend128_chunks(n < lim ? n : lim, AT_KEYS[i]);
     most = c > most ? c : most;

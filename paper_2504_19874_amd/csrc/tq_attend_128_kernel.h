@@ -596,12 +596,15 @@ hipError_t launch_attend128_tiles(const ScoreI8Args& ka, const AttendArgs& a, co
 template <int KB, bool KPROD, int VB, int VKIND, bool FUSED>
 hipError_t launch_attend128_one(const ScoreI8Args& ka, const AttendArgs& a, const AttendCoefs& cf, const AttendCoefs& cfh,
                                 int n_groups, hipStream_t s) {
-  switch (a.keys * 2 + (a.out != nullptr ? 1 : 0)) {
-    case 2 * 256: return launch_attend128_tiles<KB, KPROD, VB, VKIND, FUSED, 4, 4, false>(ka, a, cf, cfh, n_groups, s);
-    case 2 * 256 + 1: return launch_attend128_tiles<KB, KPROD, VB, VKIND, FUSED, 4, 4, true>(ka, a, cf, cfh, n_groups, s);
-    case 2 * 512: return launch_attend128_tiles<KB, KPROD, VB, VKIND, FUSED, 4, 8, false>(ka, a, cf, cfh, n_groups, s);
-    case 2 * 512 + 1: return launch_attend128_tiles<KB, KPROD, VB, VKIND, FUSED, 4, 8, true>(ka, a, cf, cfh, n_groups, s);
-    case 2 * 2048: return launch_attend128_tiles<KB, KPROD, VB, VKIND, FUSED, 16, 8, false>(ka, a, cf, cfh, n_groups, s);
+  const bool finish = a.out != nullptr;
+  if constexpr (attend128_takes_256(at_planes(VB, VKIND != 0)))
+    if (a.keys == 256)
+      return finish ? launch_attend128_tiles<KB, KPROD, VB, VKIND, FUSED, 4, 4, true>(ka, a, cf, cfh, n_groups, s)
+                    : launch_attend128_tiles<KB, KPROD, VB, VKIND, FUSED, 4, 4, false>(ka, a, cf, cfh, n_groups, s);
+  switch (a.keys) {
+    case 512: return finish ? launch_attend128_tiles<KB, KPROD, VB, VKIND, FUSED, 4, 8, true>(ka, a, cf, cfh, n_groups, s)
+                            : launch_attend128_tiles<KB, KPROD, VB, VKIND, FUSED, 4, 8, false>(ka, a, cf, cfh, n_groups, s);
+    case 2048: return finish ? hipErrorInvalidValue : launch_attend128_tiles<KB, KPROD, VB, VKIND, FUSED, 16, 8, false>(ka, a, cf, cfh, n_groups, s);
     default: return hipErrorInvalidValue;
   }
 }

@@ -230,3 +230,24 @@ def test_binding_rejects_short_or_mistyped_code_tensors():
     with pytest.raises(api.TurboQuantError, match="q:"):
         api._check_score_args(Shape, q[:7], 2, 4, good["idx"], None, None, None, 5, None, 3,
                               torch.zeros(24, dtype=torch.int32), None)
+
+
+def test_attend_kernels_are_the_ones_that_a_call_can_reach(lib):
+    """Chunks of 256 keys (four wavefronts) are taken for value codes of three planes or more only; a chunk of 2048 is never finished by its
+    own workgroup.  The library holds no kernel for the others."""
+    import shutil
+    import subprocess
+    from paper_2504_19874_amd import _lib
+    if shutil.which("nm") is None:
+        pytest.skip("no nm to list the library's symbols with")
+    names = subprocess.run(["nm", "-C", _lib.LIB_PATH], capture_output=True, text=True, check=True).stdout
+    kernels = set(re.findall(r"__device_stub__attend128_kernel<(\d), (\w+), (\d), (\d), (\w+), (\d+), (\d), (\w+)>", names))
+    value = {(vb, kind) for _, _, vb, kind, *_ in kernels}
+    assert value == {("1", "0"), ("2", "0"), ("3", "0"), ("4", "0"), ("0", "1"), ("1", "1"), ("2", "1"), ("1", "2"), ("2", "2")}
+    shapes = {}
+    for _, _, vb, kind, _, tiles, waves, finish in kernels:
+        shapes.setdefault(int(vb) + (kind != "0"), set()).add((int(tiles), int(waves), finish == "true"))
+    joined = {(4, 8, False), (4, 8, True), (16, 8, False)}
+    for planes, have in shapes.items():
+        assert have == (joined | {(4, 4, False), (4, 4, True)} if planes > 2 else joined), (planes, have)
+    assert len(kernels) == 10 * (5 * 3 + 4 * 5)
