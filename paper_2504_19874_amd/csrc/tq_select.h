@@ -4,10 +4,6 @@
 
 namespace tq {
 
-__device__ __forceinline__ bool better(float va, int ia, float vb, int ib) {
-  return va > vb || (va == vb && ia < ib);
-}
-
 // order-preserving map to the unsigned integers
 __device__ __forceinline__ uint32_t ordered(float f) {
   const uint32_t b = __float_as_uint(f);
