@@ -21,7 +21,7 @@ __device__ __forceinline__ int sum_of_lanes(int v, int lanes) {
 }
 
 // a value that at least k of the workgroup's scores reach (-inf where there are fewer), close to the k-th largest: one that k, or an
-// eighth more, of 256 maxima `mx` of T threads (-inf: none) reach, of 64 for k <= 16 (neighbouring threads' maxima joined; of 8192 scores
+// eighth more (up to 8 for k < 8), of 256 maxima `mx` of T threads (-inf: none) reach, of 64 for k <= 16 (neighbouring threads' maxima joined; of 8192 scores
 // 10.9 are expected to reach the 10th largest of 64, 10.2 that of 256).  keys [256], bar: LDS.  A wavefront halves the range between the
 // smallest and the largest of them, some five steps of a comparison or four and as many counts.  (Ranked against each other in
 // place of this: 600 instructions per wavefront for k > 16.)
@@ -53,7 +53,9 @@ __device__ __forceinline__ float kth_of_maxima(float mx, int k, uint32_t* keys, 
     hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)hi) + 1u;  // none reaches it (no score is as large as the largest integer)
     int n = lo < hi ? count(lo) : 0;  // that reach lo
     if (n < k) lo = NONE;
-    while (n > k + k / 8 && hi - lo > 1u) {
+    if (k == 1) lo = hi - 1u, n = 1;  // the largest itself
+    const int enough = k < 8 ? 8 : k + k / 8;
+    while (n > enough && hi - lo > 1u) {
       const uint32_t mid = lo + (hi - lo) / 2u;
       const int m = count(mid);
       if (m >= k) lo = mid, n = m;

@@ -88,6 +88,21 @@ def test_segments_and_threads(kind, nq, n, topk):
         assert np.array_equal(tv[r, :k].cpu().numpy().view(np.int32), s[r][want].view(np.int32))  # the sign of a zero, too
 
 
+@pytest.mark.parametrize("nq,n", [(257, 9217), (513, 8193), (513, 200003), (768, 20001),  # more rows than the chip takes of 1024 threads, up to three of 512 each
+                                  (769, 8192), (769, 40001), (1024, 8191), (1025, 20001), (1025, 40001),  # a few more, many more; long and short rows
+                                  (43, 131072), (64, 131071), (65, 131073), (24, 200001), (100, 41001)])  # chunks of 512 threads, of 1024, two to a compute unit
+@pytest.mark.parametrize("topk", [1, 3, 16, 64])  # the largest maximum is the bar, up to eight of them pass
+@pytest.mark.parametrize("kind", ["drawn", "rising", "zeros", "infinite"])
+def test_rows_that_fill_the_chip(kind, nq, n, topk):
+    p, c = case(kind, n)
+    scores, (ti, tv), _ = call(p, both_signs(nq), c, n, topk, nq)
+    for r in (0, nq // 2 - 1, nq - 1):
+        s = scores[r].cpu().numpy()
+        want = np.argsort(-s, kind="stable")[:topk]  # equal scores by lower index
+        assert np.array_equal(ti[r].cpu().numpy(), want)
+        assert np.array_equal(tv[r].cpu().numpy().view(np.int32), s[want].view(np.int32))
+
+
 @pytest.mark.parametrize("nq", [2, 129])  # a segment per workgroup, seven
 @pytest.mark.parametrize("kind", ["rising", "equal", "ties at the end", "steps"])
 def test_their_cost_is_bounded(kind, nq):
