@@ -23,10 +23,13 @@ namespace {
 constexpr int PER = 16;  // scores of a segment per thread
 constexpr int THREADS = 1024;                 // of a workgroup at most; a segment has 16384 scores then
 constexpr int SEG = THREADS * PER;
+// Workgroups that a compute unit holds: left alone, the kernel takes 65 to 69 registers, seven wavefronts on a SIMD.  For two workgroups of 1024, or four of
+// 512, the compiler is held to 64 (512 rows of 100000, k = 64: 47.5 -> 38.3 us); where fewer are at work that is 2 - 6 % slower.
+constexpr int CU_256 = 7, CU_512 = 3, CU_1024 = 2;
 // chunk_len > 0: workgroup (row, chunk) takes columns [c0, c0 + chunk_len) of the row (chunk_len is a multiple of
 // 4, so a chunk is as aligned as the row) and writes k (value, index) pairs, -inf / INT_MAX where it has fewer
-template <int T>
-__global__ __launch_bounds__(T) void topk_kernel(const float* __restrict__ scores, const int64_t n_row, const int64_t ld, const int k,
+template <int T, int PER_CU>
+__global__ __launch_bounds__(T, T / 256 * PER_CU) void topk_kernel(const float* __restrict__ scores, const int64_t n_row, const int64_t ld, const int k,
                                                  const int vec4, int32_t* __restrict__ out_idx, float* __restrict__ out_val,
                                                  const int64_t chunk_len, const int32_t* __restrict__ flags) {
   if (flags != nullptr && flags[blockIdx.x] == 0) return;
@@ -93,25 +96,24 @@ __global__ __launch_bounds__(T) void topk_merge_kernel(const float* __restrict__
 
 }  // namespace
 
-// Chunks per row when a call's rows are too few to fill the chip: 0 (one workgroup per row) unless the rows are
-// few and longer than three segments (two and a half for k > 16); then chunks of equal lengths, a segment at most (down to 4096 scores in chunks of 256 threads: no
-// faster), and no more pairs per row than the joining kernel takes (4096).  A workgroup takes 4.7 us (k = 10) or 6 (64) for a segment and 2 for every further one, its lists joined 4.3 to 6.  us, one workgroup per
-// row / chunks + joining:
-//   10 rows of 20000, k = 64   8.2 / 10.8
-//   2 rows of 49000, k = 64   10.7 / 10.4;  60: 12.0 / 10.9;  2 of 33000 9.1 / 10.3
-//   2 rows of 49000, k = 10    8.0 /  8.1;  60: 8.5 / 8.7
-//   100 rows of 41500, k = 64 11.5 / 13.9 (what more rows than compute units for their chunks lose; 23.6 before)
-//   2 rows of 56430, k = 10    9.6 /  8.4
-//   14 rows of 84645, k = 64  18.1 / 11.2
-// More segments than compute units: as many chunks as make two workgroups of 512 threads for each, all of them at work at once, so that a second
-// segment costs its 2 us only.  us, chunks of a segment / so (a workgroup per row):
-//   32 rows of 400000, k = 10  22.4 / 16.8 (42);  64 of 10^6 72.0 / 43.4 (91);  128 of 300000 47.4 / 29.5 (37)
-//   32 rows of 10^6, k = 64    50.6 / 34.3 (132);  128 of 200000 44.3 / 31.1 (37);  8 of 10^6, k = 10 12.5 / 10.9 (80)
+// Chunks per row when a call's rows are too few to fill the chip: 0 (one workgroup per row) unless the rows are few and longer than three
+// segments of 1024 threads, two and a half for k > 16 (us, one workgroup per row / chunks: 128 rows of 41000, k = 10, 8.6 / 10.1; 128 of 49200 10.2 / 9.7; 100
+// of 41000, k = 64, 12.6 / 12.8; 128 of 60000 15.6 / 13.5).  Then, while all of them are at work at once,
+//   a segment of 1024 threads each, one workgroup to a compute unit   43 rows of 60000, k = 16, 8.7 (of 512 threads 9.4)
+//   k <= 16: a segment of 512 threads each                            43 rows of 131072, k = 10, 8.8 (of 1024 9.1); 5 of 10^6 9.7 (10.0)
+//   a segment of 1024 threads each, two to a compute unit             64 rows of 131072, k = 10, 9.9; 64 of 100000, k = 64, 13.2
+//   the same by 512 threads in two steps                              65 rows of 131072, k = 10, 11.5; 86 13.9
+// and beyond, two workgroups of 512 threads to a compute unit with as many segments as it takes (33 rows of 10^6, k = 10, 27.6; three of them 28.7).
+// With segments of 1024 threads and then two workgroups of 512, whatever the row: 10.2, 10.9, 10.9 / 15.2, 13.4, 16.4; with 256 threads of 32 scores and
+// up to four chunks to a compute unit, before that: 9.0, 10.2, 9.9 / 24.9, 11.6, 20.3, 35.3.  No more pairs per row than the joining kernel takes (4096).
 int topk_chunks(int64_t rows, int64_t n, int k) {
   if (k < 1 || rows < 1 || rows > 128 || n <= (k <= 16 ? 3 * SEG : 5 * SEG / 2)) return 0;
-  int64_t c = (n + SEG - 1) / SEG;
-  if (const int64_t cus = device_cu_count(); rows * c > cus) c = std::min(c, 2 * cus / rows);
-  if (c > 4096 / k) c = 4096 / k;
+  const int64_t cus = device_cu_count(), most = 4096 / k;
+  auto of = [&](int64_t len) { return (n + len - 1) / len; };
+  int64_t c = of(SEG);
+  if (k <= 16 && rows * c > cus && rows * of(SEG / 2) <= CU_512 * cus) c = of(SEG / 2);
+  if (rows * c > CU_512 * cus) c = 2 * cus / rows;
+  c = std::min(c, most);
   return c >= 2 ? (int)c : 0;
 }
 
@@ -130,19 +132,37 @@ hipError_t launch_topk(const float* scores, int64_t rows, int64_t n, int64_t ld,
     out_idx = part_idx;
     out_val = part_val;
   }
-  // As many threads as a row's first segment needs, but more rows at a time where there are more than the chip takes of the largest
-  // workgroups (us, 256 / 512 / 1024 threads: 1000 rows of 9766, k = 10, 10.9 / 12.7 / 17.0; 871 of 16000, k = 64, 23.1 / 19.9 / 23.3;
-  // 45 of 16000, k = 64, 17.0 / 9.5 / 6.1)
-  const bool crowd = rows > 2 * (int64_t)device_cu_count();
-  const int64_t len = chunks > 0 ? chunk_len : n;
-  auto go = [&](auto t_c) {
+  const int64_t len = chunks > 0 ? chunk_len : n, cus = device_cu_count();
+  auto go = [&](auto t_c, auto per_cu_c) {
     constexpr int T = decltype(t_c)::value;
-    hipLaunchKernelGGL((topk_kernel<T>), grid, dim3(T), 0, stream, scores, n, ld, k, vec4, out_idx, out_val, chunk_len, flags);
+    hipLaunchKernelGGL((topk_kernel<T, decltype(per_cu_c)::value>), grid, dim3(T), 0, stream, scores, n, ld, k, vec4, out_idx, out_val, chunk_len, flags);
     return hipGetLastError();
   };
-  if (len <= 256 * PER || (crowd && k <= 16)) return go(std::integral_constant<int, 256>{});
-  if (len <= 512 * PER || crowd || (chunks > 0 && rows * chunks > device_cu_count())) return go(std::integral_constant<int, 512>{});
-  return go(std::integral_constant<int, THREADS>{});
+  auto go_256 = [&] { return go(std::integral_constant<int, 256>{}, std::integral_constant<int, CU_256>{}); };
+  auto go_512 = [&] { return go(std::integral_constant<int, 512>{}, std::integral_constant<int, CU_512>{}); };
+  auto go_1024 = [&](int64_t workgroups) {
+    return workgroups <= cus ? go(std::integral_constant<int, THREADS>{}, std::integral_constant<int, 1>{})
+                             : go(std::integral_constant<int, THREADS>{}, std::integral_constant<int, CU_1024>{});
+  };
+  if (len <= 256 * PER) return go_256();
+  // As many threads as a row's first segment needs, while all workgroups are at work at once
+  if (chunks > 0) return len > 512 * PER && rows * chunks <= (len <= SEG ? CU_1024 : 1) * cus ? go_1024(rows * chunks) : go_512();
+  // (us, 512 / 1024 threads: 512 rows of 8193, k = 16, 6.4 / 7.0, of 9766 7.0 / 6.8; 129 of 9766, k = 10, 5.9 / 5.2)
+  if (rows <= CU_1024 * cus) return len <= (rows <= cus ? 512 : 576) * PER ? go_512() : go_1024(rows);
+  // More rows: 512 threads; 256 for k <= 16 where those would need a second round or rows are short, and for the longest.  us, 256 / 512 / 512 threads held to 64 registers
+  // (256 of 32 scores each, before):
+  //   513 rows, k = 10, of 8192     6.4 /  5.2 /  5.4 (4.8);  of 16384 10.1 / 7.2 / 7.7 (7.4);  k = 16 of 100000 43.9 / 34.2 / 34.9 (36.1)
+  //   513 rows, k = 1, of 300000    107 /  123 /  124 (125);  577 of 527352, k = 10, 211 / 231 (231)
+  //   900 rows, k = 10, of 8192     7.3 /  7.3 /  6.4 (5.4);  of 16384 12.9 / 13.6 / 12.9 (12.3);  of 100000 64.2 / 73.6 / 70.1 (68.6)
+  //   1024 rows, k = 64, of 40000  41.8 / 38.2 / 33.3 (57.1);  of 100000 89.9 / 95.3 / 85.5 (110)
+  //   1200 rows, k = 10, of 9766   12.1 / 14.7 / 14.7 (15.5);  of 20000 18.7 / 20.0 / 21.0 (24.1)
+  //   2000 rows, k = 10, of 40000  57.4 / 52.5 / 55.5 (58.7);  of 100000 142.8 / 138.5 / 145.3 (140.2)
+  if (rows <= CU_512 * cus) return k <= 16 && len >= 12 * SEG ? go_256() : go_512();
+  if (rows <= (CU_512 + 1) * cus) {
+    if (k <= 16 && len > 512 * PER) return go_256();
+    return go(std::integral_constant<int, 512>{}, std::integral_constant<int, CU_512 + 1>{});
+  }
+  return k <= 16 && len < 2 * SEG ? go_256() : go_512();
 }
 
 hipError_t launch_topk_merge(const float* part_val, const int32_t* part_idx, int64_t rows, int ranges, int k,

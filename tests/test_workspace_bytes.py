@@ -33,3 +33,20 @@ def test_no_room_to_split_queries_that_matrix_vector_products_rotate(d, most, pr
     assert call(most + 1) >= result(most + 1) + (most + 1) * d * 4 + (2 if prod else 1) * 4 * d * d
     bound = lambda nq: lib.tq_workspace_bytes(C.byref(p), 0, nq, 0)  # noqa: E731
     assert bound(most + 1) - bound(most) >= (most + 1) * d * 4 + (2 if prod else 1) * 4 * d * d
+
+
+@pytest.mark.parametrize("rows,n,topk,chunks", [
+    (128, 41000, 10, 0), (129, 200000, 10, 0), (128, 40960, 64, 0), (100, 41000, 64, 3),  # one workgroup per row
+    (43, 60000, 16, 4), (4, 1000000, 10, 62), (1, 4000000, 64, 64),  # a segment of 1024 threads each; no more pairs than are joined in one go
+    (43, 131072, 10, 16), (5, 1000000, 1, 123), (65, 66000, 16, 9),  # of 512 threads, three to a compute unit at most
+    (43, 131072, 17, 8), (64, 131072, 10, 8), (86, 131072, 10, 8),  # of 1024 threads, two to a compute unit, or 512 threads in two steps
+    (128, 200000, 10, 4), (33, 1000000, 64, 15),  # two workgroups to a compute unit
+])
+def test_lists_of_a_top_k_over_chunks(rows, n, topk, chunks):
+    """As many chunks of a row as are all at work at once on 256 compute units: each has a list of topk pairs."""
+    c, t = (C.c_float * 4)(-1, -0.5, 0.5, 1), (C.c_float * 3)(-0.75, 0, 0.75)
+    p = _lib.TqParams()
+    p.d, p.bits_mse = 128, 2
+    p.centroids, p.bounds = C.addressof(c), C.addressof(t)
+    call = lambda k: _lib.load().tq_score_workspace_bytes(C.byref(p), rows, 1, n, 0, 1, k)  # noqa: E731
+    assert call(topk) - call(0) == 2 * ((rows * chunks * topk * 4 + 255) // 256 * 256)
