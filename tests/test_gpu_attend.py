@@ -122,6 +122,22 @@ def test_attend_over_one_chunk(vb, vprod, qpg, npg, fused):
     run_attend(128, 2, True, vb, vprod, 3, qpg, npg, fused)
 
 
+@pytest.mark.parametrize("vb,vprod,npg", [(2, False, 100), (4, False, 256), (2, True, 37), (3, False, 512)])
+def test_attend_over_one_chunk_into_rows_further_apart(vb, vprod, npg):
+    """The workgroup that rotates its own sums back keeps to the output's rows: what lies between them stays, and five queries a group leave
+    the last workgroup three places without one."""
+    d, qpg, groups = 128, 5, 3
+    pk, pv = setup(d, 2, True, 100, 200)[0], setup(d, vb, vprod, 300, 400)[0]
+    rng = np.random.default_rng(npg)
+    k_dev, v_dev = random_codes(rng, groups * npg, d, 2, True, 0.3)[1], random_codes(rng, groups * npg, d, vb, vprod, 1.0)[1]
+    q = dev(W.gaussian_queries(groups * qpg, d, 3, unit=False))
+    dense = torch.full((groups * qpg, d), float("nan"), device=DEV)
+    tq.tq_attend(pk, pv, q, groups, qpg, k_dev, v_dev, npg, 0.1, dense)
+    wide = torch.full((groups * qpg + 1, d + 72), -7.0, device=DEV)
+    tq.tq_attend(pk, pv, q, groups, qpg, k_dev, v_dev, npg, 0.1, wide[:-1, :d])
+    assert torch.equal(wide[:-1, :d], dense) and bool((wide[:, d:] == -7).all()) and bool((wide[-1] == -7).all())
+
+
 @pytest.mark.parametrize("table", [[0.02, 0.15], [-0.05, 0.03, 0.07, 0.15]])
 def test_attend_with_a_table_that_is_not_centred_and_norms_of_either_sign(table):
     """A table symmetric about a mean other than zero is what the sums of signs take with one term more; weights are

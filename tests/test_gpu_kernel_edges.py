@@ -119,14 +119,53 @@ def test_search_by_candidates(d, bits, prod, nq, n, topk):
 
 
 @pytest.mark.parametrize("d,bits,prod,nq,n,topk", [
-    (128, 1, False, 32, 70001, 10), (128, 2, False, 97, 140033, 3), (256, 3, True, 96, 8321, 64), (384, 4, True, 128, 9999, 16),
+    (1152, 1, False, 32, 140033, 10), (128, 2, False, 97, 140033, 3), (256, 3, True, 96, 8321, 64), (384, 4, True, 128, 9999, 16),
     (128, 4, True, 40, 66000, 64), (512, 0, True, 64, 16385, 1), (2048, 2, True, 145, 8192, 7), (3072, 1, False, 129, 10001, 10),
     (256, 2, True, 641, 23041, 5),
 ])
 def test_search_by_candidates_few_queries(d, bits, prod, nq, n, topk):
-    """Every block of 32 queries and kind of code of the kernel for few, several tiles to a workgroup, long codes; numbers of query blocks that
-    do not divide the chip."""
+    """The kernel for few queries: one to four blocks of 32 of them, long codes, numbers of query blocks that do not divide the chip.  (Up to 32
+    queries come to it beyond d = 1024 only.)"""
     test_search_by_candidates(d, bits, prod, nq, n, topk)
+
+
+def search_flags(p, q, c, d, prod, nq, n, topk):
+    """Which queries of a search without a score buffer overflowed their lists, from the words that say so in the workspace: behind the rotated queries
+    and the score matrix (topk > 16) that such queries need, where matrix-vector products rotate them."""
+    assert topk > 16 and (d == 128 or nq * d <= 65536)
+    p.workspace, p.c.workspace, p.c.workspace_bytes = None, 0, 0
+    p.reserve_score(1, nq, n, prod, False, topk)
+    p.workspace.fill_(85)
+    top = torch.zeros((nq, topk), dtype=torch.int32, device=T.DEV), torch.zeros((nq, topk), device=T.DEV)
+    tq.tq_score(p, q, 1, nq, c["idx"], c["qjl"], c["gamma"], c["norm"], n, None, topk, *top)
+    line = lambda b: (b + 255) // 256 * 256  # noqa: E731
+    at = line(nq * d * 4) * (2 if prod else 1) + line(nq * ((n + 3) // 4 * 4) * 4)
+    return p.workspace.view(torch.uint8)[at:at + 4 * nq].view(torch.int32).cpu().numpy()
+
+
+@pytest.mark.parametrize("d,bits,prod,nq,n,topk", [
+    (1152, 2, False, 32, 140033, 17), (1152, 3, True, 17, 140033, 64), (1152, 4, False, 21, 140033, 64), (1152, 1, True, 29, 131201, 20),
+    (1152, 0, True, 32, 135000, 17), (128, 0, True, 64, 140033, 17), (256, 4, True, 57, 70001, 33), (128, 3, True, 96, 140033, 17), (128, 4, False, 128, 140033, 64),
+    (128, 1, False, 200, 30001, 17), (128, 2, True, 500, 140033, 33),
+])
+def test_search_finds_no_more_candidates_than_it_has_room_for(d, bits, prod, nq, n, topk):
+    """Several tiles of codes to a workgroup in every block size of the kernel for few queries and in the one for many; and of random codes no query's
+    list overflows, so that the answer is the candidates' and not that of the kernels which look at everything."""
+    p = T.setup(d, bits, prod)[0]
+    c = T._random_codes(p, d, bits, prod, n, d + n)
+    q = T.dev(W.gaussian_queries(nq, d, 3, unit=False))
+    T._topk_both_ways(p, q, 1, nq, c, n, topk)
+    assert (search_flags(p, q, c, d, prod, nq, n, topk) == 0).all()
+
+
+@pytest.mark.parametrize("d,nq", [(1152, 20), (128, 70), (128, 200)])
+def test_search_says_which_lists_are_too_short(d, nq):
+    """Equal scores: every query's list overflows."""
+    n = 20000
+    p = T.setup(d, 2, False)[0]
+    c = T._random_codes(p, d, 2, False, n, 4)
+    c["idx"], c["norm"] = c["idx"][:1].repeat(n, 1).contiguous(), torch.ones(n, device=T.DEV)
+    assert (search_flags(p, T.dev(W.gaussian_queries(nq, d, 9, unit=False)), c, d, False, nq, n, 17) == 1).all()
 
 
 @pytest.mark.parametrize("d,bits,prod", [(128, 2, True), (256, 3, False)])
