@@ -352,24 +352,48 @@ hipError_t launch_t(StreamArgs a, int64_t gx, int qz, int threads, int per_cu, i
   return hipGetLastError();
 }
 
-template <int BITS, bool PROD, int W, int QB>
-hipError_t launch_w(const StreamArgs& a, int n_groups, hipStream_t s) {
-  using C = StreamCfg<BITS, PROD, QB>;
-  constexpr int T = C::tiles(W);
+// Which grid a call takes, with QB blocks of four queries a pass and wavefronts of T tiles
+struct StreamPlan {
+  bool one_tile;
+  int64_t gx;  // workgroups to a block of queries
+  int per_cu;
+  int64_t walk;  // tiles that a wavefront takes one after the other
+};
+StreamPlan stream_plan(const StreamArgs& a, int n_groups, int QB, int T, int NT, int NV) {
+  StreamPlan p;
   const int qz = (a.q_per_group + 4 * QB - 1) / (4 * QB);
   const int64_t others = (int64_t)n_groups * qz, cus = device_cu_count();
   // one workgroup per compute unit (two where registers and LDS admit them), each walking its share of the keys; a list too
-  // short for that in wavefronts of one tile and workgroups of four (10^4 codes of 3072 coordinates, 2 queries, 3 + 1 bits: 20.9 us -> 16.6),
-  // if little more of these come to a compute unit than its LDS holds at once (16 queries of 3072, 1 + 1 bits, 20000 codes: 64 -> 54).  No more
-  // workgroups than there is room for: the last few made a second round (24 queries of 768, 2 bits, 300000 codes: 258 of them 59.9, 255 41.4).
+  // short for that in wavefronts of one tile and workgroups of four (10^4 codes of 3072 coordinates, 2 queries, 3 + 1 bits: 20.9 us -> 16.6), if
+  // all of these are at work in one round.  Where a wavefront would have four tiles, a quarter more than that; two rounds with the digits of both
+  // matrices and four queries a pass.  us, several tiles / one:
+  //   two tiles, 1.04 rounds       5 queries of 3200, 4 + 1 bits, 17000 codes 51.1 / 58.7;  1.1: 3 of 3072, 2 + 1 bits, 36000 35.0 / 39.7
+  //   four, 1.53 rounds            5 of 3200, 1 + 1 bits, 25000 codes 64.6 / 53.2;  3 rounds: 16 of 3072, 20000 54 / 64
+  //   four, eight queries a pass   8 groups of 16 of 512, 1 + 1 bits, 5790 codes, 1.42 rounds 20.8 / 23.7;  13 of 3456, 1 bit, 11762 42.0 / 45.6
+  // No more workgroups than there is room for: the last few made a second round (24 queries of 768, 2 bits, 300000 codes: 258 of them 59.9, 255 41.4).
   const int64_t nwg = (a.n + 128 * T - 1) / (128 * T);
-  const int64_t short_wgs = (a.n + 63) / 64 * others, digits = a.groups_d * C::NV * QB * 384;
-  if (nwg * others * 4 <= cus * 3 && short_wgs * 4 <= cus * 5 * std::min<int64_t>(4, kMaxLdsBytes / digits))
-    return launch_t<BITS, PROD, W, QB, true>(a, (a.n + 63) / 64, qz, 256, 1, n_groups, s);
-  const int per_cu = C::NT * QB * T <= 4 && a.groups_d * C::NV * QB * 384 <= 72 * 1024 ? 2 : 1;
-  int64_t gx = std::max<int64_t>(1, per_cu * cus / others);
-  if (gx > nwg) gx = nwg;
-  return launch_t<BITS, PROD, W, QB, false>(a, gx, qz, 512, per_cu, n_groups, s);
+  const int64_t short_wgs = (a.n + 63) / 64 * others, digits = a.groups_d * NV * QB * 384, held = cus * std::min<int64_t>(4, kMaxLdsBytes / digits);
+  const int quarters = T < 4 ? 4 : QB == 1 && NV == 2 ? 8 : 5;
+  p.one_tile = nwg * others * 4 <= cus * 3 && short_wgs * 4 <= held * quarters;
+  if (p.one_tile) {
+    p.gx = (a.n + 63) / 64;
+    p.per_cu = 1;
+    p.walk = (short_wgs + held - 1) / held;
+  } else {
+    p.per_cu = NT * QB * T <= 4 && digits <= 72 * 1024 ? 2 : 1;
+    p.gx = std::min(nwg, std::max<int64_t>(1, p.per_cu * cus / others));
+    p.walk = (nwg + p.gx - 1) / p.gx * T;
+  }
+  return p;
+}
+
+template <int BITS, bool PROD, int W, int QB>
+hipError_t launch_w(const StreamArgs& a, int n_groups, hipStream_t s) {
+  using C = StreamCfg<BITS, PROD, QB>;
+  const StreamPlan p = stream_plan(a, n_groups, QB, C::tiles(W), C::NT, C::NV);
+  const int qz = (a.q_per_group + 4 * QB - 1) / (4 * QB);
+  return p.one_tile ? launch_t<BITS, PROD, W, QB, true>(a, p.gx, qz, 256, p.per_cu, n_groups, s)
+                    : launch_t<BITS, PROD, W, QB, false>(a, p.gx, qz, 512, p.per_cu, n_groups, s);
 }
 
 // word groups per step for rows of 128 m coordinates
@@ -393,15 +417,29 @@ hipError_t launch_qb(const StreamArgs& a, int n_groups, hipStream_t s) {
   return launch_w<BITS, PROD, 1, QB>(a, n_groups, s);
 }
 
-// four queries per pass over the codes, or eight where there are more than four and their digits fit LDS beside a block's scores; digits that
-// fill it only where two passes become one over a long list (us, four / eight, 3072 coordinates, 1 + 1 bits: 9 queries, 300000 codes 208 / 130;
-// 60000 77 / 63; 16 queries, 32768 codes 55 / 63; 5 queries, 60000 codes 50 / 59)
+// Four queries per pass over the codes, or eight where there are more than four and their digits fit LDS beside a block's scores.  Digits that fill it
+// (two-stage codes of 3072 and 3200 coordinates) take twice as long to fetch as those of four, so there eight have to save a wavefront tiles: any where a
+// tile takes long (3 + 1 bits; steps of one word group, each a trip to memory), four of them up to 2 + 1 bits, and at 4 + 1, where a wavefront has room
+// for the sums of one tile instead of two, more than three of eight, or a quarter.  us, four / eight a pass:
+//   3072, 1 + 1 bits   9 queries: 40000 codes 48.6 / 56.2, 400000 155 / 144;  8: 60000 41.6 / 50.5, 400000 118 / 112
+//         2 + 1        16: 30000 53.7 / 61.3, 60000 69.9 / 60.0;  4 groups of 16: 8000 110 / 121, 30000 158 / 136
+//         3 + 1        5: 20000 44.1 / 56.2, 40000 53.0 / 46.3, 400000 219 / 176
+//         4 + 1        9: 20000 55.4 / 64.0, 30000 71.4 / 64.4, 400000 379 / 394;  16: 400000 499 / 419
+//   3200, 2 + 1        5: 17000 52.6 / 63.4, 36000 65.2 / 54.3, 390000 331 / 214;  9: 36000 66.5 / 70.4
+//         3 + 1        9: 40000 72.5 / 78.2;  8: 400000 398 / 273;  8 groups of 8: 20000 244 / 207
+//         4 + 1        9: 36000 77.7 / 83.0, 200000 294 / 253;  5: 390000 369 / 267
 template <int BITS, bool PROD>
 hipError_t launch_bits(const StreamArgs& a, int n_groups, hipStream_t s) {
   using C = StreamCfg<BITS, PROD, 2>;
-  const int digits = a.groups_d * C::NV * 2 * 384, slot = 512 * 2 * C::tiles(stream_words<BITS, PROD, 2>(a.groups_d / 4)) * 4;
-  bool eight = a.q_per_group > 4 && digits + slot <= kMaxLdsBytes;
-  if (digits > 140 * 1024) eight = eight && a.q_per_group > 8 && a.n >= 49152;
+  const int m = a.groups_d / 4, words = stream_words<BITS, PROD, 2>(m), tiles = C::tiles(words), digits = a.groups_d * C::NV * 2 * 384;
+  bool eight = a.q_per_group > 4 && digits + 512 * 2 * tiles * 4 <= kMaxLdsBytes;
+  if (eight && digits > 140 * 1024) {
+    using C4 = StreamCfg<BITS, PROD, 1>;
+    const int64_t walk4 = stream_plan(a, n_groups, 1, C4::tiles(stream_words<BITS, PROD, 1>(m)), C4::NT, C4::NV).walk;
+    const int64_t walk8 = stream_plan(a, n_groups, 2, tiles, C::NT, C::NV).walk;
+    if (BITS == 4) eight = words > 1 ? 8 * walk8 < 5 * walk4 : 4 * walk8 < 3 * walk4;
+    else eight = BITS == 3 || words == 1 ? walk8 < walk4 : walk8 + 4 <= walk4;
+  }
   return eight ? launch_qb<BITS, PROD, 2>(a, n_groups, s) : launch_qb<BITS, PROD, 1>(a, n_groups, s);
 }
 

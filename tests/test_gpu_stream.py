@@ -61,3 +61,51 @@ def test_blocks_of_queries(d, bits, prod, n, groups, nq):
     for i in (0, 3, 4, 7, 8, nq - 1):
         tq.tq_score(p, q.view(groups, nq, d)[:, i].contiguous(), groups, 1, c["idx"], c["qjl"], c["gamma"], c["norm"], n, one)
         assert torch.equal(out.view(groups, nq, n)[:, i], one)
+
+
+def random_words(p, n, seed):
+    g = torch.Generator(device=T.DEV).manual_seed(seed)
+    words = lambda k: torch.randint(-2**31, 2**31 - 1, (n, k), dtype=torch.int32, device=T.DEV, generator=g)  # noqa: E731
+    return words(p.idx_words), words(p.qjl_words), torch.rand(n, device=T.DEV, generator=g), torch.rand(n, device=T.DEV, generator=g) + 0.5
+
+
+# on either side of where eight queries a pass take the place of four
+@pytest.mark.parametrize("d,bits,groups,nq,n", [(3072, 1, 1, 9, 40001), (3072, 1, 1, 5, 390001), (3072, 2, 1, 16, 30001), (3072, 2, 1, 16, 60001), (3072, 3, 1, 8, 20001),
+                                                (3072, 3, 1, 8, 40001), (3200, 3, 4, 9, 8001), (3072, 4, 1, 9, 20001), (3072, 4, 1, 11, 30001), (3200, 4, 2, 7, 17001)])
+def test_four_or_eight_queries_a_pass(d, bits, groups, nq, n):
+    """Digits that fill LDS: the bits of one query at a time."""
+    p = T.setup(d, bits, True)[0]
+    c = random_words(p, groups * n, n)
+    q = torch.randn(groups * nq, d, device=T.DEV, generator=torch.Generator(device=T.DEV).manual_seed(n))
+    p.reserve(1, groups * nq, 0)
+    out, one = torch.zeros((groups * nq, n), device=T.DEV), torch.zeros((groups, n), device=T.DEV)
+    tq.tq_score(p, q, groups, nq, *c, n, out)
+    for i in {0, 3, 4, min(8, nq - 1), nq - 1}:
+        tq.tq_score(p, q.view(groups, nq, d)[:, i].contiguous(), groups, 1, *c, n, one)
+        assert torch.equal(out.view(groups, nq, n)[:, i], one)
+
+
+@pytest.mark.parametrize("d,bits,nq,most", [(3200, 3, 8, 1.7), (3072, 4, 16, 3.7)])
+def test_a_pass_serves_eight_queries_of_a_long_list(d, bits, nq, most):
+    """Four queries at a time would take nq / 4 times as long as four queries do."""
+    n = 300000
+    p = T.setup(d, bits, True)[0]
+    c = random_words(p, n, n)
+    p.reserve(1, nq, 0)
+
+    def us(k):
+        q, out = torch.randn(k, d, device=T.DEV), torch.zeros((k, n), device=T.DEV)
+        e = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+        best = float("inf")
+        for _ in range(6):
+            e[0].record()
+            for _ in range(4):
+                tq.tq_score(p, q, 1, k, *c, n, out)
+            e[1].record()
+            torch.cuda.synchronize()
+            best = min(best, e[0].elapsed_time(e[1]) * 250)
+        return best
+
+    four, all_of_them = us(4), us(nq)
+    print(f"4 queries {four:.0f} us, {nq} {all_of_them:.0f} us")
+    assert all_of_them <= most * four
