@@ -179,9 +179,9 @@ __global__ __launch_bounds__(512, 4) void score_i8_split_kernel(const ScoreI8Arg
   float* const out0 = a.scores + ((int64_t)group * a.q_per_group + (out_live ? q0 + kq : 0)) * a.lds + wave_key0 + col;
 
   if (wave_key0 >= a.n) return;  // uniform over the wavefront; no barrier follows
-  // (a wavefront with any keys at all works through all of its tiles)
 #pragma unroll
   for (int r = 0; r < ROUNDS; ++r) {
+    if (TILES == 4 && wave_key0 + r * (RT * 16) >= a.n) break;  // uniform (with more tiles a test costs 2 - 3 % of a long list)
     const Round& c = codes[r & 1];
     if (r + 1 < ROUNDS) load_round(r + 1, codes[(r + 1) & 1]);
     __builtin_amdgcn_sched_barrier(0);
@@ -227,8 +227,8 @@ static hipError_t launch_split_one(const ScoreI8Args& a, const SplitArgs& sp, in
 template <int BITS, bool PROD, bool FUSED>
 static hipError_t launch_split_tiles(const ScoreI8Args& a, const SplitArgs& sp, int n_groups, hipStream_t s) {
   const int64_t others = (int64_t)n_groups * ((a.q_per_group + 3) / 4), cus = device_cu_count();
-  if (((a.n + 1023) / 1024) * others <= cus / 2) return launch_split_one<BITS, PROD, FUSED, 4>(a, sp, n_groups, s);
-  if (((a.n + 2047) / 2048) * others <= cus / 2) return launch_split_one<BITS, PROD, FUSED, 8>(a, sp, n_groups, s);
+  if (a.n <= 512 || ((a.n + 1023) / 1024) * others <= cus / 2) return launch_split_one<BITS, PROD, FUSED, 4>(a, sp, n_groups, s);
+  if (a.n <= 1024 || ((a.n + 2047) / 2048) * others <= cus / 2) return launch_split_one<BITS, PROD, FUSED, 8>(a, sp, n_groups, s);
   return launch_split_one<BITS, PROD, FUSED, 16>(a, sp, n_groups, s);
 }
 

@@ -236,6 +236,60 @@ def test_score_split(d_hi, bits_lo, prod, n_groups, qpg, npg, topk, own_prep):
         assert np.array_equal(ti.cpu().numpy(), o.topk(got, topk))
 
 
+@pytest.mark.parametrize("d_hi,bits_lo,prod", [(32, 3, False), (96, 0, True), (64, 2, True)])
+@pytest.mark.parametrize("n", [1, 16, 48, 512, 513, 1024, 1025, 2049])
+def test_score_split_of_short_caches_of_many_groups(d_hi, bits_lo, prod, n):
+    """Every group's scores are those of a call with this group alone, bit for bit."""
+    groups, nq = 33, 9
+    p = instances(d_hi, bits_lo, prod)[3]
+    x = torch.randn(groups * n, D, device=DEV, generator=torch.Generator(device=DEV).manual_seed(n))
+    q = torch.randn(groups * nq, D, device=DEV, generator=torch.Generator(device=DEV).manual_seed(1))
+    idx, qjl = torch.zeros((groups * n, p.idx_words), dtype=torch.int32, device=DEV), torch.zeros((groups * n, 4), dtype=torch.int32, device=DEV)
+    gamma, norm = torch.zeros((groups * n, 2), device=DEV), torch.zeros((groups * n, 2), device=DEV)
+    if prod:
+        tq.tq_quantize_prod(p, x, idx, qjl, gamma, norm)
+    else:
+        tq.tq_quantize_mse(p, x, idx, norm)
+    out, one = torch.full((groups * nq, n + 3), -7.0, device=DEV), torch.zeros((nq, n), device=DEV)
+    p.reserve_score(groups, nq, n, prod, True, 0)
+    tq.tq_score(p, q, groups, nq, idx, qjl if prod else None, gamma if prod else None, norm, n, out[:, :n])
+    assert (out[:, n:] == -7.0).all()
+    for g in (0, 1, 17, 32):
+        k = slice(g * n, (g + 1) * n)
+        tq.tq_score(p, q[g * nq:(g + 1) * nq], 1, nq, idx[k], qjl[k] if prod else None, gamma[k] if prod else None, norm[k], n, one)
+        assert torch.equal(out[g * nq:(g + 1) * nq, :n], one)
+
+
+def test_one_key_of_many_groups_is_a_short_call():
+    """A wavefront that walks 16 tiles to score one key takes twice as long."""
+    p = instances(32, 3, False)[3]
+    idx, norm = torch.zeros((32, p.idx_words), dtype=torch.int32, device=DEV), torch.ones((32, 2), device=DEV)
+
+    def us(groups, nq):
+        q, out = torch.randn(groups * nq, D, device=DEV), torch.zeros((groups * nq, 4), device=DEV)
+        p.reserve_score(groups, nq, 1, False, True, 0)
+        run = lambda: tq.tq_score(p, q, groups, nq, idx[:groups], None, None, norm[:groups], 1, out[:, :1])  # noqa: E731
+        run()
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            for _ in range(20):
+                run()
+        best = float("inf")
+        for _ in range(6):
+            e = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+            e[0].record()
+            graph.replay()
+            e[1].record()
+            torch.cuda.synchronize()
+            best = min(best, e[0].elapsed_time(e[1]) * 50)
+        return best
+
+    one, many = us(1, 4), us(32, 32)
+    print(f"one block of queries {one:.1f} us, 256 of them {many:.1f} us")
+    assert many <= 1.5 * one
+
+
 def test_split_end_to_end_statistics():
     """quantise + score through the library on isotropic keys: the estimate is unbiased and its
     mean squared error is the sum of the two instances' pi/(2 d_part) * d_part C(f_X, b_mse) *
