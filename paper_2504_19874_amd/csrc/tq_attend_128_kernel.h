@@ -126,9 +126,16 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 // planes, the table cfh and the weights exp(.) * nu_hi, the others VB planes, cf and exp(.) * nu_lo.
 // FINISH: the keys are one chunk, and the workgroup rotates its sums back itself; the joining kernel is a launch of its own, 3.5 us (8 heads, 4
 // queries each, keys of 2 + 1 bits, values of 2, a step with its two appends: 100 tokens 17.9 -> 15.2 us, 512 18.2 -> 15.5).
-template <int KB, bool KPROD, int VB, int VKIND, bool FUSED, int TILES, int WAVES, bool FINISH>
-__global__ __launch_bounds__(64 * WAVES) void attend128_kernel(const ScoreI8Args ka, const AttendArgs a, const AttendCoefs cf,
-                                                        const AttendCoefs cfh) {
+// Short chunks of values of one plane, keys of 3 + 1 or of 4 bits: 132 or 133 registers, so that one workgroup fills a compute unit.  HELD to 128, with 8
+// to 16 of them in scratch, two share it, which pays where there are more workgroups than compute units (us, as they come / held, 64 blocks of four queries over
+// 2884 tokens: keys of 4 bits, values of 1 bit 21.0 / 18.6, of signs alone 22.9 / 21.0; 3 + 1 bits 20.1 / 19.0 and 21.9 / 20.6).  With one workgroup to a compute
+// unit held ones are 1 to 9 % slower.  Keys of 4 + 1 bits take 151: not to be held.
+__host__ __device__ constexpr bool at_may_be_held(int kb, bool kprod, int npl, int tiles, int waves, bool finish, bool fused) {
+  return fused && npl == 1 && tiles < 8 && waves == 8 && !finish && (kprod ? kb == 3 : kb == 4);
+}
+template <int KB, bool KPROD, int VB, int VKIND, bool FUSED, int TILES, int WAVES, bool FINISH, bool HELD>
+__global__ __launch_bounds__(64 * WAVES, HELD ? 4 : 1) void attend128_kernel(
+    const ScoreI8Args ka, const AttendArgs a, const AttendCoefs cf, const AttendCoefs cfh) {
   constexpr bool VPROD = VKIND == 1, VSPLIT = VKIND == 2, TWO = VKIND != 0;  // TWO: a second set of weights
   fetch_arguments<sizeof(ScoreI8Args) + sizeof(AttendArgs) + 2 * sizeof(AttendCoefs)>();
   extern __shared__ __attribute__((aligned(16))) unsigned char dyn_s[];
@@ -581,16 +588,25 @@ __global__ __launch_bounds__(64 * WAVES) void attend128_kernel(const ScoreI8Args
   }
 }
 
-template <int KB, bool KPROD, int VB, int VKIND, bool FUSED, int TILES, int WAVES, bool FINISH>
-hipError_t launch_attend128_tiles(const ScoreI8Args& ka, const AttendArgs& a, const AttendCoefs& cf, const AttendCoefs& cfh,
-                                int n_groups, hipStream_t s) {
+template <int KB, bool KPROD, int VB, int VKIND, bool FUSED, int TILES, int WAVES, bool FINISH, bool HELD>
+hipError_t launch_attend128_grid(const ScoreI8Args& ka, const AttendArgs& a, const AttendCoefs& cf, const AttendCoefs& cfh, const dim3& grid,
+                                 hipStream_t s) {
   constexpr int lds = attend128_lds(KB, VB, VKIND != 0, FUSED, TILES, WAVES);
   static_assert(lds <= 160 * 1024, "LDS budget");
   static LdsLimit lds_limit;  // per instantiation: the limit is raised once per device
-  if (const hipError_t e = raise_lds_limit(lds_limit, reinterpret_cast<const void*>(&attend128_kernel<KB, KPROD, VB, VKIND, FUSED, TILES, WAVES, FINISH>), lds); e != hipSuccess) return e;
-  const dim3 grid(a.nchunks, n_groups, (a.q_per_group + 3) / 4);
-  hipLaunchKernelGGL((attend128_kernel<KB, KPROD, VB, VKIND, FUSED, TILES, WAVES, FINISH>), grid, dim3(64 * WAVES), lds, s, ka, a, cf, cfh);
+  if (const hipError_t e = raise_lds_limit(lds_limit, reinterpret_cast<const void*>(&attend128_kernel<KB, KPROD, VB, VKIND, FUSED, TILES, WAVES, FINISH, HELD>), lds); e != hipSuccess) return e;
+  hipLaunchKernelGGL((attend128_kernel<KB, KPROD, VB, VKIND, FUSED, TILES, WAVES, FINISH, HELD>), grid, dim3(64 * WAVES), lds, s, ka, a, cf, cfh);
   return hipGetLastError();
+}
+
+template <int KB, bool KPROD, int VB, int VKIND, bool FUSED, int TILES, int WAVES, bool FINISH>
+hipError_t launch_attend128_tiles(const ScoreI8Args& ka, const AttendArgs& a, const AttendCoefs& cf, const AttendCoefs& cfh,
+                                int n_groups, hipStream_t s) {
+  const dim3 grid(a.nchunks, n_groups, (a.q_per_group + 3) / 4);
+  if constexpr (at_may_be_held(KB, KPROD, at_planes(VB, VKIND != 0), TILES, WAVES, FINISH, FUSED))
+    if ((int64_t)grid.x * grid.y * grid.z > device_cu_count())
+      return launch_attend128_grid<KB, KPROD, VB, VKIND, FUSED, TILES, WAVES, FINISH, true>(ka, a, cf, cfh, grid, s);
+  return launch_attend128_grid<KB, KPROD, VB, VKIND, FUSED, TILES, WAVES, FINISH, false>(ka, a, cf, cfh, grid, s);
 }
 
 template <int KB, bool KPROD, int VB, int VKIND, bool FUSED>

@@ -122,6 +122,12 @@ def test_attend_over_one_chunk(vb, vprod, qpg, npg, fused):
     run_attend(128, 2, True, vb, vprod, 3, qpg, npg, fused)
 
 
+@pytest.mark.parametrize("kb,kprod,vb,vprod", [(4, False, 1, False), (4, False, 0, True), (3, True, 1, False), (3, True, 0, True)])
+@pytest.mark.parametrize("n_groups,npg", [(128, 600), (129, 600), (65, 1537)])  # two and four chunks: up to 256 workgroups and more
+def test_attend_with_more_workgroups_than_compute_units(kb, kprod, vb, vprod, n_groups, npg):
+    run_attend(128, kb, kprod, vb, vprod, n_groups, 3, npg, True)
+
+
 @pytest.mark.parametrize("vb,vprod,npg", [(2, False, 100), (4, False, 256), (2, True, 37), (3, False, 512)])
 def test_attend_over_one_chunk_into_rows_further_apart(vb, vprod, npg):
     """The workgroup that rotates its own sums back keeps to the output's rows: what lies between them stays, and five queries a group leave
