@@ -113,9 +113,11 @@ struct SelectArgs {
   Codebook cb;
 };
 
-// grid nq, T threads
-template <int BITS, bool PROD, int T>
-__global__ __launch_bounds__(T) void search_select_kernel(const SelectArgs a) {
+// grid nq, T threads.  HELD to the registers of four wavefronts a SIMD, where LDS admits four workgroups of 256 threads to a compute unit: a few registers more
+// make it three (813 queries of 512 over 16000 codes of 4 bits, k = 10: 22.8 us, held 15.7).  Where LDS does not, holding only costs (2048: the whole search
+// 4 to 8 %).
+template <int BITS, bool PROD, int T, bool HELD>
+__global__ __launch_bounds__(T, HELD ? 4 : 1) void search_select_kernel(const SelectArgs a) {
   constexpr int SEGS = (BITS > 0 ? 1 : 0) + (PROD ? 1 : 0);
   constexpr int NB = BITS > 0 ? BITS : 1;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
@@ -345,13 +347,14 @@ int64_t block_queries(int d, int64_t n, int64_t nq, int topk) {
   return std::min(most, ((nq + blocks - 1) / blocks + 127) / 128 * 128);
 }
 
-template <int BITS, bool PROD, int T>
+int select_lds(int segs, int d) { return CAP * 8 + segs * 2 * d * 2; }
+
+template <int BITS, bool PROD, int T, bool HELD>
 hipError_t launch_select_t(const SelectArgs& a, int nq, hipStream_t s) {
-  const int pieces = ((BITS > 0 ? 1 : 0) + (PROD ? 1 : 0)) * 2 * a.d * 2, lds = CAP * 8 + pieces;
   static LdsLimit lds_limit;  // per instantiation: the limit is raised once per device
-  if (const hipError_t e = raise_lds_limit(lds_limit, reinterpret_cast<const void*>(&search_select_kernel<BITS, PROD, T>), 80 * 1024); e != hipSuccess)
+  if (const hipError_t e = raise_lds_limit(lds_limit, reinterpret_cast<const void*>(&search_select_kernel<BITS, PROD, T, HELD>), 80 * 1024); e != hipSuccess)
     return e;
-  hipLaunchKernelGGL((search_select_kernel<BITS, PROD, T>), dim3((unsigned)nq), dim3(T), lds, s, a);
+  hipLaunchKernelGGL((search_select_kernel<BITS, PROD, T, HELD>), dim3((unsigned)nq), dim3(T), select_lds((BITS > 0 ? 1 : 0) + (PROD ? 1 : 0), a.d), s, a);
   return hipGetLastError();
 }
 
@@ -360,7 +363,10 @@ hipError_t launch_select(const SelectArgs& a, int nq, hipStream_t s) {
   // Eight wavefronts per query where a compute unit has no other (us, 4 / 8 / 16 of them: 44 queries of 1536, 1 bit, k = 64, 24 / 15.0 / 14.7;
   // 200 of 768, 4 bits, k = 10, 17.0 / 14.9 / 19.3); long codes, whose decoding they would be in each other's way for, keep four (39 of
   // 3072, 3 + 1 bits, k = 64: 54 / 65 / 66, 48 now).
-  return nq <= device_cu_count() && a.d <= 2048 ? launch_select_t<BITS, PROD, 512>(a, nq, s) : launch_select_t<BITS, PROD, 256>(a, nq, s);
+  if (nq <= device_cu_count() && a.d <= 2048) return launch_select_t<BITS, PROD, 512, false>(a, nq, s);
+  // (a kilobyte and a quarter of LDS beside what is counted here)
+  const bool four = 4 * (select_lds((BITS > 0 ? 1 : 0) + (PROD ? 1 : 0), a.d) + 1280) <= 160 * 1024;
+  return four ? launch_select_t<BITS, PROD, 256, true>(a, nq, s) : launch_select_t<BITS, PROD, 256, false>(a, nq, s);
 }
 
 hipError_t launch_block(const SearchArgs& a, const Codebook& cb, char* base, int32_t* flags, hipStream_t s) {

@@ -129,6 +129,23 @@ def test_search_by_candidates_few_queries(d, bits, prod, nq, n, topk):
     test_search_by_candidates(d, bits, prod, nq, n, topk)
 
 
+# more queries than compute units, on either side of the lengths of which four workgroups that rank find room in a compute unit's LDS
+@pytest.mark.parametrize("d,bits,prod,n,topk", [(1664, 4, False, 8300, 5), (1792, 4, False, 8300, 5), (768, 3, True, 8300, 64), (896, 3, True, 8300, 64),
+                                                (512, 4, False, 16001, 10), (128, 0, True, 20001, 1)])
+def test_search_ranks_more_queries_than_compute_units(d, bits, prod, n, topk):
+    test_search_by_candidates(d, bits, prod, 259, n, topk)
+
+
+# workgroups of 32 queries up to five, four, three and two to a compute unit, as codes are long, and of more queries beyond
+@pytest.mark.parametrize("d,bits,prod,nq,n,topk", [
+    (128, 3, False, 128, 40960, 10), (128, 3, False, 128, 40961, 10), (512, 2, True, 65, 54529, 3), (1024, 1, True, 97, 32768, 5), (1024, 1, True, 97, 32769, 5),
+    (1152, 4, False, 96, 32768, 1), (1152, 3, False, 96, 32897, 1), (1536, 4, False, 64, 32768, 10), (1536, 4, False, 64, 32769, 10), (1152, 2, True, 33, 32900, 64),
+    (2048, 4, False, 129, 13056, 2), (2048, 4, False, 129, 13185, 2),
+])
+def test_search_blocks_of_32_queries(d, bits, prod, nq, n, topk):
+    test_search_by_candidates(d, bits, prod, nq, n, topk)
+
+
 def search_flags(p, q, c, d, prod, nq, n, topk):
     """Which queries of a search without a score buffer overflowed their lists, from the words that say so in the workspace: behind the rotated queries
     and the score matrix (topk > 16) that such queries need, where matrix-vector products rotate them."""
