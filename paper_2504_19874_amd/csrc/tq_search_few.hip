@@ -343,6 +343,13 @@ hipError_t launch_tile(SearchGemmArgs a, hipStream_t s) {
 
 template <bool FIND, int BITS, bool PROD>
 hipError_t launch_fits(const SearchGemmArgs& a, hipStream_t s) {
+  // As many queries per workgroup as there are, but 32 of them while the list is so short that the chip is not full with more (of long codes, whose decoding
+  // is then done two to four times, twice over for up to 64 queries and for more than 128, four times between).  The whole search, us, 32 / 64 / 96 / 128
+  // (through LDS): 128 queries of 128, 3 bits, 11000 codes 33.0 / 35.6 / 39.0 / 42.4 (40.5); 96 of 768, 2 + 1 bits, 36000 80.8 / 90.4 / 90.4 (108), 60000
+  // 96.5 / 94.9 / 92.1; 128 of 3072, 1 + 1 bits, 16000 160 / 164 / 179 / 197 (243), 60000 235 / 222 / 260 / 233; 64 of 1536, 4 bits, 8192 69 / 76, 60000 94.0 /
+  // 87.8; 200 of 2048, 4 bits, k = 64, 16000 143, 121 with 128.
+  const int full = a.d < 1024 ? 5 : a.M <= 64 || a.M > 128 ? 2 : BITS >= 3 && !PROD ? 3 : 4;
+  if ((a.n + 127) / 128 * ((a.M + 31) / 32) <= full * (int64_t)device_cu_count()) return launch_tile<FIND, BITS, PROD, 1>(a, s);
   if (a.M > 96) return launch_tile<FIND, BITS, PROD, 4>(a, s);
   if (a.M > 64) return launch_tile<FIND, BITS, PROD, 3>(a, s);
   if (a.M > 32) return launch_tile<FIND, BITS, PROD, 2>(a, s);
