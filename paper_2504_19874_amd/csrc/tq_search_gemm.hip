@@ -458,11 +458,11 @@ hipError_t launch_tile(SearchGemmArgs a, int per_cu, hipStream_t s) {
 template <bool FIND, int BITS, bool PROD>
 hipError_t launch_fits(const SearchGemmArgs& a, hipStream_t s) {
   const int64_t cus = device_cu_count(), cols = (a.n + 255) / 256;
-  // (half of them: a tile of half the queries decodes every code twice as often)
+  // (half of them: a tile of half the queries decodes every code twice as often.  More than 128 queries: fewer go to tq_search_few.hip)
   auto fills = [&](int tm) { return (a.M + tm - 1) / tm * cols * 2 >= cus; };
-  if (a.M > 128 && fills(256)) return launch_tile<FIND, BITS, PROD, 2, 4, 2>(a, 1, s);
-  if (a.M > 64 && fills(128)) return launch_tile<FIND, BITS, PROD, 2, 2, 4>(a, 1, s);
-  if (a.M > 32 && fills(64)) return launch_tile<FIND, BITS, PROD, 1, 2, 4>(a, 1, s);
+  if (fills(256)) return launch_tile<FIND, BITS, PROD, 2, 4, 2>(a, 1, s);
+  if (fills(128)) return launch_tile<FIND, BITS, PROD, 2, 2, 4>(a, 1, s);
+  if (fills(64)) return launch_tile<FIND, BITS, PROD, 1, 2, 4>(a, 1, s);
   return launch_tile<FIND, BITS, PROD, 1, 1, 8>(a, 2, s);
 }
 template <int BITS, bool PROD>
