@@ -23,8 +23,8 @@
 // wavefront's own with long ranges; with short ones the sums are shared out by coordinate group (at_grouped), and of eight wavefronts four
 // transpose (8 heads of 1024 tokens: 17.9 -> 17.2 us a step).
 //
-// 8 heads, 4 queries each, keys of 2 + 1 bits, values of 2, a step with its two appends: 65536 keys 29.0 -> 27.4 us, 1024 19.1 ->
-// 18.1; keys and values of 4 bits, 53970 keys 61 -> 41.  Before: four base-256 digits on the integer instructions, whose byte operands
+// 8 heads, 4 queries each, keys of 2 + 1 bits, values of 2, a step with its two appends: 65536 keys 29.0 -> 27.1 us, 1024 19.1 ->
+// 17.3; keys and values of 4 bits, 53970 keys 61 -> 41.  Before: four base-256 digits on the integer instructions, whose byte operands
 // came through a table of 64 KB in LDS, passes of 128 keys with two barriers each, and every lane fetching its own code words.  What
 // bounds the 17 us after the launch: key codes until 10 (see the scoring body), then vector instructions (transposition, weights) and 2 us of matrix
 // instructions, which with an fp8 operand take 64 cycles.

@@ -1,4 +1,4 @@
-// Packed codes into fp16 operands of the matrix cores (tq_code_gemm.hip, tq_search_gemm.hip).
+// Packed codes into fp16 operands of the matrix cores (tq_code_gemm.hip, tq_search.hip, tq_search_gemm.hip, tq_search_few.hip).
 #pragma once
 #include "tq_code_gemm.h"
 

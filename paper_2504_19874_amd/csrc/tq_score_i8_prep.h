@@ -1,5 +1,5 @@
 // In-kernel query preparation shared by the single-kernel d = 128 scoring kernels
-// (tq_score_i8_128.hip, tq_score_i8_split.hip): a workgroup of 8 wavefronts rotates / sketches
+// (tq_score_i8_128.hip, tq_score_i8_split.hip): a workgroup of 8 (the read-out's: or 4) wavefronts rotates / sketches
 // its own four queries from the transposed matrices and writes their digits.
 //
 //   load      wavefront w requests its thread's column of matrix w / 4 (0: Pi^T, 1: S^T), half

@@ -223,7 +223,8 @@ static hipError_t launch_split_one(const ScoreI8Args& a, const SplitArgs& sp, in
 }
 
 // Keys per workgroup as in tq_score_i8_128.hip: 2048, fewer while that leaves compute units without one (1024 of more keys than the chip takes at
-// once: 8 x 61687, 8 queries each, 19.3 -> 23.5 us)
+// once: 8 x 61687, 8 queries each, 19.3 -> 23.5 us).  But no more than the tiles of 8 wavefronts that a short cache fills, however many groups there are:
+// 3 bits, 32 groups of 32 queries, us, 16 tiles to a wavefront / as few as hold the keys: one key 12.0 / 5.5, 512 keys 12.8 / 7.6, 1024 13.6 / 10.7.
 template <int BITS, bool PROD, bool FUSED>
 static hipError_t launch_split_tiles(const ScoreI8Args& a, const SplitArgs& sp, int n_groups, hipStream_t s) {
   const int64_t others = (int64_t)n_groups * ((a.q_per_group + 3) / 4), cus = device_cu_count();

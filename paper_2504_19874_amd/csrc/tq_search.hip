@@ -14,7 +14,7 @@
 // A list that overflows (thousands of equal scores) flags its query: the caller runs the kernels that look at everything,
 // which skip blocks of queries without a flag.
 //
-// 1000 queries, 10^6 codes, k = 10, d = 1536, 4 bits: 3.2 ms, 9.5 with every score from the exact kernel; 3.07 of it are
+// 1000 queries, 10^6 codes, k = 10, d = 1536, 4 bits: 3.1 ms, 9.5 with every score from the exact kernel; 2.93 of it are
 // the find kernel's.  500 queries, 30000 codes, k = 64, d = 512: 119 us (284 with 4096 codes in the sample: the gathering
 // overflowed).
 #include <algorithm>
@@ -303,8 +303,8 @@ size_t align256(size_t v) { return (v + 255) / 256 * 256; }
 
 // codes of the sample: of n codes about k n / m reach the k-th best of m sampled ones.  The lists are sized for four times
 // the thousand that this aims at (the number is a sum of k exponentials: for k >= 8 more than four times its mean does not
-// happen; below, the sample is that for k = 8).  And a tile of the find kernel gathers 512 of its 65536 scores: half of
-// that is what 250 k codes in the sample lead to.
+// happen; below, the sample is that for k = 8).  And a tile of 256 x 256 (tq_search_gemm.hip) gathers 512 of its 65536 scores:
+// half of that is what 250 k codes in the sample lead to; a workgroup of tq_search_few.hip gathers 256 of 4096 to 16384.
 int64_t sample_codes(int64_t n, int topk) {
   const int64_t k = topk < 8 ? 8 : topk;
   int64_t m = n * k / (CAP / 4);
