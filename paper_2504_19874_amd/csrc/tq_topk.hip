@@ -10,8 +10,8 @@
 // reach it.  A few long rows (one query against a million codes) are cut into chunks, one workgroup each, whose lists topk_merge_kernel
 // joins in the same way.
 // What such a launch costs is a chain of latencies: us, before (256 threads with 32 scores each, maxima ranked against each other,
-// what passes fetched again from memory) and now: 3 rows of 12279, k = 64, 17.3 -> 5.8; 4 of 12969, k = 10, 6.5 -> 4.7; 45 of 16000,
-// k = 64, 29.2 -> 6.1; 5 of 30000, k = 16, 13.4 -> 7.0; 4 of 10^6, k = 10, with the joining 9.9 -> 9.2; 14 of 84645, k = 64, 22.2 -> 11.2.
+// what passes fetched again from memory) and now: 3 rows of 12279, k = 64, 18.1 -> 6.0; 4 of 12969, k = 10, 6.8 -> 4.9; 45 of 16000,
+// k = 64, 27.9 -> 6.2; 5 of 30000, k = 16, 13.2 -> 6.8; 4 of 10^6, k = 10, with the joining 9.9 -> 8.9; 14 of 84645, k = 64, 20.4 -> 10.8.
 #include "tq_select.h"
 
 #include <algorithm>
