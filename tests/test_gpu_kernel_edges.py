@@ -109,7 +109,7 @@ def test_quantiser_tiles(d, bits, n, kind):
 @pytest.mark.parametrize("d,bits,prod,nq,n,topk", [
     (128, 4, False, 17, 8191, 10), (128, 4, False, 17, 8192, 10), (128, 3, True, 33, 8193, 1), (256, 2, False, 65, 20000, 16),
     (384, 0, True, 129, 9001, 5), (512, 1, True, 257, 30001, 64), (640, 3, False, 130, 40000, 64), (1536, 4, False, 64, 12000, 2),
-    (4096, 1, True, 20, 8200, 3),
+    (4096, 1, True, 20, 8200, 3), (128, 1, False, 32, 70001, 10),
 ])
 def test_search_by_candidates(d, bits, prod, nq, n, topk):
     """Top-k alone, by candidates and their exact scores: the same indices and bits as from the score matrix."""
